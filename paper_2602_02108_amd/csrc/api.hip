@@ -79,7 +79,7 @@ size_t qp_workspace_bytes(Params p, int32_t stride, bool bf, bool bwd) {
   const int32_t cap = qp_union_cap(p, stride);
   if (!force_generic() && mfma_supported(p, bf))
     return maps + (bwd ? bwd_mfma_workspace_bytes(p, cap) : fwd_mfma_workspace_bytes(p, cap));
-  return maps + (bwd ? up256((size_t)p.Hq * p.C * sizeof(float)) : 256);
+  return maps + (bwd ? bwd_generic_workspace_bytes(p, bf, cap) : fwd_generic_workspace_bytes(p, bf, cap));
 }
 
 oomb_status check_qp_list(const Params& p, const int32_t* sel, const int32_t* cnt, int32_t stride) {
@@ -102,16 +102,18 @@ size_t oomb_workspace_bytes(const oomb_attn_desc* desc, int32_t top_k, int32_t o
     case OOMB_OP_ATTN_FWD: {
       int64_t max_len = p.n;
       if (top_k >= 0 && (int64_t)top_k + p.m < max_len) max_len = (int64_t)top_k + p.m;
-      const size_t mfma = mfma_supported(p, desc->dtype == OOMB_BF16) ? fwd_mfma_workspace_bytes(p, (int32_t)max_len) : 0;
-      return mfma > 256 ? mfma : 256;
+      const bool bf = desc->dtype == OOMB_BF16;
+      const size_t need = !force_generic() && mfma_supported(p, bf) ? fwd_mfma_workspace_bytes(p, (int32_t)max_len)
+                                                                    : fwd_generic_workspace_bytes(p, bf, (int32_t)max_len);
+      return need > 256 ? need : 256;
     }
     case OOMB_OP_ATTN_BWD: {
       // longest selection list the call may be given: top_k retrieved pages + the m local pages
       int64_t max_len = p.n;
       if (top_k >= 0 && (int64_t)top_k + p.m < max_len) max_len = (int64_t)top_k + p.m;
-      const size_t generic = up256((size_t)p.Hq * p.C * sizeof(float));
-      const size_t mfma = mfma_supported(p, desc->dtype == OOMB_BF16) ? bwd_mfma_workspace_bytes(p, (int32_t)max_len) : 0;
-      return generic > mfma ? generic : mfma;
+      const bool bf = desc->dtype == OOMB_BF16;
+      return !force_generic() && mfma_supported(p, bf) ? bwd_mfma_workspace_bytes(p, (int32_t)max_len)
+                                                       : bwd_generic_workspace_bytes(p, bf, (int32_t)max_len);
     }
     case OOMB_OP_VOTE_TOPK:
       if (top_k < 0) return 0;
@@ -245,7 +247,7 @@ oomb_status oomb_paged_attn_fwd(const oomb_attn_desc* desc, const void* q, const
       return OOMB_ERR_WORKSPACE;
     e = launch_fwd_mfma(p, max_len, workspace, (hipStream_t)hip_stream);
   } else {
-    e = launch_fwd_generic(p, bf, (hipStream_t)hip_stream);
+    e = launch_fwd_generic(p, bf, max_len, workspace, aligned16(workspace) ? workspace_bytes : 0, (hipStream_t)hip_stream);
   }
   return e == hipSuccess ? OOMB_OK : OOMB_ERR_LAUNCH;
 }
@@ -269,23 +271,18 @@ oomb_status oomb_paged_attn_bwd(const oomb_attn_desc* desc, const void* q, const
   if (s != OOMB_OK) return s;
   const bool bf = desc->dtype == OOMB_BF16;
   const bool use_mfma = !force_generic() && mfma_supported(p, bf);
-  // the shape-generic dK/dV kernel walks the list entries in a grid dimension of at most 65535
-  if (!use_mfma && (max_len > 65535 || p.Hkv > 65535)) return OOMB_ERR_UNSUPPORTED;
-  const size_t need = use_mfma ? bwd_mfma_workspace_bytes(p, max_len) : up256((size_t)p.Hq * p.C * sizeof(float));
+  const size_t need = use_mfma ? bwd_mfma_workspace_bytes(p, max_len) : bwd_generic_workspace_bytes(p, bf, max_len);
   if (!workspace || workspace_bytes < need || !aligned16(workspace)) return OOMB_ERR_WORKSPACE;
   p.q = q; p.k_pool = k_pool; p.v_pool = v_pool; p.page_table = page_table;
   p.sel = sel_pages; p.sel_count = sel_count; p.sel_stride = sel_stride;
   p.o = const_cast<void*>(o); p.lse = const_cast<float*>(lse); p.d_o = d_o; p.d_q = d_q;
   p.dk_pool = dk_pool; p.dv_pool = dv_pool;
-  p.delta = (float*)workspace;
   hipStream_t st = (hipStream_t)hip_stream;
   hipError_t e;
   if (use_mfma) {
     e = launch_bwd_mfma(p, max_len, workspace, st);
   } else {
-    e = launch_delta(p, bf, st);
-    if (e != hipSuccess) return OOMB_ERR_LAUNCH;
-    e = launch_bwd_generic(p, bf, max_len, st);
+    e = launch_bwd_generic(p, bf, max_len, workspace, st);
   }
   return e == hipSuccess ? OOMB_OK : OOMB_ERR_LAUNCH;
 }
@@ -334,7 +331,8 @@ oomb_status oomb_paged_attn_fwd_qp(const oomb_attn_desc* desc, const void* q, co
     if (e != hipSuccess) return OOMB_ERR_LAUNCH;
     e = launch_fwd_mfma(p, qp_union_cap(p, sel_stride), (unsigned char*)workspace + qp_maps_bytes(p, sel_stride), st);
   } else {
-    e = launch_fwd_generic(p, bf, st);
+    const size_t maps = qp_maps_bytes(p, sel_stride);
+    e = launch_fwd_generic(p, bf, qp_union_cap(p, sel_stride), (unsigned char*)workspace + maps, workspace_bytes - maps, st);
   }
   return e == hipSuccess ? OOMB_OK : OOMB_ERR_LAUNCH;
 }
@@ -357,9 +355,8 @@ oomb_status oomb_paged_attn_bwd_qp(const oomb_attn_desc* desc, const void* q, co
   if (s != OOMB_OK) return s;
   const bool bf = desc->dtype == OOMB_BF16;
   const bool use_mfma = !force_generic() && mfma_supported(p, bf);
-  // grid dimensions of at most 65535: list entries of the shape-generic dK/dV kernel, cut pages of the slice reduction
-  if (p.Hkv > 65535 || (!use_mfma && qp_union_cap(p, sel_stride) > 65535) ||
-      (use_mfma && qp_max_multi(p, sel_stride) > 65535))
+  // (the cut pages of the slice reduction are a grid dimension of at most 65535)
+  if (p.Hkv > 65535 || (use_mfma && qp_max_multi(p, sel_stride) > 65535))
     return OOMB_ERR_UNSUPPORTED;
   if (!workspace || workspace_bytes < qp_workspace_bytes(p, sel_stride, bf, true) || !aligned16(workspace))
     return OOMB_ERR_WORKSPACE;
@@ -375,10 +372,7 @@ oomb_status oomb_paged_attn_bwd_qp(const oomb_attn_desc* desc, const void* q, co
   if (use_mfma) {
     e = launch_bwd_mfma(p, cap, rest, st);
   } else {
-    p.delta = (float*)rest;
-    e = launch_delta(p, bf, st);
-    if (e != hipSuccess) return OOMB_ERR_LAUNCH;
-    e = launch_bwd_generic(p, bf, cap, st);
+    e = launch_bwd_generic(p, bf, cap, rest, st);
   }
   return e == hipSuccess ? OOMB_OK : OOMB_ERR_LAUNCH;
 }

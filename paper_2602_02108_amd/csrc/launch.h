@@ -34,10 +34,12 @@ int32_t qp_max_pslots(const Params& p, int32_t stride);
 int32_t qp_max_multi(const Params& p, int32_t stride);
 hipError_t launch_qp_prepare(Params& p, void* ws, hipStream_t st);
 
-// attn_generic.hip: fp32 tensors and shapes without a matrix-core kernel
-hipError_t launch_delta(const Params& p, bool is_bf16, hipStream_t st);
-hipError_t launch_fwd_generic(const Params& p, bool is_bf16, hipStream_t st);
-hipError_t launch_bwd_generic(const Params& p, bool is_bf16, int32_t max_list_len, hipStream_t st);
+// attn_generic.hip: fp32 tensors, head dim 64, pages of fewer than 128 tokens.  max_len: host-side bound of the
+// list length (of the union with one list per query page)
+size_t fwd_generic_workspace_bytes(const Params& p, bool is_bf16, int32_t max_len);
+hipError_t launch_fwd_generic(const Params& p, bool is_bf16, int32_t max_len, void* ws, size_t ws_bytes, hipStream_t st);
+size_t bwd_generic_workspace_bytes(const Params& p, bool is_bf16, int32_t max_len);
+hipError_t launch_bwd_generic(const Params& p, bool is_bf16, int32_t max_len, void* ws, hipStream_t st);
 
 // kv_layout.hip: LDS-ordered images of the selected pages
 size_t kv_image_bytes(const Params& p, int32_t max_len);

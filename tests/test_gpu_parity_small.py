@@ -46,6 +46,26 @@ def test_generic_kernels(w):
     _show(w.name, rep)
 
 
+# Edges of the shape-generic kernels: tiles of 128 rows (token * G + head) and of 32 / 64 streamed tokens, list
+# tokens that fill neither, split and unsplit rows and keys, the diagonal across 16-token pages.
+GENERIC_EDGES = [
+    Workload("bf16_d64_p16_g7", 14, 2, 64, 16, 48, 16 * 37, 5, "bf16", "f32", 0.125, extra_phys=3, boost_frac=0.2, seed=61),
+    Workload("bf16_d64_p128_one_page", 3, 1, 64, 128, 128, 128, 2, "bf16", "bf16", 0.125, seed=62),
+    Workload("bf16_p32_dense", 5, 1, 128, 32, 160, 32 * 23, None, "bf16", "f32", 0.088, extra_phys=1, seed=63),
+    Workload("f32_d64_p128", 4, 4, 64, 128, 256, 128 * 9, 3, "f32", "f32", 0.125, seed=64),
+    Workload("f32_p16_keys_unsplit", 8, 4, 128, 16, 32, 16 * 1100, None, "f32", "bf16", 0.088, seed=65),
+    Workload("f32_p64_rows_unsplit", 32, 32, 64, 64, 1152, 64 * 20, 1, "f32", "f32", 0.125, seed=66),
+    Workload("bf16_d64_rows_unsplit", 32, 32, 64, 32, 1152, 32 * 41, 3, "bf16", "f32", 0.125, seed=67),
+]
+
+
+@pytest.mark.parametrize("w", GENERIC_EDGES, ids=lambda w: w.name)
+def test_generic_kernel_edges(w):
+    with pu.kernels_ran(("attn_fwd_generic", "attn_bwd_generic"), absent=pu.MFMA_KERNELS):
+        rep = pu.full_parity(w, init_grad=0.25)
+    _show(w.name, rep)
+
+
 def test_strided_views_are_honoured():
     """Q / O / dO / dQ as slices of a wider buffer and pools with padded rows."""
     w = WORKLOADS["tiny_sparse"]

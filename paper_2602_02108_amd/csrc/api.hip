@@ -247,7 +247,8 @@ oomb_status oomb_paged_attn_fwd(const oomb_attn_desc* desc, const void* q, const
       return OOMB_ERR_WORKSPACE;
     e = launch_fwd_mfma(p, max_len, workspace, (hipStream_t)hip_stream);
   } else {
-    e = launch_fwd_generic(p, bf, max_len, workspace, aligned16(workspace) ? workspace_bytes : 0, (hipStream_t)hip_stream);
+    e = launch_fwd_generic(p, bf, max_len, workspace, aligned16(workspace) ? workspace_bytes : 0, "attn_fwd_generic",
+                           (hipStream_t)hip_stream);
   }
   return e == hipSuccess ? OOMB_OK : OOMB_ERR_LAUNCH;
 }
@@ -327,12 +328,15 @@ oomb_status oomb_paged_attn_fwd_qp(const oomb_attn_desc* desc, const void* q, co
   hipStream_t st = (hipStream_t)hip_stream;
   hipError_t e;
   if (!force_generic() && mfma_supported(p, bf)) {
-    e = launch_qp_prepare(p, workspace, st);
-    if (e != hipSuccess) return OOMB_ERR_LAUNCH;
+    if (!rows_take_generic(p, qp_union_cap(p, sel_stride), false)) {   // (the split kernels walk the lists themselves)
+      e = launch_qp_prepare(p, workspace, st);
+      if (e != hipSuccess) return OOMB_ERR_LAUNCH;
+    }
     e = launch_fwd_mfma(p, qp_union_cap(p, sel_stride), (unsigned char*)workspace + qp_maps_bytes(p, sel_stride), st);
   } else {
     const size_t maps = qp_maps_bytes(p, sel_stride);
-    e = launch_fwd_generic(p, bf, qp_union_cap(p, sel_stride), (unsigned char*)workspace + maps, workspace_bytes - maps, st);
+    e = launch_fwd_generic(p, bf, qp_union_cap(p, sel_stride), (unsigned char*)workspace + maps, workspace_bytes - maps,
+                           "attn_fwd_generic", st);
   }
   return e == hipSuccess ? OOMB_OK : OOMB_ERR_LAUNCH;
 }

@@ -30,6 +30,7 @@
 // 64 KiB; the loops are unrolled by four stages to make the buffer a constant.
 #include "mfma_common.h"
 #include "launch.h"
+#include "partials.h"
 
 namespace oomb {
 
@@ -51,27 +52,13 @@ __device__ __forceinline__ uint4 kv_pack8(const f32x16& v, int base) {
   return w;
 }
 
-template <typename TG> __device__ __forceinline__ void kv_rmw4(TG* ptr, float a, float b, float c2, float d);
-template <> __device__ __forceinline__ void kv_rmw4<float>(float* ptr, float a, float b, float c2, float d) {
-  float4 v = *reinterpret_cast<float4*>(ptr);
-  v.x += a; v.y += b; v.z += c2; v.w += d;
-  *reinterpret_cast<float4*>(ptr) = v;
-}
-template <> __device__ __forceinline__ void kv_rmw4<bf16_t>(bf16_t* ptr, float a, float b, float c2, float d) {
-  const uint2 v = *reinterpret_cast<uint2*>(ptr);
-  uint2 w;
-  w.x = pack2_bf16(__uint_as_float(v.x << 16) + a, __uint_as_float(v.x & 0xffff0000u) + b);
-  w.y = pack2_bf16(__uint_as_float(v.y << 16) + c2, __uint_as_float(v.y & 0xffff0000u) + d);
-  *reinterpret_cast<uint2*>(ptr) = w;
-}
-
 // Row space of a KV head: block b = tb * G + hd holds the 32 consecutive chunk tokens
 // 32 tb .. 32 tb + 31 of query head g G + hd, so a 32-row MFMA block is one head and
 // consecutive tokens (affine addresses, one causal offset per block).  The per-row
 // statistics are laid out the same way: index 32 b + token-in-block.
 //
-// partial != nullptr: the unit's dK^T / dV^T go to partial[unit][2][128 keys][128 dims]
-// (fp32, overwritten) instead of the pool; a second kernel adds the slices to the pool.
+// partial != nullptr: the unit's dK^T / dV^T go to the fp32 slots of partials.h instead of the pool; a second
+// kernel adds the slices to the pool.
 template <typename TG>
 __global__ __launch_bounds__(KV_THREADS) void bwd_dkv_kernel(Params p, const float* __restrict__ bias,
                                                              int32_t n_stages, int32_t max_len, int32_t n_split,
@@ -401,60 +388,18 @@ __global__ __launch_bounds__(KV_THREADS) void bwd_dkv_kernel(Params p, const flo
   const float scale = role == 0 ? 1.f : p.sm_scale;
   // slices of a page go to fp32 partial pages (added to the pool by the reduce kernel), whole pages
   // straight into the pool
-  const int64_t part_idx = p.qp ? (int64_t)pslot : (partial ? ((int64_t)g * max_len + j) * n_split + sp : -1);
+  const int64_t part_idx = p.qp ? (int64_t)pslot : (partial ? ((int64_t)j * n_split + sp) * p.Hkv + g : -1);
   if (part_idx >= 0) {
-    float* dst = partial + (part_idx * 2 + (role == 0 ? 1 : 0)) * (TP * HD) + (int64_t)(32 * kbw + lq) * HD;
-#pragma unroll
-    for (int db = 0; db < 4; ++db)
-#pragma unroll
-      for (int a = 0; a < 4; ++a) {
-        float4 v = {acc[db][4 * a + 0] * scale, acc[db][4 * a + 1] * scale, acc[db][4 * a + 2] * scale,
-                    acc[db][4 * a + 3] * scale};
-        *reinterpret_cast<float4*>(dst + 32 * db + 8 * a + 4 * hh) = v;
-      }
+    part_store<bf16_t, HD>(partial, part_idx * 8 + (role == 0 ? 4 : 0) + kbw, lane, acc, scale);
   } else {
     TG* pool = (TG*)(role == 0 ? p.dv_pool : p.dk_pool) + pool_off + (int64_t)(32 * kbw + lq) * p.pool_tok_stride;
 #pragma unroll
     for (int db = 0; db < 4; ++db)
 #pragma unroll
       for (int a = 0; a < 4; ++a)
-        kv_rmw4<TG>(pool + 32 * db + 8 * a + 4 * hh, acc[db][4 * a + 0] * scale, acc[db][4 * a + 1] * scale,
+        part_add4<TG>(pool + 32 * db + 8 * a + 4 * hh, acc[db][4 * a + 0] * scale, acc[db][4 * a + 1] * scale,
                     acc[db][4 * a + 2] * scale, acc[db][4 * a + 3] * scale);
   }
-}
-
-// pool page += sum over the n_split slices of partial (one thread per 4 dims)
-template <typename TG>
-__global__ __launch_bounds__(256) void bwd_dkv_reduce_kernel(Params p, const float* __restrict__ partial,
-                                                             int32_t max_len, int32_t n_split) {
-  const int g = blockIdx.z;
-  int32_t j = blockIdx.y;
-  int64_t first_part;
-  if (p.qp) {  // only the pages that were cut into several units have partial pages: blockIdx.y walks their list
-    if (j >= p.multi_count[g]) return;
-    j = p.multi_list[(int64_t)g * p.max_multi + j];
-    n_split = p.un_ns[(int64_t)g * p.un_stride + j];
-    first_part = p.un_pbase[(int64_t)g * p.un_stride + j];
-  } else {
-    if (j >= list_len(p, g)) return;
-    first_part = ((int64_t)g * max_len + j) * n_split;
-  }
-  const int which = blockIdx.x >> 4;                       // 0: dK, 1: dV
-  const int e4 = ((blockIdx.x & 15) * 256 + threadIdx.x);  // float4 index inside the 128 x 128 page
-  const int key = e4 >> 5, d4 = (e4 & 31) * 4;
-  const int64_t l = owned_at(p, g, j);
-  const int64_t pool_off = (int64_t)p.page_table[l] * p.pool_page_stride + (int64_t)g * p.pool_head_stride +
-                           (int64_t)key * p.pool_tok_stride + d4;
-  float4 s = {0.f, 0.f, 0.f, 0.f};
-  for (int sp = 0; sp < n_split; ++sp) {
-    // (read once: non-temporal, so that the partial pages do not push anything else out of the caches)
-    typedef float f32x4_t __attribute__((ext_vector_type(4)));
-    const f32x4_t v = __builtin_nontemporal_load(
-        reinterpret_cast<const f32x4_t*>(partial + ((first_part + sp) * 2 + which) * (TP * HD) + key * HD + d4));
-    s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w;
-  }
-  TG* pool = (TG*)(which == 0 ? p.dk_pool : p.dv_pool) + pool_off;
-  kv_rmw4<TG>(pool, s.x, s.y, s.z, s.w);
 }
 
 size_t dkv_partial_bytes(const Params& p, int32_t max_len, int32_t n_split) {
@@ -464,16 +409,21 @@ size_t dkv_partial_bytes(const Params& p, int32_t max_len, int32_t n_split) {
 }
 
 // Slices per page: enough units (about 8 rounds of 256 workgroups) for the tail of the last
-// round to be short, without making the second-stage reduction large.
+// round to be short, without making the second-stage reduction large; more than four slices only where
+// four leave compute units idle, and then not below two stages each.
 int32_t dkv_splits(const Params& p, int32_t max_len) {
   const int64_t units = (int64_t)p.Hkv * max_len;
   if (units <= 0) return 1;
   const int64_t want = (2048 + units - 1) / units;
-  return (int32_t)(want < 1 ? 1 : (want > 4 ? 4 : want));
+  if (want <= 4) return (int32_t)(want < 1 ? 1 : want);
+  const int64_t fill = 256 / units, most = (p.C / 32) * p.G / 4;
+  const int64_t s = fill < most ? fill : most;
+  return (int32_t)(s < 4 ? 4 : s > 16 ? 16 : s);
 }
 
-hipError_t launch_bwd_dkv_mfma(const Params& p, const float* bias, int32_t n_stages, int32_t max_len,
-                               float* partial_ws, hipStream_t st) {
+// dq_split > 1: the last launch also adds the dQ partials
+hipError_t launch_bwd_dkv_mfma(const Params& p, const float* bias, int32_t n_stages, int32_t max_len, float* partial_ws, int32_t dq_split,
+                               const float* dq_part, hipStream_t st) {
   static DeviceOnce lds_once_f32, lds_once_bf16;
   if (hipError_t e = ensure_max_dynamic_lds(lds_once_f32, (const void*)bwd_dkv_kernel<float>, KV_LDS); e != hipSuccess) return e;
   if (hipError_t e = ensure_max_dynamic_lds(lds_once_bf16, (const void*)bwd_dkv_kernel<bf16_t>, KV_LDS); e != hipSuccess) return e;
@@ -495,12 +445,9 @@ hipError_t launch_bwd_dkv_mfma(const Params& p, const float* bias, int32_t n_sta
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  if (p.qp || n_split > 1) {
+  if (p.qp || n_split > 1 || dq_split > 1) {
     ProfScope prof_("bwd_dkv_reduce", st);
-    dim3 grid(32, (unsigned)(p.qp ? p.max_multi : max_len), (unsigned)p.Hkv);
-    if (p.grad_is_bf16) bwd_dkv_reduce_kernel<bf16_t><<<grid, dim3(256), 0, st>>>(p, partial, max_len, n_split);
-    else bwd_dkv_reduce_kernel<float><<<grid, dim3(256), 0, st>>>(p, partial, max_len, n_split);
-    e = hipGetLastError();
+    e = launch_bwd_finish(p, true, dq_split, dq_part, p.qp ? p.max_multi : n_split > 1 ? max_len : 0, n_split, partial, st);
   }
   return e;
 }

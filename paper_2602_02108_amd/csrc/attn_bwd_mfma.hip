@@ -291,10 +291,20 @@ static inline int32_t row_stages(const Params& p) { return (p.C / 32) * p.G / 2;
 static inline size_t bias_bytes(const Params& p) { return (size_t)p.Hkv * (size_t)row_stages(p) * 512; }
 
 size_t bwd_mfma_workspace_bytes(const Params& p, int32_t max_list_len) {
-  return stats_bytes(p) + bias_bytes(p) + dkv_partial_bytes(p, max_list_len, dkv_splits(p, max_list_len));
+  return (rows_take_generic(p, max_list_len, true) ? dq_generic_part_bytes(p, true, max_list_len) : stats_bytes(p)) + bias_bytes(p) + dkv_partial_bytes(p, max_list_len, dkv_splits(p, max_list_len));
 }
 
 hipError_t launch_bwd_mfma(const Params& p, int32_t max_list_len, void* ws, hipStream_t st) {
+  if (rows_take_generic(p, max_list_len, true)) {   // dQ (with the bias words) by the split kernel
+    float* dq_part = (float*)ws;
+    float* bias = (float*)((unsigned char*)ws + dq_generic_part_bytes(p, true, max_list_len));
+    int32_t splits = 1;
+    {
+      ProfScope prof_("bwd_dq_mfma", st);
+      if (hipError_t e = launch_dq_generic_bf16_128(p, max_list_len, dq_part, bias, row_stages(p), &splits, st); e != hipSuccess) return e;
+    }
+    return launch_bwd_dkv_mfma(p, bias, row_stages(p), max_list_len, (float*)((unsigned char*)bias + bias_bytes(p)), splits, dq_part, st);
+  }
   static DeviceOnce lds_once;
   if (hipError_t e = ensure_max_dynamic_lds(lds_once, (const void*)bwd_dq_kernel, DQ_LDS); e != hipSuccess) return e;
   const int64_t rows_pad = rows_padded(p);
@@ -317,7 +327,7 @@ hipError_t launch_bwd_mfma(const Params& p, int32_t max_list_len, void* ws, hipS
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  return launch_bwd_dkv_mfma(p, bias, row_stages(p), max_list_len, (float*)((unsigned char*)bias + bias_bytes(p)), st);
+  return launch_bwd_dkv_mfma(p, bias, row_stages(p), max_list_len, (float*)((unsigned char*)bias + bias_bytes(p)), 1, nullptr, st);
 }
 
 }  // namespace oomb

@@ -28,15 +28,11 @@
 // (59 GFLOP); 8 / 2 heads bf16, chunk 1088, 24 + 17 pages of 64: 18.4 -> 0.13 ms (32 GFLOP).
 #include "mfma_common.h"
 #include "launch.h"
+#include "partials.h"
 
 namespace oomb {
 
-constexpr int GN_WAVES = 4;
-constexpr int GN_THREADS = GN_WAVES * 64;
-constexpr int GN_ROWS = GN_WAVES * 32;  // rows of a tile (forward, dQ) / keys of a unit (dK / dV)
-constexpr int GN_BUF = 32768;           // one LDS buffer: two row tiles of at most 16 KiB
-constexpr int GN_STAT = 2 * GN_BUF;     // dK / dV: {lse2, delta} of the streamed rows, two buffers
-constexpr int GN_LDS = GN_STAT + 2 * 2 * 64 * 4;
+constexpr int GN_ROWS = PART_ROWS;
 
 // Geometry of a row tile: RB bytes per row, NG granules of 16 bytes, granule c of row r at position
 // c ^ swz(r).  The swizzle frees both access patterns of bank conflicts: 16 rows at one granule, and
@@ -46,25 +42,35 @@ template <typename T, int D> struct Gn {
   static constexpr int ES = sizeof(T), RB = D * ES, NG = RB / 16;
   static constexpr int NJ = NG / 2;                // k-steps of the first product (one granule per lane each)
   static constexpr int DB = D / 32;                // accumulator blocks of the second product
-  static constexpr int KT = RB == 512 ? 32 : 64;   // rows of a tile
-  static constexpr int TILE = KT * RB;
   static constexpr int RPI = 1024 / RB;            // rows per copy instruction of a wave
-  static constexpr int NI = TILE / 1024 / GN_WAVES;  // copy instructions per wave and tile
-  static constexpr int RW = NI * RPI;              // rows a wave copies: 8 or 16, so they lie in one page
   static __device__ __forceinline__ constexpr uint32_t swz(uint32_t r) {
     return !BF ? (r & 15) : RB == 256 ? row_tile_f(r) : ((((r >> 1) & 1) << 2) | ((r >> 2) & 3));
   }
 };
+// Two row tiles of KT rows (K and V, or Q and dO) per buffer, copied by four waves; two buffers.
+template <typename T, int D> struct GnTiles {
+  static constexpr int RB = Gn<T, D>::RB;
+  static constexpr int KT = Gn<T, D>::BF ? 64 : 32, U = KT / 32;   // rows of a tile, blocks of 32
+  static constexpr int TILE = KT * RB, BUF = 2 * TILE;
+  static constexpr int NI = TILE / 1024 / 4;       // copy instructions per wave and tile
+  static constexpr int RW = NI * Gn<T, D>::RPI;    // rows a wave copies: 8 or 16, so they lie in one page
+};
+// Forward and dQ: a group of four waves (128 rows) walks its share of the key tiles; with KH = 2 a workgroup
+// holds two such groups on the same rows whose results meet in LDS at the end: two waves per SIMD, and
+// half the partial results of two workgroups.
+template <typename T, int D, int KH> struct GnRow {
+  static constexpr int THREADS = 256 * KH, GROUP = 2 * GnTiles<T, D>::BUF;   // LDS of a group
+  static constexpr int MERGE = GN_ROWS * D * 4 + 4 * 64 * 8;
+  static constexpr int LDS = KH * GROUP > MERGE || KH == 1 ? KH * GROUP : MERGE;
+};
 
 // C += A B over one granule pair: A, B hold 16 bytes per lane (granule 2 j + lane / 32 of the lane's row)
-template <typename T> __device__ __forceinline__ void gn_mma(const uint4& a, const uint4& b, f32x16& c) {
+template <typename T> __device__ __forceinline__ void gn_mma(const u32x4_t& a, const u32x4_t& b, f32x16& c) {
   if constexpr (sizeof(T) == 2) {
-    c = mfma32(as_bf16x8(a), as_bf16x8(b), c);
+    c = mfma32(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c);
   } else {
-    c = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a.x), __uint_as_float(b.x), c, 0, 0, 0);
-    c = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a.y), __uint_as_float(b.y), c, 0, 0, 0);
-    c = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a.z), __uint_as_float(b.z), c, 0, 0, 0);
-    c = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a.w), __uint_as_float(b.w), c, 0, 0, 0);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) c = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a[e]), __uint_as_float(b[e]), c, 0, 0, 0);
   }
 }
 
@@ -75,102 +81,99 @@ template <int N> __device__ __forceinline__ void gn_zero(f32x16 (&v)[N]) {
     for (int x = 0; x < 16; ++x) v[k][x] = 0.f;
 }
 
-// first product: 32 rows of the tile at `base` (LDS byte offset of row 32 u) against the staying fragments
-template <typename T, int D>
-__device__ __forceinline__ f32x16 gn_chain(const unsigned char* smem, uint32_t base, uint32_t lane_row, const uint4 (&st)[Gn<T, D>::NJ]) {
-  f32x16 c;
-#pragma unroll
-  for (int x = 0; x < 16; ++x) c[x] = 0.f;
-#pragma unroll
-  for (int j = 0; j < Gn<T, D>::NJ; ++j)
-    gn_mma<T>(*reinterpret_cast<const uint4*>(smem + (base + (lane_row ^ (uint32_t)(j << 5)))), st[j], c);
-  return c;
-}
-
-__device__ __forceinline__ uint4 gn_pack8(const f32x16& v, int base) {
-  return make_uint4(pack2_bf16(v[base + 0], v[base + 1]), pack2_bf16(v[base + 2], v[base + 3]),
-                    pack2_bf16(v[base + 4], v[base + 5]), pack2_bf16(v[base + 6], v[base + 7]));
-}
-
-// second product: acc += tile^T s, s in accumulator layout (register x = tile row 8 (x / 4) + 4 hh + x % 4).
-// bf16: acc[db] row m is dim 32 db + m.  fp32: acc[e] row m is dim DB m + e (a lane reads DB consecutive dims).
-template <typename T, int D>
-__device__ __forceinline__ void gn_tprod(const unsigned char* smem, uint32_t base, int lane, const f32x16& s, f32x16 (&acc)[Gn<T, D>::DB]) {
+// LDS operand addresses of a lane.  bf16: one register per k-step and per transposing read (the swizzle is an XOR
+// on the lane's granule), so that an operand read is register + immediate; fp32 forms its addresses as it
+// goes (an instruction of its matrix pipe lasts 64 cycles).
+template <typename T, int D> struct GnAddr {
   typedef Gn<T, D> X;
-  if constexpr (X::BF) {
-    const uint32_t L = lane & 15, gq = lane >> 4, row = 4 * (gq >> 1) + (L >> 2);
-    const uint32_t t = row * X::RB + (((2 * (gq & 1) + ((L & 3) >> 1)) ^ X::swz(row)) << 4) + 8 * (L & 1);
+  static constexpr int NP = X::BF ? 2 * X::DB : 16;   // operands of the second product per block of 32 rows
+  uint32_t row[X::BF ? X::NJ : 1], tr[X::BF ? 2 * X::DB : 1];
+  __device__ __forceinline__ void init(int lane, uint32_t base) {   // base: a multiple of 1 KiB
+    const uint32_t lq = lane & 31, hh = lane >> 5;
+    if constexpr (X::BF) {
 #pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      const bf16x8 b = as_bf16x8(gn_pack8(s, 8 * u));
+      for (int j = 0; j < X::NJ; ++j) row[j] = base + ((lq * X::RB + ((hh ^ X::swz(lq)) << 4)) ^ (uint32_t)(j << 5));
+      const uint32_t L = lane & 15, gq = lane >> 4, r = 4 * (gq >> 1) + (L >> 2);
+      const uint32_t t = r * X::RB + (((2 * (gq & 1) + ((L & 3) >> 1)) ^ X::swz(r)) << 4) + 8 * (L & 1);
 #pragma unroll
       for (int db = 0; db < X::DB; ++db) {
-        const uint32_t a0 = base + (t ^ (uint32_t)(db << 6)) + 16 * u * X::RB;
-        const uint32_t a1 = base + (t ^ (uint32_t)(db << 6) ^ 32u) + (16 * u + 8) * X::RB;   // rows + 8: the swizzle changes by 2
-        const u32x2_t lo = __builtin_bit_cast(u32x2_t, __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-            (__attribute__((address_space(3))) s16x4_t*)(smem + a0)));
-        const u32x2_t hi = __builtin_bit_cast(u32x2_t, __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-            (__attribute__((address_space(3))) s16x4_t*)(smem + a1)));
-        acc[db] = mfma32(__builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3)), b, acc[db]);
+        tr[2 * db] = base + (t ^ (uint32_t)(db << 6));
+        tr[2 * db + 1] = base + (t ^ (uint32_t)(db << 6) ^ 32u);   // rows + 8: the swizzle changes by 2
       }
+    } else {
+      const uint32_t gran = D == 128 ? lq : lq >> 1, sub = D == 128 ? 0 : 8 * (lq & 1);
+      row[0] = base + lq * X::RB + ((hh ^ X::swz(lq)) << 4);
+      tr[0] = base + 4 * hh * X::RB + ((gran ^ (4 * hh)) << 4) + sub;
     }
+  }
+  // operand j (k-step) of the first product: the 32 rows at LDS offset `off`
+  __device__ __forceinline__ u32x4_t row_frag(const int j, const uint32_t off) const {
+    const uint32_t at = (X::BF ? row[X::BF ? j : 0] : row[0] ^ (uint32_t)(j << 5)) + off;
+    return *(__attribute__((address_space(3))) const u32x4_t*)at;
+  }
+  // operand v of the second product over the same rows.  bf16: key group v / DB, dim block v % DB.  fp32: row 8 (v / 4) +
+  // 4 hh + v % 4, the lane's DB consecutive dims.
+  __device__ __forceinline__ u32x4_t tr_frag(const int v, const uint32_t off) const {
+    if constexpr (X::BF) {
+      const int u = v / X::DB, db = v % X::DB;
+      const u32x2_t lo = __builtin_bit_cast(u32x2_t, __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+          (__attribute__((address_space(3))) s16x4_t*)(tr[2 * db] + (off + 16 * u * X::RB))));
+      const u32x2_t hi = __builtin_bit_cast(u32x2_t, __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+          (__attribute__((address_space(3))) s16x4_t*)(tr[2 * db + 1] + (off + (16 * u + 8) * X::RB))));
+      return __builtin_shufflevector(lo, hi, 0, 1, 2, 3);
+    } else {
+      const int r = 8 * (v >> 2) + (v & 3);
+      const uint32_t at = (tr[0] ^ (uint32_t)((r & 15) << 4)) + (off + r * X::RB);
+      if constexpr (D == 128) return *(__attribute__((address_space(3))) const u32x4_t*)at;
+      const u32x2_t w = *(__attribute__((address_space(3))) const u32x2_t*)at;
+      return __builtin_shufflevector(w, w, 0, 1, 0, 1);
+    }
+  }
+};
+
+// A block of probabilities (or dS) as the B operand of the second product: bf16 pairs, or the fp32 values themselves
+template <typename T> struct GnP;
+template <> struct GnP<bf16_t> {
+  uint32_t w[8];
+  __device__ __forceinline__ void set2(const int x, float a, float b) { w[x >> 1] = pack2_bf16(a, b); }   // registers x, x + 1
+};
+template <> struct GnP<float> {
+  float w[16];
+  __device__ __forceinline__ void set2(const int x, float a, float b) { w[x] = a; w[x + 1] = b; }
+};
+// operand v (tr_frag) of acc += tile^T P.  bf16: acc[db] row m is dim 32 db + m.  fp32: acc[e] row m is dim DB m + e.
+template <typename T, int D> __device__ __forceinline__ void gn_tr_mma(const int v, const u32x4_t& f, const GnP<T>& p, f32x16 (&acc)[D / 32]) {
+  if constexpr (sizeof(T) == 2) {
+    const int u = v / (D / 32), db = v % (D / 32);
+    const u32x4_t b = {p.w[4 * u], p.w[4 * u + 1], p.w[4 * u + 2], p.w[4 * u + 3]};
+    acc[db] = mfma32(__builtin_bit_cast(bf16x8, f), __builtin_bit_cast(bf16x8, b), acc[db]);
   } else {
-    const uint32_t lq = lane & 31, hh = lane >> 5;
-    const uint32_t gran = D == 128 ? lq : lq >> 1, sub = D == 128 ? 0 : 8 * (lq & 1);
-    const uint32_t t = 4 * hh * X::RB + ((gran ^ (4 * hh)) << 4) + sub;
 #pragma unroll
-    for (int x = 0; x < 16; ++x) {
-      const int r = 8 * (x >> 2) + (x & 3);
-      const unsigned char* at = smem + (base + (t ^ (uint32_t)((r & 15) << 4)) + r * X::RB);
-      if constexpr (D == 128) {
-        const float4 a = *reinterpret_cast<const float4*>(at);
-        acc[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a.x, s[x], acc[0], 0, 0, 0);
-        acc[1] = __builtin_amdgcn_mfma_f32_32x32x2f32(a.y, s[x], acc[1], 0, 0, 0);
-        acc[2] = __builtin_amdgcn_mfma_f32_32x32x2f32(a.z, s[x], acc[2], 0, 0, 0);
-        acc[3] = __builtin_amdgcn_mfma_f32_32x32x2f32(a.w, s[x], acc[3], 0, 0, 0);
-      } else {
-        const float2 a = *reinterpret_cast<const float2*>(at);
-        acc[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a.x, s[x], acc[0], 0, 0, 0);
-        acc[1] = __builtin_amdgcn_mfma_f32_32x32x2f32(a.y, s[x], acc[1], 0, 0, 0);
-      }
-    }
+    for (int e = 0; e < D / 32; ++e) acc[e] = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(f[e]), p.w[v], acc[e], 0, 0, 0);
   }
 }
 
-// the accumulator in groups of four consecutive dims: f(dim, a, b, c, d) for D / 8 groups per lane
-template <typename T, int D, typename F>
-__device__ __forceinline__ void gn_emit(const f32x16 (&acc)[Gn<T, D>::DB], int hh, F&& f) {
-  if constexpr (sizeof(T) == 2) {
+// A straight run of N operand reads and their matrix instructions in batches of four: the next batch is fetched while
+// one computes (left to itself the compiler waits for every operand just before its use).
+// load(i) reads operand i, use(i, operand) multiplies and may add vector work; i is a constant.
+template <int N, typename L, typename M> __device__ __forceinline__ void gn_pipeline(L&& load, M&& use) {
+  static_assert(N % 4 == 0, "whole batches");
+  u32x4_t fr[2][4];
 #pragma unroll
-    for (int db = 0; db < D / 32; ++db)
+  for (int k = 0; k < 4; ++k) fr[0][k] = load(k);
 #pragma unroll
-      for (int a = 0; a < 4; ++a)
-        f(32 * db + 8 * a + 4 * hh, acc[db][4 * a], acc[db][4 * a + 1], acc[db][4 * a + 2], acc[db][4 * a + 3]);
-  } else if constexpr (D == 128) {
+  for (int b = 0; b < N / 4; ++b) {
+    if (b + 1 < N / 4) {
 #pragma unroll
-    for (int x = 0; x < 16; ++x) f(4 * (8 * (x >> 2) + 4 * hh + (x & 3)), acc[0][x], acc[1][x], acc[2][x], acc[3][x]);
-  } else {
+      for (int k = 0; k < 4; ++k) fr[(b + 1) & 1][k] = load(4 * (b + 1) + k);
+      __builtin_amdgcn_sched_barrier(0);
+    }
 #pragma unroll
-    for (int x = 0; x < 16; x += 2)
-      f(2 * (8 * (x >> 2) + 4 * hh + (x & 3)), acc[0][x], acc[1][x], acc[0][x + 1], acc[1][x + 1]);
+    for (int k = 0; k < 4; ++k) {
+      use(4 * b + k, fr[b & 1][k]);
+      __builtin_amdgcn_sched_barrier(0);
+    }
   }
-}
-template <typename T> __device__ __forceinline__ void gn_store4(T* p, float a, float b, float c, float d);
-template <> __device__ __forceinline__ void gn_store4<float>(float* p, float a, float b, float c, float d) {
-  *reinterpret_cast<float4*>(p) = make_float4(a, b, c, d);
-}
-template <> __device__ __forceinline__ void gn_store4<bf16_t>(bf16_t* p, float a, float b, float c, float d) {
-  *reinterpret_cast<uint2*>(p) = make_uint2(pack2_bf16(a, b), pack2_bf16(c, d));
-}
-template <typename T> __device__ __forceinline__ void gn_add4(T* p, float a, float b, float c, float d);
-template <> __device__ __forceinline__ void gn_add4<float>(float* p, float a, float b, float c, float d) {
-  const float4 v = *reinterpret_cast<const float4*>(p);
-  *reinterpret_cast<float4*>(p) = make_float4(v.x + a, v.y + b, v.z + c, v.w + d);
-}
-template <> __device__ __forceinline__ void gn_add4<bf16_t>(bf16_t* p, float a, float b, float c, float d) {
-  const uint2 v = *reinterpret_cast<const uint2*>(p);
-  gn_store4<bf16_t>(p, __uint_as_float(v.x << 16) + a, __uint_as_float(v.x & 0xffff0000u) + b, __uint_as_float(v.y << 16) + c,
-                    __uint_as_float(v.y & 0xffff0000u) + d);
 }
 
 // One copy instruction of a wave: lane l moves 16 bytes from its own address to LDS byte dst + 16 l.
@@ -189,13 +192,14 @@ __host__ __device__ __forceinline__ int32_t gn_tiles(int32_t C, int32_t G, int32
 
 struct GnTile {
   int lid;
+  int64_t block;          // index of the wave's block of 32 rows among all of the call
   int32_t r, i, h;        // this lane's row (clamped to the tile's last), its chunk token and query head
   bool valid, active;     // the lane owns a row; the wave owns at least one
   int32_t T_ent;          // list entries that some row of the tile sees
   int32_t V, V_last;      // list tokens this lane's row / the tile's last row sees
 };
 
-__device__ __forceinline__ GnTile gn_tile(const Params& p, int g, int32_t tile, int wave, int lane, int lp) {
+__device__ __forceinline__ GnTile gn_tile(const Params& p, int g, int32_t tile, int rb, int lane, int lp, int32_t max_len) {
   GnTile t;
   int32_t base, end;
   if (!p.qp) {
@@ -208,10 +212,14 @@ __device__ __forceinline__ GnTile gn_tile(const Params& p, int g, int32_t tile, 
     end = (tau + 1) * rpq;
     t.lid = g * p.m + tau;
   }
+  // the last 64 entries of a list of the expected length, read while its length is on its way
+  int32_t e = max_len - 1 - lane >= 0 ? list_at(p, t.lid, max_len - 1 - lane) : -1;
+  const int32_t len = list_len(p, t.lid);
   const int32_t last = base + GN_ROWS - 1 < end - 1 ? base + GN_ROWS - 1 : end - 1;
-  const int32_t r = base + 32 * wave + (lane & 31);
+  const int32_t r = base + 32 * rb + (lane & 31);
+  t.block = ((int64_t)g * gn_tiles(p.C, p.G, p.P, p.m, p.qp) + tile) * 4 + rb;
   t.valid = r <= last;
-  t.active = base + 32 * wave <= last;
+  t.active = base + 32 * rb <= last;
   t.r = t.valid ? r : last;
   t.i = (int32_t)div_g(p, (uint32_t)t.r);
   t.h = g * p.G + (t.r - t.i * p.G);
@@ -219,53 +227,84 @@ __device__ __forceinline__ GnTile gn_tile(const Params& p, int g, int32_t tile, 
   const int32_t i_last = (int32_t)div_g(p, (uint32_t)last);
   const int64_t a = first_q + t.i, a_last = first_q + i_last;
   const int32_t pg = (int32_t)(a >> lp), pg_lo = (int32_t)((first_q + div_g(p, (uint32_t)base)) >> lp), pg_hi = (int32_t)(a_last >> lp);
-  t.T_ent = visible_len(p, t.lid, pg_hi, lane);
-  // tokens visible up to page v = entries up to v, whole pages, less the unseen tail of v itself.  The rows of
-  // a tile lie in at most nine pages, so the entries past pg_lo are among the last 64.
-  const int32_t e = t.T_ent - 1 - lane >= 0 ? list_at(p, t.lid, t.T_ent - 1 - lane) : -1;
+  // The rows of a tile lie in at most nine pages, so the entries past pg_lo that some row sees are among the last
+  // 64 up to pg_hi.
+  t.T_ent = len;
+  int32_t n_over = __builtin_popcountll(__ballot(e > pg_hi));
+  if (len != max_len || n_over > 48) {   // (shorter list, or a tile far before the list's end)
+    t.T_ent = visible_len(p, t.lid, pg_hi, lane);
+    e = t.T_ent - 1 - lane >= 0 ? list_at(p, t.lid, t.T_ent - 1 - lane) : -1;
+    n_over = 0;
+  }
+  t.T_ent -= n_over;
+  // tokens visible up to page v: entries up to v, whole pages, less the unseen tail of v itself
   t.V = 0;
   t.V_last = 0;
   for (int32_t v = pg_lo; v <= pg_hi; ++v) {
-    const int32_t whole = (t.T_ent - __builtin_popcountll(__ballot(e > v))) << lp;
+    const int32_t whole = (t.T_ent + n_over - __builtin_popcountll(__ballot(e > v))) << lp;
     const bool held = __ballot(e == v) != 0;
     if (pg == v) t.V = whole - (held ? p.P - 1 - (int32_t)(a & (p.P - 1)) : 0);
     if (v == pg_hi) t.V_last = whole - (held ? p.P - 1 - (int32_t)(a_last & (p.P - 1)) : 0);
   }
+  t.T_ent = __builtin_amdgcn_readfirstlane(t.T_ent);
+  t.V_last = __builtin_amdgcn_readfirstlane(t.V_last);
   return t;
 }
 
-// K / V tiles of a list, copied tile by tile in ascending order.  Every wave moves RW rows of K and of V.
+// Splits cut the key tiles of a list of max_len entries, so that where a split starts is known before anything is
+// read; what lies past the list, or past what the tile's rows see, is dropped.
+struct GnRange { int32_t k0, k1; };
+__device__ __forceinline__ GnRange gn_range(int32_t max_len, int lp, int32_t kt, int32_t split, int32_t n_split) {
+  const int64_t n = (((int64_t)max_len << lp) + kt - 1) / kt;
+  return {(int32_t)(n * split / n_split), (int32_t)(n * (split + 1) / n_split)};
+}
+
+// K / V tiles of a list, copied tile by tile in ascending order.  Every wave of a group moves RW rows of K and of V.
 template <typename T, int D> struct GnStream {
   typedef Gn<T, D> X;
-  PageWindow pw;
-  int64_t lane_off;   // this lane's row and granule inside the wave's rows, bytes
-  int64_t step;       // bytes between the rows of consecutive copy instructions
-  int64_t head_off;   // bytes
-  __device__ __forceinline__ void init(const Params& p, const GnTile& t, int g, int lane, int32_t first_tok, int lp) {
-    lane_off = (int64_t)(lane / X::NG) * p.pool_tok_stride * X::ES;
-    step = (int64_t)X::RPI * p.pool_tok_stride * X::ES;
-    head_off = (int64_t)g * p.pool_head_stride * X::ES;
-    pw.slots = false;
-    pw.base = first_tok >> lp;
-    pw.fetch(p, t.lid, t.T_ent, pw.base, lane, pw.l_cur, pw.p_cur);
-    pw.fetch(p, t.lid, t.T_ent, pw.base + 64, lane, pw.l_nxt, pw.p_nxt);
+  typedef GnTiles<T, D> Y;
+  int32_t base, p_cur, p_nxt;   // physical pages of the list entries base .. + 63 and of the next 64, one per lane
+  int32_t last;                 // last entry with a page
+  int64_t lane_off[Y::NI];      // this lane's row and granule, bytes from the wave's first row
+  int64_t head_off;
+  // one window of list entries; len is the host's bound, so entries past the list's own end may hold anything
+  __device__ __forceinline__ int32_t window(const Params& p, int lid, int32_t len, int32_t at, int lane) const {
+    int32_t l = at + lane < len ? list_at(p, lid, at + lane) : 0;
+    l = l >= 0 && l < p.n ? l : 0;
+    return p.page_table[l];
   }
-  __device__ __forceinline__ void copy(const Params& p, const GnTile& t, int wave, int lane, int lp, int32_t tile, uint32_t buf) {
-    const int32_t tok = tile * X::KT + wave * X::RW;
-    int32_t e = tok >> lp;
-    e = e < t.T_ent ? e : t.T_ent - 1;   // (rows past the list's end are masked: any page of the list will do)
-    e = __builtin_amdgcn_readfirstlane(e);
-    pw.advance(p, t.lid, t.T_ent, e, lane);
-    const int64_t o = (int64_t)pw.phys(e) * p.pool_page_stride * X::ES + head_off + (int64_t)(tok & (p.P - 1)) * p.pool_tok_stride * X::ES;
+  __device__ __forceinline__ void init(const Params& p, int lid, int32_t max_len, int g, int rb, int lane, int32_t first_tok, int lp) {
     const uint32_t lrow = lane / X::NG, pos = lane % X::NG;
-    const uint32_t dst = buf + wave * X::RW * X::RB;
 #pragma unroll
-    for (int k = 0; k < X::NI; ++k) {
-      const uint32_t row = (wave * X::RW + k * X::RPI + lrow) & 15;   // (the swizzle sees the row index modulo 16)
-      const int64_t at = o + lane_off + k * step + (int64_t)((pos ^ X::swz(row)) << 4);
-      gn_copy16((const unsigned char*)p.k_pool + at, dst + 1024 * k);
-      gn_copy16((const unsigned char*)p.v_pool + at, dst + X::TILE + 1024 * k);
+    for (int k = 0; k < Y::NI; ++k) {
+      const uint32_t row = k * X::RPI + lrow;
+      lane_off[k] = (int64_t)row * p.pool_tok_stride * X::ES + ((pos ^ X::swz((rb * Y::RW + row) & 15)) << 4);   // (the swizzle sees rows modulo 16)
     }
+    head_off = (int64_t)g * p.pool_head_stride * X::ES;
+    base = __builtin_amdgcn_readfirstlane(first_tok >> lp);
+    p_cur = window(p, lid, max_len, base, lane);
+    p_nxt = window(p, lid, max_len, base + 64, lane);
+  }
+  __device__ __forceinline__ void copy(const Params& p, int lid, int32_t max_len, int rb, int lane, int lp, int32_t tile, uint32_t buf) {
+    const int32_t tok = tile * Y::KT + rb * Y::RW;
+    int32_t e = tok >> lp;
+    e = __builtin_amdgcn_readfirstlane(e < last ? e : last);   // (rows past the last visible page are masked: any page of the list will do)
+    if (e >= base + 64) {
+      base += 64;
+      p_cur = p_nxt;
+      p_nxt = window(p, lid, max_len, base + 64, lane);
+      wait_copies<0>();   // (here, once per 64 entries: a wait left to the compiler would stand in front of every tile)
+    }
+    const int32_t j = e - base;
+    const int32_t ph = __builtin_amdgcn_readlane(j < 64 ? p_cur : p_nxt, j & 63);
+    const int64_t o = ((int64_t)ph * p.pool_page_stride + (int64_t)(tok & (p.P - 1)) * p.pool_tok_stride) * X::ES + head_off;
+    const unsigned char* k_src = (const unsigned char*)p.k_pool + o;
+    const unsigned char* v_src = (const unsigned char*)p.v_pool + o;
+    const uint32_t dst = buf + rb * Y::RW * X::RB;
+#pragma unroll
+    for (int k = 0; k < Y::NI; ++k) gn_copy16(k_src + lane_off[k], dst + 1024 * k);
+#pragma unroll
+    for (int k = 0; k < Y::NI; ++k) gn_copy16(v_src + lane_off[k], dst + Y::TILE + 1024 * k);
   }
 };
 
@@ -277,209 +316,326 @@ __device__ __forceinline__ GnBlock gn_block(const Params& p, int32_t tiles, int3
   return {b - rest * p.Hkv, tiles - 1 - rest / n_split, rest % n_split};   // late rows see more pages: they start first
 }
 
-// ---- forward ----------------------------------------------------------------------------------
-// n_split > 1: O (not normalised) and {running maximum in log2 units, sum} of every row go to
-// part[split][KV head][row][D] and part_ml, which the combine kernel merges.
-template <typename T, int D>
-__global__ __launch_bounds__(GN_THREADS, 2) void fwd_generic_kernel(Params p, int32_t tiles, int32_t n_split, int lp,
-                                                                    float* __restrict__ part, float2* __restrict__ part_ml) {
-  typedef Gn<T, D> X;
-  extern __shared__ __align__(16) unsigned char smem[];
-  const int lane = threadIdx.x & 63, hh = lane >> 5, lq = lane & 31, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const GnBlock b = gn_block(p, tiles, n_split);
-  const GnTile t = gn_tile(p, b.g, b.tile, wave, lane, lp);
-  const int32_t n_kt = (t.V_last + X::KT - 1) / X::KT;
-  const int32_t k0 = (int32_t)((int64_t)n_kt * b.split / n_split), k1 = (int32_t)((int64_t)n_kt * (b.split + 1) / n_split);
+// The key loop of forward and dQ: tiles kr of this wave's group.  compute(LDS offset of the tile inside the group's
+// buffers -- a constant --, first list token)
+template <typename T, int D, int KH, typename F>
+__device__ __forceinline__ void gn_key_loop(const Params& p, const GnTile& t, GnStream<T, D>& ks, GnRange kr, GnRange other, int32_t max_len,
+                                            int group, int rb, int lane, int lp, F&& compute) {
+  typedef GnTiles<T, D> Y;
+  const int32_t n_kt = (t.V_last + Y::KT - 1) / Y::KT;   // (tiles past what the last row sees are dropped)
+  const int32_t k1 = kr.k1 < n_kt ? kr.k1 : n_kt, mine = k1 - kr.k0;
+  const int32_t theirs = (other.k1 < n_kt ? other.k1 : n_kt) - other.k0, steps = KH == 2 && theirs > mine ? theirs : mine;
+  const uint32_t at = group * GnRow<T, D, KH>::GROUP;
+  ks.last = t.T_ent - 1;
+  wait_copies<0>();   // (every load so far, so that no wait for one of them is left inside the loop)
+  if (mine > 0) ks.copy(p, t.lid, max_len, rb, lane, lp, kr.k0, at);
+  for (int32_t i0 = 0; i0 < steps; i0 += 2) {
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {   // (unrolled: the buffer is a constant)
+      const int32_t i = i0 + b;
+      if (i >= steps) break;
+      wait_copies<0>();
+      __syncthreads();   // this tile is in LDS; nobody reads the one before it any more, whose buffer takes the next
+      if (i + 1 < mine) ks.copy(p, t.lid, max_len, rb, lane, lp, kr.k0 + i + 1, at + (b ^ 1) * Y::BUF);
+      if (i < mine) compute((uint32_t)(b * Y::BUF), (kr.k0 + i) * Y::KT);
+    }
+  }
+}
 
-  uint4 qf[X::NJ];
+// ---- forward ----------------------------------------------------------------------------------
+// n_split > 1: O (not normalised) and {running maximum in log2 units, sum} of every row go to part[split][block] and
+// part_ml[split][block][32], which the combine kernel merges.
+template <typename T, int D, int KH>
+__global__ __launch_bounds__(256 * KH, 2) void fwd_generic_kernel(Params p, int32_t tiles, int32_t n_split, int lp, int32_t max_len,
+                                                                  float* __restrict__ part, float2* __restrict__ part_ml) {
+  typedef Gn<T, D> X;
+  typedef GnTiles<T, D> Y;
+  extern __shared__ __align__(16) unsigned char smem[];
+  const int lane = threadIdx.x & 63, hh = lane >> 5, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), rb = wave & 3, group = wave >> 2;
+  const GnBlock b = gn_block(p, tiles, n_split);
+  const GnRange kr = gn_range(max_len, lp, Y::KT, KH * b.split + group, KH * n_split);
+  const GnRange other = gn_range(max_len, lp, Y::KT, KH * b.split + (KH - 1 - group), KH * n_split);
+  const GnTile t = gn_tile(p, b.g, b.tile, rb, lane, lp, max_len);
+  GnStream<T, D> ks;
+  ks.init(p, t.lid, max_len, b.g, rb, lane, kr.k0 * Y::KT, lp);
+
+  u32x4_t qf[X::NJ];
   const int64_t roff = (int64_t)t.i * p.q_tok_stride + (int64_t)t.h * p.q_head_stride;
 #pragma unroll
-  for (int j = 0; j < X::NJ; ++j) qf[j] = *reinterpret_cast<const uint4*>((const unsigned char*)((const T*)p.q + roff) + 32 * j + 16 * hh);
+  for (int j = 0; j < X::NJ; ++j) qf[j] = *reinterpret_cast<const u32x4_t*>((const unsigned char*)((const T*)p.q + roff) + 32 * j + 16 * hh);
 
   f32x16 of[X::DB];
   gn_zero(of);
   float m_run = -1e30f, l_run = 0.f;
   const bf16x2 ones = {(__bf16)1.0f, (__bf16)1.0f};   // (the row sum is that of the rounded probabilities)
   const float c = p.sm_scale * 1.4426950408889634f;
-  const uint32_t lane_row = lq * X::RB + ((hh ^ X::swz(lq)) << 4);
+  GnAddr<T, D> ad;
+  ad.init(lane, group * GnRow<T, D, KH>::GROUP);
   const int32_t V_min = __builtin_amdgcn_readfirstlane(t.V), V_max = __builtin_amdgcn_readlane(t.V, 31);
 
-  GnStream<T, D> ks;
-  if (k0 < k1) {
-    ks.init(p, t, b.g, lane, k0 * X::KT, lp);
-    ks.copy(p, t, wave, lane, lp, k0, 0);
-  }
-  wait_copies<0>();
-  __syncthreads();
-  for (int32_t k = k0; k < k1; ++k) {
-    const uint32_t buf = ((k - k0) & 1) * GN_BUF;
-    if (k + 1 < k1) ks.copy(p, t, wave, lane, lp, k + 1, buf ^ GN_BUF);
+  // One tile: S of its blocks, one softmax step over all of them, then O.  The exponentials of a second block
+  // run between the matrix instructions of the first block's product.
+  gn_key_loop<T, D, KH>(p, t, ks, kr, other, max_len, group, rb, lane, lp, [&](const uint32_t at, const int32_t t0) __attribute__((always_inline)) {
+    if (!t.active || t0 >= V_max) return;   // (wave-uniform)
+    constexpr int NP = GnAddr<T, D>::NP;
+    f32x16 s[Y::U];
+    gn_zero(s);
+    gn_pipeline<Y::U * X::NJ>(
+        [&](const int i) __attribute__((always_inline)) { return ad.row_frag(i % X::NJ, at + 32 * (i / X::NJ) * X::RB); },
+        [&](const int i, const u32x4_t& f) __attribute__((always_inline)) { gn_mma<T>(f, qf[i % X::NJ], s[i / X::NJ]); });
+    if (t0 + Y::KT > V_min) {
+      const int32_t rel = t.V - t0 - 4 * hh;
 #pragma unroll
-    for (int u = 0; u < X::KT / 32; ++u) {
-      const int32_t t0 = k * X::KT + 32 * u;
-      if (t.active && t0 < V_max) {   // (wave-uniform)
-        f32x16 s = gn_chain<T, D>(smem, buf + 32 * u * X::RB, lane_row, qf);
-        if (t0 + 32 > V_min) {
-          const int32_t rel = t.V - t0 - 4 * hh;
+      for (int u = 0; u < Y::U; ++u)
 #pragma unroll
-          for (int x = 0; x < 16; ++x)
-            if (8 * (x >> 2) + (x & 3) >= rel) s[x] = -INFINITY;
-        }
-        float mx = fmaxf(s[0], s[1]);
-#pragma unroll
-        for (int x = 2; x < 16; ++x) mx = fmaxf(mx, s[x]);
-        const float m_new = fmaxf(m_run, half_max(mx));
-        const float alpha = __builtin_amdgcn_exp2f((m_run - m_new) * c), mc = m_new * c;
-        m_run = m_new;
-        float sum = 0.f;
-#pragma unroll
-        for (int x = 0; x < 16; x += 2) {
-          s[x] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[x], c, -mc));
-          s[x + 1] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[x + 1], c, -mc));
-          if constexpr (X::BF) sum = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, pack2_bf16(s[x], s[x + 1])), ones, sum, false);
-          else sum += s[x] + s[x + 1];
-        }
-        l_run = __builtin_fmaf(l_run, alpha, sum);
-        if (__any(alpha != 1.f)) {
-#pragma unroll
-          for (int db = 0; db < X::DB; ++db)
-#pragma unroll
-            for (int x = 0; x < 16; ++x) of[db][x] *= alpha;
-        }
-        gn_tprod<T, D>(smem, buf + X::TILE + 32 * u * X::RB, lane, s, of);
-      }
+        for (int x = 0; x < 16; ++x)
+          if (32 * u + 8 * (x >> 2) + (x & 3) >= rel) s[u][x] = -INFINITY;
     }
-    wait_copies<0>();
-    __syncthreads();
-  }
+    float mx = s[0][0];
+#pragma unroll
+    for (int u = 0; u < Y::U; ++u)
+#pragma unroll
+      for (int x = u == 0; x < 16; ++x) mx = fmaxf(mx, s[u][x]);
+    const float m_new = fmaxf(m_run, half_max(mx));
+    const float alpha = __builtin_amdgcn_exp2f((m_run - m_new) * c), mc = m_new * c;
+    m_run = m_new;
+    if (__any(alpha != 1.f)) {
+      l_run *= alpha;
+#pragma unroll
+      for (int db = 0; db < X::DB; ++db)
+#pragma unroll
+        for (int x = 0; x < 16; ++x) of[db][x] *= alpha;
+    }
+    GnP<T> pr[Y::U];
+    auto exps = [&](const int u, const int x) __attribute__((always_inline)) {   // registers x, x + 1
+      const float a = __builtin_amdgcn_exp2f(__builtin_fmaf(s[u][x], c, -mc)), b2 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[u][x + 1], c, -mc));
+      pr[u].set2(x, a, b2);
+      if constexpr (X::BF) l_run = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, pr[u].w[x >> 1]), ones, l_run, false);
+      else l_run += a + b2;
+    };
+#pragma unroll
+    for (int x = 0; x < 16; x += 2) exps(0, x);
+    gn_pipeline<Y::U * NP>(
+        [&](const int i) __attribute__((always_inline)) { return ad.tr_frag(i % NP, at + Y::TILE + 32 * (i / NP) * X::RB); },
+        [&](const int i, const u32x4_t& f) __attribute__((always_inline)) {
+          gn_tr_mma<T, D>(i % NP, f, pr[i / NP], of);
+          if (i < NP && Y::U == 2) {   // 16 exponentials over NP instructions (4, 8 or 16)
+            if (NP == 4) exps(Y::U - 1, 4 * i);
+            if (NP <= 8) exps(Y::U - 1, NP == 4 ? 4 * i + 2 : 2 * i);
+            if (NP == 16 && !(i & 1)) exps(Y::U - 1, i);
+          }
+        });
+  });
 
-  const float l_tot = half_sum(l_run);
-  if (!t.valid) return;
+  float l_tot = half_sum(l_run);
+  if constexpr (KH == 2) {   // the second group's results through LDS
+    float* mo = reinterpret_cast<float*>(smem) + rb * (D * 32) + lane;
+    float2* ml = reinterpret_cast<float2*>(smem + GN_ROWS * D * 4) + rb * 64 + lane;
+    __syncthreads();
+    if (group == 1) {
+#pragma unroll
+      for (int k = 0; k < X::DB * 16; ++k) mo[64 * k] = of[k >> 4][k & 15];
+      *ml = make_float2(m_run, l_tot);
+    }
+    __syncthreads();
+    if (group == 1) return;
+    const float2 o = *ml;
+    const float M = fmaxf(m_run, o.x), w0 = __builtin_amdgcn_exp2f((m_run - M) * c), w1 = __builtin_amdgcn_exp2f((o.x - M) * c);
+    m_run = M;
+    l_tot = l_tot * w0 + o.y * w1;
+#pragma unroll
+    for (int k = 0; k < X::DB * 16; ++k) of[k >> 4][k & 15] = of[k >> 4][k & 15] * w0 + mo[64 * k] * w1;
+  }
   if (n_split > 1) {
-    const int64_t at = ((int64_t)b.split * p.Hkv + b.g) * ((int64_t)p.C * p.G) + t.r;
-    float* dst = part + at * D;
-    gn_emit<T, D>(of, hh, [&](int d, float v0, float v1, float v2, float v3) { gn_store4<float>(dst + d, v0, v1, v2, v3); });
-    if (hh == 0) part_ml[at] = make_float2(l_tot > 0.f ? m_run * c : -INFINITY, l_tot);
-  } else {
+    const int64_t at = (int64_t)b.split * p.Hkv * tiles * 4 + t.block;
+    if (!t.active) return;
+    part_store<T, D>(part, at, lane, of, 1.f);
+    if (hh == 0) part_ml[at * 32 + lane] = make_float2(l_tot > 0.f ? m_run * c : -INFINITY, l_tot);
+  } else if (t.valid) {
     const float inv = 1.f / l_tot;
     T* dst = (T*)p.o + roff;
-    gn_emit<T, D>(of, hh, [&](int d, float v0, float v1, float v2, float v3) { gn_store4<T>(dst + d, v0 * inv, v1 * inv, v2 * inv, v3 * inv); });
+    part_emit<T, D>(of, hh, [&](int d, float v0, float v1, float v2, float v3) { part_store4<T>(dst + d, v0 * inv, v1 * inv, v2 * inv, v3 * inv); });
     if (hh == 0) p.lse[(int64_t)t.h * p.C + t.i] = (m_run * c + __builtin_amdgcn_logf(l_tot)) * 0.6931471805599453f;
   }
 }
 
-// O = sum of the splits' O rescaled to the common maximum / sum of their l; D / 4 lanes per row
+// A lane of a combine kernel: thread (row tile, block, group of four dims, lane) -> its row and dims
+template <typename T, int D> struct GnOut {
+  int64_t block;
+  int k, lane, d, i, h;
+  bool ok;
+  __device__ __forceinline__ GnOut(const Params& p, int32_t tiles, int64_t idx) {
+    lane = (int)(idx & 63);
+    k = (int)(idx >> 6) % (D / 8);
+    block = (idx >> 6) / (D / 8);
+    d = part_group_dim<T, D>(k, lane >> 5);
+    const int64_t tg = block >> 2;
+    const int32_t g = (int32_t)(tg / tiles), tile = (int32_t)(tg - (int64_t)g * tiles);
+    int32_t r = ((int32_t)block & 3) * 32 + (lane & 31), end;
+    if (!p.qp) {
+      r += tile * GN_ROWS;
+      end = p.C * p.G;
+    } else {
+      const int32_t rpq = p.P * p.G, tpq = (rpq + GN_ROWS - 1) / GN_ROWS, tau = tile / tpq;
+      r += tau * rpq + (tile - tau * tpq) * GN_ROWS;
+      end = (tau + 1) * rpq;
+    }
+    ok = g < p.Hkv && r < end;
+    i = (int)div_g(p, (uint32_t)(ok ? r : 0));
+    h = g * p.G + (r - i * p.G);
+  }
+};
+
+// O = sum of the splits' O rescaled to the common maximum / sum of their l
 template <typename T, int D>
-__global__ __launch_bounds__(256) void fwd_combine_kernel(Params p, int32_t n_split, const float* __restrict__ part,
+__global__ __launch_bounds__(256) void fwd_combine_kernel(Params p, int32_t tiles, int32_t n_split, const float* __restrict__ part,
                                                           const float2* __restrict__ part_ml) {
-  constexpr int LPR = D / 4;
-  const int64_t rows = (int64_t)p.C * p.G, row = (int64_t)blockIdx.x * (256 / LPR) + threadIdx.x / LPR;
-  if (row >= rows * p.Hkv) return;
-  const int d = (threadIdx.x % LPR) * 4;
-  const int g = (int)(row / rows);
-  const int32_t r = (int32_t)(row - g * rows), i = (int32_t)div_g(p, (uint32_t)r), h = g * p.G + (r - i * p.G);
+  const GnOut<T, D> o(p, tiles, (int64_t)blockIdx.x * 256 + threadIdx.x);
+  if (!o.ok) return;
+  const int64_t blocks = (int64_t)p.Hkv * tiles * 4;
   float M = -INFINITY;
-  for (int s = 0; s < n_split; ++s) M = fmaxf(M, part_ml[s * rows * p.Hkv + row].x);
+  for (int s = 0; s < n_split; ++s) M = fmaxf(M, part_ml[(s * blocks + o.block) * 32 + (o.lane & 31)].x);
   float L = 0.f;
   float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
   for (int s = 0; s < n_split; ++s) {
-    const float2 ml = part_ml[s * rows * p.Hkv + row];
+    const float2 ml = part_ml[(s * blocks + o.block) * 32 + (o.lane & 31)];
     const float w = __builtin_amdgcn_exp2f(ml.x - M);
-    const float4 v = *reinterpret_cast<const float4*>(part + (s * rows * p.Hkv + row) * D + d);
+    const float4 v = reinterpret_cast<const float4*>(part)[((s * blocks + o.block) * (D / 8) + o.k) * 64 + o.lane];
     L += ml.y * w;
     acc.x += v.x * w; acc.y += v.y * w; acc.z += v.z * w; acc.w += v.w * w;
   }
   const float inv = 1.f / L;
-  gn_store4<T>((T*)p.o + (int64_t)i * p.q_tok_stride + (int64_t)h * p.q_head_stride + d, acc.x * inv, acc.y * inv, acc.z * inv, acc.w * inv);
-  if (d == 0) p.lse[(int64_t)h * p.C + i] = (M + __builtin_amdgcn_logf(L)) * 0.6931471805599453f;
+  part_store4<T>((T*)p.o + (int64_t)o.i * p.q_tok_stride + (int64_t)o.h * p.q_head_stride + o.d, acc.x * inv, acc.y * inv, acc.z * inv, acc.w * inv);
+  if (o.d == 0) p.lse[(int64_t)o.h * p.C + o.i] = (M + __builtin_amdgcn_logf(L)) * 0.6931471805599453f;
 }
 
 // ---- dQ -----------------------------------------------------------------------------------------
-// Also computes Delta = <dO, O> of its rows, which the dK / dV kernel reads (it runs afterwards).
-template <typename T, int D>
-__global__ __launch_bounds__(GN_THREADS, (Gn<T, D>::RB == 512 ? 1 : 2)) void dq_generic_kernel(Params p, int32_t tiles, int32_t n_split, int lp,
-                                                                                 float* __restrict__ part) {
+// Also computes Delta = <dO, O> of its rows for the dK / dV kernel, which runs afterwards: p.delta, or (bias != nullptr) the
+// bias words from which attn_bwd_dkv_mfma.hip starts its accumulators.
+template <typename T, int D, int KH>
+__global__ __launch_bounds__(256 * KH, (Gn<T, D>::RB == 512 ? 1 : 2)) void dq_generic_kernel(Params p, int32_t tiles, int32_t n_split, int lp,
+                                                                                             int32_t max_len, float* __restrict__ part, float* __restrict__ bias, int32_t n_stages) {
   typedef Gn<T, D> X;
+  typedef GnTiles<T, D> Y;
   extern __shared__ __align__(16) unsigned char smem[];
-  const int lane = threadIdx.x & 63, hh = lane >> 5, lq = lane & 31, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lane = threadIdx.x & 63, hh = lane >> 5, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), rb = wave & 3, group = wave >> 2;
   const GnBlock b = gn_block(p, tiles, n_split);
-  const GnTile t = gn_tile(p, b.g, b.tile, wave, lane, lp);
-  const int32_t n_kt = (t.V_last + X::KT - 1) / X::KT;
-  const int32_t k0 = (int32_t)((int64_t)n_kt * b.split / n_split), k1 = (int32_t)((int64_t)n_kt * (b.split + 1) / n_split);
+  const GnRange kr = gn_range(max_len, lp, Y::KT, KH * b.split + group, KH * n_split);
+  const GnRange other = gn_range(max_len, lp, Y::KT, KH * b.split + (KH - 1 - group), KH * n_split);
+  const GnTile t = gn_tile(p, b.g, b.tile, rb, lane, lp, max_len);
+  GnStream<T, D> ks;
+  ks.init(p, t.lid, max_len, b.g, rb, lane, kr.k0 * Y::KT, lp);
 
-  uint4 qf[X::NJ], dof[X::NJ];
+  u32x4_t qf[X::NJ], dof[X::NJ];
   const int64_t roff = (int64_t)t.i * p.q_tok_stride + (int64_t)t.h * p.q_head_stride;
   float delta = 0.f;
 #pragma unroll
   for (int j = 0; j < X::NJ; ++j) {
     const int64_t at = roff * X::ES + 32 * j + 16 * hh;
-    qf[j] = *reinterpret_cast<const uint4*>((const unsigned char*)p.q + at);
-    dof[j] = *reinterpret_cast<const uint4*>((const unsigned char*)p.d_o + at);
-    const uint4 ov = *reinterpret_cast<const uint4*>((const unsigned char*)p.o + at);
-    const T* x = reinterpret_cast<const T*>(&dof[j]);
-    const T* y = reinterpret_cast<const T*>(&ov);
+    qf[j] = *reinterpret_cast<const u32x4_t*>((const unsigned char*)p.q + at);
+    dof[j] = *reinterpret_cast<const u32x4_t*>((const unsigned char*)p.d_o + at);
+    const u32x4_t ov = *reinterpret_cast<const u32x4_t*>((const unsigned char*)p.o + at);
 #pragma unroll
-    for (int k = 0; k < 16 / X::ES; ++k) delta = __builtin_fmaf(Elem<T>::load(x + k), Elem<T>::load(y + k), delta);
+    for (int k = 0; k < 4; ++k) {
+      if constexpr (X::BF) {
+        delta = __builtin_fmaf(__uint_as_float(dof[j][k] << 16), __uint_as_float(ov[k] << 16), delta);
+        delta = __builtin_fmaf(__uint_as_float(dof[j][k] & 0xffff0000u), __uint_as_float(ov[k] & 0xffff0000u), delta);
+      } else {
+        delta = __builtin_fmaf(__uint_as_float(dof[j][k]), __uint_as_float(ov[k]), delta);
+      }
+    }
   }
   delta = half_sum(delta);
-  if (b.split == 0 && t.valid && hh == 0) p.delta[(int64_t)t.h * p.C + t.i] = delta;
   const float lse2 = p.lse[(int64_t)t.h * p.C + t.i] * 1.4426950408889634f;
 
   f32x16 dq[X::DB];
   gn_zero(dq);
   const float c = p.sm_scale * 1.4426950408889634f;
-  const uint32_t lane_row = lq * X::RB + ((hh ^ X::swz(lq)) << 4);
+  if (b.split == 0 && group == 0 && t.valid && hh == 0) {
+    if (bias) {   // row space of that kernel: blocks of 32 tokens of one head, the heads interleaved
+      const uint32_t blk = (uint32_t)(t.i >> 5) * p.G + (uint32_t)(t.h - b.g * p.G), r = 32 * blk + (t.i & 31);
+      float* w = bias + (((int64_t)b.g * n_stages + (r >> 6)) * 2) * 64 + (r & 63);
+      w[0] = -lse2 / c;
+      w[64] = -delta;
+    } else {
+      p.delta[(int64_t)t.h * p.C + t.i] = delta;
+    }
+  }
+  GnAddr<T, D> ad;
+  ad.init(lane, group * GnRow<T, D, KH>::GROUP);
   const int32_t V_min = __builtin_amdgcn_readfirstlane(t.V), V_max = __builtin_amdgcn_readlane(t.V, 31);
 
-  GnStream<T, D> ks;
-  if (k0 < k1) {
-    ks.init(p, t, b.g, lane, k0 * X::KT, lp);
-    ks.copy(p, t, wave, lane, lp, k0, 0);
-  }
-  wait_copies<0>();
-  __syncthreads();
-  for (int32_t k = k0; k < k1; ++k) {
-    const uint32_t buf = ((k - k0) & 1) * GN_BUF;
-    if (k + 1 < k1) ks.copy(p, t, wave, lane, lp, k + 1, buf ^ GN_BUF);
+  gn_key_loop<T, D, KH>(p, t, ks, kr, other, max_len, group, rb, lane, lp, [&](const uint32_t at, const int32_t t0) __attribute__((always_inline)) {
+    if (!t.active || t0 >= V_max) return;
+    constexpr int NP = GnAddr<T, D>::NP, NJ = X::NJ, L = 2 * NJ + NP;
+    const bool mask = t0 + Y::KT > V_min;
+    const int32_t rel = t.V - t0 - 4 * hh;
+    f32x16 s[2];   // S and dP of one block
+    GnP<T> ds;
+    // per block: S, then dP with the exponentials of S between its instructions, dS, then dQ
+    gn_pipeline<Y::U * L>(
+        [&](const int i) __attribute__((always_inline)) {
+          const int u = i / L, k = i % L;
+          const uint32_t o = at + 32 * u * X::RB;
+          return k < NJ ? ad.row_frag(k, o) : k < 2 * NJ ? ad.row_frag(k - NJ, o + Y::TILE) : ad.tr_frag(k - 2 * NJ, o);
+        },
+        [&](const int i, const u32x4_t& f) __attribute__((always_inline)) {
+          const int u = i / L, k = i % L;
+          if (k == 0) gn_zero(s);
+          if (k < NJ) {
+            gn_mma<T>(f, qf[k], s[0]);
+          } else if (k < 2 * NJ) {
+            gn_mma<T>(f, dof[k - NJ], s[1]);
 #pragma unroll
-    for (int u = 0; u < X::KT / 32; ++u) {
-      const int32_t t0 = k * X::KT + 32 * u;
-      if (t.active && t0 < V_max) {
-        f32x16 s = gn_chain<T, D>(smem, buf + 32 * u * X::RB, lane_row, qf);
-        const f32x16 dp = gn_chain<T, D>(smem, buf + X::TILE + 32 * u * X::RB, lane_row, dof);
-        const bool mask = t0 + 32 > V_min;
-        const int32_t rel = t.V - t0 - 4 * hh;
+            for (int x = (k - NJ) * (16 / NJ); x < (k - NJ + 1) * (16 / NJ); ++x) {
+              float pr = __builtin_amdgcn_exp2f(__builtin_fmaf(s[0][x], c, -lse2));
+              if (mask && 32 * u + 8 * (x >> 2) + (x & 3) >= rel) pr = 0.f;
+              s[0][x] = pr;
+            }
+            if (k == 2 * NJ - 1) {
 #pragma unroll
-        for (int x = 0; x < 16; ++x) {
-          float pr = __builtin_amdgcn_exp2f(__builtin_fmaf(s[x], c, -lse2));
-          if (mask && 8 * (x >> 2) + (x & 3) >= rel) pr = 0.f;
-          s[x] = pr * (dp[x] - delta);
-        }
-        gn_tprod<T, D>(smem, buf + 32 * u * X::RB, lane, s, dq);
-      }
-    }
-    wait_copies<0>();
+              for (int x = 0; x < 16; x += 2) ds.set2(x, s[0][x] * (s[1][x] - delta), s[0][x + 1] * (s[1][x + 1] - delta));
+            }
+          } else {
+            gn_tr_mma<T, D>(k - 2 * NJ, f, ds, dq);
+          }
+        });
+  });
+
+  if constexpr (KH == 2) {
+    float* mo = reinterpret_cast<float*>(smem) + rb * (D * 32) + lane;
     __syncthreads();
+    if (group == 1) {
+#pragma unroll
+      for (int k = 0; k < X::DB * 16; ++k) mo[64 * k] = dq[k >> 4][k & 15];
+    }
+    __syncthreads();
+    if (group == 1) return;
+#pragma unroll
+    for (int k = 0; k < X::DB * 16; ++k) dq[k >> 4][k & 15] += mo[64 * k];
   }
-  if (!t.valid) return;
   if (n_split > 1) {
-    float* dst = part + (((int64_t)b.split * p.Hkv + b.g) * ((int64_t)p.C * p.G) + t.r) * D;
-    gn_emit<T, D>(dq, hh, [&](int d, float v0, float v1, float v2, float v3) { gn_store4<float>(dst + d, v0, v1, v2, v3); });
-  } else {
+    if (t.active) part_store<T, D>(part, (int64_t)b.split * p.Hkv * tiles * 4 + t.block, lane, dq, 1.f);
+  } else if (t.valid) {
     T* dst = (T*)p.d_q + roff;
     const float sc = p.sm_scale;
-    gn_emit<T, D>(dq, hh, [&](int d, float v0, float v1, float v2, float v3) { gn_store4<T>(dst + d, v0 * sc, v1 * sc, v2 * sc, v3 * sc); });
+    part_emit<T, D>(dq, hh, [&](int d, float v0, float v1, float v2, float v3) { part_store4<T>(dst + d, v0 * sc, v1 * sc, v2 * sc, v3 * sc); });
   }
 }
 
 // ---- dK / dV ------------------------------------------------------------------------------------
 // A workgroup owns a unit of up to 128 keys of a KV head -- 128 / P consecutive list entries, or (one
 // list per query page) one page of the union -- or one slice of the rows that see it.  Wave w holds
-// keys 32 w .. + 31.  part[slot][dK | dV][128 keys][D]: slices, added to the pool by the finish kernel.
+// keys 32 w .. + 31.  part[slot][dK | dV][wave]: slices, added to the pool by the finish kernel.
+template <typename T, int D> struct GnKey {
+  static constexpr int KT = GnTiles<T, D>::KT;
+  static constexpr int STAT = 2 * GnTiles<T, D>::BUF, LDS = STAT + 2 * 2 * 64 * 4;   // two buffers, {lse2, delta} of their rows
+};
 template <typename T, typename TG, int D>
-__global__ __launch_bounds__(GN_THREADS, (Gn<T, D>::RB >= 256 && !(sizeof(T) == 4 && D == 64) ? 1 : 2)) void dkv_generic_kernel(
-    Params p, int32_t n_split, int lp, float* __restrict__ part) {
+__global__ __launch_bounds__(256, (D == 128 || sizeof(T) == 4 ? 1 : 2)) void dkv_generic_kernel(Params p, int32_t n_split, int lp, float* __restrict__ part) {
   typedef Gn<T, D> X;
+  typedef GnKey<T, D> R;
+  typedef GnTiles<T, D> Y;
   extern __shared__ __align__(16) unsigned char smem[];
   const int tid = threadIdx.x, lane = tid & 63, hh = lane >> 5, lq = lane & 31, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int32_t bid = blockIdx.x, rest = bid / p.Hkv, g = bid - rest * p.Hkv;
@@ -512,34 +668,35 @@ __global__ __launch_bounds__(GN_THREADS, (Gn<T, D>::RB >= 256 && !(sizeof(T) == 
   const int64_t pos0 = owned_at(p, g, e0) << lp;
   const int32_t r_lo = pos0 > first_q ? (int32_t)(pos0 - first_q) * p.G : 0, rows = p.C * p.G;
   // stages of KT rows: [s0, s1) of the chunk's, or stage v % spq of the unit's query page v / spq
-  const int32_t rpq = p.P * p.G, spq = (rpq + X::KT - 1) / X::KT;
-  const int32_t st_lo = r_lo / X::KT, st_n = (rows + X::KT - 1) / X::KT - st_lo;
+  const int32_t rpq = p.P * p.G, spq = (rpq + R::KT - 1) / R::KT;
+  const int32_t st_lo = r_lo / R::KT, st_n = (rows + R::KT - 1) / R::KT - st_lo;
   const int32_t s0 = p.qp ? 0 : st_lo + (int32_t)((int64_t)st_n * sp / n_split);
   const int32_t s1 = p.qp ? qc * spq : st_lo + (int32_t)((int64_t)st_n * (sp + 1) / n_split);
   int32_t tau_v = 0;
   if (p.qp && lane < qc) tau_v = p.inv_qp[(int64_t)g * p.m * p.sel_stride + p.inv_off[(int64_t)g * (p.un_stride + 1) + e0] + q0 + lane];
 
-  uint4 kf[X::NJ], vf[X::NJ];
+  u32x4_t kf[X::NJ], vf[X::NJ];
 #pragma unroll
   for (int j = 0; j < X::NJ; ++j) {
     const int64_t at = koff * X::ES + 32 * j + 16 * hh;
-    kf[j] = *reinterpret_cast<const uint4*>((const unsigned char*)p.k_pool + at);
-    vf[j] = *reinterpret_cast<const uint4*>((const unsigned char*)p.v_pool + at);
+    kf[j] = *reinterpret_cast<const u32x4_t*>((const unsigned char*)p.k_pool + at);
+    vf[j] = *reinterpret_cast<const u32x4_t*>((const unsigned char*)p.v_pool + at);
   }
   f32x16 dk[X::DB], dv[X::DB];
   gn_zero(dk);
   gn_zero(dv);
   const float c = p.sm_scale * 1.4426950408889634f;
-  const uint32_t lane_row = lq * X::RB + ((hh ^ X::swz(lq)) << 4);
+  GnAddr<T, D> ad;
+  ad.init(lane, 0);
 
   // rows [base, end) of stage s
   auto stage_rows = [&](int32_t s, int32_t& base, int32_t& end) {
     if (!p.qp) {
-      base = s * X::KT;
+      base = s * R::KT;
       end = rows;
     } else {
       const int32_t v = s / spq, tau = __builtin_amdgcn_readlane(tau_v, v & 63);
-      base = tau * rpq + (s - v * spq) * X::KT;
+      base = tau * rpq + (s - v * spq) * R::KT;
       end = (tau + 1) * rpq;
     }
   };
@@ -548,19 +705,19 @@ __global__ __launch_bounds__(GN_THREADS, (Gn<T, D>::RB >= 256 && !(sizeof(T) == 
     int32_t base, end;
     stage_rows(s, base, end);
     const uint32_t lrow = lane / X::NG, pos16 = lane % X::NG;
-    const uint32_t dst = buf + wave * X::RW * X::RB;
+    const uint32_t dst = buf + wave * Y::RW * X::RB;
 #pragma unroll
-    for (int k = 0; k < X::NI; ++k) {
-      const uint32_t row = wave * X::RW + k * X::RPI + lrow;
+    for (int k = 0; k < Y::NI; ++k) {
+      const uint32_t row = wave * Y::RW + k * X::RPI + lrow;
       int32_t r = base + (int32_t)row;
       r = r < end ? r : end - 1;
       const int32_t i = (int32_t)div_g(p, (uint32_t)r);
       const int64_t at = ((int64_t)i * p.q_tok_stride + (int64_t)(g * p.G + (r - i * p.G)) * p.q_head_stride) * X::ES +
                          (int64_t)((pos16 ^ X::swz(row & 15)) << 4);
       gn_copy16((const unsigned char*)p.q + at, dst + 1024 * k);
-      gn_copy16((const unsigned char*)p.d_o + at, dst + X::TILE + 1024 * k);
+      gn_copy16((const unsigned char*)p.d_o + at, dst + Y::TILE + 1024 * k);
     }
-    if (tid < X::KT) {
+    if (tid < R::KT) {
       const int32_t r = base + tid;
       st_l = INFINITY;   // rows past the end: P = 0
       st_d = 0.f;
@@ -572,9 +729,9 @@ __global__ __launch_bounds__(GN_THREADS, (Gn<T, D>::RB >= 256 && !(sizeof(T) == 
       }
     }
   };
-  auto publish = [&](uint32_t buf) {   // buf: GN_BUF * index
-    float* st = reinterpret_cast<float*>(smem + GN_STAT + (buf ? 512 : 0));
-    if (tid < X::KT) {
+  auto publish = [&](uint32_t buf) {   // buf: Y::BUF * index
+    float* st = reinterpret_cast<float*>(smem + R::STAT + (buf ? 512 : 0));
+    if (tid < R::KT) {
       st[tid] = st_l;
       st[64 + tid] = st_d;
     }
@@ -586,79 +743,103 @@ __global__ __launch_bounds__(GN_THREADS, (Gn<T, D>::RB >= 256 && !(sizeof(T) == 
   }
   wait_copies<0>();
   __syncthreads();
-  for (int32_t s = s0; s < s1; ++s) {
-    const uint32_t buf = ((s - s0) & 1) * GN_BUF;
-    if (s + 1 < s1) copy(s + 1, buf ^ GN_BUF);
+  auto stage = [&](const int32_t s, const uint32_t buf) __attribute__((always_inline)) {   // (buf: a constant)
+    if (s + 1 < s1) copy(s + 1, buf ^ Y::BUF);
     int32_t base, end;
     stage_rows(s, base, end);
-    const float* st = reinterpret_cast<const float*>(smem + GN_STAT + (buf ? 512 : 0));
+    const float* st = reinterpret_cast<const float*>(smem + R::STAT + (buf ? 512 : 0));
+    if (active) {
+      // per block of 32 rows: S; dP with the exponentials of S between its instructions; dV with dS between its
+      // instructions; dK
+      constexpr int NP = GnAddr<T, D>::NP, NJ = X::NJ, L = 2 * NJ + 2 * NP;
+      const bool mask = base < r_key_max;   // (wave-uniform)
+      const int32_t rel = r_key - base - 4 * hh;
+      f32x16 sv[2];
+      GnP<T> pr, ds;
+      gn_pipeline<Y::U * L>(
+          [&](const int i) __attribute__((always_inline)) {
+            const int u = i / L, k = i % L;
+            const uint32_t o = buf + 32 * u * X::RB;
+            return k < NJ ? ad.row_frag(k, o) : k < 2 * NJ ? ad.row_frag(k - NJ, o + Y::TILE)
+                 : k < 2 * NJ + NP ? ad.tr_frag(k - 2 * NJ, o + Y::TILE) : ad.tr_frag(k - 2 * NJ - NP, o);
+          },
+          [&](const int i, const u32x4_t& f) __attribute__((always_inline)) {
+            const int u = i / L, k = i % L;
+            if (k == 0) gn_zero(sv);
+            if (k < NJ) {
+              gn_mma<T>(f, kf[k], sv[0]);
+            } else if (k < 2 * NJ) {
+              gn_mma<T>(f, vf[k - NJ], sv[1]);
 #pragma unroll
-    for (int u = 0; u < X::KT / 32; ++u) {
-      if (active) {
-        f32x16 pr = gn_chain<T, D>(smem, buf + 32 * u * X::RB, lane_row, kf);
-        f32x16 ds = gn_chain<T, D>(smem, buf + X::TILE + 32 * u * X::RB, lane_row, vf);
-        const bool mask = base + 32 * u < r_key_max;   // (wave-uniform)
-        const int32_t rel = r_key - base - 32 * u - 4 * hh;
+              for (int x = (k - NJ) * (16 / NJ); x < (k - NJ + 1) * (16 / NJ); ++x) {
+                float v = __builtin_amdgcn_exp2f(__builtin_fmaf(sv[0][x], c, -st[32 * u + 8 * (x >> 2) + 4 * hh + (x & 3)]));
+                if (mask && 32 * u + 8 * (x >> 2) + (x & 3) < rel) v = 0.f;
+                sv[0][x] = v;
+              }
+              if (k == 2 * NJ - 1) {
 #pragma unroll
-        for (int a = 0; a < 4; ++a) {
-          const float4 l4 = *reinterpret_cast<const float4*>(st + 32 * u + 8 * a + 4 * hh);
-          const float4 d4 = *reinterpret_cast<const float4*>(st + 64 + 32 * u + 8 * a + 4 * hh);
-          const float lv[4] = {l4.x, l4.y, l4.z, l4.w}, dl[4] = {d4.x, d4.y, d4.z, d4.w};
+                for (int x = 0; x < 16; x += 2) pr.set2(x, sv[0][x], sv[0][x + 1]);
+              }
+            } else if (k < 2 * NJ + NP) {
+              gn_tr_mma<T, D>(k - 2 * NJ, f, pr, dv);
+              const int n = k - 2 * NJ;
 #pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            float v = __builtin_amdgcn_exp2f(__builtin_fmaf(pr[4 * a + q], c, -lv[q]));
-            if (mask && 8 * a + q < rel) v = 0.f;
-            pr[4 * a + q] = v;
-            ds[4 * a + q] = v * (ds[4 * a + q] - dl[q]);
-          }
-        }
-        gn_tprod<T, D>(smem, buf + X::TILE + 32 * u * X::RB, lane, pr, dv);
-        gn_tprod<T, D>(smem, buf + 32 * u * X::RB, lane, ds, dk);
-      }
+              for (int x = n * (16 / NP); x < (n + 1) * (16 / NP); ++x)
+                sv[1][x] = sv[0][x] * (sv[1][x] - st[64 + 32 * u + 8 * (x >> 2) + 4 * hh + (x & 3)]);
+              if (n == NP - 1) {
+#pragma unroll
+                for (int x = 0; x < 16; x += 2) ds.set2(x, sv[1][x], sv[1][x + 1]);
+              }
+            } else {
+              gn_tr_mma<T, D>(k - 2 * NJ - NP, f, ds, dk);
+            }
+          });
     }
-    if (s + 1 < s1) publish(buf ^ GN_BUF);
+    if (s + 1 < s1) publish(buf ^ Y::BUF);
     wait_copies<0>();
     __syncthreads();
+  };
+  for (int32_t s = s0; s < s1; s += 2) {
+    stage(s, 0);
+    if (s + 1 < s1) stage(s + 1, Y::BUF);
   }
 
   const float sc = p.sm_scale;
   if (slot >= 0) {
-    float* dst = part + ((int64_t)slot * 2 * GN_ROWS + kq) * D;
-    if (kvalid) {
-      gn_emit<T, D>(dk, hh, [&](int d, float v0, float v1, float v2, float v3) { gn_store4<float>(dst + d, v0 * sc, v1 * sc, v2 * sc, v3 * sc); });
-      dst += GN_ROWS * D;
-      gn_emit<T, D>(dv, hh, [&](int d, float v0, float v1, float v2, float v3) { gn_store4<float>(dst + d, v0, v1, v2, v3); });
+    if (active) {
+      part_store<T, D>(part, (int64_t)slot * 8 + wave, lane, dk, sc);
+      part_store<T, D>(part, (int64_t)slot * 8 + 4 + wave, lane, dv, 1.f);
     }
   } else if (kvalid) {
     TG* pk = (TG*)p.dk_pool + koff;
     TG* pv = (TG*)p.dv_pool + koff;
-    gn_emit<T, D>(dk, hh, [&](int d, float v0, float v1, float v2, float v3) { gn_add4<TG>(pk + d, v0 * sc, v1 * sc, v2 * sc, v3 * sc); });
-    gn_emit<T, D>(dv, hh, [&](int d, float v0, float v1, float v2, float v3) { gn_add4<TG>(pv + d, v0, v1, v2, v3); });
+    part_emit<T, D>(dk, hh, [&](int d, float v0, float v1, float v2, float v3) { part_add4<TG>(pk + d, v0 * sc, v1 * sc, v2 * sc, v3 * sc); });
+    part_emit<T, D>(dv, hh, [&](int d, float v0, float v1, float v2, float v3) { part_add4<TG>(pv + d, v0, v1, v2, v3); });
   }
 }
 
-// What is left of a backward with splits, in one launch: workgroups below dq_blocks add the dQ partials (D / 4
-// lanes per row), the others add the slices of a dK / dV unit to the pool (one thread per four dims).
+// What is left of a backward with splits, in one launch: workgroups below dq_blocks add the dQ partials, the others
+// add the slices of a dK / dV unit to the pool.
 template <typename T, typename TG, int D>
-__global__ __launch_bounds__(256) void bwd_finish_kernel(Params p, int32_t dq_split, const float* __restrict__ dq_part, int32_t dq_blocks,
-                                                         int32_t kv_split, const float* __restrict__ kv_part, int lp) {
-  constexpr int LPR = D / 4, BPU = 2 * GN_ROWS * LPR / 256;   // workgroups per unit
+__global__ __launch_bounds__(256) void bwd_finish_kernel(Params p, int32_t tiles, int32_t dq_split, const float* __restrict__ dq_part,
+                                                         int32_t dq_blocks, int32_t kv_split, const float* __restrict__ kv_part, int lp) {
+  constexpr int BPU = 2 * 4 * (D / 8) * 64 / 256;   // workgroups per unit
   if ((int32_t)blockIdx.x < dq_blocks) {
-    const int64_t rows = (int64_t)p.C * p.G, row = (int64_t)blockIdx.x * (256 / LPR) + threadIdx.x / LPR;
-    if (row >= rows * p.Hkv) return;
-    const int d = (threadIdx.x % LPR) * 4, g = (int)(row / rows);
-    const int32_t r = (int32_t)(row - g * rows), i = (int32_t)div_g(p, (uint32_t)r), h = g * p.G + (r - i * p.G);
+    const GnOut<T, D> o(p, tiles, (int64_t)blockIdx.x * 256 + threadIdx.x);
+    if (!o.ok) return;
+    const int64_t blocks = (int64_t)p.Hkv * tiles * 4;
     float4 a = make_float4(0.f, 0.f, 0.f, 0.f);
     for (int s = 0; s < dq_split; ++s) {
-      const float4 v = *reinterpret_cast<const float4*>(dq_part + (s * rows * p.Hkv + row) * D + d);
+      const float4 v = reinterpret_cast<const float4*>(dq_part)[((s * blocks + o.block) * (D / 8) + o.k) * 64 + o.lane];
       a.x += v.x; a.y += v.y; a.z += v.z; a.w += v.w;
     }
     const float sc = p.sm_scale;
-    gn_store4<T>((T*)p.d_q + (int64_t)i * p.q_tok_stride + (int64_t)h * p.q_head_stride + d, a.x * sc, a.y * sc, a.z * sc, a.w * sc);
+    part_store4<T>((T*)p.d_q + (int64_t)o.i * p.q_tok_stride + (int64_t)o.h * p.q_head_stride + o.d, a.x * sc, a.y * sc, a.z * sc, a.w * sc);
     return;
   }
-  const int32_t b = (int32_t)blockIdx.x - dq_blocks, blk = b % BPU, ug = b / BPU, u = ug / p.Hkv, g = ug - u * p.Hkv;
-  const int e4 = blk * 256 + threadIdx.x, which = e4 / (GN_ROWS * LPR), kq = (e4 / LPR) % GN_ROWS, d = (e4 % LPR) * 4;
+  const int32_t b = (int32_t)blockIdx.x - dq_blocks, ug = b / BPU, u = ug / p.Hkv, g = ug - u * p.Hkv;
+  const int idx = (b - ug * BPU) * 256 + threadIdx.x, lane = idx & 63, k = (idx >> 6) % (D / 8), wb = (idx >> 6) / (D / 8);   // wb: 4 which + wave
+  const int which = wb >> 2, kq = 32 * (wb & 3) + (lane & 31);
   int64_t slot, next;
   int32_t e;
   if (p.qp) {
@@ -675,104 +856,176 @@ __global__ __launch_bounds__(256) void bwd_finish_kernel(Params p, int32_t dq_sp
   }
   const int64_t l = owned_at(p, g, e);
   float4 a = make_float4(0.f, 0.f, 0.f, 0.f);
-  for (int s = 0; s < kv_split; ++s) {
-    const float4 v = *reinterpret_cast<const float4*>(kv_part + (((slot + s * next) * 2 + which) * GN_ROWS + kq) * D + d);
+  for (int s = 0; s < kv_split; ++s) {   // (read once: non-temporal, so that they push nothing else out of the caches)
+    typedef float f32x4_t __attribute__((ext_vector_type(4)));
+    const f32x4_t v = __builtin_nontemporal_load(reinterpret_cast<const f32x4_t*>(kv_part) + (((slot + s * next) * 8 + wb) * (D / 8) + k) * 64 + lane);
     a.x += v.x; a.y += v.y; a.z += v.z; a.w += v.w;
   }
   TG* pool = (TG*)(which == 0 ? p.dk_pool : p.dv_pool) + (int64_t)p.page_table[l] * p.pool_page_stride + (int64_t)g * p.pool_head_stride +
-             (int64_t)(kq & (p.P - 1)) * p.pool_tok_stride + d;
-  gn_add4<TG>(pool, a.x, a.y, a.z, a.w);
+             (int64_t)(kq & (p.P - 1)) * p.pool_tok_stride + part_group_dim<T, D>(k, lane >> 5);
+  part_add4<TG>(pool, a.x, a.y, a.z, a.w);
 }
 
 // ---- host side ----------------------------------------------------------------------------------
 static inline size_t gn_up(size_t x) { return (x + 255) & ~(size_t)255; }
 
-// Splits: enough workgroups for two per compute unit, no split shorter than two tiles of the longest list
-static int32_t gn_row_splits(const Params& p, int32_t max_len, int32_t kt) {
-  const int64_t wgs = (int64_t)gn_tiles(p.C, p.G, p.P, p.m, p.qp) * p.Hkv;
-  const int64_t longest = p.qp ? p.sel_stride : max_len;
-  const int64_t want = 512 / (wgs > 0 ? wgs : 1), most = longest * p.P / (2 * kt);
-  int64_t s = want < most ? want : most;
-  s = s < 1 ? 1 : s > 32 ? 32 : s;
-  return (int32_t)s;
+// How the rows of a forward or dQ call go onto the chip: splits of the key range and wave groups per workgroup, by an
+// estimate of the time in microseconds.  `unit` is the time of a tile of KT keys on a full chip, for a workgroup of two
+// groups (256 of them at a time) or for two workgroups of one group (512 at a time).  A round that leaves compute
+// units idle costs less than a full one -- the clock rises, single groups get a compute unit to themselves --:
+// `only` if it is the call's only round, `rest` after full ones, both growing with the part f that is filled.  On
+// top a round costs RAMP (launch, list -> page table -> first tile), and a split its combine kernel and the
+// partial sums, written and read at about 4 TB/s.  The constants are fitted to a sweep over 28 / 4 and 6 / 2 heads, 1 to
+// 48 query pages, lists of 8 to 240 + m pages, 1 to 24 splits.  E.g. 28 / 4 heads, 65 pages, one query page (28 tiles of 128
+// rows): 8 splits of two groups, 36 us against 123 without; 12 query pages (336 tiles): 3 splits of single
+// groups, 241 against 260.
+static int32_t gn_list_len(const Params& p, int32_t max_len) { return p.qp ? p.sel_stride : max_len; }
+struct GnPlan { int32_t n, groups; float us; };
+static float gn_rounds(float r, float only0, float only1, float rest0, float rest1) {
+  const float full = floorf(r), f = r - full;
+  return full + (f <= 0.f ? 0.f : full > 0.f ? rest0 + rest1 * f : only0 + only1 * f);
 }
+static GnPlan gn_plan(const Params& p, bool bf, int32_t max_len, bool dq) {
+  constexpr float RAMP = 6.f, LAUNCH = 3.f, PART = 2.56e-4f;
+  const float ds = (p.D == 128 ? 1.f : bf ? 0.65f : 0.5f) * (dq ? 1.4f : 1.f);
+  const float unit1 = (bf ? 2.15f : 7.8f) * ds, unit2 = (bf ? 1.17f : 4.0f) * ds;   // (fp32: what its matrix pipe needs)
+  const int32_t wgs = gn_tiles(p.C, p.G, p.P, p.m, p.qp) * p.Hkv, kt = bf ? 64 : 32;
+  const float len = (float)gn_list_len(p, max_len);
+  const float all = len * p.P / kt, avg = (len - 0.5f * p.m) * p.P / kt;   // tiles of the longest row, of an average one
+  const bool pairs = bf || !dq || p.D == 64;   // (fp32 dQ at head dim 128 holds 320 registers: one wave per SIMD)
+  GnPlan best = {1, 1, 1e30f};
+  for (int32_t n = 1; n <= 32 && (n == 1 || n <= all); ++n) {
+    const float x = (float)wgs * n, extra = n > 1 ? LAUNCH + x * p.D * PART : 0.f;
+    const float mine = avg / n > 1.f ? avg / n : 1.f;
+    float us = pairs ? gn_rounds(x / 512.f, bf ? 0.55f : 0.5f, 0.42f, 0.35f, 0.6f) * mine * unit1 + ceilf(x / 512.f) * RAMP
+                     : ceilf(x / 256.f) * (mine * 0.5f * unit1 + RAMP);
+    if (us + extra < best.us) best = {n, 1, us + extra};
+    if (!pairs || 2 * n > all) continue;
+    us = gn_rounds(x / 256.f, 0.78f, 0.14f, 0.58f, 0.25f) * (mine > 2.f ? mine : 2.f) * unit2 + ceilf(x / 256.f) * RAMP;
+    if (us + extra < best.us) best = {n, 2, us + extra};
+  }
+  return best;
+}
+
 static int32_t gn_key_units(const Params& p, int32_t max_len) {
   return (int32_t)(((int64_t)max_len * p.P + GN_ROWS - 1) / GN_ROWS);
 }
-static int32_t gn_key_splits(const Params& p, int32_t max_len, int32_t kt) {
+static int32_t gn_key_splits(const Params& p, bool bf, int32_t max_len) {
   if (p.qp) return 1;
+  const int32_t kt = bf ? 64 : 32;
   const int64_t wgs = (int64_t)gn_key_units(p, max_len) * p.Hkv;
-  const int64_t want = 512 / (wgs > 0 ? wgs : 1), most = ((int64_t)p.C * p.G + kt - 1) / kt / 2;
+  const int64_t want = 512 / (wgs > 0 ? wgs : 1), most = ((int64_t)p.C * p.G + kt - 1) / kt;
   int64_t s = want < most ? want : most;
   s = s < 1 ? 1 : s > 16 ? 16 : s;
   return (int32_t)s;
 }
-static int32_t gn_kt(const Params& p, bool bf) { return p.D * (bf ? 2 : 4) == 512 ? 32 : 64; }
 
-static size_t gn_row_part_bytes(const Params& p, int32_t split) {
-  return split > 1 ? gn_up((size_t)split * p.Hq * p.C * p.D * 4) : 0;
-}
+static size_t gn_row_blocks(const Params& p) { return (size_t)gn_tiles(p.C, p.G, p.P, p.m, p.qp) * p.Hkv * 4; }
+static size_t gn_row_part_bytes(const Params& p, int32_t split) { return split > 1 ? split * gn_row_blocks(p) * 32 * p.D * 4 : 0; }
 size_t fwd_generic_workspace_bytes(const Params& p, bool bf, int32_t max_len) {
-  const int32_t s = gn_row_splits(p, max_len, gn_kt(p, bf));
-  return s > 1 ? gn_row_part_bytes(p, s) + gn_up((size_t)s * p.Hq * p.C * 8) : 256;
+  const int32_t s = gn_plan(p, bf, max_len, false).n;
+  return s > 1 ? gn_row_part_bytes(p, s) + s * gn_row_blocks(p) * 32 * 8 : 256;
 }
+size_t dq_generic_part_bytes(const Params& p, bool bf, int32_t max_len) { return gn_row_part_bytes(p, gn_plan(p, bf, max_len, true).n); }
 static size_t gn_key_part_bytes(const Params& p, int32_t max_len, int32_t split) {
   const size_t slots = p.qp ? (size_t)p.Hkv * qp_max_pslots(p, p.sel_stride) : split > 1 ? (size_t)gn_key_units(p, max_len) * p.Hkv * split : 0;
   return gn_up(slots * 2 * GN_ROWS * p.D * 4);
 }
 size_t bwd_generic_workspace_bytes(const Params& p, bool bf, int32_t max_len) {
-  const int32_t kt = gn_kt(p, bf);
-  return gn_up((size_t)p.Hq * p.C * sizeof(float)) + gn_row_part_bytes(p, gn_row_splits(p, max_len, kt)) +
-         gn_key_part_bytes(p, max_len, gn_key_splits(p, max_len, kt));
+  return gn_up((size_t)p.Hq * p.C * sizeof(float)) + dq_generic_part_bytes(p, bf, max_len) +
+         gn_key_part_bytes(p, max_len, gn_key_splits(p, bf, max_len));
 }
 
-template <typename T, int D>
-static hipError_t fwd_generic(const Params& p, int32_t max_len, void* ws, size_t ws_bytes, hipStream_t st) {
+template <typename T, int D, int KH>
+static hipError_t fwd_launch(const Params& p, int32_t tiles, int32_t ns, int32_t len, float* part, float2* ml, hipStream_t st) {
+  typedef GnRow<T, D, KH> R;
   static DeviceOnce lds_once;
-  if (hipError_t e = ensure_max_dynamic_lds(lds_once, (const void*)fwd_generic_kernel<T, D>, GN_LDS); e != hipSuccess) return e;
-  const int lp = __builtin_ctz(p.P);
-  int32_t ns = gn_row_splits(p, max_len, Gn<T, D>::KT);
-  if (ns > 1 && (!ws || ws_bytes < fwd_generic_workspace_bytes(p, Gn<T, D>::BF, max_len))) ns = 1;   // (the forward also runs without a workspace)
-  float* part = (float*)ws;
-  float2* ml = (float2*)((unsigned char*)ws + gn_row_part_bytes(p, ns));
-  const int32_t tiles = gn_tiles(p.C, p.G, p.P, p.m, p.qp);
-  ProfScope prof_("attn_fwd_generic", st);
-  fwd_generic_kernel<T, D><<<dim3((unsigned)tiles * p.Hkv * ns), dim3(GN_THREADS), GN_LDS, st>>>(p, tiles, ns, lp, part, ml);
-  if (ns > 1) {
-    constexpr int RPB = 256 / (D / 4);
-    fwd_combine_kernel<T, D><<<dim3((unsigned)(((int64_t)p.Hq * p.C + RPB - 1) / RPB)), dim3(256), 0, st>>>(p, ns, part, ml);
-  }
+  if (hipError_t e = ensure_max_dynamic_lds(lds_once, (const void*)fwd_generic_kernel<T, D, KH>, R::LDS); e != hipSuccess) return e;
+  fwd_generic_kernel<T, D, KH><<<dim3((unsigned)tiles * p.Hkv * ns), dim3(R::THREADS), R::LDS, st>>>(p, tiles, ns, __builtin_ctz(p.P), len, part, ml);
   return hipGetLastError();
 }
-hipError_t launch_fwd_generic(const Params& p, bool bf, int32_t max_len, void* ws, size_t ws_bytes, hipStream_t st) {
-  if (bf) return p.D == 128 ? fwd_generic<bf16_t, 128>(p, max_len, ws, ws_bytes, st) : fwd_generic<bf16_t, 64>(p, max_len, ws, ws_bytes, st);
-  return p.D == 128 ? fwd_generic<float, 128>(p, max_len, ws, ws_bytes, st) : fwd_generic<float, 64>(p, max_len, ws, ws_bytes, st);
+template <typename T, int D>
+static hipError_t fwd_generic(const Params& p, int32_t max_len, void* ws, size_t ws_bytes, const char* name, hipStream_t st) {
+  GnPlan sp = gn_plan(p, Gn<T, D>::BF, max_len, false);
+  if (sp.n > 1 && (!ws || ws_bytes < fwd_generic_workspace_bytes(p, Gn<T, D>::BF, max_len))) sp.n = 1;   // (the forward also runs without a workspace)
+  const int32_t ns = sp.n;
+  float* part = (float*)ws;
+  float2* ml = (float2*)((unsigned char*)ws + gn_row_part_bytes(p, ns));
+  const int32_t tiles = gn_tiles(p.C, p.G, p.P, p.m, p.qp), len = gn_list_len(p, max_len);
+  ProfScope prof_(name, st);
+  hipError_t e = sp.groups == 2 ? fwd_launch<T, D, 2>(p, tiles, ns, len, part, ml, st) : fwd_launch<T, D, 1>(p, tiles, ns, len, part, ml, st);
+  if (e == hipSuccess && ns > 1) {
+    fwd_combine_kernel<T, D><<<dim3((unsigned)(gn_row_blocks(p) * (D / 8) * 64 / 256)), dim3(256), 0, st>>>(p, tiles, ns, part, ml);
+    e = hipGetLastError();
+  }
+  return e;
+}
+hipError_t launch_fwd_generic(const Params& p, bool bf, int32_t max_len, void* ws, size_t ws_bytes, const char* name, hipStream_t st) {
+  if (bf) return p.D == 128 ? fwd_generic<bf16_t, 128>(p, max_len, ws, ws_bytes, name, st) : fwd_generic<bf16_t, 64>(p, max_len, ws, ws_bytes, name, st);
+  return p.D == 128 ? fwd_generic<float, 128>(p, max_len, ws, ws_bytes, name, st) : fwd_generic<float, 64>(p, max_len, ws, ws_bytes, name, st);
+}
+
+template <typename T, int D, int KH>
+static hipError_t dq_launch(const Params& p, int32_t tiles, int32_t ns, int32_t len, float* part, float* bias, int32_t n_stages, hipStream_t st) {
+  typedef GnRow<T, D, KH> R;
+  static DeviceOnce lds_once;
+  if (hipError_t e = ensure_max_dynamic_lds(lds_once, (const void*)dq_generic_kernel<T, D, KH>, R::LDS); e != hipSuccess) return e;
+  dq_generic_kernel<T, D, KH><<<dim3((unsigned)tiles * p.Hkv * ns), dim3(R::THREADS), R::LDS, st>>>(p, tiles, ns, __builtin_ctz(p.P), len, part,
+                                                                                                   bias, n_stages);
+  return hipGetLastError();
+}
+template <typename T, int D>
+static hipError_t dq_generic(const Params& p, int32_t max_len, float* part, float* bias, int32_t n_stages, int32_t* splits, hipStream_t st) {
+  const GnPlan sp = gn_plan(p, Gn<T, D>::BF, max_len, true);
+  const int32_t tiles = gn_tiles(p.C, p.G, p.P, p.m, p.qp), len = gn_list_len(p, max_len);
+  *splits = sp.n;
+  if constexpr (Gn<T, D>::RB < 512)   // (fp32 at head dim 128 needs 320 registers: one wave per SIMD)
+    if (sp.groups == 2) return dq_launch<T, D, 2>(p, tiles, sp.n, len, part, bias, n_stages, st);
+  return dq_launch<T, D, 1>(p, tiles, sp.n, len, part, bias, n_stages, st);
+}
+hipError_t launch_dq_generic_bf16_128(const Params& p, int32_t max_len, float* part, float* bias, int32_t n_stages, int32_t* splits, hipStream_t st) {
+  return dq_generic<bf16_t, 128>(p, max_len, part, bias, n_stages, splits, st);
+}
+
+template <typename T, typename TG, int D>
+static hipError_t bwd_finish(const Params& p, int32_t dq_split, const float* dq_part, int32_t kv_units, int32_t kv_split, const float* kv_part,
+                             hipStream_t st) {
+  constexpr int BPU = 2 * 4 * (D / 8) * 64 / 256;
+  const int32_t dq_blocks = dq_split > 1 ? (int32_t)(gn_row_blocks(p) * (D / 8) * 64 / 256) : 0;
+  const int64_t blocks = dq_blocks + (int64_t)kv_units * p.Hkv * BPU;
+  if (blocks <= 0) return hipSuccess;
+  bwd_finish_kernel<T, TG, D><<<dim3((unsigned)blocks), dim3(256), 0, st>>>(p, gn_tiles(p.C, p.G, p.P, p.m, p.qp), dq_split, dq_part, dq_blocks, kv_split,
+                                                                            kv_part, __builtin_ctz(p.P));
+  return hipGetLastError();
+}
+hipError_t launch_bwd_finish(const Params& p, bool bf, int32_t dq_split, const float* dq_part, int32_t kv_units, int32_t kv_split,
+                             const float* kv_part, hipStream_t st) {
+#define OOMB_FINISH(T, TG) (p.D == 128 ? bwd_finish<T, TG, 128>(p, dq_split, dq_part, kv_units, kv_split, kv_part, st) \
+                                       : bwd_finish<T, TG, 64>(p, dq_split, dq_part, kv_units, kv_split, kv_part, st))
+  if (bf) return p.grad_is_bf16 ? OOMB_FINISH(bf16_t, bf16_t) : OOMB_FINISH(bf16_t, float);
+  return p.grad_is_bf16 ? OOMB_FINISH(float, bf16_t) : OOMB_FINISH(float, float);
+#undef OOMB_FINISH
 }
 
 template <typename T, typename TG, int D>
 static hipError_t bwd_generic(Params p, int32_t max_len, void* ws, hipStream_t st) {
-  static DeviceOnce once_q, once_kv;
-  if (hipError_t e = ensure_max_dynamic_lds(once_q, (const void*)dq_generic_kernel<T, D>, GN_LDS); e != hipSuccess) return e;
-  if (hipError_t e = ensure_max_dynamic_lds(once_kv, (const void*)dkv_generic_kernel<T, TG, D>, GN_LDS); e != hipSuccess) return e;
-  const int lp = __builtin_ctz(p.P);
-  const int32_t kt = Gn<T, D>::KT, ns = gn_row_splits(p, max_len, kt), nk = gn_key_splits(p, max_len, kt);
+  static DeviceOnce once_kv;
+  if (hipError_t e = ensure_max_dynamic_lds(once_kv, (const void*)dkv_generic_kernel<T, TG, D>, GnKey<T, D>::LDS); e != hipSuccess) return e;
+  const int32_t nk = gn_key_splits(p, Gn<T, D>::BF, max_len);
   unsigned char* w = (unsigned char*)ws;
   p.delta = (float*)w;
   w += gn_up((size_t)p.Hq * p.C * sizeof(float));
   float* dq_part = (float*)w;
-  float* kv_part = (float*)(w + gn_row_part_bytes(p, ns));
-  const int32_t tiles = gn_tiles(p.C, p.G, p.P, p.m, p.qp);
+  float* kv_part = (float*)(w + dq_generic_part_bytes(p, Gn<T, D>::BF, max_len));
   const int32_t units = p.qp ? p.max_units : gn_key_units(p, max_len);
   ProfScope prof_("attn_bwd_generic", st);
-  dq_generic_kernel<T, D><<<dim3((unsigned)tiles * p.Hkv * ns), dim3(GN_THREADS), GN_LDS, st>>>(p, tiles, ns, lp, dq_part);
-  dkv_generic_kernel<T, TG, D><<<dim3((unsigned)units * p.Hkv * nk), dim3(GN_THREADS), GN_LDS, st>>>(p, nk, lp, kv_part);
-  if (ns > 1 || nk > 1 || p.qp) {
-    constexpr int RPB = 256 / (D / 4), BPU = 2 * GN_ROWS * (D / 4) / 256;
-    const int32_t dq_blocks = ns > 1 ? (int32_t)(((int64_t)p.Hq * p.C + RPB - 1) / RPB) : 0;
-    const int64_t kv_blocks = (int64_t)(p.qp ? p.max_multi : nk > 1 ? units : 0) * p.Hkv * BPU;
-    bwd_finish_kernel<T, TG, D><<<dim3((unsigned)(dq_blocks + kv_blocks)), dim3(256), 0, st>>>(p, ns, dq_part, dq_blocks, nk, kv_part, lp);
-  }
-  return hipGetLastError();
+  int32_t ns = 1;
+  hipError_t e = dq_generic<T, D>(p, max_len, dq_part, nullptr, 0, &ns, st);
+  if (e != hipSuccess) return e;
+  dkv_generic_kernel<T, TG, D><<<dim3((unsigned)units * p.Hkv * nk), dim3(256), GnKey<T, D>::LDS, st>>>(p, nk, __builtin_ctz(p.P), kv_part);
+  e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  return bwd_finish<T, TG, D>(p, ns, dq_part, p.qp ? p.max_multi : nk > 1 ? units : 0, nk, kv_part, st);
 }
 // max_len: host-side upper bound of the list length (of the union with one list per query page)
 hipError_t launch_bwd_generic(const Params& p, bool bf, int32_t max_len, void* ws, hipStream_t st) {
@@ -780,6 +1033,18 @@ hipError_t launch_bwd_generic(const Params& p, bool bf, int32_t max_len, void* w
   if (bf) return p.grad_is_bf16 ? OOMB_BWD(bf16_t, bf16_t) : OOMB_BWD(bf16_t, float);
   return p.grad_is_bf16 ? OOMB_BWD(float, bf16_t) : OOMB_BWD(float, float);
 #undef OOMB_BWD
+}
+
+// Whether a shape with kernels of its own (bf16, P = D = 128) is faster here.  Those take 256 rows per workgroup
+// and 2.0 us (dQ: 2.55) per 64 keys, 7 to 13 % less than these with the chip full, but do not split: with
+// workgroups for less than a round, or for little more than one, they leave compute units idle.  They also need the
+// page images (forward) or the row statistics (dQ) of a kernel before them.
+bool rows_take_generic(const Params& p, int32_t max_len, bool dq) {
+  const float r = row_tiles_per_head(p.C, p.G, p.m, p.qp) * p.Hkv / 256.f;
+  const float avg = 2.f * ((float)gn_list_len(p, max_len) - 0.5f * p.m);
+  const float before = dq ? 4.f + (float)p.C * p.Hq * 7e-5f : 5.f + (float)p.Hkv * max_len * 0.02f;
+  const float own = gn_rounds(r, 0.78f, 0.2f, 0.6f, 0.3f) * avg * (dq ? 2.55f : 2.0f) + ceilf(r) * 8.f + before;
+  return gn_plan(p, true, max_len, dq).us < 0.97f * own;
 }
 
 }  // namespace oomb

@@ -37,9 +37,13 @@ hipError_t launch_qp_prepare(Params& p, void* ws, hipStream_t st);
 // attn_generic.hip: fp32 tensors, head dim 64, pages of fewer than 128 tokens.  max_len: host-side bound of the
 // list length (of the union with one list per query page)
 size_t fwd_generic_workspace_bytes(const Params& p, bool is_bf16, int32_t max_len);
-hipError_t launch_fwd_generic(const Params& p, bool is_bf16, int32_t max_len, void* ws, size_t ws_bytes, hipStream_t st);
+hipError_t launch_fwd_generic(const Params& p, bool is_bf16, int32_t max_len, void* ws, size_t ws_bytes, const char* name, hipStream_t st);
 size_t bwd_generic_workspace_bytes(const Params& p, bool is_bf16, int32_t max_len);
 hipError_t launch_bwd_generic(const Params& p, bool is_bf16, int32_t max_len, void* ws, hipStream_t st);
+// the same forward and dQ kernels for shapes with kernels of their own but too few rows to fill the chip with them
+bool rows_take_generic(const Params& p, int32_t max_len, bool dq);
+size_t dq_generic_part_bytes(const Params& p, bool is_bf16, int32_t max_len);
+hipError_t launch_dq_generic_bf16_128(const Params& p, int32_t max_len, float* part, float* bias, int32_t n_stages, int32_t* splits, hipStream_t st);
 
 // kv_layout.hip: LDS-ordered images of the selected pages
 size_t kv_image_bytes(const Params& p, int32_t max_len);
@@ -53,8 +57,8 @@ size_t bwd_mfma_workspace_bytes(const Params& p, int32_t max_list_len);
 hipError_t launch_bwd_mfma(const Params& p, int32_t max_list_len, void* ws, hipStream_t st);
 size_t dkv_partial_bytes(const Params& p, int32_t max_len, int32_t n_split);
 int32_t dkv_splits(const Params& p, int32_t max_len);
-hipError_t launch_bwd_dkv_mfma(const Params& p, const float* bias, int32_t n_stages, int32_t max_len,
-                               float* partial_ws, hipStream_t st);
+hipError_t launch_bwd_dkv_mfma(const Params& p, const float* bias, int32_t n_stages, int32_t max_len, float* partial_ws, int32_t dq_split,
+                               const float* dq_part, hipStream_t st);
 
 // offload.hip: staging plan and transfers between pinned host pools and device staging pools
 void* device_view(const void* ptr);

@@ -186,6 +186,23 @@ RING_CASES = [
 ]
 
 
+# Rows split over workgroups (forward, dQ of bf16 pages of 128): one query page against many splits of two wave
+# groups, splits of a single tile, an uneven share, and a list shorter than its row (top_k beyond the history).
+SPLIT_CASES = [
+    Workload("bf16_split_pairs", 14, 2, 128, 128, 128, 128 * 40, 30, "bf16", "f32", 0.0884, boost_frac=0.1, seed=71),
+    Workload("bf16_split_tiles", 3, 1, 128, 128, 128, 128 * 4, 2, "bf16", "bf16", 0.0884, seed=72),
+    Workload("bf16_split_uneven", 10, 2, 128, 128, 384, 128 * 23, None, "bf16", "f32", 0.0884, seed=73),
+    Workload("bf16_split_short_list", 7, 1, 128, 128, 256, 128 * 5, 9, "bf16", "f32", 0.0884, seed=74),
+]
+
+
+@pytest.mark.parametrize("w", SPLIT_CASES, ids=lambda w: w.name)
+def test_mfma_bf16_split_rows(w):
+    with pu.kernels_ran(pu.MFMA_KERNELS):
+        rep = pu.full_parity(w, init_grad=0.25)
+    _show(w.name, rep)
+
+
 @pytest.mark.parametrize("w", RING_CASES, ids=lambda w: w.name)
 def test_mfma_bf16_stage_ring_edges(w):
     with pu.kernels_ran(pu.MFMA_KERNELS):

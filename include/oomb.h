@@ -51,7 +51,7 @@ typedef enum {
   OOMB_OK = 0,
   OOMB_ERR_INVALID_ARG = 1, /* NULL pointer, non-divisible sizes, bad stride/alignment */
   OOMB_ERR_UNSUPPORTED = 2, /* shape / dtype combination with no kernel */
-  OOMB_ERR_WORKSPACE = 3,   /* workspace NULL or smaller than oomb_workspace_bytes() */
+  OOMB_ERR_WORKSPACE = 3,   /* workspace NULL or too small (oomb_workspace_bytes() is always enough) */
   OOMB_ERR_LAUNCH = 4,      /* HIP reported a launch error */
   OOMB_ERR_OUT_OF_PAGES = 5, /* oomb_page_pool_alloc: fewer free pages than asked for */
   OOMB_ERR_SCRATCH_LIMIT = 6 /* oomb_page_score_topk_noalloc: the shape needs more than the built-in scratch */

@@ -72,14 +72,17 @@ oomb_status check_list(const Params& p, const int32_t* sel, const int32_t* cnt, 
 
 // One list per (KV head, query page): [maps derived from the lists][what the kernels need with the
 // union of a KV head's lists in the place of its list].  p.sel_stride is set here.
-size_t qp_workspace_bytes(Params p, int32_t stride, bool bf, bool bwd) {
+// least: what a call cannot do without (the rest lets short calls be split).
+size_t qp_workspace_bytes(Params p, int32_t stride, bool bf, bool bwd, bool least) {
   p.qp = 1;
   p.sel_stride = stride;
   const size_t maps = qp_maps_bytes(p, stride);
   const int32_t cap = qp_union_cap(p, stride);
   if (!force_generic() && mfma_supported(p, bf))
-    return maps + (bwd ? bwd_mfma_workspace_bytes(p, cap) : fwd_mfma_workspace_bytes(p, cap));
-  return maps + (bwd ? bwd_generic_workspace_bytes(p, bf, cap) : fwd_generic_workspace_bytes(p, bf, cap));
+    return maps + (least ? (bwd ? bwd_mfma_min_bytes(p, cap) : fwd_mfma_min_bytes(p, cap))
+                         : (bwd ? bwd_mfma_workspace_bytes(p, cap) : fwd_mfma_workspace_bytes(p, cap)));
+  return maps + (least ? (bwd ? bwd_generic_min_bytes(p) : 256)
+                       : (bwd ? bwd_generic_workspace_bytes(p, bf, cap) : fwd_generic_workspace_bytes(p, bf, cap)));
 }
 
 oomb_status check_qp_list(const Params& p, const int32_t* sel, const int32_t* cnt, int32_t stride) {
@@ -125,7 +128,7 @@ size_t oomb_workspace_bytes(const oomb_attn_desc* desc, int32_t top_k, int32_t o
       if (top_k < 0) return 0;
       const int64_t stride = (int64_t)top_k + p.m;
       if (stride * p.m > INT32_MAX) return 0;
-      return qp_workspace_bytes(p, (int32_t)stride, desc->dtype == OOMB_BF16, op == OOMB_OP_ATTN_BWD_QP);
+      return qp_workspace_bytes(p, (int32_t)stride, desc->dtype == OOMB_BF16, op == OOMB_OP_ATTN_BWD_QP, false);
     }
     default:
       return 0;
@@ -142,10 +145,10 @@ oomb_status oomb_page_score_topk(const oomb_attn_desc* desc, const void* q, cons
   if (!q || !k_pool || !page_table || !sel_pages || !sel_count || top_k < 0) return OOMB_ERR_INVALID_ARG;
   if (!aligned16(q) || !aligned16(k_pool)) return OOMB_ERR_INVALID_ARG;
   if (p.n_past > (1 << 20)) return OOMB_ERR_UNSUPPORTED;
-  if (!workspace || workspace_bytes < score_workspace_bytes(p)) return OOMB_ERR_WORKSPACE;
+  if (!workspace || workspace_bytes < score_workspace_min_bytes(p)) return OOMB_ERR_WORKSPACE;
   p.q = q; p.k_pool = k_pool; p.page_table = page_table;
   hipError_t e = launch_score_topk(p, desc->dtype == OOMB_BF16, top_k, sel_pages, sel_count, scores_out,
-                                   workspace, nullptr, (hipStream_t)hip_stream);
+                                   workspace, workspace_bytes, nullptr, (hipStream_t)hip_stream);
   return e == hipSuccess ? OOMB_OK : OOMB_ERR_LAUNCH;
 }
 
@@ -158,12 +161,12 @@ oomb_status oomb_page_score_topk_noalloc(const oomb_attn_desc* desc, const void*
   if (!q || !k_pool || !page_table || !sel_pages || !sel_count || top_k < 0) return OOMB_ERR_INVALID_ARG;
   if (!aligned16(q) || !aligned16(k_pool)) return OOMB_ERR_INVALID_ARG;
   if (p.n_past > (1 << 20)) return OOMB_ERR_UNSUPPORTED;
-  if (score_workspace_bytes(p) > (size_t)OOMB_NOALLOC_SCRATCH_BYTES) return OOMB_ERR_SCRATCH_LIMIT;
+  if (score_workspace_min_bytes(p) > (size_t)OOMB_NOALLOC_SCRATCH_BYTES) return OOMB_ERR_SCRATCH_LIMIT;
   void* ws = nullptr;
   if (score_scratch_ptr(&ws) != hipSuccess) return OOMB_ERR_LAUNCH;
   p.q = q; p.k_pool = k_pool; p.page_table = page_table;
-  hipError_t e = launch_score_topk(p, desc->dtype == OOMB_BF16, top_k, sel_pages, sel_count, scores_out, ws, nullptr,
-                                   (hipStream_t)hip_stream);
+  hipError_t e = launch_score_topk(p, desc->dtype == OOMB_BF16, top_k, sel_pages, sel_count, scores_out, ws,
+                                   OOMB_NOALLOC_SCRATCH_BYTES, nullptr, (hipStream_t)hip_stream);
   return e == hipSuccess ? OOMB_OK : OOMB_ERR_LAUNCH;
 }
 
@@ -176,10 +179,10 @@ oomb_status oomb_page_score_topk_cached(const oomb_attn_desc* desc, const void* 
   if (!q || !kbar_cache || !sel_pages || !sel_count || top_k < 0) return OOMB_ERR_INVALID_ARG;
   if (!aligned16(q) || !aligned16(kbar_cache)) return OOMB_ERR_INVALID_ARG;
   if (p.n_past > (1 << 20)) return OOMB_ERR_UNSUPPORTED;
-  if (!workspace || workspace_bytes < score_workspace_bytes(p)) return OOMB_ERR_WORKSPACE;
+  if (!workspace || workspace_bytes < score_workspace_min_bytes(p)) return OOMB_ERR_WORKSPACE;
   p.q = q;
   hipError_t e = launch_score_topk(p, desc->dtype == OOMB_BF16, top_k, sel_pages, sel_count, scores_out,
-                                   workspace, kbar_cache, (hipStream_t)hip_stream);
+                                   workspace, workspace_bytes, kbar_cache, (hipStream_t)hip_stream);
   return e == hipSuccess ? OOMB_OK : OOMB_ERR_LAUNCH;
 }
 
@@ -243,9 +246,9 @@ oomb_status oomb_paged_attn_fwd(const oomb_attn_desc* desc, const void* q, const
   const bool bf = desc->dtype == OOMB_BF16;
   hipError_t e;
   if (!force_generic() && mfma_supported(p, bf)) {
-    if (!workspace || workspace_bytes < fwd_mfma_workspace_bytes(p, max_len) || !aligned16(workspace))
+    if (!workspace || workspace_bytes < fwd_mfma_min_bytes(p, max_len) || !aligned16(workspace))
       return OOMB_ERR_WORKSPACE;
-    e = launch_fwd_mfma(p, max_len, workspace, (hipStream_t)hip_stream);
+    e = launch_fwd_mfma(p, max_len, workspace, workspace_bytes, (hipStream_t)hip_stream);
   } else {
     e = launch_fwd_generic(p, bf, max_len, workspace, aligned16(workspace) ? workspace_bytes : 0, "attn_fwd_generic",
                            (hipStream_t)hip_stream);
@@ -272,7 +275,7 @@ oomb_status oomb_paged_attn_bwd(const oomb_attn_desc* desc, const void* q, const
   if (s != OOMB_OK) return s;
   const bool bf = desc->dtype == OOMB_BF16;
   const bool use_mfma = !force_generic() && mfma_supported(p, bf);
-  const size_t need = use_mfma ? bwd_mfma_workspace_bytes(p, max_len) : bwd_generic_workspace_bytes(p, bf, max_len);
+  const size_t need = use_mfma ? bwd_mfma_min_bytes(p, max_len) : bwd_generic_min_bytes(p);
   if (!workspace || workspace_bytes < need || !aligned16(workspace)) return OOMB_ERR_WORKSPACE;
   p.q = q; p.k_pool = k_pool; p.v_pool = v_pool; p.page_table = page_table;
   p.sel = sel_pages; p.sel_count = sel_count; p.sel_stride = sel_stride;
@@ -281,9 +284,9 @@ oomb_status oomb_paged_attn_bwd(const oomb_attn_desc* desc, const void* q, const
   hipStream_t st = (hipStream_t)hip_stream;
   hipError_t e;
   if (use_mfma) {
-    e = launch_bwd_mfma(p, max_len, workspace, st);
+    e = launch_bwd_mfma(p, max_len, workspace, workspace_bytes, st);
   } else {
-    e = launch_bwd_generic(p, bf, max_len, workspace, st);
+    e = launch_bwd_generic(p, bf, max_len, workspace, workspace_bytes, st);
   }
   return e == hipSuccess ? OOMB_OK : OOMB_ERR_LAUNCH;
 }
@@ -319,7 +322,7 @@ oomb_status oomb_paged_attn_fwd_qp(const oomb_attn_desc* desc, const void* q, co
   s = check_qp_list(p, sel_pages, sel_count, sel_stride);
   if (s != OOMB_OK) return s;
   const bool bf = desc->dtype == OOMB_BF16;
-  if (!workspace || workspace_bytes < qp_workspace_bytes(p, sel_stride, bf, false) || !aligned16(workspace))
+  if (!workspace || workspace_bytes < qp_workspace_bytes(p, sel_stride, bf, false, true) || !aligned16(workspace))
     return OOMB_ERR_WORKSPACE;
   p.q = q; p.k_pool = k_pool; p.v_pool = v_pool; p.page_table = page_table;
   p.sel = sel_pages; p.sel_count = sel_count; p.sel_stride = sel_stride;
@@ -332,7 +335,8 @@ oomb_status oomb_paged_attn_fwd_qp(const oomb_attn_desc* desc, const void* q, co
       e = launch_qp_prepare(p, workspace, st);
       if (e != hipSuccess) return OOMB_ERR_LAUNCH;
     }
-    e = launch_fwd_mfma(p, qp_union_cap(p, sel_stride), (unsigned char*)workspace + qp_maps_bytes(p, sel_stride), st);
+    const size_t maps = qp_maps_bytes(p, sel_stride);
+    e = launch_fwd_mfma(p, qp_union_cap(p, sel_stride), (unsigned char*)workspace + maps, workspace_bytes - maps, st);
   } else {
     const size_t maps = qp_maps_bytes(p, sel_stride);
     e = launch_fwd_generic(p, bf, qp_union_cap(p, sel_stride), (unsigned char*)workspace + maps, workspace_bytes - maps,
@@ -362,7 +366,7 @@ oomb_status oomb_paged_attn_bwd_qp(const oomb_attn_desc* desc, const void* q, co
   // (the cut pages of the slice reduction are a grid dimension of at most 65535)
   if (p.Hkv > 65535 || (use_mfma && qp_max_multi(p, sel_stride) > 65535))
     return OOMB_ERR_UNSUPPORTED;
-  if (!workspace || workspace_bytes < qp_workspace_bytes(p, sel_stride, bf, true) || !aligned16(workspace))
+  if (!workspace || workspace_bytes < qp_workspace_bytes(p, sel_stride, bf, true, true) || !aligned16(workspace))
     return OOMB_ERR_WORKSPACE;
   p.q = q; p.k_pool = k_pool; p.v_pool = v_pool; p.page_table = page_table;
   p.sel = sel_pages; p.sel_count = sel_count; p.sel_stride = sel_stride;
@@ -373,10 +377,11 @@ oomb_status oomb_paged_attn_bwd_qp(const oomb_attn_desc* desc, const void* q, co
   if (e != hipSuccess) return OOMB_ERR_LAUNCH;
   unsigned char* rest = (unsigned char*)workspace + qp_maps_bytes(p, sel_stride);
   const int32_t cap = qp_union_cap(p, sel_stride);
+  const size_t rest_bytes = workspace_bytes - qp_maps_bytes(p, sel_stride);
   if (use_mfma) {
-    e = launch_bwd_mfma(p, cap, rest, st);
+    e = launch_bwd_mfma(p, cap, rest, rest_bytes, st);
   } else {
-    e = launch_bwd_generic(p, bf, cap, rest, st);
+    e = launch_bwd_generic(p, bf, cap, rest, rest_bytes, st);
   }
   return e == hipSuccess ? OOMB_OK : OOMB_ERR_LAUNCH;
 }

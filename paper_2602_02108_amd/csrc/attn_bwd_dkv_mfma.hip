@@ -411,24 +411,24 @@ size_t dkv_partial_bytes(const Params& p, int32_t max_len, int32_t n_split) {
 // Slices per page: enough units (about 8 rounds of 256 workgroups) for the tail of the last
 // round to be short, without making the second-stage reduction large; more than four slices only where
 // four leave compute units idle, and then not below two stages each.
-int32_t dkv_splits(const Params& p, int32_t max_len) {
+int32_t dkv_splits(const Params& p, int32_t max_len, bool few) {
   const int64_t units = (int64_t)p.Hkv * max_len;
   if (units <= 0) return 1;
   const int64_t want = (2048 + units - 1) / units;
-  if (want <= 4) return (int32_t)(want < 1 ? 1 : want);
+  if (want <= 4 || !few) return (int32_t)(want < 1 ? 1 : want > 4 ? 4 : want);
   const int64_t fill = 256 / units, most = (p.C / 32) * p.G / 4;
   const int64_t s = fill < most ? fill : most;
   return (int32_t)(s < 4 ? 4 : s > 16 ? 16 : s);
 }
 
 // dq_split > 1: the last launch also adds the dQ partials
-hipError_t launch_bwd_dkv_mfma(const Params& p, const float* bias, int32_t n_stages, int32_t max_len, float* partial_ws, int32_t dq_split,
-                               const float* dq_part, hipStream_t st) {
+hipError_t launch_bwd_dkv_mfma(const Params& p, const float* bias, int32_t n_stages, int32_t max_len, int32_t n_split, float* partial_ws,
+                               int32_t dq_split, const float* dq_part, hipStream_t st) {
   static DeviceOnce lds_once_f32, lds_once_bf16;
   if (hipError_t e = ensure_max_dynamic_lds(lds_once_f32, (const void*)bwd_dkv_kernel<float>, KV_LDS); e != hipSuccess) return e;
   if (hipError_t e = ensure_max_dynamic_lds(lds_once_bf16, (const void*)bwd_dkv_kernel<bf16_t>, KV_LDS); e != hipSuccess) return e;
   // (one list per query page: the units come from the device-built table; the grid covers its capacity)
-  const int32_t n_split = p.qp ? 1 : dkv_splits(p, max_len);
+  if (p.qp) n_split = 1;
   float* partial = (p.qp || n_split > 1) ? partial_ws : nullptr;
   const int xcd_map = (p.Hkv <= 8 && 8 % p.Hkv == 0) ? 1 : 0;
   const int per = xcd_map ? 8 / p.Hkv : 1;

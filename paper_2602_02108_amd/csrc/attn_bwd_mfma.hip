@@ -290,20 +290,30 @@ static inline size_t stats_bytes(const Params& p) {
 static inline int32_t row_stages(const Params& p) { return (p.C / 32) * p.G / 2; }   // 64-row stages of the dK/dV kernel
 static inline size_t bias_bytes(const Params& p) { return (size_t)p.Hkv * (size_t)row_stages(p) * 512; }
 
+// [row statistics, or the dQ partials of the split kernel][bias words][dK / dV slices]
+size_t bwd_mfma_min_bytes(const Params& p, int32_t max_list_len) {
+  return stats_bytes(p) + bias_bytes(p) + dkv_partial_bytes(p, max_list_len, dkv_splits(p, max_list_len, false));
+}
 size_t bwd_mfma_workspace_bytes(const Params& p, int32_t max_list_len) {
-  return (rows_take_generic(p, max_list_len, true) ? dq_generic_part_bytes(p, true, max_list_len) : stats_bytes(p)) + bias_bytes(p) + dkv_partial_bytes(p, max_list_len, dkv_splits(p, max_list_len));
+  const size_t rows = rows_take_generic(p, max_list_len, true) ? dq_generic_part_bytes(p, true, max_list_len) : 0, stats = stats_bytes(p);
+  return (rows > stats ? rows : stats) + bias_bytes(p) + dkv_partial_bytes(p, max_list_len, dkv_splits(p, max_list_len, true));
 }
 
-hipError_t launch_bwd_mfma(const Params& p, int32_t max_list_len, void* ws, hipStream_t st) {
+hipError_t launch_bwd_mfma(const Params& p, int32_t max_list_len, void* ws, size_t ws_bytes, hipStream_t st) {
+  // (a workspace sized for another list length may have room for fewer slices or dQ partials)
+  int32_t n_split = dkv_splits(p, max_list_len, true);
+  if (stats_bytes(p) + bias_bytes(p) + dkv_partial_bytes(p, max_list_len, n_split) > ws_bytes) n_split = dkv_splits(p, max_list_len, false);
+  const size_t first = ws_bytes - bias_bytes(p) - dkv_partial_bytes(p, max_list_len, n_split);   // at least stats_bytes
   if (rows_take_generic(p, max_list_len, true)) {   // dQ (with the bias words) by the split kernel
+    const size_t want = dq_generic_part_bytes(p, true, max_list_len), have = (want < first ? want : first) & ~(size_t)255;
     float* dq_part = (float*)ws;
-    float* bias = (float*)((unsigned char*)ws + dq_generic_part_bytes(p, true, max_list_len));
+    float* bias = (float*)((unsigned char*)ws + have);
     int32_t splits = 1;
     {
       ProfScope prof_("bwd_dq_mfma", st);
-      if (hipError_t e = launch_dq_generic_bf16_128(p, max_list_len, dq_part, bias, row_stages(p), &splits, st); e != hipSuccess) return e;
+      if (hipError_t e = launch_dq_generic_bf16_128(p, max_list_len, dq_part, have, bias, row_stages(p), &splits, st); e != hipSuccess) return e;
     }
-    return launch_bwd_dkv_mfma(p, bias, row_stages(p), max_list_len, (float*)((unsigned char*)bias + bias_bytes(p)), splits, dq_part, st);
+    return launch_bwd_dkv_mfma(p, bias, row_stages(p), max_list_len, n_split, (float*)((unsigned char*)bias + bias_bytes(p)), splits, dq_part, st);
   }
   static DeviceOnce lds_once;
   if (hipError_t e = ensure_max_dynamic_lds(lds_once, (const void*)bwd_dq_kernel, DQ_LDS); e != hipSuccess) return e;
@@ -327,7 +337,7 @@ hipError_t launch_bwd_mfma(const Params& p, int32_t max_list_len, void* ws, hipS
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  return launch_bwd_dkv_mfma(p, bias, row_stages(p), max_list_len, (float*)((unsigned char*)bias + bias_bytes(p)), 1, nullptr, st);
+  return launch_bwd_dkv_mfma(p, bias, row_stages(p), max_list_len, n_split, (float*)((unsigned char*)bias + bias_bytes(p)), 1, nullptr, st);
 }
 
 }  // namespace oomb

@@ -322,15 +322,15 @@ bool mfma_supported(const Params& p, bool is_bf16) {
   return is_bf16 && p.D == HD && p.P == TP && p.pool_tok_stride <= (1 << 20) && p.q_tok_stride <= (1 << 20);
 }
 
+size_t fwd_mfma_min_bytes(const Params& p, int32_t max_list_len) { return kv_image_bytes(p, max_list_len); }
 size_t fwd_mfma_workspace_bytes(const Params& p, int32_t max_list_len) {
   const size_t images = kv_image_bytes(p, max_list_len);
   const size_t split = rows_take_generic(p, max_list_len, false) ? fwd_generic_workspace_bytes(p, true, max_list_len) : 0;
   return split > images ? split : images;
 }
 
-hipError_t launch_fwd_mfma(const Params& p, int32_t max_list_len, void* ws, hipStream_t st) {
-  if (rows_take_generic(p, max_list_len, false))
-    return launch_fwd_generic(p, true, max_list_len, ws, fwd_generic_workspace_bytes(p, true, max_list_len), "attn_fwd_mfma", st);
+hipError_t launch_fwd_mfma(const Params& p, int32_t max_list_len, void* ws, size_t ws_bytes, hipStream_t st) {
+  if (rows_take_generic(p, max_list_len, false)) return launch_fwd_generic(p, true, max_list_len, ws, ws_bytes, "attn_fwd_mfma", st);
   static DeviceOnce lds_once;
   if (hipError_t e = ensure_max_dynamic_lds(lds_once, (const void*)fwd_mfma_kernel, FW_LDS); e != hipSuccess) return e;
   const int tiles = row_tiles_per_head(p.C, p.G, p.m, p.qp);

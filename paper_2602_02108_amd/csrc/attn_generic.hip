@@ -459,54 +459,126 @@ __global__ __launch_bounds__(256 * KH, 2) void fwd_generic_kernel(Params p, int3
   }
 }
 
-// A lane of a combine kernel: thread (row tile, block, group of four dims, lane) -> its row and dims
-template <typename T, int D> struct GnOut {
-  int64_t block;
-  int k, lane, d, i, h;
-  bool ok;
-  __device__ __forceinline__ GnOut(const Params& p, int32_t tiles, int64_t idx) {
-    lane = (int)(idx & 63);
-    k = (int)(idx >> 6) % (D / 8);
-    block = (idx >> 6) / (D / 8);
-    d = part_group_dim<T, D>(k, lane >> 5);
-    const int64_t tg = block >> 2;
-    const int32_t g = (int32_t)(tg / tiles), tile = (int32_t)(tg - (int64_t)g * tiles);
-    int32_t r = ((int32_t)block & 3) * 32 + (lane & 31), end;
-    if (!p.qp) {
-      r += tile * GN_ROWS;
-      end = p.C * p.G;
-    } else {
-      const int32_t rpq = p.P * p.G, tpq = (rpq + GN_ROWS - 1) / GN_ROWS, tau = tile / tpq;
-      r += tau * rpq + (tile - tau * tpq) * GN_ROWS;
-      end = (tau + 1) * rpq;
-    }
-    ok = g < p.Hkv && r < end;
-    i = (int)div_g(p, (uint32_t)(ok ? r : 0));
-    h = g * p.G + (r - i * p.G);
+// Combine kernels: a workgroup takes a block of 32 rows, wave w the groups w, w + 4, ..  The sums go through LDS, so that the
+// results leave in whole rows instead of the register order of the partials.
+template <int D> constexpr int GN_GW = D / 32;   // groups per wave
+// in: the sums of this thread's groups; then f(k, row, dim, value) for the row pieces this thread writes, piece k = float4
+// k * 256 + thread of the block
+template <typename T, int D, typename F> __device__ __forceinline__ void gn_rows_out(float4 (&sh)[8 * D], const float4 (&v)[GN_GW<D>], F&& f) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, r = lane & 31;
+  constexpr int GPR = D / 4;   // float4s per row
+#pragma unroll
+  for (int j = 0; j < GN_GW<D>; ++j) sh[r * GPR + ((part_group_dim<T, D>(wave + 4 * j, lane >> 5) >> 2) ^ (r & 15))] = v[j];
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < GN_GW<D>; ++k) {
+    const int e = k * 256 + threadIdx.x, row = e / GPR, c = e % GPR;
+    f(k, row, 4 * c, sh[row * GPR + (c ^ (row & 15))]);
   }
-};
+}
+// row `row` of a block -> chunk token and query head; false past the last row
+__device__ __forceinline__ bool gn_out_row(const Params& p, int32_t tiles, int64_t block, int row, int& i, int& h) {
+  const int64_t tg = block >> 2;
+  const int32_t g = (int32_t)(tg / tiles), tile = (int32_t)(tg - (int64_t)g * tiles);
+  int32_t r = ((int32_t)block & 3) * 32 + row, end;
+  if (!p.qp) {
+    r += tile * GN_ROWS;
+    end = p.C * p.G;
+  } else {
+    const int32_t rpq = p.P * p.G, tpq = (rpq + GN_ROWS - 1) / GN_ROWS, tau = tile / tpq;
+    r += tau * rpq + (tile - tau * tpq) * GN_ROWS;
+    end = (tau + 1) * rpq;
+  }
+  if (r >= end) return false;
+  i = (int)div_g(p, (uint32_t)r);
+  h = g * p.G + (r - i * p.G);
+  return true;
+}
+__device__ __forceinline__ float4 gn_load_part(const float* part, int64_t at) {
+  typedef float f32x4_t __attribute__((ext_vector_type(4)));   // (read once: non-temporal, so that they push nothing else out of the caches)
+  const f32x4_t v = __builtin_nontemporal_load(reinterpret_cast<const f32x4_t*>(part) + at);
+  return make_float4(v.x, v.y, v.z, v.w);
+}
+// sums of n partials `step` float4s apart for the thread's groups of a block, at most four of each in flight, added in order
+// `meanwhile` runs once, while the first of them are on their way.
+template <int D, int N, typename F>
+__device__ __forceinline__ void gn_add_parts(const float* part, int64_t at, int64_t step, float4 (&a)[GN_GW<D>], F&& meanwhile) {
+  float4 v[GN_GW<D>][N];
+#pragma unroll
+  for (int u = 0; u < N; ++u)
+#pragma unroll
+    for (int j = 0; j < GN_GW<D>; ++j) v[j][u] = gn_load_part(part, at + j * 256 + u * step);
+  __builtin_amdgcn_sched_barrier(0);
+  meanwhile();
+#pragma unroll
+  for (int u = 0; u < N; ++u)
+#pragma unroll
+    for (int j = 0; j < GN_GW<D>; ++j) { a[j].x += v[j][u].x; a[j].y += v[j][u].y; a[j].z += v[j][u].z; a[j].w += v[j][u].w; }
+}
+template <int D, typename F>
+__device__ __forceinline__ void gn_sum_parts(const float* part, int64_t block, int64_t step, int n, float4 (&a)[GN_GW<D>], F&& meanwhile) {
+  int64_t at = (block * (D / 8) + (threadIdx.x >> 6)) * 64 + (threadIdx.x & 63);
+#pragma unroll
+  for (int j = 0; j < GN_GW<D>; ++j) a[j] = make_float4(0.f, 0.f, 0.f, 0.f);
+  auto nothing = [] {};
+  const int first = n & 3;   // (the odd ones first)
+  if (first == 3) gn_add_parts<D, 3>(part, at, step, a, meanwhile);
+  else if (first == 2) gn_add_parts<D, 2>(part, at, step, a, meanwhile);
+  else if (first == 1) gn_add_parts<D, 1>(part, at, step, a, meanwhile);
+  else gn_add_parts<D, 4>(part, at, step, a, meanwhile);
+  for (int done = first ? first : 4; done < n; done += 4) gn_add_parts<D, 4>(part, at + done * step, step, a, nothing);
+}
 
 // O = sum of the splits' O rescaled to the common maximum / sum of their l
 template <typename T, int D>
 __global__ __launch_bounds__(256) void fwd_combine_kernel(Params p, int32_t tiles, int32_t n_split, const float* __restrict__ part,
                                                           const float2* __restrict__ part_ml) {
-  const GnOut<T, D> o(p, tiles, (int64_t)blockIdx.x * 256 + threadIdx.x);
-  if (!o.ok) return;
-  const int64_t blocks = (int64_t)p.Hkv * tiles * 4;
-  float M = -INFINITY;
-  for (int s = 0; s < n_split; ++s) M = fmaxf(M, part_ml[(s * blocks + o.block) * 32 + (o.lane & 31)].x);
-  float L = 0.f;
-  float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-  for (int s = 0; s < n_split; ++s) {
-    const float2 ml = part_ml[(s * blocks + o.block) * 32 + (o.lane & 31)];
-    const float w = __builtin_amdgcn_exp2f(ml.x - M);
-    const float4 v = reinterpret_cast<const float4*>(part)[((s * blocks + o.block) * (D / 8) + o.k) * 64 + o.lane];
-    L += ml.y * w;
-    acc.x += v.x * w; acc.y += v.y * w; acc.z += v.z * w; acc.w += v.w * w;
+  __shared__ float4 sh[8 * D];
+  constexpr int GW = GN_GW<D>;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int64_t block = blockIdx.x, blocks = (int64_t)p.Hkv * tiles * 4;
+  const int64_t at = (block * (D / 8) + wave) * 64 + lane;
+  float M = -1e38f, L = 0.f;   // (a split that saw nothing of the row holds -inf and 0)
+  float4 acc[GW];
+#pragma unroll
+  for (int j = 0; j < GW; ++j) acc[j] = make_float4(0.f, 0.f, 0.f, 0.f);
+  for (int s0 = 0; s0 < n_split; s0 += 4) {   // four splits in flight
+    float2 ml[4];
+    float4 v[GW][4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      ml[u] = make_float2(-INFINITY, 0.f);
+      if (s0 + u < n_split) {
+        ml[u] = part_ml[((s0 + u) * blocks + block) * 32 + (lane & 31)];
+#pragma unroll
+        for (int j = 0; j < GW; ++j) v[j][u] = gn_load_part(part, at + j * 256 + (s0 + u) * blocks * (D / 8) * 64);
+      }
+    }
+    const float m_new = fmaxf(fmaxf(fmaxf(ml[0].x, ml[1].x), fmaxf(ml[2].x, ml[3].x)), M);
+    const float w0 = __builtin_amdgcn_exp2f(M - m_new);
+    M = m_new;
+    L *= w0;
+#pragma unroll
+    for (int j = 0; j < GW; ++j) { acc[j].x *= w0; acc[j].y *= w0; acc[j].z *= w0; acc[j].w *= w0; }
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      if (s0 + u < n_split) {
+        const float w = __builtin_amdgcn_exp2f(ml[u].x - m_new);
+        L += ml[u].y * w;
+#pragma unroll
+        for (int j = 0; j < GW; ++j) { acc[j].x += v[j][u].x * w; acc[j].y += v[j][u].y * w; acc[j].z += v[j][u].z * w; acc[j].w += v[j][u].w * w; }
+      }
   }
   const float inv = 1.f / L;
-  part_store4<T>((T*)p.o + (int64_t)o.i * p.q_tok_stride + (int64_t)o.h * p.q_head_stride + o.d, acc.x * inv, acc.y * inv, acc.z * inv, acc.w * inv);
-  if (o.d == 0) p.lse[(int64_t)o.h * p.C + o.i] = (M + __builtin_amdgcn_logf(L)) * 0.6931471805599453f;
+#pragma unroll
+  for (int j = 0; j < GW; ++j) { acc[j].x *= inv; acc[j].y *= inv; acc[j].z *= inv; acc[j].w *= inv; }
+  int i, h;
+  gn_rows_out<T, D>(sh, acc, [&](int, int row, int d, const float4& r) __attribute__((always_inline)) {
+    if (gn_out_row(p, tiles, block, row, i, h))
+      part_store4<T>((T*)p.o + (int64_t)i * p.q_tok_stride + (int64_t)h * p.q_head_stride + d, r.x, r.y, r.z, r.w);
+  });
+  if (threadIdx.x < 32 && gn_out_row(p, tiles, block, threadIdx.x, i, h))
+    p.lse[(int64_t)h * p.C + i] = (M + __builtin_amdgcn_logf(L)) * 0.6931471805599453f;
 }
 
 // ---- dQ -----------------------------------------------------------------------------------------
@@ -823,47 +895,56 @@ __global__ __launch_bounds__(256, (D == 128 || sizeof(T) == 4 ? 1 : 2)) void dkv
 template <typename T, typename TG, int D>
 __global__ __launch_bounds__(256) void bwd_finish_kernel(Params p, int32_t tiles, int32_t dq_split, const float* __restrict__ dq_part,
                                                          int32_t dq_blocks, int32_t kv_split, const float* __restrict__ kv_part, int lp) {
-  constexpr int BPU = 2 * 4 * (D / 8) * 64 / 256;   // workgroups per unit
+  __shared__ float4 sh[8 * D];
+  float4 a[GN_GW<D>];
   if ((int32_t)blockIdx.x < dq_blocks) {
-    const GnOut<T, D> o(p, tiles, (int64_t)blockIdx.x * 256 + threadIdx.x);
-    if (!o.ok) return;
     const int64_t blocks = (int64_t)p.Hkv * tiles * 4;
-    float4 a = make_float4(0.f, 0.f, 0.f, 0.f);
-    for (int s = 0; s < dq_split; ++s) {
-      const float4 v = reinterpret_cast<const float4*>(dq_part)[((s * blocks + o.block) * (D / 8) + o.k) * 64 + o.lane];
-      a.x += v.x; a.y += v.y; a.z += v.z; a.w += v.w;
-    }
+    gn_sum_parts<D>(dq_part, blockIdx.x, blocks * (D / 8) * 64, dq_split, a, [] {});
     const float sc = p.sm_scale;
-    part_store4<T>((T*)p.d_q + (int64_t)o.i * p.q_tok_stride + (int64_t)o.h * p.q_head_stride + o.d, a.x * sc, a.y * sc, a.z * sc, a.w * sc);
+    gn_rows_out<T, D>(sh, a, [&](int, int row, int d, const float4& r) __attribute__((always_inline)) {
+      int i, h;
+      if (gn_out_row(p, tiles, blockIdx.x, row, i, h))
+        part_store4<T>((T*)p.d_q + (int64_t)i * p.q_tok_stride + (int64_t)h * p.q_head_stride + d, r.x * sc, r.y * sc, r.z * sc, r.w * sc);
+    });
     return;
   }
-  const int32_t b = (int32_t)blockIdx.x - dq_blocks, ug = b / BPU, u = ug / p.Hkv, g = ug - u * p.Hkv;
-  const int idx = (b - ug * BPU) * 256 + threadIdx.x, lane = idx & 63, k = (idx >> 6) % (D / 8), wb = (idx >> 6) / (D / 8);   // wb: 4 which + wave
-  const int which = wb >> 2, kq = 32 * (wb & 3) + (lane & 31);
+  // (last units first: their slices were written last and are still in the memory-side cache)
+  const int32_t b = (int32_t)(gridDim.x - 1 - blockIdx.x), ug = b >> 3, u = ug / p.Hkv, g = ug - u * p.Hkv;
+  const int wb = b & 7, which = wb >> 2;   // {dK, dV}, wave
   int64_t slot, next;
-  int32_t e;
+  int32_t e0;
   if (p.qp) {
-    if (u >= p.multi_count[g] || kq >= p.P) return;
-    e = p.multi_list[(int64_t)g * p.max_multi + u];
-    kv_split = p.un_ns[(int64_t)g * p.un_stride + e];
-    slot = p.un_pbase[(int64_t)g * p.un_stride + e];
+    if (u >= p.multi_count[g] || 32 * (wb & 3) >= p.P) return;
+    e0 = p.multi_list[(int64_t)g * p.max_multi + u];
+    kv_split = p.un_ns[(int64_t)g * p.un_stride + e0];
+    slot = p.un_pbase[(int64_t)g * p.un_stride + e0];
     next = 1;
   } else {
-    e = (u << (7 - lp)) + (kq >> lp);
-    if (e >= list_len(p, g)) return;
+    e0 = (u << (7 - lp)) + (32 * (wb & 3) >> lp);
+    if (e0 >= list_len(p, g)) return;
     slot = ((int64_t)u * kv_split) * p.Hkv + g;
     next = p.Hkv;
   }
-  const int64_t l = owned_at(p, g, e);
-  float4 a = make_float4(0.f, 0.f, 0.f, 0.f);
-  for (int s = 0; s < kv_split; ++s) {   // (read once: non-temporal, so that they push nothing else out of the caches)
-    typedef float f32x4_t __attribute__((ext_vector_type(4)));
-    const f32x4_t v = __builtin_nontemporal_load(reinterpret_cast<const f32x4_t*>(kv_part) + (((slot + s * next) * 8 + wb) * (D / 8) + k) * 64 + lane);
-    a.x += v.x; a.y += v.y; a.z += v.z; a.w += v.w;
-  }
-  TG* pool = (TG*)(which == 0 ? p.dk_pool : p.dv_pool) + (int64_t)p.page_table[l] * p.pool_page_stride + (int64_t)g * p.pool_head_stride +
-             (int64_t)(kq & (p.P - 1)) * p.pool_tok_stride + part_group_dim<T, D>(k, lane >> 5);
-  part_add4<TG>(pool, a.x, a.y, a.z, a.w);
+  // The block's 32 keys lie in one page, or in two of 16 tokens.  Its rows of the pool are looked up and read behind the loads
+  // of the slices: in front of them the chain list -> page table -> pool would hold those back.
+  TG* dst[GN_GW<D>];
+  float4 old[GN_GW<D>];
+  gn_sum_parts<D>(kv_part, slot * 8 + wb, next * 8 * (D / 8) * 64, kv_split, a, [&]() __attribute__((always_inline)) {
+    TG* const pool = (TG*)(which == 0 ? p.dk_pool : p.dv_pool) + (int64_t)g * p.pool_head_stride;
+    const bool two = lp == 4 && !p.qp && e0 + 1 < list_len(p, g);
+    TG* const page0 = pool + (int64_t)p.page_table[owned_at(p, g, e0)] * p.pool_page_stride;
+    TG* const page1 = two ? pool + (int64_t)p.page_table[owned_at(p, g, e0 + 1)] * p.pool_page_stride : nullptr;
+#pragma unroll
+    for (int k = 0; k < GN_GW<D>; ++k) {
+      const int x = k * 256 + threadIdx.x, kq = 32 * (wb & 3) + x / (D / 4);
+      TG* const page = lp == 4 && (kq & 16) ? page1 : page0;
+      dst[k] = page ? page + (int64_t)(kq & (p.P - 1)) * p.pool_tok_stride + 4 * (x % (D / 4)) : nullptr;
+      if (page) old[k] = part_load4<TG>(dst[k]);
+    }
+  });
+  gn_rows_out<T, D>(sh, a, [&](int k, int, int, const float4& r) __attribute__((always_inline)) {
+    if (dst[k]) part_store4<TG>(dst[k], old[k].x + r.x, old[k].y + r.y, old[k].z + r.z, old[k].w + r.w);
+  });
 }
 
 // ---- host side ----------------------------------------------------------------------------------
@@ -885,7 +966,7 @@ static float gn_rounds(float r, float only0, float only1, float rest0, float res
   const float full = floorf(r), f = r - full;
   return full + (f <= 0.f ? 0.f : full > 0.f ? rest0 + rest1 * f : only0 + only1 * f);
 }
-static GnPlan gn_plan(const Params& p, bool bf, int32_t max_len, bool dq) {
+static GnPlan gn_plan(const Params& p, bool bf, int32_t max_len, bool dq, int32_t most = 32) {   // most: splits the workspace has room for
   constexpr float RAMP = 6.f, LAUNCH = 3.f, PART = 2.56e-4f;
   const float ds = (p.D == 128 ? 1.f : bf ? 0.65f : 0.5f) * (dq ? 1.4f : 1.f);
   const float unit1 = (bf ? 2.15f : 7.8f) * ds, unit2 = (bf ? 1.17f : 4.0f) * ds;   // (fp32: what its matrix pipe needs)
@@ -894,7 +975,7 @@ static GnPlan gn_plan(const Params& p, bool bf, int32_t max_len, bool dq) {
   const float all = len * p.P / kt, avg = (len - 0.5f * p.m) * p.P / kt;   // tiles of the longest row, of an average one
   const bool pairs = bf || !dq || p.D == 64;   // (fp32 dQ at head dim 128 holds 320 registers: one wave per SIMD)
   GnPlan best = {1, 1, 1e30f};
-  for (int32_t n = 1; n <= 32 && (n == 1 || n <= all); ++n) {
+  for (int32_t n = 1; n <= most && (n == 1 || n <= all); ++n) {
     const float x = (float)wgs * n, extra = n > 1 ? LAUNCH + x * p.D * PART : 0.f;
     const float mine = avg / n > 1.f ? avg / n : 1.f;
     float us = pairs ? gn_rounds(x / 512.f, bf ? 0.55f : 0.5f, 0.42f, 0.35f, 0.6f) * mine * unit1 + ceilf(x / 512.f) * RAMP
@@ -921,6 +1002,8 @@ static int32_t gn_key_splits(const Params& p, bool bf, int32_t max_len) {
 }
 
 static size_t gn_row_blocks(const Params& p) { return (size_t)gn_tiles(p.C, p.G, p.P, p.m, p.qp) * p.Hkv * 4; }
+// splits that fit `bytes` of partial results of `per` bytes each (at least 1: no partial results)
+static int32_t gn_fit(size_t bytes, size_t per) { return (int32_t)(bytes / per > 32 ? 32 : bytes / per < 2 ? 1 : bytes / per); }
 static size_t gn_row_part_bytes(const Params& p, int32_t split) { return split > 1 ? split * gn_row_blocks(p) * 32 * p.D * 4 : 0; }
 size_t fwd_generic_workspace_bytes(const Params& p, bool bf, int32_t max_len) {
   const int32_t s = gn_plan(p, bf, max_len, false).n;
@@ -931,6 +1014,7 @@ static size_t gn_key_part_bytes(const Params& p, int32_t max_len, int32_t split)
   const size_t slots = p.qp ? (size_t)p.Hkv * qp_max_pslots(p, p.sel_stride) : split > 1 ? (size_t)gn_key_units(p, max_len) * p.Hkv * split : 0;
   return gn_up(slots * 2 * GN_ROWS * p.D * 4);
 }
+size_t bwd_generic_min_bytes(const Params& p) { return gn_up((size_t)p.Hq * p.C * sizeof(float)) + gn_key_part_bytes(p, 0, 1); }
 size_t bwd_generic_workspace_bytes(const Params& p, bool bf, int32_t max_len) {
   return gn_up((size_t)p.Hq * p.C * sizeof(float)) + dq_generic_part_bytes(p, bf, max_len) +
          gn_key_part_bytes(p, max_len, gn_key_splits(p, bf, max_len));
@@ -946,8 +1030,8 @@ static hipError_t fwd_launch(const Params& p, int32_t tiles, int32_t ns, int32_t
 }
 template <typename T, int D>
 static hipError_t fwd_generic(const Params& p, int32_t max_len, void* ws, size_t ws_bytes, const char* name, hipStream_t st) {
-  GnPlan sp = gn_plan(p, Gn<T, D>::BF, max_len, false);
-  if (sp.n > 1 && (!ws || ws_bytes < fwd_generic_workspace_bytes(p, Gn<T, D>::BF, max_len))) sp.n = 1;   // (the forward also runs without a workspace)
+  // (the forward also runs without a workspace)
+  const GnPlan sp = gn_plan(p, Gn<T, D>::BF, max_len, false, ws ? gn_fit(ws_bytes, gn_row_blocks(p) * 32 * (p.D * 4 + 8)) : 1);
   const int32_t ns = sp.n;
   float* part = (float*)ws;
   float2* ml = (float2*)((unsigned char*)ws + gn_row_part_bytes(p, ns));
@@ -955,7 +1039,7 @@ static hipError_t fwd_generic(const Params& p, int32_t max_len, void* ws, size_t
   ProfScope prof_(name, st);
   hipError_t e = sp.groups == 2 ? fwd_launch<T, D, 2>(p, tiles, ns, len, part, ml, st) : fwd_launch<T, D, 1>(p, tiles, ns, len, part, ml, st);
   if (e == hipSuccess && ns > 1) {
-    fwd_combine_kernel<T, D><<<dim3((unsigned)(gn_row_blocks(p) * (D / 8) * 64 / 256)), dim3(256), 0, st>>>(p, tiles, ns, part, ml);
+    fwd_combine_kernel<T, D><<<dim3((unsigned)(gn_row_blocks(p))), dim3(256), 0, st>>>(p, tiles, ns, part, ml);
     e = hipGetLastError();
   }
   return e;
@@ -975,23 +1059,25 @@ static hipError_t dq_launch(const Params& p, int32_t tiles, int32_t ns, int32_t 
   return hipGetLastError();
 }
 template <typename T, int D>
-static hipError_t dq_generic(const Params& p, int32_t max_len, float* part, float* bias, int32_t n_stages, int32_t* splits, hipStream_t st) {
-  const GnPlan sp = gn_plan(p, Gn<T, D>::BF, max_len, true);
+static hipError_t dq_generic(const Params& p, int32_t max_len, float* part, size_t part_bytes, float* bias, int32_t n_stages, int32_t* splits,
+                             hipStream_t st) {
+  const GnPlan sp = gn_plan(p, Gn<T, D>::BF, max_len, true, gn_fit(part_bytes, gn_row_blocks(p) * 32 * p.D * 4));
   const int32_t tiles = gn_tiles(p.C, p.G, p.P, p.m, p.qp), len = gn_list_len(p, max_len);
   *splits = sp.n;
   if constexpr (Gn<T, D>::RB < 512)   // (fp32 at head dim 128 needs 320 registers: one wave per SIMD)
     if (sp.groups == 2) return dq_launch<T, D, 2>(p, tiles, sp.n, len, part, bias, n_stages, st);
   return dq_launch<T, D, 1>(p, tiles, sp.n, len, part, bias, n_stages, st);
 }
-hipError_t launch_dq_generic_bf16_128(const Params& p, int32_t max_len, float* part, float* bias, int32_t n_stages, int32_t* splits, hipStream_t st) {
-  return dq_generic<bf16_t, 128>(p, max_len, part, bias, n_stages, splits, st);
+hipError_t launch_dq_generic_bf16_128(const Params& p, int32_t max_len, float* part, size_t part_bytes, float* bias, int32_t n_stages,
+                                      int32_t* splits, hipStream_t st) {
+  return dq_generic<bf16_t, 128>(p, max_len, part, part_bytes, bias, n_stages, splits, st);
 }
 
 template <typename T, typename TG, int D>
 static hipError_t bwd_finish(const Params& p, int32_t dq_split, const float* dq_part, int32_t kv_units, int32_t kv_split, const float* kv_part,
                              hipStream_t st) {
-  constexpr int BPU = 2 * 4 * (D / 8) * 64 / 256;
-  const int32_t dq_blocks = dq_split > 1 ? (int32_t)(gn_row_blocks(p) * (D / 8) * 64 / 256) : 0;
+  constexpr int BPU = 8;
+  const int32_t dq_blocks = dq_split > 1 ? (int32_t)(gn_row_blocks(p)) : 0;
   const int64_t blocks = dq_blocks + (int64_t)kv_units * p.Hkv * BPU;
   if (blocks <= 0) return hipSuccess;
   bwd_finish_kernel<T, TG, D><<<dim3((unsigned)blocks), dim3(256), 0, st>>>(p, gn_tiles(p.C, p.G, p.P, p.m, p.qp), dq_split, dq_part, dq_blocks, kv_split,
@@ -1008,19 +1094,23 @@ hipError_t launch_bwd_finish(const Params& p, bool bf, int32_t dq_split, const f
 }
 
 template <typename T, typename TG, int D>
-static hipError_t bwd_generic(Params p, int32_t max_len, void* ws, hipStream_t st) {
+static hipError_t bwd_generic(Params p, int32_t max_len, void* ws, size_t ws_bytes, hipStream_t st) {
   static DeviceOnce once_kv;
   if (hipError_t e = ensure_max_dynamic_lds(once_kv, (const void*)dkv_generic_kernel<T, TG, D>, GnKey<T, D>::LDS); e != hipSuccess) return e;
-  const int32_t nk = gn_key_splits(p, Gn<T, D>::BF, max_len);
+  // [Delta][dK / dV slices][dQ partials]; a workspace without room for the slices of this call takes fewer
   unsigned char* w = (unsigned char*)ws;
   p.delta = (float*)w;
   w += gn_up((size_t)p.Hq * p.C * sizeof(float));
-  float* dq_part = (float*)w;
-  float* kv_part = (float*)(w + dq_generic_part_bytes(p, Gn<T, D>::BF, max_len));
+  size_t left = ws_bytes - gn_up((size_t)p.Hq * p.C * sizeof(float));
+  int32_t nk = gn_key_splits(p, Gn<T, D>::BF, max_len);
+  while (nk > 1 && gn_key_part_bytes(p, max_len, nk) > left) --nk;
+  float* kv_part = (float*)w;
+  float* dq_part = (float*)(w + gn_key_part_bytes(p, max_len, nk));
+  left -= gn_key_part_bytes(p, max_len, nk);
   const int32_t units = p.qp ? p.max_units : gn_key_units(p, max_len);
   ProfScope prof_("attn_bwd_generic", st);
   int32_t ns = 1;
-  hipError_t e = dq_generic<T, D>(p, max_len, dq_part, nullptr, 0, &ns, st);
+  hipError_t e = dq_generic<T, D>(p, max_len, dq_part, left, nullptr, 0, &ns, st);
   if (e != hipSuccess) return e;
   dkv_generic_kernel<T, TG, D><<<dim3((unsigned)units * p.Hkv * nk), dim3(256), GnKey<T, D>::LDS, st>>>(p, nk, __builtin_ctz(p.P), kv_part);
   e = hipGetLastError();
@@ -1028,8 +1118,8 @@ static hipError_t bwd_generic(Params p, int32_t max_len, void* ws, hipStream_t s
   return bwd_finish<T, TG, D>(p, ns, dq_part, p.qp ? p.max_multi : nk > 1 ? units : 0, nk, kv_part, st);
 }
 // max_len: host-side upper bound of the list length (of the union with one list per query page)
-hipError_t launch_bwd_generic(const Params& p, bool bf, int32_t max_len, void* ws, hipStream_t st) {
-#define OOMB_BWD(T, TG) (p.D == 128 ? bwd_generic<T, TG, 128>(p, max_len, ws, st) : bwd_generic<T, TG, 64>(p, max_len, ws, st))
+hipError_t launch_bwd_generic(const Params& p, bool bf, int32_t max_len, void* ws, size_t ws_bytes, hipStream_t st) {
+#define OOMB_BWD(T, TG) (p.D == 128 ? bwd_generic<T, TG, 128>(p, max_len, ws, ws_bytes, st) : bwd_generic<T, TG, 64>(p, max_len, ws, ws_bytes, st))
   if (bf) return p.grad_is_bf16 ? OOMB_BWD(bf16_t, bf16_t) : OOMB_BWD(bf16_t, float);
   return p.grad_is_bf16 ? OOMB_BWD(float, bf16_t) : OOMB_BWD(float, float);
 #undef OOMB_BWD

@@ -8,8 +8,9 @@ namespace oomb {
 
 // score_topk.hip: pooled query, page scores (from the keys or from cached page means), top-k lists
 size_t score_workspace_bytes(const Params& p);
+size_t score_workspace_min_bytes(const Params& p);
 hipError_t launch_score_topk(const Params& p, bool is_bf16, int32_t top_k, int32_t* sel, int32_t* sel_count,
-                             float* scores_out, void* ws, const float* kbar_cache, hipStream_t st);
+                             float* scores_out, void* ws, size_t ws_bytes, const float* kbar_cache, hipStream_t st);
 hipError_t score_scratch_ptr(void** out);  // this device's copy of the built-in scoring scratch array
 hipError_t launch_topk_select_qp(const Params& p, const float* votes, int32_t top_k, int32_t* sel, int32_t* sel_count,
                                  hipStream_t st);
@@ -39,11 +40,14 @@ hipError_t launch_qp_prepare(Params& p, void* ws, hipStream_t st);
 size_t fwd_generic_workspace_bytes(const Params& p, bool is_bf16, int32_t max_len);
 hipError_t launch_fwd_generic(const Params& p, bool is_bf16, int32_t max_len, void* ws, size_t ws_bytes, const char* name, hipStream_t st);
 size_t bwd_generic_workspace_bytes(const Params& p, bool is_bf16, int32_t max_len);
-hipError_t launch_bwd_generic(const Params& p, bool is_bf16, int32_t max_len, void* ws, hipStream_t st);
+size_t bwd_generic_min_bytes(const Params& p);   // without splits
+hipError_t launch_bwd_generic(const Params& p, bool is_bf16, int32_t max_len, void* ws, size_t ws_bytes, hipStream_t st);
 // the same forward and dQ kernels for shapes with kernels of their own but too few rows to fill the chip with them
 bool rows_take_generic(const Params& p, int32_t max_len, bool dq);
 size_t dq_generic_part_bytes(const Params& p, bool is_bf16, int32_t max_len);
-hipError_t launch_dq_generic_bf16_128(const Params& p, int32_t max_len, float* part, float* bias, int32_t n_stages, int32_t* splits, hipStream_t st);
+// (part_bytes: what the caller has for partial sums; fewer splits if it is less than dq_generic_part_bytes)
+hipError_t launch_dq_generic_bf16_128(const Params& p, int32_t max_len, float* part, size_t part_bytes, float* bias, int32_t n_stages,
+                                      int32_t* splits, hipStream_t st);
 
 // kv_layout.hip: LDS-ordered images of the selected pages
 size_t kv_image_bytes(const Params& p, int32_t max_len);
@@ -52,13 +56,15 @@ hipError_t launch_kv_layout(const Params& p, int32_t max_len, void* img, hipStre
 // attn_fwd_mfma.hip, attn_bwd_mfma.hip, attn_bwd_dkv_mfma.hip: the matrix-core kernels
 bool mfma_supported(const Params& p, bool is_bf16);
 size_t fwd_mfma_workspace_bytes(const Params& p, int32_t max_list_len);
-hipError_t launch_fwd_mfma(const Params& p, int32_t max_list_len, void* ws, hipStream_t st);
+size_t fwd_mfma_min_bytes(const Params& p, int32_t max_list_len);
+hipError_t launch_fwd_mfma(const Params& p, int32_t max_list_len, void* ws, size_t ws_bytes, hipStream_t st);
 size_t bwd_mfma_workspace_bytes(const Params& p, int32_t max_list_len);
-hipError_t launch_bwd_mfma(const Params& p, int32_t max_list_len, void* ws, hipStream_t st);
+size_t bwd_mfma_min_bytes(const Params& p, int32_t max_list_len);
+hipError_t launch_bwd_mfma(const Params& p, int32_t max_list_len, void* ws, size_t ws_bytes, hipStream_t st);
 size_t dkv_partial_bytes(const Params& p, int32_t max_len, int32_t n_split);
-int32_t dkv_splits(const Params& p, int32_t max_len);
-hipError_t launch_bwd_dkv_mfma(const Params& p, const float* bias, int32_t n_stages, int32_t max_len, float* partial_ws, int32_t dq_split,
-                               const float* dq_part, hipStream_t st);
+int32_t dkv_splits(const Params& p, int32_t max_len, bool few);   // few: more than four slices where four leave compute units idle
+hipError_t launch_bwd_dkv_mfma(const Params& p, const float* bias, int32_t n_stages, int32_t max_len, int32_t n_split, float* partial_ws,
+                               int32_t dq_split, const float* dq_part, hipStream_t st);
 
 // offload.hip: staging plan and transfers between pinned host pools and device staging pools
 void* device_view(const void* ptr);

@@ -48,15 +48,15 @@ template <> __device__ __forceinline__ void part_store4<float>(float* p, float a
 template <> __device__ __forceinline__ void part_store4<bf16_t>(bf16_t* p, float a, float b, float c, float d) {
   *reinterpret_cast<uint2*>(p) = make_uint2(pack2_bf16(a, b), pack2_bf16(c, d));
 }
-template <typename T> __device__ __forceinline__ void part_add4(T* p, float a, float b, float c, float d);
-template <> __device__ __forceinline__ void part_add4<float>(float* p, float a, float b, float c, float d) {
-  const float4 v = *reinterpret_cast<const float4*>(p);
-  *reinterpret_cast<float4*>(p) = make_float4(v.x + a, v.y + b, v.z + c, v.w + d);
-}
-template <> __device__ __forceinline__ void part_add4<bf16_t>(bf16_t* p, float a, float b, float c, float d) {
+template <typename T> __device__ __forceinline__ float4 part_load4(const T* p);
+template <> __device__ __forceinline__ float4 part_load4<float>(const float* p) { return *reinterpret_cast<const float4*>(p); }
+template <> __device__ __forceinline__ float4 part_load4<bf16_t>(const bf16_t* p) {
   const uint2 v = *reinterpret_cast<const uint2*>(p);
-  part_store4<bf16_t>(p, __uint_as_float(v.x << 16) + a, __uint_as_float(v.x & 0xffff0000u) + b, __uint_as_float(v.y << 16) + c,
-                    __uint_as_float(v.y & 0xffff0000u) + d);
+  return make_float4(__uint_as_float(v.x << 16), __uint_as_float(v.x & 0xffff0000u), __uint_as_float(v.y << 16), __uint_as_float(v.y & 0xffff0000u));
+}
+template <typename T> __device__ __forceinline__ void part_add4(T* p, float a, float b, float c, float d) {
+  const float4 v = part_load4<T>(p);
+  part_store4<T>(p, v.x + a, v.y + b, v.z + c, v.w + d);
 }
 
 // What is left of a backward with splits, in one launch (attn_generic.hip): the dQ partials of `dq_split` key ranges

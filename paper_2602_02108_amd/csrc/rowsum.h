@@ -68,4 +68,68 @@ __device__ __forceinline__ void seq_row_sum(const T* base, int64_t stride, int c
   }
 }
 
+// <q, k> over D dims held four per lane by D / 4 consecutive lanes: one product per dim, then a tree of strides D / 2 .. 1
+// (valid in the first of the lanes)
+template <int D> __device__ __forceinline__ float score_tree(const float4& q, const float4& k) {
+  float x[4] = {__fmul_rn(q.x, k.x), __fmul_rn(q.y, k.y), __fmul_rn(q.z, k.z), __fmul_rn(q.w, k.w)};
+#pragma unroll
+  for (int s = D / 2; s >= 4; s >>= 1) {
+#pragma unroll
+    for (int v = 0; v < 4; ++v) x[v] = __fadd_rn(x[v], __shfl_xor(x[v], s / 4, 64));
+  }
+  x[0] = __fadd_rn(x[0], x[2]);
+  x[1] = __fadd_rn(x[1], x[3]);
+  return __fadd_rn(x[0], x[1]);
+}
+
+// Sum of `count` rows of D elements by one workgroup, in the same order: the tile is brought into LDS with all its loads in
+// flight at once (a chain of additions that waits for its own loads, 32 in flight, takes 8 us for 128 rows; this 3 to
+// 4), then a thread owns one dim (fp32) or two (bf16) and walks the rows.
+// lds: count * D elements, 16-byte aligned; out(d, sum) gets the sums.
+template <typename T, int D, typename O>
+__device__ __forceinline__ void lds_row_sum(int count, const unsigned char* lds, O&& out) {
+  const int tid = threadIdx.x;
+  constexpr int DPT = 4 / sizeof(T), RW = D / DPT;   // dims per thread, words per row
+  if (tid >= RW) return;
+  const uint32_t* w = reinterpret_cast<const uint32_t*>(lds) + tid;
+  float a = 0.0f, b = 0.0f;
+  auto add = [&](uint32_t x) __attribute__((always_inline)) {
+    if (sizeof(T) == 4) {
+      a = __fadd_rn(a, __uint_as_float(x));
+    } else {
+      a = __fadd_rn(a, __uint_as_float(x << 16));
+      b = __fadd_rn(b, __uint_as_float(x & 0xffff0000u));
+    }
+  };
+  int t = 0;
+  for (; t + 16 <= count; t += 16) {
+    uint32_t x[16];
+#pragma unroll
+    for (int u = 0; u < 16; ++u) x[u] = w[(t + u) * RW];
+#pragma unroll
+    for (int u = 0; u < 16; ++u) add(x[u]);
+  }
+  for (; t < count; ++t) add(w[t * RW]);
+  out(DPT * tid, a);
+  if (sizeof(T) == 2) out(DPT * tid + 1, b);
+}
+template <typename T, int D, typename O>
+__device__ __forceinline__ void tile_row_sum(const T* base, int64_t stride, int count, unsigned char* lds, O&& out) {
+  constexpr int VEC = Vec16<T>::N, GPR = D / VEC, U = 8;
+  const int tid = threadIdx.x, n = blockDim.x, total = count * GPR;
+  for (int e0 = tid; e0 < total; e0 += U * n) {
+    uint4 v[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int e = e0 + u * n < total ? e0 + u * n : e0;
+      v[u] = *reinterpret_cast<const uint4*>(base + (int64_t)(e / GPR) * stride + (e % GPR) * VEC);
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (e0 + u * n < total) reinterpret_cast<uint4*>(lds)[e0 + u * n] = v[u];
+  }
+  __syncthreads();
+  lds_row_sum<T, D>(count, lds, out);
+}
+
 }  // namespace oomb

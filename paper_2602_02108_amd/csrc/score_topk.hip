@@ -16,37 +16,43 @@
 
 namespace oomb {
 
-// Step S1a: A[h][tau][d] = sum over the P tokens of query page tau of Q.  Every (head, query page, lane's
-// d) is one sequential chain of P additions: the chains are all the parallelism there is, so they are spread
-// one wave per workgroup over as many compute units as possible, each lane with 32 loads in flight.
-constexpr int QPOOL_THREADS = 64;
+// Step S1a: A[h][tau][d] = sum over the P tokens of query page tau of Q, one workgroup per (query page, head); with
+// means != nullptr the workgroups past Hq * m compute S2 for one (past page, KV head) each, means[l][g][d] as the paged
+// manager caches them (short histories, whose pages are too few to fill the chip page by page).
 template <typename T, int D>
-__global__ __launch_bounds__(QPOOL_THREADS) void qpool_partial_kernel(Params p, float* __restrict__ A) {
-  constexpr int VEC = Vec16<T>::N, LPR = D / VEC, UPB = QPOOL_THREADS / LPR;
-  const int unit = blockIdx.x * UPB + threadIdx.x / LPR;
-  const int lr = threadIdx.x % LPR;
-  if (unit >= p.Hq * p.m) return;
-  const int h = unit / p.m, tau = unit % p.m;
-  const T* base = (const T*)p.q + (int64_t)tau * p.P * p.q_tok_stride + (int64_t)h * p.q_head_stride + lr * VEC;
-  float acc[VEC];
-  seq_row_sum<T, 32>(base, p.q_tok_stride, p.P, acc);
-  float* out = A + ((int64_t)h * p.m + tau) * D + lr * VEC;
-#pragma unroll
-  for (int v = 0; v < VEC; ++v) out[v] = acc[v];
+__global__ __launch_bounds__(256) void qpool_partial_kernel(Params p, float* __restrict__ A, float* __restrict__ means, float inv_p) {
+  extern __shared__ __align__(16) unsigned char lds[];
+  const int b = blockIdx.x, n_q = p.Hq * p.m;
+  if (b < n_q) {
+    const int tau = b / p.Hq, h = b - tau * p.Hq;
+    float* out = A + ((int64_t)h * p.m + tau) * D;
+    tile_row_sum<T, D>((const T*)p.q + (int64_t)tau * p.P * p.q_tok_stride + (int64_t)h * p.q_head_stride, p.q_tok_stride, p.P, lds,
+                       [&](int d, float sum) __attribute__((always_inline)) { out[d] = sum; });
+  } else {
+    const int l = (b - n_q) / p.Hkv, g = (b - n_q) - l * p.Hkv;
+    float* out = means + ((int64_t)l * p.Hkv + g) * D;
+    tile_row_sum<T, D>((const T*)p.k_pool + (int64_t)p.page_table[l] * p.pool_page_stride + (int64_t)g * p.pool_head_stride, p.pool_tok_stride, p.P, lds,
+                       [&](int d, float sum) __attribute__((always_inline)) { out[d] = __fmul_rn(sum, inv_p); });
+  }
 }
 
 // Step S1b: qbar[g][d] = (sum over tau (outer), heads of g (inner) of A) * r.  One workgroup per KV head.  The
 // sum of a (g, d) is one sequential chain over the m G terms k = tau * G + (h - g G); the terms are brought
 // into LDS by all threads at once (rows of D floats, FINAL_ROWS at a time), then thread d walks its chain.
 constexpr int FINAL_THREADS = 1024;
-constexpr int FINAL_LDS_FLOATS = 32768;  // 128 KiB
-__global__ __launch_bounds__(FINAL_THREADS) void qpool_final_kernel(Params p, const float* __restrict__ A,
-                                                                    float* __restrict__ qbar, float r) {
-  extern __shared__ float rows[];  // [rows per pass][D]
-  const int g = blockIdx.x, tid = threadIdx.x, D = p.D;
+constexpr int FINAL_LDS_FLOATS = 32768;        // 128 KiB
+constexpr int SMALL_LDS_FLOATS = 28672;        // 112 KiB: the kernel below that also selects
+static inline size_t final_lds_bytes(const Params& p, int floats) {
+  const size_t all = (size_t)p.m * p.G * p.D;
+  return 4 * (all < (size_t)floats ? all : (size_t)floats);
+}
+// thread d < D returns qbar[g][d]; rows: LDS for FLOATS / D rows
+template <int FLOATS>
+__device__ __forceinline__ float qpool_final(const Params& p, const float* __restrict__ A, float r, int g, float* rows) {
+  const int tid = threadIdx.x, D = p.D;
   const int dshift = D == 128 ? 7 : 6;  // D is 64 or 128
   const int n = p.m * p.G;
-  const int per_pass = FINAL_LDS_FLOATS >> dshift;
+  const int per_pass = FLOATS >> dshift;
   float acc = 0.0f;
   for (int k0 = 0; k0 < n; k0 += per_pass) {
     const int cnt = n - k0 < per_pass ? n - k0 : per_pass;
@@ -80,7 +86,12 @@ __global__ __launch_bounds__(FINAL_THREADS) void qpool_final_kernel(Params p, co
     }
     __syncthreads();
   }
-  if (tid < D) qbar[g * D + tid] = __fmul_rn(acc, r);
+  return __fmul_rn(acc, r);
+}
+__global__ __launch_bounds__(FINAL_THREADS) void qpool_final_kernel(Params p, const float* __restrict__ A, float* __restrict__ qbar, float r) {
+  extern __shared__ float rows[];  // [rows per pass][D]
+  const float v = qpool_final<FINAL_LDS_FLOATS>(p, A, r, blockIdx.x, rows);
+  if ((int)threadIdx.x < p.D) qbar[blockIdx.x * p.D + threadIdx.x] = v;
 }
 
 // Steps S2 + S3: one group of LPR lanes walks one (KV head, logical page) tile
@@ -235,18 +246,23 @@ __global__ __launch_bounds__(SELECT_THREADS) void topk_select_kernel(
 // order does not matter), 256 threads add the 16 histograms and scan them from the top, and the bin where
 // the count crosses what is still wanted extends the prefix.  Four passes, three barriers each; the ordered
 // emission needs only the exclusive scan over threads.
-template <int PER>
-__global__ __launch_bounds__(SELECT_THREADS) void topk_select_reg_kernel(
-    const float* __restrict__ scores, int64_t n_past, int32_t m, int32_t top_k,
-    int32_t* __restrict__ sel, int32_t* __restrict__ sel_count, int32_t per_qp) {
-  constexpr int WAVES = SELECT_THREADS / 64;
-  __shared__ uint32_t hist[2][WAVES][256];
-  __shared__ uint32_t scan_tot[4];
-  __shared__ uint32_t picked[2];  // {bin, how many keys of that bin are still wanted}
-  __shared__ unsigned long long wave_tot[WAVES];
-  const int g = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int32_t n_loc = per_qp ? (int32_t)(blockIdx.x % m) + 1 : m;
-  const float* sc = scores + (int64_t)g * n_past;
+struct SelectLds {
+  static constexpr int WAVES = SELECT_THREADS / 64;
+  uint32_t hist[2][WAVES][256];
+  uint32_t scan_tot[4];
+  uint32_t picked[2];  // {bin, how many keys of that bin are still wanted}
+  unsigned long long wave_tot[WAVES];
+};
+// list `g` (its row of sel and sel_count), ending with n_loc local pages; load(l): score of past page l
+template <int PER, typename F>
+__device__ __forceinline__ void select_reg(SelectLds& lds, F&& load, int g, int64_t n_past, int32_t m, int32_t n_loc, int32_t top_k,
+                                           int32_t* __restrict__ sel, int32_t* __restrict__ sel_count) {
+  constexpr int WAVES = SelectLds::WAVES;
+  auto& hist = lds.hist;
+  auto& scan_tot = lds.scan_tot;
+  auto& picked = lds.picked;
+  auto& wave_tot = lds.wave_tot;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int32_t stride = top_k + m;
   int32_t* out = sel + (int64_t)g * stride;
   const int32_t k_eff = (int32_t)(top_k < n_past ? top_k : n_past);
@@ -256,7 +272,7 @@ __global__ __launch_bounds__(SELECT_THREADS) void topk_select_reg_kernel(
   const int32_t lo = tid * PER;
   uint32_t key[PER];
 #pragma unroll
-  for (int i = 0; i < PER; ++i) key[i] = lo + i < np ? order_key(sc[lo + i]) : 0u;
+  for (int i = 0; i < PER; ++i) key[i] = lo + i < np ? order_key(load(lo + i)) : 0u;
   __syncthreads();
 
   uint32_t T = 0;
@@ -346,6 +362,53 @@ __global__ __launch_bounds__(SELECT_THREADS) void topk_select_reg_kernel(
   for (int32_t j = k_eff + n_loc + tid; j < stride; j += SELECT_THREADS) out[j] = -1;
   if (tid == 0) sel_count[g] = k_eff + n_loc;
 }
+template <int PER>
+__global__ __launch_bounds__(SELECT_THREADS) void topk_select_reg_kernel(
+    const float* __restrict__ scores, int64_t n_past, int32_t m, int32_t top_k,
+    int32_t* __restrict__ sel, int32_t* __restrict__ sel_count, int32_t per_qp) {
+  __shared__ SelectLds lds;
+  const float* sc = scores + (int64_t)blockIdx.x * n_past;
+  select_reg<PER>(lds, [&](int32_t l) { return sc[l]; }, blockIdx.x, n_past, m, per_qp ? (int32_t)(blockIdx.x % m) + 1 : m, top_k, sel, sel_count);
+}
+
+// Steps S1b, S3 and S4 of a KV head in one workgroup, from page means, for short histories: three
+// kernels that do next to nothing (56 pages: 11.4 us and two launches more than the 10.2 of one).
+constexpr int SMALL_PAGES = 192;   // (0.03 us a page on top of 9: beyond this the pages want more compute units than one)
+template <int D>
+__global__ __launch_bounds__(SELECT_THREADS) void select_small_kernel(Params p, const float* __restrict__ A, float r, const float* __restrict__ means,
+                                                                      float* __restrict__ scores, int32_t top_k, int32_t* __restrict__ sel,
+                                                                      int32_t* __restrict__ sel_count) {
+  extern __shared__ __align__(16) float rows[];
+  __shared__ SelectLds lds;
+  __shared__ __align__(16) float qb[D];
+  __shared__ float sc[SMALL_PAGES];
+  constexpr int VEC = 4, LPR = D / VEC, GROUPS = SELECT_THREADS / LPR;
+  const int g = blockIdx.x, tid = threadIdx.x, lr = tid % LPR, grp = tid / LPR;
+  const int32_t np = (int32_t)p.n_past;
+  const float v = qpool_final<SMALL_LDS_FLOATS>(p, A, r, g, rows);
+  if (tid < D) qb[tid] = v;
+  __syncthreads();
+  const float4 q4 = *reinterpret_cast<const float4*>(qb + lr * VEC);
+  for (int32_t l0 = grp; l0 < np; l0 += 4 * GROUPS) {   // (four pages per group in flight)
+    float4 kb[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int32_t l = l0 + u * GROUPS < np ? l0 + u * GROUPS : l0;
+      kb[u] = *reinterpret_cast<const float4*>(means + ((int64_t)l * p.Hkv + g) * D + lr * VEC);
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const float s = score_tree<D>(q4, kb[u]);
+      const int32_t l = l0 + u * GROUPS;
+      if (lr == 0 && l < np) {
+        sc[l] = s;
+        scores[(int64_t)g * p.n_past + l] = s;
+      }
+    }
+  }
+  __syncthreads();
+  select_reg<1>(lds, [&](int32_t l) { return sc[l]; }, g, p.n_past, p.m, p.m, top_k, sel, sel_count);
+}
 
 static hipError_t launch_topk_select(const Params& p, const float* scores, int32_t top_k, int32_t* sel, int32_t* sel_count,
                                      int per_qp, hipStream_t st) {
@@ -375,61 +438,79 @@ static hipError_t launch_topk_select(const Params& p, const float* scores, int32
   return hipGetLastError();
 }
 
+// Layout of the scoring workspace.  Page means of a short history get a place of their own behind the rest, if all of
+// it fits the built-in scratch array (callers without a workspace take the same kernels).
+struct ScoreLayout {
+  size_t off_qbar, off_scores, off_means, bytes;   // (means at the end: a call works without them)
+  bool small;   // means + one workgroup per KV head for the rest
+};
+static ScoreLayout score_layout(const Params& p, bool cached, size_t ws_bytes) {
+  auto up = [](size_t x) { return (x + 255) & ~(size_t)255; };
+  ScoreLayout L{};
+  L.off_qbar = up((size_t)p.Hq * p.m * p.D * sizeof(float));
+  L.off_scores = L.off_qbar + up((size_t)p.Hkv * p.D * sizeof(float));
+  L.bytes = L.off_means = L.off_scores + up((size_t)p.Hkv * (size_t)(p.n_past > 0 ? p.n_past : 1) * sizeof(float));
+  const size_t means = up((size_t)p.n_past * p.Hkv * p.D * sizeof(float));
+  L.small = p.n_past <= SMALL_PAGES && (cached || (L.bytes + means <= (size_t)OOMB_NOALLOC_SCRATCH_BYTES && L.bytes + means <= ws_bytes));
+  if (L.small && !cached) L.bytes += means;
+  return L;
+}
+size_t score_workspace_bytes(const Params& p) { return score_layout(p, false, SIZE_MAX).bytes; }
+// what a call cannot do without: a workspace sized for a longer history (which has no place for means) serves shorter ones
+size_t score_workspace_min_bytes(const Params& p) { return score_layout(p, false, 0).bytes; }
+
 // kbar_cache != nullptr: the page means come from the cache instead of the keys
 template <typename T, int D>
-static hipError_t launch_scoring(const Params& p, float* A, float* qbar, float* scores, const float* kbar_cache, hipStream_t st) {
+static hipError_t launch_scoring(const Params& p, int32_t top_k, int32_t* sel, int32_t* sel_count, float* scores_out, unsigned char* ws,
+                                 size_t ws_bytes, const float* kbar_cache, hipStream_t st) {
   constexpr int VEC = Vec16<T>::N, LPR = D / VEC, PER_BLOCK = 256 / LPR;
-  const int units = p.Hq * p.m;
-  constexpr int UPB = QPOOL_THREADS / LPR;
-  { ProfScope prof_("qpool_partial", st); qpool_partial_kernel<T, D><<<dim3((units + UPB - 1) / UPB), dim3(QPOOL_THREADS), 0, st>>>(p, A); }
+  const ScoreLayout L = score_layout(p, kbar_cache != nullptr, ws_bytes);
+  float* A = (float*)ws;
+  float* qbar = (float*)(ws + L.off_qbar);
+  float* scores = scores_out ? scores_out : (float*)(ws + L.off_scores);
+  float* means = L.small && !kbar_cache ? (float*)(ws + L.off_means) : nullptr;
+  const float inv_p = 1.0f / (float)p.P, r = 1.0f / (float)((int64_t)p.C * p.G);
+  {
+    ProfScope prof_("qpool_partial", st);
+    const unsigned blocks = (unsigned)((int64_t)p.Hq * p.m + (means ? p.n_past * p.Hkv : 0));
+    qpool_partial_kernel<T, D><<<dim3(blocks), dim3(256), (size_t)p.P * D * sizeof(T), st>>>(p, A, means, inv_p);
+  }
   if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
-  const float r = 1.0f / (float)((int64_t)p.C * p.G);
+  if (L.small) {
+    static DeviceOnce lds_once;
+    if (hipError_t e = ensure_max_dynamic_lds(lds_once, (const void*)select_small_kernel<D>, SMALL_LDS_FLOATS * 4); e != hipSuccess) return e;
+    ProfScope prof_("select_small", st);
+    select_small_kernel<D><<<dim3(p.Hkv), dim3(SELECT_THREADS), final_lds_bytes(p, SMALL_LDS_FLOATS), st>>>(p, A, r, kbar_cache ? kbar_cache : means, scores, top_k, sel,
+                                                                                         sel_count);
+    return hipGetLastError();
+  }
   {
     static DeviceOnce lds_once;
     if (hipError_t e = ensure_max_dynamic_lds(lds_once, (const void*)qpool_final_kernel, FINAL_LDS_FLOATS * 4); e != hipSuccess) return e;
     ProfScope prof_("qpool_final", st);
-    qpool_final_kernel<<<dim3(p.Hkv), dim3(FINAL_THREADS), FINAL_LDS_FLOATS * 4, st>>>(p, A, qbar, r);
+    qpool_final_kernel<<<dim3(p.Hkv), dim3(FINAL_THREADS), final_lds_bytes(p, FINAL_LDS_FLOATS), st>>>(p, A, qbar, r);
   }
   if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
-  if (kbar_cache) return launch_page_score_cached(p, qbar, kbar_cache, scores, st);
-  if (p.n_past > 0) {
-    const float inv_p = 1.0f / (float)p.P;
+  if (kbar_cache) {
+    if (hipError_t e = launch_page_score_cached(p, qbar, kbar_cache, scores, st); e != hipSuccess) return e;
+  } else {
     dim3 grid((unsigned)((p.n_past + PER_BLOCK - 1) / PER_BLOCK), p.Hkv);
     { ProfScope prof_("page_score", st); page_score_kernel<T, D><<<grid, dim3(256), 0, st>>>(p, qbar, scores, inv_p); }
-    return hipGetLastError();
+    if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
   }
-  return hipSuccess;
-}
-
-size_t score_workspace_bytes(const Params& p) {
-  size_t a = (size_t)p.Hq * p.m * p.D * sizeof(float);
-  size_t qb = (size_t)p.Hkv * p.D * sizeof(float);
-  size_t sc = (size_t)p.Hkv * (size_t)(p.n_past > 0 ? p.n_past : 1) * sizeof(float);
-  auto up = [](size_t x) { return (x + 255) & ~(size_t)255; };
-  return up(a) + up(qb) + up(sc);
+  return launch_topk_select(p, scores, top_k, sel, sel_count, 0, st);
 }
 
 // Returns hipSuccess or the launch error.  dtype_is_bf16 picks the element type.
 hipError_t launch_score_topk(const Params& p, bool is_bf16, int32_t top_k, int32_t* sel,
-                             int32_t* sel_count, float* scores_out, void* ws, const float* kbar_cache, hipStream_t st) {
-  auto up = [](size_t x) { return (x + 255) & ~(size_t)255; };
-  char* w = (char*)ws;
-  float* A = (float*)w;
-  w += up((size_t)p.Hq * p.m * p.D * sizeof(float));
-  float* qbar = (float*)w;
-  w += up((size_t)p.Hkv * p.D * sizeof(float));
-  float* scores = scores_out ? scores_out : (float*)w;
-
-  hipError_t e;
-  if (is_bf16) {
-    e = p.D == 128 ? launch_scoring<bf16_t, 128>(p, A, qbar, scores, kbar_cache, st)
-                   : launch_scoring<bf16_t, 64>(p, A, qbar, scores, kbar_cache, st);
-  } else {
-    e = p.D == 128 ? launch_scoring<float, 128>(p, A, qbar, scores, kbar_cache, st)
-                   : launch_scoring<float, 64>(p, A, qbar, scores, kbar_cache, st);
-  }
-  if (e != hipSuccess) return e;
-  return launch_topk_select(p, scores, top_k, sel, sel_count, 0, st);
+                             int32_t* sel_count, float* scores_out, void* ws, size_t ws_bytes, const float* kbar_cache,
+                             hipStream_t st) {
+  unsigned char* w = (unsigned char*)ws;
+  if (is_bf16)
+    return p.D == 128 ? launch_scoring<bf16_t, 128>(p, top_k, sel, sel_count, scores_out, w, ws_bytes, kbar_cache, st)
+                      : launch_scoring<bf16_t, 64>(p, top_k, sel, sel_count, scores_out, w, ws_bytes, kbar_cache, st);
+  return p.D == 128 ? launch_scoring<float, 128>(p, top_k, sel, sel_count, scores_out, w, ws_bytes, kbar_cache, st)
+                    : launch_scoring<float, 64>(p, top_k, sel, sel_count, scores_out, w, ws_bytes, kbar_cache, st);
 }
 
 // Built-in scratch memory of oomb_page_score_topk_noalloc: the scoring workspace (query-page sums, pooled

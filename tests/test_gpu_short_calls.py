@@ -1,0 +1,81 @@
+"""Short calls: selection of a short history in one workgroup (edges of its range, more pooled rows than one pass
+holds), append for every element type / head dim, and workspaces sized for another length of the history."""
+import numpy as np
+import pytest
+import torch
+
+import oracle as orc
+from paper_2602_02108_amd import api
+from paper_2602_02108_amd.workloads import Workload, make_inputs, to_numpy, torch_dtype
+
+import parity_util as pu
+
+pytestmark = pytest.mark.gpu
+
+
+def _desc(w, x):
+    return api.make_desc(x["q"], x["k_pool"], w.N, w.sm_scale, torch_dtype(w.grad_dtype))
+
+
+@pytest.mark.parametrize("dtype,D,P", [("f32", 64, 16), ("bf16", 128, 128), ("bf16", 64, 32)])
+@pytest.mark.parametrize("n_past", [1, 191, 192, 193])
+def test_selection_of_short_histories(n_past, dtype, D, P):
+    w = Workload("short", 4, 2, D, P, 2 * P, (n_past + 2) * P, min(n_past, 9), dtype, "f32", 0.1, extra_phys=2, seed=400 + n_past)
+    x = make_inputs(w, "cuda")
+    sel, cnt, scores = pu.gpu_select(w, x)
+    osel, ocnt, oscores = pu.oracle_select(w, pu.host_inputs(x))
+    assert np.array_equal(scores.cpu().numpy().view(np.uint32), oscores.view(np.uint32))
+    assert np.array_equal(sel.cpu().numpy(), osel) and np.array_equal(cnt.cpu().numpy(), ocnt)
+
+
+def test_selection_with_more_pooled_rows_than_one_pass():
+    # m * G = 256 rows of 128 floats against 224 in LDS at a time
+    w = Workload("rows", 32, 1, 128, 16, 16 * 8, 16 * 48, 7, "bf16", "f32", 0.1, seed=420)
+    x = make_inputs(w, "cuda")
+    sel, cnt, scores = pu.gpu_select(w, x)
+    osel, ocnt, oscores = pu.oracle_select(w, pu.host_inputs(x))
+    assert np.array_equal(scores.cpu().numpy().view(np.uint32), oscores.view(np.uint32))
+    assert np.array_equal(sel.cpu().numpy(), osel)
+
+
+@pytest.mark.parametrize("with_means", [True, False])
+@pytest.mark.parametrize("dtype,D,P", [("f32", 128, 128), ("f32", 64, 16), ("bf16", 64, 128), ("bf16", 128, 16)])
+def test_append_for_every_tile(dtype, D, P, with_means):
+    w = Workload("append", 3, 3, D, P, 3 * P, 8 * P, None, dtype, "f32", 0.1, extra_phys=1, seed=430)
+    x = make_inputs(w, "cuda")
+    sh, dt = pu.shape_of(w), x["k_pool"].dtype
+    gen = torch.Generator(device="cpu").manual_seed(431)
+    kc, vc = (torch.randn((w.C, w.Hkv, w.D), generator=gen).to(dt).cuda() for _ in range(2))
+    cache = torch.full((sh.n, w.Hkv, w.D), 7.0, dtype=torch.float32, device="cuda")
+    ok, ov, oc = orc.kv_append(sh, to_numpy(kc), to_numpy(vc), to_numpy(x["page_table"]), to_numpy(x["k_pool"]), to_numpy(x["v_pool"]), cache.cpu().numpy())
+    api.kv_append(_desc(w, x), kc, vc, x["page_table"], x["k_pool"], x["v_pool"], cache if with_means else None)
+    torch.cuda.synchronize()
+    assert np.array_equal(to_numpy(x["k_pool"]), ok) and np.array_equal(to_numpy(x["v_pool"]), ov)
+    if with_means:
+        assert np.array_equal(cache.cpu().numpy().view(np.uint32), oc.view(np.uint32))
+
+
+@pytest.mark.parametrize("dtype,P,top_k", [("bf16", 128, None), ("bf16", 128, 4), ("f32", 64, None)])
+def test_a_workspace_of_the_longest_history_serves_the_shorter_ones(dtype, P, top_k):
+    last = Workload("grow", 6, 2, 128, P, 2 * P, 26 * P, top_k, dtype, "f32", 0.0884, seed=440)
+    x = make_inputs(last, "cuda")
+    hx = pu.host_inputs(x)
+    lk = -1 if top_k is None else top_k
+    ws = {op: torch.empty(api.workspace_bytes(_desc(last, x), k, op), dtype=torch.uint8, device="cuda")
+          for op, k in ((api.OP_SCORE_TOPK, top_k or 0), (api.OP_ATTN_FWD, lk), (api.OP_ATTN_BWD, lk))}
+    for n in (2, 3, 7, 13, 26):
+        w = last.with_(N=n * P)
+        desc = _desc(w, x)
+        sel = cnt = osel = ocnt = None
+        if top_k is not None:
+            sel, cnt = api.page_score_topk(desc, x["q"], x["k_pool"], x["page_table"], top_k, workspace=ws[api.OP_SCORE_TOPK])
+            osel, ocnt, _ = orc.page_score_topk(pu.shape_of(w), hx["q"], hx["k_pool"], hx["page_table"], top_k)
+            assert np.array_equal(sel.cpu().numpy(), osel)
+        x["dk_pool"].zero_()
+        x["dv_pool"].zero_()
+        o, lse = api.paged_attn_fwd(desc, x["q"], x["k_pool"], x["v_pool"], x["page_table"], sel, cnt, workspace=ws[api.OP_ATTN_FWD])
+        dq = api.paged_attn_bwd(desc, x["q"], x["k_pool"], x["v_pool"], x["page_table"], o, lse, x["d_o"], x["dk_pool"], x["dv_pool"], sel, cnt,
+                                workspace=ws[api.OP_ATTN_BWD])
+        ref = pu.oracle_fwd_bwd(w, hx, osel, ocnt)
+        for name, got, want in (("O", o, ref["o"]), ("dQ", dq, ref["dq"]), ("dK", x["dk_pool"], ref["dk_pool"]), ("dV", x["dv_pool"], ref["dv_pool"])):
+            pu.check(name, pu.f32(got), want, dtype)

@@ -1,6 +1,10 @@
 """Python binding of the C-ABI library (include/oomb.h): argument marshalling
 only.  Torch supplies device memory and the stream; every step of the path runs
-in the library's HIP kernels.  Function names mirror the C entry points."""
+in the library's HIP kernels.  Function names mirror the C entry points.
+
+The calls of a loop over chunks go through the native module _binding (csrc/binding.cpp), which checks the tensors against
+the descriptor and calls the library; it answers -1 if something does not fit, and the checks here then say what.
+The other entry points are marshalled with ctypes."""
 from __future__ import annotations
 
 import ctypes
@@ -114,6 +118,29 @@ def lib():
     return _lib
 
 
+_nb = None
+
+
+def _native():
+    """The native module; like the library it has no fallback."""
+    global _nb
+    if _nb is None:
+        lib()
+        from . import _binding
+        _nb = _binding
+    return _nb
+
+
+def _refused(where: str):
+    """The native module found a tensor that does not fit, and no check here said which."""
+    return OombError(ERR_INVALID_ARG, f"{where}: an argument is no device tensor or does not fit the descriptor")
+
+
+def _no_workspace(desc, top_k: int, op: int) -> bool:
+    """Whether the descriptor is one that oomb_workspace_bytes refuses, which takes precedence over the status of the call."""
+    return workspace_bytes(desc, top_k, op) == 0 and (op == OP_SCORE_TOPK or top_k >= 0 or workspace_bytes(desc, -1, op) == 0)
+
+
 def status_string(status: int) -> str:
     return lib().oomb_status_string(int(status)).decode()
 
@@ -133,6 +160,10 @@ def _dt(t: torch.dtype) -> int:
 def make_desc(q: torch.Tensor, k_pool: torch.Tensor, ctx_len: int, sm_scale: float,
               grad_dtype: torch.dtype = torch.float32) -> AttnDesc:
     """Descriptor from a query chunk [C][Hq][D] and a K pool [n_phys][Hkv][P][D]."""
+    if grad_dtype is torch.float32 or grad_dtype is torch.bfloat16:
+        desc = AttnDesc()
+        if (_nb or _native()).make_desc(desc, q, k_pool, ctx_len, sm_scale, grad_dtype is torch.bfloat16) == 0:
+            return desc
     C, Hq, D = q.shape
     n_phys, Hkv, P, D2 = k_pool.shape
     assert D == D2 and q.stride(2) == 1 and k_pool.stride(3) == 1
@@ -180,15 +211,17 @@ def workspace_bytes(desc: AttnDesc, top_k: int, op: int) -> int:
     return int(lib().oomb_workspace_bytes(ctypes.byref(desc), int(top_k), int(op)))
 
 
-def _workspace(desc, top_k, op, device, workspace):
-    need = workspace_bytes(desc, top_k, op)
-    if need == 0 and op != OP_SCORE_TOPK and top_k < 0:
-        need = workspace_bytes(desc, -1, op)
-    if need == 0:
+def _workspace(desc, top_k, op, device):
+    if _no_workspace(desc, top_k, op):
         raise OombError(ERR_INVALID_ARG, "oomb_workspace_bytes")
-    if workspace is None:
-        workspace = torch.empty(need, dtype=torch.uint8, device=device)
-    return workspace, workspace.numel() * workspace.element_size()
+    return torch.empty(workspace_bytes(desc, top_k, op), dtype=torch.uint8, device=device)
+
+
+def _failed(st: int, where: str, desc, top_k: int, op: int):
+    """The error of a call that returned `st`."""
+    if _no_workspace(desc, top_k, op):
+        return OombError(ERR_INVALID_ARG, "oomb_workspace_bytes")
+    return _refused(where) if st < 0 else OombError(st, where)
 
 
 def page_score_topk(desc: AttnDesc, q, k_pool, page_table, top_k: int, sel_pages=None, sel_count=None,
@@ -199,12 +232,11 @@ def page_score_topk(desc: AttnDesc, q, k_pool, page_table, top_k: int, sel_pages
         sel_pages = torch.empty((desc.n_kv_heads, top_k + m), dtype=torch.int32, device=q.device)
     if sel_count is None:
         sel_count = torch.empty((desc.n_kv_heads,), dtype=torch.int32, device=q.device)
-    workspace, nbytes = _workspace(desc, top_k, OP_SCORE_TOPK, q.device, workspace)
-    st = lib().oomb_page_score_topk(ctypes.byref(desc), _p(q), _p(k_pool), _p(page_table), int(top_k),
-                                    _p(sel_pages), _p(sel_count), _p(scores_out), _p(workspace), nbytes,
-                                    _stream(q))
+    if workspace is None:
+        workspace = _workspace(desc, top_k, OP_SCORE_TOPK, q.device)
+    st = (_nb or _native()).score_topk(desc, q, k_pool, page_table, top_k, sel_pages, sel_count, scores_out, workspace)
     if st != OK:
-        raise OombError(st, "oomb_page_score_topk")
+        raise _failed(st, "oomb_page_score_topk", desc, top_k, OP_SCORE_TOPK)
     return sel_pages, sel_count
 
 
@@ -217,6 +249,11 @@ def page_score_topk_noalloc(desc: AttnDesc, q, k_pool, page_table, top_k: int, s
     return sel_pages, sel_count
 
 
+def _list_k(desc, sel_pages) -> int:
+    """top_k of oomb_workspace_bytes for one list per KV head: the lists' row stride less the local pages, -1 without lists"""
+    return -1 if sel_pages is None else int(sel_pages.stride(0)) - desc.chunk_len // desc.page_size
+
+
 def paged_attn_fwd(desc: AttnDesc, q, k_pool, v_pool, page_table, sel_pages=None, sel_count=None, o=None,
                    lse=None, workspace=None):
     """oomb_paged_attn_fwd.  Returns (O [C][Hq][D], LSE [Hq][C] float32)."""
@@ -224,15 +261,13 @@ def paged_attn_fwd(desc: AttnDesc, q, k_pool, v_pool, page_table, sel_pages=None
         o = torch.empty_like(q)
     if lse is None:
         lse = torch.empty((desc.n_q_heads, desc.chunk_len), dtype=torch.float32, device=q.device)
-    _check_family("oomb_paged_attn_fwd", desc, q, k_pool, rows=[("o", o)], pools=[("v_pool", v_pool)], lse=lse)
-    stride = 0 if sel_pages is None else int(sel_pages.stride(0))
-    list_k = -1 if sel_pages is None else stride - desc.chunk_len // desc.page_size
-    workspace, nbytes = _workspace(desc, list_k, OP_ATTN_FWD, q.device, workspace)
-    st = lib().oomb_paged_attn_fwd(ctypes.byref(desc), _p(q), _p(k_pool), _p(v_pool), _p(page_table),
-                                   _p(sel_pages), _p(sel_count), stride, _p(o), _p(lse), _p(workspace), nbytes,
-                                   _stream(q))
+    if workspace is None:
+        _check_family("oomb_paged_attn_fwd", desc, q, k_pool, rows=[("o", o)], pools=[("v_pool", v_pool)], lse=lse)
+        workspace = _workspace(desc, _list_k(desc, sel_pages), OP_ATTN_FWD, q.device)
+    st = (_nb or _native()).attn_fwd(desc, q, k_pool, v_pool, page_table, sel_pages, sel_count, o, lse, workspace)
     if st != OK:
-        raise OombError(st, "oomb_paged_attn_fwd")
+        _check_family("oomb_paged_attn_fwd", desc, q, k_pool, rows=[("o", o)], pools=[("v_pool", v_pool)], lse=lse)
+        raise _failed(st, "oomb_paged_attn_fwd", desc, _list_k(desc, sel_pages), OP_ATTN_FWD)
     return o, lse
 
 
@@ -241,16 +276,16 @@ def paged_attn_bwd(desc: AttnDesc, q, k_pool, v_pool, page_table, o, lse, d_o, d
     """oomb_paged_attn_bwd.  Returns dQ; dk_pool / dv_pool are accumulated in place."""
     if d_q is None:
         d_q = torch.empty_like(q)
-    _check_family("oomb_paged_attn_bwd", desc, q, k_pool, rows=[("o", o), ("d_o", d_o), ("d_q", d_q)],
-                  pools=[("v_pool", v_pool)], grad_pools=[("dk_pool", dk_pool), ("dv_pool", dv_pool)], lse=lse)
-    stride = 0 if sel_pages is None else int(sel_pages.stride(0))
-    list_k = -1 if sel_pages is None else stride - desc.chunk_len // desc.page_size
-    workspace, nbytes = _workspace(desc, list_k, OP_ATTN_BWD, q.device, workspace)
-    st = lib().oomb_paged_attn_bwd(ctypes.byref(desc), _p(q), _p(k_pool), _p(v_pool), _p(page_table),
-                                   _p(sel_pages), _p(sel_count), stride, _p(o), _p(lse), _p(d_o), _p(d_q),
-                                   _p(dk_pool), _p(dv_pool), _p(workspace), nbytes, _stream(q))
+    def check():
+        _check_family("oomb_paged_attn_bwd", desc, q, k_pool, rows=[("o", o), ("d_o", d_o), ("d_q", d_q)],
+                      pools=[("v_pool", v_pool)], grad_pools=[("dk_pool", dk_pool), ("dv_pool", dv_pool)], lse=lse)
+    if workspace is None:
+        check()
+        workspace = _workspace(desc, _list_k(desc, sel_pages), OP_ATTN_BWD, q.device)
+    st = (_nb or _native()).attn_bwd(desc, q, k_pool, v_pool, page_table, sel_pages, sel_count, o, lse, d_o, d_q, dk_pool, dv_pool, workspace)
     if st != OK:
-        raise OombError(st, "oomb_paged_attn_bwd")
+        check()
+        raise _failed(st, "oomb_paged_attn_bwd", desc, _list_k(desc, sel_pages), OP_ATTN_BWD)
     return d_q
 
 
@@ -262,11 +297,11 @@ def page_vote_topk(desc: AttnDesc, q, kbar_cache, top_k: int, sel_pages=None, se
         sel_pages = torch.empty((desc.n_kv_heads, m, top_k + m), dtype=torch.int32, device=q.device)
     if sel_count is None:
         sel_count = torch.empty((desc.n_kv_heads, m), dtype=torch.int32, device=q.device)
-    workspace, nbytes = _workspace(desc, top_k, OP_VOTE_TOPK, q.device, workspace)
-    st = lib().oomb_page_vote_topk(ctypes.byref(desc), _p(q), _p(kbar_cache), top_k, _p(sel_pages), _p(sel_count),
-                                   _p(votes_out), _p(workspace), nbytes, _stream(q))
+    if workspace is None:
+        workspace = _workspace(desc, top_k, OP_VOTE_TOPK, q.device)
+    st = (_nb or _native()).vote_topk(desc, q, kbar_cache, top_k, sel_pages, sel_count, votes_out, workspace)
     if st != OK:
-        raise OombError(st, "oomb_page_vote_topk")
+        raise _failed(st, "oomb_page_vote_topk", desc, top_k, OP_VOTE_TOPK)
     return sel_pages, sel_count
 
 
@@ -382,14 +417,15 @@ def paged_attn_fwd_qp(desc: AttnDesc, q, k_pool, v_pool, page_table, sel_pages, 
         o = torch.empty_like(q)
     if lse is None:
         lse = torch.empty((desc.n_q_heads, desc.chunk_len), dtype=torch.float32, device=q.device)
-    _check_family("oomb_paged_attn_fwd_qp", desc, q, k_pool, rows=[("o", o)], pools=[("v_pool", v_pool)], lse=lse)
-    stride, m = _qp_lists(desc, sel_pages, sel_count)
-    workspace, nbytes = _workspace(desc, stride - m, OP_ATTN_FWD_QP, q.device, workspace)
-    st = lib().oomb_paged_attn_fwd_qp(ctypes.byref(desc), _p(q), _p(k_pool), _p(v_pool), _p(page_table),
-                                      _p(sel_pages), _p(sel_count), stride, _p(o), _p(lse), _p(workspace), nbytes,
-                                      _stream(q))
+    def check():
+        _check_family("oomb_paged_attn_fwd_qp", desc, q, k_pool, rows=[("o", o)], pools=[("v_pool", v_pool)], lse=lse)
+        stride, m = _qp_lists(desc, sel_pages, sel_count)
+        return stride - m
+    if workspace is None:
+        workspace = _workspace(desc, check(), OP_ATTN_FWD_QP, q.device)
+    st = (_nb or _native()).attn_fwd_qp(desc, q, k_pool, v_pool, page_table, sel_pages, sel_count, o, lse, workspace)
     if st != OK:
-        raise OombError(st, "oomb_paged_attn_fwd_qp")
+        raise _failed(st, "oomb_paged_attn_fwd_qp", desc, check(), OP_ATTN_FWD_QP)
     return o, lse
 
 
@@ -398,15 +434,16 @@ def paged_attn_bwd_qp(desc: AttnDesc, q, k_pool, v_pool, page_table, o, lse, d_o
     """oomb_paged_attn_bwd_qp.  Returns dQ; dk_pool / dv_pool are accumulated in place."""
     if d_q is None:
         d_q = torch.empty_like(q)
-    _check_family("oomb_paged_attn_bwd_qp", desc, q, k_pool, rows=[("o", o), ("d_o", d_o), ("d_q", d_q)],
-                  pools=[("v_pool", v_pool)], grad_pools=[("dk_pool", dk_pool), ("dv_pool", dv_pool)], lse=lse)
-    stride, m = _qp_lists(desc, sel_pages, sel_count)
-    workspace, nbytes = _workspace(desc, stride - m, OP_ATTN_BWD_QP, q.device, workspace)
-    st = lib().oomb_paged_attn_bwd_qp(ctypes.byref(desc), _p(q), _p(k_pool), _p(v_pool), _p(page_table),
-                                      _p(sel_pages), _p(sel_count), stride, _p(o), _p(lse), _p(d_o), _p(d_q),
-                                      _p(dk_pool), _p(dv_pool), _p(workspace), nbytes, _stream(q))
+    def check():
+        _check_family("oomb_paged_attn_bwd_qp", desc, q, k_pool, rows=[("o", o), ("d_o", d_o), ("d_q", d_q)],
+                      pools=[("v_pool", v_pool)], grad_pools=[("dk_pool", dk_pool), ("dv_pool", dv_pool)], lse=lse)
+        stride, m = _qp_lists(desc, sel_pages, sel_count)
+        return stride - m
+    if workspace is None:
+        workspace = _workspace(desc, check(), OP_ATTN_BWD_QP, q.device)
+    st = (_nb or _native()).attn_bwd_qp(desc, q, k_pool, v_pool, page_table, sel_pages, sel_count, o, lse, d_o, d_q, dk_pool, dv_pool, workspace)
     if st != OK:
-        raise OombError(st, "oomb_paged_attn_bwd_qp")
+        raise _failed(st, "oomb_paged_attn_bwd_qp", desc, check(), OP_ATTN_BWD_QP)
     return d_q
 
 
@@ -446,14 +483,14 @@ def calibrate(which: int, buf) -> float:
 
 def kv_append(desc: AttnDesc, k_chunk, v_chunk, page_table, k_pool, v_pool, kbar_cache=None) -> None:
     """oomb_kv_append: the chunk's K / V [C][Hkv][D] into its local pages (+ their means into kbar_cache)."""
+    st = (_nb or _native()).kv_append(desc, k_chunk, v_chunk, page_table, k_pool, v_pool, kbar_cache)
+    if st == OK:
+        return
     if not (k_chunk.is_contiguous() and v_chunk.is_contiguous()) or k_chunk.shape != v_chunk.shape or \
             k_chunk.dtype != k_pool.dtype or v_chunk.dtype != k_pool.dtype:
         raise OombError(ERR_INVALID_ARG, "oomb_kv_append: k_chunk / v_chunk must be contiguous [C][Hkv][D] of the pools' dtype")
     _like("oomb_kv_append", "v_pool", v_pool, k_pool)
-    st = lib().oomb_kv_append(ctypes.byref(desc), _p(k_chunk), _p(v_chunk), _p(page_table), _p(k_pool), _p(v_pool),
-                              _p(kbar_cache), _stream(k_pool))
-    if st != OK:
-        raise OombError(st, "oomb_kv_append")
+    raise _refused("oomb_kv_append") if st < 0 else OombError(st, "oomb_kv_append")
 
 
 class PagePool:
@@ -503,11 +540,11 @@ def page_score_topk_cached(desc: AttnDesc, q, kbar_cache, top_k: int, sel_pages=
         sel_pages = torch.empty((desc.n_kv_heads, top_k + m), dtype=torch.int32, device=q.device)
     if sel_count is None:
         sel_count = torch.empty((desc.n_kv_heads,), dtype=torch.int32, device=q.device)
-    workspace, nbytes = _workspace(desc, top_k, OP_SCORE_TOPK, q.device, workspace)
-    st = lib().oomb_page_score_topk_cached(ctypes.byref(desc), _p(q), _p(kbar_cache), int(top_k), _p(sel_pages),
-                                           _p(sel_count), _p(scores_out), _p(workspace), nbytes, _stream(q))
+    if workspace is None:
+        workspace = _workspace(desc, top_k, OP_SCORE_TOPK, q.device)
+    st = (_nb or _native()).score_topk_cached(desc, q, kbar_cache, top_k, sel_pages, sel_count, scores_out, workspace)
     if st != OK:
-        raise OombError(st, "oomb_page_score_topk_cached")
+        raise _failed(st, "oomb_page_score_topk_cached", desc, top_k, OP_SCORE_TOPK)
     return sel_pages, sel_count
 
 
@@ -518,8 +555,7 @@ def local_page_list(desc: AttnDesc, window_pages: int, device, sel_pages=None, s
         sel_pages = torch.empty((desc.n_kv_heads, window_pages + m), dtype=torch.int32, device=device)
     if sel_count is None:
         sel_count = torch.empty((desc.n_kv_heads,), dtype=torch.int32, device=device)
-    st = lib().oomb_local_page_list(ctypes.byref(desc), int(window_pages), _p(sel_pages), _p(sel_count),
-                                    _stream(sel_pages))
+    st = (_nb or _native()).local_page_list(desc, window_pages, sel_pages, sel_count)
     if st != OK:
-        raise OombError(st, "oomb_local_page_list")
+        raise _refused("oomb_local_page_list") if st < 0 else OombError(st, "oomb_local_page_list")
     return sel_pages, sel_count

@@ -296,10 +296,17 @@ size_t bwd_mfma_min_bytes(const Params& p, int32_t max_list_len) {
 }
 size_t bwd_mfma_workspace_bytes(const Params& p, int32_t max_list_len) {
   const size_t rows = rows_take_generic(p, max_list_len, true) ? dq_generic_part_bytes(p, true, max_list_len) : 0, stats = stats_bytes(p);
-  return (rows > stats ? rows : stats) + bias_bytes(p) + dkv_partial_bytes(p, max_list_len, dkv_splits(p, max_list_len, true));
+  const size_t two = (rows > stats ? rows : stats) + bias_bytes(p) + dkv_partial_bytes(p, max_list_len, dkv_splits(p, max_list_len, true));
+  const size_t pair = bwd_takes_pair(p, true, max_list_len) ? bwd_pair_bytes(p, true, max_list_len) : 0;
+  return pair > two ? pair : two;
 }
 
 hipError_t launch_bwd_mfma(const Params& p, int32_t max_list_len, void* ws, size_t ws_bytes, hipStream_t st) {
+  if (bwd_takes_pair(p, true, max_list_len)) {
+    ProfScope prof_q("bwd_dq_mfma", st), prof_kv("bwd_dkv_mfma", st);   // (one launch for both)
+    bool done = false;
+    if (hipError_t e = launch_bwd_pair_bf16_128(p, max_list_len, ws, ws_bytes, st, &done); done || e != hipSuccess) return e;
+  }
   // (a workspace sized for another list length may have room for fewer slices or dQ partials)
   int32_t n_split = dkv_splits(p, max_list_len, true);
   if (stats_bytes(p) + bias_bytes(p) + dkv_partial_bytes(p, max_list_len, n_split) > ws_bytes) n_split = dkv_splits(p, max_list_len, false);

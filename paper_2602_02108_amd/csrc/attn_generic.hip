@@ -74,6 +74,20 @@ template <typename T> __device__ __forceinline__ void gn_mma(const u32x4_t& a, c
   }
 }
 
+// c + <a, b> over 16 bytes each
+template <typename T> __device__ __forceinline__ float gn_dot(const u32x4_t& a, const u32x4_t& b, float c) {
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    if constexpr (sizeof(T) == 2) {
+      c = __builtin_fmaf(__uint_as_float(a[k] << 16), __uint_as_float(b[k] << 16), c);
+      c = __builtin_fmaf(__uint_as_float(a[k] & 0xffff0000u), __uint_as_float(b[k] & 0xffff0000u), c);
+    } else {
+      c = __builtin_fmaf(__uint_as_float(a[k]), __uint_as_float(b[k]), c);
+    }
+  }
+  return c;
+}
+
 template <int N> __device__ __forceinline__ void gn_zero(f32x16 (&v)[N]) {
 #pragma unroll
   for (int k = 0; k < N; ++k)
@@ -311,8 +325,8 @@ template <typename T, int D> struct GnStream {
 // workgroup -> (KV head, row tile, split).  The head varies fastest: workgroups are dealt round-robin to the
 // XCDs, so with 1, 2, 4 or 8 KV heads every head keeps to its own XCDs and their L2.
 struct GnBlock { int g; int32_t tile, split; };
-__device__ __forceinline__ GnBlock gn_block(const Params& p, int32_t tiles, int32_t n_split) {
-  const int32_t b = blockIdx.x, rest = b / p.Hkv;
+__device__ __forceinline__ GnBlock gn_block(const Params& p, int32_t b, int32_t tiles, int32_t n_split) {
+  const int32_t rest = b / p.Hkv;
   return {b - rest * p.Hkv, tiles - 1 - rest / n_split, rest % n_split};   // late rows see more pages: they start first
 }
 
@@ -352,7 +366,7 @@ __global__ __launch_bounds__(256 * KH, 2) void fwd_generic_kernel(Params p, int3
   typedef GnTiles<T, D> Y;
   extern __shared__ __align__(16) unsigned char smem[];
   const int lane = threadIdx.x & 63, hh = lane >> 5, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), rb = wave & 3, group = wave >> 2;
-  const GnBlock b = gn_block(p, tiles, n_split);
+  const GnBlock b = gn_block(p, blockIdx.x, tiles, n_split);
   const GnRange kr = gn_range(max_len, lp, Y::KT, KH * b.split + group, KH * n_split);
   const GnRange other = gn_range(max_len, lp, Y::KT, KH * b.split + (KH - 1 - group), KH * n_split);
   const GnTile t = gn_tile(p, b.g, b.tile, rb, lane, lp, max_len);
@@ -585,13 +599,12 @@ __global__ __launch_bounds__(256) void fwd_combine_kernel(Params p, int32_t tile
 // Also computes Delta = <dO, O> of its rows for the dK / dV kernel, which runs afterwards: p.delta, or (bias != nullptr) the
 // bias words from which attn_bwd_dkv_mfma.hip starts its accumulators.
 template <typename T, int D, int KH>
-__global__ __launch_bounds__(256 * KH, (Gn<T, D>::RB == 512 ? 1 : 2)) void dq_generic_kernel(Params p, int32_t tiles, int32_t n_split, int lp,
-                                                                                             int32_t max_len, float* __restrict__ part, float* __restrict__ bias, int32_t n_stages) {
+__device__ __forceinline__ void dq_body(const Params& p, unsigned char* smem, int32_t block, int32_t tiles, int32_t n_split, int lp, int32_t max_len,
+                                        float* __restrict__ part, float* __restrict__ bias, int32_t n_stages) {
   typedef Gn<T, D> X;
   typedef GnTiles<T, D> Y;
-  extern __shared__ __align__(16) unsigned char smem[];
   const int lane = threadIdx.x & 63, hh = lane >> 5, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), rb = wave & 3, group = wave >> 2;
-  const GnBlock b = gn_block(p, tiles, n_split);
+  const GnBlock b = gn_block(p, block, tiles, n_split);
   const GnRange kr = gn_range(max_len, lp, Y::KT, KH * b.split + group, KH * n_split);
   const GnRange other = gn_range(max_len, lp, Y::KT, KH * b.split + (KH - 1 - group), KH * n_split);
   const GnTile t = gn_tile(p, b.g, b.tile, rb, lane, lp, max_len);
@@ -606,16 +619,7 @@ __global__ __launch_bounds__(256 * KH, (Gn<T, D>::RB == 512 ? 1 : 2)) void dq_ge
     const int64_t at = roff * X::ES + 32 * j + 16 * hh;
     qf[j] = *reinterpret_cast<const u32x4_t*>((const unsigned char*)p.q + at);
     dof[j] = *reinterpret_cast<const u32x4_t*>((const unsigned char*)p.d_o + at);
-    const u32x4_t ov = *reinterpret_cast<const u32x4_t*>((const unsigned char*)p.o + at);
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      if constexpr (X::BF) {
-        delta = __builtin_fmaf(__uint_as_float(dof[j][k] << 16), __uint_as_float(ov[k] << 16), delta);
-        delta = __builtin_fmaf(__uint_as_float(dof[j][k] & 0xffff0000u), __uint_as_float(ov[k] & 0xffff0000u), delta);
-      } else {
-        delta = __builtin_fmaf(__uint_as_float(dof[j][k]), __uint_as_float(ov[k]), delta);
-      }
-    }
+    delta = gn_dot<T>(dof[j], *reinterpret_cast<const u32x4_t*>((const unsigned char*)p.o + at), delta);
   }
   delta = half_sum(delta);
   const float lse2 = p.lse[(int64_t)t.h * p.C + t.i] * 1.4426950408889634f;
@@ -629,7 +633,7 @@ __global__ __launch_bounds__(256 * KH, (Gn<T, D>::RB == 512 ? 1 : 2)) void dq_ge
       float* w = bias + (((int64_t)b.g * n_stages + (r >> 6)) * 2) * 64 + (r & 63);
       w[0] = -lse2 / c;
       w[64] = -delta;
-    } else {
+    } else if (p.delta) {
       p.delta[(int64_t)t.h * p.C + t.i] = delta;
     }
   }
@@ -694,6 +698,12 @@ __global__ __launch_bounds__(256 * KH, (Gn<T, D>::RB == 512 ? 1 : 2)) void dq_ge
     part_emit<T, D>(dq, hh, [&](int d, float v0, float v1, float v2, float v3) { part_store4<T>(dst + d, v0 * sc, v1 * sc, v2 * sc, v3 * sc); });
   }
 }
+template <typename T, int D, int KH>
+__global__ __launch_bounds__(256 * KH, (Gn<T, D>::RB == 512 ? 1 : 2)) void dq_generic_kernel(Params p, int32_t tiles, int32_t n_split, int lp, int32_t max_len,
+                                                                                             float* __restrict__ part, float* __restrict__ bias, int32_t n_stages) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  dq_body<T, D, KH>(p, smem, blockIdx.x, tiles, n_split, lp, max_len, part, bias, n_stages);
+}
 
 // ---- dK / dV ------------------------------------------------------------------------------------
 // A workgroup owns a unit of up to 128 keys of a KV head -- 128 / P consecutive list entries, or (one
@@ -703,14 +713,13 @@ template <typename T, int D> struct GnKey {
   static constexpr int KT = GnTiles<T, D>::KT;
   static constexpr int STAT = 2 * GnTiles<T, D>::BUF, LDS = STAT + 2 * 2 * 64 * 4;   // two buffers, {lse2, delta} of their rows
 };
-template <typename T, typename TG, int D>
-__global__ __launch_bounds__(256, (D == 128 || sizeof(T) == 4 ? 1 : 2)) void dkv_generic_kernel(Params p, int32_t n_split, int lp, float* __restrict__ part) {
+template <typename T, typename TG, int D, bool OWN_DELTA>
+__device__ __forceinline__ void dkv_body(const Params& p, unsigned char* smem, int32_t bid, int32_t n_split, int lp, float* __restrict__ part) {
   typedef Gn<T, D> X;
   typedef GnKey<T, D> R;
   typedef GnTiles<T, D> Y;
-  extern __shared__ __align__(16) unsigned char smem[];
   const int tid = threadIdx.x, lane = tid & 63, hh = lane >> 5, lq = lane & 31, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int32_t bid = blockIdx.x, rest = bid / p.Hkv, g = bid - rest * p.Hkv;
+  const int32_t rest = bid / p.Hkv, g = bid - rest * p.Hkv;
   int32_t e0, sp = 0, q0 = 0, qc = 0, slot = -1;
   if (p.qp) {
     const int32_t n_units = p.unit_count[g];
@@ -773,6 +782,10 @@ __global__ __launch_bounds__(256, (D == 128 || sizeof(T) == 4 ? 1 : 2)) void dkv
     }
   };
   float st_l = INFINITY, st_d = 0.f;   // statistics of row `tid` of the stage under way
+  // OWN_DELTA: Delta of the stage's rows from dO and O themselves, TPR threads per row
+  constexpr int TPR = 256 / R::KT, DG = X::NG / TPR;
+  u32x4_t dl_o[OWN_DELTA ? DG : 1], dl_do[OWN_DELTA ? DG : 1];
+  bool dl_ok = false;
   auto copy = [&](int32_t s, uint32_t buf) {
     int32_t base, end;
     stage_rows(s, base, end);
@@ -797,7 +810,19 @@ __global__ __launch_bounds__(256, (D == 128 || sizeof(T) == 4 ? 1 : 2)) void dkv
         const int32_t i = (int32_t)div_g(p, (uint32_t)r);
         const int64_t at = (int64_t)(g * p.G + (r - i * p.G)) * p.C + i;
         st_l = p.lse[at] * 1.4426950408889634f;
-        st_d = p.delta[at];
+        if (!OWN_DELTA) st_d = p.delta[at];
+      }
+    }
+    if constexpr (OWN_DELTA) {
+      int32_t r = base + tid / TPR;
+      dl_ok = r < end;
+      r = dl_ok ? r : end - 1;
+      const int32_t i = (int32_t)div_g(p, (uint32_t)r);
+      const int64_t at = ((int64_t)i * p.q_tok_stride + (int64_t)(g * p.G + (r - i * p.G)) * p.q_head_stride) * X::ES + 16 * (tid % TPR);
+#pragma unroll
+      for (int k = 0; k < DG; ++k) {
+        dl_o[k] = *reinterpret_cast<const u32x4_t*>((const unsigned char*)p.o + at + 16 * TPR * k);
+        dl_do[k] = *reinterpret_cast<const u32x4_t*>((const unsigned char*)p.d_o + at + 16 * TPR * k);
       }
     }
   };
@@ -805,7 +830,15 @@ __global__ __launch_bounds__(256, (D == 128 || sizeof(T) == 4 ? 1 : 2)) void dkv
     float* st = reinterpret_cast<float*>(smem + R::STAT + (buf ? 512 : 0));
     if (tid < R::KT) {
       st[tid] = st_l;
-      st[64 + tid] = st_d;
+      if (!OWN_DELTA) st[64 + tid] = st_d;
+    }
+    if constexpr (OWN_DELTA) {
+      float sum = 0.f;
+#pragma unroll
+      for (int k = 0; k < DG; ++k) sum = gn_dot<T>(dl_do[k], dl_o[k], sum);
+#pragma unroll
+      for (int o = 1; o < TPR; o <<= 1) sum += __shfl_xor(sum, o, 64);
+      if (tid % TPR == 0) st[64 + tid / TPR] = dl_ok ? sum : 0.f;
     }
   };
 
@@ -888,6 +921,23 @@ __global__ __launch_bounds__(256, (D == 128 || sizeof(T) == 4 ? 1 : 2)) void dkv
     part_emit<T, D>(dk, hh, [&](int d, float v0, float v1, float v2, float v3) { part_add4<TG>(pk + d, v0 * sc, v1 * sc, v2 * sc, v3 * sc); });
     part_emit<T, D>(dv, hh, [&](int d, float v0, float v1, float v2, float v3) { part_add4<TG>(pv + d, v0, v1, v2, v3); });
   }
+}
+template <typename T, typename TG, int D>
+__global__ __launch_bounds__(256, (D == 128 || sizeof(T) == 4 ? 1 : 2)) void dkv_generic_kernel(Params p, int32_t n_split, int lp, float* __restrict__ part) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  dkv_body<T, TG, D, false>(p, smem, blockIdx.x, n_split, lp, part);
+}
+
+// dQ and dK / dV of a short call in one launch: the first kv_blocks workgroups take the keys, the others the rows; neither
+// waits for the other (each computes Delta itself).  8 us of launch and start-up less than one after the other, where
+// neither fills the chip.
+template <typename T, typename TG, int D>
+__global__ __launch_bounds__(256, (D == 128 || sizeof(T) == 4 ? 1 : 2)) void bwd_pair_kernel(Params p, int32_t kv_blocks, int32_t kv_split, float* __restrict__ kv_part,
+                                                                                            int32_t tiles, int32_t n_split, int lp, int32_t max_len,
+                                                                                            float* __restrict__ part) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  if ((int32_t)blockIdx.x < kv_blocks) dkv_body<T, TG, D, true>(p, smem, blockIdx.x, kv_split, lp, kv_part);
+  else dq_body<T, D, 1>(p, smem, (int32_t)blockIdx.x - kv_blocks, tiles, n_split, lp, max_len, part, nullptr, 0);
 }
 
 // What is left of a backward with splits, in one launch: workgroups below dq_blocks add the dQ partials, the others
@@ -1001,6 +1051,38 @@ static int32_t gn_key_splits(const Params& p, bool bf, int32_t max_len) {
   return (int32_t)s;
 }
 
+// A backward in one launch (bwd_pair_kernel), by the same kind of estimate: splits of keys and rows so that all
+// workgroups run at once (256, or 512 at head dim 64 with bf16: two per compute unit) and the longer of the two is
+// shortest.  us: huge where the call does not fit that way.
+struct GnPair { int32_t kv_split, row_split; float us; };
+// us of a stage of KT rows x 128 keys in the dK / dV kernel
+static float gn_stage_us(const Params& p, bool bf) { return bf ? (p.D == 128 ? 2.6f : 1.5f) : (p.D == 128 ? 10.f : 5.f); }
+static GnPair gn_pair(const Params& p, bool bf, int32_t max_len) {
+  GnPair best = {1, 1, 1e30f};
+  const int32_t slots = bf && p.D == 64 ? 512 : 256, wq = gn_tiles(p.C, p.G, p.P, p.m, p.qp) * p.Hkv, wk = gn_key_units(p, max_len) * p.Hkv;
+  if (p.qp || 2 * wq > slots || 2 * wk > slots) return best;
+  const float kt = bf ? 64.f : 32.f, nt = (max_len - 0.5f * p.m) * p.P / kt, stages = (float)p.C * p.G / kt;
+  const float tile = bf ? (p.D == 128 ? 1.2f : 0.8f) : (p.D == 128 ? 7.f : 3.5f), stage = gn_stage_us(p, bf);
+  for (int32_t nk = 1; nk <= 16 && (nk == 1 || nk <= stages); ++nk) {
+    if (wk * nk + wq > slots) break;
+    int32_t ns = (slots - wk * nk) / wq;
+    ns = ns > 32 ? 32 : ns > nt ? (nt < 1.f ? 1 : (int32_t)nt) : ns;
+    const float tq = (nt / ns > 1.f ? nt / ns : 1.f) * tile + 6.f, tk = (stages / nk > 1.f ? stages / nk : 1.f) * stage + 8.f;
+    const float us = (tq > tk ? tq : tk) + (wk * nk * 2.f + wq * ns) * p.D * 2.56e-4f;
+    if (us < best.us) best = {nk, ns, us};
+  }
+  return best;
+}
+// against dQ and dK / dV one after the other, each with the chip to itself
+static bool gn_takes_pair(const Params& p, bool bf, int32_t max_len, const GnPair& pair) {
+  if (pair.us > 1e29f) return false;
+  const float stages = (float)p.C * p.G / (bf ? 64.f : 32.f);
+  const float stage = bf && p.D == HD && p.P == TP ? 1.75f : gn_stage_us(p, bf);   // (the kernel of pages of 128 has two roles per pair of waves)
+  int32_t n = 256 / (gn_key_units(p, max_len) * p.Hkv);
+  n = n > 16 ? 16 : n > stages ? (stages < 1.f ? 1 : (int32_t)stages) : n;
+  return pair.us < gn_plan(p, bf, max_len, true).us + stages / (n < 1 ? 1 : n) * stage + 9.f;
+}
+
 static size_t gn_row_blocks(const Params& p) { return (size_t)gn_tiles(p.C, p.G, p.P, p.m, p.qp) * p.Hkv * 4; }
 // splits that fit `bytes` of partial results of `per` bytes each (at least 1: no partial results)
 static int32_t gn_fit(size_t bytes, size_t per) { return (int32_t)(bytes / per > 32 ? 32 : bytes / per < 2 ? 1 : bytes / per); }
@@ -1014,10 +1096,16 @@ static size_t gn_key_part_bytes(const Params& p, int32_t max_len, int32_t split)
   const size_t slots = p.qp ? (size_t)p.Hkv * qp_max_pslots(p, p.sel_stride) : split > 1 ? (size_t)gn_key_units(p, max_len) * p.Hkv * split : 0;
   return gn_up(slots * 2 * GN_ROWS * p.D * 4);
 }
+static size_t gn_pair_bytes(const Params& p, int32_t max_len, const GnPair& t) {
+  return gn_key_part_bytes(p, max_len, t.kv_split) + gn_row_part_bytes(p, t.row_split);
+}
+bool bwd_takes_pair(const Params& p, bool bf, int32_t max_len) { return gn_takes_pair(p, bf, max_len, gn_pair(p, bf, max_len)); }
+size_t bwd_pair_bytes(const Params& p, bool bf, int32_t max_len) { return gn_pair_bytes(p, max_len, gn_pair(p, bf, max_len)); }
 size_t bwd_generic_min_bytes(const Params& p) { return gn_up((size_t)p.Hq * p.C * sizeof(float)) + gn_key_part_bytes(p, 0, 1); }
 size_t bwd_generic_workspace_bytes(const Params& p, bool bf, int32_t max_len) {
-  return gn_up((size_t)p.Hq * p.C * sizeof(float)) + dq_generic_part_bytes(p, bf, max_len) +
-         gn_key_part_bytes(p, max_len, gn_key_splits(p, bf, max_len));
+  const size_t delta = gn_up((size_t)p.Hq * p.C * sizeof(float)), pair = bwd_takes_pair(p, bf, max_len) ? bwd_pair_bytes(p, bf, max_len) : 0;
+  const size_t two = delta + dq_generic_part_bytes(p, bf, max_len) + gn_key_part_bytes(p, max_len, gn_key_splits(p, bf, max_len));
+  return pair > two ? pair : two;
 }
 
 template <typename T, int D, int KH>
@@ -1093,8 +1181,33 @@ hipError_t launch_bwd_finish(const Params& p, bool bf, int32_t dq_split, const f
 #undef OOMB_FINISH
 }
 
+// The one-launch backward, if the shape takes it and the workspace has room (else *done stays false)
+template <typename T, typename TG, int D>
+static hipError_t bwd_pair(Params p, int32_t max_len, void* ws, size_t ws_bytes, hipStream_t st, bool* done) {
+  const GnPair t = gn_pair(p, Gn<T, D>::BF, max_len);
+  if (!gn_takes_pair(p, Gn<T, D>::BF, max_len, t) || gn_pair_bytes(p, max_len, t) > ws_bytes) return hipSuccess;
+  *done = true;
+  constexpr int LDS = GnKey<T, D>::LDS > GnRow<T, D, 1>::LDS ? GnKey<T, D>::LDS : GnRow<T, D, 1>::LDS;
+  static DeviceOnce once;
+  if (hipError_t e = ensure_max_dynamic_lds(once, (const void*)bwd_pair_kernel<T, TG, D>, LDS); e != hipSuccess) return e;
+  p.delta = nullptr;
+  float* kv_part = (float*)ws;
+  float* dq_part = (float*)((unsigned char*)ws + gn_key_part_bytes(p, max_len, t.kv_split));
+  const int32_t tiles = gn_tiles(p.C, p.G, p.P, p.m, p.qp), units = gn_key_units(p, max_len), kv_blocks = units * p.Hkv * t.kv_split;
+  bwd_pair_kernel<T, TG, D><<<dim3((unsigned)(kv_blocks + tiles * p.Hkv * t.row_split)), dim3(256), LDS, st>>>(
+      p, kv_blocks, t.kv_split, kv_part, tiles, t.row_split, __builtin_ctz(p.P), gn_list_len(p, max_len), dq_part);
+  if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
+  return bwd_finish<T, TG, D>(p, t.row_split, dq_part, t.kv_split > 1 ? units : 0, t.kv_split, kv_part, st);
+}
+hipError_t launch_bwd_pair_bf16_128(const Params& p, int32_t max_len, void* ws, size_t ws_bytes, hipStream_t st, bool* done) {
+  return p.grad_is_bf16 ? bwd_pair<bf16_t, bf16_t, 128>(p, max_len, ws, ws_bytes, st, done) : bwd_pair<bf16_t, float, 128>(p, max_len, ws, ws_bytes, st, done);
+}
+
 template <typename T, typename TG, int D>
 static hipError_t bwd_generic(Params p, int32_t max_len, void* ws, size_t ws_bytes, hipStream_t st) {
+  ProfScope prof_("attn_bwd_generic", st);
+  bool done = false;
+  if (hipError_t e = bwd_pair<T, TG, D>(p, max_len, ws, ws_bytes, st, &done); done || e != hipSuccess) return e;
   static DeviceOnce once_kv;
   if (hipError_t e = ensure_max_dynamic_lds(once_kv, (const void*)dkv_generic_kernel<T, TG, D>, GnKey<T, D>::LDS); e != hipSuccess) return e;
   // [Delta][dK / dV slices][dQ partials]; a workspace without room for the slices of this call takes fewer
@@ -1108,7 +1221,6 @@ static hipError_t bwd_generic(Params p, int32_t max_len, void* ws, size_t ws_byt
   float* dq_part = (float*)(w + gn_key_part_bytes(p, max_len, nk));
   left -= gn_key_part_bytes(p, max_len, nk);
   const int32_t units = p.qp ? p.max_units : gn_key_units(p, max_len);
-  ProfScope prof_("attn_bwd_generic", st);
   int32_t ns = 1;
   hipError_t e = dq_generic<T, D>(p, max_len, dq_part, left, nullptr, 0, &ns, st);
   if (e != hipSuccess) return e;

@@ -85,66 +85,151 @@ __global__ __launch_bounds__(PLAN_THREADS) void offload_plan_kernel(Params p, in
   }
 }
 
-// Tile (slot s, KV head g): P rows of D elements.  The workgroups walk the tiles with stride gridDim.x.
-// MODE 0: fetch K and V (and zero the gradient staging tiles if given); MODE 1: add dK / dV back.
-template <int MODE, typename TG>
-__global__ __launch_bounds__(256) void offload_tile_kernel(Params p, const int32_t* __restrict__ slot_pages,
-                                                           const uint32_t* __restrict__ head_mask,
-                                                           const int32_t* __restrict__ n_slots, int32_t stage_cap,
-                                                           unsigned char* __restrict__ a_host, unsigned char* __restrict__ b_host,
-                                                           unsigned char* __restrict__ a_stage, unsigned char* __restrict__ b_stage,
-                                                           unsigned char* __restrict__ ga_stage, unsigned char* __restrict__ gb_stage,
-                                                           int es, int gs) {
-  const int32_t slots = n_slots[0] < stage_cap ? n_slots[0] : stage_cap;
-  for (int32_t tile = blockIdx.x; tile < slots * p.Hkv; tile += gridDim.x) {
-    const int32_t slot = tile / p.Hkv;
-    const int g = tile - slot * p.Hkv;
-    const int32_t l = slot_pages[slot];
-    if (l < 0 || l >= p.n || !((head_mask[l] >> g) & 1u)) continue;
-    const int64_t h_off = (int64_t)p.page_table[l] * p.pool_page_stride + (int64_t)g * p.pool_head_stride;
-    const int64_t s_off = (int64_t)slot * p.pool_page_stride + (int64_t)g * p.pool_head_stride;
-    if (MODE == 0) {
-      const int gran = p.D * es / 16;  // 16-byte granules per token row
-      for (int x = threadIdx.x; x < p.P * gran; x += 256) {
-        const int t = x / gran, c = x - t * gran;
-        const int64_t ho = (h_off + (int64_t)t * p.pool_tok_stride) * es + 16 * c;
-        const int64_t so = (s_off + (int64_t)t * p.pool_tok_stride) * es + 16 * c;
-        *reinterpret_cast<uint4*>(a_stage + so) = *reinterpret_cast<const uint4*>(a_host + ho);
-        *reinterpret_cast<uint4*>(b_stage + so) = *reinterpret_cast<const uint4*>(b_host + ho);
-      }
-      if (ga_stage) {
-        const int ggran = p.D * gs / 16;
-        for (int x = threadIdx.x; x < p.P * ggran; x += 256) {
-          const int t = x / ggran, c = x - t * ggran;
-          const int64_t so = (s_off + (int64_t)t * p.pool_tok_stride) * gs + 16 * c;
-          *reinterpret_cast<uint4*>(ga_stage + so) = make_uint4(0, 0, 0, 0);
-          *reinterpret_cast<uint4*>(gb_stage + so) = make_uint4(0, 0, 0, 0);
-        }
-      }
-    } else {
-      constexpr int EPG = 16 / (int)sizeof(TG);  // elements per granule
-      const int ggran = p.D / EPG;
-      for (int x = threadIdx.x; x < p.P * ggran; x += 256) {
-        const int t = x / ggran, c = x - t * ggran;
-        const int64_t ho = h_off + (int64_t)t * p.pool_tok_stride + EPG * c;
-        const int64_t so = s_off + (int64_t)t * p.pool_tok_stride + EPG * c;
-#pragma unroll
-        for (int which = 0; which < 2; ++which) {
-          TG* hp = (TG*)(which ? b_host : a_host) + ho;
-          const TG* sp = (const TG*)(which ? b_stage : a_stage) + so;
-          uint4 hv = *reinterpret_cast<const uint4*>(hp);
-          const uint4 sv = *reinterpret_cast<const uint4*>(sp);
-          TG* he = reinterpret_cast<TG*>(&hv);
-          const TG* se = reinterpret_cast<const TG*>(&sv);
-#pragma unroll
-          for (int e = 0; e < EPG; ++e) {
-            float sum = Elem<TG>::load(he + e) + Elem<TG>::load(se + e);
-            Elem<TG>::store(he + e, sum);
-          }
-          *reinterpret_cast<uint4*>(hp) = hv;
-        }
-      }
+// Tile (slot s, KV head g): P rows of D elements, in granules of 16 bytes.  The workgroups walk the held tiles with a stride of
+// `step`; a batch is BATCH granules per thread and tensor.  The link needs about 120 KB of reads under way, and a wave waits for
+// the stores that it issued before a load as well (one counter): so the loads of a batch are issued before the stores of the
+// batch in front of it, over the ends of tiles too.
+constexpr int BATCH = 4, TRANSFER_THREADS = 256;
+typedef uint32_t Granule __attribute__((ext_vector_type(4)));
+struct TileWalk {
+  const Params& p;
+  const int32_t* slot_pages;
+  const uint32_t* head_mask;
+  int32_t tiles, step, tile, shift, total, x;   // granules of a row: 1 << shift; of a tile: total
+  int64_t host, stage;                          // element offsets of the tile in the two pools
+
+  __device__ __forceinline__ TileWalk(const Params& p_, const int32_t* slot_pages_, const uint32_t* head_mask_, const int32_t* n_slots,
+                                      int32_t stage_cap, int32_t first, int32_t step_, int elem)
+      : p(p_), slot_pages(slot_pages_), head_mask(head_mask_), step(step_), tile(first - step_), shift(__builtin_ctz(p_.D * elem / 16)),
+        total(p_.P << shift), x(0), host(0), stage(0) {
+    tiles = (n_slots[0] < stage_cap ? n_slots[0] : stage_cap) * p.Hkv;
+    next_tile();
+  }
+  __device__ __forceinline__ bool more() const { return tile < tiles; }
+  __device__ __forceinline__ void next_tile() {
+    x = 0;
+    for (tile += step; tile < tiles; tile += step) {
+      const int32_t slot = tile / p.Hkv, g = tile - slot * p.Hkv, l = slot_pages[slot];
+      if (l < 0 || l >= p.n || !((head_mask[l] >> g) & 1u)) continue;
+      host = (int64_t)p.page_table[l] * p.pool_page_stride + (int64_t)g * p.pool_head_stride;
+      stage = (int64_t)slot * p.pool_page_stride + (int64_t)g * p.pool_head_stride;
+      return;
     }
+  }
+  __device__ __forceinline__ void next() {
+    x += BATCH * TRANSFER_THREADS;
+    if (x >= total) next_tile();
+  }
+  // granule u of this thread in the batch at x0: byte offset inside a tile (a thread past the end repeats its first granule,
+  // or the tile's last one)
+  __device__ __forceinline__ bool granule(int u, int elem, int64_t& off) const {
+    const int32_t e = x + u * TRANSFER_THREADS + (int32_t)threadIdx.x, i = e < total ? e : total - 1;
+    off = (int64_t)(i >> shift) * p.pool_tok_stride * elem + 16 * (i & ((1 << shift) - 1));
+    return e < total;
+  }
+};
+
+// K and V of the held tiles into the staging pools.  The last `zero_wgs` workgroups clear the gradient staging tiles instead:
+// that is work for the device's memory and would only hold the link's workgroups up.
+__global__ __launch_bounds__(TRANSFER_THREADS) void offload_fetch_kernel(Params p, const int32_t* __restrict__ slot_pages,
+                                                            const uint32_t* __restrict__ head_mask, const int32_t* __restrict__ n_slots,
+                                                            int32_t stage_cap, const unsigned char* __restrict__ a_host,
+                                                            const unsigned char* __restrict__ b_host, unsigned char* __restrict__ a_stage,
+                                                            unsigned char* __restrict__ b_stage, unsigned char* __restrict__ ga_stage,
+                                                            unsigned char* __restrict__ gb_stage, int es, int gs, int zero_wgs) {
+  const int movers = gridDim.x - zero_wgs;
+  if ((int)blockIdx.x >= movers) {
+    TileWalk w(p, slot_pages, head_mask, n_slots, stage_cap, blockIdx.x - movers, zero_wgs, gs);
+    for (; w.more(); w.next())
+#pragma unroll
+      for (int u = 0; u < BATCH; ++u) {
+        int64_t off;
+        if (!w.granule(u, gs, off)) continue;
+        *reinterpret_cast<Granule*>(ga_stage + w.stage * gs + off) = Granule{0, 0, 0, 0};
+        *reinterpret_cast<Granule*>(gb_stage + w.stage * gs + off) = Granule{0, 0, 0, 0};
+      }
+    return;
+  }
+  TileWalk w(p, slot_pages, head_mask, n_slots, stage_cap, blockIdx.x, movers, es);
+  struct Held { Granule a[BATCH], b[BATCH]; int64_t to[BATCH]; } even, odd;
+  auto load = [&](Held& h) __attribute__((always_inline)) {
+#pragma unroll
+    for (int u = 0; u < BATCH; ++u) {
+      int64_t off;
+      const bool in = w.granule(u, es, off);
+      h.a[u] = *reinterpret_cast<const Granule*>(a_host + w.host * es + off);
+      h.b[u] = *reinterpret_cast<const Granule*>(b_host + w.host * es + off);
+      h.to[u] = in ? w.stage * es + off : -1;
+    }
+    w.next();
+  };
+  auto store = [&](const Held& h) __attribute__((always_inline)) {
+#pragma unroll
+    for (int u = 0; u < BATCH; ++u)
+      if (h.to[u] >= 0) {
+        *reinterpret_cast<Granule*>(a_stage + h.to[u]) = h.a[u];
+        *reinterpret_cast<Granule*>(b_stage + h.to[u]) = h.b[u];
+      }
+  };
+  if (!w.more()) return;
+  load(even);
+  for (;;) {
+    if (!w.more()) { store(even); break; }
+    load(odd);
+    store(even);
+    if (!w.more()) { store(odd); break; }
+    load(even);
+    store(odd);
+  }
+}
+
+// host += staged gradients of the held tiles (dK and dV)
+template <typename TG>
+__global__ __launch_bounds__(TRANSFER_THREADS) void offload_writeback_kernel(Params p, const int32_t* __restrict__ slot_pages,
+                                                                const uint32_t* __restrict__ head_mask, const int32_t* __restrict__ n_slots,
+                                                                int32_t stage_cap, unsigned char* a_host, unsigned char* b_host,
+                                                                const unsigned char* __restrict__ a_stage,
+                                                                const unsigned char* __restrict__ b_stage) {
+  constexpr int GS = (int)sizeof(TG), EPG = 16 / GS;  // elements per granule
+  TileWalk w(p, slot_pages, head_mask, n_slots, stage_cap, blockIdx.x, gridDim.x, GS);
+  struct Held { Granule ha[BATCH], hb[BATCH], sa[BATCH], sb[BATCH]; int64_t to[BATCH]; } even, odd;
+  auto load = [&](Held& h) __attribute__((always_inline)) {
+#pragma unroll
+    for (int u = 0; u < BATCH; ++u) {
+      int64_t off;
+      const bool in = w.granule(u, GS, off);
+      h.ha[u] = __builtin_nontemporal_load(reinterpret_cast<const Granule*>(a_host + w.host * GS + off));
+      h.hb[u] = __builtin_nontemporal_load(reinterpret_cast<const Granule*>(b_host + w.host * GS + off));
+      h.sa[u] = *reinterpret_cast<const Granule*>(a_stage + w.stage * GS + off);
+      h.sb[u] = *reinterpret_cast<const Granule*>(b_stage + w.stage * GS + off);
+      h.to[u] = in ? w.host * GS + off : -1;
+    }
+    w.next();
+  };
+  auto add = [&](unsigned char* at, Granule h, Granule s) {
+    TG* he = reinterpret_cast<TG*>(&h);
+    const TG* se = reinterpret_cast<const TG*>(&s);
+#pragma unroll
+    for (int e = 0; e < EPG; ++e) Elem<TG>::store(he + e, Elem<TG>::load(he + e) + Elem<TG>::load(se + e));
+    __builtin_nontemporal_store(h, reinterpret_cast<Granule*>(at));
+  };
+  auto store = [&](const Held& h) __attribute__((always_inline)) {
+#pragma unroll
+    for (int u = 0; u < BATCH; ++u)
+      if (h.to[u] >= 0) {
+        add(a_host + h.to[u], h.ha[u], h.sa[u]);
+        add(b_host + h.to[u], h.hb[u], h.sb[u]);
+      }
+  };
+  if (!w.more()) return;
+  load(even);
+  for (;;) {
+    if (!w.more()) { store(even); break; }
+    load(odd);
+    store(even);
+    if (!w.more()) { store(odd); break; }
+    load(even);
+    store(odd);
   }
 }
 
@@ -161,6 +246,7 @@ void* device_view(const void* ptr) {
   return attr.devicePointer;
 }
 
+constexpr int ZERO_WGS = 48;   // workgroups that clear gradient staging tiles beside a fetch
 // workgroups of a transfer kernel (OOMB_OFFLOAD_WGS overrides the default, for experiments)
 static unsigned transfer_wgs(int64_t tiles) {
   static int v = 0;
@@ -184,9 +270,11 @@ hipError_t launch_offload_fetch(const Params& p, bool is_bf16, const int32_t* sl
                                 const int32_t* n_slots, int32_t stage_cap, void* host_k, void* host_v, void* stage_k,
                                 void* stage_v, void* stage_dk, void* stage_dv, hipStream_t st) {
   ProfScope prof_("offload_fetch", st);
-  offload_tile_kernel<0, float><<<dim3(transfer_wgs((int64_t)stage_cap * p.Hkv)), dim3(256), 0, st>>>(
-      p, slot_pages, head_mask, n_slots, stage_cap, (unsigned char*)host_k, (unsigned char*)host_v, (unsigned char*)stage_k,
-      (unsigned char*)stage_v, (unsigned char*)stage_dk, (unsigned char*)stage_dv, is_bf16 ? 2 : 4, p.grad_is_bf16 ? 2 : 4);
+  const int64_t tiles = (int64_t)stage_cap * p.Hkv;
+  const int zero_wgs = stage_dk ? (int)(tiles < ZERO_WGS ? tiles : ZERO_WGS) : 0;
+  offload_fetch_kernel<<<dim3(transfer_wgs(tiles) + zero_wgs), dim3(TRANSFER_THREADS), 0, st>>>(
+      p, slot_pages, head_mask, n_slots, stage_cap, (const unsigned char*)host_k, (const unsigned char*)host_v, (unsigned char*)stage_k,
+      (unsigned char*)stage_v, (unsigned char*)stage_dk, (unsigned char*)stage_dv, is_bf16 ? 2 : 4, p.grad_is_bf16 ? 2 : 4, zero_wgs);
   return hipGetLastError();
 }
 
@@ -194,15 +282,10 @@ hipError_t launch_offload_writeback(const Params& p, const int32_t* slot_pages, 
                                     const int32_t* n_slots, int32_t stage_cap, void* stage_dk, void* stage_dv, void* host_dk,
                                     void* host_dv, hipStream_t st) {
   ProfScope prof_("offload_writeback", st);
-  dim3 grid(transfer_wgs((int64_t)stage_cap * p.Hkv));
-  if (p.grad_is_bf16)
-    offload_tile_kernel<1, bf16_t><<<grid, dim3(256), 0, st>>>(p, slot_pages, head_mask, n_slots, stage_cap,
-                                                               (unsigned char*)host_dk, (unsigned char*)host_dv,
-                                                               (unsigned char*)stage_dk, (unsigned char*)stage_dv, nullptr, nullptr, 2, 2);
-  else
-    offload_tile_kernel<1, float><<<grid, dim3(256), 0, st>>>(p, slot_pages, head_mask, n_slots, stage_cap,
-                                                              (unsigned char*)host_dk, (unsigned char*)host_dv,
-                                                              (unsigned char*)stage_dk, (unsigned char*)stage_dv, nullptr, nullptr, 4, 4);
+  const dim3 grid(transfer_wgs((int64_t)stage_cap * p.Hkv)), block(TRANSFER_THREADS);
+  auto* kernel = p.grad_is_bf16 ? &offload_writeback_kernel<bf16_t> : &offload_writeback_kernel<float>;
+  kernel<<<grid, block, 0, st>>>(p, slot_pages, head_mask, n_slots, stage_cap, (unsigned char*)host_dk, (unsigned char*)host_dv,
+                                 (const unsigned char*)stage_dk, (const unsigned char*)stage_dv);
   return hipGetLastError();
 }
 

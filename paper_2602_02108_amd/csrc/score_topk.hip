@@ -36,62 +36,75 @@ __global__ __launch_bounds__(256) void qpool_partial_kernel(Params p, float* __r
   }
 }
 
-// Step S1b: qbar[g][d] = (sum over tau (outer), heads of g (inner) of A) * r.  One workgroup per KV head.  The
-// sum of a (g, d) is one sequential chain over the m G terms k = tau * G + (h - g G); the terms are brought
-// into LDS by all threads at once (rows of D floats, FINAL_ROWS at a time), then thread d walks its chain.
-constexpr int FINAL_THREADS = 1024;
-constexpr int FINAL_LDS_FLOATS = 32768;        // 128 KiB
-constexpr int SMALL_LDS_FLOATS = 28672;        // 112 KiB: the kernel below that also selects
-static inline size_t final_lds_bytes(const Params& p, int floats) {
-  const size_t all = (size_t)p.m * p.G * p.D;
-  return 4 * (all < (size_t)floats ? all : (size_t)floats);
+// Step S1b: qbar[g][d] = (sum over tau (outer), heads of g (inner) of A) * r.  The sum of a (g, d) is one sequential chain
+// over the m G terms k = tau * G + (h - g G); a workgroup of NT threads brings the terms of its DW dims into LDS at once
+// (FLOATS / DW rows at a time), then a thread per dim walks its chain, 16 reads ahead of the additions.
+static inline size_t final_lds_bytes(const Params& p, int dims, int floats) {
+  const size_t all = (size_t)p.m * p.G * dims;
+  return 4 * ((all < (size_t)floats ? all : (size_t)floats) + 32 * dims);   // (32 rows for the reads ahead)
 }
-// thread d < D returns qbar[g][d]; rows: LDS for FLOATS / D rows
-template <int FLOATS>
-__device__ __forceinline__ float qpool_final(const Params& p, const float* __restrict__ A, float r, int g, float* rows) {
-  const int tid = threadIdx.x, D = p.D;
-  const int dshift = D == 128 ? 7 : 6;  // D is 64 or 128
-  const int n = p.m * p.G;
-  const int per_pass = FLOATS >> dshift;
+// thread x < DW returns qbar[g][d0 + x]
+template <int DW, int NT, int FLOATS>
+__device__ __forceinline__ float qpool_final(const Params& p, const float* __restrict__ A, float r, int g, int d0, float* rows) {
+  constexpr int GPR = DW / 4, PASS = FLOATS / DW;   // float4 of a row, rows per pass
+  const int tid = threadIdx.x, n = p.m * p.G;
   float acc = 0.0f;
-  for (int k0 = 0; k0 < n; k0 += per_pass) {
-    const int cnt = n - k0 < per_pass ? n - k0 : per_pass;
-    // (eight independent loads per thread in flight)
-    const int total = cnt << dshift;
-    for (int e0 = tid; e0 < total; e0 += 8 * FINAL_THREADS) {
-      float v[8];
+  for (int k0 = 0; k0 < n; k0 += PASS) {
+    const int cnt = n - k0 < PASS ? n - k0 : PASS, total = cnt * GPR;
+    for (int e0 = tid; e0 < total; e0 += 8 * NT) {   // (eight loads per thread in flight)
+      float4 v[8];
 #pragma unroll
       for (int u = 0; u < 8; ++u) {
-        const int e = e0 + u * FINAL_THREADS;
-        const int k = k0 + (e >> dshift), d = e & (D - 1);
+        const int e = e0 + u * NT < total ? e0 + u * NT : e0, k = k0 + e / GPR;
         const int tau = (int)div_g(p, (uint32_t)k), h = g * p.G + (k - tau * p.G);
-        v[u] = e < total ? A[((int64_t)h * p.m + tau) * D + d] : 0.0f;
+        v[u] = *reinterpret_cast<const float4*>(A + ((int64_t)h * p.m + tau) * p.D + d0 + 4 * (e % GPR));
       }
 #pragma unroll
       for (int u = 0; u < 8; ++u)
-        if (e0 + u * FINAL_THREADS < total) rows[e0 + u * FINAL_THREADS] = v[u];
+        if (e0 + u * NT < total) reinterpret_cast<float4*>(rows)[e0 + u * NT] = v[u];
     }
     __syncthreads();
-    if (tid < D) {
-      // the reads are independent and issued 16 at a time; the additions stay in order
-      int k = 0;
-      for (; k + 16 <= cnt; k += 16) {
-        float v[16];
+    if (tid < DW) {
+      // (what a batch reads past the last row is inside the allocation and not added)
+      float a[16], b[16];
+      const float* at = rows + tid;
+      auto read = [&](float (&x)[16]) __attribute__((always_inline)) {
 #pragma unroll
-        for (int u = 0; u < 16; ++u) v[u] = rows[((k + u) << dshift) + tid];
+        for (int u = 0; u < 16; ++u) x[u] = at[u * DW];
+        at += 16 * DW;
+      };
+      int left = cnt;
+      auto add = [&](const float (&x)[16]) __attribute__((always_inline)) {
+        if (left >= 16) {
 #pragma unroll
-        for (int u = 0; u < 16; ++u) acc = __fadd_rn(acc, v[u]);
+          for (int u = 0; u < 16; ++u) acc = __fadd_rn(acc, x[u]);
+        } else {
+#pragma unroll
+          for (int u = 0; u < 16; ++u) acc = u < left ? __fadd_rn(acc, x[u]) : acc;
+        }
+        left -= 16;
+      };
+      read(a);
+      while (left > 0) {
+        read(b);
+        add(a);
+        if (left <= 0) break;
+        read(a);
+        add(b);
       }
-      for (; k < cnt; ++k) acc = __fadd_rn(acc, rows[(k << dshift) + tid]);
     }
     __syncthreads();
   }
   return __fmul_rn(acc, r);
 }
+// One workgroup per KV head and 16 dims: one compute unit takes about 10 bytes per ns of lines that another one wrote, so few of
+// them are slow (224 rows of 128 floats: 9.1 us with one workgroup per head, 5.7 so; 448 rows: 16.5, 8.6).
+constexpr int FINAL_DIMS = 16, FINAL_THREADS = 256, FINAL_FLOATS = 16384;
 __global__ __launch_bounds__(FINAL_THREADS) void qpool_final_kernel(Params p, const float* __restrict__ A, float* __restrict__ qbar, float r) {
-  extern __shared__ float rows[];  // [rows per pass][D]
-  const float v = qpool_final<FINAL_LDS_FLOATS>(p, A, r, blockIdx.x, rows);
-  if ((int)threadIdx.x < p.D) qbar[blockIdx.x * p.D + threadIdx.x] = v;
+  extern __shared__ __align__(16) float rows[];
+  const int g = blockIdx.x, d0 = blockIdx.y * FINAL_DIMS;
+  const float v = qpool_final<FINAL_DIMS, FINAL_THREADS, FINAL_FLOATS>(p, A, r, g, d0, rows);
+  if ((int)threadIdx.x < FINAL_DIMS) qbar[g * p.D + d0 + threadIdx.x] = v;
 }
 
 // Steps S2 + S3: one group of LPR lanes walks one (KV head, logical page) tile
@@ -240,122 +253,150 @@ __global__ __launch_bounds__(SELECT_THREADS) void topk_select_kernel(
 }
 
 // Step S4 for lists of at most PER * SELECT_THREADS candidates: the same selection with the keys held in
-// registers.  Thread t owns the PER consecutive ids from t PER on, so nothing is re-read from memory.  The
-// k_eff-th largest key is found by a radix select, eight bits per pass from the top: every wave counts the
-// byte of its keys that still match the prefix into a histogram of its own in LDS (integer additions: the
-// order does not matter), 256 threads add the 16 histograms and scan them from the top, and the bin where
-// the count crosses what is still wanted extends the prefix.  Four passes, three barriers each; the ordered
-// emission needs only the exclusive scan over threads.
+// registers, thread t's i-th that of page 1024 i + t (a run of pages per thread makes every load touch as many cache lines
+// as it has lanes: 32700 candidates 31 us, 23 now).  The
+// k_eff-th largest key is found by a radix select, eleven bits per pass from the top (sign, exponent, two bits of the
+// fraction): the keys that still match the prefix are counted into a histogram in LDS (integer additions: the
+// order does not matter), which is scanned from the top, and the bin where the count crosses what is still wanted
+// extends the prefix.  Once FEW keys or less match, mostly after the first pass, they move to LDS and each is ranked by
+// comparing it with the others.  The ordered emission counts per wave and row of pages and scans those counts.  Such a kernel is all
+// barriers and LDS round trips; eight bits per pass, four passes: 1023 candidates 6.9 us, 8160 14.0, 32700 38; now 4.8, 9.3 and 23.
 struct SelectLds {
-  static constexpr int WAVES = SELECT_THREADS / 64;
-  uint32_t hist[2][WAVES][256];
-  uint32_t scan_tot[4];
-  uint32_t picked[2];  // {bin, how many keys of that bin are still wanted}
-  unsigned long long wave_tot[WAVES];
+  static constexpr int WAVES = SELECT_THREADS / 64, BITS = 11, BINS = 1 << BITS, COPIES = 2, FEW = SELECT_THREADS / 4;
+  uint32_t hist[COPIES][BINS];   // (even and odd waves)
+  __align__(16) uint32_t few[FEW];
+  uint32_t n_few;
+  uint32_t scan_tot[WAVES];
+  uint32_t picked[3];  // {bin, how many keys of that bin are still wanted, how many it holds}
+  uint32_t before[32 * WAVES], wave_tot[8];   // {equal, above} kept keys in 16 bits each (at most 32768 of either)
 };
 // list `g` (its row of sel and sel_count), ending with n_loc local pages; load(l): score of past page l
 template <int PER, typename F>
 __device__ __forceinline__ void select_reg(SelectLds& lds, F&& load, int g, int64_t n_past, int32_t m, int32_t n_loc, int32_t top_k,
                                            int32_t* __restrict__ sel, int32_t* __restrict__ sel_count) {
-  constexpr int WAVES = SelectLds::WAVES;
-  auto& hist = lds.hist;
-  auto& scan_tot = lds.scan_tot;
+  typedef SelectLds S;
   auto& picked = lds.picked;
-  auto& wave_tot = lds.wave_tot;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int32_t stride = top_k + m;
   int32_t* out = sel + (int64_t)g * stride;
   const int32_t k_eff = (int32_t)(top_k < n_past ? top_k : n_past);
   const int32_t np = (int32_t)n_past;
 
-  for (int e = tid; e < WAVES * 256; e += SELECT_THREADS) (&hist[0][0][0])[e] = 0u;
-  const int32_t lo = tid * PER;
   uint32_t key[PER];
 #pragma unroll
-  for (int i = 0; i < PER; ++i) key[i] = lo + i < np ? order_key(load(lo + i)) : 0u;
-  __syncthreads();
+  for (int i = 0; i < PER; ++i) key[i] = 0u;
+  if (np > 0) {
+    float f[PER];   // (no load waits for another)
+#pragma unroll
+    for (int i = 0; i < PER; ++i) f[i] = load(i * SELECT_THREADS + tid < np ? i * SELECT_THREADS + tid : 0);
+#pragma unroll
+    for (int i = 0; i < PER; ++i) key[i] = i * SELECT_THREADS + tid < np ? order_key(f[i]) : 0u;
+  }
 
   uint32_t T = 0;
   int take_eq = 0;
   if (k_eff > 0) {
     uint32_t want = (uint32_t)k_eff;  // keys still wanted among those that match the prefix
-#pragma unroll 1
-    for (int pass = 0; pass < 4; ++pass) {
-      const int shift = 24 - 8 * pass, cur = pass & 1;
-      // the other histogram set is free: clear it for the next pass
-      for (int e = tid; e < WAVES * 256; e += SELECT_THREADS) (&hist[cur ^ 1][0][0])[e] = 0u;
+    if (tid == 0) lds.n_few = 0u;
+    if (tid < S::FEW) lds.few[tid] = 0u;
+    int shift = 32;   // bits not yet decided
+    while (shift > 0) {
+      const int above = shift;
+      shift = shift > S::BITS ? shift - S::BITS : 0;
+      for (int e = tid; e < S::COPIES * S::BINS; e += SELECT_THREADS) (&lds.hist[0][0])[e] = 0u;
+      __syncthreads();
 #pragma unroll
       for (int i = 0; i < PER; ++i) {
-        const bool match = lo + i < np && (pass == 0 || (key[i] >> (shift + 8)) == (T >> (shift + 8)));
-        if (match) atomicAdd(&hist[cur][wave][(key[i] >> shift) & 255u], 1u);
+        const bool match = i * SELECT_THREADS + tid < np && (above == 32 || (key[i] >> (above & 31)) == (T >> (above & 31)));
+        if (match) atomicAdd(&lds.hist[wave & 1][(key[i] >> shift) & (S::BINS - 1)], 1u);
       }
       __syncthreads();
-      // thread t < 256 takes bin 255 - t: an inclusive scan over t is the count of keys in bins >= its own
-      uint32_t v = 0, inc = 0;
-      if (tid < 256) {
+      // thread t takes bins BINS - 1 - 2 t and the one below: an inclusive scan over t counts the keys in bins >= its own
+      const int b0 = S::BINS - 1 - 2 * tid;
+      const uint32_t v0 = lds.hist[0][b0] + lds.hist[1][b0], v1 = lds.hist[0][b0 - 1] + lds.hist[1][b0 - 1];
+      uint32_t inc = v0 + v1;
 #pragma unroll
-        for (int w = 0; w < WAVES; ++w) v += hist[cur][w][255 - tid];
-        inc = v;
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-          const uint32_t nb = __shfl_up(inc, o, 64);
-          if (lane >= o) inc += nb;
-        }
-        if (lane == 63) scan_tot[wave] = inc;
+      for (int o = 1; o < 64; o <<= 1) {
+        const uint32_t nb = __shfl_up(inc, o, 64);
+        if (lane >= o) inc += nb;
       }
+      if (lane == 63) lds.scan_tot[wave] = inc;
       __syncthreads();
-      if (tid < 256) {
-        for (int w = 0; w < wave; ++w) inc += scan_tot[w];
-        const uint32_t above = inc - v;  // keys in higher bins
-        if (inc >= want && above < want) {
-          picked[0] = 255u - (uint32_t)tid;
-          picked[1] = want - above;
-        }
+#pragma unroll
+      for (int w = 0; w < S::WAVES; ++w) inc += w < wave ? lds.scan_tot[w] : 0u;
+      const uint32_t higher = inc - v0 - v1;  // keys in bins above b0
+      if (higher < want && inc >= want) {
+        const bool first = higher + v0 >= want;
+        picked[0] = (uint32_t)(first ? b0 : b0 - 1);
+        picked[1] = want - higher - (first ? 0u : v0);
+        picked[2] = first ? v0 : v1;
       }
       __syncthreads();
       T |= picked[0] << shift;
+      want = picked[1];
+      if (picked[2] <= S::FEW) break;
+    }
+    if (shift > 0) {   // (else the prefix is the key)
+#pragma unroll
+      for (int i = 0; i < PER; ++i)
+        if (i * SELECT_THREADS + tid < np && (key[i] >> shift) == (T >> shift)) lds.few[atomicAdd(&lds.n_few, 1u)] = key[i];
+      __syncthreads();
+      // four threads to a candidate count the keys above it and those not below it (the slots past n count for neither: 0
+      // is above nothing, and equal only to a key of 0, which is the last one anyway)
+      const int n = (int)lds.n_few, x = tid >> 2;
+      const uint32_t mine = lds.few[x];
+      uint32_t cnt = 0;   // {not below, above}
+      for (int j = 4 * (tid & 3); j < n; j += 16) {
+        const uint4 k = *reinterpret_cast<const uint4*>(lds.few + j);
+        cnt += (k.x > mine) + (k.y > mine) + (k.z > mine) + (k.w > mine);
+        cnt += ((k.x >= mine) + (k.y >= mine) + (k.z >= mine) + (k.w >= mine)) << 16;
+      }
+      cnt += __shfl_xor(cnt, 1, 64);
+      cnt += __shfl_xor(cnt, 2, 64);
+      if (x < n && (cnt & 0xffffu) < want && (cnt >> 16) >= want) {   // (equal candidates write the same)
+        picked[0] = mine;
+        picked[1] = want - (cnt & 0xffffu);
+      }
+      __syncthreads();
+      T = picked[0];
       want = picked[1];
     }
     take_eq = (int)want;  // how many keys equal to T are kept (lowest ids)
   }
 
-  int n_eq = 0, n_gt = 0;
   if (k_eff > 0) {
+    constexpr int ROWS = PER * S::WAVES;
+    uint32_t mine = 0;
 #pragma unroll
-    for (int i = 0; i < PER; ++i) {
-      const bool valid = lo + i < np;
-      n_eq += valid && key[i] == T;
-      n_gt += valid && key[i] > T;
+    for (int i = 0; i < PER; ++i) {   // (pages past the end have key 0: below T, or equal to a T of 0 and then behind every page)
+      const uint32_t n_gt = (uint32_t)__builtin_popcountll(__ballot(key[i] > T)), n_eq = (uint32_t)__builtin_popcountll(__ballot(key[i] == T));
+      if (lane == i) mine = n_eq << 16 | n_gt;
     }
-  }
-  // exclusive scans of (n_eq, n_gt) over threads, packed in one 64-bit add
-  const unsigned long long v = ((unsigned long long)(uint32_t)n_eq << 32) | (uint32_t)n_gt;
-  unsigned long long incl = v;
+    if (lane < PER) lds.before[lane * S::WAVES + wave] = mine;
+    __syncthreads();
+    // exclusive scan over the rows of 64 pages
+    uint32_t v = tid < ROWS ? lds.before[tid] : 0u, inc = v;
 #pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const unsigned long long nb = __shfl_up(incl, o, 64);
-    if (lane >= o) incl += nb;
-  }
-  if (lane == 63) wave_tot[tid >> 6] = incl;
-  __syncthreads();
-  unsigned long long base = 0;
-  for (int w = 0; w < (tid >> 6); ++w) base += wave_tot[w];
-  const unsigned long long excl = base + incl - v;
-  int eq_before = (int)(excl >> 32);
-  const int gt_before = (int)(excl & 0xffffffffu);
-  if (k_eff > 0) {
-    // position = kept keys with lower id = gt_before + min(eq_before, take_eq)
-    int pos = gt_before + (eq_before < take_eq ? eq_before : take_eq);
+    for (int o = 1; o < 64; o <<= 1) {
+      const uint32_t nb = __shfl_up(inc, o, 64);
+      if (lane >= o) inc += nb;
+    }
+    if (lane == 63 && wave < 8) lds.wave_tot[wave] = inc;
+    __syncthreads();
+    if (tid < ROWS) {
+      for (int w = 0; w < wave; ++w) inc += lds.wave_tot[w];
+      lds.before[tid] = inc - v;
+    }
+    __syncthreads();
+    const uint64_t lower = (1ull << lane) - 1ull;
 #pragma unroll
     for (int i = 0; i < PER; ++i) {
-      if (lo + i < np) {
-        if (key[i] > T) {
-          out[pos++] = lo + i;
-        } else if (key[i] == T) {
-          if (eq_before < take_eq) out[pos++] = lo + i;
-          ++eq_before;
-        }
-      }
+      // position = kept keys with lower id = those above T + those equal to T, of which the first take_eq are kept
+      const uint32_t at = lds.before[i * S::WAVES + wave];
+      const int gt = (int)(at & 0xffffu) + __builtin_popcountll(__ballot(key[i] > T) & lower);
+      const int eq = (int)(at >> 16) + __builtin_popcountll(__ballot(key[i] == T) & lower);
+      const bool kept = key[i] > T || (key[i] == T && eq < take_eq);
+      if (kept && i * SELECT_THREADS + tid < np) out[gt + (eq < take_eq ? eq : take_eq)] = i * SELECT_THREADS + tid;
     }
   }
   for (int32_t j = tid; j < n_loc; j += SELECT_THREADS) out[k_eff + j] = (int32_t)(n_past + j);
@@ -371,43 +412,82 @@ __global__ __launch_bounds__(SELECT_THREADS) void topk_select_reg_kernel(
   select_reg<PER>(lds, [&](int32_t l) { return sc[l]; }, blockIdx.x, n_past, m, per_qp ? (int32_t)(blockIdx.x % m) + 1 : m, top_k, sel, sel_count);
 }
 
-// Steps S1b, S3 and S4 of a KV head in one workgroup, from page means, for short histories: three
-// kernels that do next to nothing (56 pages: 11.4 us and two launches more than the 10.2 of one).
-constexpr int SMALL_PAGES = 192;   // (0.03 us a page on top of 9: beyond this the pages want more compute units than one)
+// Steps S1b, S3 and S4 of a KV head in one workgroup, from page means, for short histories and chunks: three kernels
+// that do next to nothing (56 pages: 16 us and two launches more than the 4.6 of one).  The means are under way while the
+// query is pooled; so few keys are ranked by comparing each with all others, no histograms.  One compute unit takes in
+// about 10 bytes per ns here, so the kernel ends where pages + rows to pool are SMALL_ROWS rows of D floats: about 15 us.
+constexpr int SMALL_PAGES = 192, SMALL_ROWS = 192;
 template <int D>
 __global__ __launch_bounds__(SELECT_THREADS) void select_small_kernel(Params p, const float* __restrict__ A, float r, const float* __restrict__ means,
                                                                       float* __restrict__ scores, int32_t top_k, int32_t* __restrict__ sel,
                                                                       int32_t* __restrict__ sel_count) {
   extern __shared__ __align__(16) float rows[];
-  __shared__ SelectLds lds;
   __shared__ __align__(16) float qb[D];
-  __shared__ float sc[SMALL_PAGES];
-  constexpr int VEC = 4, LPR = D / VEC, GROUPS = SELECT_THREADS / LPR;
+  __shared__ __align__(16) uint32_t keys[SMALL_PAGES];
+  __shared__ uint32_t ranks[SELECT_THREADS / SMALL_PAGES][SMALL_PAGES];
+  __shared__ int32_t kept[SMALL_PAGES / 64];
+  constexpr int VEC = 4, LPR = D / VEC, GROUPS = SELECT_THREADS / LPR, PER = SMALL_PAGES / GROUPS;   // pages per group
   const int g = blockIdx.x, tid = threadIdx.x, lr = tid % LPR, grp = tid / LPR;
   const int32_t np = (int32_t)p.n_past;
-  const float v = qpool_final<SMALL_LDS_FLOATS>(p, A, r, g, rows);
+  float4 kb[PER];
+#pragma unroll
+  for (int u = 0; u < PER; ++u)
+    if (grp + u * GROUPS < np) kb[u] = *reinterpret_cast<const float4*>(means + ((int64_t)(grp + u * GROUPS) * p.Hkv + g) * D + lr * VEC);
+  if (tid < SMALL_PAGES) keys[tid] = 0u;
+  const float v = qpool_final<D, SELECT_THREADS, SMALL_ROWS * D>(p, A, r, g, 0, rows);
   if (tid < D) qb[tid] = v;
   __syncthreads();
   const float4 q4 = *reinterpret_cast<const float4*>(qb + lr * VEC);
-  for (int32_t l0 = grp; l0 < np; l0 += 4 * GROUPS) {   // (four pages per group in flight)
-    float4 kb[4];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int32_t l = l0 + u * GROUPS < np ? l0 + u * GROUPS : l0;
-      kb[u] = *reinterpret_cast<const float4*>(means + ((int64_t)l * p.Hkv + g) * D + lr * VEC);
-    }
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const float s = score_tree<D>(q4, kb[u]);
-      const int32_t l = l0 + u * GROUPS;
-      if (lr == 0 && l < np) {
-        sc[l] = s;
-        scores[(int64_t)g * p.n_past + l] = s;
-      }
+  for (int u = 0; u < PER; ++u) {
+    const int32_t l = grp + u * GROUPS;
+    if (l >= np) break;   // (the same for all lanes of a group)
+    const float s = score_tree<D>(q4, kb[u]);
+    if (lr == 0) {
+      keys[l] = order_key(s);
+      scores[(int64_t)g * p.n_past + l] = s;
     }
   }
   __syncthreads();
-  select_reg<1>(lds, [&](int32_t l) { return sc[l]; }, g, p.n_past, p.m, p.m, top_k, sel, sel_count);
+  // rank of page tid: keys above its own, and equal ones of lower pages (real keys are above 0).  TPP threads, of
+  // different waves, count a part of the pages each.
+  const int32_t k_eff = top_k < np ? top_k : np, stride = top_k + p.m;
+  constexpr int TPP = SELECT_THREADS / SMALL_PAGES, CHUNK = (SMALL_PAGES / TPP + 3) & ~3;
+  const int part = tid / SMALL_PAGES, page = tid - part * SMALL_PAGES;
+  if (part < TPP) {
+    const uint32_t mine = keys[page];
+    const int32_t first = __builtin_amdgcn_readfirstlane(page & ~63), end = (part + 1) * CHUNK < np ? (part + 1) * CHUNK : np;   // (a wave's pages: first .. first + 63)
+    uint32_t r = 0;
+    for (int32_t j = part * CHUNK; j < end; j += 4) {
+      const uint4 k = *reinterpret_cast<const uint4*>(keys + j);
+      if (j + 4 <= first) r += (k.x >= mine) + (k.y >= mine) + (k.z >= mine) + (k.w >= mine);
+      else if (j >= first + 64) r += (k.x > mine) + (k.y > mine) + (k.z > mine) + (k.w > mine);
+      else {
+        const int32_t d = page - j;
+        r += (k.x > mine || (k.x == mine && d > 0)) + (k.y > mine || (k.y == mine && d > 1)) + (k.z > mine || (k.z == mine && d > 2)) +
+             (k.w > mine || (k.w == mine && d > 3));
+      }
+    }
+    ranks[part][page] = r;
+  }
+  __syncthreads();
+  int32_t rank = 0;
+  if (tid < SMALL_PAGES) {
+#pragma unroll
+    for (int u = 0; u < TPP; ++u) rank += (int32_t)ranks[u][tid];
+  }
+  const bool keep = tid < np && rank < k_eff;
+  const uint64_t votes = __ballot(keep);
+  if (tid < SMALL_PAGES && (tid & 63) == 0) kept[tid >> 6] = __builtin_popcountll(votes);
+  __syncthreads();
+  int32_t* out = sel + (int64_t)g * stride;
+  if (keep) {
+    int32_t pos = __builtin_popcountll(votes & ((1ull << (tid & 63)) - 1ull));
+    for (int w = 0; w < (tid >> 6); ++w) pos += kept[w];
+    out[pos] = tid;
+  }
+  for (int32_t j = tid; j < stride - k_eff; j += SELECT_THREADS) out[k_eff + j] = j < p.m ? np + j : -1;
+  if (tid == 0) sel_count[g] = k_eff + p.m;
 }
 
 static hipError_t launch_topk_select(const Params& p, const float* scores, int32_t top_k, int32_t* sel, int32_t* sel_count,
@@ -439,10 +519,13 @@ static hipError_t launch_topk_select(const Params& p, const float* scores, int32
 }
 
 // Layout of the scoring workspace.  Page means of a short history get a place of their own behind the rest, if all of
-// it fits the built-in scratch array (callers without a workspace take the same kernels).
+// it fits the built-in scratch array (callers without a workspace take the same kernels): with as many workgroups as tiles they
+// are there in 6 us more, where the kernel that walks a page per group of lanes takes 18 for 512 x 2 pages of 128 tokens (13 of 64; pages
+// of 16 and 32 are short chains there).  From MEANS_TILES tiles on that one has groups enough to be as fast.
+constexpr int64_t MEANS_TILES = 2048;
 struct ScoreLayout {
   size_t off_qbar, off_scores, off_means, bytes;   // (means at the end: a call works without them)
-  bool small;   // means + one workgroup per KV head for the rest
+  bool means, small;   // scores from means; one workgroup per KV head for what follows them
 };
 static ScoreLayout score_layout(const Params& p, bool cached, size_t ws_bytes) {
   auto up = [](size_t x) { return (x + 255) & ~(size_t)255; };
@@ -451,8 +534,10 @@ static ScoreLayout score_layout(const Params& p, bool cached, size_t ws_bytes) {
   L.off_scores = L.off_qbar + up((size_t)p.Hkv * p.D * sizeof(float));
   L.bytes = L.off_means = L.off_scores + up((size_t)p.Hkv * (size_t)(p.n_past > 0 ? p.n_past : 1) * sizeof(float));
   const size_t means = up((size_t)p.n_past * p.Hkv * p.D * sizeof(float));
-  L.small = p.n_past <= SMALL_PAGES && (cached || (L.bytes + means <= (size_t)OOMB_NOALLOC_SCRATCH_BYTES && L.bytes + means <= ws_bytes));
-  if (L.small && !cached) L.bytes += means;
+  const bool few = p.n_past <= SMALL_PAGES && p.n_past + (int64_t)p.m * p.G <= SMALL_ROWS;
+  L.means = cached || ((few || (p.P >= 64 && p.n_past * p.Hkv <= MEANS_TILES)) && L.bytes + means <= (size_t)OOMB_NOALLOC_SCRATCH_BYTES && L.bytes + means <= ws_bytes);
+  L.small = few && L.means;
+  if (L.means && !cached) L.bytes += means;
   return L;
 }
 size_t score_workspace_bytes(const Params& p) { return score_layout(p, false, SIZE_MAX).bytes; }
@@ -468,7 +553,7 @@ static hipError_t launch_scoring(const Params& p, int32_t top_k, int32_t* sel, i
   float* A = (float*)ws;
   float* qbar = (float*)(ws + L.off_qbar);
   float* scores = scores_out ? scores_out : (float*)(ws + L.off_scores);
-  float* means = L.small && !kbar_cache ? (float*)(ws + L.off_means) : nullptr;
+  float* means = L.means && !kbar_cache ? (float*)(ws + L.off_means) : nullptr;
   const float inv_p = 1.0f / (float)p.P, r = 1.0f / (float)((int64_t)p.C * p.G);
   {
     ProfScope prof_("qpool_partial", st);
@@ -478,21 +563,19 @@ static hipError_t launch_scoring(const Params& p, int32_t top_k, int32_t* sel, i
   if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
   if (L.small) {
     static DeviceOnce lds_once;
-    if (hipError_t e = ensure_max_dynamic_lds(lds_once, (const void*)select_small_kernel<D>, SMALL_LDS_FLOATS * 4); e != hipSuccess) return e;
+    if (hipError_t e = ensure_max_dynamic_lds(lds_once, (const void*)select_small_kernel<D>, (SMALL_ROWS + 32) * D * 4); e != hipSuccess) return e;
     ProfScope prof_("select_small", st);
-    select_small_kernel<D><<<dim3(p.Hkv), dim3(SELECT_THREADS), final_lds_bytes(p, SMALL_LDS_FLOATS), st>>>(p, A, r, kbar_cache ? kbar_cache : means, scores, top_k, sel,
+    select_small_kernel<D><<<dim3(p.Hkv), dim3(SELECT_THREADS), final_lds_bytes(p, D, SMALL_ROWS * D), st>>>(p, A, r, kbar_cache ? kbar_cache : means, scores, top_k, sel,
                                                                                          sel_count);
     return hipGetLastError();
   }
   {
-    static DeviceOnce lds_once;
-    if (hipError_t e = ensure_max_dynamic_lds(lds_once, (const void*)qpool_final_kernel, FINAL_LDS_FLOATS * 4); e != hipSuccess) return e;
     ProfScope prof_("qpool_final", st);
-    qpool_final_kernel<<<dim3(p.Hkv), dim3(FINAL_THREADS), final_lds_bytes(p, FINAL_LDS_FLOATS), st>>>(p, A, qbar, r);
+    qpool_final_kernel<<<dim3(p.Hkv, D / FINAL_DIMS), dim3(FINAL_THREADS), final_lds_bytes(p, FINAL_DIMS, FINAL_FLOATS), st>>>(p, A, qbar, r);
   }
   if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
-  if (kbar_cache) {
-    if (hipError_t e = launch_page_score_cached(p, qbar, kbar_cache, scores, st); e != hipSuccess) return e;
+  if (L.means) {
+    if (hipError_t e = launch_page_score_cached(p, qbar, kbar_cache ? kbar_cache : means, scores, st); e != hipSuccess) return e;
   } else {
     dim3 grid((unsigned)((p.n_past + PER_BLOCK - 1) / PER_BLOCK), p.Hkv);
     { ProfScope prof_("page_score", st); page_score_kernel<T, D><<<grid, dim3(256), 0, st>>>(p, qbar, scores, inv_p); }

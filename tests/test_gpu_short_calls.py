@@ -28,6 +28,24 @@ def test_selection_of_short_histories(n_past, dtype, D, P):
     assert np.array_equal(sel.cpu().numpy(), osel) and np.array_equal(cnt.cpu().numpy(), ocnt)
 
 
+@pytest.mark.parametrize("n_past", [300, 1500, 9000])
+def test_selection_among_close_scores(n_past):
+    # distinct scores that share their leading bits: the cut is found after several passes, among few candidates
+    hkv, D, C = 2, 64, 32
+    g = torch.Generator(device="cuda").manual_seed(430 + n_past)
+    n = n_past + 2
+    kbar = torch.randn((1, hkv, D), generator=g, device="cuda") * (1 + torch.randperm(n, generator=g, device="cuda")[:, None, None] * 2.0**-22)
+    q = torch.randn((C, 4, D), generator=g, device="cuda")
+    desc = api.make_desc(q, torch.empty((1, hkv, 16, D), device="cuda").expand(n, hkv, 16, D), n * 16, 0.125)
+    desc.pool_page_stride = hkv * 16 * D
+    for top_k in (1, 77, n_past // 2):
+        scores = torch.empty((hkv, n_past), dtype=torch.float32, device="cuda")
+        sel, cnt = api.page_score_topk_cached(desc, q, kbar, top_k, scores_out=scores)
+        osel, ocnt, oscores = orc.page_score_topk_cached(orc.Shape(4, hkv, D, 16, C, n * 16, 0.125), q.cpu().numpy(), kbar.cpu().numpy(), top_k)
+        assert np.array_equal(scores.cpu().numpy().view(np.uint32), oscores.view(np.uint32))
+        assert np.array_equal(sel.cpu().numpy(), osel) and np.array_equal(cnt.cpu().numpy(), ocnt)
+
+
 def test_selection_with_more_pooled_rows_than_one_pass():
     # m * G = 256 rows of 128 floats against 224 in LDS at a time
     w = Workload("rows", 32, 1, 128, 16, 16 * 8, 16 * 48, 7, "bf16", "f32", 0.1, seed=420)

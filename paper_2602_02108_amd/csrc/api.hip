@@ -250,8 +250,7 @@ oomb_status oomb_paged_attn_fwd(const oomb_attn_desc* desc, const void* q, const
       return OOMB_ERR_WORKSPACE;
     e = launch_fwd_mfma(p, max_len, workspace, workspace_bytes, (hipStream_t)hip_stream);
   } else {
-    e = launch_fwd_generic(p, bf, max_len, workspace, aligned16(workspace) ? workspace_bytes : 0, "attn_fwd_generic",
-                           (hipStream_t)hip_stream);
+    e = launch_fwd_generic(p, bf, max_len, workspace, aligned16(workspace) ? workspace_bytes : 0, (hipStream_t)hip_stream);
   }
   return e == hipSuccess ? OOMB_OK : OOMB_ERR_LAUNCH;
 }
@@ -339,8 +338,7 @@ oomb_status oomb_paged_attn_fwd_qp(const oomb_attn_desc* desc, const void* q, co
     e = launch_fwd_mfma(p, qp_union_cap(p, sel_stride), (unsigned char*)workspace + maps, workspace_bytes - maps, st);
   } else {
     const size_t maps = qp_maps_bytes(p, sel_stride);
-    e = launch_fwd_generic(p, bf, qp_union_cap(p, sel_stride), (unsigned char*)workspace + maps, workspace_bytes - maps,
-                           "attn_fwd_generic", st);
+    e = launch_fwd_generic(p, bf, qp_union_cap(p, sel_stride), (unsigned char*)workspace + maps, workspace_bytes - maps, st);
   }
   return e == hipSuccess ? OOMB_OK : OOMB_ERR_LAUNCH;
 }

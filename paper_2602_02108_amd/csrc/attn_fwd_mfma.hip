@@ -330,7 +330,7 @@ size_t fwd_mfma_workspace_bytes(const Params& p, int32_t max_list_len) {
 }
 
 hipError_t launch_fwd_mfma(const Params& p, int32_t max_list_len, void* ws, size_t ws_bytes, hipStream_t st) {
-  if (rows_take_generic(p, max_list_len, false)) return launch_fwd_generic(p, true, max_list_len, ws, ws_bytes, "attn_fwd_mfma", st);
+  if (rows_take_generic(p, max_list_len, false)) return launch_fwd_generic_bf16_128(p, max_list_len, ws, ws_bytes, st);
   static DeviceOnce lds_once;
   if (hipError_t e = ensure_max_dynamic_lds(lds_once, (const void*)fwd_mfma_kernel, FW_LDS); e != hipSuccess) return e;
   const int tiles = row_tiles_per_head(p.C, p.G, p.m, p.qp);

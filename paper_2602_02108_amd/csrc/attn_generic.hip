@@ -145,25 +145,43 @@ template <typename T, int D> struct GnAddr {
   }
 };
 
-// A block of probabilities (or dS) as the B operand of the second product: bf16 pairs, or the fp32 values themselves
-template <typename T> struct GnP;
-template <> struct GnP<bf16_t> {
-  uint32_t w[8];
-  __device__ __forceinline__ void set2(const int x, float a, float b) { w[x >> 1] = pack2_bf16(a, b); }   // registers x, x + 1
+// A block of probabilities (or dS) as the B operand of the second product.  fp32 tensors: the values themselves.  bf16 tensors: NT
+// bf16 terms whose sum stands for the value, each the rounding of what the ones before it left, NT matrix
+// instructions in the place of one (the fp32 instruction would take sixteen times as long).  One is the precision of the
+// kernels for pages of 128 at head dim 128, and of the short calls that those hand over.  The other shapes keep
+// fp32 precision: three terms are all 24 bits, two 17, which is used where the result is stored in bf16.
+// Error against 64 bits, 2-norm, 13 calls of 64 to 2176 keys, fp32 values -> terms: O 1.66e-3 -> 1.66e-3, dV in bf16 the same,
+// dV in fp32 0.6 to 1.5e-6 -> 0.3 to 0.7e-6 (one term: O 2.1e-3, dV 1.7e-3).
+template <typename T, int NT> struct GnP;
+template <int NT> struct GnP<bf16_t, NT> {
+  uint32_t w[NT][8];
+  __device__ __forceinline__ void set2(const int x, float a, float b) {   // registers x, x + 1
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+      const uint32_t v = w[t][x >> 1] = pack2_bf16(a, b);
+      if (t + 1 < NT) {
+        a -= __uint_as_float(v << 16);
+        b -= __uint_as_float(v & 0xffff0000u);
+      }
+    }
+  }
 };
-template <> struct GnP<float> {
-  float w[16];
-  __device__ __forceinline__ void set2(const int x, float a, float b) { w[x] = a; w[x + 1] = b; }
+template <> struct GnP<float, 1> {
+  float w[1][16];
+  __device__ __forceinline__ void set2(const int x, float a, float b) { w[0][x] = a; w[0][x + 1] = b; }
 };
 // operand v (tr_frag) of acc += tile^T P.  bf16: acc[db] row m is dim 32 db + m.  fp32: acc[e] row m is dim DB m + e.
-template <typename T, int D> __device__ __forceinline__ void gn_tr_mma(const int v, const u32x4_t& f, const GnP<T>& p, f32x16 (&acc)[D / 32]) {
+template <typename T, int D, int NT> __device__ __forceinline__ void gn_tr_mma(const int v, const u32x4_t& f, const GnP<T, NT>& p, f32x16 (&acc)[D / 32]) {
   if constexpr (sizeof(T) == 2) {
     const int u = v / (D / 32), db = v % (D / 32);
-    const u32x4_t b = {p.w[4 * u], p.w[4 * u + 1], p.w[4 * u + 2], p.w[4 * u + 3]};
-    acc[db] = mfma32(__builtin_bit_cast(bf16x8, f), __builtin_bit_cast(bf16x8, b), acc[db]);
+#pragma unroll
+    for (int t = NT - 1; t >= 0; --t) {   // (the smallest terms first)
+      const u32x4_t b = {p.w[t][4 * u], p.w[t][4 * u + 1], p.w[t][4 * u + 2], p.w[t][4 * u + 3]};
+      acc[db] = mfma32(__builtin_bit_cast(bf16x8, f), __builtin_bit_cast(bf16x8, b), acc[db]);
+    }
   } else {
 #pragma unroll
-    for (int e = 0; e < D / 32; ++e) acc[e] = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(f[e]), p.w[v], acc[e], 0, 0, 0);
+    for (int e = 0; e < D / 32; ++e) acc[e] = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(f[e]), p.w[0][v], acc[e], 0, 0, 0);
   }
 }
 
@@ -357,9 +375,14 @@ __device__ __forceinline__ void gn_key_loop(const Params& p, const GnTile& t, Gn
 }
 
 // ---- forward ----------------------------------------------------------------------------------
-// n_split > 1: O (not normalised) and {running maximum in log2 units, sum} of every row go to part[split][block] and
+// log-sum-exp of a row: m the largest product, l the sum of exponentials relative to it
+__device__ __forceinline__ float gn_lse(const Params& p, float m, float l) {
+  return __builtin_fmaf(m, p.sm_scale, __builtin_amdgcn_logf(l) * 0.6931471805599453f);
+}
+
+// n_split > 1: O (not normalised) and {running maximum of the products, sum} of every row go to part[split][block] and
 // part_ml[split][block][32], which the combine kernel merges.
-template <typename T, int D, int KH>
+template <typename T, int D, int KH, int NT>
 __global__ __launch_bounds__(256 * KH, 2) void fwd_generic_kernel(Params p, int32_t tiles, int32_t n_split, int lp, int32_t max_len,
                                                                   float* __restrict__ part, float2* __restrict__ part_ml) {
   typedef Gn<T, D> X;
@@ -381,7 +404,7 @@ __global__ __launch_bounds__(256 * KH, 2) void fwd_generic_kernel(Params p, int3
   f32x16 of[X::DB];
   gn_zero(of);
   float m_run = -1e30f, l_run = 0.f;
-  const bf16x2 ones = {(__bf16)1.0f, (__bf16)1.0f};   // (the row sum is that of the rounded probabilities)
+  [[maybe_unused]] const bf16x2 ones = {(__bf16)1.0f, (__bf16)1.0f};   // (NT = 1: the row sum is that of the rounded probabilities)
   const float c = p.sm_scale * 1.4426950408889634f;
   GnAddr<T, D> ad;
   ad.init(lane, group * GnRow<T, D, KH>::GROUP);
@@ -420,11 +443,11 @@ __global__ __launch_bounds__(256 * KH, 2) void fwd_generic_kernel(Params p, int3
 #pragma unroll
         for (int x = 0; x < 16; ++x) of[db][x] *= alpha;
     }
-    GnP<T> pr[Y::U];
+    GnP<T, NT> pr[Y::U];
     auto exps = [&](const int u, const int x) __attribute__((always_inline)) {   // registers x, x + 1
       const float a = __builtin_amdgcn_exp2f(__builtin_fmaf(s[u][x], c, -mc)), b2 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[u][x + 1], c, -mc));
       pr[u].set2(x, a, b2);
-      if constexpr (X::BF) l_run = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, pr[u].w[x >> 1]), ones, l_run, false);
+      if constexpr (X::BF && NT == 1) l_run = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, pr[u].w[0][x >> 1]), ones, l_run, false);
       else l_run += a + b2;
     };
 #pragma unroll
@@ -432,7 +455,7 @@ __global__ __launch_bounds__(256 * KH, 2) void fwd_generic_kernel(Params p, int3
     gn_pipeline<Y::U * NP>(
         [&](const int i) __attribute__((always_inline)) { return ad.tr_frag(i % NP, at + Y::TILE + 32 * (i / NP) * X::RB); },
         [&](const int i, const u32x4_t& f) __attribute__((always_inline)) {
-          gn_tr_mma<T, D>(i % NP, f, pr[i / NP], of);
+          gn_tr_mma<T, D, NT>(i % NP, f, pr[i / NP], of);
           if (i < NP && Y::U == 2) {   // 16 exponentials over NP instructions (4, 8 or 16)
             if (NP == 4) exps(Y::U - 1, 4 * i);
             if (NP <= 8) exps(Y::U - 1, NP == 4 ? 4 * i + 2 : 2 * i);
@@ -464,12 +487,12 @@ __global__ __launch_bounds__(256 * KH, 2) void fwd_generic_kernel(Params p, int3
     const int64_t at = (int64_t)b.split * p.Hkv * tiles * 4 + t.block;
     if (!t.active) return;
     part_store<T, D>(part, at, lane, of, 1.f);
-    if (hh == 0) part_ml[at * 32 + lane] = make_float2(l_tot > 0.f ? m_run * c : -INFINITY, l_tot);
+    if (hh == 0) part_ml[at * 32 + lane] = make_float2(l_tot > 0.f ? m_run : -INFINITY, l_tot);
   } else if (t.valid) {
     const float inv = 1.f / l_tot;
     T* dst = (T*)p.o + roff;
     part_emit<T, D>(of, hh, [&](int d, float v0, float v1, float v2, float v3) { part_store4<T>(dst + d, v0 * inv, v1 * inv, v2 * inv, v3 * inv); });
-    if (hh == 0) p.lse[(int64_t)t.h * p.C + t.i] = (m_run * c + __builtin_amdgcn_logf(l_tot)) * 0.6931471805599453f;
+    if (hh == 0) p.lse[(int64_t)t.h * p.C + t.i] = gn_lse(p, m_run, l_tot);
   }
 }
 
@@ -552,7 +575,8 @@ __global__ __launch_bounds__(256) void fwd_combine_kernel(Params p, int32_t tile
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int64_t block = blockIdx.x, blocks = (int64_t)p.Hkv * tiles * 4;
   const int64_t at = (block * (D / 8) + wave) * 64 + lane;
-  float M = -1e38f, L = 0.f;   // (a split that saw nothing of the row holds -inf and 0)
+  const float c = p.sm_scale * 1.4426950408889634f;
+  float M = -1e30f, L = 0.f;   // (a split that saw nothing of the row holds -inf and 0)
   float4 acc[GW];
 #pragma unroll
   for (int j = 0; j < GW; ++j) acc[j] = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -569,7 +593,7 @@ __global__ __launch_bounds__(256) void fwd_combine_kernel(Params p, int32_t tile
       }
     }
     const float m_new = fmaxf(fmaxf(fmaxf(ml[0].x, ml[1].x), fmaxf(ml[2].x, ml[3].x)), M);
-    const float w0 = __builtin_amdgcn_exp2f(M - m_new);
+    const float w0 = __builtin_amdgcn_exp2f((M - m_new) * c);
     M = m_new;
     L *= w0;
 #pragma unroll
@@ -577,7 +601,7 @@ __global__ __launch_bounds__(256) void fwd_combine_kernel(Params p, int32_t tile
 #pragma unroll
     for (int u = 0; u < 4; ++u)
       if (s0 + u < n_split) {
-        const float w = __builtin_amdgcn_exp2f(ml[u].x - m_new);
+        const float w = __builtin_amdgcn_exp2f((ml[u].x - m_new) * c);
         L += ml[u].y * w;
 #pragma unroll
         for (int j = 0; j < GW; ++j) { acc[j].x += v[j][u].x * w; acc[j].y += v[j][u].y * w; acc[j].z += v[j][u].z * w; acc[j].w += v[j][u].w * w; }
@@ -592,13 +616,13 @@ __global__ __launch_bounds__(256) void fwd_combine_kernel(Params p, int32_t tile
       part_store4<T>((T*)p.o + (int64_t)i * p.q_tok_stride + (int64_t)h * p.q_head_stride + d, r.x, r.y, r.z, r.w);
   });
   if (threadIdx.x < 32 && gn_out_row(p, tiles, block, threadIdx.x, i, h))
-    p.lse[(int64_t)h * p.C + i] = (M + __builtin_amdgcn_logf(L)) * 0.6931471805599453f;
+    p.lse[(int64_t)h * p.C + i] = gn_lse(p, M, L);
 }
 
 // ---- dQ -----------------------------------------------------------------------------------------
 // Also computes Delta = <dO, O> of its rows for the dK / dV kernel, which runs afterwards: p.delta, or (bias != nullptr) the
 // bias words from which attn_bwd_dkv_mfma.hip starts its accumulators.
-template <typename T, int D, int KH>
+template <typename T, int D, int KH, int NT>
 __device__ __forceinline__ void dq_body(const Params& p, unsigned char* smem, int32_t block, int32_t tiles, int32_t n_split, int lp, int32_t max_len,
                                         float* __restrict__ part, float* __restrict__ bias, int32_t n_stages) {
   typedef Gn<T, D> X;
@@ -647,7 +671,7 @@ __device__ __forceinline__ void dq_body(const Params& p, unsigned char* smem, in
     const bool mask = t0 + Y::KT > V_min;
     const int32_t rel = t.V - t0 - 4 * hh;
     f32x16 s[2];   // S and dP of one block
-    GnP<T> ds;
+    GnP<T, NT> ds;
     // per block: S, then dP with the exponentials of S between its instructions, dS, then dQ
     gn_pipeline<Y::U * L>(
         [&](const int i) __attribute__((always_inline)) {
@@ -673,7 +697,7 @@ __device__ __forceinline__ void dq_body(const Params& p, unsigned char* smem, in
               for (int x = 0; x < 16; x += 2) ds.set2(x, s[0][x] * (s[1][x] - delta), s[0][x + 1] * (s[1][x + 1] - delta));
             }
           } else {
-            gn_tr_mma<T, D>(k - 2 * NJ, f, ds, dq);
+            gn_tr_mma<T, D, NT>(k - 2 * NJ, f, ds, dq);
           }
         });
   });
@@ -698,11 +722,11 @@ __device__ __forceinline__ void dq_body(const Params& p, unsigned char* smem, in
     part_emit<T, D>(dq, hh, [&](int d, float v0, float v1, float v2, float v3) { part_store4<T>(dst + d, v0 * sc, v1 * sc, v2 * sc, v3 * sc); });
   }
 }
-template <typename T, int D, int KH>
+template <typename T, int D, int KH, int NT>
 __global__ __launch_bounds__(256 * KH, (Gn<T, D>::RB == 512 ? 1 : 2)) void dq_generic_kernel(Params p, int32_t tiles, int32_t n_split, int lp, int32_t max_len,
                                                                                              float* __restrict__ part, float* __restrict__ bias, int32_t n_stages) {
   extern __shared__ __align__(16) unsigned char smem[];
-  dq_body<T, D, KH>(p, smem, blockIdx.x, tiles, n_split, lp, max_len, part, bias, n_stages);
+  dq_body<T, D, KH, NT>(p, smem, blockIdx.x, tiles, n_split, lp, max_len, part, bias, n_stages);
 }
 
 // ---- dK / dV ------------------------------------------------------------------------------------
@@ -713,7 +737,7 @@ template <typename T, int D> struct GnKey {
   static constexpr int KT = GnTiles<T, D>::KT;
   static constexpr int STAT = 2 * GnTiles<T, D>::BUF, LDS = STAT + 2 * 2 * 64 * 4;   // two buffers, {lse2, delta} of their rows
 };
-template <typename T, typename TG, int D, bool OWN_DELTA>
+template <typename T, typename TG, int D, bool OWN_DELTA, int NT>
 __device__ __forceinline__ void dkv_body(const Params& p, unsigned char* smem, int32_t bid, int32_t n_split, int lp, float* __restrict__ part) {
   typedef Gn<T, D> X;
   typedef GnKey<T, D> R;
@@ -860,7 +884,7 @@ __device__ __forceinline__ void dkv_body(const Params& p, unsigned char* smem, i
       const bool mask = base < r_key_max;   // (wave-uniform)
       const int32_t rel = r_key - base - 4 * hh;
       f32x16 sv[2];
-      GnP<T> pr, ds;
+      GnP<T, NT> pr, ds;
       gn_pipeline<Y::U * L>(
           [&](const int i) __attribute__((always_inline)) {
             const int u = i / L, k = i % L;
@@ -886,7 +910,7 @@ __device__ __forceinline__ void dkv_body(const Params& p, unsigned char* smem, i
                 for (int x = 0; x < 16; x += 2) pr.set2(x, sv[0][x], sv[0][x + 1]);
               }
             } else if (k < 2 * NJ + NP) {
-              gn_tr_mma<T, D>(k - 2 * NJ, f, pr, dv);
+              gn_tr_mma<T, D, NT>(k - 2 * NJ, f, pr, dv);
               const int n = k - 2 * NJ;
 #pragma unroll
               for (int x = n * (16 / NP); x < (n + 1) * (16 / NP); ++x)
@@ -896,7 +920,7 @@ __device__ __forceinline__ void dkv_body(const Params& p, unsigned char* smem, i
                 for (int x = 0; x < 16; x += 2) ds.set2(x, sv[1][x], sv[1][x + 1]);
               }
             } else {
-              gn_tr_mma<T, D>(k - 2 * NJ - NP, f, ds, dk);
+              gn_tr_mma<T, D, NT>(k - 2 * NJ - NP, f, ds, dk);
             }
           });
     }
@@ -922,22 +946,22 @@ __device__ __forceinline__ void dkv_body(const Params& p, unsigned char* smem, i
     part_emit<T, D>(dv, hh, [&](int d, float v0, float v1, float v2, float v3) { part_add4<TG>(pv + d, v0, v1, v2, v3); });
   }
 }
-template <typename T, typename TG, int D>
+template <typename T, typename TG, int D, int NT>
 __global__ __launch_bounds__(256, (D == 128 || sizeof(T) == 4 ? 1 : 2)) void dkv_generic_kernel(Params p, int32_t n_split, int lp, float* __restrict__ part) {
   extern __shared__ __align__(16) unsigned char smem[];
-  dkv_body<T, TG, D, false>(p, smem, blockIdx.x, n_split, lp, part);
+  dkv_body<T, TG, D, false, NT>(p, smem, blockIdx.x, n_split, lp, part);
 }
 
 // dQ and dK / dV of a short call in one launch: the first kv_blocks workgroups take the keys, the others the rows; neither
 // waits for the other (each computes Delta itself).  8 us of launch and start-up less than one after the other, where
 // neither fills the chip.
-template <typename T, typename TG, int D>
+template <typename T, typename TG, int D, int NT_ROW, int NT_KEY>
 __global__ __launch_bounds__(256, (D == 128 || sizeof(T) == 4 ? 1 : 2)) void bwd_pair_kernel(Params p, int32_t kv_blocks, int32_t kv_split, float* __restrict__ kv_part,
                                                                                             int32_t tiles, int32_t n_split, int lp, int32_t max_len,
                                                                                             float* __restrict__ part) {
   extern __shared__ __align__(16) unsigned char smem[];
-  if ((int32_t)blockIdx.x < kv_blocks) dkv_body<T, TG, D, true>(p, smem, blockIdx.x, kv_split, lp, kv_part);
-  else dq_body<T, D, 1>(p, smem, (int32_t)blockIdx.x - kv_blocks, tiles, n_split, lp, max_len, part, nullptr, 0);
+  if ((int32_t)blockIdx.x < kv_blocks) dkv_body<T, TG, D, true, NT_KEY>(p, smem, blockIdx.x, kv_split, lp, kv_part);
+  else dq_body<T, D, 1, NT_ROW>(p, smem, (int32_t)blockIdx.x - kv_blocks, tiles, n_split, lp, max_len, part, nullptr, 0);
 }
 
 // What is left of a backward with splits, in one launch: workgroups below dq_blocks add the dQ partials, the others
@@ -1108,15 +1132,18 @@ size_t bwd_generic_workspace_bytes(const Params& p, bool bf, int32_t max_len) {
   return pair > two ? pair : two;
 }
 
-template <typename T, int D, int KH>
+// terms of a probability (GnP) where a shape has no kernels of its own, for results of type TO
+template <typename T, typename TO> constexpr int GN_TERMS = sizeof(T) == 4 ? 1 : sizeof(TO) == 4 ? 3 : 2;
+
+template <typename T, int D, int KH, int NT>
 static hipError_t fwd_launch(const Params& p, int32_t tiles, int32_t ns, int32_t len, float* part, float2* ml, hipStream_t st) {
   typedef GnRow<T, D, KH> R;
   static DeviceOnce lds_once;
-  if (hipError_t e = ensure_max_dynamic_lds(lds_once, (const void*)fwd_generic_kernel<T, D, KH>, R::LDS); e != hipSuccess) return e;
-  fwd_generic_kernel<T, D, KH><<<dim3((unsigned)tiles * p.Hkv * ns), dim3(R::THREADS), R::LDS, st>>>(p, tiles, ns, __builtin_ctz(p.P), len, part, ml);
+  if (hipError_t e = ensure_max_dynamic_lds(lds_once, (const void*)fwd_generic_kernel<T, D, KH, NT>, R::LDS); e != hipSuccess) return e;
+  fwd_generic_kernel<T, D, KH, NT><<<dim3((unsigned)tiles * p.Hkv * ns), dim3(R::THREADS), R::LDS, st>>>(p, tiles, ns, __builtin_ctz(p.P), len, part, ml);
   return hipGetLastError();
 }
-template <typename T, int D>
+template <typename T, int D, int NT = GN_TERMS<T, T>>
 static hipError_t fwd_generic(const Params& p, int32_t max_len, void* ws, size_t ws_bytes, const char* name, hipStream_t st) {
   // (the forward also runs without a workspace)
   const GnPlan sp = gn_plan(p, Gn<T, D>::BF, max_len, false, ws ? gn_fit(ws_bytes, gn_row_blocks(p) * 32 * (p.D * 4 + 8)) : 1);
@@ -1125,40 +1152,44 @@ static hipError_t fwd_generic(const Params& p, int32_t max_len, void* ws, size_t
   float2* ml = (float2*)((unsigned char*)ws + gn_row_part_bytes(p, ns));
   const int32_t tiles = gn_tiles(p.C, p.G, p.P, p.m, p.qp), len = gn_list_len(p, max_len);
   ProfScope prof_(name, st);
-  hipError_t e = sp.groups == 2 ? fwd_launch<T, D, 2>(p, tiles, ns, len, part, ml, st) : fwd_launch<T, D, 1>(p, tiles, ns, len, part, ml, st);
+  hipError_t e = sp.groups == 2 ? fwd_launch<T, D, 2, NT>(p, tiles, ns, len, part, ml, st) : fwd_launch<T, D, 1, NT>(p, tiles, ns, len, part, ml, st);
   if (e == hipSuccess && ns > 1) {
     fwd_combine_kernel<T, D><<<dim3((unsigned)(gn_row_blocks(p))), dim3(256), 0, st>>>(p, tiles, ns, part, ml);
     e = hipGetLastError();
   }
   return e;
 }
-hipError_t launch_fwd_generic(const Params& p, bool bf, int32_t max_len, void* ws, size_t ws_bytes, const char* name, hipStream_t st) {
+hipError_t launch_fwd_generic(const Params& p, bool bf, int32_t max_len, void* ws, size_t ws_bytes, hipStream_t st) {
+  const char* name = "attn_fwd_generic";
   if (bf) return p.D == 128 ? fwd_generic<bf16_t, 128>(p, max_len, ws, ws_bytes, name, st) : fwd_generic<bf16_t, 64>(p, max_len, ws, ws_bytes, name, st);
   return p.D == 128 ? fwd_generic<float, 128>(p, max_len, ws, ws_bytes, name, st) : fwd_generic<float, 64>(p, max_len, ws, ws_bytes, name, st);
 }
+hipError_t launch_fwd_generic_bf16_128(const Params& p, int32_t max_len, void* ws, size_t ws_bytes, hipStream_t st) {
+  return fwd_generic<bf16_t, 128, 1>(p, max_len, ws, ws_bytes, "attn_fwd_mfma", st);
+}
 
-template <typename T, int D, int KH>
+template <typename T, int D, int KH, int NT>
 static hipError_t dq_launch(const Params& p, int32_t tiles, int32_t ns, int32_t len, float* part, float* bias, int32_t n_stages, hipStream_t st) {
   typedef GnRow<T, D, KH> R;
   static DeviceOnce lds_once;
-  if (hipError_t e = ensure_max_dynamic_lds(lds_once, (const void*)dq_generic_kernel<T, D, KH>, R::LDS); e != hipSuccess) return e;
-  dq_generic_kernel<T, D, KH><<<dim3((unsigned)tiles * p.Hkv * ns), dim3(R::THREADS), R::LDS, st>>>(p, tiles, ns, __builtin_ctz(p.P), len, part,
+  if (hipError_t e = ensure_max_dynamic_lds(lds_once, (const void*)dq_generic_kernel<T, D, KH, NT>, R::LDS); e != hipSuccess) return e;
+  dq_generic_kernel<T, D, KH, NT><<<dim3((unsigned)tiles * p.Hkv * ns), dim3(R::THREADS), R::LDS, st>>>(p, tiles, ns, __builtin_ctz(p.P), len, part,
                                                                                                    bias, n_stages);
   return hipGetLastError();
 }
-template <typename T, int D>
+template <typename T, int D, int NT = GN_TERMS<T, T>>
 static hipError_t dq_generic(const Params& p, int32_t max_len, float* part, size_t part_bytes, float* bias, int32_t n_stages, int32_t* splits,
                              hipStream_t st) {
   const GnPlan sp = gn_plan(p, Gn<T, D>::BF, max_len, true, gn_fit(part_bytes, gn_row_blocks(p) * 32 * p.D * 4));
   const int32_t tiles = gn_tiles(p.C, p.G, p.P, p.m, p.qp), len = gn_list_len(p, max_len);
   *splits = sp.n;
   if constexpr (Gn<T, D>::RB < 512)   // (fp32 at head dim 128 needs 320 registers: one wave per SIMD)
-    if (sp.groups == 2) return dq_launch<T, D, 2>(p, tiles, sp.n, len, part, bias, n_stages, st);
-  return dq_launch<T, D, 1>(p, tiles, sp.n, len, part, bias, n_stages, st);
+    if (sp.groups == 2) return dq_launch<T, D, 2, NT>(p, tiles, sp.n, len, part, bias, n_stages, st);
+  return dq_launch<T, D, 1, NT>(p, tiles, sp.n, len, part, bias, n_stages, st);
 }
 hipError_t launch_dq_generic_bf16_128(const Params& p, int32_t max_len, float* part, size_t part_bytes, float* bias, int32_t n_stages,
                                       int32_t* splits, hipStream_t st) {
-  return dq_generic<bf16_t, 128>(p, max_len, part, part_bytes, bias, n_stages, splits, st);
+  return dq_generic<bf16_t, 128, 1>(p, max_len, part, part_bytes, bias, n_stages, splits, st);
 }
 
 template <typename T, typename TG, int D>
@@ -1182,25 +1213,25 @@ hipError_t launch_bwd_finish(const Params& p, bool bf, int32_t dq_split, const f
 }
 
 // The one-launch backward, if the shape takes it and the workspace has room (else *done stays false)
-template <typename T, typename TG, int D>
+template <typename T, typename TG, int D, int NT_ROW = GN_TERMS<T, T>, int NT_KEY = GN_TERMS<T, TG>>
 static hipError_t bwd_pair(Params p, int32_t max_len, void* ws, size_t ws_bytes, hipStream_t st, bool* done) {
   const GnPair t = gn_pair(p, Gn<T, D>::BF, max_len);
   if (!gn_takes_pair(p, Gn<T, D>::BF, max_len, t) || gn_pair_bytes(p, max_len, t) > ws_bytes) return hipSuccess;
   *done = true;
   constexpr int LDS = GnKey<T, D>::LDS > GnRow<T, D, 1>::LDS ? GnKey<T, D>::LDS : GnRow<T, D, 1>::LDS;
   static DeviceOnce once;
-  if (hipError_t e = ensure_max_dynamic_lds(once, (const void*)bwd_pair_kernel<T, TG, D>, LDS); e != hipSuccess) return e;
+  if (hipError_t e = ensure_max_dynamic_lds(once, (const void*)bwd_pair_kernel<T, TG, D, NT_ROW, NT_KEY>, LDS); e != hipSuccess) return e;
   p.delta = nullptr;
   float* kv_part = (float*)ws;
   float* dq_part = (float*)((unsigned char*)ws + gn_key_part_bytes(p, max_len, t.kv_split));
   const int32_t tiles = gn_tiles(p.C, p.G, p.P, p.m, p.qp), units = gn_key_units(p, max_len), kv_blocks = units * p.Hkv * t.kv_split;
-  bwd_pair_kernel<T, TG, D><<<dim3((unsigned)(kv_blocks + tiles * p.Hkv * t.row_split)), dim3(256), LDS, st>>>(
+  bwd_pair_kernel<T, TG, D, NT_ROW, NT_KEY><<<dim3((unsigned)(kv_blocks + tiles * p.Hkv * t.row_split)), dim3(256), LDS, st>>>(
       p, kv_blocks, t.kv_split, kv_part, tiles, t.row_split, __builtin_ctz(p.P), gn_list_len(p, max_len), dq_part);
   if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
   return bwd_finish<T, TG, D>(p, t.row_split, dq_part, t.kv_split > 1 ? units : 0, t.kv_split, kv_part, st);
 }
 hipError_t launch_bwd_pair_bf16_128(const Params& p, int32_t max_len, void* ws, size_t ws_bytes, hipStream_t st, bool* done) {
-  return p.grad_is_bf16 ? bwd_pair<bf16_t, bf16_t, 128>(p, max_len, ws, ws_bytes, st, done) : bwd_pair<bf16_t, float, 128>(p, max_len, ws, ws_bytes, st, done);
+  return p.grad_is_bf16 ? bwd_pair<bf16_t, bf16_t, 128, 1, 1>(p, max_len, ws, ws_bytes, st, done) : bwd_pair<bf16_t, float, 128, 1, 1>(p, max_len, ws, ws_bytes, st, done);
 }
 
 template <typename T, typename TG, int D>
@@ -1209,7 +1240,7 @@ static hipError_t bwd_generic(Params p, int32_t max_len, void* ws, size_t ws_byt
   bool done = false;
   if (hipError_t e = bwd_pair<T, TG, D>(p, max_len, ws, ws_bytes, st, &done); done || e != hipSuccess) return e;
   static DeviceOnce once_kv;
-  if (hipError_t e = ensure_max_dynamic_lds(once_kv, (const void*)dkv_generic_kernel<T, TG, D>, GnKey<T, D>::LDS); e != hipSuccess) return e;
+  if (hipError_t e = ensure_max_dynamic_lds(once_kv, (const void*)dkv_generic_kernel<T, TG, D, GN_TERMS<T, TG>>, GnKey<T, D>::LDS); e != hipSuccess) return e;
   // [Delta][dK / dV slices][dQ partials]; a workspace without room for the slices of this call takes fewer
   unsigned char* w = (unsigned char*)ws;
   p.delta = (float*)w;
@@ -1224,7 +1255,7 @@ static hipError_t bwd_generic(Params p, int32_t max_len, void* ws, size_t ws_byt
   int32_t ns = 1;
   hipError_t e = dq_generic<T, D>(p, max_len, dq_part, left, nullptr, 0, &ns, st);
   if (e != hipSuccess) return e;
-  dkv_generic_kernel<T, TG, D><<<dim3((unsigned)units * p.Hkv * nk), dim3(256), GnKey<T, D>::LDS, st>>>(p, nk, __builtin_ctz(p.P), kv_part);
+  dkv_generic_kernel<T, TG, D, GN_TERMS<T, TG>><<<dim3((unsigned)units * p.Hkv * nk), dim3(256), GnKey<T, D>::LDS, st>>>(p, nk, __builtin_ctz(p.P), kv_part);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
   return bwd_finish<T, TG, D>(p, ns, dq_part, p.qp ? p.max_multi : nk > 1 ? units : 0, nk, kv_part, st);

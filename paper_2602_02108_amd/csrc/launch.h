@@ -38,12 +38,13 @@ hipError_t launch_qp_prepare(Params& p, void* ws, hipStream_t st);
 // attn_generic.hip: fp32 tensors, head dim 64, pages of fewer than 128 tokens.  max_len: host-side bound of the
 // list length (of the union with one list per query page)
 size_t fwd_generic_workspace_bytes(const Params& p, bool is_bf16, int32_t max_len);
-hipError_t launch_fwd_generic(const Params& p, bool is_bf16, int32_t max_len, void* ws, size_t ws_bytes, const char* name, hipStream_t st);
+hipError_t launch_fwd_generic(const Params& p, bool is_bf16, int32_t max_len, void* ws, size_t ws_bytes, hipStream_t st);
 size_t bwd_generic_workspace_bytes(const Params& p, bool is_bf16, int32_t max_len);
 size_t bwd_generic_min_bytes(const Params& p);   // without splits
 hipError_t launch_bwd_generic(const Params& p, bool is_bf16, int32_t max_len, void* ws, size_t ws_bytes, hipStream_t st);
 // the same forward and dQ kernels for shapes with kernels of their own but too few rows to fill the chip with them
 bool rows_take_generic(const Params& p, int32_t max_len, bool dq);
+hipError_t launch_fwd_generic_bf16_128(const Params& p, int32_t max_len, void* ws, size_t ws_bytes, hipStream_t st);
 // dQ and dK / dV of a short call in one launch (*done: whether it was taken)
 bool bwd_takes_pair(const Params& p, bool is_bf16, int32_t max_len);
 size_t bwd_pair_bytes(const Params& p, bool is_bf16, int32_t max_len);

@@ -4,8 +4,9 @@ import numpy as np
 import pytest
 import torch
 
+import oracle as orc
 from paper_2602_02108_amd import api
-from paper_2602_02108_amd.workloads import WORKLOADS, Workload, make_inputs
+from paper_2602_02108_amd.workloads import WORKLOADS, Workload, make_inputs, to_numpy
 
 import parity_util as pu
 
@@ -64,6 +65,34 @@ def test_generic_kernel_edges(w):
     with pu.kernels_ran(("attn_fwd_generic", "attn_bwd_generic"), absent=pu.MFMA_KERNELS):
         rep = pu.full_parity(w, init_grad=0.25)
     _show(w.name, rep)
+
+
+# bf16 tensors of shapes without kernels of their own: probabilities and dS keep 32 bits.  Against 64 bits with the same O and LSE
+# in the backward, dK / dV carry the rounding of LSE (about 8: 2.4e-7 relative to a probability) and of the exponent, O and
+# dQ only that of their own storage, 2^-8 of an element at most.  Probabilities rounded to bf16 miss both by a factor of 100.
+@pytest.mark.parametrize("D,P,m,n,top_k", [(64, 16, 3, 37, 5), (64, 128, 1, 6, None), (128, 32, 5, 23, None), (128, 64, 17, 60, 24), (64, 32, 36, 60, 12)])
+def test_bf16_shapes_without_kernels_of_their_own_keep_fp32_probabilities(D, P, m, n, top_k):
+    w = Workload("wide", 8, 2, D, P, m * P, n * P, top_k, "bf16", "f32", D ** -0.5, extra_phys=2, boost_frac=0.1, seed=80 + m)
+    x = make_inputs(w, "cuda")
+    hx, sh = pu.host_inputs(x), pu.shape_of(w)
+    sel = cnt = osel = ocnt = None
+    if top_k is not None:
+        sel, cnt, _ = pu.gpu_select(w, x, want_scores=False)
+        osel, ocnt = sel.cpu().numpy(), cnt.cpu().numpy()
+    got = pu.gpu_fwd_bwd(w, x, sel, cnt)
+    args = (sh, hx["q"], hx["k_pool"], hx["v_pool"], hx["page_table"])
+    o, lse = orc.attn_fwd(*args, osel, ocnt, prec="f64")
+    assert np.abs(pu.f32(got["lse"]) - lse).max() <= 4e-6
+    glse = got["lse"].cpu().numpy().astype(np.float64)
+    delta = orc.delta(sh, hx["d_o"], to_numpy(got["o"].float()), prec="f64")
+    dq = orc.attn_bwd_dq(*args, glse, delta, hx["d_o"], osel, ocnt, prec="f64")
+    dk, dv = np.zeros(x["dk_pool"].shape), np.zeros(x["dv_pool"].shape)
+    orc.attn_bwd_dkv(*args, glse, delta, hx["d_o"], dk, dv, osel, ocnt, prec="f64")
+    for name, a, b in (("dK", got["dk_pool"], dk), ("dV", got["dv_pool"], dv)):
+        assert pu.errors(pu.f32(a), b)[1] <= 4e-6, (name, pu.errors(pu.f32(a), b))
+    for name, a, b in (("O", got["o"], o), ("dQ", got["dq"], dq)):
+        over = np.abs(pu.f32(a) - b) - 2.0**-8 * np.abs(b)
+        assert over.max() <= 4e-6 * np.abs(b).max(), (name, over.max(), np.abs(b).max())
 
 
 def test_strided_views_are_honoured():

@@ -274,6 +274,8 @@ oomb_status oomb_paged_attn_bwd(const oomb_attn_desc* desc, const void* q, const
   if (s != OOMB_OK) return s;
   const bool bf = desc->dtype == OOMB_BF16;
   const bool use_mfma = !force_generic() && mfma_supported(p, bf);
+  // lists of the shape-generic backward have at most 65535 entries
+  if (!use_mfma && (max_len > 65535 || p.Hkv > 65535)) return OOMB_ERR_UNSUPPORTED;
   const size_t need = use_mfma ? bwd_mfma_min_bytes(p, max_len) : bwd_generic_min_bytes(p);
   if (!workspace || workspace_bytes < need || !aligned16(workspace)) return OOMB_ERR_WORKSPACE;
   p.q = q; p.k_pool = k_pool; p.v_pool = v_pool; p.page_table = page_table;
@@ -361,8 +363,9 @@ oomb_status oomb_paged_attn_bwd_qp(const oomb_attn_desc* desc, const void* q, co
   if (s != OOMB_OK) return s;
   const bool bf = desc->dtype == OOMB_BF16;
   const bool use_mfma = !force_generic() && mfma_supported(p, bf);
-  // (the cut pages of the slice reduction are a grid dimension of at most 65535)
-  if (p.Hkv > 65535 || (use_mfma && qp_max_multi(p, sel_stride) > 65535))
+  // at most 65535: list entries of the shape-generic backward, cut pages of the slice reduction (a grid dimension)
+  if (p.Hkv > 65535 || (!use_mfma && qp_union_cap(p, sel_stride) > 65535) ||
+      (use_mfma && qp_max_multi(p, sel_stride) > 65535))
     return OOMB_ERR_UNSUPPORTED;
   if (!workspace || workspace_bytes < qp_workspace_bytes(p, sel_stride, bf, true, true) || !aligned16(workspace))
     return OOMB_ERR_WORKSPACE;

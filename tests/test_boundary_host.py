@@ -119,6 +119,16 @@ def test_null_pointers_and_workspace_are_rejected():
                                   None) == api.ERR_UNSUPPORTED
 
 
+@pytest.mark.parametrize("qp", [False, True])
+def test_lists_of_more_than_65535_entries_are_refused_by_the_shape_generic_backward(qp):
+    n = 65536
+    d = _good_desc(page_size=16, chunk_len=16, ctx_len=16 * n, num_phys_pages=n)
+    fake = ctypes.c_void_p(0x1000)
+    call = api.lib().oomb_paged_attn_bwd_qp if qp else api.lib().oomb_paged_attn_bwd
+    assert call(ctypes.byref(d), fake, fake, fake, fake, fake, fake, n, fake, fake, fake, fake, fake, fake, None, 0,
+                None) == api.ERR_UNSUPPORTED
+
+
 def test_calibrate_rejects_bad_arguments_before_launch():
     l = api.lib()
     out = ctypes.c_double()

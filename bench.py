@@ -554,7 +554,7 @@ def main():
     # (kv_layout belongs to the forward; qp_prepare runs once per phase)
     fwd_ms = phase_ms(["kv_layout", "qp_prepare", "attn_fwd_mfma"]) - 0.5 * phase_ms(["qp_prepare"])
     bwd_ms = phase_ms(["bwd_prep", "bwd_dq_mfma", "bwd_dkv_mfma", "bwd_dkv_reduce"]) + 0.5 * phase_ms(["qp_prepare"])
-    sel_ms = phase_ms(["qpool_partial", "qpool_final", "page_score", "page_score_cached", "topk_select", "page_means",
+    sel_ms = phase_ms(["qpool_partial", "qpool_final", "select_small", "page_score", "page_score_cached", "topk_select", "page_means",
                        "kbar_image", "vote_lse", "vote_sum", "vote_finish"])
     phases = {"select_ms": sel_ms, "fwd_ms": fwd_ms, "bwd_ms": bwd_ms,
               "fwd_tflops": 4.0 * w.D * pairs_avg * w.Hq / (fwd_ms * 1e-3) / 1e12 if fwd_ms > 0 else None,

@@ -234,7 +234,7 @@ def page_score_topk(desc: AttnDesc, q, k_pool, page_table, top_k: int, sel_pages
         sel_count = torch.empty((desc.n_kv_heads,), dtype=torch.int32, device=q.device)
     if workspace is None:
         workspace = _workspace(desc, top_k, OP_SCORE_TOPK, q.device)
-    st = (_nb or _native()).score_topk(desc, q, k_pool, page_table, top_k, sel_pages, sel_count, scores_out, workspace)
+    st = (_nb or _native()).score_topk(desc, q, k_pool, page_table, int(top_k), sel_pages, sel_count, scores_out, workspace)
     if st != OK:
         raise _failed(st, "oomb_page_score_topk", desc, top_k, OP_SCORE_TOPK)
     return sel_pages, sel_count
@@ -542,7 +542,7 @@ def page_score_topk_cached(desc: AttnDesc, q, kbar_cache, top_k: int, sel_pages=
         sel_count = torch.empty((desc.n_kv_heads,), dtype=torch.int32, device=q.device)
     if workspace is None:
         workspace = _workspace(desc, top_k, OP_SCORE_TOPK, q.device)
-    st = (_nb or _native()).score_topk_cached(desc, q, kbar_cache, top_k, sel_pages, sel_count, scores_out, workspace)
+    st = (_nb or _native()).score_topk_cached(desc, q, kbar_cache, int(top_k), sel_pages, sel_count, scores_out, workspace)
     if st != OK:
         raise _failed(st, "oomb_page_score_topk_cached", desc, top_k, OP_SCORE_TOPK)
     return sel_pages, sel_count
@@ -555,7 +555,7 @@ def local_page_list(desc: AttnDesc, window_pages: int, device, sel_pages=None, s
         sel_pages = torch.empty((desc.n_kv_heads, window_pages + m), dtype=torch.int32, device=device)
     if sel_count is None:
         sel_count = torch.empty((desc.n_kv_heads,), dtype=torch.int32, device=device)
-    st = (_nb or _native()).local_page_list(desc, window_pages, sel_pages, sel_count)
+    st = (_nb or _native()).local_page_list(desc, int(window_pages), sel_pages, sel_count)
     if st != OK:
         raise _refused("oomb_local_page_list") if st < 0 else OombError(st, "oomb_local_page_list")
     return sel_pages, sel_count

@@ -2,7 +2,9 @@
 // library costs 10 to 25 us of host time in kernel launches; marshalled through ctypes it took another 6 us and more
 // (every pointer an object, every shape and stride tuple built and compared in Python), which short calls felt.
 // Every function returns the library's status, or -1 if a tensor does not fit the descriptor -- the Python wrapper
-// then says which, or takes the call itself.  The interpreter lock is released during the call of the library.
+// then says which, or takes the call itself.  So it does where torch throws (strides of a 0-dim or sparse tensor, the
+// address of a tensor without storage): no exception leaves this file.  The interpreter lock is released during the
+// call of the library.
 #include <torch/csrc/autograd/python_variable.h>
 
 #include "../../include/oomb.h"
@@ -56,12 +58,23 @@ bool stream_of(const at::Tensor* t, void** st) {
   return true;
 }
 PyObject* status(int s) { return PyLong_FromLong(s); }
+struct Unlocked {   // (taken back on an exception too)
+  PyThreadState* s = PyEval_SaveThread();
+  ~Unlocked() { PyEval_RestoreThread(s); }
+};
 #define OOMB_CALL(expr) \
   oomb_status s_; \
-  Py_BEGIN_ALLOW_THREADS \
-  s_ = (expr); \
-  Py_END_ALLOW_THREADS \
+  { Unlocked u_; s_ = (expr); } \
   return status((int)s_)
+
+template <PyObject* (*F)(PyObject*, PyObject* const*, Py_ssize_t)> PyObject* guarded(PyObject* self, PyObject* const* a, Py_ssize_t nargs) {
+  try {
+    return F(self, a, nargs);
+  } catch (const std::exception&) {
+    PyErr_Clear();
+    return status(-1);
+  }
+}
 
 bool list_args(const oomb_attn_desc& d, const at::Tensor* sel, const at::Tensor* cnt, bool qp, int32_t* stride) {
   if (!qp) {
@@ -171,7 +184,7 @@ PyObject* local_page_list(PyObject*, PyObject* const* a, Py_ssize_t nargs) {
   OOMB_CALL(oomb_local_page_list(&d, (int32_t)window, (int32_t*)ptr(sel), (int32_t*)ptr(cnt), st));
 }
 
-#define OOMB_METHOD(name, fn) {name, (PyCFunction)(void (*)(void))(fn), METH_FASTCALL, nullptr}
+#define OOMB_METHOD(name, fn) {name, (PyCFunction)(void (*)(void))(guarded<fn>), METH_FASTCALL, nullptr}
 PyMethodDef methods[] = {
     OOMB_METHOD("make_desc", make_desc),
     OOMB_METHOD("score_topk", score_topk),

@@ -235,3 +235,35 @@ def test_binding_refuses_tensors_that_do_not_share_the_descriptor_layout():
         api.paged_attn_bwd(desc, q, k, k, pt, q, lse.double(), q, k.clone(), k.clone())
     with pytest.raises(api.OombError, match="descriptor"):
         api.paged_attn_fwd(desc, strided, k, k, pt)
+
+
+def test_tensors_that_torch_refuses_to_describe_raise_from_the_native_binding():
+    import torch
+    q, k = torch.zeros(128, 2, 128), torch.zeros(4, 1, 128, 128)
+    d = api.make_desc(q, k, 512, 0.1)
+    table, cnt, lse = torch.zeros(4, dtype=torch.int32), torch.zeros(1, dtype=torch.int32), torch.empty(2, 128)
+    ws = torch.empty(1 << 20, dtype=torch.uint8)
+    rows, pools = [torch.empty_like(q) for _ in range(3)], [torch.empty_like(k) for _ in range(2)]
+    no_dims = torch.tensor(0, dtype=torch.int32)
+    sparse = torch.zeros(4, 1, 128, 128).to_sparse()
+    with pytest.raises(Exception):
+        api.make_desc(q, sparse, 512, 0.1)
+    for sel, pool in ((no_dims, k), (None, sparse)):
+        with pytest.raises(Exception):
+            api.paged_attn_fwd(d, q, pool, k, table, sel, cnt, rows[0], lse, ws)
+        with pytest.raises(Exception):
+            api.paged_attn_bwd(d, q, pool, k, table, rows[0], lse, rows[1], *pools, sel, cnt, rows[2], ws)
+    with pytest.raises(Exception):
+        api.kv_append(d, k, k, table, k, sparse)
+
+
+def test_native_binding_refuses_tensors_without_storage():
+    import torch
+    from torch._subclasses.fake_tensor import FakeTensorMode
+    with FakeTensorMode():
+        q, k = torch.empty(128, 2, 128, device="cuda"), torch.empty(4, 1, 128, 128, device="cuda")
+        ints = torch.empty(8, 8, dtype=torch.int32, device="cuda")
+        ws = torch.empty(1 << 20, dtype=torch.uint8, device="cuda")
+    d = api.make_desc(q, k, 512, 0.1)
+    with pytest.raises(Exception):
+        api.page_score_topk(d, q, k, ints, 2, ints, ints, None, ws)

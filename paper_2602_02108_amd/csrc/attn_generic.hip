@@ -953,7 +953,7 @@ __global__ __launch_bounds__(256, (D == 128 || sizeof(T) == 4 ? 1 : 2)) void dkv
 }
 
 // dQ and dK / dV of a short call in one launch: the first kv_blocks workgroups take the keys, the others the rows; neither
-// waits for the other (each computes Delta itself).  8 us of launch and start-up less than one after the other, where
+// waits for the other (each computes Delta itself, so dQ must not be written over O).  8 us of launch and start-up less than one after the other, where
 // neither fills the chip.
 template <typename T, typename TG, int D, int NT_ROW, int NT_KEY>
 __global__ __launch_bounds__(256, (D == 128 || sizeof(T) == 4 ? 1 : 2)) void bwd_pair_kernel(Params p, int32_t kv_blocks, int32_t kv_split, float* __restrict__ kv_part,
@@ -1215,6 +1215,7 @@ hipError_t launch_bwd_finish(const Params& p, bool bf, int32_t dq_split, const f
 // The one-launch backward, if the shape takes it and the workspace has room (else *done stays false)
 template <typename T, typename TG, int D, int NT_ROW = GN_TERMS<T, T>, int NT_KEY = GN_TERMS<T, TG>>
 static hipError_t bwd_pair(Params p, int32_t max_len, void* ws, size_t ws_bytes, hipStream_t st, bool* done) {
+  if (p.d_q == p.o) return hipSuccess;   // (dQ over O: the keys' workgroups would read rows of O that the others have overwritten)
   const GnPair t = gn_pair(p, Gn<T, D>::BF, max_len);
   if (!gn_takes_pair(p, Gn<T, D>::BF, max_len, t) || gn_pair_bytes(p, max_len, t) > ws_bytes) return hipSuccess;
   *done = true;

@@ -97,3 +97,20 @@ def test_a_workspace_of_the_longest_history_serves_the_shorter_ones(dtype, P, to
         ref = pu.oracle_fwd_bwd(w, hx, osel, ocnt)
         for name, got, want in (("O", o, ref["o"]), ("dQ", dq, ref["dq"]), ("dK", x["dk_pool"], ref["dk_pool"]), ("dV", x["dv_pool"], ref["dv_pool"])):
             pu.check(name, pu.f32(got), want, dtype)
+
+
+@pytest.mark.parametrize("dtype,D,P", [("bf16", 128, 128), ("bf16", 64, 32), ("f32", 64, 16)])
+def test_dq_may_be_written_over_o(dtype, D, P):
+    # short calls, whose dQ and dK / dV otherwise run side by side, both reading O; the same sums in another split
+    w = Workload("over", 4, 2, D, P, 2 * P, 9 * P, None, dtype, "f32", D ** -0.5, seed=450)
+    x = make_inputs(w, "cuda")
+    desc = _desc(w, x)
+    args = (x["q"], x["k_pool"], x["v_pool"], x["page_table"])
+    o, lse = api.paged_attn_fwd(desc, *args)
+    x["dk_pool"].zero_()
+    x["dv_pool"].zero_()
+    dq = api.paged_attn_bwd(desc, *args, o, lse, x["d_o"], x["dk_pool"], x["dv_pool"], d_q=o)
+    assert dq.data_ptr() == o.data_ptr()
+    ref = pu.oracle_fwd_bwd(w, pu.host_inputs(x), None, None)
+    for name, got, want in (("dQ", dq, ref["dq"]), ("dK", x["dk_pool"], ref["dk_pool"]), ("dV", x["dv_pool"], ref["dv_pool"])):
+        pu.check(name, pu.f32(got), want, dtype)

@@ -576,7 +576,7 @@ static hipError_t launch_scoring(const Params& p, int32_t top_k, int32_t* sel, i
   if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
   if (L.means) {
     if (hipError_t e = launch_page_score_cached(p, qbar, kbar_cache ? kbar_cache : means, scores, st); e != hipSuccess) return e;
-  } else {
+  } else if (p.n_past > 0) {   // (a first chunk has nothing to score: a grid of no workgroups is a launch error)
     dim3 grid((unsigned)((p.n_past + PER_BLOCK - 1) / PER_BLOCK), p.Hkv);
     { ProfScope prof_("page_score", st); page_score_kernel<T, D><<<grid, dim3(256), 0, st>>>(p, qbar, scores, inv_p); }
     if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;

@@ -56,6 +56,22 @@ def test_selection_with_more_pooled_rows_than_one_pass():
     assert np.array_equal(sel.cpu().numpy(), osel)
 
 
+# No history: the lists hold the chunk's own pages, whichever kernels would have scored a past.  Pages of 16 and 32 tokens with more
+# than 192 rows to pool, and (128 tokens) query sums too large for the built-in scratch.
+@pytest.mark.parametrize("Hq,Hkv,D,P,m", [(14, 2, 64, 16, 32), (28, 4, 64, 32, 28), (32, 1, 64, 16, 6), (28, 4, 128, 128, 293)])
+def test_selection_without_a_history(Hq, Hkv, D, P, m):
+    w = Workload("first", Hq, Hkv, D, P, m * P, m * P, 5, "bf16", "f32", 0.1, seed=410)
+    x = make_inputs(w, "cuda", zero_grad_pools=False)
+    want = np.broadcast_to(np.concatenate([np.arange(m), -np.ones(5)]), (Hkv, m + 5))
+    calls = [lambda *a: api.page_score_topk(*a)]
+    if Hq * m * D + Hkv * D <= api.NOALLOC_SCRATCH_BYTES // 4 - 256:
+        calls.append(lambda *a: api.page_score_topk_noalloc(*a, torch.full((Hkv, m + 5), 9, dtype=torch.int32, device="cuda"),
+                                                            torch.full((Hkv,), 9, dtype=torch.int32, device="cuda")))
+    for call in calls:
+        sel, cnt = call(_desc(w, x), x["q"], x["k_pool"], x["page_table"], 5)
+        assert np.array_equal(sel.cpu().numpy(), want) and (cnt.cpu().numpy() == m).all()
+
+
 @pytest.mark.parametrize("with_means", [True, False])
 @pytest.mark.parametrize("dtype,D,P", [("f32", 128, 128), ("f32", 64, 16), ("bf16", 64, 128), ("bf16", 128, 16)])
 def test_append_for_every_tile(dtype, D, P, with_means):

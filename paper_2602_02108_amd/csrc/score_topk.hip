@@ -99,7 +99,7 @@ __device__ __forceinline__ float qpool_final(const Params& p, const float* __res
 }
 // One workgroup per KV head and 16 dims: one compute unit takes about 10 bytes per ns of lines that another one wrote, so few of
 // them are slow (224 rows of 128 floats: 9.1 us with one workgroup per head, 5.7 so; 448 rows: 16.5, 8.6).
-constexpr int FINAL_DIMS = 16, FINAL_THREADS = 256, FINAL_FLOATS = 16384;
+constexpr int FINAL_DIMS = 16, FINAL_THREADS = 256, FINAL_FLOATS = 16384;   // (floats of a pass in LDS)
 __global__ __launch_bounds__(FINAL_THREADS) void qpool_final_kernel(Params p, const float* __restrict__ A, float* __restrict__ qbar, float r) {
   extern __shared__ __align__(16) float rows[];
   const int g = blockIdx.x, d0 = blockIdx.y * FINAL_DIMS;
@@ -570,6 +570,8 @@ static hipError_t launch_scoring(const Params& p, int32_t top_k, int32_t* sel, i
     return hipGetLastError();
   }
   {
+    static DeviceOnce lds_once;   // (16 dims of 1024 rows and the rows read ahead: 66 KiB)
+    if (hipError_t e = ensure_max_dynamic_lds(lds_once, (const void*)qpool_final_kernel, 4 * (FINAL_FLOATS + 32 * FINAL_DIMS)); e != hipSuccess) return e;
     ProfScope prof_("qpool_final", st);
     qpool_final_kernel<<<dim3(p.Hkv, D / FINAL_DIMS), dim3(FINAL_THREADS), final_lds_bytes(p, FINAL_DIMS, FINAL_FLOATS), st>>>(p, A, qbar, r);
   }

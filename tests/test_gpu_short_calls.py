@@ -46,8 +46,8 @@ def test_selection_among_close_scores(n_past):
         assert np.array_equal(sel.cpu().numpy(), osel) and np.array_equal(cnt.cpu().numpy(), ocnt)
 
 
-def test_selection_with_more_pooled_rows_than_one_pass():
-    # m * G = 256 rows of 128 floats against 224 in LDS at a time
+def test_selection_of_a_short_history_with_many_pooled_rows():
+    # m * G = 256: the past fits the kernel of one workgroup per KV head, the rows to pool do not
     w = Workload("rows", 32, 1, 128, 16, 16 * 8, 16 * 48, 7, "bf16", "f32", 0.1, seed=420)
     x = make_inputs(w, "cuda")
     sel, cnt, scores = pu.gpu_select(w, x)
@@ -70,6 +70,18 @@ def test_selection_without_a_history(Hq, Hkv, D, P, m):
     for call in calls:
         sel, cnt = call(_desc(w, x), x["q"], x["k_pool"], x["page_table"], 5)
         assert np.array_equal(sel.cpu().numpy(), want) and (cnt.cpu().numpy() == m).all()
+
+
+# Rows to pool around what the kernel that pools them holds at once (1024 rows of 16 dims), and past it
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("m", [62, 63, 64, 65, 100, 129])
+def test_selection_pools_more_rows_than_fit_at_once(m, dtype):
+    w = Workload("rows", 16, 1, 64, 16, 16 * m, 16 * (m + 30), 7, dtype, "f32", 0.1, seed=421)
+    x = make_inputs(w, "cuda")
+    sel, cnt, scores = pu.gpu_select(w, x)
+    osel, ocnt, oscores = pu.oracle_select(w, pu.host_inputs(x))
+    assert np.array_equal(scores.cpu().numpy().view(np.uint32), oscores.view(np.uint32))
+    assert np.array_equal(sel.cpu().numpy(), osel)
 
 
 @pytest.mark.parametrize("with_means", [True, False])

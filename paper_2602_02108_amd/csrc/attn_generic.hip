@@ -428,33 +428,49 @@ __global__ __launch_bounds__(256 * KH, 2) void fwd_generic_kernel(Params p, int3
         for (int x = 0; x < 16; ++x)
           if (32 * u + 8 * (x >> 2) + (x & 3) >= rel) s[u][x] = -INFINITY;
     }
-    float mx = s[0][0];
+    // Probabilities are relative to a running maximum: of the tile, or (one bf16 term) of each block of 32 keys, as in the kernel
+    // that this one stands in for.  The key that sets a maximum has a probability of 1, which bf16 holds exactly.  Error
+    // against 64 bits, 28 / 4 heads, chunk 1536, 16 pages: one maximum per 64 keys O 2.191e-3, LSE 1.046e-5, one per 32 (and the
+    // other kernel) 2.182e-3, 1.035e-5; it costs 1 to 2 us of the 54 of a chunk of one page against 65 pages.
+    constexpr int REFS = NT == 1 ? Y::U : 1;
+    float alpha[REFS], mc[REFS];
 #pragma unroll
-    for (int u = 0; u < Y::U; ++u)
+    for (int k = 0; k < REFS; ++k) {
+      float mx = s[k][0];
 #pragma unroll
-      for (int x = u == 0; x < 16; ++x) mx = fmaxf(mx, s[u][x]);
-    const float m_new = fmaxf(m_run, half_max(mx));
-    const float alpha = __builtin_amdgcn_exp2f((m_run - m_new) * c), mc = m_new * c;
-    m_run = m_new;
-    if (__any(alpha != 1.f)) {
-      l_run *= alpha;
+      for (int u = k; u < (REFS == 1 ? Y::U : k + 1); ++u)
 #pragma unroll
-      for (int db = 0; db < X::DB; ++db)
-#pragma unroll
-        for (int x = 0; x < 16; ++x) of[db][x] *= alpha;
+        for (int x = u == k; x < 16; ++x) mx = fmaxf(mx, s[u][x]);
+      const float m_new = fmaxf(m_run, half_max(mx));
+      alpha[k] = __builtin_amdgcn_exp2f((m_run - m_new) * c);
+      mc[k] = m_new * c;
+      m_run = m_new;
     }
+    auto rescale = [&](const int k) __attribute__((always_inline)) {
+      if (__any(alpha[k] != 1.f)) {
+#pragma unroll
+        for (int db = 0; db < X::DB; ++db)
+#pragma unroll
+          for (int x = 0; x < 16; ++x) of[db][x] *= alpha[k];
+      }
+    };
+    rescale(0);
+    l_run *= alpha[0];
     GnP<T, NT> pr[Y::U];
     auto exps = [&](const int u, const int x) __attribute__((always_inline)) {   // registers x, x + 1
-      const float a = __builtin_amdgcn_exp2f(__builtin_fmaf(s[u][x], c, -mc)), b2 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[u][x + 1], c, -mc));
+      const float ref = mc[REFS == 1 ? 0 : u];
+      const float a = __builtin_amdgcn_exp2f(__builtin_fmaf(s[u][x], c, -ref)), b2 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[u][x + 1], c, -ref));
       pr[u].set2(x, a, b2);
       if constexpr (X::BF && NT == 1) l_run = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, pr[u].w[0][x >> 1]), ones, l_run, false);
       else l_run += a + b2;
     };
 #pragma unroll
     for (int x = 0; x < 16; x += 2) exps(0, x);
+    if constexpr (REFS == 2) l_run *= alpha[1];
     gn_pipeline<Y::U * NP>(
         [&](const int i) __attribute__((always_inline)) { return ad.tr_frag(i % NP, at + Y::TILE + 32 * (i / NP) * X::RB); },
         [&](const int i, const u32x4_t& f) __attribute__((always_inline)) {
+          if (REFS == 2 && i == NP) rescale(REFS - 1);
           gn_tr_mma<T, D, NT>(i % NP, f, pr[i / NP], of);
           if (i < NP && Y::U == 2) {   // 16 exponentials over NP instructions (4, 8 or 16)
             if (NP == 4) exps(Y::U - 1, 4 * i);

@@ -147,11 +147,12 @@ template <typename T, int D> struct GnAddr {
 
 // A block of probabilities (or dS) as the B operand of the second product.  fp32 tensors: the values themselves.  bf16 tensors: NT
 // bf16 terms whose sum stands for the value, each the rounding of what the ones before it left, NT matrix
-// instructions in the place of one (the fp32 instruction would take sixteen times as long).  One is the precision of the
-// kernels for pages of 128 at head dim 128, and of the short calls that those hand over.  The other shapes keep
-// fp32 precision: three terms are all 24 bits, two 17, which is used where the result is stored in bf16.
-// Error against 64 bits, 2-norm, 13 calls of 64 to 2176 keys, fp32 values -> terms: O 1.66e-3 -> 1.66e-3, dV in bf16 the same,
-// dV in fp32 0.6 to 1.5e-6 -> 0.3 to 0.7e-6 (one term: O 2.1e-3, dV 1.7e-3).
+// instructions in the place of one (the fp32 instruction would take sixteen times as long).  Three are all 24 bits: shapes
+// without kernels of their own hold probabilities and dS in fp32.  One is the precision of the kernels for pages of 128
+// at head dim 128, and of the short calls that those hand over.  Two terms are 17 bits: enough for results in bf16
+// unless their sums cancel, in which case O, dQ and bf16 gradients came out up to 30 % off.  Error against 64 bits, 2-norm, 13
+// calls of 64 to 2176 keys: O and gradients in bf16 1.66e-3 (the rounding of bf16 itself), dV in fp32 0.3 to 0.7e-6 (fp32
+// values on the vector unit 0.6 to 1.5e-6; one term: O 2.1e-3, dV 1.7e-3).
 template <typename T, int NT> struct GnP;
 template <int NT> struct GnP<bf16_t, NT> {
   uint32_t w[NT][8];
@@ -971,13 +972,13 @@ __global__ __launch_bounds__(256, (D == 128 || sizeof(T) == 4 ? 1 : 2)) void dkv
 // dQ and dK / dV of a short call in one launch: the first kv_blocks workgroups take the keys, the others the rows; neither
 // waits for the other (each computes Delta itself, so dQ must not be written over O).  8 us of launch and start-up less than one after the other, where
 // neither fills the chip.
-template <typename T, typename TG, int D, int NT_ROW, int NT_KEY>
+template <typename T, typename TG, int D, int NT>
 __global__ __launch_bounds__(256, (D == 128 || sizeof(T) == 4 ? 1 : 2)) void bwd_pair_kernel(Params p, int32_t kv_blocks, int32_t kv_split, float* __restrict__ kv_part,
                                                                                             int32_t tiles, int32_t n_split, int lp, int32_t max_len,
                                                                                             float* __restrict__ part) {
   extern __shared__ __align__(16) unsigned char smem[];
-  if ((int32_t)blockIdx.x < kv_blocks) dkv_body<T, TG, D, true, NT_KEY>(p, smem, blockIdx.x, kv_split, lp, kv_part);
-  else dq_body<T, D, 1, NT_ROW>(p, smem, (int32_t)blockIdx.x - kv_blocks, tiles, n_split, lp, max_len, part, nullptr, 0);
+  if ((int32_t)blockIdx.x < kv_blocks) dkv_body<T, TG, D, true, NT>(p, smem, blockIdx.x, kv_split, lp, kv_part);
+  else dq_body<T, D, 1, NT>(p, smem, (int32_t)blockIdx.x - kv_blocks, tiles, n_split, lp, max_len, part, nullptr, 0);
 }
 
 // What is left of a backward with splits, in one launch: workgroups below dq_blocks add the dQ partials, the others
@@ -1148,8 +1149,8 @@ size_t bwd_generic_workspace_bytes(const Params& p, bool bf, int32_t max_len) {
   return pair > two ? pair : two;
 }
 
-// terms of a probability (GnP) where a shape has no kernels of its own, for results of type TO
-template <typename T, typename TO> constexpr int GN_TERMS = sizeof(T) == 4 ? 1 : sizeof(TO) == 4 ? 3 : 2;
+// terms of a probability (GnP) where a shape has no kernels of its own
+template <typename T> constexpr int GN_TERMS = sizeof(T) == 4 ? 1 : 3;
 
 template <typename T, int D, int KH, int NT>
 static hipError_t fwd_launch(const Params& p, int32_t tiles, int32_t ns, int32_t len, float* part, float2* ml, hipStream_t st) {
@@ -1159,7 +1160,7 @@ static hipError_t fwd_launch(const Params& p, int32_t tiles, int32_t ns, int32_t
   fwd_generic_kernel<T, D, KH, NT><<<dim3((unsigned)tiles * p.Hkv * ns), dim3(R::THREADS), R::LDS, st>>>(p, tiles, ns, __builtin_ctz(p.P), len, part, ml);
   return hipGetLastError();
 }
-template <typename T, int D, int NT = GN_TERMS<T, T>>
+template <typename T, int D, int NT = GN_TERMS<T>>
 static hipError_t fwd_generic(const Params& p, int32_t max_len, void* ws, size_t ws_bytes, const char* name, hipStream_t st) {
   // (the forward also runs without a workspace)
   const GnPlan sp = gn_plan(p, Gn<T, D>::BF, max_len, false, ws ? gn_fit(ws_bytes, gn_row_blocks(p) * 32 * (p.D * 4 + 8)) : 1);
@@ -1193,7 +1194,7 @@ static hipError_t dq_launch(const Params& p, int32_t tiles, int32_t ns, int32_t 
                                                                                                    bias, n_stages);
   return hipGetLastError();
 }
-template <typename T, int D, int NT = GN_TERMS<T, T>>
+template <typename T, int D, int NT = GN_TERMS<T>>
 static hipError_t dq_generic(const Params& p, int32_t max_len, float* part, size_t part_bytes, float* bias, int32_t n_stages, int32_t* splits,
                              hipStream_t st) {
   const GnPlan sp = gn_plan(p, Gn<T, D>::BF, max_len, true, gn_fit(part_bytes, gn_row_blocks(p) * 32 * p.D * 4));
@@ -1229,7 +1230,7 @@ hipError_t launch_bwd_finish(const Params& p, bool bf, int32_t dq_split, const f
 }
 
 // The one-launch backward, if the shape takes it and the workspace has room (else *done stays false)
-template <typename T, typename TG, int D, int NT_ROW = GN_TERMS<T, T>, int NT_KEY = GN_TERMS<T, TG>>
+template <typename T, typename TG, int D, int NT = GN_TERMS<T>>
 static hipError_t bwd_pair(Params p, int32_t max_len, void* ws, size_t ws_bytes, hipStream_t st, bool* done) {
   if (p.d_q == p.o) return hipSuccess;   // (dQ over O: the keys' workgroups would read rows of O that the others have overwritten)
   const GnPair t = gn_pair(p, Gn<T, D>::BF, max_len);
@@ -1237,18 +1238,18 @@ static hipError_t bwd_pair(Params p, int32_t max_len, void* ws, size_t ws_bytes,
   *done = true;
   constexpr int LDS = GnKey<T, D>::LDS > GnRow<T, D, 1>::LDS ? GnKey<T, D>::LDS : GnRow<T, D, 1>::LDS;
   static DeviceOnce once;
-  if (hipError_t e = ensure_max_dynamic_lds(once, (const void*)bwd_pair_kernel<T, TG, D, NT_ROW, NT_KEY>, LDS); e != hipSuccess) return e;
+  if (hipError_t e = ensure_max_dynamic_lds(once, (const void*)bwd_pair_kernel<T, TG, D, NT>, LDS); e != hipSuccess) return e;
   p.delta = nullptr;
   float* kv_part = (float*)ws;
   float* dq_part = (float*)((unsigned char*)ws + gn_key_part_bytes(p, max_len, t.kv_split));
   const int32_t tiles = gn_tiles(p.C, p.G, p.P, p.m, p.qp), units = gn_key_units(p, max_len), kv_blocks = units * p.Hkv * t.kv_split;
-  bwd_pair_kernel<T, TG, D, NT_ROW, NT_KEY><<<dim3((unsigned)(kv_blocks + tiles * p.Hkv * t.row_split)), dim3(256), LDS, st>>>(
+  bwd_pair_kernel<T, TG, D, NT><<<dim3((unsigned)(kv_blocks + tiles * p.Hkv * t.row_split)), dim3(256), LDS, st>>>(
       p, kv_blocks, t.kv_split, kv_part, tiles, t.row_split, __builtin_ctz(p.P), gn_list_len(p, max_len), dq_part);
   if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
   return bwd_finish<T, TG, D>(p, t.row_split, dq_part, t.kv_split > 1 ? units : 0, t.kv_split, kv_part, st);
 }
 hipError_t launch_bwd_pair_bf16_128(const Params& p, int32_t max_len, void* ws, size_t ws_bytes, hipStream_t st, bool* done) {
-  return p.grad_is_bf16 ? bwd_pair<bf16_t, bf16_t, 128, 1, 1>(p, max_len, ws, ws_bytes, st, done) : bwd_pair<bf16_t, float, 128, 1, 1>(p, max_len, ws, ws_bytes, st, done);
+  return p.grad_is_bf16 ? bwd_pair<bf16_t, bf16_t, 128, 1>(p, max_len, ws, ws_bytes, st, done) : bwd_pair<bf16_t, float, 128, 1>(p, max_len, ws, ws_bytes, st, done);
 }
 
 template <typename T, typename TG, int D>
@@ -1257,7 +1258,7 @@ static hipError_t bwd_generic(Params p, int32_t max_len, void* ws, size_t ws_byt
   bool done = false;
   if (hipError_t e = bwd_pair<T, TG, D>(p, max_len, ws, ws_bytes, st, &done); done || e != hipSuccess) return e;
   static DeviceOnce once_kv;
-  if (hipError_t e = ensure_max_dynamic_lds(once_kv, (const void*)dkv_generic_kernel<T, TG, D, GN_TERMS<T, TG>>, GnKey<T, D>::LDS); e != hipSuccess) return e;
+  if (hipError_t e = ensure_max_dynamic_lds(once_kv, (const void*)dkv_generic_kernel<T, TG, D, GN_TERMS<T>>, GnKey<T, D>::LDS); e != hipSuccess) return e;
   // [Delta][dK / dV slices][dQ partials]; a workspace without room for the slices of this call takes fewer
   unsigned char* w = (unsigned char*)ws;
   p.delta = (float*)w;
@@ -1272,7 +1273,7 @@ static hipError_t bwd_generic(Params p, int32_t max_len, void* ws, size_t ws_byt
   int32_t ns = 1;
   hipError_t e = dq_generic<T, D>(p, max_len, dq_part, left, nullptr, 0, &ns, st);
   if (e != hipSuccess) return e;
-  dkv_generic_kernel<T, TG, D, GN_TERMS<T, TG>><<<dim3((unsigned)units * p.Hkv * nk), dim3(256), GnKey<T, D>::LDS, st>>>(p, nk, __builtin_ctz(p.P), kv_part);
+  dkv_generic_kernel<T, TG, D, GN_TERMS<T>><<<dim3((unsigned)units * p.Hkv * nk), dim3(256), GnKey<T, D>::LDS, st>>>(p, nk, __builtin_ctz(p.P), kv_part);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
   return bwd_finish<T, TG, D>(p, ns, dq_part, p.qp ? p.max_multi : nk > 1 ? units : 0, nk, kv_part, st);

@@ -1,13 +1,112 @@
-"""Values that show how probabilities are held."""
+"""Values at the ends of what the kernels of fp32 tensors, head dim 64 and pages of 16 to 64 tokens take: sums that
+cancel (every bit of a probability counts)."""
 import math
 
 import pytest
 import torch
 
 from paper_2602_02108_amd import api
-from paper_2602_02108_amd.workloads import Workload, make_inputs
+from paper_2602_02108_amd.workloads import Workload, make_inputs, torch_dtype
 
 pytestmark = pytest.mark.gpu
+
+
+def _bf(x):
+    return x.to(torch.bfloat16).double()
+
+
+def _cancelling(weight, count, seed):
+    """bf16 values [len(weight)][count] whose sums with `weight` are about 2^-14 of their terms: all random but two, of which the
+    first cancels the sum of the others to its own rounding and the second cancels 15/16 of what that leaves.  Weights off
+    by 2^-17 of themselves change such a sum by more than a tenth, by 2^-24 by about a thousandth."""
+    g = torch.Generator().manual_seed(seed)
+    v = _bf(torch.randn((len(weight), count), generator=g))
+    a, b = torch.topk(weight.abs(), 2).indices.tolist()
+    v[a] = v[b] = 0
+    v[a] = _bf(-(weight @ v) / weight[a])
+    v[b] = _bf(-(weight @ v) / weight[b] * (1 - 1 / 16))
+    return v
+
+
+def _rel(got, want):
+    return float((got.double().cpu() - want).norm() / want.norm())
+
+
+# Probabilities and dS of bf16 tensors are held in 32 bits where a shape has no kernels of its own, also where the result is
+# stored in bf16.  Bound: 2^-9 of its own storage, about 0.7 % from 24-bit weights (and the rounding of the exponent), 12 % and more
+# from 17-bit ones: 3 % lies between.
+@pytest.mark.parametrize("D,P", [(64, 16), (128, 32), (64, 128)])
+def test_cancelling_sums_over_keys(D, P):
+    # all rows alike, local keys out of reach: O over dims where dO is 0, dQ over dims where Q is 0
+    A, m, n_past = D // 2, 2, 256 // P
+    w = Workload("cancel", 4, 2, D, P, m * P, (n_past + m) * P, None, "bf16", "bf16", D ** -0.5, seed=90)
+    x = {k: v.cpu() if isinstance(v, torch.Tensor) else v for k, v in make_inputs(w, "cpu").items()}
+    x["q"][:] = x["q"][0, 0]
+    x["d_o"][:] = x["d_o"][0, 0]
+    x["q"][..., A:] = 0
+    x["d_o"][..., A:] = 0
+    pt = x["page_table"].long()
+    past, local = pt[:n_past], pt[n_past:w.n]
+    x["k_pool"][..., A:] = 0
+    x["k_pool"][local] = -30 * x["q"][0, 0]
+    x["v_pool"][local] = 0
+    q, do = x["q"][0, 0].double(), x["d_o"][0, 0].double()
+    want_o, weights = [], []
+    for g in range(w.Hkv):
+        k = x["k_pool"][past, g].reshape(-1, D).double()
+        s = k @ q * w.sm_scale
+        x["v_pool"][past, g, :, A:] = _cancelling(torch.exp(s - s.max()), D - A, 91 + g).reshape(n_past, P, D - A).bfloat16()
+        want_o.append(torch.softmax(s, 0) @ x["v_pool"][past, g, :, A:].reshape(-1, D - A).double())
+        weights.append(s)
+    dev = {k: v.cuda() if isinstance(v, torch.Tensor) else v for k, v in x.items()}
+    desc = api.make_desc(dev["q"], dev["k_pool"], w.N, w.sm_scale, torch.bfloat16)
+    o, lse = api.paged_attn_fwd(desc, dev["q"], dev["k_pool"], dev["v_pool"], dev["page_table"])
+    for g in range(w.Hkv):
+        assert _rel(o[:, 2 * g:2 * g + 2, A:], want_o[g].expand(w.C, 2, D - A)) <= 0.03, g
+    # the backward on the O and LSE that the forward gave; K may hold anything where Q is 0
+    want_dq = []
+    for g in range(w.Hkv):
+        p = torch.exp(weights[g] - lse[2 * g, 0].double().cpu())
+        ds = p * (x["v_pool"][past, g].reshape(-1, D).double() @ do - do @ o[0, 2 * g].double().cpu())
+        dev["k_pool"][past.cuda(), g, :, A:] = _cancelling(ds, D - A, 95 + g).reshape(n_past, P, D - A).bfloat16().cuda()
+        want_dq.append(ds @ dev["k_pool"][past.cuda(), g, :, A:].reshape(-1, D - A).double().cpu() * w.sm_scale)
+    dq = api.paged_attn_bwd(desc, dev["q"], dev["k_pool"], dev["v_pool"], dev["page_table"], o, lse, dev["d_o"], dev["dk_pool"], dev["dv_pool"])
+    for g in range(w.Hkv):
+        assert _rel(dq[:, 2 * g:2 * g + 2, A:], want_dq[g].expand(w.C, 2, D - A)) <= 0.03, g
+
+
+@pytest.mark.parametrize("grad_dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("D,P", [(64, 16), (128, 32), (64, 128)])
+def test_cancelling_sums_over_rows(D, P, grad_dtype):
+    # all past keys alike: dV over dims where V is 0, dK over dims where K is 0 (Q and dO may hold anything there)
+    A, m, n_past = D // 2, 2, 3
+    w = Workload("cancel", 4, 2, D, P, m * P, (n_past + m) * P, None, "bf16", grad_dtype, D ** -0.5, seed=100)
+    x = make_inputs(w, "cpu")
+    pt = x["page_table"].long()
+    past = pt[:n_past]
+    for name in ("k_pool", "v_pool"):
+        x[name][past] = x[name][past[0], 0, 0].clone()
+        x[name][..., A:] = 0
+    x["q"][..., A:] = 0
+    x["d_o"][..., A:] = 0
+    dev = {k: v.cuda() if isinstance(v, torch.Tensor) else v for k, v in x.items()}
+    desc = api.make_desc(dev["q"], dev["k_pool"], w.N, w.sm_scale, torch_dtype(grad_dtype))
+    o, lse = api.paged_attn_fwd(desc, dev["q"], dev["k_pool"], dev["v_pool"], dev["page_table"])
+    k, v = (x[name][past[0], 0, 0].double() for name in ("k_pool", "v_pool"))
+    want = []
+    for g in range(w.Hkv):
+        hs = slice(2 * g, 2 * g + 2)
+        p = torch.exp(x["q"][:, hs].double() @ k * w.sm_scale - lse[hs].T.double().cpu())
+        ds = p * (x["d_o"][:, hs].double() @ v - (x["d_o"][:, hs].double() * o[:, hs].double().cpu()).sum(-1))
+        for name, wt in (("d_o", p), ("q", ds)):
+            free = _cancelling(wt.reshape(-1), D - A, 101 + g).reshape(w.C, 2, D - A)
+            dev[name][:, hs, A:] = free.bfloat16().cuda()
+            want.append((wt.reshape(-1) @ free.reshape(-1, D - A)) * (w.sm_scale if name == "q" else 1.0))
+    api.paged_attn_bwd(desc, dev["q"], dev["k_pool"], dev["v_pool"], dev["page_table"], o, lse, dev["d_o"], dev["dk_pool"], dev["dv_pool"])
+    for g in range(w.Hkv):
+        for pool, ref in (("dv_pool", want[2 * g]), ("dk_pool", want[2 * g + 1])):
+            got = dev[pool][past.cuda(), g, :, A:]
+            assert _rel(got, ref.expand(n_past, P, D - A)) <= 0.03, (pool, g)
 
 
 # Probabilities of bf16 pages of 128 are bf16 relative to a running maximum per 32 keys, so the largest key of every 32 up to there

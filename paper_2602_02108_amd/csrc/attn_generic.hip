@@ -150,7 +150,7 @@ template <typename T, int D> struct GnAddr {
 // instructions in the place of one (the fp32 instruction would take sixteen times as long).  Three are all 24 bits: shapes
 // without kernels of their own hold probabilities and dS in fp32.  One is the precision of the kernels for pages of 128
 // at head dim 128, and of the short calls that those hand over.  Two terms are 17 bits: enough for results in bf16
-// unless their sums cancel, in which case O, dQ and bf16 gradients came out up to 30 % off.  Error against 64 bits, 2-norm, 13
+// unless their sums cancel (to 2^-14 of their terms: O, dQ and bf16 gradients 3 to 6 % off).  Error against 64 bits, 2-norm, 13
 // calls of 64 to 2176 keys: O and gradients in bf16 1.66e-3 (the rounding of bf16 itself), dV in fp32 0.3 to 0.7e-6 (fp32
 // values on the vector unit 0.6 to 1.5e-6; one term: O 2.1e-3, dV 1.7e-3).
 template <typename T, int NT> struct GnP;

@@ -376,6 +376,9 @@ __device__ __forceinline__ void gn_key_loop(const Params& p, const GnTile& t, Gn
 }
 
 // ---- forward ----------------------------------------------------------------------------------
+// Where a running maximum starts: finite, also as a logit, because a row that has seen nothing yet forms (-inf - m) c; below
+// every product that a float holds as a logit of this scale.
+__device__ __forceinline__ float gn_lowest(const Params& p) { return -1e38f / fmaxf(1.f, p.sm_scale); }
 // log-sum-exp of a row: m the largest product, l the sum of exponentials relative to it
 __device__ __forceinline__ float gn_lse(const Params& p, float m, float l) {
   return __builtin_fmaf(m, p.sm_scale, __builtin_amdgcn_logf(l) * 0.6931471805599453f);
@@ -404,7 +407,7 @@ __global__ __launch_bounds__(256 * KH, 2) void fwd_generic_kernel(Params p, int3
 
   f32x16 of[X::DB];
   gn_zero(of);
-  float m_run = -1e30f, l_run = 0.f;
+  float m_run = gn_lowest(p), l_run = 0.f;
   [[maybe_unused]] const bf16x2 ones = {(__bf16)1.0f, (__bf16)1.0f};   // (NT = 1: the row sum is that of the rounded probabilities)
   const float c = p.sm_scale * 1.4426950408889634f;
   GnAddr<T, D> ad;
@@ -593,7 +596,7 @@ __global__ __launch_bounds__(256) void fwd_combine_kernel(Params p, int32_t tile
   const int64_t block = blockIdx.x, blocks = (int64_t)p.Hkv * tiles * 4;
   const int64_t at = (block * (D / 8) + wave) * 64 + lane;
   const float c = p.sm_scale * 1.4426950408889634f;
-  float M = -1e30f, L = 0.f;   // (a split that saw nothing of the row holds -inf and 0)
+  float M = gn_lowest(p), L = 0.f;   // (a split that saw nothing of the row holds -inf and 0)
   float4 acc[GW];
 #pragma unroll
   for (int j = 0; j < GW; ++j) acc[j] = make_float4(0.f, 0.f, 0.f, 0.f);

@@ -1,12 +1,16 @@
 """Values at the ends of what the kernels of fp32 tensors, head dim 64 and pages of 16 to 64 tokens take: sums that
-cancel (every bit of a probability counts)."""
+cancel (every bit of a probability counts), scores far below zero."""
 import math
 
+import numpy as np
 import pytest
 import torch
 
+import oracle as orc
 from paper_2602_02108_amd import api
 from paper_2602_02108_amd.workloads import Workload, make_inputs, torch_dtype
+
+import parity_util as pu
 
 pytestmark = pytest.mark.gpu
 
@@ -128,3 +132,18 @@ def test_the_largest_of_32_keys_is_not_rounded(n_past, at):
     v = x["v_pool"][first].double()
     want = (v[:, at[0]] + math.e * v[:, at[1]]) / (1 + math.e)
     assert float((o.double() - want.repeat_interleave(2, 0)).abs().max()) <= 2.0**-8 * float(want.abs().max())
+
+
+@pytest.mark.parametrize("n_past", [1, 40])
+def test_rows_whose_scores_are_all_far_below_zero(n_past):
+    # products of about -1e33, logits of about -150: a running maximum must not start above them
+    w = Workload("low", 4, 2, 64, 16, 32, (n_past + 2) * 16, None, "f32", "f32", 1e-31, seed=120)
+    x = make_inputs(w, "cuda")
+    x["q"].copy_((1 + x["q"].abs()) * 1e16)
+    x["k_pool"].copy_(-(1 + x["k_pool"].abs()) * 1e15)
+    hx = pu.host_inputs(x)
+    desc = api.make_desc(x["q"], x["k_pool"], w.N, w.sm_scale)
+    o, lse = api.paged_attn_fwd(desc, x["q"], x["k_pool"], x["v_pool"], x["page_table"])
+    ro, rlse = orc.attn_fwd(pu.shape_of(w), hx["q"], hx["k_pool"], hx["v_pool"], hx["page_table"])
+    pu.check("O", pu.f32(o), ro, "f32")
+    pu.check("LSE", pu.f32(lse), rlse, "f32")

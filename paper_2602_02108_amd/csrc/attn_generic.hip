@@ -375,6 +375,115 @@ __device__ __forceinline__ void gn_key_loop(const Params& p, const GnTile& t, Gn
   }
 }
 
+// ---- values that are not finite -----------------------------------------------------------------
+// The products multiply a token that a row does not see by a probability of 0, which makes a NaN where the token holds an
+// infinity or a NaN.  So sums that are not finite are formed once more, by one wave over exactly what the row (or key) sees, in plain
+// fp32.  Finite values pay one look at the sums: 32 or 64 instructions per wave.
+template <int N> __device__ __forceinline__ bool gn_not_finite(const f32x16 (&v)[N]) {
+  float z = 0.f;   // (0 times an infinity or a NaN is a NaN)
+#pragma unroll
+  for (int k = 0; k < N; ++k)
+#pragma unroll
+    for (int x = 0; x < 16; ++x) z = __builtin_fmaf(v[k][x], 0.f, z);
+  return z != 0.f;
+}
+// lanes l and l + 32 hold one row or key: bit l of the result
+__device__ __forceinline__ uint32_t gn_either_half(bool v) {
+  const uint64_t b = __ballot(v);
+  return (uint32_t)b | (uint32_t)(b >> 32);
+}
+__device__ __forceinline__ float gn_lane(float v, int lane) { return __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(v), lane)); }
+__device__ __forceinline__ int64_t gn_lane64(int64_t v, int lane) {
+  return ((int64_t)__builtin_amdgcn_readlane((int32_t)(v >> 32), lane) << 32) | (uint32_t)__builtin_amdgcn_readlane((int32_t)v, lane);
+}
+// <a, b> of two rows of D elements
+template <typename T, int D> __device__ __forceinline__ float gn_row_dot(const T* a, const T* b) {
+  float c = 0.f;
+#pragma unroll 2
+  for (int j = 0; j < Gn<T, D>::NG; ++j) c = gn_dot<T>(reinterpret_cast<const u32x4_t*>(a)[j], reinterpret_cast<const u32x4_t*>(b)[j], c);
+  return c;
+}
+// acc += sum over the lanes x < cnt of w_x times row off_x of `rows` (elements), the lane's dims lane, lane + 64
+template <typename T, int D> __device__ __forceinline__ void gn_add_rows(float (&acc)[D / 64], const T* rows, float w, int64_t off, int cnt, int lane) {
+  for (int x = 0; x < cnt; ++x) {
+    const float wx = gn_lane(w, x);
+    const T* row = rows + gn_lane64(off, x);
+#pragma unroll
+    for (int k = 0; k < D / 64; ++k) acc[k] += wx * Elem<T>::load(row + 64 * k + lane);
+  }
+}
+// O of one row (ref: its largest logit, times log2 e; scale: 1 / the sum of its probabilities), or dQ (ref and scale unused)
+template <typename T, int D, bool DQ> __device__ __forceinline__ void gn_redo_row(const Params& p, int g, int i, int h, int lp, int lane, float ref, float scale) {
+  const int lid = list_id(p, g, i);
+  const int64_t roff = (int64_t)i * p.q_tok_stride + (int64_t)h * p.q_head_stride, a = p.N - p.C + i;
+  const T *q = (const T*)p.q + roff, *d_o = (const T*)p.d_o + roff;
+  float delta = 0.f;
+  if (DQ) {
+    ref = p.lse[(int64_t)h * p.C + i] * 1.4426950408889634f;
+    delta = gn_row_dot<T, D>(d_o, (const T*)p.o + roff);
+    scale = p.sm_scale;
+  }
+  const int32_t n_ent = visible_len(p, lid, a >> lp, lane);
+  int32_t V = n_ent << lp;   // list tokens that the row sees
+  if (n_ent > 0 && list_at(p, lid, n_ent - 1) == (int32_t)(a >> lp)) V -= p.P - 1 - (int32_t)(a & (p.P - 1));
+  if (ref != ref || delta != delta || scale != scale) {   // (all of the row is NaN)
+    V = 0;
+    scale = NAN;
+  }
+  const float c = p.sm_scale * 1.4426950408889634f;
+  float acc[D / 64] = {};
+  for (int32_t t0 = 0; t0 < V; t0 += 64) {
+    float w = 0.f;
+    int64_t off = 0;
+    if (t0 + lane < V) {
+      const int32_t t = t0 + lane;
+      off = (int64_t)p.page_table[list_at(p, lid, t >> lp)] * p.pool_page_stride + (int64_t)g * p.pool_head_stride + (int64_t)(t & (p.P - 1)) * p.pool_tok_stride;
+      w = __builtin_amdgcn_exp2f(__builtin_fmaf(gn_row_dot<T, D>(q, (const T*)p.k_pool + off), c, -ref));
+      if (DQ) w *= gn_row_dot<T, D>(d_o, (const T*)p.v_pool + off) - delta;
+    }
+    gn_add_rows<T, D>(acc, (const T*)(DQ ? p.k_pool : p.v_pool), w, off, V - t0 < 64 ? V - t0 : 64, lane);
+  }
+  T* dst = (T*)(DQ ? p.d_q : p.o) + roff;
+#pragma unroll
+  for (int k = 0; k < D / 64; ++k) Elem<T>::store(dst + 64 * k + lane, acc[k] * scale);
+}
+// dK (or dV) of token t of owned page e into the pool
+template <typename T, typename TG, int D> __device__ __forceinline__ void gn_redo_key(const Params& p, int g, int32_t e, int32_t t, bool is_dk, int lp, int lane) {
+  const int64_t l = owned_at(p, g, e), pos = (l << lp) + t, first_q = p.N - p.C;
+  const int64_t koff = (int64_t)p.page_table[l] * p.pool_page_stride + (int64_t)g * p.pool_head_stride + (int64_t)t * p.pool_tok_stride;
+  const int32_t r_key = pos > first_q ? (int32_t)(pos - first_q) * p.G : 0, rpq = p.P * p.G;   // rows before r_key do not see it
+  const int32_t* inv = p.qp ? p.inv_off + (int64_t)g * (p.un_stride + 1) + e : nullptr;
+  const int32_t n_seg = p.qp ? inv[1] - inv[0] : 1;
+  const float c = p.sm_scale * 1.4426950408889634f;
+  float acc[D / 64] = {};
+  for (int32_t seg = 0; seg < n_seg; ++seg) {   // the chunk's rows, or those of every query page that lists the page
+    int32_t r0 = 0, end = p.C * p.G;
+    if (p.qp) {
+      r0 = p.inv_qp[(int64_t)g * p.m * p.sel_stride + inv[0] + seg] * rpq;
+      end = r0 + rpq;
+    }
+    for (r0 = r0 < r_key ? r_key : r0; r0 < end; r0 += 64) {
+      float w = 0.f;
+      int64_t off = 0;
+      if (r0 + lane < end) {
+        const int32_t i = (int32_t)div_g(p, (uint32_t)(r0 + lane)), h = g * p.G + (r0 + lane - i * p.G);
+        const int64_t at = (int64_t)h * p.C + i;
+        off = (int64_t)i * p.q_tok_stride + (int64_t)h * p.q_head_stride;
+        w = __builtin_amdgcn_exp2f(__builtin_fmaf(gn_row_dot<T, D>((const T*)p.q + off, (const T*)p.k_pool + koff), c, -(p.lse[at] * 1.4426950408889634f)));
+        if (is_dk) {
+          const float delta = p.delta ? p.delta[at] : gn_row_dot<T, D>((const T*)p.d_o + off, (const T*)p.o + off);
+          w *= gn_row_dot<T, D>((const T*)p.d_o + off, (const T*)p.v_pool + koff) - delta;
+        }
+      }
+      gn_add_rows<T, D>(acc, (const T*)(is_dk ? p.q : p.d_o), w, off, end - r0 < 64 ? end - r0 : 64, lane);
+    }
+  }
+  TG* dst = (TG*)(is_dk ? p.dk_pool : p.dv_pool) + koff;
+#pragma unroll
+  for (int k = 0; k < D / 64; ++k)
+    Elem<TG>::store(dst + 64 * k + lane, Elem<TG>::load(dst + 64 * k + lane) + acc[k] * (is_dk ? p.sm_scale : 1.f));
+}
+
 // ---- forward ----------------------------------------------------------------------------------
 // Where a running maximum starts: finite, also as a logit, because a row that has seen nothing yet forms (-inf - m) c; below
 // every product that a float holds as a logit of this scale.
@@ -508,11 +617,18 @@ __global__ __launch_bounds__(256 * KH, 2) void fwd_generic_kernel(Params p, int3
     if (!t.active) return;
     part_store<T, D>(part, at, lane, of, 1.f);
     if (hh == 0) part_ml[at * 32 + lane] = make_float2(l_tot > 0.f ? m_run : -INFINITY, l_tot);
-  } else if (t.valid) {
+  } else {
     const float inv = 1.f / l_tot;
-    T* dst = (T*)p.o + roff;
-    part_emit<T, D>(of, hh, [&](int d, float v0, float v1, float v2, float v3) { part_store4<T>(dst + d, v0 * inv, v1 * inv, v2 * inv, v3 * inv); });
-    if (hh == 0) p.lse[(int64_t)t.h * p.C + t.i] = gn_lse(p, m_run, l_tot);
+    uint32_t bad = gn_either_half(t.valid && gn_not_finite(of));
+    if (t.valid && !((bad >> (lane & 31)) & 1)) {
+      T* dst = (T*)p.o + roff;
+      part_emit<T, D>(of, hh, [&](int d, float v0, float v1, float v2, float v3) { part_store4<T>(dst + d, v0 * inv, v1 * inv, v2 * inv, v3 * inv); });
+    }
+    if (t.valid && hh == 0) p.lse[(int64_t)t.h * p.C + t.i] = gn_lse(p, m_run, l_tot);
+    for (; bad; bad &= bad - 1) {
+      const int x = __builtin_ctz(bad);
+      gn_redo_row<T, D, false>(p, b.g, __builtin_amdgcn_readlane(t.i, x), __builtin_amdgcn_readlane(t.h, x), lp, lane, gn_lane(m_run * c, x), gn_lane(inv, x));
+    }
   }
 }
 
@@ -520,18 +636,27 @@ __global__ __launch_bounds__(256 * KH, 2) void fwd_generic_kernel(Params p, int3
 // results leave in whole rows instead of the register order of the partials.
 template <int D> constexpr int GN_GW = D / 32;   // groups per wave
 // in: the sums of this thread's groups; then f(k, row, dim, value) for the row pieces this thread writes, piece k = float4
-// k * 256 + thread of the block
-template <typename T, int D, typename F> __device__ __forceinline__ void gn_rows_out(float4 (&sh)[8 * D], const float4 (&v)[GN_GW<D>], F&& f) {
+// k * 256 + thread of the block.  redo: rows whose sums are not finite are left out; returns them, a bit each.
+template <int D> struct GnRowsLds { float4 v[8 * D]; uint32_t bad[4]; };
+template <typename T, int D, typename F> __device__ __forceinline__ uint32_t gn_rows_out(GnRowsLds<D>& lds, const float4 (&v)[GN_GW<D>], bool redo, F&& f) {
+  auto& sh = lds.v;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, r = lane & 31;
   constexpr int GPR = D / 4;   // float4s per row
 #pragma unroll
   for (int j = 0; j < GN_GW<D>; ++j) sh[r * GPR + ((part_group_dim<T, D>(wave + 4 * j, lane >> 5) >> 2) ^ (r & 15))] = v[j];
+  float z = 0.f;
+#pragma unroll
+  for (int j = 0; j < GN_GW<D>; ++j) z = __builtin_fmaf(v[j].x, 0.f, __builtin_fmaf(v[j].y, 0.f, __builtin_fmaf(v[j].z, 0.f, __builtin_fmaf(v[j].w, 0.f, z))));
+  const uint32_t mine = gn_either_half(redo && z != 0.f);
+  if (lane == 0) lds.bad[wave] = mine;
   __syncthreads();
+  const uint32_t bad = lds.bad[0] | lds.bad[1] | lds.bad[2] | lds.bad[3];
 #pragma unroll
   for (int k = 0; k < GN_GW<D>; ++k) {
     const int e = k * 256 + threadIdx.x, row = e / GPR, c = e % GPR;
-    f(k, row, 4 * c, sh[row * GPR + (c ^ (row & 15))]);
+    if (!((bad >> row) & 1)) f(k, row, 4 * c, sh[row * GPR + (c ^ (row & 15))]);
   }
+  return __builtin_amdgcn_readfirstlane(bad);
 }
 // row `row` of a block -> chunk token and query head; false past the last row
 __device__ __forceinline__ bool gn_out_row(const Params& p, int32_t tiles, int64_t block, int row, int& i, int& h) {
@@ -589,8 +714,8 @@ __device__ __forceinline__ void gn_sum_parts(const float* part, int64_t block, i
 // O = sum of the splits' O rescaled to the common maximum / sum of their l
 template <typename T, int D>
 __global__ __launch_bounds__(256) void fwd_combine_kernel(Params p, int32_t tiles, int32_t n_split, const float* __restrict__ part,
-                                                          const float2* __restrict__ part_ml) {
-  __shared__ float4 sh[8 * D];
+                                                          const float2* __restrict__ part_ml, int lp) {
+  __shared__ GnRowsLds<D> sh;
   constexpr int GW = GN_GW<D>;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int64_t block = blockIdx.x, blocks = (int64_t)p.Hkv * tiles * 4;
@@ -631,12 +756,17 @@ __global__ __launch_bounds__(256) void fwd_combine_kernel(Params p, int32_t tile
 #pragma unroll
   for (int j = 0; j < GW; ++j) { acc[j].x *= inv; acc[j].y *= inv; acc[j].z *= inv; acc[j].w *= inv; }
   int i, h;
-  gn_rows_out<T, D>(sh, acc, [&](int, int row, int d, const float4& r) __attribute__((always_inline)) {
+  uint32_t bad = gn_rows_out<T, D>(sh, acc, true, [&](int, int row, int d, const float4& r) __attribute__((always_inline)) {
     if (gn_out_row(p, tiles, block, row, i, h))
       part_store4<T>((T*)p.o + (int64_t)i * p.q_tok_stride + (int64_t)h * p.q_head_stride + d, r.x, r.y, r.z, r.w);
   });
   if (threadIdx.x < 32 && gn_out_row(p, tiles, block, threadIdx.x, i, h))
     p.lse[(int64_t)h * p.C + i] = gn_lse(p, M, L);
+  for (bad &= 0xffu << (8 * wave); bad; bad &= bad - 1) {   // (eight rows per wave)
+    const int x = __builtin_ctz(bad);
+    if (gn_out_row(p, tiles, block, x, i, h))
+      gn_redo_row<T, D, false>(p, h / p.G, i, h, lp, lane, gn_lane(M * c, x), gn_lane(inv, x));
+  }
 }
 
 // ---- dQ -----------------------------------------------------------------------------------------
@@ -736,10 +866,17 @@ __device__ __forceinline__ void dq_body(const Params& p, unsigned char* smem, in
   }
   if (n_split > 1) {
     if (t.active) part_store<T, D>(part, (int64_t)b.split * p.Hkv * tiles * 4 + t.block, lane, dq, 1.f);
-  } else if (t.valid) {
-    T* dst = (T*)p.d_q + roff;
-    const float sc = p.sm_scale;
-    part_emit<T, D>(dq, hh, [&](int d, float v0, float v1, float v2, float v3) { part_store4<T>(dst + d, v0 * sc, v1 * sc, v2 * sc, v3 * sc); });
+  } else {
+    uint32_t bad = gn_either_half(t.valid && gn_not_finite(dq));
+    if (t.valid && !((bad >> (lane & 31)) & 1)) {
+      T* dst = (T*)p.d_q + roff;
+      const float sc = p.sm_scale;
+      part_emit<T, D>(dq, hh, [&](int d, float v0, float v1, float v2, float v3) { part_store4<T>(dst + d, v0 * sc, v1 * sc, v2 * sc, v3 * sc); });
+    }
+    for (; bad; bad &= bad - 1) {
+      const int x = __builtin_ctz(bad);
+      gn_redo_row<T, D, true>(p, b.g, __builtin_amdgcn_readlane(t.i, x), __builtin_amdgcn_readlane(t.h, x), lp, lane, 0.f, 0.f);
+    }
   }
 }
 template <typename T, int D, int KH, int NT>
@@ -959,11 +1096,19 @@ __device__ __forceinline__ void dkv_body(const Params& p, unsigned char* smem, i
       part_store<T, D>(part, (int64_t)slot * 8 + wave, lane, dk, sc);
       part_store<T, D>(part, (int64_t)slot * 8 + 4 + wave, lane, dv, 1.f);
     }
-  } else if (kvalid) {
+  } else {
+    uint32_t bad[2] = {gn_either_half(kvalid && gn_not_finite(dv)), gn_either_half(kvalid && gn_not_finite(dk))};
     TG* pk = (TG*)p.dk_pool + koff;
     TG* pv = (TG*)p.dv_pool + koff;
-    part_emit<T, D>(dk, hh, [&](int d, float v0, float v1, float v2, float v3) { part_add4<TG>(pk + d, v0 * sc, v1 * sc, v2 * sc, v3 * sc); });
-    part_emit<T, D>(dv, hh, [&](int d, float v0, float v1, float v2, float v3) { part_add4<TG>(pv + d, v0, v1, v2, v3); });
+    if (kvalid && !((bad[1] >> lq) & 1))
+      part_emit<T, D>(dk, hh, [&](int d, float v0, float v1, float v2, float v3) { part_add4<TG>(pk + d, v0 * sc, v1 * sc, v2 * sc, v3 * sc); });
+    if (kvalid && !((bad[0] >> lq) & 1))
+      part_emit<T, D>(dv, hh, [&](int d, float v0, float v1, float v2, float v3) { part_add4<TG>(pv + d, v0, v1, v2, v3); });
+    for (int is_dk = 0; is_dk < 2; ++is_dk)
+      for (uint32_t left = bad[is_dk]; left; left &= left - 1) {
+        const int32_t k = 32 * wave + __builtin_ctz(left);
+        gn_redo_key<T, TG, D>(p, g, e0 + (p.qp ? 0 : k >> lp), k & (p.P - 1), is_dk, lp, lane);
+      }
   }
 }
 template <typename T, typename TG, int D, int NT>
@@ -988,18 +1133,22 @@ __global__ __launch_bounds__(256, (D == 128 || sizeof(T) == 4 ? 1 : 2)) void bwd
 // add the slices of a dK / dV unit to the pool.
 template <typename T, typename TG, int D>
 __global__ __launch_bounds__(256) void bwd_finish_kernel(Params p, int32_t tiles, int32_t dq_split, const float* __restrict__ dq_part,
-                                                         int32_t dq_blocks, int32_t kv_split, const float* __restrict__ kv_part, int lp) {
-  __shared__ float4 sh[8 * D];
+                                                         int32_t dq_blocks, int32_t kv_split, const float* __restrict__ kv_part, int lp,
+                                                         int redo_keys) {
+  __shared__ GnRowsLds<D> sh;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   float4 a[GN_GW<D>];
   if ((int32_t)blockIdx.x < dq_blocks) {
     const int64_t blocks = (int64_t)p.Hkv * tiles * 4;
     gn_sum_parts<D>(dq_part, blockIdx.x, blocks * (D / 8) * 64, dq_split, a, [] {});
     const float sc = p.sm_scale;
-    gn_rows_out<T, D>(sh, a, [&](int, int row, int d, const float4& r) __attribute__((always_inline)) {
-      int i, h;
+    int i, h;
+    uint32_t bad = gn_rows_out<T, D>(sh, a, true, [&](int, int row, int d, const float4& r) __attribute__((always_inline)) {
       if (gn_out_row(p, tiles, blockIdx.x, row, i, h))
         part_store4<T>((T*)p.d_q + (int64_t)i * p.q_tok_stride + (int64_t)h * p.q_head_stride + d, r.x * sc, r.y * sc, r.z * sc, r.w * sc);
     });
+    for (bad &= 0xffu << (8 * wave); bad; bad &= bad - 1)
+      if (gn_out_row(p, tiles, blockIdx.x, __builtin_ctz(bad), i, h)) gn_redo_row<T, D, true>(p, h / p.G, i, h, lp, lane, 0.f, 0.f);
     return;
   }
   // (last units first: their slices were written last and are still in the memory-side cache)
@@ -1036,9 +1185,13 @@ __global__ __launch_bounds__(256) void bwd_finish_kernel(Params p, int32_t tiles
       if (page) old[k] = part_load4<TG>(dst[k]);
     }
   });
-  gn_rows_out<T, D>(sh, a, [&](int k, int, int, const float4& r) __attribute__((always_inline)) {
+  uint32_t bad = gn_rows_out<T, D>(sh, a, redo_keys, [&](int k, int, int, const float4& r) __attribute__((always_inline)) {
     if (dst[k]) part_store4<TG>(dst[k], old[k].x + r.x, old[k].y + r.y, old[k].z + r.z, old[k].w + r.w);
   });
+  for (bad &= 0xffu << (8 * wave); bad; bad &= bad - 1) {
+    const int32_t x = __builtin_ctz(bad), k = 32 * (wb & 3) + x, e = e0 + (p.qp ? 0 : x >> lp);
+    if (p.qp ? k < p.P : e < list_len(p, g)) gn_redo_key<T, TG, D>(p, g, e, k & (p.P - 1), which == 0, lp, lane);
+  }
 }
 
 // ---- host side ----------------------------------------------------------------------------------
@@ -1174,7 +1327,7 @@ static hipError_t fwd_generic(const Params& p, int32_t max_len, void* ws, size_t
   ProfScope prof_(name, st);
   hipError_t e = sp.groups == 2 ? fwd_launch<T, D, 2, NT>(p, tiles, ns, len, part, ml, st) : fwd_launch<T, D, 1, NT>(p, tiles, ns, len, part, ml, st);
   if (e == hipSuccess && ns > 1) {
-    fwd_combine_kernel<T, D><<<dim3((unsigned)(gn_row_blocks(p))), dim3(256), 0, st>>>(p, tiles, ns, part, ml);
+    fwd_combine_kernel<T, D><<<dim3((unsigned)(gn_row_blocks(p))), dim3(256), 0, st>>>(p, tiles, ns, part, ml, __builtin_ctz(p.P));
     e = hipGetLastError();
   }
   return e;
@@ -1214,19 +1367,20 @@ hipError_t launch_dq_generic_bf16_128(const Params& p, int32_t max_len, float* p
 
 template <typename T, typename TG, int D>
 static hipError_t bwd_finish(const Params& p, int32_t dq_split, const float* dq_part, int32_t kv_units, int32_t kv_split, const float* kv_part,
-                             hipStream_t st) {
+                             bool redo_keys, hipStream_t st) {
   constexpr int BPU = 8;
   const int32_t dq_blocks = dq_split > 1 ? (int32_t)(gn_row_blocks(p)) : 0;
   const int64_t blocks = dq_blocks + (int64_t)kv_units * p.Hkv * BPU;
   if (blocks <= 0) return hipSuccess;
   bwd_finish_kernel<T, TG, D><<<dim3((unsigned)blocks), dim3(256), 0, st>>>(p, gn_tiles(p.C, p.G, p.P, p.m, p.qp), dq_split, dq_part, dq_blocks, kv_split,
-                                                                            kv_part, __builtin_ctz(p.P));
+                                                                            kv_part, __builtin_ctz(p.P), redo_keys);
   return hipGetLastError();
 }
+// (the dK / dV slices of pages with kernels of their own: keys are left as those give them)
 hipError_t launch_bwd_finish(const Params& p, bool bf, int32_t dq_split, const float* dq_part, int32_t kv_units, int32_t kv_split,
                              const float* kv_part, hipStream_t st) {
-#define OOMB_FINISH(T, TG) (p.D == 128 ? bwd_finish<T, TG, 128>(p, dq_split, dq_part, kv_units, kv_split, kv_part, st) \
-                                       : bwd_finish<T, TG, 64>(p, dq_split, dq_part, kv_units, kv_split, kv_part, st))
+#define OOMB_FINISH(T, TG) (p.D == 128 ? bwd_finish<T, TG, 128>(p, dq_split, dq_part, kv_units, kv_split, kv_part, false, st) \
+                                       : bwd_finish<T, TG, 64>(p, dq_split, dq_part, kv_units, kv_split, kv_part, false, st))
   if (bf) return p.grad_is_bf16 ? OOMB_FINISH(bf16_t, bf16_t) : OOMB_FINISH(bf16_t, float);
   return p.grad_is_bf16 ? OOMB_FINISH(float, bf16_t) : OOMB_FINISH(float, float);
 #undef OOMB_FINISH
@@ -1249,7 +1403,7 @@ static hipError_t bwd_pair(Params p, int32_t max_len, void* ws, size_t ws_bytes,
   bwd_pair_kernel<T, TG, D, NT><<<dim3((unsigned)(kv_blocks + tiles * p.Hkv * t.row_split)), dim3(256), LDS, st>>>(
       p, kv_blocks, t.kv_split, kv_part, tiles, t.row_split, __builtin_ctz(p.P), gn_list_len(p, max_len), dq_part);
   if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
-  return bwd_finish<T, TG, D>(p, t.row_split, dq_part, t.kv_split > 1 ? units : 0, t.kv_split, kv_part, st);
+  return bwd_finish<T, TG, D>(p, t.row_split, dq_part, t.kv_split > 1 ? units : 0, t.kv_split, kv_part, true, st);
 }
 hipError_t launch_bwd_pair_bf16_128(const Params& p, int32_t max_len, void* ws, size_t ws_bytes, hipStream_t st, bool* done) {
   return p.grad_is_bf16 ? bwd_pair<bf16_t, bf16_t, 128, 1>(p, max_len, ws, ws_bytes, st, done) : bwd_pair<bf16_t, float, 128, 1>(p, max_len, ws, ws_bytes, st, done);
@@ -1279,7 +1433,7 @@ static hipError_t bwd_generic(Params p, int32_t max_len, void* ws, size_t ws_byt
   dkv_generic_kernel<T, TG, D, GN_TERMS<T>><<<dim3((unsigned)units * p.Hkv * nk), dim3(256), GnKey<T, D>::LDS, st>>>(p, nk, __builtin_ctz(p.P), kv_part);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
-  return bwd_finish<T, TG, D>(p, ns, dq_part, p.qp ? p.max_multi : nk > 1 ? units : 0, nk, kv_part, st);
+  return bwd_finish<T, TG, D>(p, ns, dq_part, p.qp ? p.max_multi : nk > 1 ? units : 0, nk, kv_part, true, st);
 }
 // max_len: host-side upper bound of the list length (of the union with one list per query page)
 hipError_t launch_bwd_generic(const Params& p, bool bf, int32_t max_len, void* ws, size_t ws_bytes, hipStream_t st) {

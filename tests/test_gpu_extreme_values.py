@@ -1,5 +1,5 @@
 """Values at the ends of what the kernels of fp32 tensors, head dim 64 and pages of 16 to 64 tokens take: sums that
-cancel (every bit of a probability counts), scores far below zero."""
+cancel (every bit of a probability counts), infinities and NaN in tokens that a row does not see, scores far below zero."""
 import math
 
 import numpy as np
@@ -11,6 +11,7 @@ from paper_2602_02108_amd import api
 from paper_2602_02108_amd.workloads import Workload, make_inputs, torch_dtype
 
 import parity_util as pu
+from test_gpu_qp_attention import rand_qp_lists
 
 pytestmark = pytest.mark.gpu
 
@@ -132,6 +133,69 @@ def test_the_largest_of_32_keys_is_not_rounded(n_past, at):
     v = x["v_pool"][first].double()
     want = (v[:, at[0]] + math.e * v[:, at[1]]) / (1 + math.e)
     assert float((o.double() - want.repeat_interleave(2, 0)).abs().max()) <= 2.0**-8 * float(want.abs().max())
+
+
+# Rows and keys split over workgroups or not, several lists, tiles that hold many pages or part of one.
+UNSEEN = [
+    Workload("f32_split", 14, 2, 64, 16, 48, 16 * 37, 5, "f32", "f32", 0.125, seed=110),
+    Workload("bf16_split", 14, 2, 64, 16, 48, 16 * 37, 5, "bf16", "f32", 0.125, seed=111),
+    Workload("f32_d128", 6, 3, 128, 128, 256, 128 * 4, None, "f32", "bf16", 0.088, seed=112),
+    Workload("bf16_p32", 5, 1, 128, 32, 160, 32 * 23, None, "bf16", "bf16", 0.088, seed=113),
+    Workload("f32_rows_unsplit", 32, 32, 64, 64, 1152, 64 * 20, 1, "f32", "f32", 0.125, seed=114),
+    Workload("bf16_rows_unsplit", 32, 32, 64, 32, 1152, 32 * 41, 3, "bf16", "f32", 0.125, seed=115),
+    Workload("f32_keys_unsplit", 8, 4, 128, 16, 32, 16 * 1100, None, "f32", "f32", 0.088, seed=116),
+    # one list per query page, pages held by more lists than a unit of keys takes
+    Workload("qp_f32", 4, 2, 64, 16, 16 * 12, 16 * 30, None, "f32", "f32", 0.125, seed=117),
+    Workload("qp_bf16_p64", 6, 2, 128, 64, 64 * 11, 64 * 20, None, "bf16", "f32", 0.088, seed=118),
+]
+
+
+def _same_where_finite(name, got, want, dtype):
+    """Finite where the oracle is, and within the tolerance there; not finite where the oracle is not."""
+    got, want = np.asarray(got, np.float64), np.asarray(want, np.float64)
+    ok = np.isfinite(want)
+    assert np.array_equal(np.isfinite(got), ok), (name, int((np.isfinite(got) != ok).sum()), got.size)
+    pu.check(name, got[ok], want[ok], dtype)
+
+
+@pytest.mark.parametrize("what", ["v_nan", "v_inf", "k_nan", "do_nan", "q_inf"])
+@pytest.mark.parametrize("w", UNSEEN, ids=lambda w: w.name)
+def test_values_that_are_not_finite_stay_with_those_who_see_them(w, what):
+    x = make_inputs(w, "cuda")
+    sel = cnt = osel = ocnt = None
+    if w.top_k is not None:
+        sel, cnt, _ = pu.gpu_select(w, x, want_scores=False)
+        osel, ocnt = sel.cpu().numpy(), cnt.cpu().numpy()
+    if w.name.startswith("qp_"):
+        osel, ocnt = rand_qp_lists(w, 5, w.seed, popular=3)
+        sel, cnt = torch.as_tensor(osel, device="cuda"), torch.as_tensor(ocnt, device="cuda")
+    attn_fwd, attn_bwd = (api.paged_attn_fwd_qp, api.paged_attn_bwd_qp) if w.name.startswith("qp_") else (api.paged_attn_fwd, api.paged_attn_bwd)
+    desc = api.make_desc(x["q"], x["k_pool"], w.N, w.sm_scale, torch_dtype(w.grad_dtype))
+    fwd = lambda: attn_fwd(desc, x["q"], x["k_pool"], x["v_pool"], x["page_table"], sel, cnt)
+    bad = math.inf if what.endswith("inf") else math.nan
+    sh = pu.shape_of(w)
+    if what[0] in "kv":   # a token in the middle of the chunk's last page: the rows before it do not see it
+        x[what[0] + "_pool"][x["page_table"][w.n - 1].long(), :, w.P // 2 + 3, 3] = bad
+        o, lse = fwd()
+    else:                 # rows of the chunk's first page: keys after them are not seen by them
+        o, lse = fwd()
+        x["q" if what[0] == "q" else "d_o"][w.P // 2, :, 3] = bad
+    hx = pu.host_inputs(x)
+    args = (sh, hx["q"], hx["k_pool"], hx["v_pool"], hx["page_table"])
+    if what[0] in "kv":
+        ro, rlse = orc.attn_fwd(*args, osel, ocnt)
+        _same_where_finite("O", pu.f32(o), ro, w.dtype)
+        _same_where_finite("LSE", pu.f32(lse), rlse, w.dtype)
+    glse = lse.cpu().numpy()
+    delta = orc.delta(sh, hx["d_o"], pu.f32(o))
+    rdq = orc.attn_bwd_dq(*args, glse, delta, hx["d_o"], osel, ocnt)
+    rdk, rdv = np.zeros(x["dk_pool"].shape, np.float32), np.zeros(x["dv_pool"].shape, np.float32)
+    orc.attn_bwd_dkv(*args, glse, delta, hx["d_o"], rdk, rdv, osel, ocnt)
+    dq = attn_bwd(desc, x["q"], x["k_pool"], x["v_pool"], x["page_table"], o, lse, x["d_o"], x["dk_pool"], x["dv_pool"], sel, cnt)
+    _same_where_finite("dQ", pu.f32(dq), rdq, w.dtype)
+    gd = w.dtype if w.grad_dtype == "f32" else "bf16"
+    _same_where_finite("dK", pu.f32(x["dk_pool"]), rdk, gd)
+    _same_where_finite("dV", pu.f32(x["dv_pool"]), rdv, gd)
 
 
 @pytest.mark.parametrize("n_past", [1, 40])

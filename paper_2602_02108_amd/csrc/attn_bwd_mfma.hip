@@ -302,7 +302,8 @@ size_t bwd_mfma_workspace_bytes(const Params& p, int32_t max_list_len) {
 }
 
 hipError_t launch_bwd_mfma(const Params& p, int32_t max_list_len, void* ws, size_t ws_bytes, hipStream_t st) {
-  if (bwd_takes_pair(p, true, max_list_len)) {
+  const bool overlap = dq_overlaps_o(p, true);
+  if (!overlap && bwd_takes_pair(p, true, max_list_len)) {
     ProfScope prof_q("bwd_dq_mfma", st), prof_kv("bwd_dkv_mfma", st);   // (one launch for both)
     bool done = false;
     if (hipError_t e = launch_bwd_pair_bf16_128(p, max_list_len, ws, ws_bytes, st, &done); done || e != hipSuccess) return e;
@@ -311,7 +312,7 @@ hipError_t launch_bwd_mfma(const Params& p, int32_t max_list_len, void* ws, size
   int32_t n_split = dkv_splits(p, max_list_len, true);
   if (stats_bytes(p) + bias_bytes(p) + dkv_partial_bytes(p, max_list_len, n_split) > ws_bytes) n_split = dkv_splits(p, max_list_len, false);
   const size_t first = ws_bytes - bias_bytes(p) - dkv_partial_bytes(p, max_list_len, n_split);   // at least stats_bytes
-  if (rows_take_generic(p, max_list_len, true)) {   // dQ (with the bias words) by the split kernel
+  if ((!overlap || p.d_q == p.o) && rows_take_generic(p, max_list_len, true)) {   // dQ (with the bias words, from O) by the split kernel
     const size_t want = dq_generic_part_bytes(p, true, max_list_len), have = (want < first ? want : first) & ~(size_t)255;
     float* dq_part = (float*)ws;
     float* bias = (float*)((unsigned char*)ws + have);

@@ -403,6 +403,11 @@ template <typename T, int D> __device__ __forceinline__ float gn_row_dot(const T
   for (int j = 0; j < Gn<T, D>::NG; ++j) c = gn_dot<T>(reinterpret_cast<const u32x4_t*>(a)[j], reinterpret_cast<const u32x4_t*>(b)[j], c);
   return c;
 }
+// Delta of a row: as the dQ kernel left it, or (a backward in one launch) from O and dO
+template <typename T, int D> __device__ __forceinline__ float gn_delta(const Params& p, int i, int h) {
+  const int64_t off = (int64_t)i * p.q_tok_stride + (int64_t)h * p.q_head_stride;
+  return p.delta ? p.delta[(int64_t)h * p.C + i] : gn_row_dot<T, D>((const T*)p.d_o + off, (const T*)p.o + off);
+}
 // acc += sum over the lanes x < cnt of w_x times row off_x of `rows` (elements), the lane's dims lane, lane + 64
 template <typename T, int D> __device__ __forceinline__ void gn_add_rows(float (&acc)[D / 64], const T* rows, float w, int64_t off, int cnt, int lane) {
   for (int x = 0; x < cnt; ++x) {
@@ -412,17 +417,12 @@ template <typename T, int D> __device__ __forceinline__ void gn_add_rows(float (
     for (int k = 0; k < D / 64; ++k) acc[k] += wx * Elem<T>::load(row + 64 * k + lane);
   }
 }
-// O of one row (ref: its largest logit, times log2 e; scale: 1 / the sum of its probabilities), or dQ (ref and scale unused)
-template <typename T, int D, bool DQ> __device__ __forceinline__ void gn_redo_row(const Params& p, int g, int i, int h, int lp, int lane, float ref, float scale) {
+// O of one row (ref: its largest logit, times log2 e; scale: 1 / the sum of its probabilities), or dQ (ref: LSE times log2 e)
+template <typename T, int D, bool DQ>
+__device__ __forceinline__ void gn_redo_row(const Params& p, int g, int i, int h, int lp, int lane, float ref, float scale, float delta) {
   const int lid = list_id(p, g, i);
   const int64_t roff = (int64_t)i * p.q_tok_stride + (int64_t)h * p.q_head_stride, a = p.N - p.C + i;
   const T *q = (const T*)p.q + roff, *d_o = (const T*)p.d_o + roff;
-  float delta = 0.f;
-  if (DQ) {
-    ref = p.lse[(int64_t)h * p.C + i] * 1.4426950408889634f;
-    delta = gn_row_dot<T, D>(d_o, (const T*)p.o + roff);
-    scale = p.sm_scale;
-  }
   const int32_t n_ent = visible_len(p, lid, a >> lp, lane);
   int32_t V = n_ent << lp;   // list tokens that the row sees
   if (n_ent > 0 && list_at(p, lid, n_ent - 1) == (int32_t)(a >> lp)) V -= p.P - 1 - (int32_t)(a & (p.P - 1));
@@ -467,12 +467,10 @@ template <typename T, typename TG, int D> __device__ __forceinline__ void gn_red
       int64_t off = 0;
       if (r0 + lane < end) {
         const int32_t i = (int32_t)div_g(p, (uint32_t)(r0 + lane)), h = g * p.G + (r0 + lane - i * p.G);
-        const int64_t at = (int64_t)h * p.C + i;
         off = (int64_t)i * p.q_tok_stride + (int64_t)h * p.q_head_stride;
-        w = __builtin_amdgcn_exp2f(__builtin_fmaf(gn_row_dot<T, D>((const T*)p.q + off, (const T*)p.k_pool + koff), c, -(p.lse[at] * 1.4426950408889634f)));
+        w = __builtin_amdgcn_exp2f(__builtin_fmaf(gn_row_dot<T, D>((const T*)p.q + off, (const T*)p.k_pool + koff), c, -(p.lse[(int64_t)h * p.C + i] * 1.4426950408889634f)));
         if (is_dk) {
-          const float delta = p.delta ? p.delta[at] : gn_row_dot<T, D>((const T*)p.d_o + off, (const T*)p.o + off);
-          w *= gn_row_dot<T, D>((const T*)p.d_o + off, (const T*)p.v_pool + koff) - delta;
+          w *= gn_row_dot<T, D>((const T*)p.d_o + off, (const T*)p.v_pool + koff) - gn_delta<T, D>(p, i, h);
         }
       }
       gn_add_rows<T, D>(acc, (const T*)(is_dk ? p.q : p.d_o), w, off, end - r0 < 64 ? end - r0 : 64, lane);
@@ -627,7 +625,7 @@ __global__ __launch_bounds__(256 * KH, 2) void fwd_generic_kernel(Params p, int3
     if (t.valid && hh == 0) p.lse[(int64_t)t.h * p.C + t.i] = gn_lse(p, m_run, l_tot);
     for (; bad; bad &= bad - 1) {
       const int x = __builtin_ctz(bad);
-      gn_redo_row<T, D, false>(p, b.g, __builtin_amdgcn_readlane(t.i, x), __builtin_amdgcn_readlane(t.h, x), lp, lane, gn_lane(m_run * c, x), gn_lane(inv, x));
+      gn_redo_row<T, D, false>(p, b.g, __builtin_amdgcn_readlane(t.i, x), __builtin_amdgcn_readlane(t.h, x), lp, lane, gn_lane(m_run * c, x), gn_lane(inv, x), 0.f);
     }
   }
 }
@@ -765,13 +763,21 @@ __global__ __launch_bounds__(256) void fwd_combine_kernel(Params p, int32_t tile
   for (bad &= 0xffu << (8 * wave); bad; bad &= bad - 1) {   // (eight rows per wave)
     const int x = __builtin_ctz(bad);
     if (gn_out_row(p, tiles, block, x, i, h))
-      gn_redo_row<T, D, false>(p, h / p.G, i, h, lp, lane, gn_lane(M * c, x), gn_lane(inv, x));
+      gn_redo_row<T, D, false>(p, h / p.G, i, h, lp, lane, gn_lane(M * c, x), gn_lane(inv, x), 0.f);
   }
 }
 
 // ---- dQ -----------------------------------------------------------------------------------------
 // Also computes Delta = <dO, O> of its rows for the dK / dV kernel, which runs afterwards: p.delta, or (bias != nullptr) the
-// bias words from which attn_bwd_dkv_mfma.hip starts its accumulators.
+// bias words from which attn_bwd_dkv_mfma.hip starts its accumulators.  Where dQ overlaps O otherwise than row on row, a row of O may
+// be overwritten before its workgroup reads it: then delta_kernel has filled p.delta beforehand.
+template <typename T, int D> __global__ __launch_bounds__(256) void delta_kernel(Params p) {
+  const int64_t row = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (row >= (int64_t)p.C * p.Hq) return;
+  const int i = (int)(row / p.Hq), h = (int)(row - (int64_t)i * p.Hq);
+  const int64_t off = (int64_t)i * p.q_tok_stride + (int64_t)h * p.q_head_stride;
+  p.delta[(int64_t)h * p.C + i] = gn_row_dot<T, D>((const T*)p.d_o + off, (const T*)p.o + off);
+}
 template <typename T, int D, int KH, int NT>
 __device__ __forceinline__ void dq_body(const Params& p, unsigned char* smem, int32_t block, int32_t tiles, int32_t n_split, int lp, int32_t max_len,
                                         float* __restrict__ part, float* __restrict__ bias, int32_t n_stages) {
@@ -796,6 +802,7 @@ __device__ __forceinline__ void dq_body(const Params& p, unsigned char* smem, in
     delta = gn_dot<T>(dof[j], *reinterpret_cast<const u32x4_t*>((const unsigned char*)p.o + at), delta);
   }
   delta = half_sum(delta);
+  if (p.delta_given) delta = p.delta[(int64_t)t.h * p.C + t.i];
   const float lse2 = p.lse[(int64_t)t.h * p.C + t.i] * 1.4426950408889634f;
 
   f32x16 dq[X::DB];
@@ -807,7 +814,7 @@ __device__ __forceinline__ void dq_body(const Params& p, unsigned char* smem, in
       float* w = bias + (((int64_t)b.g * n_stages + (r >> 6)) * 2) * 64 + (r & 63);
       w[0] = -lse2 / c;
       w[64] = -delta;
-    } else if (p.delta) {
+    } else if (p.delta && !p.delta_given) {
       p.delta[(int64_t)t.h * p.C + t.i] = delta;
     }
   }
@@ -875,7 +882,7 @@ __device__ __forceinline__ void dq_body(const Params& p, unsigned char* smem, in
     }
     for (; bad; bad &= bad - 1) {
       const int x = __builtin_ctz(bad);
-      gn_redo_row<T, D, true>(p, b.g, __builtin_amdgcn_readlane(t.i, x), __builtin_amdgcn_readlane(t.h, x), lp, lane, 0.f, 0.f);
+      gn_redo_row<T, D, true>(p, b.g, __builtin_amdgcn_readlane(t.i, x), __builtin_amdgcn_readlane(t.h, x), lp, lane, gn_lane(lse2, x), p.sm_scale, gn_lane(delta, x));
     }
   }
 }
@@ -1148,7 +1155,8 @@ __global__ __launch_bounds__(256) void bwd_finish_kernel(Params p, int32_t tiles
         part_store4<T>((T*)p.d_q + (int64_t)i * p.q_tok_stride + (int64_t)h * p.q_head_stride + d, r.x * sc, r.y * sc, r.z * sc, r.w * sc);
     });
     for (bad &= 0xffu << (8 * wave); bad; bad &= bad - 1)
-      if (gn_out_row(p, tiles, blockIdx.x, __builtin_ctz(bad), i, h)) gn_redo_row<T, D, true>(p, h / p.G, i, h, lp, lane, 0.f, 0.f);
+      if (gn_out_row(p, tiles, blockIdx.x, __builtin_ctz(bad), i, h))
+        gn_redo_row<T, D, true>(p, h / p.G, i, h, lp, lane, p.lse[(int64_t)h * p.C + i] * 1.4426950408889634f, sc, gn_delta<T, D>(p, i, h));
     return;
   }
   // (last units first: their slices were written last and are still in the memory-side cache)
@@ -1389,7 +1397,7 @@ hipError_t launch_bwd_finish(const Params& p, bool bf, int32_t dq_split, const f
 // The one-launch backward, if the shape takes it and the workspace has room (else *done stays false)
 template <typename T, typename TG, int D, int NT = GN_TERMS<T>>
 static hipError_t bwd_pair(Params p, int32_t max_len, void* ws, size_t ws_bytes, hipStream_t st, bool* done) {
-  if (p.d_q == p.o) return hipSuccess;   // (dQ over O: the keys' workgroups would read rows of O that the others have overwritten)
+  if (dq_overlaps_o(p, Gn<T, D>::BF)) return hipSuccess;   // (the keys' workgroups would read rows of O that the others have overwritten)
   const GnPair t = gn_pair(p, Gn<T, D>::BF, max_len);
   if (!gn_takes_pair(p, Gn<T, D>::BF, max_len, t) || gn_pair_bytes(p, max_len, t) > ws_bytes) return hipSuccess;
   *done = true;
@@ -1427,6 +1435,11 @@ static hipError_t bwd_generic(Params p, int32_t max_len, void* ws, size_t ws_byt
   float* dq_part = (float*)(w + gn_key_part_bytes(p, max_len, nk));
   left -= gn_key_part_bytes(p, max_len, nk);
   const int32_t units = p.qp ? p.max_units : gn_key_units(p, max_len);
+  if (p.d_q != p.o && dq_overlaps_o(p, Gn<T, D>::BF)) {
+    delta_kernel<T, D><<<dim3((unsigned)(((int64_t)p.C * p.Hq + 255) / 256)), dim3(256), 0, st>>>(p);
+    if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
+    p.delta_given = 1;
+  }
   int32_t ns = 1;
   hipError_t e = dq_generic<T, D>(p, max_len, dq_part, left, nullptr, 0, &ns, st);
   if (e != hipSuccess) return e;

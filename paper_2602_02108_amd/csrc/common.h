@@ -29,6 +29,7 @@ struct Params {
   void* dk_pool;
   void* dv_pool;
   float* delta;              // [Hq][C], workspace
+  int32_t delta_given;       // it is filled before the dQ kernel, which otherwise does so
   int32_t grad_is_bf16;
   uint32_t g_magic;          // ceil(2^32 / G): row / G == umulhi(row, g_magic) for row < 2^32 / G, G > 1
   // One page list per (KV head, query page) (Sec. 4.2, retrieval by votes): sel is [Hkv][m][sel_stride],

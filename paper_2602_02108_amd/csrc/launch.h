@@ -54,6 +54,13 @@ size_t dq_generic_part_bytes(const Params& p, bool is_bf16, int32_t max_len);
 hipError_t launch_dq_generic_bf16_128(const Params& p, int32_t max_len, float* part, size_t part_bytes, float* bias, int32_t n_stages,
                                       int32_t* splits, hipStream_t st);
 
+// whether dQ and O share memory (or lie interleaved): the kernels that form dQ while others still read O are not for such a call
+inline bool dq_overlaps_o(const Params& p, bool is_bf16) {
+  const uintptr_t a = (uintptr_t)p.o, b = (uintptr_t)p.d_q;
+  const uintptr_t bytes = (uintptr_t)((p.C - 1) * p.q_tok_stride + (p.Hq - 1) * p.q_head_stride + p.D) * (is_bf16 ? 2 : 4);
+  return a < b + bytes && b < a + bytes;
+}
+
 // kv_layout.hip: LDS-ordered images of the selected pages
 size_t kv_image_bytes(const Params& p, int32_t max_len);
 hipError_t launch_kv_layout(const Params& p, int32_t max_len, void* img, hipStream_t st);

@@ -142,3 +142,28 @@ def test_dq_may_be_written_over_o(dtype, D, P):
     ref = pu.oracle_fwd_bwd(w, pu.host_inputs(x), None, None)
     for name, got, want in (("dQ", dq, ref["dq"]), ("dK", x["dk_pool"], ref["dk_pool"]), ("dV", x["dv_pool"], ref["dv_pool"])):
         pu.check(name, pu.f32(got), want, dtype)
+
+
+# dQ over O one row further on, one head further on, and beside it in the same rows
+@pytest.mark.parametrize("how", ["row", "head", "beside"])
+@pytest.mark.parametrize("dtype,D,P,n,Hq,m", [("bf16", 128, 128, 9, 4, 2), ("bf16", 64, 32, 9, 4, 2), ("f32", 64, 16, 9, 4, 2), ("f32", 128, 16, 40, 32, 24),
+                                              ("bf16", 64, 16, 80, 28, 40)])
+def test_dq_may_overlap_o(dtype, D, P, n, Hq, m, how):
+    w = Workload("overlap", Hq, 2, D, P, m * P, (n + m) * P, None, dtype, "f32", D ** -0.5, seed=460)
+    x = make_inputs(w, "cuda")
+    big = torch.empty((w.C + 1, Hq, 2 * D if how == "beside" else D), dtype=x["q"].dtype, device="cuda")
+    flat, size = big.view(-1), w.C * Hq * D
+    if how == "beside":
+        o, dq = big[:-1, :, :D], big[:-1, :, D:]
+        for k in ("q", "d_o"):
+            x[k] = torch.empty_like(big)[:-1, :, :D].copy_(x[k])
+    else:
+        at = Hq * D if how == "row" else D
+        o, dq = flat[:size].view(x["q"].shape), flat[at:at + size].view(x["q"].shape)
+    desc = _desc(w, x)
+    args = (x["q"], x["k_pool"], x["v_pool"], x["page_table"])
+    o, lse = api.paged_attn_fwd(desc, *args, o=o)
+    api.paged_attn_bwd(desc, *args, o, lse, x["d_o"], x["dk_pool"], x["dv_pool"], d_q=dq)
+    ref = pu.oracle_fwd_bwd(w, pu.host_inputs(x), None, None)
+    for name, got, want in (("dQ", dq, ref["dq"]), ("dK", x["dk_pool"], ref["dk_pool"]), ("dV", x["dv_pool"], ref["dv_pool"])):
+        pu.check(name, pu.f32(got), want, dtype)

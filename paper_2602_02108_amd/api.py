@@ -254,6 +254,14 @@ def _list_k(desc, sel_pages) -> int:
     return -1 if sel_pages is None else int(sel_pages.stride(0)) - desc.chunk_len // desc.page_size
 
 
+_SHORT_ROWS = -2   # of the native module: page lists whose last row ends with the memory before its stride does
+
+
+def _whole_rows(sel_pages):
+    """The same lists in memory of their own: the kernels read whole rows before they know how many entries are valid."""
+    return sel_pages.clone(memory_format=torch.contiguous_format)
+
+
 def paged_attn_fwd(desc: AttnDesc, q, k_pool, v_pool, page_table, sel_pages=None, sel_count=None, o=None,
                    lse=None, workspace=None):
     """oomb_paged_attn_fwd.  Returns (O [C][Hq][D], LSE [Hq][C] float32)."""
@@ -265,6 +273,8 @@ def paged_attn_fwd(desc: AttnDesc, q, k_pool, v_pool, page_table, sel_pages=None
         _check_family("oomb_paged_attn_fwd", desc, q, k_pool, rows=[("o", o)], pools=[("v_pool", v_pool)], lse=lse)
         workspace = _workspace(desc, _list_k(desc, sel_pages), OP_ATTN_FWD, q.device)
     st = (_nb or _native()).attn_fwd(desc, q, k_pool, v_pool, page_table, sel_pages, sel_count, o, lse, workspace)
+    if st == _SHORT_ROWS:
+        st = _native().attn_fwd(desc, q, k_pool, v_pool, page_table, _whole_rows(sel_pages), sel_count, o, lse, workspace)
     if st != OK:
         _check_family("oomb_paged_attn_fwd", desc, q, k_pool, rows=[("o", o)], pools=[("v_pool", v_pool)], lse=lse)
         raise _failed(st, "oomb_paged_attn_fwd", desc, _list_k(desc, sel_pages), OP_ATTN_FWD)
@@ -283,6 +293,8 @@ def paged_attn_bwd(desc: AttnDesc, q, k_pool, v_pool, page_table, o, lse, d_o, d
         check()
         workspace = _workspace(desc, _list_k(desc, sel_pages), OP_ATTN_BWD, q.device)
     st = (_nb or _native()).attn_bwd(desc, q, k_pool, v_pool, page_table, sel_pages, sel_count, o, lse, d_o, d_q, dk_pool, dv_pool, workspace)
+    if st == _SHORT_ROWS:
+        st = _native().attn_bwd(desc, q, k_pool, v_pool, page_table, _whole_rows(sel_pages), sel_count, o, lse, d_o, d_q, dk_pool, dv_pool, workspace)
     if st != OK:
         check()
         raise _failed(st, "oomb_paged_attn_bwd", desc, _list_k(desc, sel_pages), OP_ATTN_BWD)

@@ -2,7 +2,7 @@
 // library costs 10 to 25 us of host time in kernel launches; marshalled through ctypes it took another 6 us and more
 // (every pointer an object, every shape and stride tuple built and compared in Python), which short calls felt.
 // Every function returns the library's status, or -1 if a tensor does not fit the descriptor -- the Python wrapper
-// then says which, or takes the call itself.  So it does where torch throws (strides of a 0-dim or sparse tensor, the
+// then says which, or takes the call itself --, or -2 if the page lists have to be copied first.  So it does where torch throws (strides of a 0-dim or sparse tensor, the
 // address of a tensor without storage): no exception leaves this file.  The interpreter lock is released during the
 // call of the library.
 #include <torch/csrc/autograd/python_variable.h>
@@ -76,17 +76,21 @@ template <PyObject* (*F)(PyObject*, PyObject* const*, Py_ssize_t)> PyObject* gua
   }
 }
 
-bool list_args(const oomb_attn_desc& d, const at::Tensor* sel, const at::Tensor* cnt, bool qp, int32_t* stride) {
+// 0, -1 (does not fit), or -2: lists that are a view whose last row ends with the memory before its stride does.  The kernels
+// read whole rows of min(stride, n) entries before they know how many are valid.
+int list_args(const oomb_attn_desc& d, const at::Tensor* sel, const at::Tensor* cnt, bool qp, int32_t* stride) {
   if (!qp) {
     *stride = sel ? (int32_t)sel->stride(0) : 0;
-    return true;
+    if (!sel || sel->dim() != 2 || sel->size(0) != d.n_kv_heads || sel->size(1) >= sel->stride(0) || d.page_size <= 0) return 0;
+    const int64_t n = d.ctx_len / d.page_size, row = sel->stride(0) < n ? sel->stride(0) : n;
+    return (size_t)(sel->storage_offset() + (d.n_kv_heads - 1) * sel->stride(0) + row) * sel->element_size() > sel->storage().nbytes() ? -2 : 0;
   }
   const int64_t m = d.page_size > 0 ? d.chunk_len / d.page_size : 0;
   if (!sel || !cnt || sel->dim() != 3 || sel->size(0) != d.n_kv_heads || sel->size(1) != m || !sel->is_contiguous() || cnt->dim() != 2 ||
       cnt->size(0) != d.n_kv_heads || cnt->size(1) != m || !cnt->is_contiguous())
-    return false;
+    return -1;
   *stride = (int32_t)sel->size(2);
-  return true;
+  return 0;
 }
 
 #define OOMB_ARGS(n) if (nargs != (n)) { PyErr_SetString(PyExc_TypeError, "wrong number of arguments"); return nullptr; } \
@@ -140,9 +144,9 @@ template <bool QP> PyObject* attn_fwd(PyObject*, PyObject* const* a, Py_ssize_t 
   const at::Tensor *q = tensor(a[1], bad), *k = tensor(a[2], bad), *v = tensor(a[3], bad), *pt = tensor(a[4], bad), *sel = tensor(a[5], bad),
                    *cnt = tensor(a[6], bad), *o = tensor(a[7], bad), *lse = tensor(a[8], bad), *ws = tensor(a[9], bad);
   int32_t stride = 0;
-  if (bad || !family(d, q, k, lse) || !like(o, *q, q->scalar_type()) || !like(v, *k, k->scalar_type()) || !list_args(d, sel, cnt, QP, &stride) ||
-      !stream_of(q, &st))
-    return status(-1);
+  if (bad || !family(d, q, k, lse) || !like(o, *q, q->scalar_type()) || !like(v, *k, k->scalar_type())) return status(-1);
+  if (const int s = list_args(d, sel, cnt, QP, &stride); s != 0) return status(s);
+  if (!stream_of(q, &st)) return status(-1);
   OOMB_CALL((QP ? oomb_paged_attn_fwd_qp : oomb_paged_attn_fwd)(&d, ptr(q), ptr(k), ptr(v), (const int32_t*)ptr(pt), (const int32_t*)ptr(sel),
                                                                 (const int32_t*)ptr(cnt), stride, ptr(o), (float*)ptr(lse), ptr(ws), bytes(ws), st));
 }
@@ -154,10 +158,11 @@ template <bool QP> PyObject* attn_bwd(PyObject*, PyObject* const* a, Py_ssize_t 
                    *cnt = tensor(a[6], bad), *o = tensor(a[7], bad), *lse = tensor(a[8], bad), *d_o = tensor(a[9], bad), *d_q = tensor(a[10], bad),
                    *dk = tensor(a[11], bad), *dv = tensor(a[12], bad), *ws = tensor(a[13], bad);
   int32_t stride = 0;
-  if (bad || !family(d, q, k, lse) || !list_args(d, sel, cnt, QP, &stride)) return status(-1);
+  if (bad || !family(d, q, k, lse)) return status(-1);
   const at::ScalarType t = q->scalar_type(), gt = type_of(d.grad_dtype);
-  if (!like(o, *q, t) || !like(d_o, *q, t) || !like(d_q, *q, t) || !like(v, *k, k->scalar_type()) || !like(dk, *k, gt) || !like(dv, *k, gt) || !stream_of(q, &st))
-    return status(-1);
+  if (!like(o, *q, t) || !like(d_o, *q, t) || !like(d_q, *q, t) || !like(v, *k, k->scalar_type()) || !like(dk, *k, gt) || !like(dv, *k, gt)) return status(-1);
+  if (const int s = list_args(d, sel, cnt, QP, &stride); s != 0) return status(s);
+  if (!stream_of(q, &st)) return status(-1);
   OOMB_CALL((QP ? oomb_paged_attn_bwd_qp : oomb_paged_attn_bwd)(&d, ptr(q), ptr(k), ptr(v), (const int32_t*)ptr(pt), (const int32_t*)ptr(sel),
                                                                 (const int32_t*)ptr(cnt), stride, ptr(o), (const float*)ptr(lse), ptr(d_o), ptr(d_q), ptr(dk),
                                                                 ptr(dv), ptr(ws), bytes(ws), st));

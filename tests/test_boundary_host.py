@@ -267,3 +267,24 @@ def test_native_binding_refuses_tensors_without_storage():
     d = api.make_desc(q, k, 512, 0.1)
     with pytest.raises(Exception):
         api.page_score_topk(d, q, k, ints, 2, ints, ints, None, ws)
+
+
+def test_lists_that_end_before_their_stride_are_copied_first():
+    """The kernels read whole rows of the page lists; a view whose last row ends with the memory is told apart."""
+    import torch
+    C, Hq, Hkv, D, P, n = 32, 4, 2, 64, 16, 8
+    q, k = torch.zeros(C, Hq, D), torch.zeros(n, Hkv, P, D)
+    desc = api.make_desc(q, k, n * P, 0.125)
+    pt, cnt = torch.arange(n, dtype=torch.int32), torch.full((Hkv,), 4, dtype=torch.int32)
+    lse, ws = torch.zeros(Hq, C), torch.zeros(1 << 20, dtype=torch.uint8)
+    native = api._native()
+    wide = torch.zeros(Hkv, 7, dtype=torch.int32)
+    wider = torch.zeros(Hkv, 12, dtype=torch.int32)
+    for sel, short in ((wide, False), (wide[:, :4], False), (wide[:, 3:], True), (wide[:, 1:5], True), (wider[:, 4:], False), (wider[:, 5:9], True),
+                       (wide[:1].expand(Hkv, 7), False)):
+        want = api._SHORT_ROWS if short else -1   # (-1: no device tensors)
+        assert native.attn_fwd(desc, q, k, k, pt, sel, cnt, q, lse, ws) == want, sel.stride()
+        assert native.attn_bwd(desc, q, k, k, pt, sel, cnt, q, lse, q, q, k, k, ws) == want, sel.stride()
+    assert api._whole_rows(wide[:, 3:]).stride() == (4, 1)
+    one = torch.zeros(1, 9, dtype=torch.int32)[:, 2:6]
+    assert api._whole_rows(one).stride() == (4, 1)

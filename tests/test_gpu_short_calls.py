@@ -167,3 +167,18 @@ def test_dq_may_overlap_o(dtype, D, P, n, Hq, m, how):
     ref = pu.oracle_fwd_bwd(w, pu.host_inputs(x), None, None)
     for name, got, want in (("dQ", dq, ref["dq"]), ("dK", x["dk_pool"], ref["dk_pool"]), ("dV", x["dv_pool"], ref["dv_pool"])):
         pu.check(name, pu.f32(got), want, dtype)
+
+
+@pytest.mark.parametrize("dtype,D,P", [("bf16", 128, 128), ("f32", 64, 16)])
+def test_lists_may_be_a_view_that_ends_before_its_stride(dtype, D, P):
+    w = Workload("view", 4, 2, D, P, 2 * P, 9 * P, 3, dtype, "f32", D ** -0.5, seed=470)
+    x = make_inputs(w, "cuda")
+    desc = _desc(w, x)
+    sel, cnt, _ = pu.gpu_select(w, x, want_scores=False)
+    view = torch.full((w.Hkv, 9), -7, dtype=torch.int32, device="cuda")[:, 4:].copy_(sel)
+    args = (x["q"], x["k_pool"], x["v_pool"], x["page_table"])
+    o, lse = api.paged_attn_fwd(desc, *args, view, cnt)
+    dq = api.paged_attn_bwd(desc, *args, o, lse, x["d_o"], x["dk_pool"], x["dv_pool"], view, cnt)
+    ref = pu.oracle_fwd_bwd(w, pu.host_inputs(x), sel.cpu().numpy(), cnt.cpu().numpy())
+    for name, got, want in (("O", o, ref["o"]), ("dQ", dq, ref["dq"]), ("dK", x["dk_pool"], ref["dk_pool"]), ("dV", x["dv_pool"], ref["dv_pool"])):
+        pu.check(name, pu.f32(got), want, dtype)

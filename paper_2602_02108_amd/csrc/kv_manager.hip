@@ -85,8 +85,8 @@ __global__ __launch_bounds__(256) void page_score_cached_kernel(Params p, const 
   const int64_t l = (int64_t)blockIdx.x * PPB + threadIdx.x / LPR;
   const bool active = l < p.n_past;
   const int64_t lc = active ? l : 0;
-  const float4 kb = *reinterpret_cast<const float4*>(cache + ((int64_t)lc * p.Hkv + g) * D + lr * VEC);
-  const float4 qb = *reinterpret_cast<const float4*>(qbar + g * D + lr * VEC);
+  const float4 kb = load_floats(cache + ((int64_t)lc * p.Hkv + g) * D + lr * VEC);
+  const float4 qb = load_floats(qbar + g * D + lr * VEC);
   const float s = score_tree<D>(qb, kb);
   if (active && lr == 0) scores[(int64_t)g * p.n_past + l] = s;
 }

@@ -36,6 +36,13 @@ template <bool STREAM> __device__ __forceinline__ uint4 load16(const void* ptr) 
   return *reinterpret_cast<const uint4*>(ptr);
 }
 
+// four floats of a workspace, which need not be aligned beyond a float (one load all the same)
+__device__ __forceinline__ float4 load_floats(const float* ptr) {
+  typedef float f32x4_t __attribute__((ext_vector_type(4), aligned(4)));
+  const f32x4_t v = *reinterpret_cast<const f32x4_t*>(ptr);
+  return make_float4(v.x, v.y, v.z, v.w);
+}
+
 // Left-to-right sum of `count` rows (row stride `stride` elements) of the VEC
 // elements this lane owns.  Loads are issued U at a time, adds stay in order.
 // STREAM: the rows are read once and not again soon (the whole key history behind the page scorer):

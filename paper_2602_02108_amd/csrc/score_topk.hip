@@ -57,7 +57,7 @@ __device__ __forceinline__ float qpool_final(const Params& p, const float* __res
       for (int u = 0; u < 8; ++u) {
         const int e = e0 + u * NT < total ? e0 + u * NT : e0, k = k0 + e / GPR;
         const int tau = (int)div_g(p, (uint32_t)k), h = g * p.G + (k - tau * p.G);
-        v[u] = *reinterpret_cast<const float4*>(A + ((int64_t)h * p.m + tau) * p.D + d0 + 4 * (e % GPR));
+        v[u] = load_floats(A + ((int64_t)h * p.m + tau) * p.D + d0 + 4 * (e % GPR));
       }
 #pragma unroll
       for (int u = 0; u < 8; ++u)
@@ -432,7 +432,7 @@ __global__ __launch_bounds__(SELECT_THREADS) void select_small_kernel(Params p, 
   float4 kb[PER];
 #pragma unroll
   for (int u = 0; u < PER; ++u)
-    if (grp + u * GROUPS < np) kb[u] = *reinterpret_cast<const float4*>(means + ((int64_t)(grp + u * GROUPS) * p.Hkv + g) * D + lr * VEC);
+    if (grp + u * GROUPS < np) kb[u] = load_floats(means + ((int64_t)(grp + u * GROUPS) * p.Hkv + g) * D + lr * VEC);
   if (tid < SMALL_PAGES) keys[tid] = 0u;
   const float v = qpool_final<D, SELECT_THREADS, SMALL_ROWS * D>(p, A, r, g, 0, rows);
   if (tid < D) qb[tid] = v;

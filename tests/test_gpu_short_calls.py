@@ -84,6 +84,24 @@ def test_selection_pools_more_rows_than_fit_at_once(m, dtype):
     assert np.array_equal(sel.cpu().numpy(), osel)
 
 
+# The scoring workspace needs no alignment beyond that of its floats
+@pytest.mark.parametrize("n_past,P,m", [(20, 64, 2), (300, 64, 2), (300, 16, 40), (700, 16, 2)])
+def test_selection_in_a_workspace_at_any_float(n_past, P, m):
+    w = Workload("offset", 4, 2, 64, P, m * P, (n_past + m) * P, 9, "f32", "f32", 0.1, seed=425)
+    x = make_inputs(w, "cuda", zero_grad_pools=False)
+    desc = _desc(w, x)
+    osel, ocnt, _ = pu.oracle_select(w, pu.host_inputs(x))
+    kbar = torch.zeros((w.n, w.Hkv, w.D), dtype=torch.float32, device="cuda")
+    api.page_means(desc, x["k_pool"], x["page_table"], 0, w.n, kbar)
+    need = api.workspace_bytes(desc, w.top_k, api.OP_SCORE_TOPK)
+    big = torch.empty(need + 16, dtype=torch.uint8, device="cuda")
+    for off in (0, 4, 8, 12):
+        ws = big[off:off + need]
+        for sel, cnt in (api.page_score_topk(desc, x["q"], x["k_pool"], x["page_table"], w.top_k, workspace=ws),
+                         api.page_score_topk_cached(desc, x["q"], kbar, w.top_k, workspace=ws)):
+            assert np.array_equal(sel.cpu().numpy(), osel) and np.array_equal(cnt.cpu().numpy(), ocnt)
+
+
 @pytest.mark.parametrize("with_means", [True, False])
 @pytest.mark.parametrize("dtype,D,P", [("f32", 128, 128), ("f32", 64, 16), ("bf16", 64, 128), ("bf16", 128, 16)])
 def test_append_for_every_tile(dtype, D, P, with_means):

@@ -1459,13 +1459,19 @@ hipError_t launch_bwd_generic(const Params& p, bool bf, int32_t max_len, void* w
 // Whether a shape with kernels of its own (bf16, P = D = 128) is faster here.  Those take 256 rows per workgroup
 // and 2.0 us (dQ: 2.55) per 64 keys, 7 to 13 % less than these with the chip full, but do not split: with
 // workgroups for less than a round, or for little more than one, they leave compute units idle.  They also need the
-// page images (forward) or the row statistics (dQ) of a kernel before them.
+// page images (forward) or the row statistics (dQ) of a kernel before them: 20 ns per page and head.  With one list per query page the
+// images are those of the union of a head's lists, whose length the host does not know: 2.5 lists (32 lists of 160 entries of the 1M
+// votes workload: 400 pages; max_len, the worst case, would be 5120, 410 us for a kernel of 32).  Forward of 28 / 4, 32 / 8 and
+// 14 / 2 heads, 4 to 64 query pages, 8 to 128 past pages each, lists all alike to 1/8 their own: what is chosen is at most
+// 4 % slower than the other, e.g. 32 / 8, 32 query pages, 128 past pages: 1192 to 1263 us (these 1261 to 1268), 16 query
+// pages, 32 past pages: these 223 to 226 (231 to 238).
 bool rows_take_generic(const Params& p, int32_t max_len, bool dq) {
   const float r = row_tiles_per_head(p.C, p.G, p.m, p.qp) * p.Hkv / 256.f;
   const float avg = 2.f * ((float)gn_list_len(p, max_len) - 0.5f * p.m);
-  const float before = dq ? 4.f + (float)p.C * p.Hq * 7e-5f : 5.f + (float)p.Hkv * max_len * 0.02f;
+  const float lists = 2.5f * (float)p.sel_stride, images = p.qp && lists < (float)max_len ? lists : (float)max_len;
+  const float before = dq ? 4.f + (float)p.C * p.Hq * 7e-5f : 5.f + (float)p.Hkv * images * 0.02f;
   const float own = gn_rounds(r, 0.78f, 0.2f, 0.6f, 0.3f) * avg * (dq ? 2.55f : 2.0f) + ceilf(r) * 8.f + before;
-  return gn_plan(p, true, max_len, dq).us < 0.97f * own;
+  return gn_plan(p, true, max_len, dq).us < (p.qp && !dq ? 1.f : 0.97f) * own;
 }
 
 }  // namespace oomb

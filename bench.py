@@ -241,7 +241,7 @@ def quick_measure(api, torch, name, steps, warmup):
     pairs = pairs_of(w, w.N)
     flops = 14.0 * w.D * pairs * w.Hq
     kern = {kn: v[0] / max(v[1], 1) for kn, v in prof.items()}
-    credited = {"attn_fwd_mfma": 4.0, "bwd_dq_mfma": 6.0, "bwd_dkv_mfma": 4.0}
+    credited = {"attn_fwd_mfma": 4.0, "attn_fwd_split": 4.0, "bwd_dq_mfma": 6.0, "bwd_dq_split": 6.0, "bwd_dkv_mfma": 4.0, "bwd_pair": 10.0}
     dom = max(kern, key=kern.get)
     out = {"ms_per_step": dt * 1e3 / steps, "steps": steps, "warmup": warmup, "tflops": flops * steps / dt / 1e12,
            "frac_mfma_peak": flops * steps / dt / 1e12 / MFMA_BF16_PEAK_TFLOPS,
@@ -449,7 +449,7 @@ def main():
         step(s)
     torch.cuda.synchronize()
     api.profile_reset()
-    api.profile_enable(2)   # the timed region brackets only the four large kernels with events
+    api.profile_enable(2)   # the timed region brackets only the large kernels with events
     flops = 0.0
     kv_bytes = 0.0
     pairs_sum = 0
@@ -502,7 +502,7 @@ def main():
     name, (ms_tot, launches) = max(prof.items(), key=lambda kv: kv[1][0])
     avg_ms = ms_tot / max(launches, 1)
     pairs_avg = pairs_sum / args.steps
-    credited = {"attn_fwd_mfma": 4.0, "bwd_dq_mfma": 6.0, "bwd_dkv_mfma": 4.0}  # x D x pairs x Hq, algorithmic
+    credited = {"attn_fwd_mfma": 4.0, "attn_fwd_split": 4.0, "bwd_dq_mfma": 6.0, "bwd_dq_split": 6.0, "bwd_dkv_mfma": 4.0, "bwd_pair": 10.0}  # x D x pairs x Hq, algorithmic
     if name in credited:
         ach = credited[name] * w.D * pairs_avg * w.Hq / (avg_ms * 1e-3) / 1e12
         roof = {"kernel": name, "bound": "mfma", "achieved": ach, "peak": MFMA_BF16_PEAK_TFLOPS, "unit": "TFLOP/s",
@@ -551,9 +551,10 @@ def main():
     # per phase: algorithmic FLOPs over the summed kernel times of the phase
     def phase_ms(names):
         return sum(kernels[k]["avg_ms"] * kernels[k]["launches"] for k in names if k in kernels) / args.steps
-    # (kv_layout belongs to the forward; qp_prepare runs once per phase)
-    fwd_ms = phase_ms(["kv_layout", "qp_prepare", "attn_fwd_mfma"]) - 0.5 * phase_ms(["qp_prepare"])
-    bwd_ms = phase_ms(["bwd_prep", "bwd_dq_mfma", "bwd_dkv_mfma", "bwd_dkv_reduce"]) + 0.5 * phase_ms(["qp_prepare"])
+    # (kv_layout belongs to the forward; qp_prepare runs in the backward, and in the forward unless that is split)
+    qp_fwd_ms = phase_ms(["qp_prepare"]) * (0.5 if "attn_fwd_mfma" in kernels else 0.0)
+    fwd_ms = phase_ms(["kv_layout", "attn_fwd_mfma", "attn_fwd_split"]) + qp_fwd_ms
+    bwd_ms = phase_ms(["bwd_prep", "bwd_dq_mfma", "bwd_dq_split", "bwd_dkv_mfma", "bwd_dkv_reduce", "bwd_pair", "qp_prepare"]) - qp_fwd_ms
     sel_ms = phase_ms(["qpool_partial", "qpool_final", "select_small", "page_score", "page_score_cached", "topk_select", "page_means",
                        "kbar_image", "vote_lse", "vote_sum", "vote_finish"])
     phases = {"select_ms": sel_ms, "fwd_ms": fwd_ms, "bwd_ms": bwd_ms,

@@ -17,7 +17,7 @@ extern "C" {
  * Benchmark aid (not part of the paper's method): per-kernel device time.  While
  * enabled (on = 1), every kernel the library launches is bracketed by two HIP events
  * recorded on the caller's stream (events are host objects created on demand; no
- * device memory is allocated).  on = 2 brackets only the four large kernels (page
+ * device memory is allocated).  on = 2 brackets only the large kernels (page
  * scoring, forward, dQ, dK/dV), which disturbs back-to-back launches less; on = 0
  * switches the timing off.  oomb_profile_read waits for the recorded events of
  * entry idx (0 <= idx < oomb_profile_count()) and returns the kernel's name, its

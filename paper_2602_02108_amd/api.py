@@ -461,7 +461,7 @@ def paged_attn_bwd_qp(desc: AttnDesc, q, k_pool, v_pool, page_table, o, lse, d_o
 
 def profile_enable(on) -> None:
     """oomb_profile_enable: 1 / True brackets every kernel launch with HIP events on the launch stream,
-    2 only the four large kernels, 0 / False none."""
+    2 only the large kernels, 0 / False none."""
     lib().oomb_profile_enable(int(on))
 
 

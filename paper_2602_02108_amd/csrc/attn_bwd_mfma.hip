@@ -304,7 +304,6 @@ size_t bwd_mfma_workspace_bytes(const Params& p, int32_t max_list_len) {
 hipError_t launch_bwd_mfma(const Params& p, int32_t max_list_len, void* ws, size_t ws_bytes, hipStream_t st) {
   const bool overlap = dq_overlaps_o(p, true);
   if (!overlap && bwd_takes_pair(p, true, max_list_len)) {
-    ProfScope prof_q("bwd_dq_mfma", st), prof_kv("bwd_dkv_mfma", st);   // (one launch for both)
     bool done = false;
     if (hipError_t e = launch_bwd_pair_bf16_128(p, max_list_len, ws, ws_bytes, st, &done); done || e != hipSuccess) return e;
   }
@@ -318,7 +317,7 @@ hipError_t launch_bwd_mfma(const Params& p, int32_t max_list_len, void* ws, size
     float* bias = (float*)((unsigned char*)ws + have);
     int32_t splits = 1;
     {
-      ProfScope prof_("bwd_dq_mfma", st);
+      ProfScope prof_("bwd_dq_split", st);
       if (hipError_t e = launch_dq_generic_bf16_128(p, max_list_len, dq_part, have, bias, row_stages(p), &splits, st); e != hipSuccess) return e;
     }
     return launch_bwd_dkv_mfma(p, bias, row_stages(p), max_list_len, n_split, (float*)((unsigned char*)bias + bias_bytes(p)), splits, dq_part, st);

@@ -1346,7 +1346,7 @@ hipError_t launch_fwd_generic(const Params& p, bool bf, int32_t max_len, void* w
   return p.D == 128 ? fwd_generic<float, 128>(p, max_len, ws, ws_bytes, name, st) : fwd_generic<float, 64>(p, max_len, ws, ws_bytes, name, st);
 }
 hipError_t launch_fwd_generic_bf16_128(const Params& p, int32_t max_len, void* ws, size_t ws_bytes, hipStream_t st) {
-  return fwd_generic<bf16_t, 128, 1>(p, max_len, ws, ws_bytes, "attn_fwd_mfma", st);
+  return fwd_generic<bf16_t, 128, 1>(p, max_len, ws, ws_bytes, "attn_fwd_split", st);
 }
 
 template <typename T, int D, int KH, int NT>
@@ -1396,11 +1396,12 @@ hipError_t launch_bwd_finish(const Params& p, bool bf, int32_t dq_split, const f
 
 // The one-launch backward, if the shape takes it and the workspace has room (else *done stays false)
 template <typename T, typename TG, int D, int NT = GN_TERMS<T>>
-static hipError_t bwd_pair(Params p, int32_t max_len, void* ws, size_t ws_bytes, hipStream_t st, bool* done) {
+static hipError_t bwd_pair(Params p, int32_t max_len, void* ws, size_t ws_bytes, const char* name, hipStream_t st, bool* done) {
   if (dq_overlaps_o(p, Gn<T, D>::BF)) return hipSuccess;   // (the keys' workgroups would read rows of O that the others have overwritten)
   const GnPair t = gn_pair(p, Gn<T, D>::BF, max_len);
   if (!gn_takes_pair(p, Gn<T, D>::BF, max_len, t) || gn_pair_bytes(p, max_len, t) > ws_bytes) return hipSuccess;
   *done = true;
+  ProfScope prof_(name, st);
   constexpr int LDS = GnKey<T, D>::LDS > GnRow<T, D, 1>::LDS ? GnKey<T, D>::LDS : GnRow<T, D, 1>::LDS;
   static DeviceOnce once;
   if (hipError_t e = ensure_max_dynamic_lds(once, (const void*)bwd_pair_kernel<T, TG, D, NT>, LDS); e != hipSuccess) return e;
@@ -1414,14 +1415,16 @@ static hipError_t bwd_pair(Params p, int32_t max_len, void* ws, size_t ws_bytes,
   return bwd_finish<T, TG, D>(p, t.row_split, dq_part, t.kv_split > 1 ? units : 0, t.kv_split, kv_part, true, st);
 }
 hipError_t launch_bwd_pair_bf16_128(const Params& p, int32_t max_len, void* ws, size_t ws_bytes, hipStream_t st, bool* done) {
-  return p.grad_is_bf16 ? bwd_pair<bf16_t, bf16_t, 128, 1>(p, max_len, ws, ws_bytes, st, done) : bwd_pair<bf16_t, float, 128, 1>(p, max_len, ws, ws_bytes, st, done);
+  return p.grad_is_bf16 ? bwd_pair<bf16_t, bf16_t, 128, 1>(p, max_len, ws, ws_bytes, "bwd_pair", st, done)
+                        : bwd_pair<bf16_t, float, 128, 1>(p, max_len, ws, ws_bytes, "bwd_pair", st, done);
 }
 
 template <typename T, typename TG, int D>
 static hipError_t bwd_generic(Params p, int32_t max_len, void* ws, size_t ws_bytes, hipStream_t st) {
-  ProfScope prof_("attn_bwd_generic", st);
+  const char* name = "attn_bwd_generic";
   bool done = false;
-  if (hipError_t e = bwd_pair<T, TG, D>(p, max_len, ws, ws_bytes, st, &done); done || e != hipSuccess) return e;
+  if (hipError_t e = bwd_pair<T, TG, D>(p, max_len, ws, ws_bytes, name, st, &done); done || e != hipSuccess) return e;
+  ProfScope prof_(name, st);
   static DeviceOnce once_kv;
   if (hipError_t e = ensure_max_dynamic_lds(once_kv, (const void*)dkv_generic_kernel<T, TG, D, GN_TERMS<T>>, GnKey<T, D>::LDS); e != hipSuccess) return e;
   // [Delta][dK / dV slices][dQ partials]; a workspace without room for the slices of this call takes fewer

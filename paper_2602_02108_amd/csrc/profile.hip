@@ -18,7 +18,7 @@ struct Entry {
   int64_t launches = 0;
 };
 std::mutex g_mu;
-int g_level = 0;  // 0 off, 1 every kernel, 2 only the four large kernels
+int g_level = 0;  // 0 off, 1 every kernel, 2 only the large kernels
 std::vector<Entry> g_entries;
 std::vector<hipEvent_t> g_free;
 
@@ -62,9 +62,12 @@ hipError_t ensure_max_dynamic_lds(DeviceOnce& once, const void* kernel, int byte
 
 ProfScope::ProfScope(const char* name, hipStream_t st) : stream_(st), slot_(-1), start_(nullptr) {
   if (!g_level) return;
-  if (g_level == 2 && std::strcmp(name, "attn_fwd_mfma") && std::strcmp(name, "bwd_dq_mfma") &&
-      std::strcmp(name, "bwd_dkv_mfma") && std::strcmp(name, "page_score"))
-    return;
+  if (g_level == 2) {
+    bool large = false;
+    for (const char* n : {"attn_fwd_mfma", "attn_fwd_split", "bwd_dq_mfma", "bwd_dq_split", "bwd_dkv_mfma", "bwd_pair", "page_score"})
+      large = large || !std::strcmp(name, n);
+    if (!large) return;
+  }
   std::lock_guard<std::mutex> lk(g_mu);
   for (size_t i = 0; i < g_entries.size(); ++i)
     if (g_entries[i].name == name) slot_ = (int)i;

@@ -16,13 +16,15 @@ from paper_2602_02108_amd.workloads import Workload, make_inputs, to_numpy, torc
 TOL = {"bf16": dict(max_abs=2e-2, rel_l2=5e-3), "f32": dict(max_abs=1e-3, rel_l2=1e-4)}
 
 
-MFMA_KERNELS = ("attn_fwd_mfma", "bwd_dq_mfma", "bwd_dkv_mfma")
+MFMA_KERNELS = ("attn_fwd_mfma", "bwd_dq_mfma", "bwd_dkv_mfma")   # bf16 pages of 128, rows enough to fill the chip
+SPLIT_KERNELS = ("attn_fwd_split", "bwd_dq_split", "bwd_pair")      # the same pages in short calls
+GENERIC_KERNELS = ("attn_fwd_generic", "attn_bwd_generic", "delta")
 
 
 @contextlib.contextmanager
-def kernels_ran(names=MFMA_KERNELS, absent=("attn_fwd_generic", "attn_bwd_generic", "delta")):
+def kernels_ran(names=MFMA_KERNELS, absent=GENERIC_KERNELS + SPLIT_KERNELS):
     """Asserts that the library launched every kernel in `names` (and none in `absent`) inside the block:
-    a bf16 test that silently ran the generic fp32 kernels would still pass its tolerances."""
+    a test that silently ran other kernels than those it is about would still pass its tolerances."""
     api.profile_reset()
     api.profile_enable(1)
     try:

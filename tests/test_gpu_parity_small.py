@@ -9,6 +9,8 @@ from paper_2602_02108_amd import api
 from paper_2602_02108_amd.workloads import WORKLOADS, Workload, make_inputs, to_numpy
 
 import parity_util as pu
+from test_gpu_parity_full import _sample_rows as sample_rows
+from test_gpu_qp_attention import rand_qp_lists
 
 pytestmark = pytest.mark.gpu
 
@@ -62,7 +64,7 @@ GENERIC_EDGES = [
 
 @pytest.mark.parametrize("w", GENERIC_EDGES, ids=lambda w: w.name)
 def test_generic_kernel_edges(w):
-    with pu.kernels_ran(("attn_fwd_generic", "attn_bwd_generic"), absent=pu.MFMA_KERNELS):
+    with pu.kernels_ran(("attn_fwd_generic", "attn_bwd_generic"), absent=pu.MFMA_KERNELS + pu.SPLIT_KERNELS):
         rep = pu.full_parity(w, init_grad=0.25)
     _show(w.name, rep)
 
@@ -227,13 +229,105 @@ SPLIT_CASES = [
 
 @pytest.mark.parametrize("w", SPLIT_CASES, ids=lambda w: w.name)
 def test_mfma_bf16_split_rows(w):
-    with pu.kernels_ran(pu.MFMA_KERNELS):
+    with pu.kernels_ran(("attn_fwd_split",), absent=("attn_fwd_mfma", "bwd_dq_mfma") + pu.GENERIC_KERNELS):
         rep = pu.full_parity(w, init_grad=0.25)
     _show(w.name, rep)
+
+
+def _backward_with_dq_over_the_next_row_of_o(w, pad=0):
+    """Short calls of bf16 pages of 128 reach the kernels for many rows where dQ overlaps O: dQ one row further on than O.
+    pad: elements between the rows of Q / O / dO / dQ and of the pools."""
+    x = make_inputs(w, "cuda")
+    hx = pu.host_inputs(x)
+    gen = torch.Generator(device="cuda").manual_seed(w.seed + 77)
+    for k in ("dk_pool", "dv_pool"):
+        x[k].copy_((torch.randn(x[k].shape, generator=gen, device="cuda") * 0.25).to(x[k].dtype))
+    dk0, dv0 = pu.f32(x["dk_pool"]), pu.f32(x["dv_pool"])
+    for k in ("q", "d_o", "k_pool", "v_pool", "dk_pool", "dv_pool"):
+        x[k] = torch.empty(x[k].shape[:-1] + (w.D + pad,), dtype=x[k].dtype, device="cuda")[..., :w.D].copy_(x[k])
+    sel = cnt = osel = ocnt = None
+    if w.top_k is not None:
+        sel, cnt, _ = pu.gpu_select(w, x, want_scores=False)
+        osel, ocnt = sel.cpu().numpy(), cnt.cpu().numpy()
+    both = torch.empty((w.C + 1, w.Hq, w.D + pad), dtype=torch.bfloat16, device="cuda")
+    o, dq = both[:-1, :, :w.D], both[1:, :, :w.D]
+    desc = api.make_desc(x["q"], x["k_pool"], w.N, w.sm_scale, x["dk_pool"].dtype)
+    args = (desc, x["q"], x["k_pool"], x["v_pool"], x["page_table"])
+    _, lse = api.paged_attn_fwd(*args, sel, cnt, o=o)
+    with pu.kernels_ran(("bwd_prep", "bwd_dq_mfma", "bwd_dkv_mfma")):
+        api.paged_attn_bwd(*args, o, lse, x["d_o"], x["dk_pool"], x["dv_pool"], sel, cnt, d_q=dq)
+    ref = pu.oracle_fwd_bwd(w, hx, osel, ocnt, dk0, dv0)
+    pu.check("dQ", pu.f32(dq), ref["dq"], "bf16")
+    pu.check("dK", pu.f32(x["dk_pool"]), ref["dk_pool"], "bf16")
+    pu.check("dV", pu.f32(x["dv_pool"]), ref["dv_pool"], "bf16")
 
 
 @pytest.mark.parametrize("w", RING_CASES, ids=lambda w: w.name)
 def test_mfma_bf16_stage_ring_edges(w):
-    with pu.kernels_ran(pu.MFMA_KERNELS):
-        rep = pu.full_parity(w, init_grad=0.25)
-    _show(w.name, rep)
+    _backward_with_dq_over_the_next_row_of_o(w)
+
+
+@pytest.mark.parametrize("pad", [0, 8])
+@pytest.mark.parametrize("w", [WORKLOADS["mid_sparse_bf16"], WORKLOADS["mid_dense_bf16"],
+                               Workload("bf16_g1_one_page", 2, 2, 128, 128, 128, 512, 2, "bf16", "f32", 0.0884, seed=31),
+                               Workload("bf16_g7", 14, 2, 128, 128, 256, 128 * 11, 3, "bf16", "bf16", 0.0884, extra_phys=2, seed=41)], ids=lambda w: w.name)
+def test_mfma_bf16_backward_kernels_for_many_rows(w, pad):
+    _backward_with_dq_over_the_next_row_of_o(w, pad)
+
+
+# The forward kernel for many rows at its edges: last row tile of half its blocks or whole, two to seven query heads
+# per KV head.  Oracle rows: page and block boundaries and random ones.
+FULL_ROWS = [
+    Workload("bf16_rows_g7", 28, 4, 128, 128, 128 * 17, 128 * 70, None, "bf16", "f32", 0.0884, extra_phys=1, seed=76),
+    Workload("bf16_rows_g3", 48, 16, 128, 128, 128 * 20, 128 * 36, None, "bf16", "f32", 0.0884, seed=77),
+    Workload("bf16_rows_g3_ragged", 24, 8, 128, 128, 128 * 21, 128 * 90, None, "bf16", "f32", 0.0884, seed=78),
+    Workload("bf16_rows_g7_sparse", 14, 2, 128, 128, 128 * 33, 128 * 200, 39, "bf16", "f32", 0.0884, boost_frac=0.05, seed=79),
+]
+
+
+def _check_forward_rows(w, x, o, lse, osel, ocnt):
+    hx, rows = pu.host_inputs(x), sample_rows(w, 300, w.seed)
+    ro, rlse = orc.attn_fwd(pu.shape_of(w), hx["q"], hx["k_pool"], hx["v_pool"], hx["page_table"], osel, ocnt, rows=rows)
+    pu.check("O", pu.f32(o)[rows[:, 1], rows[:, 0]], ro, "bf16")
+    pu.check("LSE", pu.f32(lse)[rows[:, 0], rows[:, 1]], rlse, "bf16")
+
+
+@pytest.mark.parametrize("w", FULL_ROWS, ids=lambda w: w.name)
+def test_mfma_bf16_forward_kernel_for_many_rows(w):
+    x = make_inputs(w, "cuda", zero_grad_pools=False)
+    sel = cnt = osel = ocnt = None
+    if w.top_k is not None:
+        sel, cnt, _ = pu.gpu_select(w, x, want_scores=False)
+        osel, ocnt = sel.cpu().numpy(), cnt.cpu().numpy()
+    desc = api.make_desc(x["q"], x["k_pool"], w.N, w.sm_scale)
+    with pu.kernels_ran(("kv_layout", "attn_fwd_mfma")):
+        o, lse = api.paged_attn_fwd(desc, x["q"], x["k_pool"], x["v_pool"], x["page_table"], sel, cnt)
+    _check_forward_rows(w, x, o, lse, osel, ocnt)
+
+
+# One list per query page: images of two and a half lists are cheap enough for the kernel for many rows, or they are not
+@pytest.mark.parametrize("m,k,ran", [(32, 64, "attn_fwd_mfma"), (16, 32, "attn_fwd_split")])
+def test_forward_with_lists_per_query_page_takes_the_kernel_that_the_rows_ask_for(m, k, ran):
+    w = Workload("bf16_qp_rows", 32, 8, 128, 128, 128 * m, 128 * (m + 100), None, "bf16", "f32", 0.0884, seed=82)
+    x = make_inputs(w, "cuda", zero_grad_pools=False)
+    osel, ocnt = rand_qp_lists(w, k, w.seed, popular=k // 2)
+    desc = api.make_desc(x["q"], x["k_pool"], w.N, w.sm_scale)
+    other = {"attn_fwd_mfma": "attn_fwd_split", "attn_fwd_split": "attn_fwd_mfma"}[ran]
+    with pu.kernels_ran((ran,), absent=(other,) + pu.GENERIC_KERNELS):
+        o, lse = api.paged_attn_fwd_qp(desc, x["q"], x["k_pool"], x["v_pool"], x["page_table"], torch.as_tensor(osel, device="cuda"),
+                                       torch.as_tensor(ocnt, device="cuda"))
+    _check_forward_rows(w, x, o, lse, osel, ocnt)
+
+
+# The one-launch backward has one name and runs once per call; a call that declines it does not carry the name
+def test_the_one_launch_backward_is_timed_once():
+    w = WORKLOADS["smoke_bf16"]
+    x = make_inputs(w, "cuda")
+    desc = api.make_desc(x["q"], x["k_pool"], w.N, w.sm_scale)
+    args = (desc, x["q"], x["k_pool"], x["v_pool"], x["page_table"])
+    o, lse = api.paged_attn_fwd(*args)
+    for d_q, names in ((torch.empty_like(o), ("bwd_pair",)), (o, ("bwd_dq_split", "bwd_dkv_mfma"))):
+        with pu.kernels_ran(names, absent=[n for n in pu.SPLIT_KERNELS + pu.MFMA_KERNELS if n not in names]):
+            api.paged_attn_bwd(*args, o, lse, x["d_o"], x["dk_pool"], x["dv_pool"], d_q=d_q)
+            torch.cuda.synchronize()
+            assert all(api.profile_read()[n][1] == 1 for n in names)

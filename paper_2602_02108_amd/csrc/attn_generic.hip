@@ -1100,8 +1100,9 @@ __device__ __forceinline__ void dkv_body(const Params& p, unsigned char* smem, i
   const float sc = p.sm_scale;
   if (slot >= 0) {
     if (active) {
-      part_store<T, D>(part, (int64_t)slot * 8 + wave, lane, dk, sc);
-      part_store<T, D>(part, (int64_t)slot * 8 + 4 + wave, lane, dv, 1.f);
+      const int nb = part_key_blocks(p);
+      part_store<T, D>(part, ((int64_t)slot * 2) * nb + wave, lane, dk, sc);
+      part_store<T, D>(part, ((int64_t)slot * 2 + 1) * nb + wave, lane, dv, 1.f);
     }
   } else {
     uint32_t bad[2] = {gn_either_half(kvalid && gn_not_finite(dv)), gn_either_half(kvalid && gn_not_finite(dk))};
@@ -1160,18 +1161,18 @@ __global__ __launch_bounds__(256) void bwd_finish_kernel(Params p, int32_t tiles
     return;
   }
   // (last units first: their slices were written last and are still in the memory-side cache)
-  const int32_t b = (int32_t)(gridDim.x - 1 - blockIdx.x), ug = b >> 3, u = ug / p.Hkv, g = ug - u * p.Hkv;
-  const int wb = b & 7, which = wb >> 2;   // {dK, dV}, wave
+  const int32_t nb = part_key_blocks(p), b = (int32_t)(gridDim.x - 1 - blockIdx.x), ug = b / (2 * nb), u = ug / p.Hkv, g = ug - u * p.Hkv;
+  const int wb = b - ug * 2 * nb, which = wb >= nb, kb = which ? wb - nb : wb;   // block of the slot, {dK, dV}, block of keys
   int64_t slot, next;
   int32_t e0;
   if (p.qp) {
-    if (u >= p.multi_count[g] || 32 * (wb & 3) >= p.P) return;
+    if (u >= p.multi_count[g]) return;
     e0 = p.multi_list[(int64_t)g * p.max_multi + u];
     kv_split = p.un_ns[(int64_t)g * p.un_stride + e0];
     slot = p.un_pbase[(int64_t)g * p.un_stride + e0];
     next = 1;
   } else {
-    e0 = (u << (7 - lp)) + (32 * (wb & 3) >> lp);
+    e0 = (u << (7 - lp)) + (32 * kb >> lp);
     if (e0 >= list_len(p, g)) return;
     slot = ((int64_t)u * kv_split) * p.Hkv + g;
     next = p.Hkv;
@@ -1180,14 +1181,14 @@ __global__ __launch_bounds__(256) void bwd_finish_kernel(Params p, int32_t tiles
   // of the slices: in front of them the chain list -> page table -> pool would hold those back.
   TG* dst[GN_GW<D>];
   float4 old[GN_GW<D>];
-  gn_sum_parts<D>(kv_part, slot * 8 + wb, next * 8 * (D / 8) * 64, kv_split, a, [&]() __attribute__((always_inline)) {
+  gn_sum_parts<D>(kv_part, slot * 2 * nb + wb, next * 2 * nb * (D / 8) * 64, kv_split, a, [&]() __attribute__((always_inline)) {
     TG* const pool = (TG*)(which == 0 ? p.dk_pool : p.dv_pool) + (int64_t)g * p.pool_head_stride;
     const bool two = lp == 4 && !p.qp && e0 + 1 < list_len(p, g);
     TG* const page0 = pool + (int64_t)p.page_table[owned_at(p, g, e0)] * p.pool_page_stride;
     TG* const page1 = two ? pool + (int64_t)p.page_table[owned_at(p, g, e0 + 1)] * p.pool_page_stride : nullptr;
 #pragma unroll
     for (int k = 0; k < GN_GW<D>; ++k) {
-      const int x = k * 256 + threadIdx.x, kq = 32 * (wb & 3) + x / (D / 4);
+      const int x = k * 256 + threadIdx.x, kq = 32 * kb + x / (D / 4);
       TG* const page = lp == 4 && (kq & 16) ? page1 : page0;
       dst[k] = page ? page + (int64_t)(kq & (p.P - 1)) * p.pool_tok_stride + 4 * (x % (D / 4)) : nullptr;
       if (page) old[k] = part_load4<TG>(dst[k]);
@@ -1197,7 +1198,7 @@ __global__ __launch_bounds__(256) void bwd_finish_kernel(Params p, int32_t tiles
     if (dst[k]) part_store4<TG>(dst[k], old[k].x + r.x, old[k].y + r.y, old[k].z + r.z, old[k].w + r.w);
   });
   for (bad &= 0xffu << (8 * wave); bad; bad &= bad - 1) {
-    const int32_t x = __builtin_ctz(bad), k = 32 * (wb & 3) + x, e = e0 + (p.qp ? 0 : x >> lp);
+    const int32_t x = __builtin_ctz(bad), k = 32 * kb + x, e = e0 + (p.qp ? 0 : x >> lp);
     if (p.qp ? k < p.P : e < list_len(p, g)) gn_redo_key<T, TG, D>(p, g, e, k & (p.P - 1), which == 0, lp, lane);
   }
 }
@@ -1299,7 +1300,7 @@ size_t fwd_generic_workspace_bytes(const Params& p, bool bf, int32_t max_len) {
 size_t dq_generic_part_bytes(const Params& p, bool bf, int32_t max_len) { return gn_row_part_bytes(p, gn_plan(p, bf, max_len, true).n); }
 static size_t gn_key_part_bytes(const Params& p, int32_t max_len, int32_t split) {
   const size_t slots = p.qp ? (size_t)p.Hkv * qp_max_pslots(p, p.sel_stride) : split > 1 ? (size_t)gn_key_units(p, max_len) * p.Hkv * split : 0;
-  return gn_up(slots * 2 * GN_ROWS * p.D * 4);
+  return gn_up(slots * 2 * part_key_blocks(p) * 32 * p.D * 4);
 }
 static size_t gn_pair_bytes(const Params& p, int32_t max_len, const GnPair& t) {
   return gn_key_part_bytes(p, max_len, t.kv_split) + gn_row_part_bytes(p, t.row_split);
@@ -1376,9 +1377,8 @@ hipError_t launch_dq_generic_bf16_128(const Params& p, int32_t max_len, float* p
 template <typename T, typename TG, int D>
 static hipError_t bwd_finish(const Params& p, int32_t dq_split, const float* dq_part, int32_t kv_units, int32_t kv_split, const float* kv_part,
                              bool redo_keys, hipStream_t st) {
-  constexpr int BPU = 8;
   const int32_t dq_blocks = dq_split > 1 ? (int32_t)(gn_row_blocks(p)) : 0;
-  const int64_t blocks = dq_blocks + (int64_t)kv_units * p.Hkv * BPU;
+  const int64_t blocks = dq_blocks + (int64_t)kv_units * p.Hkv * 2 * part_key_blocks(p);
   if (blocks <= 0) return hipSuccess;
   bwd_finish_kernel<T, TG, D><<<dim3((unsigned)blocks), dim3(256), 0, st>>>(p, gn_tiles(p.C, p.G, p.P, p.m, p.qp), dq_split, dq_part, dq_blocks, kv_split,
                                                                             kv_part, __builtin_ctz(p.P), redo_keys);

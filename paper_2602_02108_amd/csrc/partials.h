@@ -6,6 +6,8 @@
 namespace oomb {
 
 constexpr int PART_ROWS = 128;  // rows of a row tile / keys of a unit: four blocks of 32
+// blocks of 32 keys in a dK / dV unit: 128 keys, or (one list per query page) one page
+__host__ __device__ __forceinline__ int part_key_blocks(const Params& p) { return !p.qp ? PART_ROWS / 32 : p.P <= 32 ? 1 : p.P / 32; }
 
 // the accumulator in groups of four consecutive dims: f(dim, a, b, c, d) for D / 8 groups per lane
 template <typename T, int D, typename F>
@@ -61,8 +63,8 @@ template <typename T> __device__ __forceinline__ void part_add4(T* p, float a, f
 
 // What is left of a backward with splits, in one launch (attn_generic.hip): the dQ partials of `dq_split` key ranges
 // (1: none) and, with kv_units > 0, the slices of that many dK / dV units per KV head.  Slot of slice sp of unit u and KV
-// head g: (u kv_split + sp) Hkv + g, or as the work table says with one list per query page; a slot holds eight blocks
-// of 32 keys x D: dK, then dV.
+// head g: (u kv_split + sp) Hkv + g, or as the work table says with one list per query page; a slot holds the blocks of
+// 32 keys x D of a unit (part_key_blocks): dK, then dV.
 hipError_t launch_bwd_finish(const Params& p, bool is_bf16, int32_t dq_split, const float* dq_part, int32_t kv_units, int32_t kv_split,
                              const float* kv_part, hipStream_t st);
 

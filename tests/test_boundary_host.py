@@ -269,6 +269,19 @@ def test_native_binding_refuses_tensors_without_storage():
         api.page_score_topk(d, q, k, ints, 2, ints, ints, None, ws)
 
 
+@pytest.mark.parametrize("page,keys", [(16, 32), (32, 32), (64, 64), (128, 128)])
+def test_partial_sums_of_a_page_take_the_room_of_its_keys(page, keys):
+    """Backward with one list per query page: a page that many lists hold is cut into units, each with fp32 partial sums of its
+    keys in blocks of 32 -- not of the 128 keys that a unit has with one list per KV head."""
+    m, k, hkv, D = 64, 128, 2, 64
+    d = _good_desc(n_q_heads=4, n_kv_heads=hkv, head_dim=D, page_size=page, chunk_len=m * page, ctx_len=2048 * page, num_phys_pages=2048, dtype=api.F32,
+                   pool_page_stride=hkv * page * D, pool_head_stride=page * D, pool_tok_stride=D, q_tok_stride=4 * D, q_head_stride=D)
+    slots = hkv * (2 * m * (k + m) // 8 + 1)
+    maps = api.workspace_bytes(d, k, api.OP_ATTN_FWD_QP)
+    need = api.workspace_bytes(d, k, api.OP_ATTN_BWD_QP)
+    assert slots * 2 * keys * D * 4 <= need <= slots * 2 * keys * D * 4 + maps + (8 << 20)
+
+
 def test_lists_that_end_before_their_stride_are_copied_first():
     """The kernels read whole rows of the page lists; a view whose last row ends with the memory is told apart."""
     import torch

@@ -17,15 +17,40 @@ def _desc(w, x):
     return api.make_desc(x["q"], x["k_pool"], w.N, w.sm_scale, torch_dtype(w.grad_dtype))
 
 
+# One workgroup per KV head selects where n_past + m * G <= 192 (here m * G = 4, so up to 188 pages), in three groups of 64 pages;
+# from 189 on the ordinary kernels do
 @pytest.mark.parametrize("dtype,D,P", [("f32", 64, 16), ("bf16", 128, 128), ("bf16", 64, 32)])
-@pytest.mark.parametrize("n_past", [1, 191, 192, 193])
+@pytest.mark.parametrize("n_past", [1, 63, 64, 65, 127, 128, 129, 187, 188, 189, 192, 193])
 def test_selection_of_short_histories(n_past, dtype, D, P):
     w = Workload("short", 4, 2, D, P, 2 * P, (n_past + 2) * P, min(n_past, 9), dtype, "f32", 0.1, extra_phys=2, seed=400 + n_past)
     x = make_inputs(w, "cuda")
-    sel, cnt, scores = pu.gpu_select(w, x)
+    ran = ("select_small", "topk_select") if n_past <= 188 else ("topk_select", "select_small")
+    with pu.kernels_ran(ran[:1], absent=ran[1:]):
+        sel, cnt, scores = pu.gpu_select(w, x)
     osel, ocnt, oscores = pu.oracle_select(w, pu.host_inputs(x))
     assert np.array_equal(scores.cpu().numpy().view(np.uint32), oscores.view(np.uint32))
     assert np.array_equal(sel.cpu().numpy(), osel) and np.array_equal(cnt.cpu().numpy(), ocnt)
+
+
+# Equal scores on both sides of pages 64 and 128: groups of pages with the same mean, zeros of either sign, ties to the lower page
+@pytest.mark.parametrize("n_past", [64, 65, 130, 188])
+def test_selection_of_short_histories_with_tied_scores(n_past):
+    hkv, D, P, m = 2, 64, 16, 2
+    g = torch.Generator(device="cuda").manual_seed(480 + n_past)
+    n = n_past + m
+    base = torch.randn((4, hkv, D), generator=g, device="cuda")
+    base[2], base[3] = 0.0, -0.0
+    kbar = base[torch.randint(0, 4, (n,), generator=g, device="cuda")].contiguous()
+    q = torch.randn((m * P, 4, D), generator=g, device="cuda").abs() + 0.1
+    desc = api.make_desc(q, torch.empty((1, hkv, P, D), device="cuda").expand(n, hkv, P, D), n * P, 0.125)
+    desc.pool_page_stride = hkv * P * D
+    for top_k in (1, 5, n_past // 3, 64, n_past - 1, n_past, n_past + 4):
+        scores = torch.empty((hkv, n_past), dtype=torch.float32, device="cuda")
+        with pu.kernels_ran(("select_small",), absent=("topk_select",)):
+            sel, cnt = api.page_score_topk_cached(desc, q, kbar, top_k, scores_out=scores)
+        osel, ocnt, oscores = orc.page_score_topk_cached(orc.Shape(4, hkv, D, P, m * P, n * P, 0.125), q.cpu().numpy(), kbar.cpu().numpy(), top_k)
+        assert np.array_equal(scores.cpu().numpy().view(np.uint32), oscores.view(np.uint32))
+        assert np.array_equal(sel.cpu().numpy(), osel) and np.array_equal(cnt.cpu().numpy(), ocnt), top_k
 
 
 @pytest.mark.parametrize("n_past", [300, 1500, 9000])
@@ -50,7 +75,8 @@ def test_selection_of_a_short_history_with_many_pooled_rows():
     # m * G = 256: the past fits the kernel of one workgroup per KV head, the rows to pool do not
     w = Workload("rows", 32, 1, 128, 16, 16 * 8, 16 * 48, 7, "bf16", "f32", 0.1, seed=420)
     x = make_inputs(w, "cuda")
-    sel, cnt, scores = pu.gpu_select(w, x)
+    with pu.kernels_ran(("qpool_final",), absent=("select_small",)):
+        sel, cnt, scores = pu.gpu_select(w, x)
     osel, ocnt, oscores = pu.oracle_select(w, pu.host_inputs(x))
     assert np.array_equal(scores.cpu().numpy().view(np.uint32), oscores.view(np.uint32))
     assert np.array_equal(sel.cpu().numpy(), osel)

@@ -387,6 +387,12 @@ template <int N> __device__ __forceinline__ bool gn_not_finite(const f32x16 (&v)
     for (int x = 0; x < 16; ++x) z = __builtin_fmaf(v[k][x], 0.f, z);
   return z != 0.f;
 }
+// The launch parameters (every kernel's first argument) read anew: held for this path they would be spilled in front of the main loops.
+__device__ __forceinline__ const Params& gn_params_again() {
+  auto args = __builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(args));
+  return *(const Params*)args;
+}
 // lanes l and l + 32 hold one row or key: bit l of the result
 __device__ __forceinline__ uint32_t gn_either_half(bool v) {
   const uint64_t b = __ballot(v);
@@ -625,7 +631,7 @@ __global__ __launch_bounds__(256 * KH, 2) void fwd_generic_kernel(Params p, int3
     if (t.valid && hh == 0) p.lse[(int64_t)t.h * p.C + t.i] = gn_lse(p, m_run, l_tot);
     for (; bad; bad &= bad - 1) {
       const int x = __builtin_ctz(bad);
-      gn_redo_row<T, D, false>(p, b.g, __builtin_amdgcn_readlane(t.i, x), __builtin_amdgcn_readlane(t.h, x), lp, lane, gn_lane(m_run * c, x), gn_lane(inv, x), 0.f);
+      gn_redo_row<T, D, false>(gn_params_again(), b.g, __builtin_amdgcn_readlane(t.i, x), __builtin_amdgcn_readlane(t.h, x), lp, lane, gn_lane(m_run * c, x), gn_lane(inv, x), 0.f);
     }
   }
 }
@@ -763,7 +769,7 @@ __global__ __launch_bounds__(256) void fwd_combine_kernel(Params p, int32_t tile
   for (bad &= 0xffu << (8 * wave); bad; bad &= bad - 1) {   // (eight rows per wave)
     const int x = __builtin_ctz(bad);
     if (gn_out_row(p, tiles, block, x, i, h))
-      gn_redo_row<T, D, false>(p, h / p.G, i, h, lp, lane, gn_lane(M * c, x), gn_lane(inv, x), 0.f);
+      gn_redo_row<T, D, false>(gn_params_again(), h / p.G, i, h, lp, lane, gn_lane(M * c, x), gn_lane(inv, x), 0.f);
   }
 }
 
@@ -882,7 +888,7 @@ __device__ __forceinline__ void dq_body(const Params& p, unsigned char* smem, in
     }
     for (; bad; bad &= bad - 1) {
       const int x = __builtin_ctz(bad);
-      gn_redo_row<T, D, true>(p, b.g, __builtin_amdgcn_readlane(t.i, x), __builtin_amdgcn_readlane(t.h, x), lp, lane, gn_lane(lse2, x), p.sm_scale, gn_lane(delta, x));
+      gn_redo_row<T, D, true>(gn_params_again(), b.g, __builtin_amdgcn_readlane(t.i, x), __builtin_amdgcn_readlane(t.h, x), lp, lane, gn_lane(lse2, x), p.sm_scale, gn_lane(delta, x));
     }
   }
 }
@@ -1115,7 +1121,7 @@ __device__ __forceinline__ void dkv_body(const Params& p, unsigned char* smem, i
     for (int is_dk = 0; is_dk < 2; ++is_dk)
       for (uint32_t left = bad[is_dk]; left; left &= left - 1) {
         const int32_t k = 32 * wave + __builtin_ctz(left);
-        gn_redo_key<T, TG, D>(p, g, e0 + (p.qp ? 0 : k >> lp), k & (p.P - 1), is_dk, lp, lane);
+        gn_redo_key<T, TG, D>(gn_params_again(), g, e0 + (p.qp ? 0 : k >> lp), k & (p.P - 1), is_dk, lp, lane);
       }
   }
 }
@@ -1157,7 +1163,7 @@ __global__ __launch_bounds__(256) void bwd_finish_kernel(Params p, int32_t tiles
     });
     for (bad &= 0xffu << (8 * wave); bad; bad &= bad - 1)
       if (gn_out_row(p, tiles, blockIdx.x, __builtin_ctz(bad), i, h))
-        gn_redo_row<T, D, true>(p, h / p.G, i, h, lp, lane, p.lse[(int64_t)h * p.C + i] * 1.4426950408889634f, sc, gn_delta<T, D>(p, i, h));
+        gn_redo_row<T, D, true>(gn_params_again(), h / p.G, i, h, lp, lane, p.lse[(int64_t)h * p.C + i] * 1.4426950408889634f, sc, gn_delta<T, D>(p, i, h));
     return;
   }
   // (last units first: their slices were written last and are still in the memory-side cache)
@@ -1199,7 +1205,7 @@ __global__ __launch_bounds__(256) void bwd_finish_kernel(Params p, int32_t tiles
   });
   for (bad &= 0xffu << (8 * wave); bad; bad &= bad - 1) {
     const int32_t x = __builtin_ctz(bad), k = 32 * kb + x, e = e0 + (p.qp ? 0 : x >> lp);
-    if (p.qp ? k < p.P : e < list_len(p, g)) gn_redo_key<T, TG, D>(p, g, e, k & (p.P - 1), which == 0, lp, lane);
+    if (p.qp ? k < p.P : e < list_len(p, g)) gn_redo_key<T, TG, D>(gn_params_again(), g, e, k & (p.P - 1), which == 0, lp, lane);
   }
 }
 

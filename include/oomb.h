@@ -30,7 +30,8 @@
  *   LSE               [Hq][C] float, natural log of the sum of exp(scaled logits)
  *   selection lists   [Hkv][sel_stride] int32 LOGICAL page ids, ascending, distinct,
  *                     with sel_count[g] valid entries; they must contain the m local
- *                     pages n_past..n-1 (so that no query row is empty)
+ *                     pages n_past..n-1 (so that no query row is empty).  The entries past
+ *                     sel_count[g] may hold anything, but the whole row may be read
  * All base pointers and strides must keep 16-byte alignment of every D-row.
  *
  * Errors: every entry point validates host-visible scalars and pointers before
@@ -140,6 +141,14 @@ oomb_status oomb_page_score_topk_noalloc(const oomb_attn_desc* desc, const void*
                                          int32_t* sel_count, float* scores_out, void* hip_stream);
 
 /*
+ * Values that are not finite (forward and backward, with either kind of lists): a row takes up the tokens
+ * that it sees, a key the rows that see it, and an infinity or NaN anywhere else does not reach them.
+ * Except in bf16 calls with page size and head dim 128 and rows or keys enough to fill the device: their kernels
+ * give a token of the chunk that a row does not see a weight of zero, so a NaN or infinity in its V (backward:
+ * K, Q or dO) may reach rows and keys of the same tile.  Tokens padded past the end of a text hold zeros.
+ */
+
+/*
  * Paged attention forward (Sec. 4.1 operator over the pages of Sec. 4.2).
  * For every query head h and chunk row i:
  *   s_t = sm_scale * <Q[i,h], K[t,g]> over the visible tokens t,
@@ -168,7 +177,7 @@ oomb_status oomb_paged_attn_fwd(const oomb_attn_desc* desc, const void* q, const
  * pools are never zeroed here.  Each (KV head, page) is updated by exactly one
  * workgroup with plain loads and stores (no atomics), so results do not depend
  * on scheduling.  `sel_pages` must be the list the forward used; `o` and `lse`
- * are the forward's outputs.
+ * are the forward's outputs.  `d_q` may overlap `o`.
  */
 oomb_status oomb_paged_attn_bwd(const oomb_attn_desc* desc, const void* q, const void* k_pool,
                                 const void* v_pool, const int32_t* page_table,

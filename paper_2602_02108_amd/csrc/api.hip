@@ -15,7 +15,7 @@ size_t up256(size_t x) { return (x + 255) & ~(size_t)255; }
 size_t elem_size(int32_t dt) { return dt == OOMB_BF16 ? 2 : 4; }
 bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
-// Kernels without MFMA can be forced for debugging and cross-checks.
+// The shape-generic kernels (votes: those without matrix instructions) can be forced for debugging and cross-checks.
 bool force_generic() {
   static int v = -1;
   if (v < 0) {
@@ -363,7 +363,7 @@ oomb_status oomb_paged_attn_bwd_qp(const oomb_attn_desc* desc, const void* q, co
   if (s != OOMB_OK) return s;
   const bool bf = desc->dtype == OOMB_BF16;
   const bool use_mfma = !force_generic() && mfma_supported(p, bf);
-  // at most 65535: list entries of the shape-generic backward, cut pages of the slice reduction (a grid dimension)
+  // at most 65535: list entries of the shape-generic backward, cut pages of the others
   if (p.Hkv > 65535 || (!use_mfma && qp_union_cap(p, sel_stride) > 65535) ||
       (use_mfma && qp_max_multi(p, sel_stride) > 65535))
     return OOMB_ERR_UNSUPPORTED;

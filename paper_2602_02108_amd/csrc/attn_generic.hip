@@ -25,7 +25,7 @@
 // of workgroups, which is why the streamed side is cut into splits whose partial sums a second
 // kernel combines in a fixed order.  Measured against one wave per query row (per key in dK / dV)
 // with plain fp32 arithmetic: 28 / 4 heads fp32, chunk 512, 16 + 4 pages of 128: 41.5 -> 0.84 ms
-// (59 GFLOP); 8 / 2 heads bf16, chunk 1088, 24 + 17 pages of 64: 18.4 -> 0.13 ms (32 GFLOP).
+// (59 GFLOP); 8 / 2 heads bf16, chunk 1088, 24 + 17 pages of 64: 18.4 -> 0.15 ms (32 GFLOP).
 #include "mfma_common.h"
 #include "launch.h"
 #include "partials.h"
@@ -1220,7 +1220,7 @@ static inline size_t gn_up(size_t x) { return (x + 255) & ~(size_t)255; }
 // top a round costs RAMP (launch, list -> page table -> first tile), and a split its combine kernel and the
 // partial sums, written and read at about 4 TB/s.  The constants are fitted to a sweep over 28 / 4 and 6 / 2 heads, 1 to
 // 48 query pages, lists of 8 to 240 + m pages, 1 to 24 splits.  E.g. 28 / 4 heads, 65 pages, one query page (28 tiles of 128
-// rows): 8 splits of two groups, 36 us against 123 without; 12 query pages (336 tiles): 3 splits of single
+// rows): 9 splits of two groups, 36 us against 123 without; 12 query pages (336 tiles): 3 splits of single
 // groups, 241 against 260.
 static int32_t gn_list_len(const Params& p, int32_t max_len) { return p.qp ? p.sel_stride : max_len; }
 struct GnPlan { int32_t n, groups; float us; };

@@ -414,14 +414,16 @@ template <typename T, int D> __device__ __forceinline__ float gn_delta(const Par
   const int64_t off = (int64_t)i * p.q_tok_stride + (int64_t)h * p.q_head_stride;
   return p.delta ? p.delta[(int64_t)h * p.C + i] : gn_row_dot<T, D>((const T*)p.d_o + off, (const T*)p.o + off);
 }
-// acc += sum over the lanes x < cnt of w_x times row off_x of `rows` (elements), the lane's dims lane, lane + 64
-template <typename T, int D> __device__ __forceinline__ void gn_add_rows(float (&acc)[D / 64], const T* rows, float w, int64_t off, int cnt, int lane) {
+// acc += sum over the lanes x < cnt of w_x times row off_x of `rows` (elements), the lane's dims lane, lane + 64.  True: every
+// dim is NaN and stays so (a row or key that sees a NaN mostly ends here after its first 64).
+template <typename T, int D> __device__ __forceinline__ bool gn_add_rows(float (&acc)[D / 64], const T* rows, float w, int64_t off, int cnt, int lane) {
   for (int x = 0; x < cnt; ++x) {
     const float wx = gn_lane(w, x);
     const T* row = rows + gn_lane64(off, x);
 #pragma unroll
     for (int k = 0; k < D / 64; ++k) acc[k] += wx * Elem<T>::load(row + 64 * k + lane);
   }
+  return __all(D == 64 ? acc[0] != acc[0] : acc[0] != acc[0] && acc[D / 64 - 1] != acc[D / 64 - 1]);
 }
 // O of one row (ref: its largest logit, times log2 e; scale: 1 / the sum of its probabilities), or dQ (ref: LSE times log2 e)
 template <typename T, int D, bool DQ>
@@ -447,7 +449,7 @@ __device__ __forceinline__ void gn_redo_row(const Params& p, int g, int i, int h
       w = __builtin_amdgcn_exp2f(__builtin_fmaf(gn_row_dot<T, D>(q, (const T*)p.k_pool + off), c, -ref));
       if (DQ) w *= gn_row_dot<T, D>(d_o, (const T*)p.v_pool + off) - delta;
     }
-    gn_add_rows<T, D>(acc, (const T*)(DQ ? p.k_pool : p.v_pool), w, off, V - t0 < 64 ? V - t0 : 64, lane);
+    if (gn_add_rows<T, D>(acc, (const T*)(DQ ? p.k_pool : p.v_pool), w, off, V - t0 < 64 ? V - t0 : 64, lane)) break;
   }
   T* dst = (T*)(DQ ? p.d_q : p.o) + roff;
 #pragma unroll
@@ -462,13 +464,14 @@ template <typename T, typename TG, int D> __device__ __forceinline__ void gn_red
   const int32_t n_seg = p.qp ? inv[1] - inv[0] : 1;
   const float c = p.sm_scale * 1.4426950408889634f;
   float acc[D / 64] = {};
-  for (int32_t seg = 0; seg < n_seg; ++seg) {   // the chunk's rows, or those of every query page that lists the page
+  bool done = false;
+  for (int32_t seg = 0; seg < n_seg && !done; ++seg) {   // the chunk's rows, or those of every query page that lists the page
     int32_t r0 = 0, end = p.C * p.G;
     if (p.qp) {
       r0 = p.inv_qp[(int64_t)g * p.m * p.sel_stride + inv[0] + seg] * rpq;
       end = r0 + rpq;
     }
-    for (r0 = r0 < r_key ? r_key : r0; r0 < end; r0 += 64) {
+    for (r0 = r0 < r_key ? r_key : r0; r0 < end && !done; r0 += 64) {
       float w = 0.f;
       int64_t off = 0;
       if (r0 + lane < end) {
@@ -479,7 +482,7 @@ template <typename T, typename TG, int D> __device__ __forceinline__ void gn_red
           w *= gn_row_dot<T, D>((const T*)p.d_o + off, (const T*)p.v_pool + koff) - gn_delta<T, D>(p, i, h);
         }
       }
-      gn_add_rows<T, D>(acc, (const T*)(is_dk ? p.q : p.d_o), w, off, end - r0 < 64 ? end - r0 : 64, lane);
+      done = gn_add_rows<T, D>(acc, (const T*)(is_dk ? p.q : p.d_o), w, off, end - r0 < 64 ? end - r0 : 64, lane);
     }
   }
   TG* dst = (TG*)(is_dk ? p.dk_pool : p.dv_pool) + koff;

@@ -198,6 +198,33 @@ def test_values_that_are_not_finite_stay_with_those_who_see_them(w, what):
     _same_where_finite("dV", pu.f32(x["dv_pool"]), rdv, gd)
 
 
+@pytest.mark.parametrize("w", [UNSEEN[1], UNSEEN[4], UNSEEN[7]], ids=lambda w: w.name)
+def test_what_everyone_sees_reaches_everyone(w):
+    # a NaN in a key that every row sees: nothing of the results is finite but the gradients of pages that nobody lists
+    x = make_inputs(w, "cuda")
+    sel = cnt = None
+    if w.top_k is not None:
+        sel, cnt, _ = pu.gpu_select(w, x, want_scores=False)
+    if w.name.startswith("qp_"):
+        osel, ocnt = rand_qp_lists(w, w.n_past, w.seed)
+        sel, cnt = torch.as_tensor(osel, device="cuda"), torch.as_tensor(ocnt, device="cuda")
+    attn_fwd, attn_bwd = (api.paged_attn_fwd_qp, api.paged_attn_bwd_qp) if w.name.startswith("qp_") else (api.paged_attn_fwd, api.paged_attn_bwd)
+    for g in range(w.Hkv):
+        first = int(sel.reshape(w.Hkv, -1)[g, 0])
+        x["k_pool"][x["page_table"][first].long(), g, 0, 0] = math.nan
+    desc = api.make_desc(x["q"], x["k_pool"], w.N, w.sm_scale, torch_dtype(w.grad_dtype))
+    args = (desc, x["q"], x["k_pool"], x["v_pool"], x["page_table"])
+    o, lse = attn_fwd(*args, sel, cnt)
+    dq = attn_bwd(*args, o, lse, x["d_o"], x["dk_pool"], x["dv_pool"], sel, cnt)
+    assert o.isnan().all() and lse.isnan().all() and dq.isnan().all()
+    listed = torch.zeros((w.n_phys, w.Hkv), dtype=torch.bool, device="cuda")
+    for g in range(w.Hkv):
+        pages = sel.reshape(w.Hkv, -1)[g]
+        listed[x["page_table"][pages[pages >= 0].long()].long(), g] = True
+    for pool in ("dk_pool", "dv_pool"):
+        assert x[pool][listed].isnan().all() and (x[pool][~listed] == 0).all()
+
+
 @pytest.mark.parametrize("n_past", [1, 40])
 def test_rows_whose_scores_are_all_far_below_zero(n_past):
     # products of about -1e33, logits of about -150: a running maximum must not start above them

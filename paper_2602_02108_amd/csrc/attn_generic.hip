@@ -1473,17 +1473,18 @@ hipError_t launch_bwd_generic(const Params& p, bool bf, int32_t max_len, void* w
 // workgroups for less than a round, or for little more than one, they leave compute units idle.  They also need the
 // page images (forward) or the row statistics (dQ) of a kernel before them: 20 ns per page and head.  With one list per query page the
 // images are those of the union of a head's lists, whose length the host does not know: 2.5 lists (32 lists of 160 entries of the 1M
-// votes workload: 400 pages; max_len, the worst case, would be 5120, 410 us for a kernel of 32).  Forward of 28 / 4, 32 / 8 and
-// 14 / 2 heads, 4 to 64 query pages, 8 to 128 past pages each, lists all alike to 1/8 their own: what is chosen is at most
-// 4 % slower than the other, e.g. 32 / 8, 32 query pages, 128 past pages: 1192 to 1263 us (these 1261 to 1268), 16 query
-// pages, 32 past pages: these 223 to 226 (231 to 238).
+// votes workload: 400 pages; max_len, the worst case, would be 5120, 410 us for a kernel of 32), after the maps of those lists.
+// The constants are fitted to both kernels timed at 28 / 4, 32 / 8, 14 / 2, 6 / 2 and 4 / 4 heads, 1 to 64 query pages, 8 to 256 past pages
+// (289 shapes; 180 with lists of their own per query page).  What is chosen is on average 0.2 % slower than the better one, at most
+// 8 % (14 % with lists per query page) -- forward; with the first constants, of fewer shapes, 0.7 % and 30 %, e.g. 14 / 2, 48
+// query pages, 64 past pages: these 717, those 552 us.  dQ: 0.2 %, at most 16 %.
 bool rows_take_generic(const Params& p, int32_t max_len, bool dq) {
   const float r = row_tiles_per_head(p.C, p.G, p.m, p.qp) * p.Hkv / 256.f;
-  const float avg = 2.f * ((float)gn_list_len(p, max_len) - 0.5f * p.m);
+  const float avg = 2.f * ((float)gn_list_len(p, max_len) - 0.5f * p.m), plan = gn_plan(p, true, max_len, dq).us;
+  if (dq) return plan < 0.97f * (gn_rounds(r, 0.78f, 0.2f, 0.6f, 0.3f) * avg * 2.55f + ceilf(r) * 8.f + 4.f + (float)p.C * p.Hq * 7e-5f);
   const float lists = 2.5f * (float)p.sel_stride, images = p.qp && lists < (float)max_len ? lists : (float)max_len;
-  const float before = dq ? 4.f + (float)p.C * p.Hq * 7e-5f : 5.f + (float)p.Hkv * images * 0.02f;
-  const float own = gn_rounds(r, 0.78f, 0.2f, 0.6f, 0.3f) * avg * (dq ? 2.55f : 2.0f) + ceilf(r) * 8.f + before;
-  return gn_plan(p, true, max_len, dq).us < (p.qp && !dq ? 1.f : 0.97f) * own;
+  const float before = (p.qp ? 60.f : 30.f) + (float)p.Hkv * images * 0.02f;
+  return plan < 0.98f * (gn_rounds(r, 0.6f, 0.28f, 0.35f, 0.45f) * avg * 2.0f + before);
 }
 
 }  // namespace oomb

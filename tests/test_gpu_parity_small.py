@@ -279,8 +279,8 @@ def test_mfma_bf16_backward_kernels_for_many_rows(w, pad):
 # per KV head.  Oracle rows: page and block boundaries and random ones.
 FULL_ROWS = [
     Workload("bf16_rows_g7", 28, 4, 128, 128, 128 * 17, 128 * 70, None, "bf16", "f32", 0.0884, extra_phys=1, seed=76),
-    Workload("bf16_rows_g3", 48, 16, 128, 128, 128 * 20, 128 * 36, None, "bf16", "f32", 0.0884, seed=77),
-    Workload("bf16_rows_g3_ragged", 24, 8, 128, 128, 128 * 21, 128 * 90, None, "bf16", "f32", 0.0884, seed=78),
+    Workload("bf16_rows_g3", 48, 16, 128, 128, 128 * 20, 128 * 80, None, "bf16", "f32", 0.0884, seed=77),
+    Workload("bf16_rows_g5_ragged", 20, 4, 128, 128, 128 * 25, 128 * 120, None, "bf16", "f32", 0.0884, seed=78),
     Workload("bf16_rows_g7_sparse", 14, 2, 128, 128, 128 * 33, 128 * 200, 39, "bf16", "f32", 0.0884, boost_frac=0.05, seed=79),
 ]
 
@@ -306,7 +306,7 @@ def test_mfma_bf16_forward_kernel_for_many_rows(w):
 
 
 # One list per query page: images of two and a half lists are cheap enough for the kernel for many rows, or they are not
-@pytest.mark.parametrize("m,k,ran", [(32, 64, "attn_fwd_mfma"), (16, 32, "attn_fwd_split")])
+@pytest.mark.parametrize("m,k,ran", [(64, 64, "attn_fwd_mfma"), (16, 32, "attn_fwd_split")])
 def test_forward_with_lists_per_query_page_takes_the_kernel_that_the_rows_ask_for(m, k, ran):
     w = Workload("bf16_qp_rows", 32, 8, 128, 128, 128 * m, 128 * (m + 100), None, "bf16", "f32", 0.0884, seed=82)
     x = make_inputs(w, "cuda", zero_grad_pools=False)

@@ -10,8 +10,8 @@
 // They run on a FEW workgroups that walk the tiles: host accesses take microseconds, and
 // a grid that covers the chip fills the memory pipeline of every compute unit with them,
 // which stalls a concurrently running kernel almost completely (measured: with 128 or more
-// workgroups nothing overlaps); 8 workgroups of 256 threads nearly saturate the link (55 GB/s in, 45 GB/s
-// each way) and disturb only the compute units they sit on.
+// workgroups nothing overlaps); 10 to 12 workgroups of 256 threads saturate the link (55 GB/s in, 47 GB/s each
+// way) and disturb only the compute units they sit on.
 //   offload_plan       which KV heads hold each page (bit mask over the lists: one list per
 //                      KV head, or one per KV head and query page) and the staging slot of
 //                      every held page (ascending logical page order), one workgroup.  The
@@ -247,19 +247,23 @@ void* device_view(const void* ptr) {
 }
 
 // Workgroups of a transfer kernel (OOMB_OFFLOAD_WGS overrides the default, for experiments), and those that clear gradient
-// staging tiles beside a fetch.  Each takes a compute unit from the attention that the transfer hides behind.  1M tokens, 28 / 4
-// heads, 128 pages: step with overlapped transfers / with transfers in series / fetch / write-back in ms,
-//   12 + 48: 4.90 / 7.25 / 0.76 / 1.80      10 + 16: 4.94 / 7.38 / 0.76 / 1.80      8 + 4: 4.82 / 7.36 / 0.77 / 1.88
-//   7 + 4:   4.81 / 7.40 / 0.79 / 1.87      6 + 16:  4.86 / 7.87 / 0.81 / 2.19
-// (12 workgroups that waited for their own stores: 4.84 / 7.51 / 0.87 / 1.89; the step without transfers: 4.45).
+// staging tiles beside a fetch.  Each takes a compute unit from the attention that the transfer hides behind.  Long transfers, those
+// that are hidden, take the fewest that carry what the link does; short ones two more, for their ends and host memory that is cold.
+// 1M tokens, 28 / 4 heads, 128 pages (2560 tiles of capacity), movers + clearing: step with overlapped transfers / with transfers
+// in series / fetch / write-back in ms,
+//   12 + 48: 4.85 / 7.24 / 0.76 / 1.81    12 + 4: 4.87 / 7.23 / 0.76 / 1.81    10 + 4: 4.81 / 7.22 / 0.76 / 1.80    8 + 4: 4.77 / 7.33 / 0.77 / 1.88
+// (12 that wait for their own stores: 4.79 / 7.43 / 0.87 / 1.89; the step without transfers: 4.35).  Steps in series, inputs that change, 12 + 48,
+// 12 + 4, 10 + 48 in us: 384 tiles 541, 541, 560; 564 tiles 616, 618, 642; 1280 tiles 2628, 2631, 2658.
 constexpr int ZERO_WGS = 4;
+constexpr int64_t LONG_TRANSFER = 2048;   // tiles of the staging pools' capacity
 static unsigned transfer_wgs(int64_t tiles) {
-  static int v = 0;
-  if (!v) {
+  static int forced = -1;
+  if (forced < 0) {
     const char* e = std::getenv("OOMB_OFFLOAD_WGS");
-    v = e ? std::atoi(e) : 8;
-    if (v < 1) v = 8;
+    const int v = e ? std::atoi(e) : 0;
+    forced = v < 1 ? 0 : v;
   }
+  const int v = forced ? forced : tiles >= LONG_TRANSFER ? 10 : 12;
   return (unsigned)(tiles < v ? (tiles > 0 ? tiles : 1) : v);
 }
 

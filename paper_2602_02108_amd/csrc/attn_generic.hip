@@ -21,6 +21,7 @@
 // and the rows of a query page are contiguous for every page size.
 //
 // What bounds them: fp32 the matrix pipe itself (256 flops per cycle and compute unit, 157 TFLOP/s);
+// (fp32 at head dim 128, calls that are not short: dQ, dK and dV in one kernel, which forms S and dP once, bwd_units_kernel;)
 // bf16 the exposed vector work and LDS latency of one or two waves per SIMD; short calls the number
 // of workgroups, which is why the streamed side is cut into splits whose partial sums a second
 // kernel combines in a fixed order.  Measured against one wave per query row (per key in dK / dV)
@@ -781,11 +782,20 @@ __global__ __launch_bounds__(256) void fwd_combine_kernel(Params p, int32_t tile
 // bias words from which attn_bwd_dkv_mfma.hip starts its accumulators.  Where dQ overlaps O otherwise than row on row, a row of O may
 // be overwritten before its workgroup reads it: then delta_kernel has filled p.delta beforehand.
 template <typename T, int D> __global__ __launch_bounds__(256) void delta_kernel(Params p) {
-  const int64_t row = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  constexpr int NG = Gn<T, D>::NG;   // lanes of a row, 16 bytes each
+  const int64_t row = (int64_t)blockIdx.x * (256 / NG) + threadIdx.x / NG;
   if (row >= (int64_t)p.C * p.Hq) return;
-  const int i = (int)(row / p.Hq), h = (int)(row - (int64_t)i * p.Hq);
+  const int i = (int)(row / p.Hq), h = (int)(row - (int64_t)i * p.Hq), c = threadIdx.x % NG;
   const int64_t off = (int64_t)i * p.q_tok_stride + (int64_t)h * p.q_head_stride;
-  p.delta[(int64_t)h * p.C + i] = gn_row_dot<T, D>((const T*)p.d_o + off, (const T*)p.o + off);
+  float d = gn_dot<T>(reinterpret_cast<const u32x4_t*>((const T*)p.d_o + off)[c], reinterpret_cast<const u32x4_t*>((const T*)p.o + off)[c], 0.f);
+#pragma unroll
+  for (int o = 1; o < NG; o <<= 1) d += __shfl_xor(d, o, 64);
+  if (c == 0) p.delta[(int64_t)h * p.C + i] = d;
+}
+template <typename T, int D> static hipError_t launch_delta(const Params& p, hipStream_t st) {
+  constexpr int R = 256 / Gn<T, D>::NG;
+  delta_kernel<T, D><<<dim3((unsigned)(((int64_t)p.C * p.Hq + R - 1) / R)), dim3(256), 0, st>>>(p);
+  return hipGetLastError();
 }
 template <typename T, int D, int KH, int NT>
 __device__ __forceinline__ void dq_body(const Params& p, unsigned char* smem, int32_t block, int32_t tiles, int32_t n_split, int lp, int32_t max_len,
@@ -909,16 +919,33 @@ __global__ __launch_bounds__(256 * KH, (Gn<T, D>::RB == 512 ? 1 : 2)) void dq_ge
 template <typename T, int D> struct GnKey {
   static constexpr int KT = GnTiles<T, D>::KT;
   static constexpr int STAT = 2 * GnTiles<T, D>::BUF, LDS = STAT + 2 * 2 * 64 * 4;   // two buffers, {lse2, delta} of their rows
+  // with dQ: dS of a stage as [row][key], rows 544 bytes apart (both the dwords of 32 keys x 2 rows that a store moves and the 16 bytes x 64 rows
+  // of a read fall on all banks)
+  static constexpr int DS = LDS, DS_ROW = GN_ROWS * 4 + 32, KL = DS + KT * DS_ROW, KL_ROW = GN_ROWS * 4 + 16, LDS_DQ = KL + GN_ROWS * KL_ROW;
 };
-template <typename T, typename TG, int D, bool OWN_DELTA, int NT>
-__device__ __forceinline__ void dkv_body(const Params& p, unsigned char* smem, int32_t bid, int32_t n_split, int lp, float* __restrict__ part) {
+// first stage of KT rows that sees list entry e of KV head g
+template <int KT> __device__ __forceinline__ int32_t gn_first_stage(const Params& p, int g, int32_t e, int lp) {
+  const int64_t pos = owned_at(p, g, e) << lp, first_q = p.N - p.C;
+  return (pos > first_q ? (int32_t)(pos - first_q) * p.G : 0) / KT;
+}
+// DQ (fp32, one list per KV head): the unit's share of dQ as well, dq_part[unit][block of 32 rows] in the layout of part_store: S
+// and dP are formed once instead of once here and once in the dQ kernel.
+struct GnPiece { int32_t g, e0, s0, s1, slot; float* dq_part; int32_t row_blocks; };   // DQ: stages s0 .. s1 - 1 of the unit from list entry e0 on
+template <typename T, typename TG, int D, bool OWN_DELTA, int NT, bool DQ = false>
+__device__ __forceinline__ void dkv_body(const Params& p, unsigned char* smem, int32_t bid, int32_t n_split, int lp, float* __restrict__ part,
+                                         const GnPiece& piece = GnPiece()) {
   typedef Gn<T, D> X;
   typedef GnKey<T, D> R;
   typedef GnTiles<T, D> Y;
-  const int tid = threadIdx.x, lane = tid & 63, hh = lane >> 5, lq = lane & 31, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int32_t rest = bid / p.Hkv, g = bid - rest * p.Hkv;
+  int tid = threadIdx.x;
+  if (DQ) asm volatile("" : "+v"(tid));   // (nothing that depends on the lane is kept from one piece to the next: it would be spilled)
+  const int lane = tid & 63, hh = lane >> 5, lq = lane & 31, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int32_t rest = DQ ? 0 : bid / p.Hkv, g = DQ ? piece.g : bid - rest * p.Hkv;
   int32_t e0, sp = 0, q0 = 0, qc = 0, slot = -1;
-  if (p.qp) {
+  if constexpr (DQ) {
+    e0 = piece.e0;
+    slot = piece.slot;
+  } else if (p.qp) {
     const int32_t n_units = p.unit_count[g];
     if (rest >= n_units) return;
     const int4 un = p.units[(int64_t)g * p.max_units + (n_units - 1 - rest)];
@@ -941,15 +968,16 @@ __device__ __forceinline__ void dkv_body(const Params& p, unsigned char* smem, i
   const int64_t l = owned_at(p, g, e), pos = (l << lp) + (kq & (p.P - 1));
   const int64_t koff = (int64_t)p.page_table[l] * p.pool_page_stride + (int64_t)g * p.pool_head_stride + (int64_t)(kq & (p.P - 1)) * p.pool_tok_stride;
   // rows before r_key do not see the key
-  const int32_t r_key = pos > first_q ? (int32_t)(pos - first_q) * p.G : 0;
+  int32_t r_key = pos > first_q ? (int32_t)(pos - first_q) * p.G : 0;
+  if (DQ && !kvalid) r_key = INT32_MAX;
   const int32_t r_key_max = __builtin_amdgcn_readlane(r_key, 31);
   const int64_t pos0 = owned_at(p, g, e0) << lp;
   const int32_t r_lo = pos0 > first_q ? (int32_t)(pos0 - first_q) * p.G : 0, rows = p.C * p.G;
   // stages of KT rows: [s0, s1) of the chunk's, or stage v % spq of the unit's query page v / spq
   const int32_t rpq = p.P * p.G, spq = (rpq + R::KT - 1) / R::KT;
   const int32_t st_lo = r_lo / R::KT, st_n = (rows + R::KT - 1) / R::KT - st_lo;
-  const int32_t s0 = p.qp ? 0 : st_lo + (int32_t)((int64_t)st_n * sp / n_split);
-  const int32_t s1 = p.qp ? qc * spq : st_lo + (int32_t)((int64_t)st_n * (sp + 1) / n_split);
+  const int32_t s0 = DQ ? piece.s0 : p.qp ? 0 : st_lo + (int32_t)((int64_t)st_n * sp / n_split);
+  const int32_t s1 = DQ ? piece.s1 : p.qp ? qc * spq : st_lo + (int32_t)((int64_t)st_n * (sp + 1) / n_split);
   int32_t tau_v = 0;
   if (p.qp && lane < qc) tau_v = p.inv_qp[(int64_t)g * p.m * p.sel_stride + p.inv_off[(int64_t)g * (p.un_stride + 1) + e0] + q0 + lane];
 
@@ -966,6 +994,15 @@ __device__ __forceinline__ void dkv_body(const Params& p, unsigned char* smem, i
   const float c = p.sm_scale * 1.4426950408889634f;
   GnAddr<T, D> ad;
   ad.init(lane, 0);
+  if constexpr (DQ) {   // K of all keys of the unit as [key][dim] in LDS
+#pragma unroll
+    for (int j = 0; j < X::NJ; ++j) *reinterpret_cast<u32x4_t*>(smem + R::KL + (32 * wave + lq) * R::KL_ROW + 32 * j + 16 * hh) = kf[j];
+    if (!active) {   // (keys past the list: dS is and stays zero)
+      float* ds = reinterpret_cast<float*>(smem + R::DS) + 32 * wave + lq;
+#pragma unroll
+      for (int x = 0; x < 16; ++x) ds[(8 * (x >> 2) + 4 * hh + (x & 3)) * (R::DS_ROW / 4)] = 0.f;
+    }
+  }
 
   // rows [base, end) of stage s
   auto stage_rows = [&](int32_t s, int32_t& base, int32_t& end) {
@@ -1091,6 +1128,11 @@ __device__ __forceinline__ void dkv_body(const Params& p, unsigned char* smem, i
               if (n == NP - 1) {
 #pragma unroll
                 for (int x = 0; x < 16; x += 2) ds.set2(x, sv[1][x], sv[1][x + 1]);
+                if constexpr (DQ) {
+                  float* o = reinterpret_cast<float*>(smem + R::DS) + 32 * wave + lq;
+#pragma unroll
+                  for (int x = 0; x < 16; ++x) o[(8 * (x >> 2) + 4 * hh + (x & 3)) * (R::DS_ROW / 4)] = sv[1][x];
+                }
               }
             } else {
               gn_tr_mma<T, D, NT>(k - 2 * NJ - NP, f, ds, dk);
@@ -1098,6 +1140,37 @@ __device__ __forceinline__ void dkv_body(const Params& p, unsigned char* smem, i
           });
     }
     if (s + 1 < s1) publish(buf ^ Y::BUF);
+    if constexpr (DQ) {
+      __syncthreads();
+      f32x16 dq;
+#pragma unroll
+      for (int x = 0; x < 16; ++x) dq[x] = 0.f;
+      // operands of four instructions: dS of keys 8 t + 4 hh .. + 3 (row lq), K of the same keys (dim 32 wave + lq)
+      const uint32_t at_ds = R::DS + lq * R::DS_ROW + 16 * hh, at_k = R::KL + 4 * hh * R::KL_ROW + (32 * wave + lq) * 4;
+      u32x4_t fd[2];
+      float fk[2][4];
+      auto load = [&](const int t) __attribute__((always_inline)) {
+        fd[t & 1] = *reinterpret_cast<const u32x4_t*>(smem + (at_ds + 32 * t));
+#pragma unroll
+        for (int x = 0; x < 4; ++x) fk[t & 1][x] = *reinterpret_cast<const float*>(smem + (at_k + (8 * t + x) * R::KL_ROW));
+      };
+      load(0);
+#pragma unroll
+      for (int t = 0; t < 16; ++t) {
+        if (t + 1 < 16) {
+          load(t + 1);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+#pragma unroll
+        for (int x = 0; x < 4; ++x) dq = __builtin_amdgcn_mfma_f32_32x32x2f32(fk[t & 1][x], __uint_as_float(fd[t & 1][x]), dq, 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      // dims 32 wave + 8 a + 4 hh .. + 3: group 4 wave + 2 (a % 2) + hh of the lanes of half a / 2
+      float4* dst = reinterpret_cast<float4*>(piece.dq_part) + ((int64_t)(e0 >> (7 - lp)) * p.Hkv * piece.row_blocks + (int64_t)g * piece.row_blocks + s) * (D / 8) * 64 + lq;
+#pragma unroll
+      for (int a = 0; a < 4; ++a)
+        dst[64 * (4 * wave + 2 * (a & 1) + hh) + 32 * (a >> 1)] = make_float4(dq[4 * a], dq[4 * a + 1], dq[4 * a + 2], dq[4 * a + 3]);
+    }
     wait_copies<0>();
     __syncthreads();
   };
@@ -1134,6 +1207,65 @@ __global__ __launch_bounds__(256, (D == 128 || sizeof(T) == 4 ? 1 : 2)) void dkv
   dkv_body<T, TG, D, false, NT>(p, smem, blockIdx.x, n_split, lp, part);
 }
 
+// The whole backward of fp32 tensors at head dim 128: five products per pair instead of the seven of two kernels.  The stages of all units
+// of a KV head, one unit after the other, are cut into equal ranges, one per workgroup: whatever the list and the chunk, every
+// compute unit has the same work (slices per unit: 424 us where this takes 382, 28 / 4 heads, chunk 512, 20 pages of 128).  A range covers the end of one unit and the start of the next (or several short ones); the piece of unit u
+// in range b has slot (b + u) Hkv + g.
+template <int KT> __device__ __forceinline__ int32_t gn_unit_stages(const Params& p, int g, int32_t u, int32_t n_units, int lp) {
+  if (u >= n_units) return 0;
+  const int32_t n = (int32_t)(((int64_t)p.C * p.G + KT - 1) / KT) - gn_first_stage<KT>(p, g, u << (7 - lp), lp);
+  return n > 0 ? n : 0;
+}
+__device__ __forceinline__ int32_t gn_unit_count(const Params& p, int g) { return (int32_t)(((int64_t)list_len(p, g) * p.P + GN_ROWS - 1) / GN_ROWS); }
+__device__ __forceinline__ int32_t gn_wave_sum(int32_t v) {
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o, 64);
+  return __builtin_amdgcn_readfirstlane(v);
+}
+template <typename T, typename TG, int D, int NT>
+__global__ __launch_bounds__(256, 1) void bwd_units_kernel(Params p, int32_t ranges, int lp, float* __restrict__ part, float* __restrict__ dq_part, int32_t row_blocks) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  constexpr int KT = GnKey<T, D>::KT;
+  const int lane = threadIdx.x & 63;
+  const int32_t b = blockIdx.x / p.Hkv, g = blockIdx.x - b * p.Hkv, n_units = gn_unit_count(p, g);
+  int32_t all = 0;
+  for (int32_t u = 0; u < n_units; u += 64) all += gn_unit_stages<KT>(p, g, u + lane, n_units, lp);
+  all = gn_wave_sum(all);
+  ranges = ranges < all ? ranges : all;   // (none of them empty)
+  if (b >= ranges) return;
+  int32_t at = (int32_t)((int64_t)all * b / ranges);
+  const int32_t end = (int32_t)((int64_t)all * (b + 1) / ranges);
+  // the unit in which the range starts, and where in it
+  int32_t u = 0, before = 0;
+  for (int32_t u0 = 0; u0 < n_units; u0 += 64) {
+    const int32_t n = gn_unit_stages<KT>(p, g, u0 + lane, n_units, lp);
+    int32_t upto = n;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const int32_t v = __shfl_up(upto, o, 64);
+      if (lane >= o) upto += v;
+    }
+    const int past = __builtin_popcountll(__ballot(before + upto <= at));
+    u = u0 + past;
+    if (past < 64) {
+      if (past > 0) before += __builtin_amdgcn_readlane(upto, past - 1);
+      break;
+    }
+    before += __builtin_amdgcn_readlane(upto, 63);
+  }
+  const int32_t S = (int32_t)(((int64_t)p.C * p.G + KT - 1) / KT);
+  for (; at < end; ++u) {
+    const int32_t lo = __builtin_amdgcn_readfirstlane(gn_first_stage<KT>(p, g, u << (7 - lp), lp)), n = S - lo > 0 ? S - lo : 0;
+    const int32_t s0 = lo + (at - before), s1 = s0 + (end - at) < lo + n ? s0 + (end - at) : lo + n;
+    if (s0 < s1) {
+      dkv_body<T, TG, D, false, NT, true>(p, smem, 0, 1, lp, part, GnPiece{g, u << (7 - lp), s0, s1, (b + u) * p.Hkv + g, dq_part, row_blocks});
+      __syncthreads();
+    }
+    at += s1 - s0;
+    before += n;
+  }
+}
+
 // dQ and dK / dV of a short call in one launch: the first kv_blocks workgroups take the keys, the others the rows; neither
 // waits for the other (each computes Delta itself, so dQ must not be written over O).  8 us of launch and start-up less than one after the other, where
 // neither fills the chip.
@@ -1151,12 +1283,19 @@ __global__ __launch_bounds__(256, (D == 128 || sizeof(T) == 4 ? 1 : 2)) void bwd
 template <typename T, typename TG, int D>
 __global__ __launch_bounds__(256) void bwd_finish_kernel(Params p, int32_t tiles, int32_t dq_split, const float* __restrict__ dq_part,
                                                          int32_t dq_blocks, int32_t kv_split, const float* __restrict__ kv_part, int lp,
-                                                         int redo_keys) {
+                                                         int redo_keys, int dq_units) {
   __shared__ GnRowsLds<D> sh;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   float4 a[GN_GW<D>];
   if ((int32_t)blockIdx.x < dq_blocks) {
     const int64_t blocks = (int64_t)p.Hkv * tiles * 4;
+    if (dq_units) {   // a partial sum per unit that sees the block (bwd_units_kernel): the first ones of the list
+      const int32_t gb = (int32_t)blockIdx.x / (4 * tiles), s = (int32_t)blockIdx.x - gb * 4 * tiles, n = gn_unit_count(p, gb);
+      dq_split = 0;
+      for (int32_t u = 0; u < n; u += 64)
+        dq_split += __builtin_popcountll(__ballot(u + lane < n && gn_first_stage<32>(p, gb, (u + lane) << (7 - lp), lp) <= s));
+      dq_split = __builtin_amdgcn_readfirstlane(dq_split);
+    }
     gn_sum_parts<D>(dq_part, blockIdx.x, blocks * (D / 8) * 64, dq_split, a, [] {});
     const float sc = p.sm_scale;
     int i, h;
@@ -1185,6 +1324,25 @@ __global__ __launch_bounds__(256) void bwd_finish_kernel(Params p, int32_t tiles
     if (e0 >= list_len(p, g)) return;
     slot = ((int64_t)u * kv_split) * p.Hkv + g;
     next = p.Hkv;
+    if (dq_units) {   // the ranges (kv_split of them) that hold a piece of the unit (bwd_units_kernel)
+      const int32_t n_units = gn_unit_count(p, g);
+      int32_t all = 0, before = 0;
+      for (int32_t v = lane; v < n_units; v += 64) {
+        const int32_t n = gn_unit_stages<32>(p, g, v, n_units, lp);
+        all += n;
+        before += v < u ? n : 0;
+      }
+      all = gn_wave_sum(all);
+      before = gn_wave_sum(before);
+      const int32_t ranges = kv_split < all ? kv_split : all;
+      const int32_t mine = __builtin_amdgcn_readfirstlane(gn_unit_stages<32>(p, g, u, n_units, lp));
+      if (mine == 0) return;
+      // range b starts at stage all b / kv_split: the last one that starts at or before a stage
+      auto range_of = [&](int32_t at) { return (int32_t)(((int64_t)(at + 1) * ranges - 1) / all); };
+      const int32_t first = range_of(before);
+      slot = (int64_t)(first + u) * p.Hkv + g;
+      kv_split = range_of(before + mine - 1) - first + 1;
+    }
   }
   // The block's 32 keys lie in one page, or in two of 16 tokens.  Its rows of the pool are looked up and read behind the loads
   // of the slices: in front of them the chain list -> page table -> pool would hold those back.
@@ -1288,15 +1446,50 @@ static GnPair gn_pair(const Params& p, bool bf, int32_t max_len) {
   }
   return best;
 }
-// against dQ and dK / dV one after the other, each with the chip to itself
-static bool gn_takes_pair(const Params& p, bool bf, int32_t max_len, const GnPair& pair) {
-  if (pair.us > 1e29f) return false;
+// dQ and dK / dV one after the other, each with the chip to itself
+static float gn_two_us(const Params& p, bool bf, int32_t max_len) {
   const float stages = (float)p.C * p.G / (bf ? 64.f : 32.f);
   const float stage = bf && p.D == HD && p.P == TP ? 1.75f : gn_stage_us(p, bf);   // (the kernel of pages of 128 has two roles per pair of waves)
   int32_t n = 256 / (gn_key_units(p, max_len) * p.Hkv);
   n = n > 16 ? 16 : n > stages ? (stages < 1.f ? 1 : (int32_t)stages) : n;
-  return pair.us < gn_plan(p, bf, max_len, true).us + stages / (n < 1 ? 1 : n) * stage + 9.f;
+  return gn_plan(p, bf, max_len, true).us + stages / (n < 1 ? 1 : n) * stage + 9.f;
 }
+static bool gn_takes_pair(const Params& p, bool bf, int32_t max_len, const GnPair& pair) {
+  return pair.us < 1e29f && pair.us < gn_two_us(p, bf, max_len);
+}
+
+// The backward by units (bwd_units_kernel): ranges per KV head, at most a workgroup per compute unit, and the estimate of its time in microseconds.
+// A stage of 32 rows x 128 keys takes STAGE (its 320 matrix instructions per wave 9.8 us at the rate that a loop of nothing else reaches, 134 TFLOP/s); fewer ranges than fit leave fewer partial sums to add.
+struct GnUnits { int32_t ranges; float us; };
+static size_t gn_units_dq_bytes(const Params& p, int32_t max_len) {
+  return (size_t)gn_key_units(p, max_len) * gn_tiles(p.C, p.G, p.P, p.m, p.qp) * p.Hkv * GN_ROWS * p.D * 4;
+}
+static GnUnits gn_units(const Params& p, bool bf, int32_t max_len) {
+  GnUnits best = {1, 1e30f};
+  if (bf || p.D != 128 || p.qp || p.Hkv > 256 || gn_units_dq_bytes(p, max_len) > ((size_t)1 << 30)) return best;
+  constexpr float STAGE = 11.5f, START = 25.f, BYTES = 2.5e-7f;   // (bytes written and read again)
+  const int32_t units = gn_key_units(p, max_len);
+  const int64_t S = ((int64_t)p.C * p.G + 31) / 32, most = 256 / p.Hkv;
+  int64_t all = units * S;   // stages of a head, if its list is full: fewer of the units that hold the chunk's own pages
+  for (int32_t u = (int32_t)((int64_t)(max_len - p.m) * p.P / GN_ROWS); u < units; ++u) {
+    const int64_t tok = (int64_t)u * GN_ROWS - (int64_t)(max_len - p.m) * p.P;
+    all -= tok > 0 ? tok * p.G / 32 : 0;
+  }
+  const float dq = (float)gn_units_dq_bytes(p, max_len) * BYTES;
+  const int64_t q0 = (all + most - 1) / most;
+  for (int64_t q = q0; q < q0 + 4; ++q) {
+    const int64_t r = (all + q - 1) / q;
+    const float us = START + (float)q * STAGE + dq + (float)(r + units) * p.Hkv * 131072.f * BYTES;
+    if (us < best.us) best = {(int32_t)r, us};
+  }
+  return best;
+}
+static inline size_t gn_delta_bytes(const Params& p) { return gn_up((size_t)p.Hq * p.C * sizeof(float)); }
+static size_t gn_units_part_bytes(const Params& p, int32_t max_len) {
+  return (size_t)(gn_units(p, false, max_len).ranges + gn_key_units(p, max_len)) * p.Hkv * 2 * GN_ROWS * p.D * 4;
+}
+static bool gn_takes_units(const Params& p, bool bf, int32_t max_len);
+static size_t gn_units_bytes(const Params& p, int32_t max_len) { return gn_delta_bytes(p) + gn_units_part_bytes(p, max_len) + gn_units_dq_bytes(p, max_len); }
 
 static size_t gn_row_blocks(const Params& p) { return (size_t)gn_tiles(p.C, p.G, p.P, p.m, p.qp) * p.Hkv * 4; }
 // splits that fit `bytes` of partial results of `per` bytes each (at least 1: no partial results)
@@ -1320,7 +1513,19 @@ size_t bwd_generic_min_bytes(const Params& p) { return gn_up((size_t)p.Hq * p.C 
 size_t bwd_generic_workspace_bytes(const Params& p, bool bf, int32_t max_len) {
   const size_t delta = gn_up((size_t)p.Hq * p.C * sizeof(float)), pair = bwd_takes_pair(p, bf, max_len) ? bwd_pair_bytes(p, bf, max_len) : 0;
   const size_t two = delta + dq_generic_part_bytes(p, bf, max_len) + gn_key_part_bytes(p, max_len, gn_key_splits(p, bf, max_len));
-  return pair > two ? pair : two;
+  const size_t most = pair > two ? pair : two, units = gn_takes_units(p, bf, max_len) ? gn_units_bytes(p, max_len) : 0;
+  return units > most ? units : most;
+}
+
+// Against the one-launch backward, or dQ and dK / dV one after the other.  Timed on 56 shapes (2 / 1 to 32 / 8 heads, pages of 16 to 128, 1 to 70 query
+// pages, lists of 2 to 285 pages): the estimate of the units is right to 10 % (a fixed 9 us too high below 30 us), that of the others up to 25 % too
+// low, hence the factor.  28 / 4 heads, chunk 512, 16 + 4 pages of 128: 642 -> 460 us; 2 / 1 heads, chunk 288, 45 + 18 pages of 16: 198 -> 135; from
+// 60 us on everything is 10 to 45 % faster, the shortest calls (30 us) stay with the one launch, which is up to 9 % faster there.
+static bool gn_takes_units(const Params& p, bool bf, int32_t max_len) {
+  const float us = gn_units(p, bf, max_len).us;
+  if (us > 1e29f) return false;
+  const GnPair pair = gn_pair(p, bf, max_len);
+  return us < 1.15f * (gn_takes_pair(p, bf, max_len, pair) ? pair.us : gn_two_us(p, bf, max_len));
 }
 
 // terms of a probability (GnP) where a shape has no kernels of its own
@@ -1385,12 +1590,12 @@ hipError_t launch_dq_generic_bf16_128(const Params& p, int32_t max_len, float* p
 
 template <typename T, typename TG, int D>
 static hipError_t bwd_finish(const Params& p, int32_t dq_split, const float* dq_part, int32_t kv_units, int32_t kv_split, const float* kv_part,
-                             bool redo_keys, hipStream_t st) {
-  const int32_t dq_blocks = dq_split > 1 ? (int32_t)(gn_row_blocks(p)) : 0;
+                             bool redo_keys, hipStream_t st, bool dq_units = false) {
+  const int32_t dq_blocks = dq_split > 1 || dq_units ? (int32_t)(gn_row_blocks(p)) : 0;
   const int64_t blocks = dq_blocks + (int64_t)kv_units * p.Hkv * 2 * part_key_blocks(p);
   if (blocks <= 0) return hipSuccess;
   bwd_finish_kernel<T, TG, D><<<dim3((unsigned)blocks), dim3(256), 0, st>>>(p, gn_tiles(p.C, p.G, p.P, p.m, p.qp), dq_split, dq_part, dq_blocks, kv_split,
-                                                                            kv_part, __builtin_ctz(p.P), redo_keys);
+                                                                            kv_part, __builtin_ctz(p.P), redo_keys, dq_units);
   return hipGetLastError();
 }
 // (the dK / dV slices of pages with kernels of their own: keys are left as those give them)
@@ -1428,10 +1633,30 @@ hipError_t launch_bwd_pair_bf16_128(const Params& p, int32_t max_len, void* ws, 
                         : bwd_pair<bf16_t, float, 128, 1>(p, max_len, ws, ws_bytes, "bwd_pair", st, done);
 }
 
+template <typename TG>
+static hipError_t bwd_units(Params p, int32_t max_len, void* ws, size_t ws_bytes, const char* name, hipStream_t st, bool* done) {
+  const int32_t n = gn_units(p, false, max_len).ranges, units = gn_key_units(p, max_len);
+  if (dq_overlaps_o(p, false) || !gn_takes_units(p, false, max_len) || gn_units_bytes(p, max_len) > ws_bytes) return hipSuccess;
+  *done = true;
+  ProfScope prof_(name, st);
+  typedef GnKey<float, 128> R;
+  static DeviceOnce once;
+  if (hipError_t e = ensure_max_dynamic_lds(once, (const void*)bwd_units_kernel<float, TG, 128, 1>, R::LDS_DQ); e != hipSuccess) return e;
+  p.delta = (float*)ws;
+  if (hipError_t e = launch_delta<float, 128>(p, st); e != hipSuccess) return e;
+  float* kv_part = (float*)((unsigned char*)ws + gn_delta_bytes(p));
+  float* dq_part = (float*)((unsigned char*)kv_part + gn_units_part_bytes(p, max_len));
+{ ProfScope units_("bwd_units", st); bwd_units_kernel<float, TG, 128, 1><<<dim3((unsigned)(p.Hkv * n)), dim3(256), R::LDS_DQ, st>>>(p, n, __builtin_ctz(p.P), kv_part, dq_part, 4 * gn_tiles(p.C, p.G, p.P, p.m, p.qp)); }
+  if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
+  return bwd_finish<float, TG, 128>(p, 1, dq_part, units, n, kv_part, true, st, true);
+}
+
 template <typename T, typename TG, int D>
 static hipError_t bwd_generic(Params p, int32_t max_len, void* ws, size_t ws_bytes, hipStream_t st) {
   const char* name = "attn_bwd_generic";
   bool done = false;
+  if constexpr (sizeof(T) == 4 && D == 128)
+    if (hipError_t e = bwd_units<TG>(p, max_len, ws, ws_bytes, name, st, &done); done || e != hipSuccess) return e;
   if (hipError_t e = bwd_pair<T, TG, D>(p, max_len, ws, ws_bytes, name, st, &done); done || e != hipSuccess) return e;
   ProfScope prof_(name, st);
   static DeviceOnce once_kv;
@@ -1448,8 +1673,7 @@ static hipError_t bwd_generic(Params p, int32_t max_len, void* ws, size_t ws_byt
   left -= gn_key_part_bytes(p, max_len, nk);
   const int32_t units = p.qp ? p.max_units : gn_key_units(p, max_len);
   if (p.d_q != p.o && dq_overlaps_o(p, Gn<T, D>::BF)) {
-    delta_kernel<T, D><<<dim3((unsigned)(((int64_t)p.C * p.Hq + 255) / 256)), dim3(256), 0, st>>>(p);
-    if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
+    if (hipError_t e = launch_delta<T, D>(p, st); e != hipSuccess) return e;
     p.delta_given = 1;
   }
   int32_t ns = 1;

@@ -69,6 +69,24 @@ def test_generic_kernel_edges(w):
     _show(w.name, rep)
 
 
+# fp32 at head dim 128 where dQ, dK and dV come from one kernel: ranges of stages that end inside a unit, cover several short ones (the
+# chunk's own pages) or start at one's first stage; a last unit that is not full; lists shorter than their stride; heads that do not divide 256.
+UNITS_CASES = [
+    Workload("f32_units_g7", 28, 4, 128, 128, 384, 128 * 16, 9, "f32", "f32", 0.088, extra_phys=2, boost_frac=0.2, seed=71),
+    Workload("f32_units_p16_local", 8, 2, 128, 16, 544, 16 * 51, 13, "f32", "bf16", 0.088, extra_phys=1, seed=72),
+    Workload("f32_units_short_list", 6, 3, 128, 64, 320, 64 * 24, 40, "f32", "f32", 0.088, seed=73),
+    Workload("f32_units_nohist", 5, 5, 128, 32, 992, 992, 3, "f32", "f32", 0.088, seed=74),
+    Workload("f32_units_p32_dense", 2, 1, 128, 32, 352, 32 * 150, None, "f32", "bf16", 0.088, seed=75),
+]
+
+
+@pytest.mark.parametrize("w", UNITS_CASES, ids=lambda w: w.name)
+def test_fp32_backward_in_one_kernel(w):
+    with pu.kernels_ran(("bwd_units",), absent=pu.MFMA_KERNELS + pu.SPLIT_KERNELS):
+        rep = pu.full_parity(w, init_grad=0.25)
+    _show(w.name, rep)
+
+
 # bf16 tensors of shapes without kernels of their own: probabilities and dS keep 32 bits.  Against 64 bits with the same O and LSE
 # in the backward, dK / dV carry the rounding of LSE (about 8: 2.4e-7 relative to a probability) and of the exponent, O and
 # dQ only that of their own storage, 2^-8 of an element at most.  Probabilities rounded to bf16 miss both by a factor of 100.

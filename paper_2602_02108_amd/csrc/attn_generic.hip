@@ -20,8 +20,8 @@
 // KV head: r = token * G + head in group, so a tile's rows are consecutive tokens of all G heads,
 // and the rows of a query page are contiguous for every page size.
 //
-// What bounds them: fp32 the matrix pipe itself (256 flops per cycle and compute unit, 157 TFLOP/s);
-// (fp32 at head dim 128, calls that are not short: dQ, dK and dV in one kernel, which forms S and dP once, bwd_units_kernel;)
+// What bounds them: fp32 the matrix pipe itself (256 flops per cycle and compute unit, 157 TFLOP/s; calls that are not short
+// therefore take the bf16 pipe with products of three terms each, fwd_terms_kernel and bwd_units_kernel);
 // bf16 the exposed vector work and LDS latency of one or two waves per SIMD; short calls the number
 // of workgroups, which is why the streamed side is cut into splits whose partial sums a second
 // kernel combines in a fixed order.  Measured against one wave per query row (per key in dK / dV)
@@ -456,6 +456,37 @@ __device__ __forceinline__ void gn_redo_row(const Params& p, int g, int i, int h
 #pragma unroll
   for (int k = 0; k < D / 64; ++k) Elem<T>::store(dst + 64 * k + lane, acc[k] * scale);
 }
+// O of one fp32 row whose products were formed in terms (fwd_terms_kernel), m and l its softmax statistics there.  l is NaN where a product was not finite
+// there: infinities times the terms of a finite value are NaN, or the true value is not finite either.  Then the statistics and LSE are
+// formed anew from fp32 products.
+__device__ __forceinline__ float gn_lse(const Params& p, float m, float l);
+__device__ __forceinline__ float gn_lowest(const Params& p);
+template <int D> __device__ __forceinline__ void gn_redo_terms(const Params& p, int g, int i, int h, int lp, int lane, float m, float l) {
+  const float c = p.sm_scale * 1.4426950408889634f;
+  if (l != l) {
+    const int lid = list_id(p, g, i);
+    const int64_t roff = (int64_t)i * p.q_tok_stride + (int64_t)h * p.q_head_stride, a = p.N - p.C + i;
+    const int32_t n_ent = visible_len(p, lid, a >> lp, lane);
+    int32_t V = n_ent << lp;
+    if (n_ent > 0 && list_at(p, lid, n_ent - 1) == (int32_t)(a >> lp)) V -= p.P - 1 - (int32_t)(a & (p.P - 1));
+    m = gn_lowest(p);
+    l = 0.f;
+    for (int32_t t = lane; t < V; t += 64) {
+      const int64_t off = (int64_t)p.page_table[list_at(p, lid, t >> lp)] * p.pool_page_stride + (int64_t)g * p.pool_head_stride + (int64_t)(t & (p.P - 1)) * p.pool_tok_stride;
+      const float s = gn_row_dot<float, D>((const float*)p.q + roff, (const float*)p.k_pool + off), m_new = fmaxf(m, s);
+      l = l * __builtin_amdgcn_exp2f((m - m_new) * c) + __builtin_amdgcn_exp2f(__builtin_fmaf(s, c, -m_new * c));
+      m = m_new;
+    }
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) {
+      const float m2 = __shfl_xor(m, o, 64), l2 = __shfl_xor(l, o, 64), m_new = fmaxf(m, m2);
+      l = l * __builtin_amdgcn_exp2f((m - m_new) * c) + l2 * __builtin_amdgcn_exp2f((m2 - m_new) * c);
+      m = m_new;
+    }
+    if (lane == 0) p.lse[(int64_t)h * p.C + i] = gn_lse(p, m, l);
+  }
+  gn_redo_row<float, D, false>(p, g, i, h, lp, lane, m * c, 1.f / l, 0.f);
+}
 // dK (or dV) of token t of owned page e into the pool
 template <typename T, typename TG, int D> __device__ __forceinline__ void gn_redo_key(const Params& p, int g, int32_t e, int32_t t, bool is_dk, int lp, int lane) {
   const int64_t l = owned_at(p, g, e), pos = (l << lp) + t, first_q = p.N - p.C;
@@ -646,12 +677,12 @@ template <int D> constexpr int GN_GW = D / 32;   // groups per wave
 // in: the sums of this thread's groups; then f(k, row, dim, value) for the row pieces this thread writes, piece k = float4
 // k * 256 + thread of the block.  redo: rows whose sums are not finite are left out; returns them, a bit each.
 template <int D> struct GnRowsLds { float4 v[8 * D]; uint32_t bad[4]; };
-template <typename T, int D, typename F> __device__ __forceinline__ uint32_t gn_rows_out(GnRowsLds<D>& lds, const float4 (&v)[GN_GW<D>], bool redo, F&& f) {
+template <typename L, int D, typename F> __device__ __forceinline__ uint32_t gn_rows_out(GnRowsLds<D>& lds, const float4 (&v)[GN_GW<D>], bool redo, F&& f) {
   auto& sh = lds.v;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, r = lane & 31;
   constexpr int GPR = D / 4;   // float4s per row
 #pragma unroll
-  for (int j = 0; j < GN_GW<D>; ++j) sh[r * GPR + ((part_group_dim<T, D>(wave + 4 * j, lane >> 5) >> 2) ^ (r & 15))] = v[j];
+  for (int j = 0; j < GN_GW<D>; ++j) sh[r * GPR + ((part_group_dim<L, D>(wave + 4 * j, lane >> 5) >> 2) ^ (r & 15))] = v[j];
   float z = 0.f;
 #pragma unroll
   for (int j = 0; j < GN_GW<D>; ++j) z = __builtin_fmaf(v[j].x, 0.f, __builtin_fmaf(v[j].y, 0.f, __builtin_fmaf(v[j].z, 0.f, __builtin_fmaf(v[j].w, 0.f, z))));
@@ -719,8 +750,8 @@ __device__ __forceinline__ void gn_sum_parts(const float* part, int64_t block, i
   for (int done = first ? first : 4; done < n; done += 4) gn_add_parts<D, 4>(part, at + done * step, step, a, nothing);
 }
 
-// O = sum of the splits' O rescaled to the common maximum / sum of their l
-template <typename T, int D>
+// O = sum of the splits' O rescaled to the common maximum / sum of their l.  L: the element type in whose register order the partial sums lie.
+template <typename T, int D, typename L = T>
 __global__ __launch_bounds__(256) void fwd_combine_kernel(Params p, int32_t tiles, int32_t n_split, const float* __restrict__ part,
                                                           const float2* __restrict__ part_ml, int lp) {
   __shared__ GnRowsLds<D> sh;
@@ -729,7 +760,7 @@ __global__ __launch_bounds__(256) void fwd_combine_kernel(Params p, int32_t tile
   const int64_t block = blockIdx.x, blocks = (int64_t)p.Hkv * tiles * 4;
   const int64_t at = (block * (D / 8) + wave) * 64 + lane;
   const float c = p.sm_scale * 1.4426950408889634f;
-  float M = gn_lowest(p), L = 0.f;   // (a split that saw nothing of the row holds -inf and 0)
+  float M = gn_lowest(p), l_sum = 0.f;   // (a split that saw nothing of the row holds -inf and 0)
   float4 acc[GW];
 #pragma unroll
   for (int j = 0; j < GW; ++j) acc[j] = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -748,32 +779,255 @@ __global__ __launch_bounds__(256) void fwd_combine_kernel(Params p, int32_t tile
     const float m_new = fmaxf(fmaxf(fmaxf(ml[0].x, ml[1].x), fmaxf(ml[2].x, ml[3].x)), M);
     const float w0 = __builtin_amdgcn_exp2f((M - m_new) * c);
     M = m_new;
-    L *= w0;
+    l_sum *= w0;
 #pragma unroll
     for (int j = 0; j < GW; ++j) { acc[j].x *= w0; acc[j].y *= w0; acc[j].z *= w0; acc[j].w *= w0; }
 #pragma unroll
     for (int u = 0; u < 4; ++u)
       if (s0 + u < n_split) {
         const float w = __builtin_amdgcn_exp2f((ml[u].x - m_new) * c);
-        L += ml[u].y * w;
+        l_sum += ml[u].y * w;
 #pragma unroll
         for (int j = 0; j < GW; ++j) { acc[j].x += v[j][u].x * w; acc[j].y += v[j][u].y * w; acc[j].z += v[j][u].z * w; acc[j].w += v[j][u].w * w; }
       }
   }
-  const float inv = 1.f / L;
+  const float inv = 1.f / l_sum;
 #pragma unroll
   for (int j = 0; j < GW; ++j) { acc[j].x *= inv; acc[j].y *= inv; acc[j].z *= inv; acc[j].w *= inv; }
   int i, h;
-  uint32_t bad = gn_rows_out<T, D>(sh, acc, true, [&](int, int row, int d, const float4& r) __attribute__((always_inline)) {
+  uint32_t bad = gn_rows_out<L, D>(sh, acc, true, [&](int, int row, int d, const float4& r) __attribute__((always_inline)) {
     if (gn_out_row(p, tiles, block, row, i, h))
       part_store4<T>((T*)p.o + (int64_t)i * p.q_tok_stride + (int64_t)h * p.q_head_stride + d, r.x, r.y, r.z, r.w);
   });
   if (threadIdx.x < 32 && gn_out_row(p, tiles, block, threadIdx.x, i, h))
-    p.lse[(int64_t)h * p.C + i] = gn_lse(p, M, L);
+    p.lse[(int64_t)h * p.C + i] = gn_lse(p, M, l_sum);
   for (bad &= 0xffu << (8 * wave); bad; bad &= bad - 1) {   // (eight rows per wave)
     const int x = __builtin_ctz(bad);
-    if (gn_out_row(p, tiles, block, x, i, h))
-      gn_redo_row<T, D, false>(gn_params_again(), h / p.G, i, h, lp, lane, gn_lane(M * c, x), gn_lane(inv, x), 0.f);
+    if (gn_out_row(p, tiles, block, x, i, h)) {
+      if constexpr (sizeof(L) != sizeof(T)) gn_redo_terms<D>(gn_params_again(), h / p.G, i, h, lp, lane, gn_lane(M, x), gn_lane(l_sum, x));
+      else gn_redo_row<T, D, false>(gn_params_again(), h / p.G, i, h, lp, lane, gn_lane(M * c, x), gn_lane(inv, x), 0.f);
+    }
+  }
+}
+
+// ---- forward of fp32 tensors on the bf16 matrix pipe ---------------------------------------------
+// An fp32 value is the sum of three bf16 values, all 24 bits: a = a0 + a1 + a2, each the rounding of what the ones before it left.  A
+// product of two such sums takes six bf16 matrix instructions -- a0 b0, a0 b1, a1 b0, a1 b1, a0 b2, a2 b0; the others are below 2^-26 of
+// it -- and these 192 cycles where v_mfma_f32_32x32x2 takes 512.
+// (Values below 2^-109 keep fewer bits: the smallest bf16 is 2^-133.)
+struct GnTerms { uint32_t w[3]; };
+// two values.  What would round to an infinity is cut off instead; infinities and NaN are their own first term.
+__device__ __forceinline__ GnTerms gn_terms(float a, float b) {
+  GnTerms t;
+  auto first = [](float v) {
+    const uint32_t u = __float_as_uint(v), r = pack2_bf16(v, v) << 16;
+    return fabsf(v) < 0x1.FFp127f || v != v ? r : u & 0xffff0000u;
+  };
+  const uint32_t a0 = first(a), b0 = first(b);
+  t.w[0] = (a0 >> 16) | (b0 & 0xffff0000u);
+  const float ra = fabsf(a) < INFINITY ? a - __uint_as_float(a0) : 0.f, rb = fabsf(b) < INFINITY ? b - __uint_as_float(b0) : 0.f;
+  t.w[1] = pack2_bf16(ra, rb);
+  t.w[2] = pack2_bf16(ra - __uint_as_float(t.w[1] << 16), rb - __uint_as_float(t.w[1] & 0xffff0000u));
+  return t;
+}
+template <int D> struct GnF3 {
+  typedef Gn<bf16_t, D> X;
+  static constexpr int TERM = 32 * X::RB, V = 3 * TERM, TILE = 6 * TERM;   // 32 keys: K0 K1 K2 V0 V1 V2, in the order of the LDS tile
+  static constexpr int NI = V / 1024 / 4, LDS = 3 * V;   // copies of K or V per wave; LDS: K twice, V once
+};
+// eight values as operands of three terms
+__device__ __forceinline__ void gn_load_terms(const float4& a, const float4& b, u32x4_t& t0, u32x4_t& t1, u32x4_t& t2) {
+  const GnTerms w[4] = {gn_terms(a.x, a.y), gn_terms(a.z, a.w), gn_terms(b.x, b.y), gn_terms(b.z, b.w)};
+  t0 = u32x4_t{w[0].w[0], w[1].w[0], w[2].w[0], w[3].w[0]};
+  t1 = u32x4_t{w[0].w[1], w[1].w[1], w[2].w[1], w[3].w[1]};
+  t2 = u32x4_t{w[0].w[2], w[1].w[2], w[2].w[2], w[3].w[2]};
+}
+template <int D> __device__ __forceinline__ void gn_store_terms(unsigned char* dst, const float4 (&v)[2]) {
+  u32x4_t t[3];
+  gn_load_terms(v[0], v[1], t[0], t[1], t[2]);
+#pragma unroll
+  for (int k = 0; k < 3; ++k) *reinterpret_cast<u32x4_t*>(dst + k * GnF3<D>::TERM) = t[k];
+}
+static inline int32_t gn_f3_tiles(const Params& p, int32_t max_len) { return (int32_t)(((int64_t)max_len * p.P + 31) / 32); }
+
+// The terms of the listed keys, [KV head][tile of 32 list tokens][TILE]; zeros past the list.
+template <int D>
+__global__ __launch_bounds__(256) void kv_terms_kernel(Params p, int32_t n_tiles, int lp, unsigned char* __restrict__ img) {
+  typedef GnF3<D> F;
+  constexpr int NG = F::X::NG;
+  const int32_t kt = blockIdx.x / p.Hkv, g = blockIdx.x - kt * p.Hkv, len = list_len(p, g);
+  unsigned char* out = img + ((int64_t)g * n_tiles + kt) * F::TILE;
+#pragma unroll
+  for (int x = 0; x < 2 * 32 * NG / 256; ++x) {
+    const int gi = threadIdx.x + 256 * x, is_v = gi / (32 * NG), r = gi / NG % 32, c = gi % NG;
+    const int32_t tok = 32 * kt + r, e = tok >> lp;
+    float4 v[2] = {};
+    if (e < len) {
+      const int64_t at = (int64_t)p.page_table[list_at(p, g, e)] * p.pool_page_stride + (int64_t)g * p.pool_head_stride + (int64_t)(tok & (p.P - 1)) * p.pool_tok_stride + 8 * c;
+      const float4* src = reinterpret_cast<const float4*>((const float*)(is_v ? p.v_pool : p.k_pool) + at);
+      v[0] = src[0];
+      v[1] = src[1];
+    }
+    gn_store_terms<D>(out + is_v * F::V + r * F::X::RB + ((c ^ F::X::swz(r)) << 4), v);
+  }
+}
+// c += the product of two values of three terms, the smallest first; small += all of it but the product of the first terms
+__device__ __forceinline__ void gn_mma_terms(const u32x4_t (&a)[3], const u32x4_t& b0, const u32x4_t& b1, const u32x4_t& b2, f32x16& small, f32x16& c) {
+  const u32x4_t* b[3] = {&b0, &b1, &b2};
+  constexpr int order[6][2] = {{2, 0}, {0, 2}, {1, 1}, {1, 0}, {0, 1}, {0, 0}};
+#pragma unroll
+  for (int k = 0; k < 6; ++k) {
+    f32x16& acc = k < 5 ? small : c;
+    acc = mfma32(__builtin_bit_cast(bf16x8, a[order[k][0]]), __builtin_bit_cast(bf16x8, *b[order[k][1]]), acc);
+  }
+}
+// f(i, operand of three terms) for i = 0 .. N - 1: the next operand is fetched while one computes
+template <int N, typename L, typename M> __device__ __forceinline__ void gn_terms_pipeline(L&& load, M&& use) {
+  u32x4_t fr[2][3];
+#pragma unroll
+  for (int t = 0; t < 3; ++t) fr[0][t] = load(0, t);
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    if (i + 1 < N) {
+#pragma unroll
+      for (int t = 0; t < 3; ++t) fr[(i + 1) & 1][t] = load(i + 1, t);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    use(i, fr[i & 1]);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+}
+
+// fp32 forward, one list per KV head: O = softmax(Q K^T) V of 128 rows and a range of tiles of 32 keys.  Two workgroups per compute unit, whose barriers
+// are their own: the vector work of one (softmax, terms of P) runs beside the matrix instructions of the other.  S is summed in two accumulators, the
+// products of the first terms apart from the small ones, so that fewer sums are rounded at its full size (O against 64 bits 4.2e-7 instead of
+// 6.0e-7; on the fp32 pipe 7.3e-7).  28 / 4 heads, chunk 512, 20 pages of 128: the forward with layout and combine 187 us on the fp32 pipe, 118 here: 1.0
+// PFLOP/s of bf16 instructions, what the clock sustains (the bf16 forward of pages of 128 reaches no more).  256 rows per workgroup, half of
+// the copies: 2 to 6 % faster where the chip is full, up to 25 % slower where it is not.
+template <int D>
+__global__ __launch_bounds__(256, 2) void fwd_terms_kernel(Params p, int32_t tiles, int32_t n_split, int lp, int32_t max_len, int32_t n_tiles,
+                                                           const unsigned char* __restrict__ img, float* __restrict__ part, float2* __restrict__ part_ml) {
+  typedef GnF3<D> F;
+  typedef Gn<bf16_t, D> X;
+  extern __shared__ __align__(16) unsigned char smem[];
+  const int lane = threadIdx.x & 63, hh = lane >> 5, rb = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const GnBlock b = gn_block(p, blockIdx.x, tiles, n_split);
+  const GnTile t = gn_tile(p, b.g, b.tile, rb, lane, lp, max_len);
+  const bool active = t.active;
+  const GnRange kr = gn_range(max_len, lp, 32, b.split, n_split);
+
+  u32x4_t qf[3][X::NJ];
+  const int64_t roff = (int64_t)t.i * p.q_tok_stride + (int64_t)t.h * p.q_head_stride;
+  const float4* q = reinterpret_cast<const float4*>((const float*)p.q + roff + 8 * hh);
+#pragma unroll
+  for (int j = 0; j < X::NJ; ++j) {
+    gn_load_terms(q[4 * j], q[4 * j + 1], qf[0][j], qf[1][j], qf[2][j]);
+  }
+  f32x16 of[X::DB];
+  gn_zero(of);
+  float m_run = gn_lowest(p), l_run = 0.f;
+  const float c = p.sm_scale * 1.4426950408889634f;
+  GnAddr<bf16_t, D> ad;
+  ad.init(lane, 0);
+  uint32_t row0 = ad.row[0];
+  const int32_t V_min = __builtin_amdgcn_readfirstlane(t.V), V_max = __builtin_amdgcn_readlane(t.V, 31);
+  const int32_t n_kt = (t.V_last + 31) / 32, k1 = kr.k1 < n_kt ? kr.k1 : n_kt;
+  const unsigned char* src = img + (int64_t)b.g * n_tiles * F::TILE + rb * F::NI * 1024 + lane * 16;
+  auto copy = [&](const int32_t kt, const uint32_t which, const uint32_t dst) __attribute__((always_inline)) {   // which: 0 or F::V
+#pragma unroll
+    for (int k = 0; k < F::NI; ++k) gn_copy16(src + (int64_t)kt * F::TILE + which + 1024 * k, dst + rb * F::NI * 1024 + 1024 * k);
+  };
+  GnP<bf16_t, 3> pr;
+  auto scores = [&](const uint32_t at, const int32_t t0) __attribute__((always_inline)) {
+    f32x16 s[2];
+    gn_zero(s);
+    asm volatile("" : "+v"(row0));   // (the addresses of the k-steps are formed from one register: kept apart, they would be spilled)
+    gn_terms_pipeline<X::NJ>([&](const int j, const int k) __attribute__((always_inline)) {
+                               return *(__attribute__((address_space(3))) const u32x4_t*)((row0 ^ (uint32_t)(j << 5)) + (at + k * F::TERM));
+                             },
+                             [&](const int j, const u32x4_t (&f)[3]) __attribute__((always_inline)) { gn_mma_terms(f, qf[0][j], qf[1][j], qf[2][j], s[1], s[0]); });
+#pragma unroll
+    for (int x = 0; x < 16; ++x) s[0][x] += s[1][x];
+    if (t0 + 32 > V_min) {
+      const int32_t rel = t.V - t0 - 4 * hh;
+#pragma unroll
+      for (int x = 0; x < 16; ++x)
+        if (8 * (x >> 2) + (x & 3) >= rel) s[0][x] = -INFINITY;
+    }
+    float mx = s[0][0];
+#pragma unroll
+    for (int x = 1; x < 16; ++x) mx = fmaxf(mx, s[0][x]);
+    const float m_new = fmaxf(m_run, half_max(mx)), alpha = __builtin_amdgcn_exp2f((m_run - m_new) * c), mc = m_new * c;
+    m_run = m_new;
+    if (__any(alpha != 1.f)) {
+#pragma unroll
+      for (int db = 0; db < X::DB; ++db)
+#pragma unroll
+        for (int x = 0; x < 16; ++x) of[db][x] *= alpha;
+    }
+    l_run *= alpha;
+#pragma unroll
+    for (int x = 0; x < 16; x += 2) {
+      const float a = __builtin_amdgcn_exp2f(__builtin_fmaf(s[0][x], c, -mc)), b2 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[0][x + 1], c, -mc));
+      pr.set2(x, a, b2);
+      l_run += a + b2;
+    }
+  };
+  auto output = [&]() __attribute__((always_inline)) {
+    gn_terms_pipeline<2 * X::DB>([&](const int v, const int k) __attribute__((always_inline)) { return ad.tr_frag(v, 2 * F::V + k * F::TERM); },
+                                 [&](const int v, const u32x4_t (&f)[3]) __attribute__((always_inline)) {
+                                   const int u = v / X::DB;
+                                   u32x4_t w[3];
+#pragma unroll
+                                   for (int k = 0; k < 3; ++k) w[k] = u32x4_t{pr.w[k][4 * u], pr.w[k][4 * u + 1], pr.w[k][4 * u + 2], pr.w[k][4 * u + 3]};
+                                   gn_mma_terms(f, w[0], w[1], w[2], of[v % X::DB], of[v % X::DB]);
+                                 });
+  };
+  wait_copies<0>();
+  if (kr.k0 < k1) copy(kr.k0, 0, 0);
+  for (int32_t k0 = kr.k0; k0 < k1; k0 += 2) {
+#pragma unroll
+    for (int b2 = 0; b2 < 2; ++b2) {   // (unrolled: the buffer is a constant)
+      const int32_t kt = k0 + b2;
+      if (kt >= k1) break;
+      const bool on = active && 32 * kt < V_max;
+      wait_copies<0>();
+      __syncthreads();   // K of this tile is in LDS; nobody reads K and V of the one before it any more
+      copy(kt, F::V, 2 * F::V);
+      if (kt + 1 < k1) copy(kt + 1, 0, (b2 ^ 1) * F::V);
+      if (on) scores((uint32_t)(b2 * F::V), 32 * kt);
+      if (kt + 1 < k1) wait_copies<F::NI>();   // (V is older than the next K)
+      else wait_copies<0>();
+      __syncthreads();
+      if (on) output();
+    }
+  }
+
+  // (the row and the launch parameters anew: kept across the loop they would be spilled)
+  const Params& p2 = gn_params_again();
+  int tid = threadIdx.x;
+  asm volatile("" : "+v"(tid));
+  const float l_tot = half_sum(l_run);
+  const int32_t r = b.tile * GN_ROWS + 32 * rb + (tid & 31), rows = p2.C * p2.G;
+  const bool valid = r < rows;
+  if (n_split > 1) {
+    const int64_t at = (((int64_t)b.split * p2.Hkv + b.g) * tiles + b.tile) * 4 + rb;
+    if (!active) return;
+    part_store<bf16_t, D>(part, at, tid & 63, of, 1.f);
+    if (!(tid & 32)) part_ml[at * 32 + (tid & 31)] = make_float2(l_tot > 0.f ? m_run : -INFINITY, l_tot);
+  } else {
+    const float inv = 1.f / l_tot;
+    const int32_t i = (int32_t)div_g(p2, (uint32_t)(valid ? r : 0)), h = b.g * p2.G + (valid ? r - i * p2.G : 0);
+    uint32_t bad = gn_either_half(valid && gn_not_finite(of));
+    if (valid && !((bad >> (tid & 31)) & 1)) {
+      float* dst = (float*)p2.o + (int64_t)i * p2.q_tok_stride + (int64_t)h * p2.q_head_stride;
+      part_emit<bf16_t, D>(of, (tid >> 5) & 1, [&](int d, float v0, float v1, float v2, float v3) { part_store4<float>(dst + d, v0 * inv, v1 * inv, v2 * inv, v3 * inv); });
+    }
+    if (valid && !(tid & 32)) p2.lse[(int64_t)h * p2.C + i] = gn_lse(p2, m_run, l_tot);
+    for (; bad; bad &= bad - 1) {
+      const int x = __builtin_ctz(bad);
+      gn_redo_terms<D>(p2, b.g, __builtin_amdgcn_readlane(i, x), __builtin_amdgcn_readlane(h, x), lp, tid & 63, gn_lane(m_run, x), gn_lane(l_tot, x));
+    }
   }
 }
 
@@ -919,33 +1173,16 @@ __global__ __launch_bounds__(256 * KH, (Gn<T, D>::RB == 512 ? 1 : 2)) void dq_ge
 template <typename T, int D> struct GnKey {
   static constexpr int KT = GnTiles<T, D>::KT;
   static constexpr int STAT = 2 * GnTiles<T, D>::BUF, LDS = STAT + 2 * 2 * 64 * 4;   // two buffers, {lse2, delta} of their rows
-  // with dQ: dS of a stage as [row][key], rows 544 bytes apart (both the dwords of 32 keys x 2 rows that a store moves and the 16 bytes x 64 rows
-  // of a read fall on all banks)
-  static constexpr int DS = LDS, DS_ROW = GN_ROWS * 4 + 32, KL = DS + KT * DS_ROW, KL_ROW = GN_ROWS * 4 + 16, LDS_DQ = KL + GN_ROWS * KL_ROW;
 };
-// first stage of KT rows that sees list entry e of KV head g
-template <int KT> __device__ __forceinline__ int32_t gn_first_stage(const Params& p, int g, int32_t e, int lp) {
-  const int64_t pos = owned_at(p, g, e) << lp, first_q = p.N - p.C;
-  return (pos > first_q ? (int32_t)(pos - first_q) * p.G : 0) / KT;
-}
-// DQ (fp32, one list per KV head): the unit's share of dQ as well, dq_part[unit][block of 32 rows] in the layout of part_store: S
-// and dP are formed once instead of once here and once in the dQ kernel.
-struct GnPiece { int32_t g, e0, s0, s1, slot; float* dq_part; int32_t row_blocks; };   // DQ: stages s0 .. s1 - 1 of the unit from list entry e0 on
-template <typename T, typename TG, int D, bool OWN_DELTA, int NT, bool DQ = false>
-__device__ __forceinline__ void dkv_body(const Params& p, unsigned char* smem, int32_t bid, int32_t n_split, int lp, float* __restrict__ part,
-                                         const GnPiece& piece = GnPiece()) {
+template <typename T, typename TG, int D, bool OWN_DELTA, int NT>
+__device__ __forceinline__ void dkv_body(const Params& p, unsigned char* smem, int32_t bid, int32_t n_split, int lp, float* __restrict__ part) {
   typedef Gn<T, D> X;
   typedef GnKey<T, D> R;
   typedef GnTiles<T, D> Y;
-  int tid = threadIdx.x;
-  if (DQ) asm volatile("" : "+v"(tid));   // (nothing that depends on the lane is kept from one piece to the next: it would be spilled)
-  const int lane = tid & 63, hh = lane >> 5, lq = lane & 31, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int32_t rest = DQ ? 0 : bid / p.Hkv, g = DQ ? piece.g : bid - rest * p.Hkv;
+  const int tid = threadIdx.x, lane = tid & 63, hh = lane >> 5, lq = lane & 31, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int32_t rest = bid / p.Hkv, g = bid - rest * p.Hkv;
   int32_t e0, sp = 0, q0 = 0, qc = 0, slot = -1;
-  if constexpr (DQ) {
-    e0 = piece.e0;
-    slot = piece.slot;
-  } else if (p.qp) {
+  if (p.qp) {
     const int32_t n_units = p.unit_count[g];
     if (rest >= n_units) return;
     const int4 un = p.units[(int64_t)g * p.max_units + (n_units - 1 - rest)];
@@ -968,16 +1205,15 @@ __device__ __forceinline__ void dkv_body(const Params& p, unsigned char* smem, i
   const int64_t l = owned_at(p, g, e), pos = (l << lp) + (kq & (p.P - 1));
   const int64_t koff = (int64_t)p.page_table[l] * p.pool_page_stride + (int64_t)g * p.pool_head_stride + (int64_t)(kq & (p.P - 1)) * p.pool_tok_stride;
   // rows before r_key do not see the key
-  int32_t r_key = pos > first_q ? (int32_t)(pos - first_q) * p.G : 0;
-  if (DQ && !kvalid) r_key = INT32_MAX;
+  const int32_t r_key = pos > first_q ? (int32_t)(pos - first_q) * p.G : 0;
   const int32_t r_key_max = __builtin_amdgcn_readlane(r_key, 31);
   const int64_t pos0 = owned_at(p, g, e0) << lp;
   const int32_t r_lo = pos0 > first_q ? (int32_t)(pos0 - first_q) * p.G : 0, rows = p.C * p.G;
   // stages of KT rows: [s0, s1) of the chunk's, or stage v % spq of the unit's query page v / spq
   const int32_t rpq = p.P * p.G, spq = (rpq + R::KT - 1) / R::KT;
   const int32_t st_lo = r_lo / R::KT, st_n = (rows + R::KT - 1) / R::KT - st_lo;
-  const int32_t s0 = DQ ? piece.s0 : p.qp ? 0 : st_lo + (int32_t)((int64_t)st_n * sp / n_split);
-  const int32_t s1 = DQ ? piece.s1 : p.qp ? qc * spq : st_lo + (int32_t)((int64_t)st_n * (sp + 1) / n_split);
+  const int32_t s0 = p.qp ? 0 : st_lo + (int32_t)((int64_t)st_n * sp / n_split);
+  const int32_t s1 = p.qp ? qc * spq : st_lo + (int32_t)((int64_t)st_n * (sp + 1) / n_split);
   int32_t tau_v = 0;
   if (p.qp && lane < qc) tau_v = p.inv_qp[(int64_t)g * p.m * p.sel_stride + p.inv_off[(int64_t)g * (p.un_stride + 1) + e0] + q0 + lane];
 
@@ -994,15 +1230,6 @@ __device__ __forceinline__ void dkv_body(const Params& p, unsigned char* smem, i
   const float c = p.sm_scale * 1.4426950408889634f;
   GnAddr<T, D> ad;
   ad.init(lane, 0);
-  if constexpr (DQ) {   // K of all keys of the unit as [key][dim] in LDS
-#pragma unroll
-    for (int j = 0; j < X::NJ; ++j) *reinterpret_cast<u32x4_t*>(smem + R::KL + (32 * wave + lq) * R::KL_ROW + 32 * j + 16 * hh) = kf[j];
-    if (!active) {   // (keys past the list: dS is and stays zero)
-      float* ds = reinterpret_cast<float*>(smem + R::DS) + 32 * wave + lq;
-#pragma unroll
-      for (int x = 0; x < 16; ++x) ds[(8 * (x >> 2) + 4 * hh + (x & 3)) * (R::DS_ROW / 4)] = 0.f;
-    }
-  }
 
   // rows [base, end) of stage s
   auto stage_rows = [&](int32_t s, int32_t& base, int32_t& end) {
@@ -1128,11 +1355,6 @@ __device__ __forceinline__ void dkv_body(const Params& p, unsigned char* smem, i
               if (n == NP - 1) {
 #pragma unroll
                 for (int x = 0; x < 16; x += 2) ds.set2(x, sv[1][x], sv[1][x + 1]);
-                if constexpr (DQ) {
-                  float* o = reinterpret_cast<float*>(smem + R::DS) + 32 * wave + lq;
-#pragma unroll
-                  for (int x = 0; x < 16; ++x) o[(8 * (x >> 2) + 4 * hh + (x & 3)) * (R::DS_ROW / 4)] = sv[1][x];
-                }
               }
             } else {
               gn_tr_mma<T, D, NT>(k - 2 * NJ - NP, f, ds, dk);
@@ -1140,37 +1362,6 @@ __device__ __forceinline__ void dkv_body(const Params& p, unsigned char* smem, i
           });
     }
     if (s + 1 < s1) publish(buf ^ Y::BUF);
-    if constexpr (DQ) {
-      __syncthreads();
-      f32x16 dq;
-#pragma unroll
-      for (int x = 0; x < 16; ++x) dq[x] = 0.f;
-      // operands of four instructions: dS of keys 8 t + 4 hh .. + 3 (row lq), K of the same keys (dim 32 wave + lq)
-      const uint32_t at_ds = R::DS + lq * R::DS_ROW + 16 * hh, at_k = R::KL + 4 * hh * R::KL_ROW + (32 * wave + lq) * 4;
-      u32x4_t fd[2];
-      float fk[2][4];
-      auto load = [&](const int t) __attribute__((always_inline)) {
-        fd[t & 1] = *reinterpret_cast<const u32x4_t*>(smem + (at_ds + 32 * t));
-#pragma unroll
-        for (int x = 0; x < 4; ++x) fk[t & 1][x] = *reinterpret_cast<const float*>(smem + (at_k + (8 * t + x) * R::KL_ROW));
-      };
-      load(0);
-#pragma unroll
-      for (int t = 0; t < 16; ++t) {
-        if (t + 1 < 16) {
-          load(t + 1);
-          __builtin_amdgcn_sched_barrier(0);
-        }
-#pragma unroll
-        for (int x = 0; x < 4; ++x) dq = __builtin_amdgcn_mfma_f32_32x32x2f32(fk[t & 1][x], __uint_as_float(fd[t & 1][x]), dq, 0, 0, 0);
-        __builtin_amdgcn_sched_barrier(0);
-      }
-      // dims 32 wave + 8 a + 4 hh .. + 3: group 4 wave + 2 (a % 2) + hh of the lanes of half a / 2
-      float4* dst = reinterpret_cast<float4*>(piece.dq_part) + ((int64_t)(e0 >> (7 - lp)) * p.Hkv * piece.row_blocks + (int64_t)g * piece.row_blocks + s) * (D / 8) * 64 + lq;
-#pragma unroll
-      for (int a = 0; a < 4; ++a)
-        dst[64 * (4 * wave + 2 * (a & 1) + hh) + 32 * (a >> 1)] = make_float4(dq[4 * a], dq[4 * a + 1], dq[4 * a + 2], dq[4 * a + 3]);
-    }
     wait_copies<0>();
     __syncthreads();
   };
@@ -1207,13 +1398,30 @@ __global__ __launch_bounds__(256, (D == 128 || sizeof(T) == 4 ? 1 : 2)) void dkv
   dkv_body<T, TG, D, false, NT>(p, smem, blockIdx.x, n_split, lp, part);
 }
 
-// The whole backward of fp32 tensors at head dim 128: five products per pair instead of the seven of two kernels.  The stages of all units
-// of a KV head, one unit after the other, are cut into equal ranges, one per workgroup: whatever the list and the chunk, every
-// compute unit has the same work (slices per unit: 424 us where this takes 382, 28 / 4 heads, chunk 512, 20 pages of 128).  A range covers the end of one unit and the start of the next (or several short ones); the piece of unit u
+// The whole backward of fp32 tensors at head dim 128: five products per pair instead of the seven of two kernels, all but dQ's as products of three
+// bf16 terms.  A unit is 128 list tokens, 32 per wave: their K and V stay in registers (as terms), the rows of the head stream through
+// LDS in stages of 32, as terms too (row_terms_kernel).  dS goes through LDS, dQ of a stage is left as one fp32 partial sum per unit.  One wave per
+// SIMD (512 registers); the vector work of a product runs between the matrix instructions of the next one.
+// The stages of all units of a KV head, one unit after the other, are cut into equal ranges, one per workgroup: whatever the list and the chunk, every
+// compute unit has the same work.  A range covers the end of one unit and the start of the next (or several short ones); the piece of unit u
 // in range b has slot (b + u) Hkv + g.
-template <int KT> __device__ __forceinline__ int32_t gn_unit_stages(const Params& p, int g, int32_t u, int32_t n_units, int lp) {
+template <int D> struct GnU {
+  typedef Gn<bf16_t, D> X;
+  typedef GnF3<D> F;
+  // a stage: Q0 Q1 Q2 dO0 dO1 dO2; {lse2, delta} of two stages; dS as [row][key], rows 544 bytes apart (both the dwords of 32 keys x 2 rows that a store
+  // moves and the 16 bytes x 64 rows of a read fall on all banks); K as [key][dim]
+  static constexpr int STAT = F::TILE, DS = STAT + 2 * 64 * 4, DS_ROW = GN_ROWS * 4 + 32, KL = DS + 32 * DS_ROW, KL_ROW = D * 4 + 16, LDS = KL + GN_ROWS * KL_ROW;
+  // dQ of a stage: wave w takes dim block w % DB and the keys of part w / DB; a partial sum per part
+  static constexpr int PARTS = 4 / X::DB, KEYS = GN_ROWS / PARTS, WGS = D == 64 ? 2 : 1;   // workgroups per compute unit
+};
+// first stage of 32 rows that sees list entry e of KV head g
+__device__ __forceinline__ int32_t gn_first_stage(const Params& p, int g, int32_t e, int lp) {
+  const int64_t pos = owned_at(p, g, e) << lp, first_q = p.N - p.C;
+  return (pos > first_q ? (int32_t)(pos - first_q) * p.G : 0) / 32;
+}
+__device__ __forceinline__ int32_t gn_unit_stages(const Params& p, int g, int32_t u, int32_t n_units, int lp) {
   if (u >= n_units) return 0;
-  const int32_t n = (int32_t)(((int64_t)p.C * p.G + KT - 1) / KT) - gn_first_stage<KT>(p, g, u << (7 - lp), lp);
+  const int32_t n = (int32_t)(((int64_t)p.C * p.G + 31) / 32) - gn_first_stage(p, g, u << (7 - lp), lp);
   return n > 0 ? n : 0;
 }
 __device__ __forceinline__ int32_t gn_unit_count(const Params& p, int g) { return (int32_t)(((int64_t)list_len(p, g) * p.P + GN_ROWS - 1) / GN_ROWS); }
@@ -1222,14 +1430,197 @@ __device__ __forceinline__ int32_t gn_wave_sum(int32_t v) {
   for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o, 64);
   return __builtin_amdgcn_readfirstlane(v);
 }
-template <typename T, typename TG, int D, int NT>
-__global__ __launch_bounds__(256, 1) void bwd_units_kernel(Params p, int32_t ranges, int lp, float* __restrict__ part, float* __restrict__ dq_part, int32_t row_blocks) {
+// The terms of the rows of Q and dO, [KV head][stage of 32 rows][GnF3::TILE], zeros past the last row; and Delta = <dO, O>.
+template <int D> __global__ __launch_bounds__(256) void row_terms_kernel(Params p, int32_t stages, unsigned char* __restrict__ img) {
+  typedef GnF3<D> F;
+  constexpr int NG = F::X::NG;   // lanes of a row, eight values each
+  const int32_t s = blockIdx.x / p.Hkv, g = blockIdx.x - s * p.Hkv;
+  unsigned char* out = img + ((int64_t)g * stages + s) * F::TILE;
+#pragma unroll
+  for (int x = 0; x < 2 * 32 * NG / 256; ++x) {
+    const int gi = threadIdx.x + 256 * x, is_do = gi / (32 * NG), r = gi / NG % 32, c = gi % NG;   // (is_do is the same for a whole row)
+    const int32_t row = 32 * s + r;
+    const bool valid = row < p.C * p.G;
+    const int32_t i = (int32_t)div_g(p, (uint32_t)(valid ? row : 0)), h = g * p.G + (valid ? row - i * p.G : 0);
+    const int64_t at = (int64_t)i * p.q_tok_stride + (int64_t)h * p.q_head_stride + 8 * c;
+    float4 v[2] = {};
+    if (valid) {
+      const float4* src = reinterpret_cast<const float4*>((const float*)(is_do ? p.d_o : p.q) + at);
+      v[0] = src[0];
+      v[1] = src[1];
+    }
+    if (is_do) {
+      const u32x4_t* o = reinterpret_cast<const u32x4_t*>((const float*)p.o + at);
+      float d = 0.f;
+      if (valid) d = gn_dot<float>(__builtin_bit_cast(u32x4_t, v[1]), o[1], gn_dot<float>(__builtin_bit_cast(u32x4_t, v[0]), o[0], 0.f));
+#pragma unroll
+      for (int k = 1; k < NG; k <<= 1) d += __shfl_xor(d, k, 64);
+      if (valid && c == 0) p.delta[(int64_t)h * p.C + i] = d;
+    }
+    gn_store_terms<D>(out + is_do * F::V + r * F::X::RB + ((c ^ F::X::swz(r)) << 4), v);
+  }
+}
+struct GnPiece { int32_t g, u, s0, s1, slot, stages; };   // stages s0 .. s1 - 1 of unit u
+template <int D>
+__device__ __forceinline__ void units_body(const Params& p, unsigned char* smem, int lp, const unsigned char* __restrict__ img, float* __restrict__ part,
+                                           float* __restrict__ dq_part, const GnPiece& t) {
+  typedef GnU<D> R;
+  typedef GnF3<D> F;
+  typedef Gn<bf16_t, D> X;
+  int tid = threadIdx.x;
+  asm volatile("" : "+v"(tid));   // (nothing that depends on the lane is kept from one piece to the next: it would be spilled)
+  const int lane = tid & 63, hh = lane >> 5, lq = lane & 31, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int32_t e0 = t.u << (7 - lp), len = list_len(p, t.g), kq = 32 * wave + lq;   // this lane's key
+  int32_t e = e0 + (kq >> lp);
+  const bool kvalid = e < len, active = e0 + (32 * wave >> lp) < len;
+  e = e < len ? e : len - 1;
+  const int64_t l = list_at(p, t.g, e), pos = (l << lp) + (kq & (p.P - 1)), first_q = p.N - p.C;
+  const int64_t koff = (int64_t)p.page_table[l] * p.pool_page_stride + (int64_t)t.g * p.pool_head_stride + (int64_t)(kq & (p.P - 1)) * p.pool_tok_stride;
+  // rows before r_key do not see the key
+  const int32_t r_key = !kvalid ? INT32_MAX : pos > first_q ? (int32_t)(pos - first_q) * p.G : 0, r_key_max = __builtin_amdgcn_readlane(r_key, 31);
+  u32x4_t kf[3][X::NJ], vf[3][X::NJ];
+#pragma unroll
+  for (int j = 0; j < X::NJ; ++j) {
+    const float4* k = reinterpret_cast<const float4*>((const float*)p.k_pool + koff + 16 * j + 8 * hh);
+    const float4* v = reinterpret_cast<const float4*>((const float*)p.v_pool + koff + 16 * j + 8 * hh);
+    const float4 k0 = k[0], k1 = k[1];
+    float4* kl = reinterpret_cast<float4*>(smem + R::KL + kq * R::KL_ROW + 64 * j + 32 * hh);
+    kl[0] = k0;
+    kl[1] = k1;
+    gn_load_terms(k0, k1, kf[0][j], kf[1][j], kf[2][j]);
+    gn_load_terms(v[0], v[1], vf[0][j], vf[1][j], vf[2][j]);
+  }
+  f32x16 dk[X::DB], dv[X::DB];
+  gn_zero(dk);
+  gn_zero(dv);
+  const float c = p.sm_scale * 1.4426950408889634f;
+  GnAddr<bf16_t, D> ad;
+  ad.init(lane, 0);
+  float* const ds_out = reinterpret_cast<float*>(smem + R::DS) + kq + 4 * hh * (R::DS_ROW / 4);
+  if (!active) {   // (keys past the list: dS is and stays zero)
+#pragma unroll
+    for (int x = 0; x < 16; ++x) ds_out[(8 * (x >> 2) + (x & 3)) * (R::DS_ROW / 4)] = 0.f;
+  }
+  const unsigned char* src = img + ((int64_t)t.g * t.stages) * F::TILE + wave * (F::TILE / 4) + lane * 16;
+  float st_l = INFINITY, st_d = 0.f;   // statistics of row `tid` of the stage under way
+  auto copy = [&](const int32_t s) __attribute__((always_inline)) {
+#pragma unroll
+    for (int k = 0; k < F::TILE / 4096; ++k) gn_copy16(src + (int64_t)s * F::TILE + 1024 * k, wave * (F::TILE / 4) + 1024 * k);
+    if (tid < 32) {
+      const int32_t r = 32 * s + tid;
+      st_l = INFINITY;   // rows past the end: P = 0
+      st_d = 0.f;
+      if (r < p.C * p.G) {
+        const int32_t i = (int32_t)div_g(p, (uint32_t)r);
+        const int64_t at = (int64_t)(t.g * p.G + (r - i * p.G)) * p.C + i;
+        st_l = p.lse[at] * 1.4426950408889634f;
+        st_d = p.delta[at];
+      }
+    }
+  };
+  float* const st = reinterpret_cast<float*>(smem + R::STAT);
+  auto publish = [&] {
+    if (tid < 32) {
+      st[tid] = st_l;
+      st[64 + tid] = st_d;
+    }
+    wait_copies<0>();
+    __syncthreads();
+  };
+  copy(t.s0);
+  publish();
+  for (int32_t s = t.s0; s < t.s1; ++s) {
+    if (active) {
+      const int32_t base = 32 * s, rel = r_key - base - 4 * hh;
+      const bool mask = base < r_key_max;   // (wave-uniform)
+      f32x16 sv[2], dp[2];
+      GnP<bf16_t, 3> pr, ds;
+      gn_zero(sv);
+      gn_zero(dp);
+      auto terms = [&](const GnP<bf16_t, 3>& v, const int u, const int k) __attribute__((always_inline)) { return u32x4_t{v.w[k][4 * u], v.w[k][4 * u + 1], v.w[k][4 * u + 2], v.w[k][4 * u + 3]}; };
+      gn_terms_pipeline<2 * X::NJ + 4 * X::DB>(
+          [&](const int i, const int k) __attribute__((always_inline)) {
+            return i < X::NJ ? ad.row_frag(i, k * F::TERM) : i < 2 * X::NJ ? ad.row_frag(i - X::NJ, F::V + k * F::TERM)
+                 : i < 2 * X::NJ + 2 * X::DB ? ad.tr_frag(i - 2 * X::NJ, F::V + k * F::TERM) : ad.tr_frag(i - 2 * X::NJ - 2 * X::DB, k * F::TERM);
+          },
+          [&](const int i, const u32x4_t (&f)[3]) __attribute__((always_inline)) {
+            constexpr int NJ = X::NJ, NV = 2 * X::DB;
+            if (i < NJ) {
+              gn_mma_terms(f, kf[0][i], kf[1][i], kf[2][i], sv[1], sv[0]);
+            } else if (i < 2 * NJ) {   // dP, and P
+              const int j = i - NJ;
+              gn_mma_terms(f, vf[0][j], vf[1][j], vf[2][j], dp[1], dp[0]);
+#pragma unroll
+              for (int x = j * (16 / NJ); x < (j + 1) * (16 / NJ); ++x) {
+                const int row = 8 * (x >> 2) + (x & 3);
+                float v = __builtin_amdgcn_exp2f(__builtin_fmaf(sv[0][x] + sv[1][x], c, -st[row + 4 * hh]));
+                if (mask && row < rel) v = 0.f;
+                sv[0][x] = v;
+              }
+#pragma unroll
+              for (int x = j * (16 / NJ); x < (j + 1) * (16 / NJ); x += 2) pr.set2(x, sv[0][x], sv[0][x + 1]);
+            } else if (i < 2 * NJ + NV) {   // dV, and dS
+              const int v = i - 2 * NJ, u = v / X::DB;
+              gn_mma_terms(f, terms(pr, u, 0), terms(pr, u, 1), terms(pr, u, 2), dv[v % X::DB], dv[v % X::DB]);
+#pragma unroll
+              for (int x = v * (16 / NV); x < (v + 1) * (16 / NV); ++x) {
+                const int row = 8 * (x >> 2) + (x & 3);
+                sv[0][x] = sv[0][x] * (dp[0][x] + dp[1][x] - st[64 + row + 4 * hh]);
+                ds_out[row * (R::DS_ROW / 4)] = sv[0][x];
+              }
+#pragma unroll
+              for (int x = v * (16 / NV); x < (v + 1) * (16 / NV); x += 2) ds.set2(x, sv[0][x], sv[0][x + 1]);
+            } else {
+              const int v = i - 2 * NJ - NV, u = v / X::DB;
+              gn_mma_terms(f, terms(ds, u, 0), terms(ds, u, 1), terms(ds, u, 2), dk[v % X::DB], dk[v % X::DB]);
+            }
+          });
+    }
+    __syncthreads();   // dS is in LDS; nobody reads the stage any more, whose place takes the next
+    if (s + 1 < t.s1) copy(s + 1);
+    f32x16 dq;
+#pragma unroll
+    for (int x = 0; x < 16; ++x) dq[x] = 0.f;
+    // operands of four instructions: dS of keys 8 n + 4 hh .. + 3 of the part (row lq), K of the same keys (dim 32 db + lq)
+    const int db = wave % X::DB, kp = wave / X::DB;
+    const uint32_t at_ds = R::DS + lq * R::DS_ROW + 16 * hh + kp * R::KEYS * 4, at_k = R::KL + (kp * R::KEYS + 4 * hh) * R::KL_ROW + (32 * db + lq) * 4;
+    u32x4_t fd[2];
+    float fk[2][4];
+    auto load = [&](const int n) __attribute__((always_inline)) {
+      fd[n & 1] = *reinterpret_cast<const u32x4_t*>(smem + (at_ds + 32 * n));
+#pragma unroll
+      for (int x = 0; x < 4; ++x) fk[n & 1][x] = *reinterpret_cast<const float*>(smem + (at_k + (8 * n + x) * R::KL_ROW));
+    };
+    load(0);
+#pragma unroll
+    for (int n = 0; n < R::KEYS / 8; ++n) {
+      if (n + 1 < R::KEYS / 8) {
+        load(n + 1);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+#pragma unroll
+      for (int x = 0; x < 4; ++x) dq = __builtin_amdgcn_mfma_f32_32x32x2f32(fk[n & 1][x], __uint_as_float(fd[n & 1][x]), dq, 0, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    // dims 32 db + 8 a + 4 hh .. + 3: group 4 db + a of the block
+    float4* dst = reinterpret_cast<float4*>(dq_part) + (((int64_t)(t.u * R::PARTS + kp) * p.Hkv + t.g) * (4 * gn_tiles(p.C, p.G, p.P, p.m, 0)) + s) * (D / 8) * 64 + lane;
+#pragma unroll
+    for (int a = 0; a < 4; ++a) dst[64 * (4 * db + a)] = make_float4(dq[4 * a], dq[4 * a + 1], dq[4 * a + 2], dq[4 * a + 3]);
+    publish();
+  }
+  if (active) {
+    part_store<bf16_t, D>(part, ((int64_t)t.slot * 2) * 4 + wave, lane, dk, p.sm_scale);
+    part_store<bf16_t, D>(part, ((int64_t)t.slot * 2 + 1) * 4 + wave, lane, dv, 1.f);
+  }
+}
+template <int D>
+__global__ __launch_bounds__(256, GnU<D>::WGS) void bwd_units_kernel(Params p, int32_t ranges, int lp, const unsigned char* __restrict__ img, float* __restrict__ part,
+                                                              float* __restrict__ dq_part) {
   extern __shared__ __align__(16) unsigned char smem[];
-  constexpr int KT = GnKey<T, D>::KT;
   const int lane = threadIdx.x & 63;
   const int32_t b = blockIdx.x / p.Hkv, g = blockIdx.x - b * p.Hkv, n_units = gn_unit_count(p, g);
   int32_t all = 0;
-  for (int32_t u = 0; u < n_units; u += 64) all += gn_unit_stages<KT>(p, g, u + lane, n_units, lp);
+  for (int32_t u = 0; u < n_units; u += 64) all += gn_unit_stages(p, g, u + lane, n_units, lp);
   all = gn_wave_sum(all);
   ranges = ranges < all ? ranges : all;   // (none of them empty)
   if (b >= ranges) return;
@@ -1238,7 +1629,7 @@ __global__ __launch_bounds__(256, 1) void bwd_units_kernel(Params p, int32_t ran
   // the unit in which the range starts, and where in it
   int32_t u = 0, before = 0;
   for (int32_t u0 = 0; u0 < n_units; u0 += 64) {
-    const int32_t n = gn_unit_stages<KT>(p, g, u0 + lane, n_units, lp);
+    const int32_t n = gn_unit_stages(p, g, u0 + lane, n_units, lp);
     int32_t upto = n;
 #pragma unroll
     for (int o = 1; o < 64; o <<= 1) {
@@ -1253,12 +1644,12 @@ __global__ __launch_bounds__(256, 1) void bwd_units_kernel(Params p, int32_t ran
     }
     before += __builtin_amdgcn_readlane(upto, 63);
   }
-  const int32_t S = (int32_t)(((int64_t)p.C * p.G + KT - 1) / KT);
+  const int32_t S = (int32_t)(((int64_t)p.C * p.G + 31) / 32);
   for (; at < end; ++u) {
-    const int32_t lo = __builtin_amdgcn_readfirstlane(gn_first_stage<KT>(p, g, u << (7 - lp), lp)), n = S - lo > 0 ? S - lo : 0;
+    const int32_t lo = __builtin_amdgcn_readfirstlane(gn_first_stage(p, g, u << (7 - lp), lp)), n = S - lo > 0 ? S - lo : 0;
     const int32_t s0 = lo + (at - before), s1 = s0 + (end - at) < lo + n ? s0 + (end - at) : lo + n;
     if (s0 < s1) {
-      dkv_body<T, TG, D, false, NT, true>(p, smem, 0, 1, lp, part, GnPiece{g, u << (7 - lp), s0, s1, (b + u) * p.Hkv + g, dq_part, row_blocks});
+      units_body<D>(p, smem, lp, img, part, dq_part, GnPiece{g, u, s0, s1, (b + u) * p.Hkv + g, S});
       __syncthreads();
     }
     at += s1 - s0;
@@ -1280,26 +1671,27 @@ __global__ __launch_bounds__(256, (D == 128 || sizeof(T) == 4 ? 1 : 2)) void bwd
 
 // What is left of a backward with splits, in one launch: workgroups below dq_blocks add the dQ partials, the others
 // add the slices of a dK / dV unit to the pool.
-template <typename T, typename TG, int D>
+template <typename T, typename TG, int D, typename L = T>
 __global__ __launch_bounds__(256) void bwd_finish_kernel(Params p, int32_t tiles, int32_t dq_split, const float* __restrict__ dq_part,
                                                          int32_t dq_blocks, int32_t kv_split, const float* __restrict__ kv_part, int lp,
-                                                         int redo_keys, int dq_units) {
+                                                         int redo_keys) {
+  constexpr bool UNITS = sizeof(L) != sizeof(T);   // the partial sums are those of bwd_units_kernel
   __shared__ GnRowsLds<D> sh;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   float4 a[GN_GW<D>];
   if ((int32_t)blockIdx.x < dq_blocks) {
     const int64_t blocks = (int64_t)p.Hkv * tiles * 4;
-    if (dq_units) {   // a partial sum per unit that sees the block (bwd_units_kernel): the first ones of the list
+    if constexpr (UNITS) {   // a partial sum per unit that sees the block: the first ones of the list
       const int32_t gb = (int32_t)blockIdx.x / (4 * tiles), s = (int32_t)blockIdx.x - gb * 4 * tiles, n = gn_unit_count(p, gb);
       dq_split = 0;
       for (int32_t u = 0; u < n; u += 64)
-        dq_split += __builtin_popcountll(__ballot(u + lane < n && gn_first_stage<32>(p, gb, (u + lane) << (7 - lp), lp) <= s));
-      dq_split = __builtin_amdgcn_readfirstlane(dq_split);
+        dq_split += __builtin_popcountll(__ballot(u + lane < n && gn_first_stage(p, gb, (u + lane) << (7 - lp), lp) <= s));
+      dq_split = __builtin_amdgcn_readfirstlane(dq_split) * GnU<D>::PARTS;
     }
     gn_sum_parts<D>(dq_part, blockIdx.x, blocks * (D / 8) * 64, dq_split, a, [] {});
     const float sc = p.sm_scale;
     int i, h;
-    uint32_t bad = gn_rows_out<T, D>(sh, a, true, [&](int, int row, int d, const float4& r) __attribute__((always_inline)) {
+    uint32_t bad = gn_rows_out<L, D>(sh, a, true, [&](int, int row, int d, const float4& r) __attribute__((always_inline)) {
       if (gn_out_row(p, tiles, blockIdx.x, row, i, h))
         part_store4<T>((T*)p.d_q + (int64_t)i * p.q_tok_stride + (int64_t)h * p.q_head_stride + d, r.x * sc, r.y * sc, r.z * sc, r.w * sc);
     });
@@ -1324,18 +1716,18 @@ __global__ __launch_bounds__(256) void bwd_finish_kernel(Params p, int32_t tiles
     if (e0 >= list_len(p, g)) return;
     slot = ((int64_t)u * kv_split) * p.Hkv + g;
     next = p.Hkv;
-    if (dq_units) {   // the ranges (kv_split of them) that hold a piece of the unit (bwd_units_kernel)
+    if constexpr (UNITS) {   // the ranges (kv_split of them) that hold a piece of the unit
       const int32_t n_units = gn_unit_count(p, g);
       int32_t all = 0, before = 0;
       for (int32_t v = lane; v < n_units; v += 64) {
-        const int32_t n = gn_unit_stages<32>(p, g, v, n_units, lp);
+        const int32_t n = gn_unit_stages(p, g, v, n_units, lp);
         all += n;
         before += v < u ? n : 0;
       }
       all = gn_wave_sum(all);
       before = gn_wave_sum(before);
       const int32_t ranges = kv_split < all ? kv_split : all;
-      const int32_t mine = __builtin_amdgcn_readfirstlane(gn_unit_stages<32>(p, g, u, n_units, lp));
+      const int32_t mine = __builtin_amdgcn_readfirstlane(gn_unit_stages(p, g, u, n_units, lp));
       if (mine == 0) return;
       // range b starts at stage all b / kv_split: the last one that starts at or before a stage
       auto range_of = [&](int32_t at) { return (int32_t)(((int64_t)(at + 1) * ranges - 1) / all); };
@@ -1361,7 +1753,7 @@ __global__ __launch_bounds__(256) void bwd_finish_kernel(Params p, int32_t tiles
       if (page) old[k] = part_load4<TG>(dst[k]);
     }
   });
-  uint32_t bad = gn_rows_out<T, D>(sh, a, redo_keys, [&](int k, int, int, const float4& r) __attribute__((always_inline)) {
+  uint32_t bad = gn_rows_out<L, D>(sh, a, redo_keys, [&](int k, int, int, const float4& r) __attribute__((always_inline)) {
     if (dst[k]) part_store4<TG>(dst[k], old[k].x + r.x, old[k].y + r.y, old[k].z + r.z, old[k].w + r.w);
   });
   for (bad &= 0xffu << (8 * wave); bad; bad &= bad - 1) {
@@ -1458,18 +1850,21 @@ static bool gn_takes_pair(const Params& p, bool bf, int32_t max_len, const GnPai
   return pair.us < 1e29f && pair.us < gn_two_us(p, bf, max_len);
 }
 
-// The backward by units (bwd_units_kernel): ranges per KV head, at most a workgroup per compute unit, and the estimate of its time in microseconds.
-// A stage of 32 rows x 128 keys takes STAGE (its 320 matrix instructions per wave 9.8 us at the rate that a loop of nothing else reaches, 134 TFLOP/s); fewer ranges than fit leave fewer partial sums to add.
+// The backward by units (bwd_units_kernel): ranges per KV head, as many workgroups as run at once, and the estimate of its time in microseconds.
+// A stage of 32 rows x 128 keys takes STAGE (head dim 64: with two workgroups on a compute unit); fewer ranges than fit leave fewer partial sums to add.
 struct GnUnits { int32_t ranges; float us; };
+static int32_t gn_row_stages(const Params& p) { return (int32_t)(((int64_t)p.C * p.G + 31) / 32); }
+static size_t gn_row_img_bytes(const Params& p) { return gn_up((size_t)p.Hkv * gn_row_stages(p) * 6 * 32 * p.D * 2); }
 static size_t gn_units_dq_bytes(const Params& p, int32_t max_len) {
-  return (size_t)gn_key_units(p, max_len) * gn_tiles(p.C, p.G, p.P, p.m, p.qp) * p.Hkv * GN_ROWS * p.D * 4;
+  return (size_t)gn_key_units(p, max_len) * gn_tiles(p.C, p.G, p.P, p.m, p.qp) * p.Hkv * GN_ROWS * 128 * 4;   // (at head dim 64 two per unit)
 }
 static GnUnits gn_units(const Params& p, bool bf, int32_t max_len) {
   GnUnits best = {1, 1e30f};
-  if (bf || p.D != 128 || p.qp || p.Hkv > 256 || gn_units_dq_bytes(p, max_len) > ((size_t)1 << 30)) return best;
-  constexpr float STAGE = 11.5f, START = 25.f, BYTES = 2.5e-7f;   // (bytes written and read again)
+  if (bf || p.qp || p.Hkv > 256 || gn_units_dq_bytes(p, max_len) > ((size_t)4 << 30) || gn_row_img_bytes(p) > ((size_t)1 << 30)) return best;
+  constexpr float START = 28.f, BYTES = 2.5e-7f;   // (bytes written and read again)
+  const float STAGE = p.D == 128 ? 7.8f : 6.5f;
   const int32_t units = gn_key_units(p, max_len);
-  const int64_t S = ((int64_t)p.C * p.G + 31) / 32, most = 256 / p.Hkv;
+  const int64_t S = gn_row_stages(p), most = (p.D == 128 ? 256 : 512) / p.Hkv;
   int64_t all = units * S;   // stages of a head, if its list is full: fewer of the units that hold the chunk's own pages
   for (int32_t u = (int32_t)((int64_t)(max_len - p.m) * p.P / GN_ROWS); u < units; ++u) {
     const int64_t tok = (int64_t)u * GN_ROWS - (int64_t)(max_len - p.m) * p.P;
@@ -1479,7 +1874,7 @@ static GnUnits gn_units(const Params& p, bool bf, int32_t max_len) {
   const int64_t q0 = (all + most - 1) / most;
   for (int64_t q = q0; q < q0 + 4; ++q) {
     const int64_t r = (all + q - 1) / q;
-    const float us = START + (float)q * STAGE + dq + (float)(r + units) * p.Hkv * 131072.f * BYTES;
+    const float us = START + (float)q * STAGE + dq + (float)(r + units) * p.Hkv * 1024.f * p.D * BYTES;
     if (us < best.us) best = {(int32_t)r, us};
   }
   return best;
@@ -1489,15 +1884,47 @@ static size_t gn_units_part_bytes(const Params& p, int32_t max_len) {
   return (size_t)(gn_units(p, false, max_len).ranges + gn_key_units(p, max_len)) * p.Hkv * 2 * GN_ROWS * p.D * 4;
 }
 static bool gn_takes_units(const Params& p, bool bf, int32_t max_len);
-static size_t gn_units_bytes(const Params& p, int32_t max_len) { return gn_delta_bytes(p) + gn_units_part_bytes(p, max_len) + gn_units_dq_bytes(p, max_len); }
+static size_t gn_units_bytes(const Params& p, int32_t max_len) { return gn_delta_bytes(p) + gn_row_img_bytes(p) + gn_units_part_bytes(p, max_len) + gn_units_dq_bytes(p, max_len); }
 
 static size_t gn_row_blocks(const Params& p) { return (size_t)gn_tiles(p.C, p.G, p.P, p.m, p.qp) * p.Hkv * 4; }
 // splits that fit `bytes` of partial results of `per` bytes each (at least 1: no partial results)
 static int32_t gn_fit(size_t bytes, size_t per) { return (int32_t)(bytes / per > 32 ? 32 : bytes / per < 2 ? 1 : bytes / per); }
 static size_t gn_row_part_bytes(const Params& p, int32_t split) { return split > 1 ? split * gn_row_blocks(p) * 32 * p.D * 4 : 0; }
+// The fp32 forward in terms: splits of the key range and the estimate of its time in microseconds, the layout of the terms included.  Two workgroups
+// of a compute unit take `unit` for a tile of 32 keys each (192 matrix instructions per SIMD); 512 run at a time.
+struct GnF3Plan { int32_t n; float us; };
+static size_t gn_f3_img_bytes(const Params& p, int32_t max_len) { return gn_up((size_t)p.Hkv * gn_f3_tiles(p, max_len) * 6 * 32 * p.D * 2); }
+static GnF3Plan gn_f3_plan(const Params& p, bool bf, int32_t max_len) {
+  GnF3Plan best = {1, 1e30f};
+  if (bf || p.qp || gn_f3_img_bytes(p, max_len) > ((size_t)1 << 31)) return best;
+  constexpr float RAMP = 6.f, LAUNCH = 3.f, PART = 2.56e-4f, LAYOUT = 5.f, BYTES = 5e-7f;
+  const float unit = 3.3f * (p.D == 128 ? 1.f : 0.55f), all = (float)gn_f3_tiles(p, max_len), avg = (max_len - 0.5f * p.m) * p.P / 32.f;
+  const int32_t tiles = gn_tiles(p.C, p.G, p.P, p.m, 0), wgs = tiles * p.Hkv;
+  for (int32_t n = 1; n <= 32 && (n == 1 || n <= all); ++n) {
+    const float x = (float)wgs * n, extra = n > 1 ? LAUNCH + x * p.D * PART : 0.f, mine = avg / n > 1.f ? avg / n : 1.f;
+    const float us = gn_rounds(x / 512.f, 0.55f, 0.45f, 0.55f, 0.45f) * mine * unit + ceilf(x / 512.f) * RAMP + extra + LAYOUT + (float)gn_f3_img_bytes(p, max_len) * BYTES;
+    if (us < best.us) best = {n, us};
+  }
+  return best;
+}
+// Against the fp32 matrix pipe.  Timed on 60 shapes (2 / 1 to 28 / 4 heads, head dims 64 and 128, pages of 16 to 128, chunks of 64 to 2048, lists of 8 to 190
+// pages): both estimates are low, the other one by more, hence the factor.  Calls of 30 us and less are up to 15 % faster there, from 45 us on the
+// terms are 1.1 to 1.85 times as fast.  Where the backward takes terms the forward does too (between 27 and 36 us at most 6 % slower), and where
+// it has no room for that the forward does not either: LSE and the products that the backward forms anew then have the same errors, which
+// cancel in dQ (28 / 4 heads, chunk 512, 20 pages of 128, against 64 bits: both fp32 1.11e-6, only the forward in terms 1.33e-6, both in terms 0.71e-6).
+static bool gn_takes_f3(const Params& p, bool bf, int32_t max_len, const GnF3Plan& f) {
+  if (f.us > 1e29f || gn_units(p, bf, max_len).us > 1e29f) return false;
+  return f.us < 1.12f * gn_plan(p, bf, max_len, false).us || gn_takes_units(p, bf, max_len);
+}
+static size_t gn_f3_bytes(const Params& p, int32_t max_len, int32_t n) {
+  return gn_f3_img_bytes(p, max_len) + (n > 1 ? gn_row_part_bytes(p, n) + n * gn_row_blocks(p) * 32 * 8 : 0);
+}
 size_t fwd_generic_workspace_bytes(const Params& p, bool bf, int32_t max_len) {
   const int32_t s = gn_plan(p, bf, max_len, false).n;
-  return s > 1 ? gn_row_part_bytes(p, s) + s * gn_row_blocks(p) * 32 * 8 : 256;
+  const size_t plain = s > 1 ? gn_row_part_bytes(p, s) + s * gn_row_blocks(p) * 32 * 8 : 256;
+  const GnF3Plan f = gn_f3_plan(p, bf, max_len);
+  const size_t terms = gn_takes_f3(p, bf, max_len, f) ? gn_f3_bytes(p, max_len, f.n) : 0;
+  return terms > plain ? terms : plain;
 }
 size_t dq_generic_part_bytes(const Params& p, bool bf, int32_t max_len) { return gn_row_part_bytes(p, gn_plan(p, bf, max_len, true).n); }
 static size_t gn_key_part_bytes(const Params& p, int32_t max_len, int32_t split) {
@@ -1517,15 +1944,15 @@ size_t bwd_generic_workspace_bytes(const Params& p, bool bf, int32_t max_len) {
   return units > most ? units : most;
 }
 
-// Against the one-launch backward, or dQ and dK / dV one after the other.  Timed on 56 shapes (2 / 1 to 32 / 8 heads, pages of 16 to 128, 1 to 70 query
-// pages, lists of 2 to 285 pages): the estimate of the units is right to 10 % (a fixed 9 us too high below 30 us), that of the others up to 25 % too
-// low, hence the factor.  28 / 4 heads, chunk 512, 16 + 4 pages of 128: 642 -> 460 us; 2 / 1 heads, chunk 288, 45 + 18 pages of 16: 198 -> 135; from
-// 60 us on everything is 10 to 45 % faster, the shortest calls (30 us) stay with the one launch, which is up to 9 % faster there.
+// Against the one-launch backward, or dQ and dK / dV one after the other.  Timed on the 60 shapes above: the estimate of the units is right to 15 % (up to
+// 12 us too high below 35 us), that of the others mostly low, hence the factor.  Calls of 50 us and less are up to 30 % faster without, from
+// 60 us on this is 1.1 to 2.3 times as fast: 28 / 4 heads, chunk 512, 16 + 4 pages of 128: 603 -> 309 us; 14 / 2 heads of 64 dims, chunk 1664,
+// 14 + 13 pages of 128: 629 -> 334; 28 / 4 heads of 64, chunk 2048, 128 + 32 pages of 64: 5870 -> 2741.
 static bool gn_takes_units(const Params& p, bool bf, int32_t max_len) {
   const float us = gn_units(p, bf, max_len).us;
   if (us > 1e29f) return false;
   const GnPair pair = gn_pair(p, bf, max_len);
-  return us < 1.15f * (gn_takes_pair(p, bf, max_len, pair) ? pair.us : gn_two_us(p, bf, max_len));
+  return us < 1.08f * (gn_takes_pair(p, bf, max_len, pair) ? pair.us : gn_two_us(p, bf, max_len));
 }
 
 // terms of a probability (GnP) where a shape has no kernels of its own
@@ -1555,8 +1982,31 @@ static hipError_t fwd_generic(const Params& p, int32_t max_len, void* ws, size_t
   }
   return e;
 }
+// *done: whether the call was taken (it has the room, and the estimate is below that of the fp32 matrix pipe)
+template <int D> static hipError_t fwd_terms(const Params& p, int32_t max_len, void* ws, size_t ws_bytes, const char* name, hipStream_t st, bool* done) {
+  typedef GnF3<D> F;
+  const GnF3Plan f = gn_f3_plan(p, false, max_len);
+  if (!ws || !gn_takes_f3(p, false, max_len, f) || gn_f3_bytes(p, max_len, f.n) > ws_bytes) return hipSuccess;
+  *done = true;
+  ProfScope prof_(name, st);
+  static DeviceOnce once;
+  if (hipError_t e = ensure_max_dynamic_lds(once, (const void*)fwd_terms_kernel<D>, F::LDS); e != hipSuccess) return e;
+  const int32_t tiles = gn_tiles(p.C, p.G, p.P, p.m, 0), n_tiles = gn_f3_tiles(p, max_len), lp = __builtin_ctz(p.P);
+  unsigned char* img = (unsigned char*)ws;
+  float* part = (float*)(img + gn_f3_img_bytes(p, max_len));
+  float2* ml = (float2*)((unsigned char*)part + gn_row_part_bytes(p, f.n));
+  { ProfScope layout_("kv_terms", st); kv_terms_kernel<D><<<dim3((unsigned)(n_tiles * p.Hkv)), dim3(256), 0, st>>>(p, n_tiles, lp, img); }
+  if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
+  { ProfScope fwd_("fwd_terms", st); fwd_terms_kernel<D><<<dim3((unsigned)(tiles * p.Hkv * f.n)), dim3(256), F::LDS, st>>>(p, tiles, f.n, lp, max_len, n_tiles, img, part, ml); }
+  if (hipError_t e = hipGetLastError(); e != hipSuccess || f.n == 1) return e;
+  fwd_combine_kernel<float, D, bf16_t><<<dim3((unsigned)(gn_row_blocks(p))), dim3(256), 0, st>>>(p, tiles, f.n, part, ml, lp);
+  return hipGetLastError();
+}
 hipError_t launch_fwd_generic(const Params& p, bool bf, int32_t max_len, void* ws, size_t ws_bytes, hipStream_t st) {
   const char* name = "attn_fwd_generic";
+  bool done = false;
+  if (!bf)
+    if (hipError_t e = p.D == 128 ? fwd_terms<128>(p, max_len, ws, ws_bytes, name, st, &done) : fwd_terms<64>(p, max_len, ws, ws_bytes, name, st, &done); done) return e;
   if (bf) return p.D == 128 ? fwd_generic<bf16_t, 128>(p, max_len, ws, ws_bytes, name, st) : fwd_generic<bf16_t, 64>(p, max_len, ws, ws_bytes, name, st);
   return p.D == 128 ? fwd_generic<float, 128>(p, max_len, ws, ws_bytes, name, st) : fwd_generic<float, 64>(p, max_len, ws, ws_bytes, name, st);
 }
@@ -1588,14 +2038,14 @@ hipError_t launch_dq_generic_bf16_128(const Params& p, int32_t max_len, float* p
   return dq_generic<bf16_t, 128, 1>(p, max_len, part, part_bytes, bias, n_stages, splits, st);
 }
 
-template <typename T, typename TG, int D>
+template <typename T, typename TG, int D, typename L = T>
 static hipError_t bwd_finish(const Params& p, int32_t dq_split, const float* dq_part, int32_t kv_units, int32_t kv_split, const float* kv_part,
-                             bool redo_keys, hipStream_t st, bool dq_units = false) {
-  const int32_t dq_blocks = dq_split > 1 || dq_units ? (int32_t)(gn_row_blocks(p)) : 0;
+                             bool redo_keys, hipStream_t st) {
+  const int32_t dq_blocks = dq_split > 1 || sizeof(L) != sizeof(T) ? (int32_t)(gn_row_blocks(p)) : 0;
   const int64_t blocks = dq_blocks + (int64_t)kv_units * p.Hkv * 2 * part_key_blocks(p);
   if (blocks <= 0) return hipSuccess;
-  bwd_finish_kernel<T, TG, D><<<dim3((unsigned)blocks), dim3(256), 0, st>>>(p, gn_tiles(p.C, p.G, p.P, p.m, p.qp), dq_split, dq_part, dq_blocks, kv_split,
-                                                                            kv_part, __builtin_ctz(p.P), redo_keys, dq_units);
+  bwd_finish_kernel<T, TG, D, L><<<dim3((unsigned)blocks), dim3(256), 0, st>>>(p, gn_tiles(p.C, p.G, p.P, p.m, p.qp), dq_split, dq_part, dq_blocks, kv_split,
+                                                                            kv_part, __builtin_ctz(p.P), redo_keys);
   return hipGetLastError();
 }
 // (the dK / dV slices of pages with kernels of their own: keys are left as those give them)
@@ -1633,30 +2083,38 @@ hipError_t launch_bwd_pair_bf16_128(const Params& p, int32_t max_len, void* ws, 
                         : bwd_pair<bf16_t, float, 128, 1>(p, max_len, ws, ws_bytes, "bwd_pair", st, done);
 }
 
-template <typename TG>
+template <typename TG, int D>
 static hipError_t bwd_units(Params p, int32_t max_len, void* ws, size_t ws_bytes, const char* name, hipStream_t st, bool* done) {
   const int32_t n = gn_units(p, false, max_len).ranges, units = gn_key_units(p, max_len);
   if (dq_overlaps_o(p, false) || !gn_takes_units(p, false, max_len) || gn_units_bytes(p, max_len) > ws_bytes) return hipSuccess;
   *done = true;
   ProfScope prof_(name, st);
-  typedef GnKey<float, 128> R;
   static DeviceOnce once;
-  if (hipError_t e = ensure_max_dynamic_lds(once, (const void*)bwd_units_kernel<float, TG, 128, 1>, R::LDS_DQ); e != hipSuccess) return e;
+  if (hipError_t e = ensure_max_dynamic_lds(once, (const void*)bwd_units_kernel<D>, GnU<D>::LDS); e != hipSuccess) return e;
+  const int32_t stages = gn_row_stages(p), lp = __builtin_ctz(p.P);
   p.delta = (float*)ws;
-  if (hipError_t e = launch_delta<float, 128>(p, st); e != hipSuccess) return e;
-  float* kv_part = (float*)((unsigned char*)ws + gn_delta_bytes(p));
+  unsigned char* img = (unsigned char*)ws + gn_delta_bytes(p);
+  float* kv_part = (float*)(img + gn_row_img_bytes(p));
   float* dq_part = (float*)((unsigned char*)kv_part + gn_units_part_bytes(p, max_len));
-{ ProfScope units_("bwd_units", st); bwd_units_kernel<float, TG, 128, 1><<<dim3((unsigned)(p.Hkv * n)), dim3(256), R::LDS_DQ, st>>>(p, n, __builtin_ctz(p.P), kv_part, dq_part, 4 * gn_tiles(p.C, p.G, p.P, p.m, p.qp)); }
+  {
+    ProfScope terms_("row_terms", st);
+    row_terms_kernel<D><<<dim3((unsigned)(stages * p.Hkv)), dim3(256), 0, st>>>(p, stages, img);
+  }
   if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
-  return bwd_finish<float, TG, 128>(p, 1, dq_part, units, n, kv_part, true, st, true);
+  {
+    ProfScope units_("bwd_units", st);
+    bwd_units_kernel<D><<<dim3((unsigned)(p.Hkv * n)), dim3(256), GnU<D>::LDS, st>>>(p, n, lp, img, kv_part, dq_part);
+  }
+  if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
+  return bwd_finish<float, TG, D, bf16_t>(p, 1, dq_part, units, n, kv_part, true, st);
 }
 
 template <typename T, typename TG, int D>
 static hipError_t bwd_generic(Params p, int32_t max_len, void* ws, size_t ws_bytes, hipStream_t st) {
   const char* name = "attn_bwd_generic";
   bool done = false;
-  if constexpr (sizeof(T) == 4 && D == 128)
-    if (hipError_t e = bwd_units<TG>(p, max_len, ws, ws_bytes, name, st, &done); done || e != hipSuccess) return e;
+  if constexpr (sizeof(T) == 4)
+    if (hipError_t e = bwd_units<TG, D>(p, max_len, ws, ws_bytes, name, st, &done); done || e != hipSuccess) return e;
   if (hipError_t e = bwd_pair<T, TG, D>(p, max_len, ws, ws_bytes, name, st, &done); done || e != hipSuccess) return e;
   ProfScope prof_(name, st);
   static DeviceOnce once_kv;

@@ -69,22 +69,78 @@ def test_generic_kernel_edges(w):
     _show(w.name, rep)
 
 
-# fp32 at head dim 128 where dQ, dK and dV come from one kernel: ranges of stages that end inside a unit, cover several short ones (the
-# chunk's own pages) or start at one's first stage; a last unit that is not full; lists shorter than their stride; heads that do not divide 256.
+# fp32 where the products are formed in three bf16 terms per value, and dQ, dK and dV in one kernel: ranges of stages that end inside a unit, cover
+# several short ones (the chunk's own pages) or start at one's first stage; a last unit or tile of 32 keys that is not full; a last row tile that
+# is not; lists shorter than their stride; heads that do not divide 256; one split and many.
 UNITS_CASES = [
     Workload("f32_units_g7", 28, 4, 128, 128, 384, 128 * 16, 9, "f32", "f32", 0.088, extra_phys=2, boost_frac=0.2, seed=71),
     Workload("f32_units_p16_local", 8, 2, 128, 16, 544, 16 * 51, 13, "f32", "bf16", 0.088, extra_phys=1, seed=72),
     Workload("f32_units_short_list", 6, 3, 128, 64, 320, 64 * 24, 40, "f32", "f32", 0.088, seed=73),
     Workload("f32_units_nohist", 5, 5, 128, 32, 992, 992, 3, "f32", "f32", 0.088, seed=74),
     Workload("f32_units_p32_dense", 2, 1, 128, 32, 352, 32 * 150, None, "f32", "bf16", 0.088, seed=75),
+    Workload("f32_units_d64_g7", 14, 2, 64, 16, 624, 16 * 90, 22, "f32", "f32", 0.125, extra_phys=1, seed=76),
+    Workload("f32_units_d64_dense", 3, 3, 64, 128, 1024, 128 * 19, None, "f32", "bf16", 0.125, seed=77),
+    Workload("f32_units_d64_many_rows", 32, 8, 64, 64, 1088, 64 * 23, 2, "f32", "f32", 0.125, seed=78),
 ]
 
 
 @pytest.mark.parametrize("w", UNITS_CASES, ids=lambda w: w.name)
-def test_fp32_backward_in_one_kernel(w):
-    with pu.kernels_ran(("bwd_units",), absent=pu.MFMA_KERNELS + pu.SPLIT_KERNELS):
+def test_fp32_passes_in_terms(w):
+    with pu.kernels_ran(("kv_terms", "fwd_terms", "row_terms", "bwd_units"), absent=pu.MFMA_KERNELS + pu.SPLIT_KERNELS):
         rep = pu.full_parity(w, init_grad=0.25)
     _show(w.name, rep)
+
+
+# Against 64 bits: sums of fp32 products are 0.5 to 2.4e-6 off (2-norm) at these lengths; without one of the six products of terms a
+# product of two values is 2^-18 = 3.8e-6 (rms; up to 2^-16) off in S, which the softmax and the gradients of S amplify by |S| of 1 to 3.
+@pytest.mark.parametrize("w", [UNITS_CASES[2], UNITS_CASES[5]], ids=lambda w: w.name)
+def test_fp32_terms_hold_24_bits(w):
+    x = make_inputs(w, "cuda")
+    hx, sh = pu.host_inputs(x), pu.shape_of(w)
+    sel, cnt, _ = pu.gpu_select(w, x)
+    res = pu.gpu_fwd_bwd(w, x, sel, cnt)
+    ref = orc.attn_fwd_bwd(sh, hx["q"], hx["k_pool"], hx["v_pool"], hx["page_table"], hx["d_o"], sel.cpu().numpy(), cnt.cpu().numpy(), prec="f64")
+    for name in ("o", "dq", "dk_pool", "dv_pool"):
+        rel = pu.errors(pu.f32(res[name]), ref[name])[1]
+        print(w.name, name, f"{rel:.2e}", flush=True)
+        assert rel <= 2.5e-6, (name, rel)
+
+
+# Values at the edges of fp32 where products are formed in terms: what would round to an infinity as bf16, an infinity that gives its key
+# a weight of 0 (its terms times those of a finite value are NaN), one that makes a row NaN, and a NaN.
+@pytest.mark.parametrize("P", [16, 128])
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("what", ["huge", "weight_0", "inf", "nan"])
+def test_fp32_terms_of_values_at_the_edges(D, P, what):
+    C, n_past = 512, 2048 // P
+    w = Workload("edges", 8, 2, D, P, C, C + n_past * P, None, "f32", "f32", D ** -0.5, seed=79)
+    x = make_inputs(w, "cuda")
+    page = x["page_table"][n_past // 2].long()
+    k, q = x["k_pool"], x["q"]
+    if what == "huge":
+        k[page, :, 3, 0] = 3.4e38
+        q[..., 0] = -1
+    elif what == "weight_0":
+        k[page, :, 3, 0] = float("-inf")
+        q[..., 0].abs_().add_(0.01)
+    elif what == "inf":
+        q[100, 3, 5] = float("inf")
+    else:
+        k[page, 1, 3, 7] = float("nan")
+    desc = api.make_desc(q, k, w.N, w.sm_scale)
+    with pu.kernels_ran(("fwd_terms",), absent=()):
+        o, lse = api.paged_attn_fwd(desc, q, k, x["v_pool"], x["page_table"])
+    pages = x["page_table"].long()
+    mask = torch.arange(w.N)[None] <= (w.N - C + torch.arange(C))[:, None]
+    for h in range(w.Hq):
+        K, V = (x[n][pages, h // 4].reshape(-1, D).double().cpu() for n in ("k_pool", "v_pool"))
+        S = ((q[:, h].double().cpu() @ K.T) * w.sm_scale).masked_fill(~mask, float("-inf"))
+        want_o, want_lse = torch.softmax(S, 1) @ V, torch.logsumexp(S, 1)
+        bad = torch.isnan(want_o).any(1)
+        assert torch.equal(torch.isnan(o[:, h].cpu()).all(1), bad), (h, int(bad.sum()))
+        if what in ("huge", "weight_0"):
+            assert not bad.any()
+        assert pu.errors(o[~bad.cuda(), h].cpu(), want_o[~bad])[1] <= 5e-6 and pu.errors(lse[h].cpu()[~bad], want_lse[~bad])[1] <= 1e-6
 
 
 # bf16 tensors of shapes without kernels of their own: probabilities and dS keep 32 bits.  Against 64 bits with the same O and LSE

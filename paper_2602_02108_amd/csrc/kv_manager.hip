@@ -15,18 +15,18 @@
 
 namespace oomb {
 
-// chunk K / V [C][Hkv][D] (contiguous) -> pool page page_table[n_past + page of the chunk], one workgroup per (page, KV head), and (cache given) the
+// chunk K / V [C][Hkv][D] (contiguous) -> pool page page_table[n_past + page of the chunk], one workgroup per (page, KV head, slice of DW dims), and (cache given) the
 // page's mean while its keys are in LDS: one launch for both.  32 + 1 pages x 4 heads: 36 -> 6 us with the means, which used to
 // walk the pool once more, one thread per dim.
-template <typename T, int D>
+template <typename T, int D, int DW>
 __global__ __launch_bounds__(256) void kv_append_kernel(Params p, const T* __restrict__ kc, const T* __restrict__ vc, T* __restrict__ k_pool,
                                                         T* __restrict__ v_pool, float inv_p, float* __restrict__ cache) {
   extern __shared__ __align__(16) unsigned char lds[];
-  constexpr int VEC = Vec16<T>::N, GPR = D / VEC;
-  const int tau = blockIdx.x / p.Hkv, g = blockIdx.x - tau * p.Hkv, tid = threadIdx.x;
+  constexpr int VEC = Vec16<T>::N, GPR = DW / VEC, NS = D / DW;
+  const int b = blockIdx.x / NS, d0 = (blockIdx.x - b * NS) * DW, tau = b / p.Hkv, g = b - tau * p.Hkv, tid = threadIdx.x;
   const int64_t l = p.n_past + tau;
-  const int64_t src = ((int64_t)tau * p.P * p.Hkv + g) * D, stride = (int64_t)p.Hkv * D;
-  const int64_t dst = (int64_t)p.page_table[l] * p.pool_page_stride + (int64_t)g * p.pool_head_stride;
+  const int64_t src = ((int64_t)tau * p.P * p.Hkv + g) * D + d0, stride = (int64_t)p.Hkv * D;
+  const int64_t dst = (int64_t)p.page_table[l] * p.pool_page_stride + (int64_t)g * p.pool_head_stride + d0;
   const int total = p.P * GPR;
   for (int e0 = tid; e0 < total; e0 += 8 * 256) {   // (the loads of K and V are all in flight before the first store)
     uint4 a[8], b[8];
@@ -49,8 +49,8 @@ __global__ __launch_bounds__(256) void kv_append_kernel(Params p, const T* __res
   }
   if (!cache) return;
   __syncthreads();
-  float* out = cache + ((int64_t)l * p.Hkv + g) * D;
-  lds_row_sum<T, D>(p.P, lds, [&](int d, float sum) __attribute__((always_inline)) { out[d] = __fmul_rn(sum, inv_p); });
+  float* out = cache + ((int64_t)l * p.Hkv + g) * D + d0;
+  lds_row_sum<T, DW>(p.P, lds, [&](int d, float sum) __attribute__((always_inline)) { out[d] = __fmul_rn(sum, inv_p); });
 }
 
 // mean of logical pages [first, first + count) with 16-byte loads: a group of LPR lanes walks one (page, KV head)
@@ -101,13 +101,17 @@ __global__ void local_page_list_kernel(int64_t n_past, int64_t n, int32_t window
   if (threadIdx.x == 0) sel_count[g] = cnt;
 }
 
-template <typename T, int D>
+template <typename T, int D, int DW>
 static hipError_t append(const Params& p, const void* kc, const void* vc, void* k_pool, void* v_pool, float* cache, hipStream_t st) {
   ProfScope prof_("kv_append", st);
-  const size_t lds = cache ? (size_t)p.P * D * sizeof(T) : 0;   // (at most 64 KiB)
-  kv_append_kernel<T, D><<<dim3((unsigned)p.m * p.Hkv), dim3(256), lds, st>>>(p, (const T*)kc, (const T*)vc, (T*)k_pool, (T*)v_pool,
-                                                                                      1.0f / (float)p.P, cache);
+  const size_t lds = cache ? (size_t)p.P * DW * sizeof(T) : 0;   // (at most 16 KiB)
+  kv_append_kernel<T, D, DW><<<dim3((unsigned)p.m * p.Hkv * (D / DW)), dim3(256), lds, st>>>(p, (const T*)kc, (const T*)vc, (T*)k_pool, (T*)v_pool,
+                                                                                             1.0f / (float)p.P, cache);
   return hipGetLastError();
+}
+template <typename T, int D>
+static hipError_t append(const Params& p, const void* kc, const void* vc, void* k_pool, void* v_pool, float* cache, hipStream_t st) {
+  return page_in_slices<T>(p) ? append<T, D, LINE_DIMS<T>>(p, kc, vc, k_pool, v_pool, cache, st) : append<T, D, D>(p, kc, vc, k_pool, v_pool, cache, st);
 }
 hipError_t launch_kv_append(const Params& p, bool is_bf16, const void* kc, const void* vc, void* k_pool, void* v_pool,
                             float* cache, hipStream_t st) {

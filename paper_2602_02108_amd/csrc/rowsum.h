@@ -139,4 +139,12 @@ __device__ __forceinline__ void tile_row_sum(const T* base, int64_t stride, int 
   lds_row_sum<T, D>(count, lds, out);
 }
 
+// Dims of a 128-byte line, and whether a page's tile is cut into slices of that width, a workgroup each.  What bounds a short call is how fast one
+// compute unit takes in its tile (32 KiB: 3 us of a launch of 5 to 6), so more of them take less each; the 64 KiB of an fp32 page also left two
+// workgroups to a compute unit.  Per launch, whole -> in slices: 28 query heads, one page of 128 in bf16 6.1 -> 5.1 us, the append of 4 KV heads with
+// means 7.1 -> 6.1; fp32, 4 query pages and 124 past ones 14.7 -> 10.3 us (608 tiles).  Where the tiles fill the chip by themselves
+// nothing changes (896 bf16 tiles: 9.1, 9.2).  Tiles below 16 KiB hold a few loads per thread as they are.
+template <typename T> constexpr int LINE_DIMS = 128 / (int)sizeof(T);
+template <typename T> static inline bool page_in_slices(const Params& p) { return p.D > LINE_DIMS<T> && (size_t)p.P * p.D * sizeof(T) >= 16384; }
+
 }  // namespace oomb

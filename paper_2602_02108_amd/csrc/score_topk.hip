@@ -16,24 +16,29 @@
 
 namespace oomb {
 
-// Step S1a: A[h][tau][d] = sum over the P tokens of query page tau of Q, one workgroup per (query page, head); with
-// means != nullptr the workgroups past Hq * m compute S2 for one (past page, KV head) each, means[l][g][d] as the paged
+// Step S1a: A[h][tau][d] = sum over the P tokens of query page tau of Q, one workgroup per (query page, head, slice of DW dims); with
+// means != nullptr the workgroups past those compute S2 for one (past page, KV head, slice) each, means[l][g][d] as the paged
 // manager caches them (short histories, whose pages are too few to fill the chip page by page).
-template <typename T, int D>
+template <typename T, int D, int DW>
 __global__ __launch_bounds__(256) void qpool_partial_kernel(Params p, float* __restrict__ A, float* __restrict__ means, float inv_p) {
   extern __shared__ __align__(16) unsigned char lds[];
-  const int b = blockIdx.x, n_q = p.Hq * p.m;
+  constexpr int NS = D / DW;
+  const int b = blockIdx.x / NS, d0 = (blockIdx.x - b * NS) * DW, n_q = p.Hq * p.m;
   if (b < n_q) {
     const int tau = b / p.Hq, h = b - tau * p.Hq;
-    float* out = A + ((int64_t)h * p.m + tau) * D;
-    tile_row_sum<T, D>((const T*)p.q + (int64_t)tau * p.P * p.q_tok_stride + (int64_t)h * p.q_head_stride, p.q_tok_stride, p.P, lds,
-                       [&](int d, float sum) __attribute__((always_inline)) { out[d] = sum; });
+    float* out = A + ((int64_t)h * p.m + tau) * D + d0;
+    tile_row_sum<T, DW>((const T*)p.q + (int64_t)tau * p.P * p.q_tok_stride + (int64_t)h * p.q_head_stride + d0, p.q_tok_stride, p.P, lds,
+                        [&](int d, float sum) __attribute__((always_inline)) { out[d] = sum; });
   } else {
     const int l = (b - n_q) / p.Hkv, g = (b - n_q) - l * p.Hkv;
-    float* out = means + ((int64_t)l * p.Hkv + g) * D;
-    tile_row_sum<T, D>((const T*)p.k_pool + (int64_t)p.page_table[l] * p.pool_page_stride + (int64_t)g * p.pool_head_stride, p.pool_tok_stride, p.P, lds,
-                       [&](int d, float sum) __attribute__((always_inline)) { out[d] = __fmul_rn(sum, inv_p); });
+    float* out = means + ((int64_t)l * p.Hkv + g) * D + d0;
+    tile_row_sum<T, DW>((const T*)p.k_pool + (int64_t)p.page_table[l] * p.pool_page_stride + (int64_t)g * p.pool_head_stride + d0, p.pool_tok_stride, p.P, lds,
+                        [&](int d, float sum) __attribute__((always_inline)) { out[d] = __fmul_rn(sum, inv_p); });
   }
+}
+template <typename T, int D, int DW> static void run_qpool_partial(const Params& p, float* A, float* means, float inv_p, hipStream_t st) {
+  const int64_t tiles = (int64_t)p.Hq * p.m + (means ? p.n_past * p.Hkv : 0);
+  qpool_partial_kernel<T, D, DW><<<dim3((unsigned)(tiles * (D / DW))), dim3(256), (size_t)p.P * DW * sizeof(T), st>>>(p, A, means, inv_p);
 }
 
 // Step S1b: qbar[g][d] = (sum over tau (outer), heads of g (inner) of A) * r.  The sum of a (g, d) is one sequential chain
@@ -557,8 +562,8 @@ static hipError_t launch_scoring(const Params& p, int32_t top_k, int32_t* sel, i
   const float inv_p = 1.0f / (float)p.P, r = 1.0f / (float)((int64_t)p.C * p.G);
   {
     ProfScope prof_("qpool_partial", st);
-    const unsigned blocks = (unsigned)((int64_t)p.Hq * p.m + (means ? p.n_past * p.Hkv : 0));
-    qpool_partial_kernel<T, D><<<dim3(blocks), dim3(256), (size_t)p.P * D * sizeof(T), st>>>(p, A, means, inv_p);
+    if (page_in_slices<T>(p)) run_qpool_partial<T, D, LINE_DIMS<T>>(p, A, means, inv_p, st);
+    else run_qpool_partial<T, D, D>(p, A, means, inv_p, st);
   }
   if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
   if (L.small) {

@@ -91,3 +91,21 @@ def test_local_page_list_and_attention_over_it(name, window):
     pu.check("dQ", pu.f32(res["dq"]), ref["dq"], dt)
     pu.check("dK", pu.f32(res["dk_pool"]), ref["dk_pool"], dt)
     pu.check("dV", pu.f32(res["dv_pool"]), ref["dv_pool"], dt)
+
+
+# A page's tile of 16 KiB and more is summed and appended in slices of a 128-byte line, a smaller one whole: either side of that line for
+# both types and head dims, with the widest tile (64 KiB) and rows of exactly one line (never cut).
+@pytest.mark.parametrize("dtype,D,P", [("bf16", 128, 128), ("bf16", 128, 64), ("bf16", 128, 32), ("bf16", 64, 128), ("f32", 128, 128), ("f32", 128, 32),
+                                       ("f32", 128, 16), ("f32", 64, 64), ("f32", 64, 32)])
+def test_sums_in_slices_are_bit_exact(dtype, D, P):
+    w = Workload("slices", 6, 3, D, P, 3 * P, 14 * P, 4, dtype, "f32", 0.088, extra_phys=2, seed=31)
+    test_append_and_page_means_are_bit_exact(w)
+    x = make_inputs(w, "cuda")
+    sh, hx = pu.shape_of(w), pu.host_inputs(x)
+    desc = api.make_desc(x["q"], x["k_pool"], w.N, w.sm_scale, torch_dtype(w.grad_dtype))
+    scores = torch.empty((w.Hkv, sh.n_past), dtype=torch.float32, device="cuda")
+    sel, cnt = api.page_score_topk(desc, x["q"], x["k_pool"], x["page_table"], w.top_k, scores_out=scores)
+    torch.cuda.synchronize()
+    osel, ocnt, oscores = pu.oracle_select(w, hx)
+    assert np.array_equal(scores.cpu().numpy().view(np.uint32), oscores.view(np.uint32)), "scores differ"
+    assert np.array_equal(cnt.cpu().numpy(), ocnt) and np.array_equal(sel.cpu().numpy(), osel)

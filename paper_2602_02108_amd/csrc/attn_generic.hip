@@ -671,28 +671,30 @@ __global__ __launch_bounds__(256 * KH, 2) void fwd_generic_kernel(Params p, int3
   }
 }
 
-// Combine kernels: a workgroup takes a block of 32 rows, wave w the groups w, w + 4, ..  The sums go through LDS, so that the
+// Combine kernels: a workgroup of NW waves takes a block of 32 rows, wave w the groups w, w + NW, ..  The sums go through LDS, so that the
 // results leave in whole rows instead of the register order of the partials.
-template <int D> constexpr int GN_GW = D / 32;   // groups per wave
+template <int D, int NW = 4> constexpr int GN_GW = D / 8 / NW;   // groups per wave
 // in: the sums of this thread's groups; then f(k, row, dim, value) for the row pieces this thread writes, piece k = float4
-// k * 256 + thread of the block.  redo: rows whose sums are not finite are left out; returns them, a bit each.
-template <int D> struct GnRowsLds { float4 v[8 * D]; uint32_t bad[4]; };
-template <typename L, int D, typename F> __device__ __forceinline__ uint32_t gn_rows_out(GnRowsLds<D>& lds, const float4 (&v)[GN_GW<D>], bool redo, F&& f) {
+// k * 64 NW + thread of the block.  redo: rows whose sums are not finite are left out; returns them, a bit each.
+template <int D> struct GnRowsLds { float4 v[8 * D]; uint32_t bad[8]; };
+template <typename L, int D, int NW = 4, typename F> __device__ __forceinline__ uint32_t gn_rows_out(GnRowsLds<D>& lds, const float4 (&v)[GN_GW<D, NW>], bool redo, F&& f) {
   auto& sh = lds.v;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, r = lane & 31;
   constexpr int GPR = D / 4;   // float4s per row
 #pragma unroll
-  for (int j = 0; j < GN_GW<D>; ++j) sh[r * GPR + ((part_group_dim<L, D>(wave + 4 * j, lane >> 5) >> 2) ^ (r & 15))] = v[j];
+  for (int j = 0; j < GN_GW<D, NW>; ++j) sh[r * GPR + ((part_group_dim<L, D>(wave + NW * j, lane >> 5) >> 2) ^ (r & 15))] = v[j];
   float z = 0.f;
 #pragma unroll
-  for (int j = 0; j < GN_GW<D>; ++j) z = __builtin_fmaf(v[j].x, 0.f, __builtin_fmaf(v[j].y, 0.f, __builtin_fmaf(v[j].z, 0.f, __builtin_fmaf(v[j].w, 0.f, z))));
+  for (int j = 0; j < GN_GW<D, NW>; ++j) z = __builtin_fmaf(v[j].x, 0.f, __builtin_fmaf(v[j].y, 0.f, __builtin_fmaf(v[j].z, 0.f, __builtin_fmaf(v[j].w, 0.f, z))));
   const uint32_t mine = gn_either_half(redo && z != 0.f);
   if (lane == 0) lds.bad[wave] = mine;
   __syncthreads();
-  const uint32_t bad = lds.bad[0] | lds.bad[1] | lds.bad[2] | lds.bad[3];
+  uint32_t bad = 0;
 #pragma unroll
-  for (int k = 0; k < GN_GW<D>; ++k) {
-    const int e = k * 256 + threadIdx.x, row = e / GPR, c = e % GPR;
+  for (int w = 0; w < NW; ++w) bad |= lds.bad[w];
+#pragma unroll
+  for (int k = 0; k < GN_GW<D, NW>; ++k) {
+    const int e = k * 64 * NW + threadIdx.x, row = e / GPR, c = e % GPR;
     if (!((bad >> row) & 1)) f(k, row, 4 * c, sh[row * GPR + (c ^ (row & 15))]);
   }
   return __builtin_amdgcn_readfirstlane(bad);
@@ -751,11 +753,15 @@ __device__ __forceinline__ void gn_sum_parts(const float* part, int64_t block, i
 }
 
 // O = sum of the splits' O rescaled to the common maximum / sum of their l.  L: the element type in whose register order the partial sums lie.
+// What bounds it is how much a compute unit has in flight: eight waves with eight splits each.  Against four waves with four splits, whole passes: 28 / 4
+// heads, one page, 9 splits (112 blocks) 52.5 -> 51.8 us; 14 / 2 heads, two pages 54.6 -> 53.8; 14 / 2 heads of 64 dims 34.15 -> 33.9; at 448
+// blocks the same.
+constexpr int COMBINE_WAVES = 8;
 template <typename T, int D, typename L = T>
-__global__ __launch_bounds__(256) void fwd_combine_kernel(Params p, int32_t tiles, int32_t n_split, const float* __restrict__ part,
+__global__ __launch_bounds__(64 * COMBINE_WAVES) void fwd_combine_kernel(Params p, int32_t tiles, int32_t n_split, const float* __restrict__ part,
                                                           const float2* __restrict__ part_ml, int lp) {
   __shared__ GnRowsLds<D> sh;
-  constexpr int GW = GN_GW<D>;
+  constexpr int NW = COMBINE_WAVES, GW = GN_GW<D, NW>, N = 8;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int64_t block = blockIdx.x, blocks = (int64_t)p.Hkv * tiles * 4;
   const int64_t at = (block * (D / 8) + wave) * 64 + lane;
@@ -764,44 +770,48 @@ __global__ __launch_bounds__(256) void fwd_combine_kernel(Params p, int32_t tile
   float4 acc[GW];
 #pragma unroll
   for (int j = 0; j < GW; ++j) acc[j] = make_float4(0.f, 0.f, 0.f, 0.f);
-  for (int s0 = 0; s0 < n_split; s0 += 4) {   // four splits in flight
-    float2 ml[4];
-    float4 v[GW][4];
+  for (int s0 = 0; s0 < n_split; s0 += N) {   // N splits in flight
+    float2 ml[N];
+    float4 v[GW][N];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
+    for (int u = 0; u < N; ++u) {
       ml[u] = make_float2(-INFINITY, 0.f);
       if (s0 + u < n_split) {
         ml[u] = part_ml[((s0 + u) * blocks + block) * 32 + (lane & 31)];
 #pragma unroll
-        for (int j = 0; j < GW; ++j) v[j][u] = gn_load_part(part, at + j * 256 + (s0 + u) * blocks * (D / 8) * 64);
+        for (int j = 0; j < GW; ++j) v[j][u] = gn_load_part(part, at + j * 64 * NW + (s0 + u) * blocks * (D / 8) * 64);
       }
     }
-    const float m_new = fmaxf(fmaxf(fmaxf(ml[0].x, ml[1].x), fmaxf(ml[2].x, ml[3].x)), M);
-    const float w0 = __builtin_amdgcn_exp2f((M - m_new) * c);
-    M = m_new;
-    l_sum *= w0;
 #pragma unroll
-    for (int j = 0; j < GW; ++j) { acc[j].x *= w0; acc[j].y *= w0; acc[j].z *= w0; acc[j].w *= w0; }
+    for (int u0 = 0; u0 < N; u0 += 4) {   // (added four at a time)
+      if (s0 + u0 >= n_split) break;
+      const float m_new = fmaxf(fmaxf(fmaxf(ml[u0].x, ml[u0 + 1].x), fmaxf(ml[u0 + 2].x, ml[u0 + 3].x)), M);
+      const float w0 = __builtin_amdgcn_exp2f((M - m_new) * c);
+      M = m_new;
+      l_sum *= w0;
 #pragma unroll
-    for (int u = 0; u < 4; ++u)
-      if (s0 + u < n_split) {
-        const float w = __builtin_amdgcn_exp2f((ml[u].x - m_new) * c);
-        l_sum += ml[u].y * w;
+      for (int j = 0; j < GW; ++j) { acc[j].x *= w0; acc[j].y *= w0; acc[j].z *= w0; acc[j].w *= w0; }
 #pragma unroll
-        for (int j = 0; j < GW; ++j) { acc[j].x += v[j][u].x * w; acc[j].y += v[j][u].y * w; acc[j].z += v[j][u].z * w; acc[j].w += v[j][u].w * w; }
-      }
+      for (int u = u0; u < u0 + 4; ++u)
+        if (s0 + u < n_split) {
+          const float w = __builtin_amdgcn_exp2f((ml[u].x - m_new) * c);
+          l_sum += ml[u].y * w;
+#pragma unroll
+          for (int j = 0; j < GW; ++j) { acc[j].x += v[j][u].x * w; acc[j].y += v[j][u].y * w; acc[j].z += v[j][u].z * w; acc[j].w += v[j][u].w * w; }
+        }
+    }
   }
   const float inv = 1.f / l_sum;
 #pragma unroll
   for (int j = 0; j < GW; ++j) { acc[j].x *= inv; acc[j].y *= inv; acc[j].z *= inv; acc[j].w *= inv; }
   int i, h;
-  uint32_t bad = gn_rows_out<L, D>(sh, acc, true, [&](int, int row, int d, const float4& r) __attribute__((always_inline)) {
+  uint32_t bad = gn_rows_out<L, D, NW>(sh, acc, true, [&](int, int row, int d, const float4& r) __attribute__((always_inline)) {
     if (gn_out_row(p, tiles, block, row, i, h))
       part_store4<T>((T*)p.o + (int64_t)i * p.q_tok_stride + (int64_t)h * p.q_head_stride + d, r.x, r.y, r.z, r.w);
   });
   if (threadIdx.x < 32 && gn_out_row(p, tiles, block, threadIdx.x, i, h))
     p.lse[(int64_t)h * p.C + i] = gn_lse(p, M, l_sum);
-  for (bad &= 0xffu << (8 * wave); bad; bad &= bad - 1) {   // (eight rows per wave)
+  for (bad &= 0xfu << (4 * wave); bad; bad &= bad - 1) {   // (four rows per wave)
     const int x = __builtin_ctz(bad);
     if (gn_out_row(p, tiles, block, x, i, h)) {
       if constexpr (sizeof(L) != sizeof(T)) gn_redo_terms<D>(gn_params_again(), h / p.G, i, h, lp, lane, gn_lane(M, x), gn_lane(l_sum, x));
@@ -1398,7 +1408,7 @@ __global__ __launch_bounds__(256, (D == 128 || sizeof(T) == 4 ? 1 : 2)) void dkv
   dkv_body<T, TG, D, false, NT>(p, smem, blockIdx.x, n_split, lp, part);
 }
 
-// The whole backward of fp32 tensors at head dim 128: five products per pair instead of the seven of two kernels, all but dQ's as products of three
+// The whole backward of fp32 tensors: five products per pair instead of the seven of two kernels, all but dQ's as products of three
 // bf16 terms.  A unit is 128 list tokens, 32 per wave: their K and V stay in registers (as terms), the rows of the head stream through
 // LDS in stages of 32, as terms too (row_terms_kernel).  dS goes through LDS, dQ of a stage is left as one fp32 partial sum per unit.  One wave per
 // SIMD (512 registers); the vector work of a product runs between the matrix instructions of the next one.
@@ -1977,7 +1987,7 @@ static hipError_t fwd_generic(const Params& p, int32_t max_len, void* ws, size_t
   ProfScope prof_(name, st);
   hipError_t e = sp.groups == 2 ? fwd_launch<T, D, 2, NT>(p, tiles, ns, len, part, ml, st) : fwd_launch<T, D, 1, NT>(p, tiles, ns, len, part, ml, st);
   if (e == hipSuccess && ns > 1) {
-    fwd_combine_kernel<T, D><<<dim3((unsigned)(gn_row_blocks(p))), dim3(256), 0, st>>>(p, tiles, ns, part, ml, __builtin_ctz(p.P));
+    fwd_combine_kernel<T, D><<<dim3((unsigned)(gn_row_blocks(p))), dim3(64 * COMBINE_WAVES), 0, st>>>(p, tiles, ns, part, ml, __builtin_ctz(p.P));
     e = hipGetLastError();
   }
   return e;
@@ -1999,7 +2009,7 @@ template <int D> static hipError_t fwd_terms(const Params& p, int32_t max_len, v
   if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
   { ProfScope fwd_("fwd_terms", st); fwd_terms_kernel<D><<<dim3((unsigned)(tiles * p.Hkv * f.n)), dim3(256), F::LDS, st>>>(p, tiles, f.n, lp, max_len, n_tiles, img, part, ml); }
   if (hipError_t e = hipGetLastError(); e != hipSuccess || f.n == 1) return e;
-  fwd_combine_kernel<float, D, bf16_t><<<dim3((unsigned)(gn_row_blocks(p))), dim3(256), 0, st>>>(p, tiles, f.n, part, ml, lp);
+  fwd_combine_kernel<float, D, bf16_t><<<dim3((unsigned)(gn_row_blocks(p))), dim3(64 * COMBINE_WAVES), 0, st>>>(p, tiles, f.n, part, ml, lp);
   return hipGetLastError();
 }
 hipError_t launch_fwd_generic(const Params& p, bool bf, int32_t max_len, void* ws, size_t ws_bytes, hipStream_t st) {

@@ -25,7 +25,7 @@
 // bf16 the exposed vector work and LDS latency of one or two waves per SIMD; short calls the number
 // of workgroups, which is why the streamed side is cut into splits whose partial sums a second
 // kernel combines in a fixed order.  Measured against one wave per query row (per key in dK / dV)
-// with plain fp32 arithmetic: 28 / 4 heads fp32, chunk 512, 16 + 4 pages of 128: 41.5 -> 0.84 ms
+// with plain fp32 arithmetic: 28 / 4 heads fp32, chunk 512, 16 + 4 pages of 128: 41.5 -> 0.43 ms
 // (59 GFLOP); 8 / 2 heads bf16, chunk 1088, 24 + 17 pages of 64: 18.4 -> 0.15 ms (32 GFLOP).
 #include "mfma_common.h"
 #include "launch.h"
@@ -724,32 +724,32 @@ __device__ __forceinline__ float4 gn_load_part(const float* part, int64_t at) {
 }
 // sums of n partials `step` float4s apart for the thread's groups of a block, at most four of each in flight, added in order
 // `meanwhile` runs once, while the first of them are on their way.
-template <int D, int N, typename F>
-__device__ __forceinline__ void gn_add_parts(const float* part, int64_t at, int64_t step, float4 (&a)[GN_GW<D>], F&& meanwhile) {
-  float4 v[GN_GW<D>][N];
+template <int D, int NW, int N, typename F>
+__device__ __forceinline__ void gn_add_parts(const float* part, int64_t at, int64_t step, float4 (&a)[GN_GW<D, NW>], F&& meanwhile) {
+  float4 v[GN_GW<D, NW>][N];
 #pragma unroll
   for (int u = 0; u < N; ++u)
 #pragma unroll
-    for (int j = 0; j < GN_GW<D>; ++j) v[j][u] = gn_load_part(part, at + j * 256 + u * step);
+    for (int j = 0; j < GN_GW<D, NW>; ++j) v[j][u] = gn_load_part(part, at + j * 64 * NW + u * step);
   __builtin_amdgcn_sched_barrier(0);
   meanwhile();
 #pragma unroll
   for (int u = 0; u < N; ++u)
 #pragma unroll
-    for (int j = 0; j < GN_GW<D>; ++j) { a[j].x += v[j][u].x; a[j].y += v[j][u].y; a[j].z += v[j][u].z; a[j].w += v[j][u].w; }
+    for (int j = 0; j < GN_GW<D, NW>; ++j) { a[j].x += v[j][u].x; a[j].y += v[j][u].y; a[j].z += v[j][u].z; a[j].w += v[j][u].w; }
 }
-template <int D, typename F>
-__device__ __forceinline__ void gn_sum_parts(const float* part, int64_t block, int64_t step, int n, float4 (&a)[GN_GW<D>], F&& meanwhile) {
+template <int D, int NW, typename F>
+__device__ __forceinline__ void gn_sum_parts(const float* part, int64_t block, int64_t step, int n, float4 (&a)[GN_GW<D, NW>], F&& meanwhile) {
   int64_t at = (block * (D / 8) + (threadIdx.x >> 6)) * 64 + (threadIdx.x & 63);
 #pragma unroll
-  for (int j = 0; j < GN_GW<D>; ++j) a[j] = make_float4(0.f, 0.f, 0.f, 0.f);
+  for (int j = 0; j < GN_GW<D, NW>; ++j) a[j] = make_float4(0.f, 0.f, 0.f, 0.f);
   auto nothing = [] {};
   const int first = n & 3;   // (the odd ones first)
-  if (first == 3) gn_add_parts<D, 3>(part, at, step, a, meanwhile);
-  else if (first == 2) gn_add_parts<D, 2>(part, at, step, a, meanwhile);
-  else if (first == 1) gn_add_parts<D, 1>(part, at, step, a, meanwhile);
-  else gn_add_parts<D, 4>(part, at, step, a, meanwhile);
-  for (int done = first ? first : 4; done < n; done += 4) gn_add_parts<D, 4>(part, at + done * step, step, a, nothing);
+  if (first == 3) gn_add_parts<D, NW, 3>(part, at, step, a, meanwhile);
+  else if (first == 2) gn_add_parts<D, NW, 2>(part, at, step, a, meanwhile);
+  else if (first == 1) gn_add_parts<D, NW, 1>(part, at, step, a, meanwhile);
+  else gn_add_parts<D, NW, 4>(part, at, step, a, meanwhile);
+  for (int done = first ? first : 4; done < n; done += 4) gn_add_parts<D, NW, 4>(part, at + done * step, step, a, nothing);
 }
 
 // O = sum of the splits' O rescaled to the common maximum / sum of their l.  L: the element type in whose register order the partial sums lie.
@@ -1681,14 +1681,18 @@ __global__ __launch_bounds__(256, (D == 128 || sizeof(T) == 4 ? 1 : 2)) void bwd
 
 // What is left of a backward with splits, in one launch: workgroups below dq_blocks add the dQ partials, the others
 // add the slices of a dK / dV unit to the pool.
-template <typename T, typename TG, int D, typename L = T>
-__global__ __launch_bounds__(256) void bwd_finish_kernel(Params p, int32_t tiles, int32_t dq_split, const float* __restrict__ dq_part,
+// Eight waves per block (NW) keep more loads in flight where there are few blocks: 14 / 2 heads, two pages, 53.3 -> 52.2 us a pass; 8 / 2 heads, 17 + 24 pages of
+// 64: 145.3 -> 144.3; 6 / 2 heads, 93 pages (1700 blocks): 250.6 -> 249.3.  At 5000 blocks it makes no difference, and where many
+// more fill the chip four waves are faster (4096 tokens of 28 / 4 heads with a list per page: 91 us against 98).
+constexpr int64_t FINISH_FEW = 4096;
+template <typename T, typename TG, int D, typename L, int NW>
+__global__ __launch_bounds__(64 * NW) void bwd_finish_kernel(Params p, int32_t tiles, int32_t dq_split, const float* __restrict__ dq_part,
                                                          int32_t dq_blocks, int32_t kv_split, const float* __restrict__ kv_part, int lp,
                                                          int redo_keys) {
   constexpr bool UNITS = sizeof(L) != sizeof(T);   // the partial sums are those of bwd_units_kernel
   __shared__ GnRowsLds<D> sh;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  float4 a[GN_GW<D>];
+  float4 a[GN_GW<D, NW>];
   if ((int32_t)blockIdx.x < dq_blocks) {
     const int64_t blocks = (int64_t)p.Hkv * tiles * 4;
     if constexpr (UNITS) {   // a partial sum per unit that sees the block: the first ones of the list
@@ -1698,14 +1702,14 @@ __global__ __launch_bounds__(256) void bwd_finish_kernel(Params p, int32_t tiles
         dq_split += __builtin_popcountll(__ballot(u + lane < n && gn_first_stage(p, gb, (u + lane) << (7 - lp), lp) <= s));
       dq_split = __builtin_amdgcn_readfirstlane(dq_split) * GnU<D>::PARTS;
     }
-    gn_sum_parts<D>(dq_part, blockIdx.x, blocks * (D / 8) * 64, dq_split, a, [] {});
+    gn_sum_parts<D, NW>(dq_part, blockIdx.x, blocks * (D / 8) * 64, dq_split, a, [] {});
     const float sc = p.sm_scale;
     int i, h;
-    uint32_t bad = gn_rows_out<L, D>(sh, a, true, [&](int, int row, int d, const float4& r) __attribute__((always_inline)) {
+    uint32_t bad = gn_rows_out<L, D, NW>(sh, a, true, [&](int, int row, int d, const float4& r) __attribute__((always_inline)) {
       if (gn_out_row(p, tiles, blockIdx.x, row, i, h))
         part_store4<T>((T*)p.d_q + (int64_t)i * p.q_tok_stride + (int64_t)h * p.q_head_stride + d, r.x * sc, r.y * sc, r.z * sc, r.w * sc);
     });
-    for (bad &= 0xffu << (8 * wave); bad; bad &= bad - 1)
+    for (bad &= ((1u << 32 / NW) - 1) << (32 / NW * wave); bad; bad &= bad - 1)
       if (gn_out_row(p, tiles, blockIdx.x, __builtin_ctz(bad), i, h))
         gn_redo_row<T, D, true>(gn_params_again(), h / p.G, i, h, lp, lane, p.lse[(int64_t)h * p.C + i] * 1.4426950408889634f, sc, gn_delta<T, D>(p, i, h));
     return;
@@ -1748,25 +1752,25 @@ __global__ __launch_bounds__(256) void bwd_finish_kernel(Params p, int32_t tiles
   }
   // The block's 32 keys lie in one page, or in two of 16 tokens.  Its rows of the pool are looked up and read behind the loads
   // of the slices: in front of them the chain list -> page table -> pool would hold those back.
-  TG* dst[GN_GW<D>];
-  float4 old[GN_GW<D>];
-  gn_sum_parts<D>(kv_part, slot * 2 * nb + wb, next * 2 * nb * (D / 8) * 64, kv_split, a, [&]() __attribute__((always_inline)) {
+  TG* dst[GN_GW<D, NW>];
+  float4 old[GN_GW<D, NW>];
+  gn_sum_parts<D, NW>(kv_part, slot * 2 * nb + wb, next * 2 * nb * (D / 8) * 64, kv_split, a, [&]() __attribute__((always_inline)) {
     TG* const pool = (TG*)(which == 0 ? p.dk_pool : p.dv_pool) + (int64_t)g * p.pool_head_stride;
     const bool two = lp == 4 && !p.qp && e0 + 1 < list_len(p, g);
     TG* const page0 = pool + (int64_t)p.page_table[owned_at(p, g, e0)] * p.pool_page_stride;
     TG* const page1 = two ? pool + (int64_t)p.page_table[owned_at(p, g, e0 + 1)] * p.pool_page_stride : nullptr;
 #pragma unroll
-    for (int k = 0; k < GN_GW<D>; ++k) {
-      const int x = k * 256 + threadIdx.x, kq = 32 * kb + x / (D / 4);
+    for (int k = 0; k < GN_GW<D, NW>; ++k) {
+      const int x = k * 64 * NW + threadIdx.x, kq = 32 * kb + x / (D / 4);
       TG* const page = lp == 4 && (kq & 16) ? page1 : page0;
       dst[k] = page ? page + (int64_t)(kq & (p.P - 1)) * p.pool_tok_stride + 4 * (x % (D / 4)) : nullptr;
       if (page) old[k] = part_load4<TG>(dst[k]);
     }
   });
-  uint32_t bad = gn_rows_out<L, D>(sh, a, redo_keys, [&](int k, int, int, const float4& r) __attribute__((always_inline)) {
+  uint32_t bad = gn_rows_out<L, D, NW>(sh, a, redo_keys, [&](int k, int, int, const float4& r) __attribute__((always_inline)) {
     if (dst[k]) part_store4<TG>(dst[k], old[k].x + r.x, old[k].y + r.y, old[k].z + r.z, old[k].w + r.w);
   });
-  for (bad &= 0xffu << (8 * wave); bad; bad &= bad - 1) {
+  for (bad &= ((1u << 32 / NW) - 1) << (32 / NW * wave); bad; bad &= bad - 1) {
     const int32_t x = __builtin_ctz(bad), k = 32 * kb + x, e = e0 + (p.qp ? 0 : x >> lp);
     if (p.qp ? k < p.P : e < list_len(p, g)) gn_redo_key<T, TG, D>(gn_params_again(), g, e, k & (p.P - 1), which == 0, lp, lane);
   }
@@ -2054,8 +2058,12 @@ static hipError_t bwd_finish(const Params& p, int32_t dq_split, const float* dq_
   const int32_t dq_blocks = dq_split > 1 || sizeof(L) != sizeof(T) ? (int32_t)(gn_row_blocks(p)) : 0;
   const int64_t blocks = dq_blocks + (int64_t)kv_units * p.Hkv * 2 * part_key_blocks(p);
   if (blocks <= 0) return hipSuccess;
-  bwd_finish_kernel<T, TG, D, L><<<dim3((unsigned)blocks), dim3(256), 0, st>>>(p, gn_tiles(p.C, p.G, p.P, p.m, p.qp), dq_split, dq_part, dq_blocks, kv_split,
-                                                                            kv_part, __builtin_ctz(p.P), redo_keys);
+  auto run = [&](auto kernel, unsigned waves) {
+    kernel<<<dim3((unsigned)blocks), dim3(64 * waves), 0, st>>>(p, gn_tiles(p.C, p.G, p.P, p.m, p.qp), dq_split, dq_part, dq_blocks, kv_split, kv_part,
+                                                                __builtin_ctz(p.P), redo_keys);
+  };
+  if (blocks <= FINISH_FEW) run(bwd_finish_kernel<T, TG, D, L, 8>, 8);
+  else run(bwd_finish_kernel<T, TG, D, L, 4>, 4);
   return hipGetLastError();
 }
 // (the dK / dV slices of pages with kernels of their own: keys are left as those give them)

@@ -456,37 +456,6 @@ __device__ __forceinline__ void gn_redo_row(const Params& p, int g, int i, int h
 #pragma unroll
   for (int k = 0; k < D / 64; ++k) Elem<T>::store(dst + 64 * k + lane, acc[k] * scale);
 }
-// O of one fp32 row whose products were formed in terms (fwd_terms_kernel), m and l its softmax statistics there.  l is NaN where a product was not finite
-// there: infinities times the terms of a finite value are NaN, or the true value is not finite either.  Then the statistics and LSE are
-// formed anew from fp32 products.
-__device__ __forceinline__ float gn_lse(const Params& p, float m, float l);
-__device__ __forceinline__ float gn_lowest(const Params& p);
-template <int D> __device__ __forceinline__ void gn_redo_terms(const Params& p, int g, int i, int h, int lp, int lane, float m, float l) {
-  const float c = p.sm_scale * 1.4426950408889634f;
-  if (l != l) {
-    const int lid = list_id(p, g, i);
-    const int64_t roff = (int64_t)i * p.q_tok_stride + (int64_t)h * p.q_head_stride, a = p.N - p.C + i;
-    const int32_t n_ent = visible_len(p, lid, a >> lp, lane);
-    int32_t V = n_ent << lp;
-    if (n_ent > 0 && list_at(p, lid, n_ent - 1) == (int32_t)(a >> lp)) V -= p.P - 1 - (int32_t)(a & (p.P - 1));
-    m = gn_lowest(p);
-    l = 0.f;
-    for (int32_t t = lane; t < V; t += 64) {
-      const int64_t off = (int64_t)p.page_table[list_at(p, lid, t >> lp)] * p.pool_page_stride + (int64_t)g * p.pool_head_stride + (int64_t)(t & (p.P - 1)) * p.pool_tok_stride;
-      const float s = gn_row_dot<float, D>((const float*)p.q + roff, (const float*)p.k_pool + off), m_new = fmaxf(m, s);
-      l = l * __builtin_amdgcn_exp2f((m - m_new) * c) + __builtin_amdgcn_exp2f(__builtin_fmaf(s, c, -m_new * c));
-      m = m_new;
-    }
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) {
-      const float m2 = __shfl_xor(m, o, 64), l2 = __shfl_xor(l, o, 64), m_new = fmaxf(m, m2);
-      l = l * __builtin_amdgcn_exp2f((m - m_new) * c) + l2 * __builtin_amdgcn_exp2f((m2 - m_new) * c);
-      m = m_new;
-    }
-    if (lane == 0) p.lse[(int64_t)h * p.C + i] = gn_lse(p, m, l);
-  }
-  gn_redo_row<float, D, false>(p, g, i, h, lp, lane, m * c, 1.f / l, 0.f);
-}
 // dK (or dV) of token t of owned page e into the pool
 template <typename T, typename TG, int D> __device__ __forceinline__ void gn_redo_key(const Params& p, int g, int32_t e, int32_t t, bool is_dk, int lp, int lane) {
   const int64_t l = owned_at(p, g, e), pos = (l << lp) + t, first_q = p.N - p.C;
@@ -813,10 +782,8 @@ __global__ __launch_bounds__(64 * COMBINE_WAVES) void fwd_combine_kernel(Params 
     p.lse[(int64_t)h * p.C + i] = gn_lse(p, M, l_sum);
   for (bad &= 0xfu << (4 * wave); bad; bad &= bad - 1) {   // (four rows per wave)
     const int x = __builtin_ctz(bad);
-    if (gn_out_row(p, tiles, block, x, i, h)) {
-      if constexpr (sizeof(L) != sizeof(T)) gn_redo_terms<D>(gn_params_again(), h / p.G, i, h, lp, lane, gn_lane(M, x), gn_lane(l_sum, x));
-      else gn_redo_row<T, D, false>(gn_params_again(), h / p.G, i, h, lp, lane, gn_lane(M * c, x), gn_lane(inv, x), 0.f);
-    }
+    if (gn_out_row(p, tiles, block, x, i, h))
+      gn_redo_row<T, D, false>(gn_params_again(), h / p.G, i, h, lp, lane, gn_lane(M * c, x), gn_lane(inv, x), 0.f);
   }
 }
 
@@ -891,6 +858,23 @@ __device__ __forceinline__ void gn_mma_terms(const u32x4_t (&a)[3], const u32x4_
     acc = mfma32(__builtin_bit_cast(bf16x8, a[order[k][0]]), __builtin_bit_cast(bf16x8, *b[order[k][1]]), acc);
   }
 }
+// The two sums of gn_mma_terms as one, into c.  The small products of an infinity are infinities of either sign or (0 times infinity) NaN; that of the first terms
+// is what the values themselves give: there it stands alone.  One look at the small sums, 16 instructions per block.
+__device__ __forceinline__ void gn_add_small(f32x16& c, const f32x16& small) {
+  float z0 = 0.f, z1 = 0.f;   // (0 times an infinity or a NaN is a NaN)
+#pragma unroll
+  for (int x = 0; x < 16; x += 2) {
+    z0 = __builtin_fmaf(small[x], 0.f, z0);
+    z1 = __builtin_fmaf(small[x + 1], 0.f, z1);
+  }
+  if (__any(z0 + z1 != 0.f)) {
+#pragma unroll
+    for (int x = 0; x < 16; ++x) c[x] = fabsf(small[x]) < INFINITY ? c[x] + small[x] : c[x];
+  } else {
+#pragma unroll
+    for (int x = 0; x < 16; ++x) c[x] += small[x];
+  }
+}
 // f(i, operand of three terms) for i = 0 .. N - 1: the next operand is fetched while one computes
 template <int N, typename L, typename M> __device__ __forceinline__ void gn_terms_pipeline(L&& load, M&& use) {
   u32x4_t fr[2][3];
@@ -956,8 +940,7 @@ __global__ __launch_bounds__(256, 2) void fwd_terms_kernel(Params p, int32_t til
                                return *(__attribute__((address_space(3))) const u32x4_t*)((row0 ^ (uint32_t)(j << 5)) + (at + k * F::TERM));
                              },
                              [&](const int j, const u32x4_t (&f)[3]) __attribute__((always_inline)) { gn_mma_terms(f, qf[0][j], qf[1][j], qf[2][j], s[1], s[0]); });
-#pragma unroll
-    for (int x = 0; x < 16; ++x) s[0][x] += s[1][x];
+    gn_add_small(s[0], s[1]);
     if (t0 + 32 > V_min) {
       const int32_t rel = t.V - t0 - 4 * hh;
 #pragma unroll
@@ -1036,7 +1019,7 @@ __global__ __launch_bounds__(256, 2) void fwd_terms_kernel(Params p, int32_t til
     if (valid && !(tid & 32)) p2.lse[(int64_t)h * p2.C + i] = gn_lse(p2, m_run, l_tot);
     for (; bad; bad &= bad - 1) {
       const int x = __builtin_ctz(bad);
-      gn_redo_terms<D>(p2, b.g, __builtin_amdgcn_readlane(i, x), __builtin_amdgcn_readlane(h, x), lp, tid & 63, gn_lane(m_run, x), gn_lane(l_tot, x));
+      gn_redo_row<float, D, false>(p2, b.g, __builtin_amdgcn_readlane(i, x), __builtin_amdgcn_readlane(h, x), lp, tid & 63, gn_lane(m_run * c, x), gn_lane(inv, x), 0.f);
     }
   }
 }

@@ -143,6 +143,40 @@ def test_fp32_terms_of_values_at_the_edges(D, P, what):
         assert pu.errors(o[~bad.cuda(), h].cpu(), want_o[~bad])[1] <= 5e-6 and pu.errors(lse[h].cpu()[~bad], want_lse[~bad])[1] <= 1e-6
 
 
+# Keys of minus infinity that every row sees with a weight of 0, where products are formed in terms: O and LSE are those of the other keys, with
+# partial sums that a second kernel combines and without, and no row is formed once more by a wave of its own (which would take many
+# times as long as the pass; the line is drawn at 3).
+@pytest.mark.parametrize("w", [Workload("split", 28, 4, 128, 128, 512, 128 * 20, None, "f32", "f32", 0.088, seed=80),
+                               Workload("unsplit", 32, 32, 64, 32, 2048, 32 * 80, None, "f32", "f32", 0.125, seed=81)], ids=lambda w: w.name)
+def test_fp32_terms_of_keys_at_minus_infinity(w):
+    x = make_inputs(w, "cuda")
+    q, k = x["q"], x["k_pool"]
+    q[..., 0].abs_().add_(0.01)
+    desc = api.make_desc(q, k, w.N, w.sm_scale)
+
+    def run():
+        with pu.kernels_ran(("fwd_terms",), absent=()):
+            api.paged_attn_fwd(desc, q, k, x["v_pool"], x["page_table"])   # (the first call also loads the kernel)
+            torch.cuda.synchronize()
+            api.profile_reset()
+            o, lse = api.paged_attn_fwd(desc, q, k, x["v_pool"], x["page_table"])
+            torch.cuda.synchronize()
+            return o, lse, api.profile_read()["attn_fwd_generic"][0]
+
+    _, _, plain = run()
+    page = x["page_table"][1].long()
+    k[page, :, 3, 0] = float("-inf")
+    o, lse, ms = run()
+    pages, pos = x["page_table"].long(), torch.arange(w.N, device="cuda")
+    for h in range(0, w.Hq, 5):
+        K, V = (x[n][pages, h // w.G].reshape(-1, w.D).double() for n in ("k_pool", "v_pool"))
+        S = ((q[:, h].double() @ K.T) * w.sm_scale).masked_fill(pos[None] > (w.N - w.C + torch.arange(w.C, device="cuda"))[:, None], float("-inf"))
+        assert pu.errors(o[:, h].cpu(), (torch.softmax(S, 1) @ V).cpu())[1] <= 5e-6
+        assert pu.errors(lse[h].cpu(), torch.logsumexp(S, 1).cpu())[1] <= 1e-6
+    print(w.name, f"{plain:.3f} {ms:.3f} ms", flush=True)
+    assert ms <= 3 * plain, (ms, plain)
+
+
 # bf16 tensors of shapes without kernels of their own: probabilities and dS keep 32 bits.  Against 64 bits with the same O and LSE
 # in the backward, dK / dV carry the rounding of LSE (about 8: 2.4e-7 relative to a probability) and of the exponent, O and
 # dQ only that of their own storage, 2^-8 of an element at most.  Probabilities rounded to bf16 miss both by a factor of 100.

@@ -75,6 +75,170 @@ template <typename T> __device__ __forceinline__ void gn_mma(const u32x4_t& a, c
   }
 }
 
+template <int N> __device__ __forceinline__ void gn_zero(f32x16 (&v)[N]) {
+#pragma unroll
+  for (int k = 0; k < N; ++k)
+#pragma unroll
+    for (int x = 0; x < 16; ++x) v[k][x] = 0.f;
+}
+
+// ---- products of fp32 tensors on the bf16 matrix pipe ---------------------------------------------
+// An fp32 value is the sum of three bf16 values, all 24 bits: a = a0 + a1 + a2, each the rounding of what the ones before it left.  A
+// product of two such sums takes six bf16 matrix instructions -- a0 b0, a0 b1, a1 b0, a1 b1, a0 b2, a2 b0; the others are below 2^-26 of
+// it -- and these 192 cycles where v_mfma_f32_32x32x2 takes 512.
+// (Values below 2^-109 keep fewer bits: the smallest bf16 is 2^-133.)
+// S is formed this way on every route.  What the backward makes of S and LSE then has the errors that the forward's S has, whichever
+// kernels the two passes take; those of different products do not cancel in dQ.  Against 64 bits, 2 / 1 heads of 128, logits of 3 times
+// the spread, chunk 1024, 40 pages: dQ both passes with fp32 products 1.95e-6, one of them in terms 4.5e-6 (forward) and 4.1e-6 (backward), S in
+// terms on either route 1.2 to 1.4e-6.
+constexpr float GN_EDGE = 0x1.FFp127f;   // the least value that bf16 rounds to an infinity
+struct GnTerms { uint32_t w[3]; };
+// two values.  What would round to an infinity is cut off instead; infinities and NaN are their own first term.
+__device__ __forceinline__ GnTerms gn_terms(float a, float b) {
+  GnTerms t;
+  auto first = [](float v) {
+    const uint32_t u = __float_as_uint(v), r = pack2_bf16(v, v) << 16;
+    return fabsf(v) < GN_EDGE || v != v ? r : u & 0xffff0000u;
+  };
+  const uint32_t a0 = first(a), b0 = first(b);
+  t.w[0] = (a0 >> 16) | (b0 & 0xffff0000u);
+  const float ra = fabsf(a) < INFINITY ? a - __uint_as_float(a0) : 0.f, rb = fabsf(b) < INFINITY ? b - __uint_as_float(b0) : 0.f;
+  t.w[1] = pack2_bf16(ra, rb);
+  t.w[2] = pack2_bf16(ra - __uint_as_float(t.w[1] << 16), rb - __uint_as_float(t.w[1] & 0xffff0000u));
+  return t;
+}
+// the same in 11 instructions, for values below GN_EDGE (and NaN)
+__device__ __forceinline__ GnTerms gn_terms_plain(float a, float b) {
+  GnTerms t;
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    t.w[k] = pack2_bf16(a, b);
+    a -= __uint_as_float(t.w[k] << 16);
+    b -= __uint_as_float(t.w[k] & 0xffff0000u);
+  }
+  return t;
+}
+// eight values as operands of three terms
+template <bool PLAIN> __device__ __forceinline__ void gn_load_terms(const u32x4_t& a, const u32x4_t& b, u32x4_t (&t)[3]) {
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const float x = __uint_as_float(k < 2 ? a[2 * k] : b[2 * k - 4]), y = __uint_as_float(k < 2 ? a[2 * k + 1] : b[2 * k - 3]);
+    const GnTerms w = PLAIN ? gn_terms_plain(x, y) : gn_terms(x, y);
+#pragma unroll
+    for (int n = 0; n < 3; ++n) t[n][k] = w.w[n];
+  }
+}
+// c += the product of two values of three terms, the smallest first; small += all of it but the product of the first terms
+__device__ __forceinline__ void gn_mma_terms(const u32x4_t (&a)[3], const u32x4_t& b0, const u32x4_t& b1, const u32x4_t& b2, f32x16& small, f32x16& c) {
+  const u32x4_t* b[3] = {&b0, &b1, &b2};
+  constexpr int order[6][2] = {{2, 0}, {0, 2}, {1, 1}, {1, 0}, {0, 1}, {0, 0}};
+#pragma unroll
+  for (int k = 0; k < 6; ++k) {
+    f32x16& acc = k < 5 ? small : c;
+    acc = mfma32(__builtin_bit_cast(bf16x8, a[order[k][0]]), __builtin_bit_cast(bf16x8, *b[order[k][1]]), acc);
+  }
+}
+// Whether a small sum is not finite: 16 instructions per block (0 times an infinity or a NaN is a NaN)
+__device__ __forceinline__ bool gn_odd(const f32x16& small) {
+  float z0 = 0.f, z1 = 0.f;
+#pragma unroll
+  for (int x = 0; x < 16; x += 2) {
+    z0 = __builtin_fmaf(small[x], 0.f, z0);
+    z1 = __builtin_fmaf(small[x + 1], 0.f, z1);
+  }
+  return __any(z0 + z1 != 0.f);
+}
+// The two sums of gn_mma_terms as one, into c.  The small products of an infinity are infinities of either sign or (0 times infinity) NaN; that of the first terms
+// is what the values themselves give: there it stands alone.
+__device__ __forceinline__ void gn_add_small(f32x16& c, const f32x16& small, bool odd) {
+  if (odd) {
+#pragma unroll
+    for (int x = 0; x < 16; ++x) c[x] = fabsf(small[x]) < INFINITY ? c[x] + small[x] : c[x];
+  } else {
+#pragma unroll
+    for (int x = 0; x < 16; ++x) c[x] += small[x];
+  }
+}
+// Granule j of an operand of a first product.  fp32: granules 2 k and 2 k + 1 are eight consecutive dims, half a k-step of the bf16 pipe.
+template <typename T> __host__ __device__ __forceinline__ constexpr int gn_granule(const int j, const int hh) { return sizeof(T) == 2 ? 2 * j + hh : 4 * (j >> 1) + 2 * hh + (j & 1); }
+// The staying operand of S; fp32: as terms, 96 registers for 64 at head dim 128
+template <typename T, int D> struct GnStay {
+  static constexpr int NJ = Gn<T, D>::NJ;
+  u32x4_t f[NJ];
+  __device__ __forceinline__ void load(const T* row, const int hh) {
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) f[j] = reinterpret_cast<const u32x4_t*>(row)[gn_granule<T>(j, hh)];
+  }
+  __device__ __forceinline__ void here() {}
+  template <bool> __device__ __forceinline__ void split() {}
+};
+template <int D> struct GnStay<float, D> {
+  static constexpr int NJ = Gn<float, D>::NJ;
+  const u32x4_t* src;
+  u32x4_t raw[NJ], t[NJ / 2][3];
+  __device__ __forceinline__ void load(const float* row, const int hh) {
+    src = reinterpret_cast<const u32x4_t*>(row) + gn_granule<float>(0, hh);
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) raw[j] = src[gn_granule<float>(j, 0)];
+  }
+  // waits for the granules
+  __device__ __forceinline__ void here() {
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) asm volatile("" : "+v"(raw[j]));
+  }
+  template <bool PLAIN> __device__ __forceinline__ void split() {
+#pragma unroll
+    for (int j = 0; j < NJ; j += 2) gn_load_terms<PLAIN>(raw[j], raw[j + 1], t[j >> 1]);
+  }
+};
+// S of 32 rows of the streamed side.  fp32: in terms, those of the streamed side formed on the way; only matrix cores that run the other
+// products keep to fp32 instructions.  28 / 4 heads of 128, chunk 512, 20 pages: forward 178 -> 148 us, backward 607 -> 574 against S on the
+// fp32 pipe; 14 / 2 heads of 64, chunk 1664, 27 pages of 128: 233 -> 195 and 635 -> 547.
+template <typename T> struct GnSum {
+  f32x16 v[sizeof(T) == 4 ? 2 : 1];
+  u32x4_t held;
+  __device__ __forceinline__ void zero() { gn_zero(v); }
+  template <int D> __device__ __forceinline__ void step(const int j, const u32x4_t& f, const GnStay<T, D>& stay) {   // granule j of the streamed side
+    if constexpr (sizeof(T) == 2) {
+      v[0] = mfma32(__builtin_bit_cast(bf16x8, f), __builtin_bit_cast(bf16x8, stay.f[j]), v[0]);
+    } else if (!(j & 1)) {
+      held = f;
+    } else {
+      u32x4_t a[3];
+      const u32x4_t(&b)[3] = stay.t[j >> 1];
+      gn_load_terms<true>(held, f, a);
+      gn_mma_terms(a, b[0], b[1], b[2], v[1], v[0]);
+    }
+  }
+  // After the last granule: S is v[0].  again(j): granule j once more.  LOOP: the rare second sum in a loop, which takes fewer registers but
+  // where accumulators live in the other half of the register file (dQ, dK / dV).
+  template <bool LOOP, int D, typename L> __device__ __forceinline__ void close(const GnStay<T, D>& stay, L&& again) {
+    if constexpr (sizeof(T) == 4) {
+      constexpr int NJ = Gn<T, D>::NJ;
+      const bool odd = gn_odd(v[1]);
+      if (odd) {   // a value at the edge of fp32: with the terms of gn_terms
+        zero();
+        auto add = [&](const int j) __attribute__((always_inline)) {
+          u32x4_t a[3], b[3];
+          gn_load_terms<false>(again(j), again(j + 1), a);
+          __builtin_amdgcn_sched_barrier(0);
+          gn_load_terms<false>(stay.src[gn_granule<T>(j, 0)], stay.src[gn_granule<T>(j + 1, 0)], b);
+          gn_mma_terms(a, b[0], b[1], b[2], v[1], v[0]);
+          __builtin_amdgcn_sched_barrier(0);
+        };
+        if constexpr (LOOP) {
+#pragma unroll 1
+          for (int j = 0; j < NJ; j += 2) add(j);
+        } else {
+#pragma unroll
+          for (int j = 0; j < NJ; j += 2) add(j);
+        }
+      }
+      gn_add_small(v[0], v[1], odd);
+    }
+  }
+};
+
 // c + <a, b> over 16 bytes each
 template <typename T> __device__ __forceinline__ float gn_dot(const u32x4_t& a, const u32x4_t& b, float c) {
 #pragma unroll
@@ -87,13 +251,6 @@ template <typename T> __device__ __forceinline__ float gn_dot(const u32x4_t& a, 
     }
   }
   return c;
-}
-
-template <int N> __device__ __forceinline__ void gn_zero(f32x16 (&v)[N]) {
-#pragma unroll
-  for (int k = 0; k < N; ++k)
-#pragma unroll
-    for (int x = 0; x < 16; ++x) v[k][x] = 0.f;
 }
 
 // LDS operand addresses of a lane.  bf16: one register per k-step and per transposing read (the swizzle is an XOR
@@ -117,13 +274,17 @@ template <typename T, int D> struct GnAddr {
       }
     } else {
       const uint32_t gran = D == 128 ? lq : lq >> 1, sub = D == 128 ? 0 : 8 * (lq & 1);
-      row[0] = base + lq * X::RB + ((hh ^ X::swz(lq)) << 4);
+      row[0] = base + lq * X::RB + (((2 * hh) ^ X::swz(lq)) << 4);
       tr[0] = base + 4 * hh * X::RB + ((gran ^ (4 * hh)) << 4) + sub;
     }
   }
-  // operand j (k-step) of the first product: the 32 rows at LDS offset `off`
+  // fp32, once per tile: operand addresses are formed from these registers each time (kept across the loop they would be spilled)
+  __device__ __forceinline__ void anew() {
+    if constexpr (!X::BF) asm volatile("" : "+v"(row[0]), "+v"(tr[0]));
+  }
+  // granule j of the first product: the 32 rows at LDS offset `off`
   __device__ __forceinline__ u32x4_t row_frag(const int j, const uint32_t off) const {
-    const uint32_t at = (X::BF ? row[X::BF ? j : 0] : row[0] ^ (uint32_t)(j << 5)) + off;
+    const uint32_t at = (X::BF ? row[X::BF ? j : 0] : row[0] ^ (uint32_t)(gn_granule<T>(j, 0) << 4)) + off;
     return *(__attribute__((address_space(3))) const u32x4_t*)at;
   }
   // operand v of the second product over the same rows.  bf16: key group v / DB, dim block v % DB.  fp32: row 8 (v / 4) +
@@ -190,21 +351,22 @@ template <typename T, int D, int NT> __device__ __forceinline__ void gn_tr_mma(c
 // A straight run of N operand reads and their matrix instructions in batches of four: the next batch is fetched while
 // one computes (left to itself the compiler waits for every operand just before its use).
 // load(i) reads operand i, use(i, operand) multiplies and may add vector work; i is a constant.
-template <int N, typename L, typename M> __device__ __forceinline__ void gn_pipeline(L&& load, M&& use) {
-  static_assert(N % 4 == 0, "whole batches");
-  u32x4_t fr[2][4];
+template <typename T, int D> constexpr int GN_BATCH = sizeof(T) == 4 && D == 128 ? 2 : 4;   // (fp32 at head dim 128: registers)
+template <int N, int B = 4, typename L, typename M> __device__ __forceinline__ void gn_pipeline(L&& load, M&& use) {
+  static_assert(N % B == 0, "whole batches");
+  u32x4_t fr[2][B];
 #pragma unroll
-  for (int k = 0; k < 4; ++k) fr[0][k] = load(k);
+  for (int k = 0; k < B; ++k) fr[0][k] = load(k);
 #pragma unroll
-  for (int b = 0; b < N / 4; ++b) {
-    if (b + 1 < N / 4) {
+  for (int b = 0; b < N / B; ++b) {
+    if (b + 1 < N / B) {
 #pragma unroll
-      for (int k = 0; k < 4; ++k) fr[(b + 1) & 1][k] = load(4 * (b + 1) + k);
+      for (int k = 0; k < B; ++k) fr[(b + 1) & 1][k] = load(B * (b + 1) + k);
       __builtin_amdgcn_sched_barrier(0);
     }
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      use(4 * b + k, fr[b & 1][k]);
+    for (int k = 0; k < B; ++k) {
+      use(B * b + k, fr[b & 1][k]);
       __builtin_amdgcn_sched_barrier(0);
     }
   }
@@ -354,7 +516,7 @@ __device__ __forceinline__ GnBlock gn_block(const Params& p, int32_t b, int32_t 
 // buffers -- a constant --, first list token)
 template <typename T, int D, int KH, typename F>
 __device__ __forceinline__ void gn_key_loop(const Params& p, const GnTile& t, GnStream<T, D>& ks, GnRange kr, GnRange other, int32_t max_len,
-                                            int group, int rb, int lane, int lp, F&& compute) {
+                                            int group, int rb, int lane, int lp, GnStay<T, D>& qs, F&& compute) {
   typedef GnTiles<T, D> Y;
   const int32_t n_kt = (t.V_last + Y::KT - 1) / Y::KT;   // (tiles past what the last row sees are dropped)
   const int32_t k1 = kr.k1 < n_kt ? kr.k1 : n_kt, mine = k1 - kr.k0;
@@ -362,7 +524,9 @@ __device__ __forceinline__ void gn_key_loop(const Params& p, const GnTile& t, Gn
   const uint32_t at = group * GnRow<T, D, KH>::GROUP;
   ks.last = t.T_ent - 1;
   wait_copies<0>();   // (every load so far, so that no wait for one of them is left inside the loop)
+  qs.here();
   if (mine > 0) ks.copy(p, t.lid, max_len, rb, lane, lp, kr.k0, at);
+  qs.template split<true>();   // (while the first tile is on its way)
   for (int32_t i0 = 0; i0 < steps; i0 += 2) {
 #pragma unroll
     for (int b = 0; b < 2; ++b) {   // (unrolled: the buffer is a constant)
@@ -517,10 +681,9 @@ __global__ __launch_bounds__(256 * KH, 2) void fwd_generic_kernel(Params p, int3
   GnStream<T, D> ks;
   ks.init(p, t.lid, max_len, b.g, rb, lane, kr.k0 * Y::KT, lp);
 
-  u32x4_t qf[X::NJ];
+  GnStay<T, D> qs;
   const int64_t roff = (int64_t)t.i * p.q_tok_stride + (int64_t)t.h * p.q_head_stride;
-#pragma unroll
-  for (int j = 0; j < X::NJ; ++j) qf[j] = *reinterpret_cast<const u32x4_t*>((const unsigned char*)((const T*)p.q + roff) + 32 * j + 16 * hh);
+  qs.load((const T*)p.q + roff, hh);
 
   f32x16 of[X::DB];
   gn_zero(of);
@@ -533,14 +696,22 @@ __global__ __launch_bounds__(256 * KH, 2) void fwd_generic_kernel(Params p, int3
 
   // One tile: S of its blocks, one softmax step over all of them, then O.  The exponentials of a second block
   // run between the matrix instructions of the first block's product.
-  gn_key_loop<T, D, KH>(p, t, ks, kr, other, max_len, group, rb, lane, lp, [&](const uint32_t at, const int32_t t0) __attribute__((always_inline)) {
+  gn_key_loop<T, D, KH>(p, t, ks, kr, other, max_len, group, rb, lane, lp, qs, [&](const uint32_t at, const int32_t t0) __attribute__((always_inline)) {
     if (!t.active || t0 >= V_max) return;   // (wave-uniform)
     constexpr int NP = GnAddr<T, D>::NP;
-    f32x16 s[Y::U];
-    gn_zero(s);
-    gn_pipeline<Y::U * X::NJ>(
+    ad.anew();
+    GnSum<T> sums[Y::U];
+#pragma unroll
+    for (int u = 0; u < Y::U; ++u) sums[u].zero();
+    gn_pipeline<Y::U * X::NJ, GN_BATCH<T, D>>(
         [&](const int i) __attribute__((always_inline)) { return ad.row_frag(i % X::NJ, at + 32 * (i / X::NJ) * X::RB); },
-        [&](const int i, const u32x4_t& f) __attribute__((always_inline)) { gn_mma<T>(f, qf[i % X::NJ], s[i / X::NJ]); });
+        [&](const int i, const u32x4_t& f) __attribute__((always_inline)) { sums[i / X::NJ].step(i % X::NJ, f, qs); });
+    f32x16 s[Y::U];
+#pragma unroll
+    for (int u = 0; u < Y::U; ++u) {
+      sums[u].template close<true>(qs, [&](const int j) __attribute__((always_inline)) { return ad.row_frag(j, at + 32 * u * X::RB); });
+      s[u] = sums[u].v[0];
+    }
     if (t0 + Y::KT > V_min) {
       const int32_t rel = t.V - t0 - 4 * hh;
 #pragma unroll
@@ -588,7 +759,7 @@ __global__ __launch_bounds__(256 * KH, 2) void fwd_generic_kernel(Params p, int3
 #pragma unroll
     for (int x = 0; x < 16; x += 2) exps(0, x);
     if constexpr (REFS == 2) l_run *= alpha[1];
-    gn_pipeline<Y::U * NP>(
+    gn_pipeline<Y::U * NP, GN_BATCH<T, D>>(
         [&](const int i) __attribute__((always_inline)) { return ad.tr_frag(i % NP, at + Y::TILE + 32 * (i / NP) * X::RB); },
         [&](const int i, const u32x4_t& f) __attribute__((always_inline)) {
           if (REFS == 2 && i == NP) rescale(REFS - 1);
@@ -788,40 +959,14 @@ __global__ __launch_bounds__(64 * COMBINE_WAVES) void fwd_combine_kernel(Params 
 }
 
 // ---- forward of fp32 tensors on the bf16 matrix pipe ---------------------------------------------
-// An fp32 value is the sum of three bf16 values, all 24 bits: a = a0 + a1 + a2, each the rounding of what the ones before it left.  A
-// product of two such sums takes six bf16 matrix instructions -- a0 b0, a0 b1, a1 b0, a1 b1, a0 b2, a2 b0; the others are below 2^-26 of
-// it -- and these 192 cycles where v_mfma_f32_32x32x2 takes 512.
-// (Values below 2^-109 keep fewer bits: the smallest bf16 is 2^-133.)
-struct GnTerms { uint32_t w[3]; };
-// two values.  What would round to an infinity is cut off instead; infinities and NaN are their own first term.
-__device__ __forceinline__ GnTerms gn_terms(float a, float b) {
-  GnTerms t;
-  auto first = [](float v) {
-    const uint32_t u = __float_as_uint(v), r = pack2_bf16(v, v) << 16;
-    return fabsf(v) < 0x1.FFp127f || v != v ? r : u & 0xffff0000u;
-  };
-  const uint32_t a0 = first(a), b0 = first(b);
-  t.w[0] = (a0 >> 16) | (b0 & 0xffff0000u);
-  const float ra = fabsf(a) < INFINITY ? a - __uint_as_float(a0) : 0.f, rb = fabsf(b) < INFINITY ? b - __uint_as_float(b0) : 0.f;
-  t.w[1] = pack2_bf16(ra, rb);
-  t.w[2] = pack2_bf16(ra - __uint_as_float(t.w[1] << 16), rb - __uint_as_float(t.w[1] & 0xffff0000u));
-  return t;
-}
 template <int D> struct GnF3 {
   typedef Gn<bf16_t, D> X;
   static constexpr int TERM = 32 * X::RB, V = 3 * TERM, TILE = 6 * TERM;   // 32 keys: K0 K1 K2 V0 V1 V2, in the order of the LDS tile
   static constexpr int NI = V / 1024 / 4, LDS = 3 * V;   // copies of K or V per wave; LDS: K twice, V once
 };
-// eight values as operands of three terms
-__device__ __forceinline__ void gn_load_terms(const float4& a, const float4& b, u32x4_t& t0, u32x4_t& t1, u32x4_t& t2) {
-  const GnTerms w[4] = {gn_terms(a.x, a.y), gn_terms(a.z, a.w), gn_terms(b.x, b.y), gn_terms(b.z, b.w)};
-  t0 = u32x4_t{w[0].w[0], w[1].w[0], w[2].w[0], w[3].w[0]};
-  t1 = u32x4_t{w[0].w[1], w[1].w[1], w[2].w[1], w[3].w[1]};
-  t2 = u32x4_t{w[0].w[2], w[1].w[2], w[2].w[2], w[3].w[2]};
-}
-template <int D> __device__ __forceinline__ void gn_store_terms(unsigned char* dst, const float4 (&v)[2]) {
+template <int D> __device__ __forceinline__ void gn_store_terms(unsigned char* dst, const u32x4_t (&v)[2]) {
   u32x4_t t[3];
-  gn_load_terms(v[0], v[1], t[0], t[1], t[2]);
+  gn_load_terms<false>(v[0], v[1], t);
 #pragma unroll
   for (int k = 0; k < 3; ++k) *reinterpret_cast<u32x4_t*>(dst + k * GnF3<D>::TERM) = t[k];
 }
@@ -838,41 +983,14 @@ __global__ __launch_bounds__(256) void kv_terms_kernel(Params p, int32_t n_tiles
   for (int x = 0; x < 2 * 32 * NG / 256; ++x) {
     const int gi = threadIdx.x + 256 * x, is_v = gi / (32 * NG), r = gi / NG % 32, c = gi % NG;
     const int32_t tok = 32 * kt + r, e = tok >> lp;
-    float4 v[2] = {};
+    u32x4_t v[2] = {};
     if (e < len) {
       const int64_t at = (int64_t)p.page_table[list_at(p, g, e)] * p.pool_page_stride + (int64_t)g * p.pool_head_stride + (int64_t)(tok & (p.P - 1)) * p.pool_tok_stride + 8 * c;
-      const float4* src = reinterpret_cast<const float4*>((const float*)(is_v ? p.v_pool : p.k_pool) + at);
+      const u32x4_t* src = reinterpret_cast<const u32x4_t*>((const float*)(is_v ? p.v_pool : p.k_pool) + at);
       v[0] = src[0];
       v[1] = src[1];
     }
     gn_store_terms<D>(out + is_v * F::V + r * F::X::RB + ((c ^ F::X::swz(r)) << 4), v);
-  }
-}
-// c += the product of two values of three terms, the smallest first; small += all of it but the product of the first terms
-__device__ __forceinline__ void gn_mma_terms(const u32x4_t (&a)[3], const u32x4_t& b0, const u32x4_t& b1, const u32x4_t& b2, f32x16& small, f32x16& c) {
-  const u32x4_t* b[3] = {&b0, &b1, &b2};
-  constexpr int order[6][2] = {{2, 0}, {0, 2}, {1, 1}, {1, 0}, {0, 1}, {0, 0}};
-#pragma unroll
-  for (int k = 0; k < 6; ++k) {
-    f32x16& acc = k < 5 ? small : c;
-    acc = mfma32(__builtin_bit_cast(bf16x8, a[order[k][0]]), __builtin_bit_cast(bf16x8, *b[order[k][1]]), acc);
-  }
-}
-// The two sums of gn_mma_terms as one, into c.  The small products of an infinity are infinities of either sign or (0 times infinity) NaN; that of the first terms
-// is what the values themselves give: there it stands alone.  One look at the small sums, 16 instructions per block.
-__device__ __forceinline__ void gn_add_small(f32x16& c, const f32x16& small) {
-  float z0 = 0.f, z1 = 0.f;   // (0 times an infinity or a NaN is a NaN)
-#pragma unroll
-  for (int x = 0; x < 16; x += 2) {
-    z0 = __builtin_fmaf(small[x], 0.f, z0);
-    z1 = __builtin_fmaf(small[x + 1], 0.f, z1);
-  }
-  if (__any(z0 + z1 != 0.f)) {
-#pragma unroll
-    for (int x = 0; x < 16; ++x) c[x] = fabsf(small[x]) < INFINITY ? c[x] + small[x] : c[x];
-  } else {
-#pragma unroll
-    for (int x = 0; x < 16; ++x) c[x] += small[x];
   }
 }
 // f(i, operand of three terms) for i = 0 .. N - 1: the next operand is fetched while one computes
@@ -910,13 +1028,9 @@ __global__ __launch_bounds__(256, 2) void fwd_terms_kernel(Params p, int32_t til
   const bool active = t.active;
   const GnRange kr = gn_range(max_len, lp, 32, b.split, n_split);
 
-  u32x4_t qf[3][X::NJ];
-  const int64_t roff = (int64_t)t.i * p.q_tok_stride + (int64_t)t.h * p.q_head_stride;
-  const float4* q = reinterpret_cast<const float4*>((const float*)p.q + roff + 8 * hh);
-#pragma unroll
-  for (int j = 0; j < X::NJ; ++j) {
-    gn_load_terms(q[4 * j], q[4 * j + 1], qf[0][j], qf[1][j], qf[2][j]);
-  }
+  GnStay<float, D> qs;
+  qs.load((const float*)p.q + (int64_t)t.i * p.q_tok_stride + (int64_t)t.h * p.q_head_stride, hh);
+  qs.template split<false>();
   f32x16 of[X::DB];
   gn_zero(of);
   float m_run = gn_lowest(p), l_run = 0.f;
@@ -939,8 +1053,8 @@ __global__ __launch_bounds__(256, 2) void fwd_terms_kernel(Params p, int32_t til
     gn_terms_pipeline<X::NJ>([&](const int j, const int k) __attribute__((always_inline)) {
                                return *(__attribute__((address_space(3))) const u32x4_t*)((row0 ^ (uint32_t)(j << 5)) + (at + k * F::TERM));
                              },
-                             [&](const int j, const u32x4_t (&f)[3]) __attribute__((always_inline)) { gn_mma_terms(f, qf[0][j], qf[1][j], qf[2][j], s[1], s[0]); });
-    gn_add_small(s[0], s[1]);
+                             [&](const int j, const u32x4_t (&f)[3]) __attribute__((always_inline)) { gn_mma_terms(f, qs.t[j][0], qs.t[j][1], qs.t[j][2], s[1], s[0]); });
+    gn_add_small(s[0], s[1], gn_odd(s[1]));
     if (t0 + 32 > V_min) {
       const int32_t rel = t.V - t0 - 4 * hh;
 #pragma unroll
@@ -1057,13 +1171,14 @@ __device__ __forceinline__ void dq_body(const Params& p, unsigned char* smem, in
   GnStream<T, D> ks;
   ks.init(p, t.lid, max_len, b.g, rb, lane, kr.k0 * Y::KT, lp);
 
-  u32x4_t qf[X::NJ], dof[X::NJ];
+  GnStay<T, D> qs;
+  u32x4_t dof[X::NJ];
   const int64_t roff = (int64_t)t.i * p.q_tok_stride + (int64_t)t.h * p.q_head_stride;
   float delta = 0.f;
+  qs.load((const T*)p.q + roff, hh);
 #pragma unroll
   for (int j = 0; j < X::NJ; ++j) {
-    const int64_t at = roff * X::ES + 32 * j + 16 * hh;
-    qf[j] = *reinterpret_cast<const u32x4_t*>((const unsigned char*)p.q + at);
+    const int64_t at = roff * X::ES + 16 * gn_granule<T>(j, hh);
     dof[j] = *reinterpret_cast<const u32x4_t*>((const unsigned char*)p.d_o + at);
     delta = gn_dot<T>(dof[j], *reinterpret_cast<const u32x4_t*>((const unsigned char*)p.o + at), delta);
   }
@@ -1088,15 +1203,18 @@ __device__ __forceinline__ void dq_body(const Params& p, unsigned char* smem, in
   ad.init(lane, group * GnRow<T, D, KH>::GROUP);
   const int32_t V_min = __builtin_amdgcn_readfirstlane(t.V), V_max = __builtin_amdgcn_readlane(t.V, 31);
 
-  gn_key_loop<T, D, KH>(p, t, ks, kr, other, max_len, group, rb, lane, lp, [&](const uint32_t at, const int32_t t0) __attribute__((always_inline)) {
+  gn_key_loop<T, D, KH>(p, t, ks, kr, other, max_len, group, rb, lane, lp, qs, [&](const uint32_t at, const int32_t t0) __attribute__((always_inline)) {
     if (!t.active || t0 >= V_max) return;
     constexpr int NP = GnAddr<T, D>::NP, NJ = X::NJ, L = 2 * NJ + NP;
     const bool mask = t0 + Y::KT > V_min;
     const int32_t rel = t.V - t0 - 4 * hh;
-    f32x16 s[2];   // S and dP of one block
+    ad.anew();
+    GnSum<T> s;   // of one block
+    f32x16 dp[1];
+    f32x16& pr = s.v[0];   // P
     GnP<T, NT> ds;
     // per block: S, then dP with the exponentials of S between its instructions, dS, then dQ
-    gn_pipeline<Y::U * L>(
+    gn_pipeline<Y::U * L, GN_BATCH<T, D>>(
         [&](const int i) __attribute__((always_inline)) {
           const int u = i / L, k = i % L;
           const uint32_t o = at + 32 * u * X::RB;
@@ -1104,20 +1222,24 @@ __device__ __forceinline__ void dq_body(const Params& p, unsigned char* smem, in
         },
         [&](const int i, const u32x4_t& f) __attribute__((always_inline)) {
           const int u = i / L, k = i % L;
-          if (k == 0) gn_zero(s);
+          if (k == 0) {
+            s.zero();
+            gn_zero(dp);
+          }
           if (k < NJ) {
-            gn_mma<T>(f, qf[k], s[0]);
+            s.step(k, f, qs);
+            if (k == NJ - 1) s.template close<false>(qs, [&](const int j) __attribute__((always_inline)) { return ad.row_frag(j, at + 32 * u * X::RB); });
           } else if (k < 2 * NJ) {
-            gn_mma<T>(f, dof[k - NJ], s[1]);
+            gn_mma<T>(f, dof[k - NJ], dp[0]);
 #pragma unroll
             for (int x = (k - NJ) * (16 / NJ); x < (k - NJ + 1) * (16 / NJ); ++x) {
-              float pr = __builtin_amdgcn_exp2f(__builtin_fmaf(s[0][x], c, -lse2));
-              if (mask && 32 * u + 8 * (x >> 2) + (x & 3) >= rel) pr = 0.f;
-              s[0][x] = pr;
+              float v = __builtin_amdgcn_exp2f(__builtin_fmaf(pr[x], c, -lse2));
+              if (mask && 32 * u + 8 * (x >> 2) + (x & 3) >= rel) v = 0.f;
+              pr[x] = v;
             }
             if (k == 2 * NJ - 1) {
 #pragma unroll
-              for (int x = 0; x < 16; x += 2) ds.set2(x, s[0][x] * (s[1][x] - delta), s[0][x + 1] * (s[1][x + 1] - delta));
+              for (int x = 0; x < 16; x += 2) ds.set2(x, pr[x] * (dp[0][x] - delta), pr[x + 1] * (dp[0][x + 1] - delta));
             }
           } else {
             gn_tr_mma<T, D, NT>(k - 2 * NJ, f, ds, dq);
@@ -1210,11 +1332,12 @@ __device__ __forceinline__ void dkv_body(const Params& p, unsigned char* smem, i
   int32_t tau_v = 0;
   if (p.qp && lane < qc) tau_v = p.inv_qp[(int64_t)g * p.m * p.sel_stride + p.inv_off[(int64_t)g * (p.un_stride + 1) + e0] + q0 + lane];
 
-  u32x4_t kf[X::NJ], vf[X::NJ];
+  GnStay<T, D> ks;
+  u32x4_t vf[X::NJ];
+  ks.load((const T*)p.k_pool + koff, hh);
 #pragma unroll
   for (int j = 0; j < X::NJ; ++j) {
-    const int64_t at = koff * X::ES + 32 * j + 16 * hh;
-    kf[j] = *reinterpret_cast<const u32x4_t*>((const unsigned char*)p.k_pool + at);
+    const int64_t at = koff * X::ES + 16 * gn_granule<T>(j, hh);
     vf[j] = *reinterpret_cast<const u32x4_t*>((const unsigned char*)p.v_pool + at);
   }
   f32x16 dk[X::DB], dv[X::DB];
@@ -1298,6 +1421,7 @@ __device__ __forceinline__ void dkv_body(const Params& p, unsigned char* smem, i
 
   if (s0 < s1) {
     copy(s0, 0);
+    ks.template split<true>();   // (while the first stage is on its way)
     publish(0);
   }
   wait_copies<0>();
@@ -1313,9 +1437,12 @@ __device__ __forceinline__ void dkv_body(const Params& p, unsigned char* smem, i
       constexpr int NP = GnAddr<T, D>::NP, NJ = X::NJ, L = 2 * NJ + 2 * NP;
       const bool mask = base < r_key_max;   // (wave-uniform)
       const int32_t rel = r_key - base - 4 * hh;
-      f32x16 sv[2];
+      ad.anew();
+      GnSum<T> sv;
+      f32x16 dp[1];
+      f32x16& w = sv.v[0];   // P, then dS
       GnP<T, NT> pr, ds;
-      gn_pipeline<Y::U * L>(
+      gn_pipeline<Y::U * L, GN_BATCH<T, D>>(
           [&](const int i) __attribute__((always_inline)) {
             const int u = i / L, k = i % L;
             const uint32_t o = buf + 32 * u * X::RB;
@@ -1324,30 +1451,34 @@ __device__ __forceinline__ void dkv_body(const Params& p, unsigned char* smem, i
           },
           [&](const int i, const u32x4_t& f) __attribute__((always_inline)) {
             const int u = i / L, k = i % L;
-            if (k == 0) gn_zero(sv);
+            if (k == 0) {
+              sv.zero();
+              gn_zero(dp);
+            }
             if (k < NJ) {
-              gn_mma<T>(f, kf[k], sv[0]);
+              sv.step(k, f, ks);
+              if (k == NJ - 1) sv.template close<false>(ks, [&](const int j) __attribute__((always_inline)) { return ad.row_frag(j, buf + 32 * u * X::RB); });
             } else if (k < 2 * NJ) {
-              gn_mma<T>(f, vf[k - NJ], sv[1]);
+              gn_mma<T>(f, vf[k - NJ], dp[0]);
 #pragma unroll
               for (int x = (k - NJ) * (16 / NJ); x < (k - NJ + 1) * (16 / NJ); ++x) {
-                float v = __builtin_amdgcn_exp2f(__builtin_fmaf(sv[0][x], c, -st[32 * u + 8 * (x >> 2) + 4 * hh + (x & 3)]));
+                float v = __builtin_amdgcn_exp2f(__builtin_fmaf(w[x], c, -st[32 * u + 8 * (x >> 2) + 4 * hh + (x & 3)]));
                 if (mask && 32 * u + 8 * (x >> 2) + (x & 3) < rel) v = 0.f;
-                sv[0][x] = v;
+                w[x] = v;
               }
               if (k == 2 * NJ - 1) {
 #pragma unroll
-                for (int x = 0; x < 16; x += 2) pr.set2(x, sv[0][x], sv[0][x + 1]);
+                for (int x = 0; x < 16; x += 2) pr.set2(x, w[x], w[x + 1]);
               }
             } else if (k < 2 * NJ + NP) {
               gn_tr_mma<T, D, NT>(k - 2 * NJ, f, pr, dv);
               const int n = k - 2 * NJ;
 #pragma unroll
               for (int x = n * (16 / NP); x < (n + 1) * (16 / NP); ++x)
-                sv[1][x] = sv[0][x] * (sv[1][x] - st[64 + 32 * u + 8 * (x >> 2) + 4 * hh + (x & 3)]);
+                w[x] = w[x] * (dp[0][x] - st[64 + 32 * u + 8 * (x >> 2) + 4 * hh + (x & 3)]);
               if (n == NP - 1) {
 #pragma unroll
-                for (int x = 0; x < 16; x += 2) ds.set2(x, sv[1][x], sv[1][x + 1]);
+                for (int x = 0; x < 16; x += 2) ds.set2(x, w[x], w[x + 1]);
               }
             } else {
               gn_tr_mma<T, D, NT>(k - 2 * NJ - NP, f, ds, dk);
@@ -1436,16 +1567,16 @@ template <int D> __global__ __launch_bounds__(256) void row_terms_kernel(Params 
     const bool valid = row < p.C * p.G;
     const int32_t i = (int32_t)div_g(p, (uint32_t)(valid ? row : 0)), h = g * p.G + (valid ? row - i * p.G : 0);
     const int64_t at = (int64_t)i * p.q_tok_stride + (int64_t)h * p.q_head_stride + 8 * c;
-    float4 v[2] = {};
+    u32x4_t v[2] = {};
     if (valid) {
-      const float4* src = reinterpret_cast<const float4*>((const float*)(is_do ? p.d_o : p.q) + at);
+      const u32x4_t* src = reinterpret_cast<const u32x4_t*>((const float*)(is_do ? p.d_o : p.q) + at);
       v[0] = src[0];
       v[1] = src[1];
     }
     if (is_do) {
       const u32x4_t* o = reinterpret_cast<const u32x4_t*>((const float*)p.o + at);
       float d = 0.f;
-      if (valid) d = gn_dot<float>(__builtin_bit_cast(u32x4_t, v[1]), o[1], gn_dot<float>(__builtin_bit_cast(u32x4_t, v[0]), o[0], 0.f));
+      if (valid) d = gn_dot<float>(v[1], o[1], gn_dot<float>(v[0], o[0], 0.f));
 #pragma unroll
       for (int k = 1; k < NG; k <<= 1) d += __shfl_xor(d, k, 64);
       if (valid && c == 0) p.delta[(int64_t)h * p.C + i] = d;
@@ -1471,17 +1602,17 @@ __device__ __forceinline__ void units_body(const Params& p, unsigned char* smem,
   const int64_t koff = (int64_t)p.page_table[l] * p.pool_page_stride + (int64_t)t.g * p.pool_head_stride + (int64_t)(kq & (p.P - 1)) * p.pool_tok_stride;
   // rows before r_key do not see the key
   const int32_t r_key = !kvalid ? INT32_MAX : pos > first_q ? (int32_t)(pos - first_q) * p.G : 0, r_key_max = __builtin_amdgcn_readlane(r_key, 31);
-  u32x4_t kf[3][X::NJ], vf[3][X::NJ];
+  u32x4_t kf[X::NJ][3], vf[X::NJ][3];
 #pragma unroll
   for (int j = 0; j < X::NJ; ++j) {
-    const float4* k = reinterpret_cast<const float4*>((const float*)p.k_pool + koff + 16 * j + 8 * hh);
-    const float4* v = reinterpret_cast<const float4*>((const float*)p.v_pool + koff + 16 * j + 8 * hh);
-    const float4 k0 = k[0], k1 = k[1];
-    float4* kl = reinterpret_cast<float4*>(smem + R::KL + kq * R::KL_ROW + 64 * j + 32 * hh);
+    const u32x4_t* k = reinterpret_cast<const u32x4_t*>((const float*)p.k_pool + koff + 16 * j + 8 * hh);
+    const u32x4_t* v = reinterpret_cast<const u32x4_t*>((const float*)p.v_pool + koff + 16 * j + 8 * hh);
+    const u32x4_t k0 = k[0], k1 = k[1];
+    u32x4_t* kl = reinterpret_cast<u32x4_t*>(smem + R::KL + kq * R::KL_ROW + 64 * j + 32 * hh);
     kl[0] = k0;
     kl[1] = k1;
-    gn_load_terms(k0, k1, kf[0][j], kf[1][j], kf[2][j]);
-    gn_load_terms(v[0], v[1], vf[0][j], vf[1][j], vf[2][j]);
+    gn_load_terms<false>(k0, k1, kf[j]);
+    gn_load_terms<false>(v[0], v[1], vf[j]);
   }
   f32x16 dk[X::DB], dv[X::DB];
   gn_zero(dk);
@@ -1539,10 +1670,10 @@ __device__ __forceinline__ void units_body(const Params& p, unsigned char* smem,
           [&](const int i, const u32x4_t (&f)[3]) __attribute__((always_inline)) {
             constexpr int NJ = X::NJ, NV = 2 * X::DB;
             if (i < NJ) {
-              gn_mma_terms(f, kf[0][i], kf[1][i], kf[2][i], sv[1], sv[0]);
+              gn_mma_terms(f, kf[i][0], kf[i][1], kf[i][2], sv[1], sv[0]);
             } else if (i < 2 * NJ) {   // dP, and P
               const int j = i - NJ;
-              gn_mma_terms(f, vf[0][j], vf[1][j], vf[2][j], dp[1], dp[0]);
+              gn_mma_terms(f, vf[j][0], vf[j][1], vf[j][2], dp[1], dp[0]);
 #pragma unroll
               for (int x = j * (16 / NJ); x < (j + 1) * (16 / NJ); ++x) {
                 const int row = 8 * (x >> 2) + (x & 3);

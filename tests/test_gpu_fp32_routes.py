@@ -1,0 +1,132 @@
+"""fp32 passes on every route that a call can take: with the workspaces that the library asks for (products in terms, backward by units), without
+room for them (the kernels of every shape), and with dQ written over O."""
+import math
+
+import pytest
+import torch
+
+from paper_2602_02108_amd import api
+from paper_2602_02108_amd.workloads import Workload, make_inputs
+
+import parity_util as pu
+
+pytestmark = pytest.mark.gpu
+
+# heads that do not fill a tile, logits of three times the usual spread (few keys carry a row), keys with a common part
+SHAPES = [Workload("d128", 2, 1, 128, 128, 1024, 128 * 40, None, "f32", "f32", 128 ** -0.5, q_scale=3., boost_frac=0.05, seed=501),
+          Workload("d64", 6, 2, 64, 32, 800, 32 * 130, None, "f32", "f32", 0.125, q_scale=3., boost_frac=0.05, seed=502)]
+ROUTES = [("asked", "asked"), ("asked", "least"), ("none", "asked"), ("none", "least"), ("asked", "over_o")]
+PINNED = {"asked": (("fwd_terms",), ()), "none": ((), ("fwd_terms",))}
+PINNED_BWD = {"asked": (("bwd_units",), ()), "least": ((), ("bwd_units",)), "over_o": ((), ())}
+
+
+def exact(w, x):
+    """O, LSE, dQ, dK, dV of a dense call in 64 bits, dK / dV as pools."""
+    q, d_o = x["q"].double(), x["d_o"].double()
+    pages, t = x["page_table"].long()[:w.n], torch.arange(w.N, device="cuda")
+    unseen = t[None] > (w.N - w.C + torch.arange(w.C, device="cuda"))[:, None]
+    o, dq, lse = torch.zeros_like(q), torch.zeros_like(q), torch.zeros((w.Hq, w.C), dtype=torch.float64, device="cuda")
+    dk, dv = (torch.zeros(x["k_pool"].shape, dtype=torch.float64, device="cuda") for _ in range(2))
+    for g in range(w.Hkv):
+        K, V = (x[n][pages, g].reshape(-1, w.D).double() for n in ("k_pool", "v_pool"))
+        dK, dV = torch.zeros_like(K), torch.zeros_like(V)
+        for h in range(g * w.G, (g + 1) * w.G):
+            S = ((q[:, h] @ K.T) * w.sm_scale).masked_fill(unseen, -math.inf)
+            lse[h] = torch.logsumexp(S, 1)
+            P = torch.exp(S - lse[h][:, None])
+            o[:, h] = P @ V
+            dS = P * (d_o[:, h] @ V.T - (d_o[:, h] * o[:, h]).sum(1, keepdim=True))
+            dq[:, h] = dS @ K * w.sm_scale
+            dK += dS.T @ q[:, h] * w.sm_scale
+            dV += P.T @ d_o[:, h]
+        dk[pages, g], dv[pages, g] = dK.reshape(-1, w.P, w.D), dV.reshape(-1, w.P, w.D)
+    return o, lse, dq, dk, dv
+
+
+def run(w, x, fwd, bwd):
+    """The same from the library, on the route that the workspaces leave."""
+    desc = api.make_desc(x["q"], x["k_pool"], w.N, w.sm_scale)
+    args = (desc, x["q"], x["k_pool"], x["v_pool"], x["page_table"])
+    least = (w.Hq * w.C * 4 + 255) // 256 * 256
+    ws = torch.empty(256, dtype=torch.uint8, device="cuda") if fwd == "none" else None
+    with pu.kernels_ran(*PINNED[fwd]):
+        o, lse = api.paged_attn_fwd(*args, workspace=ws)
+    x["dk_pool"].zero_()
+    x["dv_pool"].zero_()
+    out = o.clone()
+    ws = torch.empty(least, dtype=torch.uint8, device="cuda") if bwd == "least" else None
+    with pu.kernels_ran(*PINNED_BWD[bwd]):
+        dq = api.paged_attn_bwd(*args, o, lse, x["d_o"], x["dk_pool"], x["dv_pool"], d_q=o if bwd == "over_o" else None, workspace=ws)
+    return out, lse, dq, x["dk_pool"], x["dv_pool"]
+
+
+NAMES = ("o", "lse", "dq", "dk", "dv")
+
+
+def rel(got, want):
+    return float((got.double() - want).norm() / want.norm())
+
+
+# Where forward and backward form S in the same products, what the backward makes of S and LSE carries the errors of the forward's S, and they cancel in dQ.
+# Measured, forward with room for splits: O 5.0 to 5.8e-7, dQ 1.0 to 1.7e-6, dK / dV 0.8 to 1.3e-6; without (a row's sums are one chain): O 8.9 to
+# 9.6e-7, dQ 1.7 to 2.4e-6, dK / dV 1.0 to 1.4e-6.  With S as fp32 products in both passes O 1.1 to 1.8e-6, dQ 1.6 to 2.6e-6, dK / dV 1.3 to 2.0e-6; in one
+# pass only, dQ 3.2 to 4.7e-6, dK / dV up to 2.9e-6.
+LIMITS = {"asked": dict(o=9e-7, lse=7e-8, dq=2.1e-6, dk=1.7e-6, dv=1.7e-6), "none": dict(o=1.3e-6, lse=7e-8, dq=2.8e-6, dk=1.7e-6, dv=1.7e-6)}
+
+
+@pytest.mark.parametrize("w", SHAPES, ids=lambda w: w.name)
+def test_the_error_does_not_depend_on_the_route(w):
+    x = make_inputs(w, "cuda")
+    want = exact(w, x)
+    for fwd, bwd in ROUTES:
+        errs = {n: rel(a, b) for n, a, b in zip(NAMES, run(w, x, fwd, bwd), want)}
+        print(w.name, fwd, bwd, {n: f"{e:.2e}" for n, e in errs.items()}, flush=True)
+        assert all(errs[n] <= LIMITS[fwd][n] for n in NAMES), (fwd, bwd, errs)
+
+
+# Keys at the edge of fp32 that carry weight: their first bf16 term must not be rounded to an infinity.  One dim decides: keys of N(0, 1) 1e38, some at
+# 3.4e38, queries of about 2^-100 and a scale that makes the logits N(0, 1).  An infinity shows as one, a lost second term as 2^-9; the keys of either sign
+# cancel in dQ, whose chains of up to 5120 additions are sqrt(5120) 2^-24 = 4e-6 of their terms off: the line is 2e-5.
+@pytest.mark.parametrize("fwd,bwd", ROUTES)
+@pytest.mark.parametrize("w", SHAPES, ids=lambda w: w.name)
+def test_values_at_the_edge_of_fp32_that_carry_weight(w, fwd, bwd):
+    w = w.with_(sm_scale=2. ** 100 / 1e38, boost_frac=0., q_scale=1.)
+    x = make_inputs(w, "cuda")
+    x["q"].mul_(2. ** -100)
+    x["d_o"].mul_(2. ** -10)   # (dQ is summed before it is scaled: dS times such a key has to stay finite)
+    x["k_pool"][..., 0] = (x["k_pool"][..., 0] * 1e38).clamp_(-3.4e38, 3.4e38)
+    x["k_pool"][:, :, 5, 0] = 3.4e38
+    x["k_pool"][:, :, 11, 0] = -3.4028e38
+    for n, a, b in zip(NAMES, run(w, x, fwd, bwd), exact(w, x)):
+        if n != "dk":   # (dS / K: below what fp32 holds)
+            assert rel(a, b) <= 2e-5, (n, rel(a, b))
+
+
+# Values that are not finite, without room for the other route: as they reach those who see them there.
+@pytest.mark.parametrize("what", ["huge", "weight_0", "inf", "nan"])
+@pytest.mark.parametrize("w", SHAPES, ids=lambda w: w.name)
+def test_values_that_are_not_finite_without_a_workspace(w, what):
+    w = w.with_(q_scale=1.)
+    x = make_inputs(w, "cuda")
+    page, k, q = x["page_table"][w.n_past // 2].long(), x["k_pool"], x["q"]
+    if what == "huge":
+        k[page, :, 3, 0] = 3.4e38
+        q[..., 0] = -1
+    elif what == "weight_0":
+        k[page, :, 3, 0] = -math.inf
+        q[..., 0].abs_().add_(0.01)
+    elif what == "inf":
+        q[100, 1, 5] = math.inf
+    else:
+        k[x["page_table"][w.n - 2].long(), 0, 3, 7] = math.nan   # (the rows before it do not see it)
+    got, want = run(w, x, "none", "least"), exact(w, x)
+    row_nan = want[0].isnan().any(2)
+    for n, a, b in zip(NAMES[:2], got[:2], want[:2]):
+        nan = row_nan if n == "o" else row_nan.T
+        assert torch.equal(a.isnan() if n == "lse" else a.isnan().all(2), nan), n
+        assert rel(a[~nan], b[~nan]) <= 5e-6, n
+    if what in ("huge", "weight_0"):
+        assert not row_nan.any()
+    if what == "huge":
+        for n, a, b in zip(NAMES[2:], got[2:], want[2:]):
+            assert rel(a, b) <= 5e-6, n

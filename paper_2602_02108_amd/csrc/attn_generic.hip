@@ -151,7 +151,7 @@ __device__ __forceinline__ bool gn_odd(const f32x16& small) {
 // The two sums of gn_mma_terms as one, into c.  The small products of an infinity are infinities of either sign or (0 times infinity) NaN; that of the first terms
 // is what the values themselves give: there it stands alone.
 __device__ __forceinline__ void gn_add_small(f32x16& c, const f32x16& small, bool odd) {
-  if (odd) {
+  if (__builtin_expect(odd, 0)) {
 #pragma unroll
     for (int x = 0; x < 16; ++x) c[x] = fabsf(small[x]) < INFINITY ? c[x] + small[x] : c[x];
   } else {
@@ -164,11 +164,10 @@ template <typename T> __host__ __device__ __forceinline__ constexpr int gn_granu
 // The staying operand of S; fp32: as terms, 96 registers for 64 at head dim 128
 template <typename T, int D> struct GnStay {
   static constexpr int NJ = Gn<T, D>::NJ;
+  const u32x4_t* src;
   u32x4_t f[NJ];
-  __device__ __forceinline__ void load(const T* row, const int hh) {
-#pragma unroll
-    for (int j = 0; j < NJ; ++j) f[j] = reinterpret_cast<const u32x4_t*>(row)[gn_granule<T>(j, hh)];
-  }
+  __device__ __forceinline__ void at(const T* row, const int hh) { src = reinterpret_cast<const u32x4_t*>(row) + gn_granule<T>(0, hh); }
+  __device__ __forceinline__ void load(const int j) { f[j] = src[gn_granule<T>(j, 0)]; }
   __device__ __forceinline__ void here() {}
   template <bool> __device__ __forceinline__ void split() {}
 };
@@ -176,15 +175,23 @@ template <int D> struct GnStay<float, D> {
   static constexpr int NJ = Gn<float, D>::NJ;
   const u32x4_t* src;
   u32x4_t raw[NJ], t[NJ / 2][3];
-  __device__ __forceinline__ void load(const float* row, const int hh) {
-    src = reinterpret_cast<const u32x4_t*>(row) + gn_granule<float>(0, hh);
-#pragma unroll
-    for (int j = 0; j < NJ; ++j) raw[j] = src[gn_granule<float>(j, 0)];
-  }
+  __device__ __forceinline__ void at(const float* row, const int hh) { src = reinterpret_cast<const u32x4_t*>(row) + gn_granule<float>(0, hh); }
+  __device__ __forceinline__ void load(const int j) { raw[j] = src[gn_granule<float>(j, 0)]; }
   // waits for the granules
   __device__ __forceinline__ void here() {
 #pragma unroll
     for (int j = 0; j < NJ; ++j) asm volatile("" : "+v"(raw[j]));
+  }
+  __device__ __forceinline__ bool finite() const {   // (of this lane)
+    uint32_t m = 0;
+#pragma unroll
+    for (int j = 0; j < NJ / 2; ++j)
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const uint32_t w = t[j][0][k] & 0x7f807f80u, e = (w & 0xffffu) > w >> 16 ? w & 0xffffu : w >> 16;   // (the exponents of two first terms)
+        m = m > e ? m : e;
+      }
+    return m != 0x7f80u;
   }
   template <bool PLAIN> __device__ __forceinline__ void split() {
 #pragma unroll
@@ -216,7 +223,7 @@ template <typename T> struct GnSum {
     if constexpr (sizeof(T) == 4) {
       constexpr int NJ = Gn<T, D>::NJ;
       const bool odd = gn_odd(v[1]);
-      if (odd) {   // a value at the edge of fp32: with the terms of gn_terms
+      if (__builtin_expect(odd, 0)) {   // a value at the edge of fp32: with the terms of gn_terms
         zero();
         auto add = [&](const int j) __attribute__((always_inline)) {
           u32x4_t a[3], b[3];
@@ -683,7 +690,9 @@ __global__ __launch_bounds__(256 * KH, 2) void fwd_generic_kernel(Params p, int3
 
   GnStay<T, D> qs;
   const int64_t roff = (int64_t)t.i * p.q_tok_stride + (int64_t)t.h * p.q_head_stride;
-  qs.load((const T*)p.q + roff, hh);
+  qs.at((const T*)p.q + roff, hh);
+#pragma unroll
+  for (int j = 0; j < X::NJ; ++j) qs.load(j);
 
   f32x16 of[X::DB];
   gn_zero(of);
@@ -972,17 +981,19 @@ template <int D> __device__ __forceinline__ void gn_store_terms(unsigned char* d
 }
 static inline int32_t gn_f3_tiles(const Params& p, int32_t max_len) { return (int32_t)(((int64_t)max_len * p.P + 31) / 32); }
 
-// The terms of the listed keys, [KV head][tile of 32 list tokens][TILE]; zeros past the list.
+// The terms of the listed keys of n_tiles tiles from t0 on, [KV head][tile of 32 list tokens][TILE]; zeros past the list.  odd[KV head][tile][4]: a byte per
+// wave, whether a key of the tile is not finite.
 template <int D>
-__global__ __launch_bounds__(256) void kv_terms_kernel(Params p, int32_t n_tiles, int lp, unsigned char* __restrict__ img) {
+__global__ __launch_bounds__(256) void kv_terms_kernel(Params p, int32_t t0, int32_t n_tiles, int lp, unsigned char* __restrict__ img, unsigned char* __restrict__ odd) {
   typedef GnF3<D> F;
   constexpr int NG = F::X::NG;
+  float z = 0.f;   // (0 times an infinity or a NaN is a NaN)
   const int32_t kt = blockIdx.x / p.Hkv, g = blockIdx.x - kt * p.Hkv, len = list_len(p, g);
   unsigned char* out = img + ((int64_t)g * n_tiles + kt) * F::TILE;
 #pragma unroll
   for (int x = 0; x < 2 * 32 * NG / 256; ++x) {
     const int gi = threadIdx.x + 256 * x, is_v = gi / (32 * NG), r = gi / NG % 32, c = gi % NG;
-    const int32_t tok = 32 * kt + r, e = tok >> lp;
+    const int32_t tok = 32 * (t0 + kt) + r, e = tok >> lp;
     u32x4_t v[2] = {};
     if (e < len) {
       const int64_t at = (int64_t)p.page_table[list_at(p, g, e)] * p.pool_page_stride + (int64_t)g * p.pool_head_stride + (int64_t)(tok & (p.P - 1)) * p.pool_tok_stride + 8 * c;
@@ -990,8 +1001,14 @@ __global__ __launch_bounds__(256) void kv_terms_kernel(Params p, int32_t n_tiles
       v[0] = src[0];
       v[1] = src[1];
     }
+    if (!is_v) {
+#pragma unroll
+      for (int k = 0; k < 8; ++k) z = __builtin_fmaf(__uint_as_float(v[k >> 2][k & 3]), 0.f, z);
+    }
     gn_store_terms<D>(out + is_v * F::V + r * F::X::RB + ((c ^ F::X::swz(r)) << 4), v);
   }
+  const bool any = __any(z != 0.f);
+  if ((threadIdx.x & 63) == 0) odd[((int64_t)g * n_tiles + kt) * 4 + (threadIdx.x >> 6)] = any;
 }
 // f(i, operand of three terms) for i = 0 .. N - 1: the next operand is fetched while one computes
 template <int N, typename L, typename M> __device__ __forceinline__ void gn_terms_pipeline(L&& load, M&& use) {
@@ -1016,31 +1033,53 @@ template <int N, typename L, typename M> __device__ __forceinline__ void gn_term
 // 6.0e-7; on the fp32 pipe 7.3e-7).  28 / 4 heads, chunk 512, 20 pages of 128: the forward with layout and combine 187 us on the fp32 pipe, 118 here: 1.0
 // PFLOP/s of bf16 instructions, what the clock sustains (the bf16 forward of pages of 128 reaches no more).  256 rows per workgroup, half of
 // the copies: 2 to 6 % faster where the chip is full, up to 25 % slower where it is not.
-template <int D>
-__global__ __launch_bounds__(256, 2) void fwd_terms_kernel(Params p, int32_t tiles, int32_t n_split, int lp, int32_t max_len, int32_t n_tiles,
-                                                           const unsigned char* __restrict__ img, float* __restrict__ part, float2* __restrict__ part_ml) {
+template <int D, bool FIRST>
+__global__ __launch_bounds__(256, 2) void fwd_terms_kernel(Params p, int32_t tiles, int32_t n_split, int lp, int32_t max_len, int32_t t0, int32_t n_tiles, bool last, const unsigned char* __restrict__ img,
+                                                           const int32_t* __restrict__ odd_tiles, float* __restrict__ part, float2* __restrict__ part_ml) {
   typedef GnF3<D> F;
   typedef Gn<bf16_t, D> X;
   extern __shared__ __align__(16) unsigned char smem[];
   const int lane = threadIdx.x & 63, hh = lane >> 5, rb = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const GnBlock b = gn_block(p, blockIdx.x, tiles, n_split);
+  // this launch: tiles t0 .. t0 + n_tiles - 1 of the list, which the splits share
+  const GnRange kr = {t0 + (int32_t)((int64_t)n_tiles * b.split / n_split), t0 + (int32_t)((int64_t)n_tiles * (b.split + 1) / n_split)};
+  // whether the wave meets a value that is not finite: a key's, or (below) its row's.  (Looked up once: 16 instructions per tile were 2 to 7 % of the kernel.)
+  odd_tiles += (int64_t)b.g * n_tiles - t0;
+  int32_t odd_key = kr.k0 + lane < kr.k1 ? odd_tiles[kr.k0 + lane] : 0;
   const GnTile t = gn_tile(p, b.g, b.tile, rb, lane, lp, max_len);
   const bool active = t.active;
-  const GnRange kr = gn_range(max_len, lp, 32, b.split, n_split);
 
   GnStay<float, D> qs;
-  qs.load((const float*)p.q + (int64_t)t.i * p.q_tok_stride + (int64_t)t.h * p.q_head_stride, hh);
+  qs.at((const float*)p.q + (int64_t)t.i * p.q_tok_stride + (int64_t)t.h * p.q_head_stride, hh);
+#pragma unroll
+  for (int j = 0; j < GnStay<float, D>::NJ; ++j) qs.load(j);
   qs.template split<false>();
+  for (int32_t kt = kr.k0 + 64 + lane; kt < kr.k1; kt += 64) odd_key |= odd_tiles[kt];
+  const bool odd = __any(odd_key != 0 || !qs.finite());
   f32x16 of[X::DB];
   gn_zero(of);
   float m_run = gn_lowest(p), l_run = 0.f;
+  if (!FIRST && active) {   // on from where the launch before left the split
+    const int64_t at = (((int64_t)b.split * p.Hkv + b.g) * tiles + b.tile) * 4 + rb;
+    const float4* src = reinterpret_cast<const float4*>(part) + at * (D / 8) * 64 + lane;
+#pragma unroll
+    for (int k = 0; k < D / 8; ++k) {
+      const float4 v = src[64 * k];
+      f32x16& o = of[k >> 2];
+      const int a = 4 * (k & 3);
+      o[a] = v.x; o[a + 1] = v.y; o[a + 2] = v.z; o[a + 3] = v.w;
+    }
+    const float2 ml = part_ml[at * 32 + (lane & 31)];
+    m_run = fmaxf(m_run, ml.x);
+    l_run = hh ? 0.f : ml.y;
+  }
   const float c = p.sm_scale * 1.4426950408889634f;
   GnAddr<bf16_t, D> ad;
   ad.init(lane, 0);
   uint32_t row0 = ad.row[0];
   const int32_t V_min = __builtin_amdgcn_readfirstlane(t.V), V_max = __builtin_amdgcn_readlane(t.V, 31);
   const int32_t n_kt = (t.V_last + 31) / 32, k1 = kr.k1 < n_kt ? kr.k1 : n_kt;
-  const unsigned char* src = img + (int64_t)b.g * n_tiles * F::TILE + rb * F::NI * 1024 + lane * 16;
+  const unsigned char* src = img + ((int64_t)b.g * n_tiles - t0) * F::TILE + rb * F::NI * 1024 + lane * 16;
   auto copy = [&](const int32_t kt, const uint32_t which, const uint32_t dst) __attribute__((always_inline)) {   // which: 0 or F::V
 #pragma unroll
     for (int k = 0; k < F::NI; ++k) gn_copy16(src + (int64_t)kt * F::TILE + which + 1024 * k, dst + rb * F::NI * 1024 + 1024 * k);
@@ -1054,16 +1093,20 @@ __global__ __launch_bounds__(256, 2) void fwd_terms_kernel(Params p, int32_t til
                                return *(__attribute__((address_space(3))) const u32x4_t*)((row0 ^ (uint32_t)(j << 5)) + (at + k * F::TERM));
                              },
                              [&](const int j, const u32x4_t (&f)[3]) __attribute__((always_inline)) { gn_mma_terms(f, qs.t[j][0], qs.t[j][1], qs.t[j][2], s[1], s[0]); });
-    gn_add_small(s[0], s[1], gn_odd(s[1]));
-    if (t0 + 32 > V_min) {
+#pragma unroll
+    for (int x = 0; x < 16; ++x) s[1][x] += s[0][x];
+    if (t0 + 32 > V_min || odd) {   // (one branch for both)
       const int32_t rel = t.V - t0 - 4 * hh;
 #pragma unroll
-      for (int x = 0; x < 16; ++x)
-        if (8 * (x >> 2) + (x & 3) >= rel) s[0][x] = -INFINITY;
+      for (int x = 0; x < 16; ++x) {
+        // the small products of an infinity are infinities of either sign or (0 times infinity) NaN; that of the first terms is what the values give
+        s[1][x] = fabsf(s[1][x]) < INFINITY ? s[1][x] : s[0][x];
+        if (8 * (x >> 2) + (x & 3) >= rel) s[1][x] = -INFINITY;
+      }
     }
-    float mx = s[0][0];
+    float mx = s[1][0];
 #pragma unroll
-    for (int x = 1; x < 16; ++x) mx = fmaxf(mx, s[0][x]);
+    for (int x = 1; x < 16; ++x) mx = fmaxf(mx, s[1][x]);
     const float m_new = fmaxf(m_run, half_max(mx)), alpha = __builtin_amdgcn_exp2f((m_run - m_new) * c), mc = m_new * c;
     m_run = m_new;
     if (__any(alpha != 1.f)) {
@@ -1075,7 +1118,7 @@ __global__ __launch_bounds__(256, 2) void fwd_terms_kernel(Params p, int32_t til
     l_run *= alpha;
 #pragma unroll
     for (int x = 0; x < 16; x += 2) {
-      const float a = __builtin_amdgcn_exp2f(__builtin_fmaf(s[0][x], c, -mc)), b2 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[0][x + 1], c, -mc));
+      const float a = __builtin_amdgcn_exp2f(__builtin_fmaf(s[1][x], c, -mc)), b2 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[1][x + 1], c, -mc));
       pr.set2(x, a, b2);
       l_run += a + b2;
     }
@@ -1117,7 +1160,7 @@ __global__ __launch_bounds__(256, 2) void fwd_terms_kernel(Params p, int32_t til
   const float l_tot = half_sum(l_run);
   const int32_t r = b.tile * GN_ROWS + 32 * rb + (tid & 31), rows = p2.C * p2.G;
   const bool valid = r < rows;
-  if (n_split > 1) {
+  if (n_split > 1 || !last) {
     const int64_t at = (((int64_t)b.split * p2.Hkv + b.g) * tiles + b.tile) * 4 + rb;
     if (!active) return;
     part_store<bf16_t, D>(part, at, tid & 63, of, 1.f);
@@ -1175,9 +1218,10 @@ __device__ __forceinline__ void dq_body(const Params& p, unsigned char* smem, in
   u32x4_t dof[X::NJ];
   const int64_t roff = (int64_t)t.i * p.q_tok_stride + (int64_t)t.h * p.q_head_stride;
   float delta = 0.f;
-  qs.load((const T*)p.q + roff, hh);
+  qs.at((const T*)p.q + roff, hh);
 #pragma unroll
   for (int j = 0; j < X::NJ; ++j) {
+    qs.load(j);
     const int64_t at = roff * X::ES + 16 * gn_granule<T>(j, hh);
     dof[j] = *reinterpret_cast<const u32x4_t*>((const unsigned char*)p.d_o + at);
     delta = gn_dot<T>(dof[j], *reinterpret_cast<const u32x4_t*>((const unsigned char*)p.o + at), delta);
@@ -1334,9 +1378,10 @@ __device__ __forceinline__ void dkv_body(const Params& p, unsigned char* smem, i
 
   GnStay<T, D> ks;
   u32x4_t vf[X::NJ];
-  ks.load((const T*)p.k_pool + koff, hh);
+  ks.at((const T*)p.k_pool + koff, hh);
 #pragma unroll
   for (int j = 0; j < X::NJ; ++j) {
+    ks.load(j);
     const int64_t at = koff * X::ES + 16 * gn_granule<T>(j, hh);
     vf[j] = *reinterpret_cast<const u32x4_t*>((const unsigned char*)p.v_pool + at);
   }
@@ -1529,6 +1574,8 @@ __global__ __launch_bounds__(256, (D == 128 || sizeof(T) == 4 ? 1 : 2)) void dkv
 // The stages of all units of a KV head, one unit after the other, are cut into equal ranges, one per workgroup: whatever the list and the chunk, every
 // compute unit has the same work.  A range covers the end of one unit and the start of the next (or several short ones); the piece of unit u
 // in range b has slot (b + u) Hkv + g.
+// A launch takes the units u0 .. u0 + un - 1 of every head (the slots count from u0); the launches after the first add to the partial sums of dQ, which are
+// un in number: their room is bounded whatever the list.  Any launch sees the stages of a unit's set that the ones before it see, or fewer.
 template <int D> struct GnU {
   typedef Gn<bf16_t, D> X;
   typedef GnF3<D> F;
@@ -1548,12 +1595,12 @@ __device__ __forceinline__ int32_t gn_unit_stages(const Params& p, int g, int32_
   const int32_t n = (int32_t)(((int64_t)p.C * p.G + 31) / 32) - gn_first_stage(p, g, u << (7 - lp), lp);
   return n > 0 ? n : 0;
 }
-__device__ __forceinline__ int32_t gn_unit_count(const Params& p, int g) { return (int32_t)(((int64_t)list_len(p, g) * p.P + GN_ROWS - 1) / GN_ROWS); }
 __device__ __forceinline__ int32_t gn_wave_sum(int32_t v) {
 #pragma unroll
   for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o, 64);
   return __builtin_amdgcn_readfirstlane(v);
 }
+__device__ __forceinline__ int32_t gn_unit_count(const Params& p, int g) { return (int32_t)(((int64_t)list_len(p, g) * p.P + GN_ROWS - 1) / GN_ROWS); }
 // The terms of the rows of Q and dO, [KV head][stage of 32 rows][GnF3::TILE], zeros past the last row; and Delta = <dO, O>.
 template <int D> __global__ __launch_bounds__(256) void row_terms_kernel(Params p, int32_t stages, unsigned char* __restrict__ img) {
   typedef GnF3<D> F;
@@ -1584,8 +1631,8 @@ template <int D> __global__ __launch_bounds__(256) void row_terms_kernel(Params 
     gn_store_terms<D>(out + is_do * F::V + r * F::X::RB + ((c ^ F::X::swz(r)) << 4), v);
   }
 }
-struct GnPiece { int32_t g, u, s0, s1, slot, stages; };   // stages s0 .. s1 - 1 of unit u
-template <int D>
+struct GnPiece { int32_t g, u, s0, s1, slot, set, stages; };   // stages s0 .. s1 - 1 of unit u; its set of partial sums of dQ
+template <int D, bool ADD>
 __device__ __forceinline__ void units_body(const Params& p, unsigned char* smem, int lp, const unsigned char* __restrict__ img, float* __restrict__ part,
                                            float* __restrict__ dq_part, const GnPiece& t) {
   typedef GnU<D> R;
@@ -1715,6 +1762,14 @@ __device__ __forceinline__ void units_body(const Params& p, unsigned char* smem,
 #pragma unroll
       for (int x = 0; x < 4; ++x) fk[n & 1][x] = *reinterpret_cast<const float*>(smem + (at_k + (8 * n + x) * R::KL_ROW));
     };
+    // dims 32 db + 8 a + 4 hh .. + 3: group 4 db + a of the block
+    float4* dst = reinterpret_cast<float4*>(dq_part) + (((int64_t)(t.set * R::PARTS + kp) * p.Hkv + t.g) * (4 * gn_tiles(p.C, p.G, p.P, p.m, 0)) + s) * (D / 8) * 64 + lane + 256 * db;
+    float4 old[4];
+    auto fetch = [&] {
+#pragma unroll
+      for (int a = 0; a < 4; ++a) old[a] = dst[64 * a];
+    };
+    if constexpr (ADD && D == 128) fetch();   // (on their way during the product; at head dim 64 the other workgroup computes meanwhile, and there are no registers for them)
     load(0);
 #pragma unroll
     for (int n = 0; n < R::KEYS / 8; ++n) {
@@ -1726,10 +1781,18 @@ __device__ __forceinline__ void units_body(const Params& p, unsigned char* smem,
       for (int x = 0; x < 4; ++x) dq = __builtin_amdgcn_mfma_f32_32x32x2f32(fk[n & 1][x], __uint_as_float(fd[n & 1][x]), dq, 0, 0, 0);
       __builtin_amdgcn_sched_barrier(0);
     }
-    // dims 32 db + 8 a + 4 hh .. + 3: group 4 db + a of the block
-    float4* dst = reinterpret_cast<float4*>(dq_part) + (((int64_t)(t.u * R::PARTS + kp) * p.Hkv + t.g) * (4 * gn_tiles(p.C, p.G, p.P, p.m, 0)) + s) * (D / 8) * 64 + lane;
+    if constexpr (ADD) {
+      if constexpr (D == 64) fetch();
 #pragma unroll
-    for (int a = 0; a < 4; ++a) dst[64 * (4 * db + a)] = make_float4(dq[4 * a], dq[4 * a + 1], dq[4 * a + 2], dq[4 * a + 3]);
+      for (int a = 0; a < 4; ++a) {
+        dq[4 * a] += old[a].x;
+        dq[4 * a + 1] += old[a].y;
+        dq[4 * a + 2] += old[a].z;
+        dq[4 * a + 3] += old[a].w;
+      }
+    }
+#pragma unroll
+    for (int a = 0; a < 4; ++a) dst[64 * a] = make_float4(dq[4 * a], dq[4 * a + 1], dq[4 * a + 2], dq[4 * a + 3]);
     publish();
   }
   if (active) {
@@ -1737,23 +1800,23 @@ __device__ __forceinline__ void units_body(const Params& p, unsigned char* smem,
     part_store<bf16_t, D>(part, ((int64_t)t.slot * 2 + 1) * 4 + wave, lane, dv, 1.f);
   }
 }
-template <int D>
-__global__ __launch_bounds__(256, GnU<D>::WGS) void bwd_units_kernel(Params p, int32_t ranges, int lp, const unsigned char* __restrict__ img, float* __restrict__ part,
-                                                              float* __restrict__ dq_part) {
+template <int D, bool ADD>
+__global__ __launch_bounds__(256, GnU<D>::WGS) void bwd_units_kernel(Params p, int32_t u0, int32_t un, int32_t ranges, int lp, const unsigned char* __restrict__ img,
+                                                                              float* __restrict__ part, float* __restrict__ dq_part) {
   extern __shared__ __align__(16) unsigned char smem[];
   const int lane = threadIdx.x & 63;
-  const int32_t b = blockIdx.x / p.Hkv, g = blockIdx.x - b * p.Hkv, n_units = gn_unit_count(p, g);
+  const int32_t b = blockIdx.x / p.Hkv, g = blockIdx.x - b * p.Hkv, n_units = gn_unit_count(p, g) < u0 + un ? gn_unit_count(p, g) : u0 + un;
   int32_t all = 0;
-  for (int32_t u = 0; u < n_units; u += 64) all += gn_unit_stages(p, g, u + lane, n_units, lp);
+  for (int32_t u = u0; u < n_units; u += 64) all += gn_unit_stages(p, g, u + lane, n_units, lp);
   all = gn_wave_sum(all);
   ranges = ranges < all ? ranges : all;   // (none of them empty)
   if (b >= ranges) return;
   int32_t at = (int32_t)((int64_t)all * b / ranges);
   const int32_t end = (int32_t)((int64_t)all * (b + 1) / ranges);
   // the unit in which the range starts, and where in it
-  int32_t u = 0, before = 0;
-  for (int32_t u0 = 0; u0 < n_units; u0 += 64) {
-    const int32_t n = gn_unit_stages(p, g, u0 + lane, n_units, lp);
+  int32_t u = u0, before = 0;
+  for (int32_t v0 = u0; v0 < n_units; v0 += 64) {
+    const int32_t n = gn_unit_stages(p, g, v0 + lane, n_units, lp);
     int32_t upto = n;
 #pragma unroll
     for (int o = 1; o < 64; o <<= 1) {
@@ -1761,7 +1824,7 @@ __global__ __launch_bounds__(256, GnU<D>::WGS) void bwd_units_kernel(Params p, i
       if (lane >= o) upto += v;
     }
     const int past = __builtin_popcountll(__ballot(before + upto <= at));
-    u = u0 + past;
+    u = v0 + past;
     if (past < 64) {
       if (past > 0) before += __builtin_amdgcn_readlane(upto, past - 1);
       break;
@@ -1773,7 +1836,7 @@ __global__ __launch_bounds__(256, GnU<D>::WGS) void bwd_units_kernel(Params p, i
     const int32_t lo = __builtin_amdgcn_readfirstlane(gn_first_stage(p, g, u << (7 - lp), lp)), n = S - lo > 0 ? S - lo : 0;
     const int32_t s0 = lo + (at - before), s1 = s0 + (end - at) < lo + n ? s0 + (end - at) : lo + n;
     if (s0 < s1) {
-      units_body<D>(p, smem, lp, img, part, dq_part, GnPiece{g, u, s0, s1, (b + u) * p.Hkv + g, S});
+      units_body<D, ADD>(p, smem, lp, img, part, dq_part, GnPiece{g, u, s0, s1, (b + u - u0) * p.Hkv + g, u - u0, S});
       __syncthreads();
     }
     at += s1 - s0;
@@ -1802,8 +1865,8 @@ constexpr int64_t FINISH_FEW = 4096;
 template <typename T, typename TG, int D, typename L, int NW>
 __global__ __launch_bounds__(64 * NW) void bwd_finish_kernel(Params p, int32_t tiles, int32_t dq_split, const float* __restrict__ dq_part,
                                                          int32_t dq_blocks, int32_t kv_split, const float* __restrict__ kv_part, int lp,
-                                                         int redo_keys) {
-  constexpr bool UNITS = sizeof(L) != sizeof(T);   // the partial sums are those of bwd_units_kernel
+                                                         int redo_keys, int32_t u0, int32_t un) {
+  constexpr bool UNITS = sizeof(L) != sizeof(T);   // the partial sums are those of bwd_units_kernel, its units u0 .. u0 + un - 1
   __shared__ GnRowsLds<D> sh;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   float4 a[GN_GW<D, NW>];
@@ -1814,7 +1877,7 @@ __global__ __launch_bounds__(64 * NW) void bwd_finish_kernel(Params p, int32_t t
       dq_split = 0;
       for (int32_t u = 0; u < n; u += 64)
         dq_split += __builtin_popcountll(__ballot(u + lane < n && gn_first_stage(p, gb, (u + lane) << (7 - lp), lp) <= s));
-      dq_split = __builtin_amdgcn_readfirstlane(dq_split) * GnU<D>::PARTS;
+      dq_split = __builtin_amdgcn_readfirstlane(dq_split < un ? dq_split : un) * GnU<D>::PARTS;
     }
     gn_sum_parts<D, NW>(dq_part, blockIdx.x, blocks * (D / 8) * 64, dq_split, a, [] {});
     const float sc = p.sm_scale;
@@ -1829,7 +1892,7 @@ __global__ __launch_bounds__(64 * NW) void bwd_finish_kernel(Params p, int32_t t
     return;
   }
   // (last units first: their slices were written last and are still in the memory-side cache)
-  const int32_t nb = part_key_blocks(p), b = (int32_t)(gridDim.x - 1 - blockIdx.x), ug = b / (2 * nb), u = ug / p.Hkv, g = ug - u * p.Hkv;
+  const int32_t nb = part_key_blocks(p), b = (int32_t)(gridDim.x - 1 - blockIdx.x), ug = b / (2 * nb), u = u0 + ug / p.Hkv, g = ug - (u - u0) * p.Hkv;
   const int wb = b - ug * 2 * nb, which = wb >= nb, kb = which ? wb - nb : wb;   // block of the slot, {dK, dV}, block of keys
   int64_t slot, next;
   int32_t e0;
@@ -1845,9 +1908,9 @@ __global__ __launch_bounds__(64 * NW) void bwd_finish_kernel(Params p, int32_t t
     slot = ((int64_t)u * kv_split) * p.Hkv + g;
     next = p.Hkv;
     if constexpr (UNITS) {   // the ranges (kv_split of them) that hold a piece of the unit
-      const int32_t n_units = gn_unit_count(p, g);
+      const int32_t n_units = gn_unit_count(p, g) < u0 + un ? gn_unit_count(p, g) : u0 + un;
       int32_t all = 0, before = 0;
-      for (int32_t v = lane; v < n_units; v += 64) {
+      for (int32_t v = u0 + lane; v < n_units; v += 64) {
         const int32_t n = gn_unit_stages(p, g, v, n_units, lp);
         all += n;
         before += v < u ? n : 0;
@@ -1860,7 +1923,7 @@ __global__ __launch_bounds__(64 * NW) void bwd_finish_kernel(Params p, int32_t t
       // range b starts at stage all b / kv_split: the last one that starts at or before a stage
       auto range_of = [&](int32_t at) { return (int32_t)(((int64_t)(at + 1) * ranges - 1) / all); };
       const int32_t first = range_of(before);
-      slot = (int64_t)(first + u) * p.Hkv + g;
+      slot = (int64_t)(first + u - u0) * p.Hkv + g;
       kv_split = range_of(before + mine - 1) - first + 1;
     }
   }
@@ -1970,87 +2033,127 @@ static GnPair gn_pair(const Params& p, bool bf, int32_t max_len) {
 static float gn_two_us(const Params& p, bool bf, int32_t max_len) {
   const float stages = (float)p.C * p.G / (bf ? 64.f : 32.f);
   const float stage = bf && p.D == HD && p.P == TP ? 1.75f : gn_stage_us(p, bf);   // (the kernel of pages of 128 has two roles per pair of waves)
-  int32_t n = 256 / (gn_key_units(p, max_len) * p.Hkv);
-  n = n > 16 ? 16 : n > stages ? (stages < 1.f ? 1 : (int32_t)stages) : n;
-  return gn_plan(p, bf, max_len, true).us + stages / (n < 1 ? 1 : n) * stage + 9.f;
+  const int64_t wgs = (int64_t)gn_key_units(p, max_len) * p.Hkv;
+  int64_t n = 256 / wgs;
+  n = n > 16 ? 16 : n > stages ? (int64_t)stages : n;
+  n = n < 1 ? 1 : n;
+  return gn_plan(p, bf, max_len, true).us + (float)((wgs * n + 255) / 256) * stages / n * stage + 9.f;   // (256 workgroups at a time)
 }
 static bool gn_takes_pair(const Params& p, bool bf, int32_t max_len, const GnPair& pair) {
   return pair.us < 1e29f && pair.us < gn_two_us(p, bf, max_len);
 }
 
-// The backward by units (bwd_units_kernel): ranges per KV head, as many workgroups as run at once, and the estimate of its time in microseconds.
-// A stage of 32 rows x 128 keys takes STAGE (head dim 64: with two workgroups on a compute unit); fewer ranges than fit leave fewer partial sums to add.
-struct GnUnits { int32_t ranges; float us; };
+// The backward by units (bwd_units_kernel): units per launch, ranges per KV head -- as many workgroups as run at once --, and the estimate of its time in
+// microseconds.  A stage of 32 rows x 128 keys takes STAGE (head dim 64: with two workgroups on a compute unit), the partial sums (written, then read) BYTES a
+// byte, K, V and the gradient pool POOL; fewer ranges than fit leave fewer partial sums to add.  Fitted to 35 shapes (2 / 1 to 28 / 4 heads, chunks of
+// 16 to 2048, lists of 1K to 65K tokens): right to 10 % for most, 15 to 30 % low where a unit has only a few stages at head dim 64.
+// Partial sums of dQ take at most UNITS_ROOM, the slots of dK / dV half of it: a launch then still has UNITS_ROOM / 16 KiB = 32768 stages, 128 per workgroup.  In one launch 28 / 4 heads,
+// chunk 512, 100 pages take 1.37 ms and 842 MB of workspace, in two 1.43 and 449; chunk 2048, 40 pages 1.86 and 1317 MB, 1.84 and 540 (half this
+// room: 1.89 and 361); chunk 2048, 200 pages 10.8 ms and 630 MB, for which one launch would need 6 GB.
+constexpr size_t UNITS_ROOM = (size_t)512 << 20;
+struct GnUnits { int32_t un, ranges; float us; };
+static inline size_t gn_delta_bytes(const Params& p) { return gn_up((size_t)p.Hq * p.C * sizeof(float)); }
 static int32_t gn_row_stages(const Params& p) { return (int32_t)(((int64_t)p.C * p.G + 31) / 32); }
 static size_t gn_row_img_bytes(const Params& p) { return gn_up((size_t)p.Hkv * gn_row_stages(p) * 6 * 32 * p.D * 2); }
-static size_t gn_units_dq_bytes(const Params& p, int32_t max_len) {
-  return (size_t)gn_key_units(p, max_len) * gn_tiles(p.C, p.G, p.P, p.m, p.qp) * p.Hkv * GN_ROWS * 128 * 4;   // (at head dim 64 two per unit)
+static size_t gn_unit_dq_bytes(const Params& p) { return (size_t)gn_tiles(p.C, p.G, p.P, p.m, 0) * p.Hkv * GN_ROWS * 128 * 4; }   // (at head dim 64 two per unit)
+static size_t gn_unit_slot_bytes(const Params& p) { return (size_t)p.Hkv * 2 * GN_ROWS * p.D * 4; }
+static int32_t gn_units_most(const Params& p) {   // ranges that run at once
+  const int32_t n = (p.D == 128 ? 256 : 512) / p.Hkv;
+  return n < 1 ? 1 : n;
 }
-static GnUnits gn_units(const Params& p, bool bf, int32_t max_len) {
-  GnUnits best = {1, 1e30f};
-  if (bf || p.qp || p.Hkv > 256 || gn_units_dq_bytes(p, max_len) > ((size_t)4 << 30) || gn_row_img_bytes(p) > ((size_t)1 << 30)) return best;
-  constexpr float START = 28.f, BYTES = 2.5e-7f;   // (bytes written and read again)
-  const float STAGE = p.D == 128 ? 7.8f : 6.5f;
+// what a call needs whose launches take un units each
+static size_t gn_units_bytes(const Params& p, int32_t un) {
+  return gn_delta_bytes(p) + gn_row_img_bytes(p) + (size_t)(gn_units_most(p) + un) * gn_unit_slot_bytes(p) + un * gn_unit_dq_bytes(p);
+}
+static int32_t gn_units_fit(const Params& p, int32_t max_len) {   // most units of a launch
+  const size_t slots = 2 * gn_unit_slot_bytes(p), each = gn_unit_dq_bytes(p) > slots ? gn_unit_dq_bytes(p) : slots;
+  const size_t units = gn_key_units(p, max_len), fit = UNITS_ROOM / each;
+  return (int32_t)(fit < 1 ? 1 : fit < units ? fit : units);
+}
+static GnUnits gn_units(const Params& p, int32_t max_len, size_t room) {   // room: of the workspace
+  GnUnits best = {0, 1, 1e30f};
   const int32_t units = gn_key_units(p, max_len);
-  const int64_t S = gn_row_stages(p), most = (p.D == 128 ? 256 : 512) / p.Hkv;
-  int64_t all = units * S;   // stages of a head, if its list is full: fewer of the units that hold the chunk's own pages
+  if (units < 1 || gn_units_bytes(p, 1) > room) return best;
+  const size_t more = 1 + (room - gn_units_bytes(p, 1)) / (gn_unit_slot_bytes(p) + gn_unit_dq_bytes(p));
+  int32_t fit = gn_units_fit(p, max_len);
+  if (more < (size_t)fit) fit = (int32_t)more;
+  const int32_t launches = (units + fit - 1) / fit, un = (units + launches - 1) / launches;
+  constexpr float START = 22.f, GROUP = 25.f, BYTES = 3e-7f, POOL = 2e-7f;
+  const float STAGE = p.D == 128 ? 6.f : 5.6f, slot = (float)gn_unit_slot_bytes(p);
+  const int64_t S = gn_row_stages(p), most = gn_units_most(p), full = (int64_t)un * S;
+  int64_t last = (int64_t)(units - un * (launches - 1)) * S;   // stages of a head in the last launch, if its list is full: fewer of the units that hold the chunk's own pages
   for (int32_t u = (int32_t)((int64_t)(max_len - p.m) * p.P / GN_ROWS); u < units; ++u) {
     const int64_t tok = (int64_t)u * GN_ROWS - (int64_t)(max_len - p.m) * p.P;
-    all -= tok > 0 ? tok * p.G / 32 : 0;
+    last -= tok > 0 ? tok * p.G / 32 : 0;
   }
-  const float dq = (float)gn_units_dq_bytes(p, max_len) * BYTES;
-  const int64_t q0 = (all + most - 1) / most;
+  last = last < 1 ? 1 : last;
+  const float dq = (float)units * (float)gn_unit_dq_bytes(p) * BYTES;
+  const int64_t q0 = ((launches > 1 ? full : last) + most - 1) / most;
   for (int64_t q = q0; q < q0 + 4; ++q) {
-    const int64_t r = (all + q - 1) / q;
-    const float us = START + (float)q * STAGE + dq + (float)(r + units) * p.Hkv * 1024.f * p.D * BYTES;
-    if (us < best.us) best = {(int32_t)r, us};
+    const int64_t r = ((launches > 1 ? full : last) + q - 1) / q;
+    const float us = START + (launches - 1) * ((float)q * STAGE + GROUP) + (float)((last + r - 1) / r) * STAGE + dq +
+                     (float)(r * launches + units) * slot * BYTES + units * slot * 3.f * POOL;
+    if (us < best.us) best = {un, (int32_t)r, us};
   }
   return best;
 }
-static inline size_t gn_delta_bytes(const Params& p) { return gn_up((size_t)p.Hq * p.C * sizeof(float)); }
-static size_t gn_units_part_bytes(const Params& p, int32_t max_len) {
-  return (size_t)(gn_units(p, false, max_len).ranges + gn_key_units(p, max_len)) * p.Hkv * 2 * GN_ROWS * p.D * 4;
-}
-static bool gn_takes_units(const Params& p, bool bf, int32_t max_len);
-static size_t gn_units_bytes(const Params& p, int32_t max_len) { return gn_delta_bytes(p) + gn_row_img_bytes(p) + gn_units_part_bytes(p, max_len) + gn_units_dq_bytes(p, max_len); }
+static bool gn_takes_units(const Params& p, bool bf, int32_t max_len, const GnUnits& u);
 
 static size_t gn_row_blocks(const Params& p) { return (size_t)gn_tiles(p.C, p.G, p.P, p.m, p.qp) * p.Hkv * 4; }
 // splits that fit `bytes` of partial results of `per` bytes each (at least 1: no partial results)
 static int32_t gn_fit(size_t bytes, size_t per) { return (int32_t)(bytes / per > 32 ? 32 : bytes / per < 2 ? 1 : bytes / per); }
 static size_t gn_row_part_bytes(const Params& p, int32_t split) { return split > 1 ? split * gn_row_blocks(p) * 32 * p.D * 4 : 0; }
-// The fp32 forward in terms: splits of the key range and the estimate of its time in microseconds, the layout of the terms included.  Two workgroups
-// of a compute unit take `unit` for a tile of 32 keys each (192 matrix instructions per SIMD); 512 run at a time.
-struct GnF3Plan { int32_t n; float us; };
-static size_t gn_f3_img_bytes(const Params& p, int32_t max_len) { return gn_up((size_t)p.Hkv * gn_f3_tiles(p, max_len) * 6 * 32 * p.D * 2); }
-static GnF3Plan gn_f3_plan(const Params& p, bool bf, int32_t max_len) {
-  GnF3Plan best = {1, 1e30f};
-  if (bf || p.qp || gn_f3_img_bytes(p, max_len) > ((size_t)1 << 31)) return best;
+// The fp32 forward in terms: splits of the key range, how many launches walk it (each with the image of its own part of the list, which takes
+// at most IMAGE_ROOM: 1.5 times what the listed keys and values take; the sums go on from launch to launch), and the estimate of the time in microseconds, the layout of the terms included.  Two workgroups of a compute unit take `unit` for a
+// tile of 32 keys each (192 matrix instructions per SIMD); 512 run at a time.
+constexpr size_t IMAGE_ROOM = (size_t)512 << 20;
+struct GnF3Plan { int32_t n, launches; float us; };
+static size_t gn_f3_tile_bytes(const Params& p) { return (size_t)p.Hkv * 6 * 32 * p.D * 2; }
+static int32_t gn_f3_fit(const Params& p, int32_t max_len) {   // most tiles of a launch
+  const size_t n = gn_f3_tiles(p, max_len), fit = IMAGE_ROOM / gn_f3_tile_bytes(p);
+  return (int32_t)(fit < 1 ? 1 : fit < n ? fit : n);
+}
+static int32_t gn_f3_launches(const Params& p, int32_t max_len) {
+  const int32_t fit = gn_f3_fit(p, max_len);
+  return (gn_f3_tiles(p, max_len) + fit - 1) / fit;
+}
+static size_t gn_f3_img_bytes(const Params& p, int32_t max_len) {   // (not less for a longer list, whose launches may take fewer)
+  return gn_up((size_t)gn_f3_fit(p, max_len) * gn_f3_tile_bytes(p));
+}
+static size_t gn_f3_split_bytes(const Params& p) { return gn_row_part_bytes(p, 2) / 2 + gn_row_blocks(p) * 32 * 8; }
+static size_t gn_f3_odd_bytes(const Params& p, int32_t max_len) { return gn_up((size_t)gn_f3_fit(p, max_len) * p.Hkv * 4); }   // a word per tile
+static size_t gn_f3_bytes(const Params& p, int32_t max_len, int32_t n) {
+  return gn_f3_img_bytes(p, max_len) + gn_f3_odd_bytes(p, max_len) + (n > 1 || gn_f3_launches(p, max_len) > 1 ? n * gn_f3_split_bytes(p) : 0);
+}
+static GnF3Plan gn_f3_plan(const Params& p, bool bf, int32_t max_len, size_t room) {   // room: of the workspace
+  GnF3Plan best = {1, 1, 1e30f};
+  if (bf || p.qp || gn_f3_bytes(p, max_len, 1) > room) return best;
   constexpr float RAMP = 6.f, LAUNCH = 3.f, PART = 2.56e-4f, LAYOUT = 5.f, BYTES = 5e-7f;
   const float unit = 3.3f * (p.D == 128 ? 1.f : 0.55f), all = (float)gn_f3_tiles(p, max_len), avg = (max_len - 0.5f * p.m) * p.P / 32.f;
-  const int32_t tiles = gn_tiles(p.C, p.G, p.P, p.m, 0), wgs = tiles * p.Hkv;
-  for (int32_t n = 1; n <= 32 && (n == 1 || n <= all); ++n) {
-    const float x = (float)wgs * n, extra = n > 1 ? LAUNCH + x * p.D * PART : 0.f, mine = avg / n > 1.f ? avg / n : 1.f;
-    const float us = gn_rounds(x / 512.f, 0.55f, 0.45f, 0.55f, 0.45f) * mine * unit + ceilf(x / 512.f) * RAMP + extra + LAYOUT + (float)gn_f3_img_bytes(p, max_len) * BYTES;
-    if (us < best.us) best = {n, us};
+  const int32_t tiles = gn_tiles(p.C, p.G, p.P, p.m, 0), wgs = tiles * p.Hkv, launches = gn_f3_launches(p, max_len);
+  for (int32_t n = 1; n <= 32 && (n == 1 || n * launches <= all); ++n) {
+    if (gn_f3_bytes(p, max_len, n) > room) break;
+    const float x = (float)wgs * n, extra = n > 1 ? LAUNCH + x * p.D * PART : 0.f, mine = avg / (n * launches) > 1.f ? avg / (n * launches) : 1.f;
+    const float us = launches * (gn_rounds(x / 512.f, 0.55f, 0.45f, 0.55f, 0.45f) * mine * unit + ceilf(x / 512.f) * RAMP + LAYOUT) +
+                     (launches - 1) * x * p.D * PART + extra + all * (float)gn_f3_tile_bytes(p) * BYTES;
+    if (us < best.us) best = {n, launches, us};
   }
   return best;
 }
-// Against the fp32 matrix pipe.  Timed on 60 shapes (2 / 1 to 28 / 4 heads, head dims 64 and 128, pages of 16 to 128, chunks of 64 to 2048, lists of 8 to 190
-// pages): both estimates are low, the other one by more, hence the factor.  Calls of 30 us and less are up to 15 % faster there, from 45 us on the
-// terms are 1.1 to 1.85 times as fast.  Where the backward takes terms the forward does too (between 27 and 36 us at most 6 % slower), and where
-// it has no room for that the forward does not either: LSE and the products that the backward forms anew then have the same errors, which
-// cancel in dQ (28 / 4 heads, chunk 512, 20 pages of 128, against 64 bits: both fp32 1.11e-6, only the forward in terms 1.33e-6, both in terms 0.71e-6).
+// Against the kernel of every shape, each by its own estimate (S is formed in terms by both, so the backward need not follow).  Timed on the 35 shapes above,
+// the estimates of both are low alike: below 1 the terms are the better one or at most 2 % slower.  The layout of the terms is what few rows do not
+// pay for: 28 / 4 heads of 128, 16 tokens against 16K 82 us with it and 72 without, 128 tokens 180 and 210; 8 / 4 heads, 64 tokens against 64K 300 and 234.
+// Up to 1.22 where the backward takes terms: calls of 27 to 37 us, up to 5 us slower than they could be (6 / 3 heads, chunk 320, 30 pages of 64: 36.7
+// and 31.1), with which the tests reach the edges of this kernel.
 static bool gn_takes_f3(const Params& p, bool bf, int32_t max_len, const GnF3Plan& f) {
-  if (f.us > 1e29f || gn_units(p, bf, max_len).us > 1e29f) return false;
-  return f.us < 1.12f * gn_plan(p, bf, max_len, false).us || gn_takes_units(p, bf, max_len);
-}
-static size_t gn_f3_bytes(const Params& p, int32_t max_len, int32_t n) {
-  return gn_f3_img_bytes(p, max_len) + (n > 1 ? gn_row_part_bytes(p, n) + n * gn_row_blocks(p) * 32 * 8 : 0);
+  if (f.us > 1e29f) return false;
+  const float other = gn_plan(p, bf, max_len, false).us;
+  return f.us < other || (f.us < 1.22f * other && gn_takes_units(p, bf, max_len, gn_units(p, max_len, SIZE_MAX)));
 }
 size_t fwd_generic_workspace_bytes(const Params& p, bool bf, int32_t max_len) {
   const int32_t s = gn_plan(p, bf, max_len, false).n;
   const size_t plain = s > 1 ? gn_row_part_bytes(p, s) + s * gn_row_blocks(p) * 32 * 8 : 256;
-  const GnF3Plan f = gn_f3_plan(p, bf, max_len);
+  const GnF3Plan f = gn_f3_plan(p, bf, max_len, SIZE_MAX);
   const size_t terms = gn_takes_f3(p, bf, max_len, f) ? gn_f3_bytes(p, max_len, f.n) : 0;
   return terms > plain ? terms : plain;
 }
@@ -2068,19 +2171,20 @@ size_t bwd_generic_min_bytes(const Params& p) { return gn_up((size_t)p.Hq * p.C 
 size_t bwd_generic_workspace_bytes(const Params& p, bool bf, int32_t max_len) {
   const size_t delta = gn_up((size_t)p.Hq * p.C * sizeof(float)), pair = bwd_takes_pair(p, bf, max_len) ? bwd_pair_bytes(p, bf, max_len) : 0;
   const size_t two = delta + dq_generic_part_bytes(p, bf, max_len) + gn_key_part_bytes(p, max_len, gn_key_splits(p, bf, max_len));
-  const size_t most = pair > two ? pair : two, units = gn_takes_units(p, bf, max_len) ? gn_units_bytes(p, max_len) : 0;
+  const size_t most = pair > two ? pair : two;
+  if (bf || p.qp) return most;
+  const GnUnits u = gn_units(p, max_len, SIZE_MAX);
+  const size_t units = gn_takes_units(p, bf, max_len, u) ? gn_units_bytes(p, gn_units_fit(p, max_len)) : 0;   // (not less for a longer list, whose launches may take fewer)
   return units > most ? units : most;
 }
 
-// Against the one-launch backward, or dQ and dK / dV one after the other.  Timed on the 60 shapes above: the estimate of the units is right to 15 % (up to
-// 12 us too high below 35 us), that of the others mostly low, hence the factor.  Calls of 50 us and less are up to 30 % faster without, from
-// 60 us on this is 1.1 to 2.3 times as fast: 28 / 4 heads, chunk 512, 16 + 4 pages of 128: 603 -> 309 us; 14 / 2 heads of 64 dims, chunk 1664,
-// 14 + 13 pages of 128: 629 -> 334; 28 / 4 heads of 64, chunk 2048, 128 + 32 pages of 64: 5870 -> 2741.
-static bool gn_takes_units(const Params& p, bool bf, int32_t max_len) {
-  const float us = gn_units(p, bf, max_len).us;
-  if (us > 1e29f) return false;
+// Against the one-launch backward, or dQ and dK / dV one after the other.  On the 35 shapes above what is chosen is the better one, or within 3 %: calls of 50 us
+// and less are up to 30 % faster without, from 60 us on this is 1.2 to 2.3 times as fast: 28 / 4 heads, chunk 512, 16 + 4 pages of 128: 576 -> 284 us, 300 pages
+// 7.7 -> 4.2 ms; 14 / 2 heads of 64 dims, chunk 1664, 14 + 13 pages of 128: 598 -> 323.
+static bool gn_takes_units(const Params& p, bool bf, int32_t max_len, const GnUnits& u) {
+  if (u.us > 1e29f) return false;
   const GnPair pair = gn_pair(p, bf, max_len);
-  return us < 1.08f * (gn_takes_pair(p, bf, max_len, pair) ? pair.us : gn_two_us(p, bf, max_len));
+  return u.us < (gn_takes_pair(p, bf, max_len, pair) ? pair.us : gn_two_us(p, bf, max_len));
 }
 
 // terms of a probability (GnP) where a shape has no kernels of its own
@@ -2113,20 +2217,30 @@ static hipError_t fwd_generic(const Params& p, int32_t max_len, void* ws, size_t
 // *done: whether the call was taken (it has the room, and the estimate is below that of the fp32 matrix pipe)
 template <int D> static hipError_t fwd_terms(const Params& p, int32_t max_len, void* ws, size_t ws_bytes, const char* name, hipStream_t st, bool* done) {
   typedef GnF3<D> F;
-  const GnF3Plan f = gn_f3_plan(p, false, max_len);
-  if (!ws || !gn_takes_f3(p, false, max_len, f) || gn_f3_bytes(p, max_len, f.n) > ws_bytes) return hipSuccess;
+  const GnF3Plan f = ws ? gn_f3_plan(p, false, max_len, ws_bytes) : GnF3Plan{1, 1, 1e30f};
+  if (!gn_takes_f3(p, false, max_len, f)) return hipSuccess;
   *done = true;
   ProfScope prof_(name, st);
-  static DeviceOnce once;
-  if (hipError_t e = ensure_max_dynamic_lds(once, (const void*)fwd_terms_kernel<D>, F::LDS); e != hipSuccess) return e;
+  static DeviceOnce once, once_on;
+  if (hipError_t e = ensure_max_dynamic_lds(once, (const void*)fwd_terms_kernel<D, true>, F::LDS); e != hipSuccess) return e;
+  if (hipError_t e = ensure_max_dynamic_lds(once_on, (const void*)fwd_terms_kernel<D, false>, F::LDS); e != hipSuccess) return e;
   const int32_t tiles = gn_tiles(p.C, p.G, p.P, p.m, 0), n_tiles = gn_f3_tiles(p, max_len), lp = __builtin_ctz(p.P);
   unsigned char* img = (unsigned char*)ws;
-  float* part = (float*)(img + gn_f3_img_bytes(p, max_len));
-  float2* ml = (float2*)((unsigned char*)part + gn_row_part_bytes(p, f.n));
-  { ProfScope layout_("kv_terms", st); kv_terms_kernel<D><<<dim3((unsigned)(n_tiles * p.Hkv)), dim3(256), 0, st>>>(p, n_tiles, lp, img); }
-  if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
-  { ProfScope fwd_("fwd_terms", st); fwd_terms_kernel<D><<<dim3((unsigned)(tiles * p.Hkv * f.n)), dim3(256), F::LDS, st>>>(p, tiles, f.n, lp, max_len, n_tiles, img, part, ml); }
-  if (hipError_t e = hipGetLastError(); e != hipSuccess || f.n == 1) return e;
+  unsigned char* odd = img + gn_f3_img_bytes(p, max_len);
+  float* part = (float*)(odd + gn_f3_odd_bytes(p, max_len));
+  float2* ml = (float2*)((unsigned char*)part + (size_t)f.n * gn_row_blocks(p) * 32 * p.D * 4);
+  for (int32_t l = 0; l < f.launches; ++l) {
+    const int32_t t0 = (int32_t)((int64_t)n_tiles * l / f.launches), nt = (int32_t)((int64_t)n_tiles * (l + 1) / f.launches) - t0;
+    { ProfScope layout_("kv_terms", st); kv_terms_kernel<D><<<dim3((unsigned)(nt * p.Hkv)), dim3(256), 0, st>>>(p, t0, nt, lp, img, odd); }
+    if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
+    {
+      ProfScope fwd_("fwd_terms", st);
+      auto kernel = l ? fwd_terms_kernel<D, false> : fwd_terms_kernel<D, true>;
+      kernel<<<dim3((unsigned)(tiles * p.Hkv * f.n)), dim3(256), F::LDS, st>>>(p, tiles, f.n, lp, max_len, t0, nt, l + 1 == f.launches, img, (const int32_t*)odd, part, ml);
+    }
+    if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
+  }
+  if (f.n == 1) return hipSuccess;
   fwd_combine_kernel<float, D, bf16_t><<<dim3((unsigned)(gn_row_blocks(p))), dim3(64 * COMBINE_WAVES), 0, st>>>(p, tiles, f.n, part, ml, lp);
   return hipGetLastError();
 }
@@ -2168,13 +2282,13 @@ hipError_t launch_dq_generic_bf16_128(const Params& p, int32_t max_len, float* p
 
 template <typename T, typename TG, int D, typename L = T>
 static hipError_t bwd_finish(const Params& p, int32_t dq_split, const float* dq_part, int32_t kv_units, int32_t kv_split, const float* kv_part,
-                             bool redo_keys, hipStream_t st) {
-  const int32_t dq_blocks = dq_split > 1 || sizeof(L) != sizeof(T) ? (int32_t)(gn_row_blocks(p)) : 0;
+                             bool redo_keys, hipStream_t st, int32_t u0 = 0, int32_t un = 0) {
+  const int32_t dq_blocks = dq_split > 1 ? (int32_t)(gn_row_blocks(p)) : 0;
   const int64_t blocks = dq_blocks + (int64_t)kv_units * p.Hkv * 2 * part_key_blocks(p);
   if (blocks <= 0) return hipSuccess;
   auto run = [&](auto kernel, unsigned waves) {
     kernel<<<dim3((unsigned)blocks), dim3(64 * waves), 0, st>>>(p, gn_tiles(p.C, p.G, p.P, p.m, p.qp), dq_split, dq_part, dq_blocks, kv_split, kv_part,
-                                                                __builtin_ctz(p.P), redo_keys);
+                                                                __builtin_ctz(p.P), redo_keys, u0, un);
   };
   if (blocks <= FINISH_FEW) run(bwd_finish_kernel<T, TG, D, L, 8>, 8);
   else run(bwd_finish_kernel<T, TG, D, L, 4>, 4);
@@ -2217,28 +2331,36 @@ hipError_t launch_bwd_pair_bf16_128(const Params& p, int32_t max_len, void* ws, 
 
 template <typename TG, int D>
 static hipError_t bwd_units(Params p, int32_t max_len, void* ws, size_t ws_bytes, const char* name, hipStream_t st, bool* done) {
-  const int32_t n = gn_units(p, false, max_len).ranges, units = gn_key_units(p, max_len);
-  if (dq_overlaps_o(p, false) || !gn_takes_units(p, false, max_len) || gn_units_bytes(p, max_len) > ws_bytes) return hipSuccess;
+  if (p.qp) return hipSuccess;
+  const GnUnits t = gn_units(p, max_len, ws_bytes);
+  if (!gn_takes_units(p, false, max_len, t)) return hipSuccess;
   *done = true;
   ProfScope prof_(name, st);
-  static DeviceOnce once;
-  if (hipError_t e = ensure_max_dynamic_lds(once, (const void*)bwd_units_kernel<D>, GnU<D>::LDS); e != hipSuccess) return e;
-  const int32_t stages = gn_row_stages(p), lp = __builtin_ctz(p.P);
-  p.delta = (float*)ws;
+  static DeviceOnce once, once_add;
+  if (hipError_t e = ensure_max_dynamic_lds(once, (const void*)bwd_units_kernel<D, false>, GnU<D>::LDS); e != hipSuccess) return e;
+  if (hipError_t e = ensure_max_dynamic_lds(once_add, (const void*)bwd_units_kernel<D, true>, GnU<D>::LDS); e != hipSuccess) return e;
+  const int32_t units = gn_key_units(p, max_len), stages = gn_row_stages(p), lp = __builtin_ctz(p.P);
+  p.delta = (float*)ws;   // (formed before anything of dQ is written, which may overlap O, and read again by rows that are formed once more)
   unsigned char* img = (unsigned char*)ws + gn_delta_bytes(p);
   float* kv_part = (float*)(img + gn_row_img_bytes(p));
-  float* dq_part = (float*)((unsigned char*)kv_part + gn_units_part_bytes(p, max_len));
+  float* dq_part = (float*)((unsigned char*)kv_part + (size_t)(t.ranges + t.un) * gn_unit_slot_bytes(p));
   {
     ProfScope terms_("row_terms", st);
     row_terms_kernel<D><<<dim3((unsigned)(stages * p.Hkv)), dim3(256), 0, st>>>(p, stages, img);
   }
   if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
-  {
-    ProfScope units_("bwd_units", st);
-    bwd_units_kernel<D><<<dim3((unsigned)(p.Hkv * n)), dim3(256), GnU<D>::LDS, st>>>(p, n, lp, img, kv_part, dq_part);
+  for (int32_t u0 = 0; u0 < units; u0 += t.un) {
+    const int32_t n = units - u0 < t.un ? units - u0 : t.un;
+    {
+      ProfScope units_("bwd_units", st);
+      auto kernel = u0 ? bwd_units_kernel<D, true> : bwd_units_kernel<D, false>;
+      kernel<<<dim3((unsigned)(p.Hkv * t.ranges)), dim3(256), GnU<D>::LDS, st>>>(p, u0, t.un, t.ranges, lp, img, kv_part, dq_part);
+    }
+    if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
+    // dK / dV of these units, and dQ with the last
+    if (hipError_t e = bwd_finish<float, TG, D, bf16_t>(p, u0 + n < units ? 1 : 2, dq_part, n, t.ranges, kv_part, true, st, u0, t.un); e != hipSuccess) return e;
   }
-  if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
-  return bwd_finish<float, TG, D, bf16_t>(p, 1, dq_part, units, n, kv_part, true, st);
+  return hipSuccess;
 }
 
 template <typename T, typename TG, int D>

@@ -301,3 +301,21 @@ def test_lists_that_end_before_their_stride_are_copied_first():
     assert api._whole_rows(wide[:, 3:]).stride() == (4, 1)
     one = torch.zeros(1, 9, dtype=torch.int32)[:, 2:6]
     assert api._whole_rows(one).stride() == (4, 1)
+
+
+# One workspace, sized for the longest history, leaves the shorter ones the route that they would choose: what the fp32 passes ask for does not fall with the
+# history once they take terms, and partial sums and images have a bound of their own (4 GiB and more without: chunk 2048, 200 pages).
+@pytest.mark.parametrize("heads,D,P,C", [((28, 4), 128, 128, 512), ((28, 4), 128, 128, 2048), ((8, 2), 128, 64, 1088), ((14, 2), 64, 64, 640), ((32, 32), 64, 64, 1152)])
+def test_fp32_workspaces_grow_with_the_history_up_to_a_bound(heads, D, P, C):
+    hq, hkv = heads
+    m, most_f, most_b = C // P, 0, 0
+    rows = C * hq * D * 4
+    for n in sorted({m + i for i in range(0, 300, 7)} | {m + int(300 * 1.25 ** i) for i in range(24)}):
+        if n > 65535:
+            break
+        d = api.AttnDesc(hq, hkv, D, P, C, api.F32, api.F32, D ** -0.5, n * P, hkv * P * D, P * D, D, hq * D, D, n)
+        f, b = api.workspace_bytes(d, -1, api.OP_ATTN_FWD), api.workspace_bytes(d, -1, api.OP_ATTN_BWD)
+        assert b >= most_b, (n, b, most_b)
+        assert f >= 0.9 * most_f, (n, f, most_f)   # (fewer partial sums of O where a longer list needs fewer splits)
+        assert f <= (513 << 20) + 32 * (rows + C * hq * 8) and b <= (820 << 20) + 3 * rows + 16384, (n, f, b)
+        most_f, most_b = max(f, most_f), b

@@ -17,7 +17,7 @@ SHAPES = [Workload("d128", 2, 1, 128, 128, 1024, 128 * 40, None, "f32", "f32", 1
           Workload("d64", 6, 2, 64, 32, 800, 32 * 130, None, "f32", "f32", 0.125, q_scale=3., boost_frac=0.05, seed=502)]
 ROUTES = [("asked", "asked"), ("asked", "least"), ("none", "asked"), ("none", "least"), ("asked", "over_o")]
 PINNED = {"asked": (("fwd_terms",), ()), "none": ((), ("fwd_terms",))}
-PINNED_BWD = {"asked": (("bwd_units",), ()), "least": ((), ("bwd_units",)), "over_o": ((), ())}
+PINNED_BWD = {"asked": (("bwd_units",), ()), "least": ((), ("bwd_units",)), "over_o": (("bwd_units",), ())}
 
 
 def exact(w, x):
@@ -130,3 +130,72 @@ def test_values_that_are_not_finite_without_a_workspace(w, what):
     if what == "huge":
         for n, a, b in zip(NAMES[2:], got[2:], want[2:]):
             assert rel(a, b) <= 5e-6, n
+
+
+# Lists that the passes walk in several launches: the backward because of the room that its workspace leaves for the partial sums of dQ (`units` units of 128
+# keys of all heads a launch), the forward where the terms of the listed keys pass 512 MiB.  A last launch that is not full, units of the chunk's own pages
+# in it, values that are not finite in a key of an early launch that all rows see, and in one of a later launch that few see.
+def room_for(w, units):
+    up = lambda x: (x + 255) // 256 * 256
+    stages, tiles = (w.C * w.G + 31) // 32, (w.C * w.G + 127) // 128
+    slot = w.Hkv * 2 * 128 * w.D * 4
+    most = (256 if w.D == 128 else 512) // w.Hkv
+    return up(w.Hq * w.C * 4) + up(w.Hkv * stages * 6 * 32 * w.D * 2) + (most + units) * slot + units * tiles * w.Hkv * 128 * 128 * 4
+
+
+IN_LAUNCHES = [(Workload("d128", 28, 4, 128, 128, 512, 128 * 40, None, "f32", "f32", 128 ** -0.5, boost_frac=0.05, seed=511), 7, 6),
+               (Workload("d64", 14, 2, 64, 64, 704, 64 * 61, None, "f32", "bf16", 0.125, boost_frac=0.05, seed=512), 12, 3)]
+
+
+@pytest.mark.parametrize("what", ["finite", "seen by all", "seen by few"])
+@pytest.mark.parametrize("w,units,launches", IN_LAUNCHES, ids=lambda v: getattr(v, "name", str(v)))
+def test_backward_in_several_launches(w, units, launches, what):
+    x = make_inputs(w, "cuda")
+    desc = api.make_desc(x["q"], x["k_pool"], w.N, w.sm_scale, x["dk_pool"].dtype)
+    args = (desc, x["q"], x["k_pool"], x["v_pool"], x["page_table"])
+    want = exact(w, x)
+    hit = torch.zeros((w.C, w.Hq), dtype=torch.bool, device="cuda")   # rows that see the value, in the heads of KV head 0
+    if what != "finite":
+        page = 1 if what == "seen by all" else w.n - 1
+        x["v_pool"][x["page_table"][page].long(), 0, w.P // 2, 3] = math.inf
+        hit[:, :w.G] = (w.N - w.C + torch.arange(w.C, device="cuda") >= page * w.P + w.P // 2)[:, None]
+    o, lse = api.paged_attn_fwd(*args)
+    for pool in ("dk_pool", "dv_pool"):
+        x[pool].fill_(0.25)
+    ws = torch.empty(room_for(w, units), dtype=torch.uint8, device="cuda")
+    api.profile_reset()
+    api.profile_enable(1)
+    dq = api.paged_attn_bwd(*args, o, lse, x["d_o"], x["dk_pool"], x["dv_pool"], workspace=ws)
+    torch.cuda.synchronize()
+    seen = api.profile_read()
+    api.profile_enable(0)
+    assert seen["bwd_units"][1] == launches
+    lost = torch.zeros((w.n_phys, w.Hkv), dtype=torch.bool, device="cuda")   # Delta of those rows is not finite: dK of every key that they see
+    lost[:, 0] = bool(hit.any())
+    assert torch.equal(dq.isfinite().all(2), ~hit) and torch.equal(x["dk_pool"].isfinite().all(3).all(2), ~lost) and x["dv_pool"].isfinite().all()
+    bf = w.grad_dtype == "bf16"
+    for n, a, b in (("dq", dq[~hit], want[2][~hit]), ("dk", x["dk_pool"][~lost], want[3][~lost] + 0.25), ("dv", x["dv_pool"], want[4] + 0.25)):
+        err = rel(a, b)
+        print(w.name, what, n, f"{err:.2e}", flush=True)
+        assert err <= (3e-3 if bf and n != "dq" else 2e-6), (n, err)   # (2^-9 of a bf16 element; fp32 sums as above)
+
+
+@pytest.mark.parametrize("w", [Workload("d128", 64, 32, 128, 128, 512, 128 * 100, None, "f32", "f32", 128 ** -0.5, seed=513),
+                               Workload("d64", 64, 32, 64, 64, 512, 64 * 400, None, "f32", "f32", 0.125, seed=514)], ids=lambda w: w.name)
+def test_forward_in_several_launches(w):
+    x = make_inputs(w, "cuda")
+    x["k_pool"][x["page_table"][3].long(), :, 7, 0] = -math.inf   # (a weight of 0, seen in the first launch)
+    x["q"][..., 0].abs_().add_(0.01)
+    desc = api.make_desc(x["q"], x["k_pool"], w.N, w.sm_scale)
+    api.profile_reset()
+    api.profile_enable(1)
+    o, lse = api.paged_attn_fwd(desc, x["q"], x["k_pool"], x["v_pool"], x["page_table"])
+    torch.cuda.synchronize()
+    seen = api.profile_read()
+    api.profile_enable(0)
+    assert seen["fwd_terms"][1] >= 2 and seen["kv_terms"][1] == seen["fwd_terms"][1]
+    pages, unseen = x["page_table"].long()[:w.n], torch.arange(w.N, device="cuda")[None] > (w.N - w.C + torch.arange(w.C, device="cuda"))[:, None]
+    for h in range(0, w.Hq, 9):
+        K, V = (x[n][pages, h // w.G].reshape(-1, w.D).double() for n in ("k_pool", "v_pool"))
+        S = ((x["q"][:, h].double() @ K.T) * w.sm_scale).masked_fill(unseen, -math.inf)
+        assert rel(o[:, h], torch.softmax(S, 1) @ V) <= 2e-6 and rel(lse[h], torch.logsumexp(S, 1)) <= 1e-7, h

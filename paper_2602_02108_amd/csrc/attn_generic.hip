@@ -84,14 +84,17 @@ template <int N> __device__ __forceinline__ void gn_zero(f32x16 (&v)[N]) {
 
 // ---- products of fp32 tensors on the bf16 matrix pipe ---------------------------------------------
 // An fp32 value is the sum of three bf16 values, all 24 bits: a = a0 + a1 + a2, each the rounding of what the ones before it left.  A
-// product of two such sums takes six bf16 matrix instructions -- a0 b0, a0 b1, a1 b0, a1 b1, a0 b2, a2 b0; the others are below 2^-26 of
-// it -- and these 192 cycles where v_mfma_f32_32x32x2 takes 512.
-// (Values below 2^-109 keep fewer bits: the smallest bf16 is 2^-133.)
+// product of two such sums takes six bf16 matrix instructions -- a0 b0, a0 b1, a1 b0, a1 b1, a0 b2, a2 b0; the others are at most 2^-24 of
+// it, 2^-27 rms -- and these 192 cycles where v_mfma_f32_32x32x2 takes 512.
+// Values below 2^-109 keep fewer bits: the smallest bf16 is 2^-133.  V, dO and dS, on which the results depend linearly, are therefore lifted by 2^16 first (GN_LIFT;
+// what overflows -- products of dO and V of 2^96 -- is not finite and formed anew from fp32 products): they keep their bits down to the smallest normal fp32 value.  Not lifted are Q and K,
+// whose products are the argument of an exponential, and P, whose largest value in a row is not small: a product is off by 2^-134 times the other value.
 // S is formed this way on every route.  What the backward makes of S and LSE then has the errors that the forward's S has, whichever
 // kernels the two passes take; those of different products do not cancel in dQ.  Against 64 bits, 2 / 1 heads of 128, logits of 3 times
 // the spread, chunk 1024, 40 pages: dQ both passes with fp32 products 1.95e-6, one of them in terms 4.5e-6 (forward) and 4.1e-6 (backward), S in
 // terms on either route 1.2 to 1.4e-6.
 constexpr float GN_EDGE = 0x1.FFp127f;   // the least value that bf16 rounds to an infinity
+constexpr float GN_LIFT = 0x1p16f, GN_LOWER = 0x1p-16f;
 struct GnTerms { uint32_t w[3]; };
 // two values.  What would round to an infinity is cut off instead; infinities and NaN are their own first term.
 __device__ __forceinline__ GnTerms gn_terms(float a, float b) {
@@ -127,6 +130,10 @@ template <bool PLAIN> __device__ __forceinline__ void gn_load_terms(const u32x4_
 #pragma unroll
     for (int n = 0; n < 3; ++n) t[n][k] = w.w[n];
   }
+}
+__device__ __forceinline__ void gn_lift(u32x4_t& v) {
+#pragma unroll
+  for (int k = 0; k < 4; ++k) v[k] = __float_as_uint(__uint_as_float(v[k]) * GN_LIFT);
 }
 // c += the product of two values of three terms, the smallest first; small += all of it but the product of the first terms
 __device__ __forceinline__ void gn_mma_terms(const u32x4_t (&a)[3], const u32x4_t& b0, const u32x4_t& b1, const u32x4_t& b2, f32x16& small, f32x16& c) {
@@ -950,9 +957,9 @@ __global__ __launch_bounds__(64 * COMBINE_WAVES) void fwd_combine_kernel(Params 
         }
     }
   }
-  const float inv = 1.f / l_sum;
+  const float inv = 1.f / l_sum, by = sizeof(L) != sizeof(T) ? inv * GN_LOWER : inv;   // (sums of lifted values)
 #pragma unroll
-  for (int j = 0; j < GW; ++j) { acc[j].x *= inv; acc[j].y *= inv; acc[j].z *= inv; acc[j].w *= inv; }
+  for (int j = 0; j < GW; ++j) { acc[j].x *= by; acc[j].y *= by; acc[j].z *= by; acc[j].w *= by; }
   int i, h;
   uint32_t bad = gn_rows_out<L, D, NW>(sh, acc, true, [&](int, int row, int d, const float4& r) __attribute__((always_inline)) {
     if (gn_out_row(p, tiles, block, row, i, h))
@@ -981,7 +988,7 @@ template <int D> __device__ __forceinline__ void gn_store_terms(unsigned char* d
 }
 static inline int32_t gn_f3_tiles(const Params& p, int32_t max_len) { return (int32_t)(((int64_t)max_len * p.P + 31) / 32); }
 
-// The terms of the listed keys of n_tiles tiles from t0 on, [KV head][tile of 32 list tokens][TILE]; zeros past the list.  odd[KV head][tile][4]: a byte per
+// The terms of the listed keys (V lifted) of n_tiles tiles from t0 on, [KV head][tile of 32 list tokens][TILE]; zeros past the list.  odd[KV head][tile][4]: a byte per
 // wave, whether a key of the tile is not finite.
 template <int D>
 __global__ __launch_bounds__(256) void kv_terms_kernel(Params p, int32_t t0, int32_t n_tiles, int lp, unsigned char* __restrict__ img, unsigned char* __restrict__ odd) {
@@ -1004,6 +1011,9 @@ __global__ __launch_bounds__(256) void kv_terms_kernel(Params p, int32_t t0, int
     if (!is_v) {
 #pragma unroll
       for (int k = 0; k < 8; ++k) z = __builtin_fmaf(__uint_as_float(v[k >> 2][k & 3]), 0.f, z);
+    } else {
+      gn_lift(v[0]);
+      gn_lift(v[1]);
     }
     gn_store_terms<D>(out + is_v * F::V + r * F::X::RB + ((c ^ F::X::swz(r)) << 4), v);
   }
@@ -1166,12 +1176,12 @@ __global__ __launch_bounds__(256, 2) void fwd_terms_kernel(Params p, int32_t til
     part_store<bf16_t, D>(part, at, tid & 63, of, 1.f);
     if (!(tid & 32)) part_ml[at * 32 + (tid & 31)] = make_float2(l_tot > 0.f ? m_run : -INFINITY, l_tot);
   } else {
-    const float inv = 1.f / l_tot;
+    const float inv = 1.f / l_tot, low = inv * GN_LOWER;
     const int32_t i = (int32_t)div_g(p2, (uint32_t)(valid ? r : 0)), h = b.g * p2.G + (valid ? r - i * p2.G : 0);
     uint32_t bad = gn_either_half(valid && gn_not_finite(of));
     if (valid && !((bad >> (tid & 31)) & 1)) {
       float* dst = (float*)p2.o + (int64_t)i * p2.q_tok_stride + (int64_t)h * p2.q_head_stride;
-      part_emit<bf16_t, D>(of, (tid >> 5) & 1, [&](int d, float v0, float v1, float v2, float v3) { part_store4<float>(dst + d, v0 * inv, v1 * inv, v2 * inv, v3 * inv); });
+      part_emit<bf16_t, D>(of, (tid >> 5) & 1, [&](int d, float v0, float v1, float v2, float v3) { part_store4<float>(dst + d, v0 * low, v1 * low, v2 * low, v3 * low); });
     }
     if (valid && !(tid & 32)) p2.lse[(int64_t)h * p2.C + i] = gn_lse(p2, m_run, l_tot);
     for (; bad; bad &= bad - 1) {
@@ -1601,7 +1611,7 @@ __device__ __forceinline__ int32_t gn_wave_sum(int32_t v) {
   return __builtin_amdgcn_readfirstlane(v);
 }
 __device__ __forceinline__ int32_t gn_unit_count(const Params& p, int g) { return (int32_t)(((int64_t)list_len(p, g) * p.P + GN_ROWS - 1) / GN_ROWS); }
-// The terms of the rows of Q and dO, [KV head][stage of 32 rows][GnF3::TILE], zeros past the last row; and Delta = <dO, O>.
+// The terms of the rows of Q and (lifted) dO, [KV head][stage of 32 rows][GnF3::TILE], zeros past the last row; and Delta = <dO, O>.
 template <int D> __global__ __launch_bounds__(256) void row_terms_kernel(Params p, int32_t stages, unsigned char* __restrict__ img) {
   typedef GnF3<D> F;
   constexpr int NG = F::X::NG;   // lanes of a row, eight values each
@@ -1627,6 +1637,8 @@ template <int D> __global__ __launch_bounds__(256) void row_terms_kernel(Params 
 #pragma unroll
       for (int k = 1; k < NG; k <<= 1) d += __shfl_xor(d, k, 64);
       if (valid && c == 0) p.delta[(int64_t)h * p.C + i] = d;
+      gn_lift(v[0]);
+      gn_lift(v[1]);
     }
     gn_store_terms<D>(out + is_do * F::V + r * F::X::RB + ((c ^ F::X::swz(r)) << 4), v);
   }
@@ -1649,17 +1661,24 @@ __device__ __forceinline__ void units_body(const Params& p, unsigned char* smem,
   const int64_t koff = (int64_t)p.page_table[l] * p.pool_page_stride + (int64_t)t.g * p.pool_head_stride + (int64_t)(kq & (p.P - 1)) * p.pool_tok_stride;
   // rows before r_key do not see the key
   const int32_t r_key = !kvalid ? INT32_MAX : pos > first_q ? (int32_t)(pos - first_q) * p.G : 0, r_key_max = __builtin_amdgcn_readlane(r_key, 31);
-  u32x4_t kf[X::NJ][3], vf[X::NJ][3];
+  u32x4_t kf[X::NJ][3], vf[X::NJ][3], raw[2][X::NJ][2];
+#pragma unroll
+  for (int j = 0; j < X::NJ; ++j)
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+      raw[0][j][e] = reinterpret_cast<const u32x4_t*>((const float*)p.k_pool + koff + 16 * j + 8 * hh)[e];
+      raw[1][j][e] = reinterpret_cast<const u32x4_t*>((const float*)p.v_pool + koff + 16 * j + 8 * hh)[e];
+    }
 #pragma unroll
   for (int j = 0; j < X::NJ; ++j) {
-    const u32x4_t* k = reinterpret_cast<const u32x4_t*>((const float*)p.k_pool + koff + 16 * j + 8 * hh);
-    const u32x4_t* v = reinterpret_cast<const u32x4_t*>((const float*)p.v_pool + koff + 16 * j + 8 * hh);
-    const u32x4_t k0 = k[0], k1 = k[1];
     u32x4_t* kl = reinterpret_cast<u32x4_t*>(smem + R::KL + kq * R::KL_ROW + 64 * j + 32 * hh);
-    kl[0] = k0;
-    kl[1] = k1;
-    gn_load_terms<false>(k0, k1, kf[j]);
-    gn_load_terms<false>(v[0], v[1], vf[j]);
+    kl[0] = raw[0][j][0];
+    kl[1] = raw[0][j][1];
+    gn_load_terms<false>(raw[0][j][0], raw[0][j][1], kf[j]);
+    gn_lift(raw[1][j][0]);
+    gn_lift(raw[1][j][1]);
+    gn_load_terms<false>(raw[1][j][0], raw[1][j][1], vf[j]);
+    __builtin_amdgcn_sched_barrier(0);   // (one after the other: the comparisons of all of them would be spilled)
   }
   f32x16 dk[X::DB], dv[X::DB];
   gn_zero(dk);
@@ -1685,7 +1704,7 @@ __device__ __forceinline__ void units_body(const Params& p, unsigned char* smem,
         const int32_t i = (int32_t)div_g(p, (uint32_t)r);
         const int64_t at = (int64_t)(t.g * p.G + (r - i * p.G)) * p.C + i;
         st_l = p.lse[at] * 1.4426950408889634f;
-        st_d = p.delta[at];
+        st_d = p.delta[at] * (GN_LIFT * GN_LIFT);
       }
     }
   };
@@ -1736,7 +1755,7 @@ __device__ __forceinline__ void units_body(const Params& p, unsigned char* smem,
 #pragma unroll
               for (int x = v * (16 / NV); x < (v + 1) * (16 / NV); ++x) {
                 const int row = 8 * (x >> 2) + (x & 3);
-                sv[0][x] = sv[0][x] * (dp[0][x] + dp[1][x] - st[64 + row + 4 * hh]);
+                sv[0][x] = sv[0][x] * (dp[0][x] + dp[1][x] - st[64 + row + 4 * hh]);   // (dP, Delta and dS: lifted twice)
                 ds_out[row * (R::DS_ROW / 4)] = sv[0][x];
               }
 #pragma unroll
@@ -1866,7 +1885,8 @@ template <typename T, typename TG, int D, typename L, int NW>
 __global__ __launch_bounds__(64 * NW) void bwd_finish_kernel(Params p, int32_t tiles, int32_t dq_split, const float* __restrict__ dq_part,
                                                          int32_t dq_blocks, int32_t kv_split, const float* __restrict__ kv_part, int lp,
                                                          int redo_keys, int32_t u0, int32_t un) {
-  constexpr bool UNITS = sizeof(L) != sizeof(T);   // the partial sums are those of bwd_units_kernel, its units u0 .. u0 + un - 1
+  constexpr bool UNITS = sizeof(L) != sizeof(T);   // the partial sums are those of bwd_units_kernel, its units u0 .. u0 + un - 1: of lifted values (dV), or of dS, lifted twice
+  constexpr float low = UNITS ? GN_LOWER * GN_LOWER : 1.f;
   __shared__ GnRowsLds<D> sh;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   float4 a[GN_GW<D, NW>];
@@ -1884,7 +1904,7 @@ __global__ __launch_bounds__(64 * NW) void bwd_finish_kernel(Params p, int32_t t
     int i, h;
     uint32_t bad = gn_rows_out<L, D, NW>(sh, a, true, [&](int, int row, int d, const float4& r) __attribute__((always_inline)) {
       if (gn_out_row(p, tiles, blockIdx.x, row, i, h))
-        part_store4<T>((T*)p.d_q + (int64_t)i * p.q_tok_stride + (int64_t)h * p.q_head_stride + d, r.x * sc, r.y * sc, r.z * sc, r.w * sc);
+        part_store4<T>((T*)p.d_q + (int64_t)i * p.q_tok_stride + (int64_t)h * p.q_head_stride + d, r.x * sc * low, r.y * sc * low, r.z * sc * low, r.w * sc * low);
     });
     for (bad &= ((1u << 32 / NW) - 1) << (32 / NW * wave); bad; bad &= bad - 1)
       if (gn_out_row(p, tiles, blockIdx.x, __builtin_ctz(bad), i, h))
@@ -1945,7 +1965,8 @@ __global__ __launch_bounds__(64 * NW) void bwd_finish_kernel(Params p, int32_t t
     }
   });
   uint32_t bad = gn_rows_out<L, D, NW>(sh, a, redo_keys, [&](int k, int, int, const float4& r) __attribute__((always_inline)) {
-    if (dst[k]) part_store4<TG>(dst[k], old[k].x + r.x, old[k].y + r.y, old[k].z + r.z, old[k].w + r.w);
+    const float by = UNITS && which ? GN_LOWER : low;
+    if (dst[k]) part_store4<TG>(dst[k], old[k].x + r.x * by, old[k].y + r.y * by, old[k].z + r.z * by, old[k].w + r.w * by);
   });
   for (bad &= ((1u << 32 / NW) - 1) << (32 / NW * wave); bad; bad &= bad - 1) {
     const int32_t x = __builtin_ctz(bad), k = 32 * kb + x, e = e0 + (p.qp ? 0 : x >> lp);

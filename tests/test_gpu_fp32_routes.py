@@ -132,6 +132,22 @@ def test_values_that_are_not_finite_without_a_workspace(w, what):
             assert rel(a, b) <= 5e-6, n
 
 
+# Tensors that are small throughout: what the results depend on linearly keeps 24 bits down to the smallest normal value, 2^-126 (as three bf16 terms without
+# more: down to 2^-109; at 2^-117 they would be 4e-6 off, at 2^-121 7e-5), also where two of them together make dS small.  The line is that of values of
+# the usual size.  Where dO V passes 2^96 the sums overflow on the way and are formed once more from fp32 products: the tolerance of fp32.
+@pytest.mark.parametrize("fwd,bwd", [("asked", "asked"), ("none", "least")])
+@pytest.mark.parametrize("v_exp,do_exp", [(-117, 0), (0, -117), (-58, -58), (-110, 90), (85, 0), (0, 85), (105, 0)])
+@pytest.mark.parametrize("w", [SHAPES[0].with_(C=384, N=128 * 24), SHAPES[1].with_(N=32 * 130)], ids=lambda w: w.name)
+def test_tensors_of_any_size_keep_their_bits(w, v_exp, do_exp, fwd, bwd):
+    x = make_inputs(w, "cuda")
+    x["v_pool"].mul_(2. ** v_exp)
+    x["d_o"].mul_(2. ** do_exp)
+    errs = {n: rel(a, b) for n, a, b in zip(NAMES, run(w, x, fwd, bwd), exact(w, x))}
+    print(w.name, v_exp, do_exp, fwd, bwd, {n: f"{e:.2e}" for n, e in errs.items()}, flush=True)
+    if fwd == "asked":
+        assert all(errs[n] <= (2e-5 if v_exp == 105 else LIMITS[fwd][n]) for n in NAMES), errs
+
+
 # Lists that the passes walk in several launches: the backward because of the room that its workspace leaves for the partial sums of dQ (`units` units of 128
 # keys of all heads a launch), the forward where the terms of the listed keys pass 512 MiB.  A last launch that is not full, units of the chunk's own pages
 # in it, values that are not finite in a key of an early launch that all rows see, and in one of a later launch that few see.
@@ -199,3 +215,46 @@ def test_forward_in_several_launches(w):
         K, V = (x[n][pages, h // w.G].reshape(-1, w.D).double() for n in ("k_pool", "v_pool"))
         S = ((x["q"][:, h].double() @ K.T) * w.sm_scale).masked_fill(unseen, -math.inf)
         assert rel(o[:, h], torch.softmax(S, 1) @ V) <= 2e-6 and rel(lse[h], torch.logsumexp(S, 1)) <= 1e-7, h
+
+
+# Calls large enough that neither rows nor keys are split: the kernels of every shape write O, dQ and the gradient pools themselves.  They are left to calls
+# with the least workspace; with dQ over O, Delta is formed beforehand or by the dQ kernel.
+UNSPLIT = [Workload("keys_d128", 8, 4, 128, 16, 32, 16 * 1100, None, "f32", "bf16", 0.088, seed=521),
+           Workload("rows_d64", 32, 32, 64, 64, 1152, 64 * 20, None, "f32", "f32", 0.125, seed=522),
+           Workload("rows_d128", 64, 32, 128, 32, 320, 32 * 40, None, "f32", "f32", 0.088, seed=523),
+           Workload("keys_d64", 6, 3, 64, 32, 64, 32 * 1100, None, "f32", "f32", 0.125, seed=524)]
+
+
+@pytest.mark.parametrize("what", ["plain", "over_o", "beside_o", "v_nan", "q_inf"])
+@pytest.mark.parametrize("w", UNSPLIT, ids=lambda w: w.name)
+def test_unsplit_kernels_with_the_least_workspace(w, what):
+    x = make_inputs(w, "cuda")
+    desc = api.make_desc(x["q"], x["k_pool"], w.N, w.sm_scale, x["dk_pool"].dtype)
+    args = (desc, x["q"], x["k_pool"], x["v_pool"], x["page_table"])
+    want = exact(w, x)
+    hit, lost = torch.zeros((w.C, w.Hq), dtype=torch.bool, device="cuda"), torch.zeros((w.n_phys, w.Hkv), dtype=torch.bool, device="cuda")
+    if what == "v_nan":     # a token of the chunk's last page: the rows before it do not see it
+        x["v_pool"][x["page_table"][w.n - 1].long(), 0, w.P // 2, 3] = math.nan
+        hit[w.C - w.P // 2:, :w.G] = True
+    elif what == "q_inf":   # a row of the chunk's first page: the keys after it are not seen by it
+        x["q"][w.P // 2, 0, 5] = math.inf
+        hit[w.P // 2, 0] = True
+    if hit.any():
+        lost[x["page_table"].long()[:w.n if what == "v_nan" else w.n_past + 1], 0] = True   # (dK of the keys that they see)
+    big = torch.empty((w.C + 1, w.Hq, w.D), device="cuda")
+    o, out = big[:-1], big[1:] if what == "beside_o" else None   # (dQ one row further on than O)
+    with pu.kernels_ran(("attn_fwd_generic",), absent=("fwd_terms",)):
+        o, lse = api.paged_attn_fwd(*args, o=o, workspace=torch.empty(256, dtype=torch.uint8, device="cuda"))
+    assert torch.equal(o.isfinite().all(2), ~hit) and rel(o[~hit], want[0][~hit]) <= 3e-6
+    ws = torch.empty((w.Hq * w.C * 4 + 255) // 256 * 256, dtype=torch.uint8, device="cuda")
+    with pu.kernels_ran(("attn_bwd_generic",), absent=("bwd_units",)):
+        dq = api.paged_attn_bwd(*args, o, lse, x["d_o"], x["dk_pool"], x["dv_pool"], d_q=o if what == "over_o" else out, workspace=ws)
+    assert torch.equal(dq.isfinite().all(2), ~hit)
+    tol = 3e-3 if w.grad_dtype == "bf16" else 6e-6
+    seen_dv = ~lost if what == "q_inf" else torch.ones_like(lost)
+    part = torch.zeros_like(lost)
+    part[x["page_table"].long()[w.n_past], 0] = bool(hit.any())   # (a page of which the row sees the first half only)
+    for n, a, b, ok in (("dk", x["dk_pool"], want[3], ~lost), ("dv", x["dv_pool"], want[4], seen_dv)):
+        ok = ok & ~part
+        assert a[ok].isfinite().all() and rel(a[ok], b[ok]) <= tol, (n, rel(a[ok], b[ok]))
+    assert rel(dq[~hit], want[2][~hit]) <= 6e-6

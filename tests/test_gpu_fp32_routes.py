@@ -102,13 +102,15 @@ def test_values_at_the_edge_of_fp32_that_carry_weight(w, fwd, bwd):
             assert rel(a, b) <= 2e-5, (n, rel(a, b))
 
 
-# Values that are not finite, without room for the other route: as they reach those who see them there.
+# Values that are not finite, on either route: as they reach those who see them there.
+@pytest.mark.parametrize("fwd,bwd", [("none", "least"), ("asked", "asked")])
 @pytest.mark.parametrize("what", ["huge", "weight_0", "inf", "nan"])
 @pytest.mark.parametrize("w", SHAPES, ids=lambda w: w.name)
-def test_values_that_are_not_finite_without_a_workspace(w, what):
+def test_values_that_are_not_finite(w, what, fwd, bwd):
     w = w.with_(q_scale=1.)
     x = make_inputs(w, "cuda")
     page, k, q = x["page_table"][w.n_past // 2].long(), x["k_pool"], x["q"]
+    hit = torch.zeros((w.C, w.Hq), dtype=torch.bool, device="cuda")   # rows that take up the value
     if what == "huge":
         k[page, :, 3, 0] = 3.4e38
         q[..., 0] = -1
@@ -117,19 +119,28 @@ def test_values_that_are_not_finite_without_a_workspace(w, what):
         q[..., 0].abs_().add_(0.01)
     elif what == "inf":
         q[100, 1, 5] = math.inf
-    else:
-        k[x["page_table"][w.n - 2].long(), 0, 3, 7] = math.nan   # (the rows before it do not see it)
-    got, want = run(w, x, "none", "least"), exact(w, x)
-    row_nan = want[0].isnan().any(2)
-    for n, a, b in zip(NAMES[:2], got[:2], want[:2]):
-        nan = row_nan if n == "o" else row_nan.T
-        assert torch.equal(a.isnan() if n == "lse" else a.isnan().all(2), nan), n
-        assert rel(a[~nan], b[~nan]) <= 5e-6, n
-    if what in ("huge", "weight_0"):
-        assert not row_nan.any()
+        hit[100, 1] = True
+    else:   # (the rows before it do not see it)
+        k[x["page_table"][w.n - 2].long(), 0, 3, 7] = math.nan
+        hit[:, :w.G] = (w.N - w.C + torch.arange(w.C, device="cuda") >= (w.n - 2) * w.P + 3)[:, None]
+    got, want = run(w, x, fwd, bwd), exact(w, x)
+    assert torch.equal(want[0].isnan().any(2), hit)
+    assert torch.equal(got[0].isnan().all(2), hit) and torch.equal(got[1].isnan(), hit.T)
+    assert rel(got[0][~hit], want[0][~hit]) <= 5e-6 and rel(got[1][~hit.T], want[1][~hit.T]) <= 5e-6
     if what == "huge":
         for n, a, b in zip(NAMES[2:], got[2:], want[2:]):
             assert rel(a, b) <= 5e-6, n
+    elif what != "weight_0":
+        # dQ of those rows, and dK, dV of every key that one of them sees (of page pg and before it all do, of the pages after it none or some)
+        pages = x["page_table"].long()[:w.n]
+        seen = pages if what == "nan" else pages[:w.n_past + 100 // w.P]
+        clear = torch.ones((w.n_phys, w.Hkv), dtype=torch.bool, device="cuda")
+        clear[seen, 0] = False
+        ok = ~hit & want[2].isfinite().all(2)   # (the reference multiplies an unseen NaN by 0)
+        assert torch.equal(got[2].isnan().all(2), hit) and got[2][~hit].isfinite().all() and (not ok.any() or rel(got[2][ok], want[2][ok]) <= 5e-6)
+        assert got[3][seen, 0].isnan().all() and got[4][seen[:w.n_past], 0].isnan().all()
+        clear[pages[w.n_past:], 0] = False
+        assert not clear.any() or (rel(got[3][clear], want[3][clear]) <= 5e-6 and rel(got[4][clear], want[4][clear]) <= 5e-6)
 
 
 # Tensors that are small throughout: what the results depend on linearly keeps 24 bits down to the smallest normal value, 2^-126 (as three bf16 terms without

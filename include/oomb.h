@@ -146,6 +146,12 @@ oomb_status oomb_page_score_topk_noalloc(const oomb_attn_desc* desc, const void*
  * Except in bf16 calls with page size and head dim 128 and rows or keys enough to fill the device: their kernels
  * give a token of the chunk that a row does not see a weight of zero, so a NaN or infinity in its V (backward:
  * K, Q or dO) may reach rows and keys of the same tile.  Tokens padded past the end of a text hold zeros.
+ *
+ * fp32 tensors: products are formed as sums of six bf16 products of three terms per value (24 bits; at most 2^-24
+ * of a product is left out) or as fp32 products, all sums in fp32.  Values of Q and K below 2^-109 are off by up to
+ * 2^-134 in <q, k>, and dK of a Q, dV of a probability that small throughout hold fewer than 24 bits; V, dO and their products
+ * hold 24 down to the smallest normal value.  With dO V from 2^96 on, and with infinities in V or dO, rows and keys are formed one by one,
+ * which takes many times as long.
  */
 
 /*

@@ -10,10 +10,10 @@
 //   dK / dV  K, V stay,     Q / dO stream: S = Q K^T, dP = dO V^T, dV^T += dO^T P, dK^T += Q^T dS
 // With 32 x 32 accumulators a lane owns one column of the staying side, so softmax statistics are
 // per-lane scalars (forward, dQ) and the accumulator feeds the second product from registers.
-// bf16: v_mfma_f32_32x32x16_bf16, the transposed operand by transposing LDS reads.  fp32:
-// v_mfma_f32_32x32x2_f32 (fp32 products and sums); an operand is one dword per lane, so any
-// order of the contraction index that both operands share will do, and four instructions
-// take one 16-byte read.
+// bf16: v_mfma_f32_32x32x16_bf16, the transposed operand by transposing LDS reads.  fp32: S in three
+// bf16 terms per value (below), the other products by v_mfma_f32_32x32x2_f32; an operand is one dword
+// per lane, so any order of the contraction index that both operands share will do, and four
+// instructions take one 16-byte read.
 //
 // Page sizes disappear in "list-token space": the tokens of a page list in list order.  The list is
 // ascending, so what a row sees is a prefix of that sequence: one number per row.  Row space of a
@@ -21,7 +21,7 @@
 // and the rows of a query page are contiguous for every page size.
 //
 // What bounds them: fp32 the matrix pipe itself (256 flops per cycle and compute unit, 157 TFLOP/s; calls that are not short
-// therefore take the bf16 pipe with products of three terms each, fwd_terms_kernel and bwd_units_kernel);
+// therefore form the other products in terms, too: fwd_terms_kernel and bwd_units_kernel);
 // bf16 the exposed vector work and LDS latency of one or two waves per SIMD; short calls the number
 // of workgroups, which is why the streamed side is cut into splits whose partial sums a second
 // kernel combines in a fixed order.  Measured against one wave per query row (per key in dK / dV)
@@ -205,9 +205,9 @@ template <int D> struct GnStay<float, D> {
     for (int j = 0; j < NJ; j += 2) gn_load_terms<PLAIN>(raw[j], raw[j + 1], t[j >> 1]);
   }
 };
-// S of 32 rows of the streamed side.  fp32: in terms, those of the streamed side formed on the way; only matrix cores that run the other
-// products keep to fp32 instructions.  28 / 4 heads of 128, chunk 512, 20 pages: forward 178 -> 148 us, backward 607 -> 574 against S on the
-// fp32 pipe; 14 / 2 heads of 64, chunk 1664, 27 pages of 128: 233 -> 195 and 635 -> 547.
+// S of 32 rows of the streamed side.  fp32: in terms, those of the streamed side formed on the way (11 vector instructions for two values, beside
+// 192 matrix cycles for 512).  28 / 4 heads of 128, chunk 512, 20 pages: forward 177 -> 148 us, backward 604 -> 570 against S on the
+// fp32 pipe; 14 / 2 heads of 64, chunk 1664, 27 pages of 128: 233 -> 198 and 632 -> 598; one tile per wave (2 / 1 heads) the same to 0.1 us.
 template <typename T> struct GnSum {
   f32x16 v[sizeof(T) == 4 ? 2 : 1];
   u32x4_t held;
@@ -910,7 +910,7 @@ __device__ __forceinline__ void gn_sum_parts(const float* part, int64_t block, i
 
 // O = sum of the splits' O rescaled to the common maximum / sum of their l.  L: the element type in whose register order the partial sums lie.
 // What bounds it is how much a compute unit has in flight: eight waves with eight splits each.  Against four waves with four splits, whole passes: 28 / 4
-// heads, one page, 9 splits (112 blocks) 52.5 -> 51.8 us; 14 / 2 heads, two pages 54.6 -> 53.8; 14 / 2 heads of 64 dims 34.15 -> 33.9; at 448
+// heads, one page, 9 splits (112 blocks) 52.5 -> 51.8 us; 14 / 2 heads, two pages 54.6 -> 53.8; at 448
 // blocks the same.
 constexpr int COMBINE_WAVES = 8;
 template <typename T, int D, typename L = T>
@@ -1040,8 +1040,8 @@ template <int N, typename L, typename M> __device__ __forceinline__ void gn_term
 // fp32 forward, one list per KV head: O = softmax(Q K^T) V of 128 rows and a range of tiles of 32 keys.  Two workgroups per compute unit, whose barriers
 // are their own: the vector work of one (softmax, terms of P) runs beside the matrix instructions of the other.  S is summed in two accumulators, the
 // products of the first terms apart from the small ones, so that fewer sums are rounded at its full size (O against 64 bits 4.2e-7 instead of
-// 6.0e-7; on the fp32 pipe 7.3e-7).  28 / 4 heads, chunk 512, 20 pages of 128: the forward with layout and combine 187 us on the fp32 pipe, 118 here: 1.0
-// PFLOP/s of bf16 instructions, what the clock sustains (the bf16 forward of pages of 128 reaches no more).  256 rows per workgroup, half of
+// 6.0e-7; on the fp32 pipe 7.3e-7).  28 / 4 heads, chunk 512, 20 pages of 128: the forward with layout and combine 187 us on the fp32 pipe, 148 with S
+// alone in terms, 118 here: 1.0 PFLOP/s of bf16 instructions, the matrix pipe busy for 61 % of the cycles of the compute units in use, waves waiting 13 %.  256 rows per workgroup, half of
 // the copies: 2 to 6 % faster where the chip is full, up to 25 % slower where it is not.
 template <int D, bool FIRST>
 __global__ __launch_bounds__(256, 2) void fwd_terms_kernel(Params p, int32_t tiles, int32_t n_split, int lp, int32_t max_len, int32_t t0, int32_t n_tiles, bool last, const unsigned char* __restrict__ img,
@@ -1585,7 +1585,8 @@ __global__ __launch_bounds__(256, (D == 128 || sizeof(T) == 4 ? 1 : 2)) void dkv
 // compute unit has the same work.  A range covers the end of one unit and the start of the next (or several short ones); the piece of unit u
 // in range b has slot (b + u) Hkv + g.
 // A launch takes the units u0 .. u0 + un - 1 of every head (the slots count from u0); the launches after the first add to the partial sums of dQ, which are
-// un in number: their room is bounded whatever the list.  Any launch sees the stages of a unit's set that the ones before it see, or fewer.
+// un in number: their room is bounded whatever the list.  (The stages that a unit's rows have are among those of the unit un before it, whose
+// partial sums it adds to: a later page of the list is seen by fewer rows.)
 template <int D> struct GnU {
   typedef Gn<bf16_t, D> X;
   typedef GnF3<D> F;
@@ -1877,9 +1878,9 @@ __global__ __launch_bounds__(256, (D == 128 || sizeof(T) == 4 ? 1 : 2)) void bwd
 
 // What is left of a backward with splits, in one launch: workgroups below dq_blocks add the dQ partials, the others
 // add the slices of a dK / dV unit to the pool.
-// Eight waves per block (NW) keep more loads in flight where there are few blocks: 14 / 2 heads, two pages, 53.3 -> 52.2 us a pass; 8 / 2 heads, 17 + 24 pages of
-// 64: 145.3 -> 144.3; 6 / 2 heads, 93 pages (1700 blocks): 250.6 -> 249.3.  At 5000 blocks it makes no difference, and where many
-// more fill the chip four waves are faster (4096 tokens of 28 / 4 heads with a list per page: 91 us against 98).
+// Eight waves per block (NW) keep more loads in flight where there are few blocks: 14 / 2 heads, two pages, 53.3 -> 52.2 us a pass; 6 / 2 heads, 93 pages
+// (1700 blocks): 250.6 -> 249.3.  At 5000 blocks it makes no difference, and where many more fill the chip four waves are faster (4096 tokens of 28 / 4
+// heads with a list per page: 91 us against 98).
 constexpr int64_t FINISH_FEW = 4096;
 template <typename T, typename TG, int D, typename L, int NW>
 __global__ __launch_bounds__(64 * NW) void bwd_finish_kernel(Params p, int32_t tiles, int32_t dq_split, const float* __restrict__ dq_part,
@@ -2124,8 +2125,8 @@ static size_t gn_row_blocks(const Params& p) { return (size_t)gn_tiles(p.C, p.G,
 // splits that fit `bytes` of partial results of `per` bytes each (at least 1: no partial results)
 static int32_t gn_fit(size_t bytes, size_t per) { return (int32_t)(bytes / per > 32 ? 32 : bytes / per < 2 ? 1 : bytes / per); }
 static size_t gn_row_part_bytes(const Params& p, int32_t split) { return split > 1 ? split * gn_row_blocks(p) * 32 * p.D * 4 : 0; }
-// The fp32 forward in terms: splits of the key range, how many launches walk it (each with the image of its own part of the list, which takes
-// at most IMAGE_ROOM: 1.5 times what the listed keys and values take; the sums go on from launch to launch), and the estimate of the time in microseconds, the layout of the terms included.  Two workgroups of a compute unit take `unit` for a
+// The fp32 forward in terms: splits of the key range, how many launches walk it (each with the image of its own part of the list, 1.5 times what
+// the keys and values there take and at most IMAGE_ROOM; the sums go on from launch to launch), and the estimate of the time in microseconds, the layout of the terms included.  Two workgroups of a compute unit take `unit` for a
 // tile of 32 keys each (192 matrix instructions per SIMD); 512 run at a time.
 constexpr size_t IMAGE_ROOM = (size_t)512 << 20;
 struct GnF3Plan { int32_t n, launches; float us; };

@@ -269,3 +269,18 @@ def test_unsplit_kernels_with_the_least_workspace(w, what):
         ok = ok & ~part
         assert a[ok].isfinite().all() and rel(a[ok], b[ok]) <= tol, (n, rel(a[ok], b[ok]))
     assert rel(dq[~hit], want[2][~hit]) <= 6e-6
+
+
+# More KV heads than compute units (a range per head, all of them longer), and rows enough that one launch takes two units.
+@pytest.mark.parametrize("w", [Workload("heads", 300, 300, 64, 16, 224, 16 * 40, None, "f32", "f32", 0.125, seed=531),
+                               Workload("heads_d128", 264, 264, 128, 32, 160, 32 * 20, None, "f32", "bf16", 0.088, seed=532),
+                               Workload("rows", 32, 2, 128, 128, 8192, 128 * 68, None, "f32", "f32", 0.088, seed=533)], ids=lambda w: w.name)
+def test_backward_by_units_of_many_heads_and_rows(w):
+    x = make_inputs(w, "cuda")
+    desc = api.make_desc(x["q"], x["k_pool"], w.N, w.sm_scale, x["dk_pool"].dtype)
+    args = (desc, x["q"], x["k_pool"], x["v_pool"], x["page_table"])
+    o, lse = api.paged_attn_fwd(*args)
+    with pu.kernels_ran(("bwd_units",), absent=()):
+        dq = api.paged_attn_bwd(*args, o, lse, x["d_o"], x["dk_pool"], x["dv_pool"])
+    for n, a, b in zip(NAMES, (o, lse, dq, x["dk_pool"], x["dv_pool"]), exact(w, x)):
+        assert rel(a, b) <= (3e-3 if a.dtype == torch.bfloat16 else 2e-6), (n, rel(a, b))

@@ -407,6 +407,7 @@ struct GnTile {
   bool valid, active;     // the lane owns a row; the wave owns at least one
   int32_t T_ent;          // list entries that some row of the tile sees
   int32_t V, V_last;      // list tokens this lane's row / the tile's last row sees
+  int32_t V_first;        // those that every row of the tile sees
 };
 
 __device__ __forceinline__ GnTile gn_tile(const Params& p, int g, int32_t tile, int rb, int lane, int lp, int32_t max_len) {
@@ -435,8 +436,8 @@ __device__ __forceinline__ GnTile gn_tile(const Params& p, int g, int32_t tile, 
   t.h = g * p.G + (t.r - t.i * p.G);
   const int64_t first_q = p.N - p.C;
   const int32_t i_last = (int32_t)div_g(p, (uint32_t)last);
-  const int64_t a = first_q + t.i, a_last = first_q + i_last;
-  const int32_t pg = (int32_t)(a >> lp), pg_lo = (int32_t)((first_q + div_g(p, (uint32_t)base)) >> lp), pg_hi = (int32_t)(a_last >> lp);
+  const int64_t a = first_q + t.i, a_last = first_q + i_last, a_first = first_q + div_g(p, (uint32_t)base);
+  const int32_t pg = (int32_t)(a >> lp), pg_lo = (int32_t)(a_first >> lp), pg_hi = (int32_t)(a_last >> lp);
   // The rows of a tile lie in at most nine pages, so the entries past pg_lo that some row sees are among the last
   // 64 up to pg_hi.
   t.T_ent = len;
@@ -450,14 +451,17 @@ __device__ __forceinline__ GnTile gn_tile(const Params& p, int g, int32_t tile, 
   // tokens visible up to page v: entries up to v, whole pages, less the unseen tail of v itself
   t.V = 0;
   t.V_last = 0;
+  t.V_first = 0;
   for (int32_t v = pg_lo; v <= pg_hi; ++v) {
     const int32_t whole = (t.T_ent + n_over - __builtin_popcountll(__ballot(e > v))) << lp;
     const bool held = __ballot(e == v) != 0;
     if (pg == v) t.V = whole - (held ? p.P - 1 - (int32_t)(a & (p.P - 1)) : 0);
+    if (v == pg_lo) t.V_first = whole - (held ? p.P - 1 - (int32_t)(a_first & (p.P - 1)) : 0);
     if (v == pg_hi) t.V_last = whole - (held ? p.P - 1 - (int32_t)(a_last & (p.P - 1)) : 0);
   }
   t.T_ent = __builtin_amdgcn_readfirstlane(t.T_ent);
   t.V_last = __builtin_amdgcn_readfirstlane(t.V_last);
+  t.V_first = __builtin_amdgcn_readfirstlane(t.V_first);
   return t;
 }
 
@@ -527,8 +531,9 @@ __device__ __forceinline__ GnBlock gn_block(const Params& p, int32_t b, int32_t 
 }
 
 // The key loop of forward and dQ: tiles kr of this wave's group.  compute(LDS offset of the tile inside the group's
-// buffers -- a constant --, first list token)
-template <typename T, int D, int KH, typename F>
+// buffers -- a constant --, first list token, whether some row of the workgroup's tile may not see all of it).  APART: the tiles that
+// every row sees have a loop of their own, without masks.
+template <typename T, int D, int KH, bool APART, typename F>
 __device__ __forceinline__ void gn_key_loop(const Params& p, const GnTile& t, GnStream<T, D>& ks, GnRange kr, GnRange other, int32_t max_len,
                                             int group, int rb, int lane, int lp, GnStay<T, D>& qs, F&& compute) {
   typedef GnTiles<T, D> Y;
@@ -541,17 +546,29 @@ __device__ __forceinline__ void gn_key_loop(const Params& p, const GnTile& t, Gn
   qs.here();
   if (mine > 0) ks.copy(p, t.lid, max_len, rb, lane, lp, kr.k0, at);
   qs.template split<true>();   // (while the first tile is on its way)
-  for (int32_t i0 = 0; i0 < steps; i0 += 2) {
+  auto walk = [&](int32_t i0, const int32_t end, auto mask) __attribute__((always_inline)) {   // (i0 is even)
+    for (; i0 < end; i0 += 2) {
 #pragma unroll
-    for (int b = 0; b < 2; ++b) {   // (unrolled: the buffer is a constant)
-      const int32_t i = i0 + b;
-      if (i >= steps) break;
-      wait_copies<0>();
-      __syncthreads();   // this tile is in LDS; nobody reads the one before it any more, whose buffer takes the next
-      if (i + 1 < mine) ks.copy(p, t.lid, max_len, rb, lane, lp, kr.k0 + i + 1, at + (b ^ 1) * Y::BUF);
-      if (i < mine) compute((uint32_t)(b * Y::BUF), (kr.k0 + i) * Y::KT);
+      for (int b = 0; b < 2; ++b) {   // (unrolled: the buffer is a constant)
+        const int32_t i = i0 + b;
+        if (mask.value && i >= end) break;
+        wait_copies<0>();
+        __syncthreads();   // this tile is in LDS; nobody reads the one before it any more, whose buffer takes the next
+        if (i + 1 < mine) ks.copy(p, t.lid, max_len, rb, lane, lp, kr.k0 + i + 1, at + (b ^ 1) * Y::BUF);
+        if (!mask.value || i < mine) compute((uint32_t)(b * Y::BUF), (kr.k0 + i) * Y::KT, mask);
+      }
     }
+  };
+  int32_t seen = 0;   // (the same for both groups)
+  if constexpr (APART) {
+    const int32_t all = t.V_first / Y::KT, k_hi = KH == 2 && other.k0 > kr.k0 ? other.k0 : kr.k0;
+    seen = all - k_hi;
+    seen = (seen < mine ? seen : mine) & ~1;
+    if (KH == 2) seen = seen < theirs ? seen : theirs & ~1;
+    seen = seen > 0 ? seen : 0;
+    walk(0, seen, std::false_type());
   }
+  walk(seen, steps, std::true_type());
 }
 
 // ---- values that are not finite -----------------------------------------------------------------
@@ -712,7 +729,7 @@ __global__ __launch_bounds__(256 * KH, 2) void fwd_generic_kernel(Params p, int3
 
   // One tile: S of its blocks, one softmax step over all of them, then O.  The exponentials of a second block
   // run between the matrix instructions of the first block's product.
-  gn_key_loop<T, D, KH>(p, t, ks, kr, other, max_len, group, rb, lane, lp, qs, [&](const uint32_t at, const int32_t t0) __attribute__((always_inline)) {
+  gn_key_loop<T, D, KH, false>(p, t, ks, kr, other, max_len, group, rb, lane, lp, qs, [&](const uint32_t at, const int32_t t0, auto) __attribute__((always_inline)) {
     if (!t.active || t0 >= V_max) return;   // (wave-uniform)
     constexpr int NP = GnAddr<T, D>::NP;
     ad.anew();
@@ -1255,12 +1272,11 @@ __device__ __forceinline__ void dq_body(const Params& p, unsigned char* smem, in
   }
   GnAddr<T, D> ad;
   ad.init(lane, group * GnRow<T, D, KH>::GROUP);
-  const int32_t V_min = __builtin_amdgcn_readfirstlane(t.V), V_max = __builtin_amdgcn_readlane(t.V, 31);
+  const int32_t V_max = __builtin_amdgcn_readlane(t.V, 31);
 
-  gn_key_loop<T, D, KH>(p, t, ks, kr, other, max_len, group, rb, lane, lp, qs, [&](const uint32_t at, const int32_t t0) __attribute__((always_inline)) {
+  gn_key_loop<T, D, KH, true>(p, t, ks, kr, other, max_len, group, rb, lane, lp, qs, [&](const uint32_t at, const int32_t t0, auto mask) __attribute__((always_inline)) {
     if (!t.active || t0 >= V_max) return;
     constexpr int NP = GnAddr<T, D>::NP, NJ = X::NJ, L = 2 * NJ + NP;
-    const bool mask = t0 + Y::KT > V_min;
     const int32_t rel = t.V - t0 - 4 * hh;
     ad.anew();
     GnSum<T> s;   // of one block
@@ -1288,7 +1304,7 @@ __device__ __forceinline__ void dq_body(const Params& p, unsigned char* smem, in
 #pragma unroll
             for (int x = (k - NJ) * (16 / NJ); x < (k - NJ + 1) * (16 / NJ); ++x) {
               float v = __builtin_amdgcn_exp2f(__builtin_fmaf(pr[x], c, -lse2));
-              if (mask && 32 * u + 8 * (x >> 2) + (x & 3) >= rel) v = 0.f;
+              if (mask.value && 32 * u + 8 * (x >> 2) + (x & 3) >= rel) v = 0.f;
               pr[x] = v;
             }
             if (k == 2 * NJ - 1) {
@@ -1375,7 +1391,6 @@ __device__ __forceinline__ void dkv_body(const Params& p, unsigned char* smem, i
   const int64_t koff = (int64_t)p.page_table[l] * p.pool_page_stride + (int64_t)g * p.pool_head_stride + (int64_t)(kq & (p.P - 1)) * p.pool_tok_stride;
   // rows before r_key do not see the key
   const int32_t r_key = pos > first_q ? (int32_t)(pos - first_q) * p.G : 0;
-  const int32_t r_key_max = __builtin_amdgcn_readlane(r_key, 31);
   const int64_t pos0 = owned_at(p, g, e0) << lp;
   const int32_t r_lo = pos0 > first_q ? (int32_t)(pos0 - first_q) * p.G : 0, rows = p.C * p.G;
   // stages of KT rows: [s0, s1) of the chunk's, or stage v % spq of the unit's query page v / spq
@@ -1481,7 +1496,12 @@ __device__ __forceinline__ void dkv_body(const Params& p, unsigned char* smem, i
   }
   wait_copies<0>();
   __syncthreads();
-  auto stage = [&](const int32_t s, const uint32_t buf) __attribute__((always_inline)) {   // (buf: a constant)
+  // The stages whose rows all see every key of the unit come last: they have a loop of their own, without masks
+  int32_t e1 = e0 + (p.qp ? 1 : 128 >> lp);
+  e1 = (e1 < len ? e1 : len) - 1;
+  const int64_t pos1 = (owned_at(p, g, e1) << lp) + p.P - 1;
+  const int32_t r_all = __builtin_amdgcn_readfirstlane(pos1 > first_q ? (int32_t)(pos1 - first_q) * p.G : 0);
+  auto stage = [&](const int32_t s, const uint32_t buf, auto mask) __attribute__((always_inline)) {   // (buf: a constant)
     if (s + 1 < s1) copy(s + 1, buf ^ Y::BUF);
     int32_t base, end;
     stage_rows(s, base, end);
@@ -1490,7 +1510,6 @@ __device__ __forceinline__ void dkv_body(const Params& p, unsigned char* smem, i
       // per block of 32 rows: S; dP with the exponentials of S between its instructions; dV with dS between its
       // instructions; dK
       constexpr int NP = GnAddr<T, D>::NP, NJ = X::NJ, L = 2 * NJ + 2 * NP;
-      const bool mask = base < r_key_max;   // (wave-uniform)
       const int32_t rel = r_key - base - 4 * hh;
       ad.anew();
       GnSum<T> sv;
@@ -1518,7 +1537,7 @@ __device__ __forceinline__ void dkv_body(const Params& p, unsigned char* smem, i
 #pragma unroll
               for (int x = (k - NJ) * (16 / NJ); x < (k - NJ + 1) * (16 / NJ); ++x) {
                 float v = __builtin_amdgcn_exp2f(__builtin_fmaf(w[x], c, -st[32 * u + 8 * (x >> 2) + 4 * hh + (x & 3)]));
-                if (mask && 32 * u + 8 * (x >> 2) + (x & 3) < rel) v = 0.f;
+                if (mask.value && 32 * u + 8 * (x >> 2) + (x & 3) < rel) v = 0.f;
                 w[x] = v;
               }
               if (k == 2 * NJ - 1) {
@@ -1544,9 +1563,17 @@ __device__ __forceinline__ void dkv_body(const Params& p, unsigned char* smem, i
     wait_copies<0>();
     __syncthreads();
   };
-  for (int32_t s = s0; s < s1; s += 2) {
-    stage(s, 0);
-    if (s + 1 < s1) stage(s + 1, Y::BUF);
+  int32_t s = s0;
+  for (; s < s1; s += 2) {
+    int32_t base, end;
+    stage_rows(s, base, end);
+    if (base >= r_all) break;
+    stage(s, 0, std::true_type());
+    if (s + 1 < s1) stage(s + 1, Y::BUF, std::true_type());
+  }
+  for (; s < s1; s += 2) {
+    stage(s, 0, std::false_type());
+    if (s + 1 < s1) stage(s + 1, Y::BUF, std::false_type());
   }
 
   const float sc = p.sm_scale;

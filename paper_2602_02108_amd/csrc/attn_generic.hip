@@ -1228,7 +1228,7 @@ template <typename T, int D> static hipError_t launch_delta(const Params& p, hip
   delta_kernel<T, D><<<dim3((unsigned)(((int64_t)p.C * p.Hq + R - 1) / R)), dim3(256), 0, st>>>(p);
   return hipGetLastError();
 }
-template <typename T, int D, int KH, int NT>
+template <typename T, int D, int KH, int NT, bool ALONE>
 __device__ __forceinline__ void dq_body(const Params& p, unsigned char* smem, int32_t block, int32_t tiles, int32_t n_split, int lp, int32_t max_len,
                                         float* __restrict__ part, float* __restrict__ bias, int32_t n_stages) {
   typedef Gn<T, D> X;
@@ -1279,42 +1279,81 @@ __device__ __forceinline__ void dq_body(const Params& p, unsigned char* smem, in
     constexpr int NP = GnAddr<T, D>::NP, NJ = X::NJ, L = 2 * NJ + NP;
     const int32_t rel = t.V - t0 - 4 * hh;
     ad.anew();
-    GnSum<T> s;   // of one block
-    f32x16 dp[1];
-    f32x16& pr = s.v[0];   // P
-    GnP<T, NT> ds;
-    // per block: S, then dP with the exponentials of S between its instructions, dS, then dQ
-    gn_pipeline<Y::U * L, GN_BATCH<T, D>>(
-        [&](const int i) __attribute__((always_inline)) {
-          const int u = i / L, k = i % L;
-          const uint32_t o = at + 32 * u * X::RB;
-          return k < NJ ? ad.row_frag(k, o) : k < 2 * NJ ? ad.row_frag(k - NJ, o + Y::TILE) : ad.tr_frag(k - 2 * NJ, o);
-        },
-        [&](const int i, const u32x4_t& f) __attribute__((always_inline)) {
-          const int u = i / L, k = i % L;
-          if (k == 0) {
-            s.zero();
-            gn_zero(dp);
-          }
-          if (k < NJ) {
-            s.step(k, f, qs);
-            if (k == NJ - 1) s.template close<false>(qs, [&](const int j) __attribute__((always_inline)) { return ad.row_frag(j, at + 32 * u * X::RB); });
-          } else if (k < 2 * NJ) {
-            gn_mma<T>(f, dof[k - NJ], dp[0]);
+    if constexpr (ALONE) {
+      // A wave alone on its SIMD, whose vector work runs only beside its own matrix instructions: S and dP of block 0; those of block 1 beside
+      // dS of block 0; dQ of block 0 beside dS of block 1; dQ of block 1.  (Block by block, as below: the backward of 8 / 2 heads, 41 pages of 64,
+      // chunk 1088 in one launch 103 us, so 92; with two waves per SIMD it only costs registers.)
+      static_assert(Y::U == 2 && 16 % NP == 0 && 32 % (2 * NJ) == 0, "two blocks of bf16");
+      f32x16 sum[2][2];   // [block][S, then P, then dS | dP]
+      gn_zero(sum[0]);
+      gn_zero(sum[1]);
+      GnP<T, NT> dsp[2];
+      auto form = [&](const int u, const int x) __attribute__((always_inline)) {
+        float v = __builtin_amdgcn_exp2f(__builtin_fmaf(sum[u][0][x], c, -lse2));
+        if (mask.value && 32 * u + 8 * (x >> 2) + (x & 3) >= rel) v = 0.f;
+        sum[u][0][x] = v * (sum[u][1][x] - delta);
+        if (x & 1) dsp[u].set2(x - 1, sum[u][0][x - 1], sum[u][0][x]);
+      };
+      gn_pipeline<4 * NJ + 2 * NP, GN_BATCH<T, D>>(
+          [&](const int i) __attribute__((always_inline)) {
+            if (i < 4 * NJ) return ad.row_frag(i % NJ, at + 32 * (i / (2 * NJ)) * X::RB + (i / NJ % 2 ? Y::TILE : 0));
+            const int v = i - 4 * NJ;
+            return ad.tr_frag(v % NP, at + 32 * (v / NP) * X::RB);
+          },
+          [&](const int i, const u32x4_t& f) __attribute__((always_inline)) {
+            if (i < 4 * NJ) {
+              const int u = i / (2 * NJ), j = i % NJ, e = 16 / (2 * NJ);
+              sum[u][i / NJ % 2] = mfma32(__builtin_bit_cast(bf16x8, f), __builtin_bit_cast(bf16x8, i / NJ % 2 ? dof[j] : qs.f[j]), sum[u][i / NJ % 2]);
+              if (u == 1)
 #pragma unroll
-            for (int x = (k - NJ) * (16 / NJ); x < (k - NJ + 1) * (16 / NJ); ++x) {
-              float v = __builtin_amdgcn_exp2f(__builtin_fmaf(pr[x], c, -lse2));
-              if (mask.value && 32 * u + 8 * (x >> 2) + (x & 3) >= rel) v = 0.f;
-              pr[x] = v;
-            }
-            if (k == 2 * NJ - 1) {
+                for (int x = (i - 2 * NJ) * e; x < (i - 2 * NJ + 1) * e; ++x) form(0, x);
+            } else {
+              const int v = i - 4 * NJ, e = 16 / NP;
+              gn_tr_mma<T, D, NT>(v % NP, f, dsp[v / NP], dq);
+              if (v < NP)
 #pragma unroll
-              for (int x = 0; x < 16; x += 2) ds.set2(x, pr[x] * (dp[0][x] - delta), pr[x + 1] * (dp[0][x + 1] - delta));
+                for (int x = v * e; x < (v + 1) * e; ++x) form(1, x);
             }
-          } else {
-            gn_tr_mma<T, D, NT>(k - 2 * NJ, f, ds, dq);
-          }
-        });
+          });
+      return;
+    } else {
+      GnSum<T> s;   // of one block
+      f32x16 dp[1];
+      f32x16& pr = s.v[0];   // P
+      GnP<T, NT> ds;
+      // per block: S, then dP with the exponentials of S between its instructions, dS, then dQ
+      gn_pipeline<Y::U * L, GN_BATCH<T, D>>(
+          [&](const int i) __attribute__((always_inline)) {
+            const int u = i / L, k = i % L;
+            const uint32_t o = at + 32 * u * X::RB;
+            return k < NJ ? ad.row_frag(k, o) : k < 2 * NJ ? ad.row_frag(k - NJ, o + Y::TILE) : ad.tr_frag(k - 2 * NJ, o);
+          },
+          [&](const int i, const u32x4_t& f) __attribute__((always_inline)) {
+            const int u = i / L, k = i % L;
+            if (k == 0) {
+              s.zero();
+              gn_zero(dp);
+            }
+            if (k < NJ) {
+              s.step(k, f, qs);
+              if (k == NJ - 1) s.template close<false>(qs, [&](const int j) __attribute__((always_inline)) { return ad.row_frag(j, at + 32 * u * X::RB); });
+            } else if (k < 2 * NJ) {
+              gn_mma<T>(f, dof[k - NJ], dp[0]);
+  #pragma unroll
+              for (int x = (k - NJ) * (16 / NJ); x < (k - NJ + 1) * (16 / NJ); ++x) {
+                float v = __builtin_amdgcn_exp2f(__builtin_fmaf(pr[x], c, -lse2));
+                if (mask.value && 32 * u + 8 * (x >> 2) + (x & 3) >= rel) v = 0.f;
+                pr[x] = v;
+              }
+              if (k == 2 * NJ - 1) {
+  #pragma unroll
+                for (int x = 0; x < 16; x += 2) ds.set2(x, pr[x] * (dp[0][x] - delta), pr[x + 1] * (dp[0][x + 1] - delta));
+              }
+            } else {
+              gn_tr_mma<T, D, NT>(k - 2 * NJ, f, ds, dq);
+            }
+          });
+    }
   });
 
   if constexpr (KH == 2) {
@@ -1348,7 +1387,7 @@ template <typename T, int D, int KH, int NT>
 __global__ __launch_bounds__(256 * KH, (Gn<T, D>::RB == 512 ? 1 : 2)) void dq_generic_kernel(Params p, int32_t tiles, int32_t n_split, int lp, int32_t max_len,
                                                                                              float* __restrict__ part, float* __restrict__ bias, int32_t n_stages) {
   extern __shared__ __align__(16) unsigned char smem[];
-  dq_body<T, D, KH, NT>(p, smem, blockIdx.x, tiles, n_split, lp, max_len, part, bias, n_stages);
+  dq_body<T, D, KH, NT, false>(p, smem, blockIdx.x, tiles, n_split, lp, max_len, part, bias, n_stages);
 }
 
 // ---- dK / dV ------------------------------------------------------------------------------------
@@ -1359,7 +1398,7 @@ template <typename T, int D> struct GnKey {
   static constexpr int KT = GnTiles<T, D>::KT;
   static constexpr int STAT = 2 * GnTiles<T, D>::BUF, LDS = STAT + 2 * 2 * 64 * 4;   // two buffers, {lse2, delta} of their rows
 };
-template <typename T, typename TG, int D, bool OWN_DELTA, int NT>
+template <typename T, typename TG, int D, bool OWN_DELTA, int NT, bool ALONE>
 __device__ __forceinline__ void dkv_body(const Params& p, unsigned char* smem, int32_t bid, int32_t n_split, int lp, float* __restrict__ part) {
   typedef Gn<T, D> X;
   typedef GnKey<T, D> R;
@@ -1512,52 +1551,96 @@ __device__ __forceinline__ void dkv_body(const Params& p, unsigned char* smem, i
       constexpr int NP = GnAddr<T, D>::NP, NJ = X::NJ, L = 2 * NJ + 2 * NP;
       const int32_t rel = r_key - base - 4 * hh;
       ad.anew();
-      GnSum<T> sv;
-      f32x16 dp[1];
-      f32x16& w = sv.v[0];   // P, then dS
-      GnP<T, NT> pr, ds;
-      gn_pipeline<Y::U * L, GN_BATCH<T, D>>(
-          [&](const int i) __attribute__((always_inline)) {
-            const int u = i / L, k = i % L;
-            const uint32_t o = buf + 32 * u * X::RB;
-            return k < NJ ? ad.row_frag(k, o) : k < 2 * NJ ? ad.row_frag(k - NJ, o + Y::TILE)
-                 : k < 2 * NJ + NP ? ad.tr_frag(k - 2 * NJ, o + Y::TILE) : ad.tr_frag(k - 2 * NJ - NP, o);
-          },
-          [&](const int i, const u32x4_t& f) __attribute__((always_inline)) {
-            const int u = i / L, k = i % L;
-            if (k == 0) {
-              sv.zero();
-              gn_zero(dp);
-            }
-            if (k < NJ) {
-              sv.step(k, f, ks);
-              if (k == NJ - 1) sv.template close<false>(ks, [&](const int j) __attribute__((always_inline)) { return ad.row_frag(j, buf + 32 * u * X::RB); });
-            } else if (k < 2 * NJ) {
-              gn_mma<T>(f, vf[k - NJ], dp[0]);
+      if constexpr (ALONE) {
+        // S and dP of block 0; those of block 1 beside P of block 0; dV of block 0 beside its dS; dK of block 0 beside P of block 1;
+        // dV of block 1 beside its dS; dK of block 1
+        static_assert(Y::U == 2 && 16 % NP == 0 && 16 % (2 * NJ) == 0, "two blocks of bf16");
+        f32x16 sum[2][2];   // [block][S, then P, then dS | dP]
+        gn_zero(sum[0]);
+        gn_zero(sum[1]);
+        GnP<T, NT> pr, ds;
+        auto form_p = [&](const int u, const int x) __attribute__((always_inline)) {
+          float v = __builtin_amdgcn_exp2f(__builtin_fmaf(sum[u][0][x], c, -st[32 * u + 8 * (x >> 2) + 4 * hh + (x & 3)]));
+          if (mask.value && 32 * u + 8 * (x >> 2) + (x & 3) < rel) v = 0.f;
+          sum[u][0][x] = v;
+          if (x & 1) pr.set2(x - 1, sum[u][0][x - 1], sum[u][0][x]);
+        };
+        auto form_ds = [&](const int u, const int x) __attribute__((always_inline)) {
+          sum[u][0][x] *= sum[u][1][x] - st[64 + 32 * u + 8 * (x >> 2) + 4 * hh + (x & 3)];
+          if (x & 1) ds.set2(x - 1, sum[u][0][x - 1], sum[u][0][x]);
+        };
+        gn_pipeline<4 * NJ + 4 * NP, GN_BATCH<T, D>>(
+            [&](const int i) __attribute__((always_inline)) {
+              if (i < 4 * NJ) return ad.row_frag(i % NJ, buf + 32 * (i / (2 * NJ)) * X::RB + (i / NJ % 2 ? Y::TILE : 0));
+              const int v = i - 4 * NJ;   // (dV takes dO, dK takes Q)
+              return ad.tr_frag(v % NP, buf + 32 * (v / (2 * NP)) * X::RB + (v / NP % 2 ? 0 : Y::TILE));
+            },
+            [&](const int i, const u32x4_t& f) __attribute__((always_inline)) {
+              if (i < 4 * NJ) {
+                const int u = i / (2 * NJ), j = i % NJ, e = 16 / (2 * NJ);
+                sum[u][i / NJ % 2] = mfma32(__builtin_bit_cast(bf16x8, f), __builtin_bit_cast(bf16x8, i / NJ % 2 ? vf[j] : ks.f[j]), sum[u][i / NJ % 2]);
+                if (u == 1)
 #pragma unroll
-              for (int x = (k - NJ) * (16 / NJ); x < (k - NJ + 1) * (16 / NJ); ++x) {
-                float v = __builtin_amdgcn_exp2f(__builtin_fmaf(w[x], c, -st[32 * u + 8 * (x >> 2) + 4 * hh + (x & 3)]));
-                if (mask.value && 32 * u + 8 * (x >> 2) + (x & 3) < rel) v = 0.f;
-                w[x] = v;
+                  for (int x = (i - 2 * NJ) * e; x < (i - 2 * NJ + 1) * e; ++x) form_p(0, x);
+              } else {
+                const int v = i - 4 * NJ, part = v / NP, n = v % NP, e = 16 / NP;
+                if (part % 2 == 0) gn_tr_mma<T, D, NT>(n, f, pr, dv);
+                else gn_tr_mma<T, D, NT>(n, f, ds, dk);
+#pragma unroll
+                for (int x = n * e; x < (n + 1) * e; ++x) {
+                  if (part % 2 == 0) form_ds(part / 2, x);
+                  else if (part == 1) form_p(1, x);
+                }
               }
-              if (k == 2 * NJ - 1) {
-#pragma unroll
-                for (int x = 0; x < 16; x += 2) pr.set2(x, w[x], w[x + 1]);
+            });
+      } else {
+        GnSum<T> sv;
+        f32x16 dp[1];
+        f32x16& w = sv.v[0];   // P, then dS
+        GnP<T, NT> pr, ds;
+        gn_pipeline<Y::U * L, GN_BATCH<T, D>>(
+            [&](const int i) __attribute__((always_inline)) {
+              const int u = i / L, k = i % L;
+              const uint32_t o = buf + 32 * u * X::RB;
+              return k < NJ ? ad.row_frag(k, o) : k < 2 * NJ ? ad.row_frag(k - NJ, o + Y::TILE)
+                   : k < 2 * NJ + NP ? ad.tr_frag(k - 2 * NJ, o + Y::TILE) : ad.tr_frag(k - 2 * NJ - NP, o);
+            },
+            [&](const int i, const u32x4_t& f) __attribute__((always_inline)) {
+              const int u = i / L, k = i % L;
+              if (k == 0) {
+                sv.zero();
+                gn_zero(dp);
               }
-            } else if (k < 2 * NJ + NP) {
-              gn_tr_mma<T, D, NT>(k - 2 * NJ, f, pr, dv);
-              const int n = k - 2 * NJ;
-#pragma unroll
-              for (int x = n * (16 / NP); x < (n + 1) * (16 / NP); ++x)
-                w[x] = w[x] * (dp[0][x] - st[64 + 32 * u + 8 * (x >> 2) + 4 * hh + (x & 3)]);
-              if (n == NP - 1) {
-#pragma unroll
-                for (int x = 0; x < 16; x += 2) ds.set2(x, w[x], w[x + 1]);
+              if (k < NJ) {
+                sv.step(k, f, ks);
+                if (k == NJ - 1) sv.template close<false>(ks, [&](const int j) __attribute__((always_inline)) { return ad.row_frag(j, buf + 32 * u * X::RB); });
+              } else if (k < 2 * NJ) {
+                gn_mma<T>(f, vf[k - NJ], dp[0]);
+  #pragma unroll
+                for (int x = (k - NJ) * (16 / NJ); x < (k - NJ + 1) * (16 / NJ); ++x) {
+                  float v = __builtin_amdgcn_exp2f(__builtin_fmaf(w[x], c, -st[32 * u + 8 * (x >> 2) + 4 * hh + (x & 3)]));
+                  if (mask.value && 32 * u + 8 * (x >> 2) + (x & 3) < rel) v = 0.f;
+                  w[x] = v;
+                }
+                if (k == 2 * NJ - 1) {
+  #pragma unroll
+                  for (int x = 0; x < 16; x += 2) pr.set2(x, w[x], w[x + 1]);
+                }
+              } else if (k < 2 * NJ + NP) {
+                gn_tr_mma<T, D, NT>(k - 2 * NJ, f, pr, dv);
+                const int n = k - 2 * NJ;
+  #pragma unroll
+                for (int x = n * (16 / NP); x < (n + 1) * (16 / NP); ++x)
+                  w[x] = w[x] * (dp[0][x] - st[64 + 32 * u + 8 * (x >> 2) + 4 * hh + (x & 3)]);
+                if (n == NP - 1) {
+  #pragma unroll
+                  for (int x = 0; x < 16; x += 2) ds.set2(x, w[x], w[x + 1]);
+                }
+              } else {
+                gn_tr_mma<T, D, NT>(k - 2 * NJ - NP, f, ds, dk);
               }
-            } else {
-              gn_tr_mma<T, D, NT>(k - 2 * NJ - NP, f, ds, dk);
-            }
-          });
+            });
+      }
     }
     if (s + 1 < s1) publish(buf ^ Y::BUF);
     wait_copies<0>();
@@ -1601,7 +1684,7 @@ __device__ __forceinline__ void dkv_body(const Params& p, unsigned char* smem, i
 template <typename T, typename TG, int D, int NT>
 __global__ __launch_bounds__(256, (D == 128 || sizeof(T) == 4 ? 1 : 2)) void dkv_generic_kernel(Params p, int32_t n_split, int lp, float* __restrict__ part) {
   extern __shared__ __align__(16) unsigned char smem[];
-  dkv_body<T, TG, D, false, NT>(p, smem, blockIdx.x, n_split, lp, part);
+  dkv_body<T, TG, D, false, NT, sizeof(T) == 2 && D == 128>(p, smem, blockIdx.x, n_split, lp, part);
 }
 
 // The whole backward of fp32 tensors: five products per pair instead of the seven of two kernels, all but dQ's as products of three
@@ -1899,8 +1982,8 @@ __global__ __launch_bounds__(256, (D == 128 || sizeof(T) == 4 ? 1 : 2)) void bwd
                                                                                             int32_t tiles, int32_t n_split, int lp, int32_t max_len,
                                                                                             float* __restrict__ part) {
   extern __shared__ __align__(16) unsigned char smem[];
-  if ((int32_t)blockIdx.x < kv_blocks) dkv_body<T, TG, D, true, NT>(p, smem, blockIdx.x, kv_split, lp, kv_part);
-  else dq_body<T, D, 1, NT>(p, smem, (int32_t)blockIdx.x - kv_blocks, tiles, n_split, lp, max_len, part, nullptr, 0);
+  if ((int32_t)blockIdx.x < kv_blocks) dkv_body<T, TG, D, true, NT, sizeof(T) == 2 && D == 128>(p, smem, blockIdx.x, kv_split, lp, kv_part);
+  else dq_body<T, D, 1, NT, sizeof(T) == 2 && D == 128>(p, smem, (int32_t)blockIdx.x - kv_blocks, tiles, n_split, lp, max_len, part, nullptr, 0);
 }
 
 // What is left of a backward with splits, in one launch: workgroups below dq_blocks add the dQ partials, the others

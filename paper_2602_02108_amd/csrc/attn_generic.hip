@@ -386,6 +386,20 @@ template <int N, int B = 4, typename L, typename M> __device__ __forceinline__ v
   }
 }
 
+// A row statistic of a block of 32 rows in LDS: value x of a lane is that of row 8 (x / 4) + 4 hh + x % 4.  A group of four is fetched while the one before
+// it is in use: read where it is needed, every value waits for the LDS and for all operands fetched ahead of it (the one-launch backward of 8 / 2 heads,
+// 41 pages of 64, chunk 1088: two thirds of a stage).
+struct GnStat {
+  float4 v[2];
+  __device__ __forceinline__ void fetch(const float* block, const int hh, const int a) { v[a & 1] = *reinterpret_cast<const float4*>(block + 8 * a + 4 * hh); }
+  __device__ __forceinline__ float at(const float* block, const int hh, const int x) {   // (in order)
+    const float4& w = v[(x >> 2) & 1];
+    const float r = (x & 3) == 0 ? w.x : (x & 3) == 1 ? w.y : (x & 3) == 2 ? w.z : w.w;
+    if ((x & 3) == 0 && x < 12) fetch(block, hh, (x >> 2) + 1);
+    return r;
+  }
+};
+
 // One copy instruction of a wave: lane l moves 16 bytes from its own address to LDS byte dst + 16 l.
 __device__ __forceinline__ void gn_copy16(const unsigned char* src, uint32_t dst) {
   asm volatile(
@@ -1208,6 +1222,69 @@ __global__ __launch_bounds__(256, 2) void fwd_terms_kernel(Params p, int32_t til
   }
 }
 
+// ---- how a backward's work is shared out ----------------------------------------------------------
+// A row tile (dQ) takes as many steps as it sees key tiles, a unit of 128 keys (dK / dV) as many as there are stages of rows that see it: those that hold the chunk's
+// own pages fewer than the others.  Each is cut into equal parts of at most `most` steps, a workgroup each, so that all workgroups have about the same work; parts of one
+// row tile or unit leave partial sums, of which workgroup b of KV head g has number b Hkv + g.  (The same number of parts for all: the backward of 8 / 2 heads,
+// chunk 1088, 24 + 17 pages of 64 in one launch 97 us for 83; equal ranges across row tiles and units, with one part more per workgroup and rows that
+// no other workgroup reads at the same time, 83 us there, but 8 to 30 % slower where parts fit well.)
+// The steps are counted for a list of the greatest length that ends with the chunk's own pages, so that nothing has to be read first; with other lists the shares
+// are less even.  The first part of a unit takes every stage up to its end, the last part of a row tile every tile from its start.
+struct GnShare { int32_t n, most; };   // workgroups per KV head
+struct GnShares { GnShare kv, rows; float *kv_part, *row_part; };
+struct GnPart { int32_t u, s0, s1, slot; bool first, last; };   // steps s0 .. s1 - 1 of row tile or unit u; slot of the partial sums, or < 0
+// of units of 128 keys: steps are stages of `rows` rows, counted from `from`; of row tiles: tiles of kt keys
+struct GnKeySteps {
+  int32_t PG, rows, all, past, lp;   // past: list entries before the chunk's own pages
+  __host__ __device__ __forceinline__ GnKeySteps(const Params& p, int lp, int32_t max_len, int32_t kt)
+      : PG(p.P * p.G), rows(kt), all((int32_t)(((int64_t)p.C * p.G + kt - 1) / kt)), past(max_len - p.m), lp(lp) {}
+  __host__ __device__ __forceinline__ int32_t from(int32_t u) const {
+    const int32_t j = (u << (7 - lp)) - past, s = j > 0 ? (int32_t)((int64_t)j * PG / rows) : 0;
+    return s < all ? s : all - 1;
+  }
+  __host__ __device__ __forceinline__ int32_t operator()(int32_t u) const { return all - from(u); }
+};
+struct GnRowSteps {
+  int32_t G, rows, past, P, kt, lp;
+  uint32_t magic;
+  __host__ __device__ __forceinline__ GnRowSteps(const Params& p, int lp, int32_t max_len, int32_t kt)
+      : G(p.G), rows(p.C * p.G), past(max_len - p.m), P(p.P), kt(kt), lp(lp), magic(p.g_magic) {}
+  __host__ __device__ __forceinline__ int32_t operator()(int32_t t) const {
+    const int32_t r = t * GN_ROWS + GN_ROWS - 1 < rows - 1 ? t * GN_ROWS + GN_ROWS - 1 : rows - 1, i = G == 1 ? r : (int32_t)(((uint64_t)(uint32_t)r * magic) >> 32);
+    const int64_t seen = ((int64_t)(past + (i >> lp)) << lp) + (i & (P - 1)) + 1;
+    const int32_t n = (int32_t)((seen + kt - 1) / kt);
+    return n > 1 ? n : 1;
+  }
+};
+template <typename N> __host__ __device__ __forceinline__ int32_t gn_parts(const N& steps, const GnShare& w, int32_t u) { return (steps(u) + w.most - 1) / w.most; }
+// what workgroup b of KV head g does of `units` row tiles or units
+template <typename N> __device__ __forceinline__ GnPart gn_part(int32_t units, const GnShare& w, int32_t b, int g, int32_t Hkv, const N& steps) {
+  const int lane = threadIdx.x & 63;
+  int32_t u = 0, before = 0;
+  for (int32_t u0 = 0; u0 < units; u0 += 64) {
+    int32_t upto = u0 + lane < units ? gn_parts(steps, w, u0 + lane) : 0;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const int32_t v = __shfl_up(upto, o, 64);
+      if (lane >= o) upto += v;
+    }
+    const int past = __builtin_popcountll(__ballot(before + upto <= b));   // (of the 64; the last of all are never past)
+    u = u0 + past;
+    if (past > 0) before += __builtin_amdgcn_readlane(upto, past - 1);
+    if (past < 64) break;
+  }
+  const int32_t e = __builtin_amdgcn_readfirstlane(gn_parts(steps, w, u)), n = __builtin_amdgcn_readfirstlane(steps(u)), x = b - before;
+  return {u, (int32_t)((int64_t)n * x / e), (int32_t)((int64_t)n * (x + 1) / e), e == 1 ? -1 : b * Hkv + g, x == 0, x + 1 == e};
+}
+// {the first part of u, parts}
+template <typename N> __device__ __forceinline__ int2 gn_parts_of(const GnShare& w, int32_t u, const N& steps) {
+  int32_t before = 0;
+  for (int32_t v = threadIdx.x & 63; v < u; v += 64) before += gn_parts(steps, w, v);
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1) before += __shfl_xor(before, o, 64);
+  return make_int2(__builtin_amdgcn_readfirstlane(before), __builtin_amdgcn_readfirstlane(gn_parts(steps, w, u)));
+}
+
 // ---- dQ -----------------------------------------------------------------------------------------
 // Also computes Delta = <dO, O> of its rows for the dK / dV kernel, which runs afterwards: p.delta, or (bias != nullptr) the
 // bias words from which attn_bwd_dkv_mfma.hip starts its accumulators.  Where dQ overlaps O otherwise than row on row, a row of O may
@@ -1228,15 +1305,15 @@ template <typename T, int D> static hipError_t launch_delta(const Params& p, hip
   delta_kernel<T, D><<<dim3((unsigned)(((int64_t)p.C * p.Hq + R - 1) / R)), dim3(256), 0, st>>>(p);
   return hipGetLastError();
 }
+// the key tiles kr[w] of wave group w of a row tile; the first of them: Delta is left for the other kernels.  slot: of the partial sums (blocks of 128 rows), or < 0
+template <int KH> struct GnRowPiece { int32_t g, tile; GnRange kr[KH]; bool first; int64_t slot; };
 template <typename T, int D, int KH, int NT, bool ALONE>
-__device__ __forceinline__ void dq_body(const Params& p, unsigned char* smem, int32_t block, int32_t tiles, int32_t n_split, int lp, int32_t max_len,
-                                        float* __restrict__ part, float* __restrict__ bias, int32_t n_stages) {
+__device__ __forceinline__ void dq_body(const Params& p, unsigned char* smem, const GnRowPiece<KH>& b, int lp, int32_t max_len, float* __restrict__ part,
+                                        float* __restrict__ bias, int32_t n_stages) {
   typedef Gn<T, D> X;
   typedef GnTiles<T, D> Y;
-  const int lane = threadIdx.x & 63, hh = lane >> 5, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), rb = wave & 3, group = wave >> 2;
-  const GnBlock b = gn_block(p, block, tiles, n_split);
-  const GnRange kr = gn_range(max_len, lp, Y::KT, KH * b.split + group, KH * n_split);
-  const GnRange other = gn_range(max_len, lp, Y::KT, KH * b.split + (KH - 1 - group), KH * n_split);
+  const int lane = threadIdx.x & 63, hh = lane >> 5, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), rb = wave & 3, group = KH == 1 ? 0 : wave >> 2;
+  const GnRange kr = group ? b.kr[KH - 1] : b.kr[0], other = group ? b.kr[0] : b.kr[KH - 1];
   const GnTile t = gn_tile(p, b.g, b.tile, rb, lane, lp, max_len);
   GnStream<T, D> ks;
   ks.init(p, t.lid, max_len, b.g, rb, lane, kr.k0 * Y::KT, lp);
@@ -1260,7 +1337,7 @@ __device__ __forceinline__ void dq_body(const Params& p, unsigned char* smem, in
   f32x16 dq[X::DB];
   gn_zero(dq);
   const float c = p.sm_scale * 1.4426950408889634f;
-  if (b.split == 0 && group == 0 && t.valid && hh == 0) {
+  if (b.first && group == 0 && t.valid && hh == 0) {
     if (bias) {   // row space of that kernel: blocks of 32 tokens of one head, the heads interleaved
       const uint32_t blk = (uint32_t)(t.i >> 5) * p.G + (uint32_t)(t.h - b.g * p.G), r = 32 * blk + (t.i & 31);
       float* w = bias + (((int64_t)b.g * n_stages + (r >> 6)) * 2) * 64 + (r & 63);
@@ -1368,8 +1445,8 @@ __device__ __forceinline__ void dq_body(const Params& p, unsigned char* smem, in
 #pragma unroll
     for (int k = 0; k < X::DB * 16; ++k) dq[k >> 4][k & 15] += mo[64 * k];
   }
-  if (n_split > 1) {
-    if (t.active) part_store<T, D>(part, (int64_t)b.split * p.Hkv * tiles * 4 + t.block, lane, dq, 1.f);
+  if (b.slot >= 0) {
+    if (t.active) part_store<T, D>(part, b.slot * 4 + rb, lane, dq, 1.f);
   } else {
     uint32_t bad = gn_either_half(t.valid && gn_not_finite(dq));
     if (t.valid && !((bad >> (lane & 31)) & 1)) {
@@ -1387,7 +1464,11 @@ template <typename T, int D, int KH, int NT>
 __global__ __launch_bounds__(256 * KH, (Gn<T, D>::RB == 512 ? 1 : 2)) void dq_generic_kernel(Params p, int32_t tiles, int32_t n_split, int lp, int32_t max_len,
                                                                                              float* __restrict__ part, float* __restrict__ bias, int32_t n_stages) {
   extern __shared__ __align__(16) unsigned char smem[];
-  dq_body<T, D, KH, NT, false>(p, smem, blockIdx.x, tiles, n_split, lp, max_len, part, bias, n_stages);
+  const GnBlock b = gn_block(p, blockIdx.x, tiles, n_split);
+  GnRowPiece<KH> t = {b.g, b.tile, {}, b.split == 0, n_split > 1 ? ((int64_t)b.split * p.Hkv + b.g) * tiles + b.tile : -1};
+#pragma unroll
+  for (int k = 0; k < KH; ++k) t.kr[k] = gn_range(max_len, lp, GnTiles<T, D>::KT, KH * b.split + k, KH * n_split);
+  dq_body<T, D, KH, NT, false>(p, smem, t, lp, max_len, part, bias, n_stages);
 }
 
 // ---- dK / dV ------------------------------------------------------------------------------------
@@ -1398,25 +1479,26 @@ template <typename T, int D> struct GnKey {
   static constexpr int KT = GnTiles<T, D>::KT;
   static constexpr int STAT = 2 * GnTiles<T, D>::BUF, LDS = STAT + 2 * 2 * 64 * 4;   // two buffers, {lse2, delta} of their rows
 };
+// stages s0 .. s1 - 1 of the unit from list entry e0 on, or of the query pages q0 .. q0 + qc - 1 of a page of the union; slot: of the partial sums, or < 0
+struct GnKeyPiece { int32_t g, e0, s0, s1, slot, q0, qc; bool first; };
+// first stage of `rows` rows that sees list entry e of KV head g
+__device__ __forceinline__ int32_t gn_first_stage(const Params& p, int g, int32_t e, int lp, int32_t rows) {
+  const int64_t pos = owned_at(p, g, e) << lp, first_q = p.N - p.C;
+  return (pos > first_q ? (int32_t)(pos - first_q) * p.G : 0) / rows;
+}
 template <typename T, typename TG, int D, bool OWN_DELTA, int NT, bool ALONE>
-__device__ __forceinline__ void dkv_body(const Params& p, unsigned char* smem, int32_t bid, int32_t n_split, int lp, float* __restrict__ part) {
+__device__ __forceinline__ void dkv_body(const Params& p, unsigned char* smem, const GnKeyPiece& piece, int lp, float* __restrict__ part) {
   typedef Gn<T, D> X;
   typedef GnKey<T, D> R;
   typedef GnTiles<T, D> Y;
-  const int tid = threadIdx.x, lane = tid & 63, hh = lane >> 5, lq = lane & 31, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int32_t rest = bid / p.Hkv, g = bid - rest * p.Hkv;
-  int32_t e0, sp = 0, q0 = 0, qc = 0, slot = -1;
-  if (p.qp) {
-    const int32_t n_units = p.unit_count[g];
-    if (rest >= n_units) return;
-    const int4 un = p.units[(int64_t)g * p.max_units + (n_units - 1 - rest)];
-    e0 = un.x; q0 = un.y; qc = un.z; slot = un.w;
-  } else {
-    const int32_t u = rest / n_split;
-    sp = rest - u * n_split;
-    e0 = u << (7 - lp);
+  const int tid = threadIdx.x;
+  const int lane = tid & 63, hh = lane >> 5, lq = lane & 31, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int32_t g = piece.g, e0 = piece.e0, q0 = piece.q0, qc = piece.qc, slot = piece.slot, s1 = piece.s1;
+  int32_t s0 = piece.s0;
+  if (!p.qp) {
     if (e0 >= list_len(p, g)) return;
-    if (n_split > 1) slot = bid;   // (every slice of every unit has a slot of its own: the workgroup index)
+    const int32_t seen = __builtin_amdgcn_readfirstlane(gn_first_stage(p, g, e0, lp, R::KT));   // the first stage that sees the unit
+    s0 = piece.first || s0 < seen ? seen : s0;
   }
   const int32_t len = owned_len(p, g);
   const int64_t first_q = p.N - p.C;
@@ -1430,13 +1512,9 @@ __device__ __forceinline__ void dkv_body(const Params& p, unsigned char* smem, i
   const int64_t koff = (int64_t)p.page_table[l] * p.pool_page_stride + (int64_t)g * p.pool_head_stride + (int64_t)(kq & (p.P - 1)) * p.pool_tok_stride;
   // rows before r_key do not see the key
   const int32_t r_key = pos > first_q ? (int32_t)(pos - first_q) * p.G : 0;
-  const int64_t pos0 = owned_at(p, g, e0) << lp;
-  const int32_t r_lo = pos0 > first_q ? (int32_t)(pos0 - first_q) * p.G : 0, rows = p.C * p.G;
-  // stages of KT rows: [s0, s1) of the chunk's, or stage v % spq of the unit's query page v / spq
+  const int32_t rows = p.C * p.G;
+  // a stage: KT rows of the chunk's, or stage v % spq of the piece's query page v / spq
   const int32_t rpq = p.P * p.G, spq = (rpq + R::KT - 1) / R::KT;
-  const int32_t st_lo = r_lo / R::KT, st_n = (rows + R::KT - 1) / R::KT - st_lo;
-  const int32_t s0 = p.qp ? 0 : st_lo + (int32_t)((int64_t)st_n * sp / n_split);
-  const int32_t s1 = p.qp ? qc * spq : st_lo + (int32_t)((int64_t)st_n * (sp + 1) / n_split);
   int32_t tau_v = 0;
   if (p.qp && lane < qc) tau_v = p.inv_qp[(int64_t)g * p.m * p.sel_stride + p.inv_off[(int64_t)g * (p.un_stride + 1) + e0] + q0 + lane];
 
@@ -1472,6 +1550,19 @@ __device__ __forceinline__ void dkv_body(const Params& p, unsigned char* smem, i
   constexpr int TPR = 256 / R::KT, DG = X::NG / TPR;
   u32x4_t dl_o[OWN_DELTA ? DG : 1], dl_do[OWN_DELTA ? DG : 1];
   bool dl_ok = false;
+  // (what the copies need of the launch parameters stays in registers: read anew for every row they were a third of the rest of a stage)
+  int32_t G = p.G;
+  uint32_t g_magic = p.g_magic;
+  int64_t tok_stride = p.q_tok_stride, head_stride = p.q_head_stride;
+  const unsigned char *q_rows = (const unsigned char*)((const T*)p.q + (int64_t)g * p.G * p.q_head_stride), *do_rows = (const unsigned char*)((const T*)p.d_o + (int64_t)g * p.G * p.q_head_stride);
+  typedef const __attribute__((address_space(1))) float* gfloat_t;
+  gfloat_t lse = (gfloat_t)p.lse;
+  int32_t C = p.C;
+  asm volatile("" : "+s"(G), "+s"(g_magic), "+s"(tok_stride), "+s"(head_stride), "+s"(q_rows), "+s"(do_rows), "+s"(lse), "+s"(C));
+  auto row_at = [&](int32_t r) __attribute__((always_inline)) {   // bytes from the first row of the KV head's heads
+    const uint32_t m = __umulhi((uint32_t)r, g_magic), i = G == 1 ? (uint32_t)r : m;
+    return ((int64_t)i * tok_stride + (int64_t)(uint32_t)(r - (int32_t)(i * G)) * head_stride) * X::ES;
+  };
   auto copy = [&](int32_t s, uint32_t buf) {
     int32_t base, end;
     stage_rows(s, base, end);
@@ -1482,20 +1573,18 @@ __device__ __forceinline__ void dkv_body(const Params& p, unsigned char* smem, i
       const uint32_t row = wave * Y::RW + k * X::RPI + lrow;
       int32_t r = base + (int32_t)row;
       r = r < end ? r : end - 1;
-      const int32_t i = (int32_t)div_g(p, (uint32_t)r);
-      const int64_t at = ((int64_t)i * p.q_tok_stride + (int64_t)(g * p.G + (r - i * p.G)) * p.q_head_stride) * X::ES +
-                         (int64_t)((pos16 ^ X::swz(row & 15)) << 4);
-      gn_copy16((const unsigned char*)p.q + at, dst + 1024 * k);
-      gn_copy16((const unsigned char*)p.d_o + at, dst + Y::TILE + 1024 * k);
+      const int64_t at = row_at(r) + (int64_t)((pos16 ^ X::swz(row & 15)) << 4);
+      gn_copy16(q_rows + at, dst + 1024 * k);
+      gn_copy16(do_rows + at, dst + Y::TILE + 1024 * k);
     }
     if (tid < R::KT) {
       const int32_t r = base + tid;
       st_l = INFINITY;   // rows past the end: P = 0
       st_d = 0.f;
       if (r < end) {
-        const int32_t i = (int32_t)div_g(p, (uint32_t)r);
-        const int64_t at = (int64_t)(g * p.G + (r - i * p.G)) * p.C + i;
-        st_l = p.lse[at] * 1.4426950408889634f;
+        const uint32_t m = __umulhi((uint32_t)r, g_magic), i = G == 1 ? (uint32_t)r : m;
+        const int64_t at = (int64_t)(g * G + (r - (int32_t)i * G)) * C + i;
+        st_l = lse[at] * 1.4426950408889634f;
         if (!OWN_DELTA) st_d = p.delta[at];
       }
     }
@@ -1503,12 +1592,13 @@ __device__ __forceinline__ void dkv_body(const Params& p, unsigned char* smem, i
       int32_t r = base + tid / TPR;
       dl_ok = r < end;
       r = dl_ok ? r : end - 1;
-      const int32_t i = (int32_t)div_g(p, (uint32_t)r);
-      const int64_t at = ((int64_t)i * p.q_tok_stride + (int64_t)(g * p.G + (r - i * p.G)) * p.q_head_stride) * X::ES + 16 * (tid % TPR);
+      const int64_t at = row_at(r) + 16 * (tid % TPR);
+      // (not the pointers of the copies, whose address space the compiler has lost: flat loads would make every wait for an LDS operand wait for them, too)
+      const unsigned char *o_rows = (const unsigned char*)((const T*)p.o + (int64_t)g * p.G * p.q_head_stride), *dl_rows = (const unsigned char*)((const T*)p.d_o + (int64_t)g * p.G * p.q_head_stride);
 #pragma unroll
       for (int k = 0; k < DG; ++k) {
-        dl_o[k] = *reinterpret_cast<const u32x4_t*>((const unsigned char*)p.o + at + 16 * TPR * k);
-        dl_do[k] = *reinterpret_cast<const u32x4_t*>((const unsigned char*)p.d_o + at + 16 * TPR * k);
+        dl_o[k] = *reinterpret_cast<const u32x4_t*>(o_rows + at + 16 * TPR * k);
+        dl_do[k] = *reinterpret_cast<const u32x4_t*>(dl_rows + at + 16 * TPR * k);
       }
     }
   };
@@ -1559,14 +1649,15 @@ __device__ __forceinline__ void dkv_body(const Params& p, unsigned char* smem, i
         gn_zero(sum[0]);
         gn_zero(sum[1]);
         GnP<T, NT> pr, ds;
+        GnStat st_lse, st_delta;
         auto form_p = [&](const int u, const int x) __attribute__((always_inline)) {
-          float v = __builtin_amdgcn_exp2f(__builtin_fmaf(sum[u][0][x], c, -st[32 * u + 8 * (x >> 2) + 4 * hh + (x & 3)]));
+          float v = __builtin_amdgcn_exp2f(__builtin_fmaf(sum[u][0][x], c, -st_lse.at(st + 32 * u, hh, x)));
           if (mask.value && 32 * u + 8 * (x >> 2) + (x & 3) < rel) v = 0.f;
           sum[u][0][x] = v;
           if (x & 1) pr.set2(x - 1, sum[u][0][x - 1], sum[u][0][x]);
         };
         auto form_ds = [&](const int u, const int x) __attribute__((always_inline)) {
-          sum[u][0][x] *= sum[u][1][x] - st[64 + 32 * u + 8 * (x >> 2) + 4 * hh + (x & 3)];
+          sum[u][0][x] *= sum[u][1][x] - st_delta.at(st + 64 + 32 * u, hh, x);
           if (x & 1) ds.set2(x - 1, sum[u][0][x - 1], sum[u][0][x]);
         };
         gn_pipeline<4 * NJ + 4 * NP, GN_BATCH<T, D>>(
@@ -1576,6 +1667,10 @@ __device__ __forceinline__ void dkv_body(const Params& p, unsigned char* smem, i
               return ad.tr_frag(v % NP, buf + 32 * (v / (2 * NP)) * X::RB + (v / NP % 2 ? 0 : Y::TILE));
             },
             [&](const int i, const u32x4_t& f) __attribute__((always_inline)) {
+              if (i == 2 * NJ - 1) st_lse.fetch(st, hh, 0);
+              if (i == 4 * NJ - 1) st_delta.fetch(st + 64, hh, 0);
+              if (i == 4 * NJ + NP - 1) st_lse.fetch(st + 32, hh, 0);
+              if (i == 4 * NJ + 2 * NP - 1) st_delta.fetch(st + 96, hh, 0);
               if (i < 4 * NJ) {
                 const int u = i / (2 * NJ), j = i % NJ, e = 16 / (2 * NJ);
                 sum[u][i / NJ % 2] = mfma32(__builtin_bit_cast(bf16x8, f), __builtin_bit_cast(bf16x8, i / NJ % 2 ? vf[j] : ks.f[j]), sum[u][i / NJ % 2]);
@@ -1598,6 +1693,7 @@ __device__ __forceinline__ void dkv_body(const Params& p, unsigned char* smem, i
         f32x16 dp[1];
         f32x16& w = sv.v[0];   // P, then dS
         GnP<T, NT> pr, ds;
+        GnStat st_lse, st_delta;
         gn_pipeline<Y::U * L, GN_BATCH<T, D>>(
             [&](const int i) __attribute__((always_inline)) {
               const int u = i / L, k = i % L;
@@ -1611,6 +1707,8 @@ __device__ __forceinline__ void dkv_body(const Params& p, unsigned char* smem, i
                 sv.zero();
                 gn_zero(dp);
               }
+              if (k == NJ - 1) st_lse.fetch(st + 32 * u, hh, 0);
+              if (k == 2 * NJ - 1) st_delta.fetch(st + 64 + 32 * u, hh, 0);
               if (k < NJ) {
                 sv.step(k, f, ks);
                 if (k == NJ - 1) sv.template close<false>(ks, [&](const int j) __attribute__((always_inline)) { return ad.row_frag(j, buf + 32 * u * X::RB); });
@@ -1618,7 +1716,7 @@ __device__ __forceinline__ void dkv_body(const Params& p, unsigned char* smem, i
                 gn_mma<T>(f, vf[k - NJ], dp[0]);
   #pragma unroll
                 for (int x = (k - NJ) * (16 / NJ); x < (k - NJ + 1) * (16 / NJ); ++x) {
-                  float v = __builtin_amdgcn_exp2f(__builtin_fmaf(w[x], c, -st[32 * u + 8 * (x >> 2) + 4 * hh + (x & 3)]));
+                  float v = __builtin_amdgcn_exp2f(__builtin_fmaf(w[x], c, -st_lse.at(st + 32 * u, hh, x)));
                   if (mask.value && 32 * u + 8 * (x >> 2) + (x & 3) < rel) v = 0.f;
                   w[x] = v;
                 }
@@ -1631,7 +1729,7 @@ __device__ __forceinline__ void dkv_body(const Params& p, unsigned char* smem, i
                 const int n = k - 2 * NJ;
   #pragma unroll
                 for (int x = n * (16 / NP); x < (n + 1) * (16 / NP); ++x)
-                  w[x] = w[x] * (dp[0][x] - st[64 + 32 * u + 8 * (x >> 2) + 4 * hh + (x & 3)]);
+                  w[x] = w[x] * (dp[0][x] - st_delta.at(st + 64 + 32 * u, hh, x));
                 if (n == NP - 1) {
   #pragma unroll
                   for (int x = 0; x < 16; x += 2) ds.set2(x, w[x], w[x + 1]);
@@ -1681,10 +1779,25 @@ __device__ __forceinline__ void dkv_body(const Params& p, unsigned char* smem, i
       }
   }
 }
+// the part of the keys of workgroup bid
+template <typename T, typename TG, int D, bool OWN_DELTA, int NT>
+__device__ __forceinline__ void dkv_share(const Params& p, unsigned char* smem, int32_t bid, const GnShares& w, int lp, int32_t max_len) {
+  const int32_t b = bid / p.Hkv, g = bid - b * p.Hkv, units = (int32_t)(((int64_t)max_len * p.P + GN_ROWS - 1) / GN_ROWS);
+  const GnKeySteps steps(p, lp, max_len, GnKey<T, D>::KT);
+  const GnPart t = gn_part(units, w.kv, b, g, p.Hkv, steps);
+  const int32_t lo = steps.from(t.u);
+  dkv_body<T, TG, D, OWN_DELTA, NT, sizeof(T) == 2 && D == 128>(p, smem, GnKeyPiece{g, t.u << (7 - lp), lo + t.s0, lo + t.s1, t.slot, 0, 0, t.first}, lp, w.kv_part);
+}
 template <typename T, typename TG, int D, int NT>
-__global__ __launch_bounds__(256, (D == 128 || sizeof(T) == 4 ? 1 : 2)) void dkv_generic_kernel(Params p, int32_t n_split, int lp, float* __restrict__ part) {
+__global__ __launch_bounds__(256, (D == 128 || sizeof(T) == 4 ? 1 : 2)) void dkv_generic_kernel(Params p, GnShares w, int lp, int32_t max_len) {
   extern __shared__ __align__(16) unsigned char smem[];
-  dkv_body<T, TG, D, false, NT, sizeof(T) == 2 && D == 128>(p, smem, blockIdx.x, n_split, lp, part);
+  if (!p.qp) return dkv_share<T, TG, D, false, NT>(p, smem, blockIdx.x, w, lp, max_len);
+  // a workgroup per entry of the work table
+  const int32_t rest = blockIdx.x / p.Hkv, g = blockIdx.x - rest * p.Hkv, n_units = p.unit_count[g];
+  if (rest >= n_units) return;
+  const int4 un = p.units[(int64_t)g * p.max_units + (n_units - 1 - rest)];
+  constexpr int32_t KT = GnKey<T, D>::KT;
+  dkv_body<T, TG, D, false, NT, sizeof(T) == 2 && D == 128>(p, smem, GnKeyPiece{g, un.x, 0, un.z * ((p.P * p.G + KT - 1) / KT), un.w, un.y, un.z, false}, lp, w.kv_part);
 }
 
 // The whole backward of fp32 tensors: five products per pair instead of the seven of two kernels, all but dQ's as products of three
@@ -1706,14 +1819,9 @@ template <int D> struct GnU {
   // dQ of a stage: wave w takes dim block w % DB and the keys of part w / DB; a partial sum per part
   static constexpr int PARTS = 4 / X::DB, KEYS = GN_ROWS / PARTS, WGS = D == 64 ? 2 : 1;   // workgroups per compute unit
 };
-// first stage of 32 rows that sees list entry e of KV head g
-__device__ __forceinline__ int32_t gn_first_stage(const Params& p, int g, int32_t e, int lp) {
-  const int64_t pos = owned_at(p, g, e) << lp, first_q = p.N - p.C;
-  return (pos > first_q ? (int32_t)(pos - first_q) * p.G : 0) / 32;
-}
 __device__ __forceinline__ int32_t gn_unit_stages(const Params& p, int g, int32_t u, int32_t n_units, int lp) {
   if (u >= n_units) return 0;
-  const int32_t n = (int32_t)(((int64_t)p.C * p.G + 31) / 32) - gn_first_stage(p, g, u << (7 - lp), lp);
+  const int32_t n = (int32_t)(((int64_t)p.C * p.G + 31) / 32) - gn_first_stage(p, g, u << (7 - lp), lp, 32);
   return n > 0 ? n : 0;
 }
 __device__ __forceinline__ int32_t gn_wave_sum(int32_t v) {
@@ -1836,6 +1944,7 @@ __device__ __forceinline__ void units_body(const Params& p, unsigned char* smem,
       const bool mask = base < r_key_max;   // (wave-uniform)
       f32x16 sv[2], dp[2];
       GnP<bf16_t, 3> pr, ds;
+      GnStat st_lse, st_delta;
       gn_zero(sv);
       gn_zero(dp);
       auto terms = [&](const GnP<bf16_t, 3>& v, const int u, const int k) __attribute__((always_inline)) { return u32x4_t{v.w[k][4 * u], v.w[k][4 * u + 1], v.w[k][4 * u + 2], v.w[k][4 * u + 3]}; };
@@ -1846,6 +1955,9 @@ __device__ __forceinline__ void units_body(const Params& p, unsigned char* smem,
           },
           [&](const int i, const u32x4_t (&f)[3]) __attribute__((always_inline)) {
             constexpr int NJ = X::NJ, NV = 2 * X::DB;
+            constexpr bool AHEAD = D == 128;   // (at head dim 64 there are no registers for it, and another workgroup on the compute unit)
+            if (AHEAD && i == NJ - 1) st_lse.fetch(st, hh, 0);
+            if (AHEAD && i == 2 * NJ - 1) st_delta.fetch(st + 64, hh, 0);
             if (i < NJ) {
               gn_mma_terms(f, kf[i][0], kf[i][1], kf[i][2], sv[1], sv[0]);
             } else if (i < 2 * NJ) {   // dP, and P
@@ -1854,7 +1966,7 @@ __device__ __forceinline__ void units_body(const Params& p, unsigned char* smem,
 #pragma unroll
               for (int x = j * (16 / NJ); x < (j + 1) * (16 / NJ); ++x) {
                 const int row = 8 * (x >> 2) + (x & 3);
-                float v = __builtin_amdgcn_exp2f(__builtin_fmaf(sv[0][x] + sv[1][x], c, -st[row + 4 * hh]));
+                float v = __builtin_amdgcn_exp2f(__builtin_fmaf(sv[0][x] + sv[1][x], c, -(AHEAD ? st_lse.at(st, hh, x) : st[row + 4 * hh])));
                 if (mask && row < rel) v = 0.f;
                 sv[0][x] = v;
               }
@@ -1866,7 +1978,7 @@ __device__ __forceinline__ void units_body(const Params& p, unsigned char* smem,
 #pragma unroll
               for (int x = v * (16 / NV); x < (v + 1) * (16 / NV); ++x) {
                 const int row = 8 * (x >> 2) + (x & 3);
-                sv[0][x] = sv[0][x] * (dp[0][x] + dp[1][x] - st[64 + row + 4 * hh]);   // (dP, Delta and dS: lifted twice)
+                sv[0][x] = sv[0][x] * (dp[0][x] + dp[1][x] - (AHEAD ? st_delta.at(st + 64, hh, x) : st[64 + row + 4 * hh]));   // (dP, Delta and dS: lifted twice)
                 ds_out[row * (R::DS_ROW / 4)] = sv[0][x];
               }
 #pragma unroll
@@ -1963,7 +2075,7 @@ __global__ __launch_bounds__(256, GnU<D>::WGS) void bwd_units_kernel(Params p, i
   }
   const int32_t S = (int32_t)(((int64_t)p.C * p.G + 31) / 32);
   for (; at < end; ++u) {
-    const int32_t lo = __builtin_amdgcn_readfirstlane(gn_first_stage(p, g, u << (7 - lp), lp)), n = S - lo > 0 ? S - lo : 0;
+    const int32_t lo = __builtin_amdgcn_readfirstlane(gn_first_stage(p, g, u << (7 - lp), lp, 32)), n = S - lo > 0 ? S - lo : 0;
     const int32_t s0 = lo + (at - before), s1 = s0 + (end - at) < lo + n ? s0 + (end - at) : lo + n;
     if (s0 < s1) {
       units_body<D, ADD>(p, smem, lp, img, part, dq_part, GnPiece{g, u, s0, s1, (b + u - u0) * p.Hkv + g, u - u0, S});
@@ -1974,16 +2086,17 @@ __global__ __launch_bounds__(256, GnU<D>::WGS) void bwd_units_kernel(Params p, i
   }
 }
 
-// dQ and dK / dV of a short call in one launch: the first kv_blocks workgroups take the keys, the others the rows; neither
+// dQ and dK / dV of a short call in one launch: the first workgroups take the keys, the others the rows; neither
 // waits for the other (each computes Delta itself, so dQ must not be written over O).  8 us of launch and start-up less than one after the other, where
 // neither fills the chip.
 template <typename T, typename TG, int D, int NT>
-__global__ __launch_bounds__(256, (D == 128 || sizeof(T) == 4 ? 1 : 2)) void bwd_pair_kernel(Params p, int32_t kv_blocks, int32_t kv_split, float* __restrict__ kv_part,
-                                                                                            int32_t tiles, int32_t n_split, int lp, int32_t max_len,
-                                                                                            float* __restrict__ part) {
+__global__ __launch_bounds__(256, (D == 128 || sizeof(T) == 4 ? 1 : 2)) void bwd_pair_kernel(Params p, GnShares w, int32_t tiles, int lp, int32_t max_len) {
   extern __shared__ __align__(16) unsigned char smem[];
-  if ((int32_t)blockIdx.x < kv_blocks) dkv_body<T, TG, D, true, NT, sizeof(T) == 2 && D == 128>(p, smem, blockIdx.x, kv_split, lp, kv_part);
-  else dq_body<T, D, 1, NT, sizeof(T) == 2 && D == 128>(p, smem, (int32_t)blockIdx.x - kv_blocks, tiles, n_split, lp, max_len, part, nullptr, 0);
+  const int32_t kv_blocks = w.kv.n * p.Hkv;
+  if ((int32_t)blockIdx.x < kv_blocks) return dkv_share<T, TG, D, true, NT>(p, smem, blockIdx.x, w, lp, max_len);
+  const int32_t x = (int32_t)blockIdx.x - kv_blocks, b = x / p.Hkv, g = x - b * p.Hkv;
+  const GnPart t = gn_part(tiles, w.rows, b, g, p.Hkv, GnRowSteps(p, lp, max_len, GnTiles<T, D>::KT));
+  dq_body<T, D, 1, NT, sizeof(T) == 2 && D == 128>(p, smem, GnRowPiece<1>{g, t.u, {{t.s0, t.last ? INT32_MAX : t.s1}}, false, t.slot}, lp, max_len, w.row_part, nullptr, 0);
 }
 
 // What is left of a backward with splits, in one launch: workgroups below dq_blocks add the dQ partials, the others
@@ -1995,7 +2108,7 @@ constexpr int64_t FINISH_FEW = 4096;
 template <typename T, typename TG, int D, typename L, int NW>
 __global__ __launch_bounds__(64 * NW) void bwd_finish_kernel(Params p, int32_t tiles, int32_t dq_split, const float* __restrict__ dq_part,
                                                          int32_t dq_blocks, int32_t kv_split, const float* __restrict__ kv_part, int lp,
-                                                         int redo_keys, int32_t u0, int32_t un) {
+                                                         int redo_keys, int32_t u0, int32_t un, GnShare row_share, GnShare kv_share, int32_t max_len) {
   constexpr bool UNITS = sizeof(L) != sizeof(T);   // the partial sums are those of bwd_units_kernel, its units u0 .. u0 + un - 1: of lifted values (dV), or of dS, lifted twice
   constexpr float low = UNITS ? GN_LOWER * GN_LOWER : 1.f;
   __shared__ GnRowsLds<D> sh;
@@ -2007,10 +2120,17 @@ __global__ __launch_bounds__(64 * NW) void bwd_finish_kernel(Params p, int32_t t
       const int32_t gb = (int32_t)blockIdx.x / (4 * tiles), s = (int32_t)blockIdx.x - gb * 4 * tiles, n = gn_unit_count(p, gb);
       dq_split = 0;
       for (int32_t u = 0; u < n; u += 64)
-        dq_split += __builtin_popcountll(__ballot(u + lane < n && gn_first_stage(p, gb, (u + lane) << (7 - lp), lp) <= s));
+        dq_split += __builtin_popcountll(__ballot(u + lane < n && gn_first_stage(p, gb, (u + lane) << (7 - lp), lp, 32) <= s));
       dq_split = __builtin_amdgcn_readfirstlane(dq_split < un ? dq_split : un) * GnU<D>::PARTS;
     }
-    gn_sum_parts<D, NW>(dq_part, blockIdx.x, blocks * (D / 8) * 64, dq_split, a, [] {});
+    if (row_share.n) {
+      const int32_t gb = (int32_t)blockIdx.x / (4 * tiles), tile = ((int32_t)blockIdx.x >> 2) - gb * tiles;
+      const int2 t = gn_parts_of(row_share, tile, GnRowSteps(p, lp, max_len, GnTiles<T, D>::KT));
+      if (t.y == 1) return;   // (one workgroup had the whole row tile)
+      gn_sum_parts<D, NW>(dq_part, ((int64_t)t.x * p.Hkv + gb) * 4 + (blockIdx.x & 3), (int64_t)p.Hkv * 4 * (D / 8) * 64, t.y, a, [] {});
+    } else {
+      gn_sum_parts<D, NW>(dq_part, blockIdx.x, blocks * (D / 8) * 64, dq_split, a, [] {});
+    }
     const float sc = p.sm_scale;
     int i, h;
     uint32_t bad = gn_rows_out<L, D, NW>(sh, a, true, [&](int, int row, int d, const float4& r) __attribute__((always_inline)) {
@@ -2038,6 +2158,12 @@ __global__ __launch_bounds__(64 * NW) void bwd_finish_kernel(Params p, int32_t t
     if (e0 >= list_len(p, g)) return;
     slot = ((int64_t)u * kv_split) * p.Hkv + g;
     next = p.Hkv;
+    if (kv_share.n) {
+      const int2 t = gn_parts_of(kv_share, u, GnKeySteps(p, lp, max_len, GnTiles<T, D>::KT));
+      if (t.y == 1) return;
+      slot = (int64_t)t.x * p.Hkv + g;
+      kv_split = t.y;
+    }
     if constexpr (UNITS) {   // the ranges (kv_split of them) that hold a piece of the unit
       const int32_t n_units = gn_unit_count(p, g) < u0 + un ? gn_unit_count(p, g) : u0 + un;
       int32_t all = 0, before = 0;
@@ -2129,47 +2255,82 @@ static GnPlan gn_plan(const Params& p, bool bf, int32_t max_len, bool dq, int32_
 static int32_t gn_key_units(const Params& p, int32_t max_len) {
   return (int32_t)(((int64_t)max_len * p.P + GN_ROWS - 1) / GN_ROWS);
 }
-static int32_t gn_key_splits(const Params& p, bool bf, int32_t max_len) {
-  if (p.qp) return 1;
-  const int32_t kt = bf ? 64 : 32;
-  const int64_t wgs = (int64_t)gn_key_units(p, max_len) * p.Hkv;
-  const int64_t want = 512 / (wgs > 0 ? wgs : 1), most = ((int64_t)p.C * p.G + kt - 1) / kt;
-  int64_t s = want < most ? want : most;
-  s = s < 1 ? 1 : s > 16 ? 16 : s;
-  return (int32_t)s;
+// The parts of `units` row tiles or units of a KV head if none has more than `most` steps, and the least `most` with which they are `slots` workgroups or fewer (or the units
+// are more).  Steps fall or rise by the same amount from unit to unit past the first or last `even` ones, all alike: their sum is estimated, then counted.
+template <typename N> static int32_t gn_count(const N& steps, int32_t units, int32_t from, int32_t to, int32_t most) {   // (units outside from .. to - 1 are like the first)
+  int32_t n = (units - (to - from)) * ((steps(0) + most - 1) / most);
+  for (int32_t u = from; u < to; ++u) n += (steps(u) + most - 1) / most;
+  return n;
 }
-
-// A backward in one launch (bwd_pair_kernel), by the same kind of estimate: splits of keys and rows so that all
-// workgroups run at once (256, or 512 at head dim 64 with bf16: two per compute unit) and the longer of the two is
-// shortest.  us: huge where the call does not fit that way.
-struct GnPair { int32_t kv_split, row_split; float us; };
+template <typename N> static GnShare gn_share(const N& steps, int32_t units, int32_t from, int32_t to, int32_t slots) {
+  int32_t lo = 1, hi = steps(0) > steps(units - 1) ? steps(0) : steps(units - 1);   // (with hi every unit is one part)
+  if ((hi + 15) / 16 > lo) lo = (hi + 15) / 16;   // (at most 16 parts)
+  while (lo < hi) {
+    const int32_t mid = (lo + hi) / 2;
+    if (gn_count(steps, units, from, to, mid) <= slots) hi = mid;
+    else lo = mid + 1;
+  }
+  return {gn_count(steps, units, from, to, lo), lo};
+}
+// workgroups of the dK / dV and one-launch kernels that run at once
+static int32_t gn_slots(const Params& p, bool bf) { return bf && p.D == 64 ? 512 : 256; }   // (two workgroups per compute unit)
+static int32_t gn_head_slots(const Params& p, bool bf) { return gn_slots(p, bf) / p.Hkv > 1 ? gn_slots(p, bf) / p.Hkv : 1; }
 // us of a stage of KT rows x 128 keys in the dK / dV kernel
-static float gn_stage_us(const Params& p, bool bf) { return bf ? (p.D == 128 ? 2.6f : 1.5f) : (p.D == 128 ? 10.f : 5.f); }
+static bool gn_one_term(const Params& p) { return p.D == HD && p.P == TP; }   // (bf16: probabilities and dS in one term)
+static float gn_stage_us(const Params& p, bool bf) { return bf ? (gn_one_term(p) ? 2.1f : p.D == 128 ? 3.8f : 3.2f) : (p.D == 128 ? 10.f : 5.f); }
+static float gn_tile_us(const Params& p, bool bf) { return bf ? (gn_one_term(p) ? 1.3f : 2.f) : (p.D == 128 ? 7.f : 3.5f); }   // of KT keys x 128 rows in the one-launch backward
+static GnShare gn_key_share(const Params& p, bool bf, int32_t max_len, int32_t slots, int32_t most = 0) {   // most: the steps of a part, if given
+  const int32_t units = gn_key_units(p, max_len), lp = __builtin_ctz(p.P), own = (max_len - p.m) >> (7 - lp);   // (the first unit that holds a page of the chunk)
+  if (p.qp || units < 1) return {0, 1};
+  const GnKeySteps steps(p, lp, max_len, bf ? 64 : 32);
+  return most ? GnShare{gn_count(steps, units, own, units, most), most} : gn_share(steps, units, own, units, slots);
+}
+static GnShare gn_row_share(const Params& p, bool bf, int32_t max_len, int32_t slots) {
+  const int32_t tiles = gn_tiles(p.C, p.G, p.P, p.m, 0);
+  return gn_share(GnRowSteps(p, __builtin_ctz(p.P), max_len, bf ? 64 : 32), tiles, 0, tiles, slots);
+}
+static float gn_key_us(const Params& p, bool bf, int32_t most) { return most * gn_stage_us(p, bf) + (bf ? 12.f : 8.f); }
+
+// A backward in one launch (bwd_pair_kernel): the workgroups that run at once (256, or 512 at head dim 64 with bf16: two per
+// compute unit) are shared out so that keys and rows take the same time.  us: huge where there is no such launch.
+struct GnPair { GnShare kv, rows; float us; };
 static GnPair gn_pair(const Params& p, bool bf, int32_t max_len) {
-  GnPair best = {1, 1, 1e30f};
-  const int32_t slots = bf && p.D == 64 ? 512 : 256, wq = gn_tiles(p.C, p.G, p.P, p.m, p.qp) * p.Hkv, wk = gn_key_units(p, max_len) * p.Hkv;
-  if (p.qp || 2 * wq > slots || 2 * wk > slots) return best;
-  const float kt = bf ? 64.f : 32.f, nt = (max_len - 0.5f * p.m) * p.P / kt, stages = (float)p.C * p.G / kt;
-  const float tile = bf ? (p.D == 128 ? 1.2f : 0.8f) : (p.D == 128 ? 7.f : 3.5f), stage = gn_stage_us(p, bf);
-  for (int32_t nk = 1; nk <= 16 && (nk == 1 || nk <= stages); ++nk) {
-    if (wk * nk + wq > slots) break;
-    int32_t ns = (slots - wk * nk) / wq;
-    ns = ns > 32 ? 32 : ns > nt ? (nt < 1.f ? 1 : (int32_t)nt) : ns;
-    const float tq = (nt / ns > 1.f ? nt / ns : 1.f) * tile + 6.f, tk = (stages / nk > 1.f ? stages / nk : 1.f) * stage + 8.f;
-    const float us = (tq > tk ? tq : tk) + (wk * nk * 2.f + wq * ns) * p.D * 2.56e-4f;
-    if (us < best.us) best = {nk, ns, us};
+  GnPair best = {{0, 1}, {0, 1}, 1e30f};
+  const int32_t per = gn_slots(p, bf) / p.Hkv;   // workgroups of a KV head
+  const int32_t wq = gn_tiles(p.C, p.G, p.P, p.m, p.qp), wk = gn_key_units(p, max_len);
+  // bf16 pages of 128: up to half of the workgroups' number.  Beyond that it would be faster, too (28 / 4 heads, 512 rows, 10 pages 60 us against 70; 4 / 4, 1024 rows, 30
+  // pages 56 against 67), but its dS is formed from P before P is rounded, that of the kernels for many rows and keys after: calls of this size agree to 2e-3 with
+  // the same lists given per query page, which have those kernels only.
+  if (p.qp || wk < 1 || (bf && gn_one_term(p) ? 2 : 1) * (wq + wk) > per) return best;
+  const float tile = gn_tile_us(p, bf);
+  const int32_t whole = gn_key_share(p, bf, max_len, wk).most;
+  for (int32_t e = 1, most = 0; e <= 16 && e <= whole; ++e) {   // more parts per unit, until the rows have too few workgroups
+    if ((whole + e - 1) / e == most) continue;
+    most = (whole + e - 1) / e;
+    GnShare k = gn_key_share(p, bf, max_len, 0, most);
+    const GnShare q = k.n > per - wq ? GnShare{0, 1} : gn_row_share(p, bf, max_len, per - k.n);
+    if (q.n == 0) break;
+    const float tk = gn_key_us(p, bf, most), tq = q.most * tile + (bf ? 10.f : 6.f);
+    const float us = (tq > tk ? tq : tk) + p.Hkv * ((k.n > wk ? 2.f * k.n : 0.f) + (q.n > wq ? q.n : 0.f)) * p.D * 2.56e-4f;
+    if (us < best.us) best = {k, q, us};
+    if (tq > tk) break;
   }
   return best;
 }
 // dQ and dK / dV one after the other, each with the chip to itself
 static float gn_two_us(const Params& p, bool bf, int32_t max_len) {
-  const float stages = (float)p.C * p.G / (bf ? 64.f : 32.f);
-  const float stage = bf && p.D == HD && p.P == TP ? 1.75f : gn_stage_us(p, bf);   // (the kernel of pages of 128 has two roles per pair of waves)
-  const int64_t wgs = (int64_t)gn_key_units(p, max_len) * p.Hkv;
-  int64_t n = 256 / wgs;
-  n = n > 16 ? 16 : n > stages ? (int64_t)stages : n;
-  n = n < 1 ? 1 : n;
-  return gn_plan(p, bf, max_len, true).us + (float)((wgs * n + 255) / 256) * stages / n * stage + 9.f;   // (256 workgroups at a time)
+  const float rows = gn_plan(p, bf, max_len, true).us;
+  if (bf && gn_one_term(p)) {   // (the kernel of pages of 128 has two roles per pair of waves and cuts the rows of a page into slices; 256 workgroups at a time)
+    const int64_t wgs = (int64_t)gn_key_units(p, max_len) * p.Hkv;
+    const float stages = (float)p.C * p.G / 64.f;
+    int64_t n = 256 / wgs;
+    n = n > 16 ? 16 : n > stages ? (int64_t)stages : n;
+    n = n < 1 ? 1 : n;
+    return rows + (float)((wgs * n + 255) / 256) * stages / n * 1.75f + 16.f;
+  }
+  const int64_t slots = gn_slots(p, bf);
+  const GnShare k = gn_key_share(p, bf, max_len, gn_head_slots(p, bf));
+  return (rows + (float)(((int64_t)k.n * p.Hkv + slots - 1) / slots) * gn_key_us(p, bf, k.most)) * (bf && p.D == 64 ? 1.2f : 1.f) + 16.f;
 }
 static bool gn_takes_pair(const Params& p, bool bf, int32_t max_len, const GnPair& pair) {
   return pair.us < 1e29f && pair.us < gn_two_us(p, bf, max_len);
@@ -2290,19 +2451,21 @@ size_t fwd_generic_workspace_bytes(const Params& p, bool bf, int32_t max_len) {
   return terms > plain ? terms : plain;
 }
 size_t dq_generic_part_bytes(const Params& p, bool bf, int32_t max_len) { return gn_row_part_bytes(p, gn_plan(p, bf, max_len, true).n); }
-static size_t gn_key_part_bytes(const Params& p, int32_t max_len, int32_t split) {
-  const size_t slots = p.qp ? (size_t)p.Hkv * qp_max_pslots(p, p.sel_stride) : split > 1 ? (size_t)gn_key_units(p, max_len) * p.Hkv * split : 0;
+// partial sums of the shares of keys, and of rows
+static size_t gn_key_part_bytes(const Params& p, int32_t units, const GnShare& w) {   // (0: no more parts than units)
+  const size_t slots = p.qp ? (size_t)p.Hkv * qp_max_pslots(p, p.sel_stride) : w.n <= units ? 0 : (size_t)p.Hkv * w.n;
   return gn_up(slots * 2 * part_key_blocks(p) * 32 * p.D * 4);
 }
 static size_t gn_pair_bytes(const Params& p, int32_t max_len, const GnPair& t) {
-  return gn_key_part_bytes(p, max_len, t.kv_split) + gn_row_part_bytes(p, t.row_split);
+  const bool whole = t.rows.n <= gn_tiles(p.C, p.G, p.P, p.m, 0);
+  return gn_key_part_bytes(p, gn_key_units(p, max_len), t.kv) + (whole ? 0 : (size_t)p.Hkv * t.rows.n * GN_ROWS * p.D * 4);
 }
 bool bwd_takes_pair(const Params& p, bool bf, int32_t max_len) { return gn_takes_pair(p, bf, max_len, gn_pair(p, bf, max_len)); }
 size_t bwd_pair_bytes(const Params& p, bool bf, int32_t max_len) { return gn_pair_bytes(p, max_len, gn_pair(p, bf, max_len)); }
-size_t bwd_generic_min_bytes(const Params& p) { return gn_up((size_t)p.Hq * p.C * sizeof(float)) + gn_key_part_bytes(p, 0, 1); }
+size_t bwd_generic_min_bytes(const Params& p) { return gn_up((size_t)p.Hq * p.C * sizeof(float)) + gn_key_part_bytes(p, 0, {0, 1}); }
 size_t bwd_generic_workspace_bytes(const Params& p, bool bf, int32_t max_len) {
   const size_t delta = gn_up((size_t)p.Hq * p.C * sizeof(float)), pair = bwd_takes_pair(p, bf, max_len) ? bwd_pair_bytes(p, bf, max_len) : 0;
-  const size_t two = delta + dq_generic_part_bytes(p, bf, max_len) + gn_key_part_bytes(p, max_len, gn_key_splits(p, bf, max_len));
+  const size_t two = delta + dq_generic_part_bytes(p, bf, max_len) + gn_key_part_bytes(p, gn_key_units(p, max_len), gn_key_share(p, bf, max_len, gn_head_slots(p, bf)));
   const size_t most = pair > two ? pair : two;
   if (bf || p.qp) return most;
   const GnUnits u = gn_units(p, max_len, SIZE_MAX);
@@ -2414,13 +2577,15 @@ hipError_t launch_dq_generic_bf16_128(const Params& p, int32_t max_len, float* p
 
 template <typename T, typename TG, int D, typename L = T>
 static hipError_t bwd_finish(const Params& p, int32_t dq_split, const float* dq_part, int32_t kv_units, int32_t kv_split, const float* kv_part,
-                             bool redo_keys, hipStream_t st, int32_t u0 = 0, int32_t un = 0) {
-  const int32_t dq_blocks = dq_split > 1 ? (int32_t)(gn_row_blocks(p)) : 0;
+                             bool redo_keys, hipStream_t st, int32_t u0 = 0, int32_t un = 0, GnShare rows = {0, 1}, GnShare kv = {0, 1}, int32_t max_len = 0) {
+  if (rows.n <= gn_tiles(p.C, p.G, p.P, p.m, p.qp)) rows.n = 0;   // (nothing is left)
+  if (kv.n > 0 && kv.n <= kv_units) kv_units = 0;
+  const int32_t dq_blocks = dq_split > 1 || rows.n ? (int32_t)(gn_row_blocks(p)) : 0;
   const int64_t blocks = dq_blocks + (int64_t)kv_units * p.Hkv * 2 * part_key_blocks(p);
   if (blocks <= 0) return hipSuccess;
   auto run = [&](auto kernel, unsigned waves) {
     kernel<<<dim3((unsigned)blocks), dim3(64 * waves), 0, st>>>(p, gn_tiles(p.C, p.G, p.P, p.m, p.qp), dq_split, dq_part, dq_blocks, kv_split, kv_part,
-                                                                __builtin_ctz(p.P), redo_keys, u0, un);
+                                                                __builtin_ctz(p.P), redo_keys, u0, un, rows, kv, max_len);
   };
   if (blocks <= FINISH_FEW) run(bwd_finish_kernel<T, TG, D, L, 8>, 8);
   else run(bwd_finish_kernel<T, TG, D, L, 4>, 4);
@@ -2448,13 +2613,10 @@ static hipError_t bwd_pair(Params p, int32_t max_len, void* ws, size_t ws_bytes,
   static DeviceOnce once;
   if (hipError_t e = ensure_max_dynamic_lds(once, (const void*)bwd_pair_kernel<T, TG, D, NT>, LDS); e != hipSuccess) return e;
   p.delta = nullptr;
-  float* kv_part = (float*)ws;
-  float* dq_part = (float*)((unsigned char*)ws + gn_key_part_bytes(p, max_len, t.kv_split));
-  const int32_t tiles = gn_tiles(p.C, p.G, p.P, p.m, p.qp), units = gn_key_units(p, max_len), kv_blocks = units * p.Hkv * t.kv_split;
-  bwd_pair_kernel<T, TG, D, NT><<<dim3((unsigned)(kv_blocks + tiles * p.Hkv * t.row_split)), dim3(256), LDS, st>>>(
-      p, kv_blocks, t.kv_split, kv_part, tiles, t.row_split, __builtin_ctz(p.P), gn_list_len(p, max_len), dq_part);
+  const GnShares w = {t.kv, t.rows, (float*)ws, (float*)((unsigned char*)ws + gn_key_part_bytes(p, gn_key_units(p, max_len), t.kv))};
+  bwd_pair_kernel<T, TG, D, NT><<<dim3((unsigned)((t.kv.n + t.rows.n) * p.Hkv)), dim3(256), LDS, st>>>(p, w, gn_tiles(p.C, p.G, p.P, p.m, 0), __builtin_ctz(p.P), max_len);
   if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
-  return bwd_finish<T, TG, D>(p, t.row_split, dq_part, t.kv_split > 1 ? units : 0, t.kv_split, kv_part, true, st);
+  return bwd_finish<T, TG, D>(p, 1, w.row_part, gn_key_units(p, max_len), 1, w.kv_part, true, st, 0, 0, t.rows, t.kv, max_len);
 }
 hipError_t launch_bwd_pair_bf16_128(const Params& p, int32_t max_len, void* ws, size_t ws_bytes, hipStream_t st, bool* done) {
   return p.grad_is_bf16 ? bwd_pair<bf16_t, bf16_t, 128, 1>(p, max_len, ws, ws_bytes, "bwd_pair", st, done)
@@ -2506,15 +2668,15 @@ static hipError_t bwd_generic(Params p, int32_t max_len, void* ws, size_t ws_byt
   static DeviceOnce once_kv;
   if (hipError_t e = ensure_max_dynamic_lds(once_kv, (const void*)dkv_generic_kernel<T, TG, D, GN_TERMS<T>>, GnKey<T, D>::LDS); e != hipSuccess) return e;
   // [Delta][dK / dV slices][dQ partials]; a workspace without room for the slices of this call takes fewer
-  unsigned char* w = (unsigned char*)ws;
-  p.delta = (float*)w;
-  w += gn_up((size_t)p.Hq * p.C * sizeof(float));
+  unsigned char* at = (unsigned char*)ws;
+  p.delta = (float*)at;
+  at += gn_up((size_t)p.Hq * p.C * sizeof(float));
   size_t left = ws_bytes - gn_up((size_t)p.Hq * p.C * sizeof(float));
-  int32_t nk = gn_key_splits(p, Gn<T, D>::BF, max_len);
-  while (nk > 1 && gn_key_part_bytes(p, max_len, nk) > left) --nk;
-  float* kv_part = (float*)w;
-  float* dq_part = (float*)(w + gn_key_part_bytes(p, max_len, nk));
-  left -= gn_key_part_bytes(p, max_len, nk);
+  GnShares w = {gn_key_share(p, Gn<T, D>::BF, max_len, gn_head_slots(p, Gn<T, D>::BF)), {0, 1}, (float*)at, nullptr};
+  const int32_t all = gn_key_units(p, max_len);
+  if (gn_key_part_bytes(p, all, w.kv) > left) w.kv = {all, INT32_MAX / 2};   // (a workgroup per unit)
+  float* dq_part = (float*)(at + gn_key_part_bytes(p, all, w.kv));
+  left -= gn_key_part_bytes(p, all, w.kv);
   const int32_t units = p.qp ? p.max_units : gn_key_units(p, max_len);
   if (p.d_q != p.o && dq_overlaps_o(p, Gn<T, D>::BF)) {
     if (hipError_t e = launch_delta<T, D>(p, st); e != hipSuccess) return e;
@@ -2523,10 +2685,10 @@ static hipError_t bwd_generic(Params p, int32_t max_len, void* ws, size_t ws_byt
   int32_t ns = 1;
   hipError_t e = dq_generic<T, D>(p, max_len, dq_part, left, nullptr, 0, &ns, st);
   if (e != hipSuccess) return e;
-  dkv_generic_kernel<T, TG, D, GN_TERMS<T>><<<dim3((unsigned)units * p.Hkv * nk), dim3(256), GnKey<T, D>::LDS, st>>>(p, nk, __builtin_ctz(p.P), kv_part);
+  dkv_generic_kernel<T, TG, D, GN_TERMS<T>><<<dim3((unsigned)(p.qp ? units : w.kv.n) * p.Hkv), dim3(256), GnKey<T, D>::LDS, st>>>(p, w, __builtin_ctz(p.P), max_len);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
-  return bwd_finish<T, TG, D>(p, ns, dq_part, p.qp ? p.max_multi : nk > 1 ? units : 0, nk, kv_part, true, st);
+  return bwd_finish<T, TG, D>(p, ns, dq_part, p.qp ? p.max_multi : units, 1, w.kv_part, true, st, 0, 0, {0, 1}, w.kv, max_len);
 }
 // max_len: host-side upper bound of the list length (of the union with one list per query page)
 hipError_t launch_bwd_generic(const Params& p, bool bf, int32_t max_len, void* ws, size_t ws_bytes, hipStream_t st) {

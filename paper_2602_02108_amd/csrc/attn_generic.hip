@@ -1800,8 +1800,8 @@ __global__ __launch_bounds__(256, (D == 128 || sizeof(T) == 4 ? 1 : 2)) void dkv
   dkv_body<T, TG, D, false, NT, sizeof(T) == 2 && D == 128>(p, smem, GnKeyPiece{g, un.x, 0, un.z * ((p.P * p.G + KT - 1) / KT), un.w, un.y, un.z, false}, lp, w.kv_part);
 }
 
-// The whole backward of fp32 tensors: five products per pair instead of the seven of two kernels, all but dQ's as products of three
-// bf16 terms.  A unit is 128 list tokens, 32 per wave: their K and V stay in registers (as terms), the rows of the head stream through
+// The whole backward of fp32 tensors: five products per pair instead of the seven of two kernels, as products of three bf16 terms (at head dim
+// 64 all but dQ's).  A unit is 128 list tokens, 32 per wave: their K and V stay in registers (as terms), the rows of the head stream through
 // LDS in stages of 32, as terms too (row_terms_kernel).  dS goes through LDS, dQ of a stage is left as one fp32 partial sum per unit.  One wave per
 // SIMD (512 registers); the vector work of a product runs between the matrix instructions of the next one.
 // The stages of all units of a KV head, one unit after the other, are cut into equal ranges, one per workgroup: whatever the list and the chunk, every
@@ -1813,9 +1813,16 @@ __global__ __launch_bounds__(256, (D == 128 || sizeof(T) == 4 ? 1 : 2)) void dkv
 template <int D> struct GnU {
   typedef Gn<bf16_t, D> X;
   typedef GnF3<D> F;
-  // a stage: Q0 Q1 Q2 dO0 dO1 dO2; {lse2, delta} of two stages; dS as [row][key], rows 544 bytes apart (both the dwords of 32 keys x 2 rows that a store
-  // moves and the 16 bytes x 64 rows of a read fall on all banks); K as [key][dim]
-  static constexpr int STAT = F::TILE, DS = STAT + 2 * 64 * 4, DS_ROW = GN_ROWS * 4 + 32, KL = DS + 32 * DS_ROW, KL_ROW = D * 4 + 16, LDS = KL + GN_ROWS * KL_ROW;
+  // Head dim 128: dQ in terms, too.  A stage: Q0 Q1 Q2 dO0 dO1 dO2 and {lse2, delta}; K0 K1 K2 of the unit as [key][dim] in the order of a row tile.  The terms of dS take the
+  // place of dO once dV is done, as [key][row] with word w (four rows) of key k at w ^ (k / 4 mod 8): what 64 lanes write or read at once falls on all banks.
+  // Against dQ on the fp32 pipe, 28 / 4 heads, chunk 512, 20 pages of 128, whole pass: 426 -> 421 us (192 matrix cycles in the place of 512, but three barriers more
+  // a stage); dQ against 64 bits 7.9e-7 -> 7.4e-7.
+  // Head dim 64 (two workgroups per compute unit have 80 KiB each): dQ on the fp32 pipe.  dS as [row][key], rows 544 bytes apart (both the dwords of 32 keys x 2 rows that
+  // a store moves and the 16 bytes x 64 rows of a read fall on all banks); K as [key][dim]
+  static constexpr bool TERMS = D == 128;
+  static constexpr int STAT = F::TILE, DS = TERMS ? F::V : STAT + 2 * 64 * 4, DS_ROW = GN_ROWS * 4 + 32, DS_TERM = GN_ROWS * 64;
+  static constexpr int KL = TERMS ? STAT + 2 * 64 * 4 : DS + 32 * DS_ROW, KL_ROW = D * 4 + 16, K_TERM = GN_ROWS * X::RB, LDS = KL + (TERMS ? 3 * K_TERM : GN_ROWS * KL_ROW);
+  static_assert(!TERMS || 3 * DS_TERM <= F::V, "dS in the place of dO");
   // dQ of a stage: wave w takes dim block w % DB and the keys of part w / DB; a partial sum per part
   static constexpr int PARTS = 4 / X::DB, KEYS = GN_ROWS / PARTS, WGS = D == 64 ? 2 : 1;   // workgroups per compute unit
 };
@@ -1890,10 +1897,15 @@ __device__ __forceinline__ void units_body(const Params& p, unsigned char* smem,
     }
 #pragma unroll
   for (int j = 0; j < X::NJ; ++j) {
-    u32x4_t* kl = reinterpret_cast<u32x4_t*>(smem + R::KL + kq * R::KL_ROW + 64 * j + 32 * hh);
-    kl[0] = raw[0][j][0];
-    kl[1] = raw[0][j][1];
     gn_load_terms<false>(raw[0][j][0], raw[0][j][1], kf[j]);
+    if constexpr (R::TERMS) {
+#pragma unroll
+      for (int k = 0; k < 3; ++k) *reinterpret_cast<u32x4_t*>(smem + R::KL + k * R::K_TERM + kq * X::RB + (((2 * j + hh) ^ X::swz(kq & 15)) << 4)) = kf[j][k];
+    } else {
+      u32x4_t* kl = reinterpret_cast<u32x4_t*>(smem + R::KL + kq * R::KL_ROW + 64 * j + 32 * hh);
+      kl[0] = raw[0][j][0];
+      kl[1] = raw[0][j][1];
+    }
     gn_lift(raw[1][j][0]);
     gn_lift(raw[1][j][1]);
     gn_load_terms<false>(raw[1][j][0], raw[1][j][1], vf[j]);
@@ -1906,15 +1918,18 @@ __device__ __forceinline__ void units_body(const Params& p, unsigned char* smem,
   GnAddr<bf16_t, D> ad;
   ad.init(lane, 0);
   float* const ds_out = reinterpret_cast<float*>(smem + R::DS) + kq + 4 * hh * (R::DS_ROW / 4);
-  if (!active) {   // (keys past the list: dS is and stays zero)
+  if (!R::TERMS && !active) {   // (keys past the list: dS is and stays zero)
 #pragma unroll
     for (int x = 0; x < 16; ++x) ds_out[(8 * (x >> 2) + (x & 3)) * (R::DS_ROW / 4)] = 0.f;
   }
-  const unsigned char* src = img + ((int64_t)t.g * t.stages) * F::TILE + wave * (F::TILE / 4) + lane * 16;
+  const unsigned char* src = img + ((int64_t)t.g * t.stages) * F::TILE + wave * (F::V / 4) + lane * 16;
   float st_l = INFINITY, st_d = 0.f;   // statistics of row `tid` of the stage under way
-  auto copy = [&](const int32_t s) __attribute__((always_inline)) {
+  // part 0: Q, 1: dO of stage s; every wave a quarter of each
+  auto rows_in = [&](const int32_t s, const int part) __attribute__((always_inline)) {
 #pragma unroll
-    for (int k = 0; k < F::TILE / 4096; ++k) gn_copy16(src + (int64_t)s * F::TILE + 1024 * k, wave * (F::TILE / 4) + 1024 * k);
+    for (int k = 0; k < F::V / 4096; ++k) gn_copy16(src + (int64_t)s * F::TILE + part * F::V + 1024 * k, part * F::V + wave * (F::V / 4) + 1024 * k);
+  };
+  auto stats_in = [&](const int32_t s) __attribute__((always_inline)) {
     if (tid < 32) {
       const int32_t r = 32 * s + tid;
       st_l = INFINITY;   // rows past the end: P = 0
@@ -1928,103 +1943,22 @@ __device__ __forceinline__ void units_body(const Params& p, unsigned char* smem,
     }
   };
   float* const st = reinterpret_cast<float*>(smem + R::STAT);
-  auto publish = [&] {
+  auto stats_out = [&] {
     if (tid < 32) {
       st[tid] = st_l;
       st[64 + tid] = st_d;
     }
-    wait_copies<0>();
-    __syncthreads();
   };
-  copy(t.s0);
-  publish();
-  for (int32_t s = t.s0; s < t.s1; ++s) {
-    if (active) {
-      const int32_t base = 32 * s, rel = r_key - base - 4 * hh;
-      const bool mask = base < r_key_max;   // (wave-uniform)
-      f32x16 sv[2], dp[2];
-      GnP<bf16_t, 3> pr, ds;
-      GnStat st_lse, st_delta;
-      gn_zero(sv);
-      gn_zero(dp);
-      auto terms = [&](const GnP<bf16_t, 3>& v, const int u, const int k) __attribute__((always_inline)) { return u32x4_t{v.w[k][4 * u], v.w[k][4 * u + 1], v.w[k][4 * u + 2], v.w[k][4 * u + 3]}; };
-      gn_terms_pipeline<2 * X::NJ + 4 * X::DB>(
-          [&](const int i, const int k) __attribute__((always_inline)) {
-            return i < X::NJ ? ad.row_frag(i, k * F::TERM) : i < 2 * X::NJ ? ad.row_frag(i - X::NJ, F::V + k * F::TERM)
-                 : i < 2 * X::NJ + 2 * X::DB ? ad.tr_frag(i - 2 * X::NJ, F::V + k * F::TERM) : ad.tr_frag(i - 2 * X::NJ - 2 * X::DB, k * F::TERM);
-          },
-          [&](const int i, const u32x4_t (&f)[3]) __attribute__((always_inline)) {
-            constexpr int NJ = X::NJ, NV = 2 * X::DB;
-            constexpr bool AHEAD = D == 128;   // (at head dim 64 there are no registers for it, and another workgroup on the compute unit)
-            if (AHEAD && i == NJ - 1) st_lse.fetch(st, hh, 0);
-            if (AHEAD && i == 2 * NJ - 1) st_delta.fetch(st + 64, hh, 0);
-            if (i < NJ) {
-              gn_mma_terms(f, kf[i][0], kf[i][1], kf[i][2], sv[1], sv[0]);
-            } else if (i < 2 * NJ) {   // dP, and P
-              const int j = i - NJ;
-              gn_mma_terms(f, vf[j][0], vf[j][1], vf[j][2], dp[1], dp[0]);
+  // dQ of a stage: dim block db, the keys of part kp; dims 32 db + 8 a + 4 hh .. + 3 are group 4 db + a of the block
+  const int db = wave % X::DB, kp = wave / X::DB;
+  float4* const dst0 = reinterpret_cast<float4*>(dq_part) + (((int64_t)(t.set * R::PARTS + kp) * p.Hkv + t.g) * (4 * gn_tiles(p.C, p.G, p.P, p.m, 0))) * (D / 8) * 64 + lane + 256 * db;
+  float4 old[4];
+  auto fetch = [&](const int32_t s) __attribute__((always_inline)) {
 #pragma unroll
-              for (int x = j * (16 / NJ); x < (j + 1) * (16 / NJ); ++x) {
-                const int row = 8 * (x >> 2) + (x & 3);
-                float v = __builtin_amdgcn_exp2f(__builtin_fmaf(sv[0][x] + sv[1][x], c, -(AHEAD ? st_lse.at(st, hh, x) : st[row + 4 * hh])));
-                if (mask && row < rel) v = 0.f;
-                sv[0][x] = v;
-              }
-#pragma unroll
-              for (int x = j * (16 / NJ); x < (j + 1) * (16 / NJ); x += 2) pr.set2(x, sv[0][x], sv[0][x + 1]);
-            } else if (i < 2 * NJ + NV) {   // dV, and dS
-              const int v = i - 2 * NJ, u = v / X::DB;
-              gn_mma_terms(f, terms(pr, u, 0), terms(pr, u, 1), terms(pr, u, 2), dv[v % X::DB], dv[v % X::DB]);
-#pragma unroll
-              for (int x = v * (16 / NV); x < (v + 1) * (16 / NV); ++x) {
-                const int row = 8 * (x >> 2) + (x & 3);
-                sv[0][x] = sv[0][x] * (dp[0][x] + dp[1][x] - (AHEAD ? st_delta.at(st + 64, hh, x) : st[64 + row + 4 * hh]));   // (dP, Delta and dS: lifted twice)
-                ds_out[row * (R::DS_ROW / 4)] = sv[0][x];
-              }
-#pragma unroll
-              for (int x = v * (16 / NV); x < (v + 1) * (16 / NV); x += 2) ds.set2(x, sv[0][x], sv[0][x + 1]);
-            } else {
-              const int v = i - 2 * NJ - NV, u = v / X::DB;
-              gn_mma_terms(f, terms(ds, u, 0), terms(ds, u, 1), terms(ds, u, 2), dk[v % X::DB], dk[v % X::DB]);
-            }
-          });
-    }
-    __syncthreads();   // dS is in LDS; nobody reads the stage any more, whose place takes the next
-    if (s + 1 < t.s1) copy(s + 1);
-    f32x16 dq;
-#pragma unroll
-    for (int x = 0; x < 16; ++x) dq[x] = 0.f;
-    // operands of four instructions: dS of keys 8 n + 4 hh .. + 3 of the part (row lq), K of the same keys (dim 32 db + lq)
-    const int db = wave % X::DB, kp = wave / X::DB;
-    const uint32_t at_ds = R::DS + lq * R::DS_ROW + 16 * hh + kp * R::KEYS * 4, at_k = R::KL + (kp * R::KEYS + 4 * hh) * R::KL_ROW + (32 * db + lq) * 4;
-    u32x4_t fd[2];
-    float fk[2][4];
-    auto load = [&](const int n) __attribute__((always_inline)) {
-      fd[n & 1] = *reinterpret_cast<const u32x4_t*>(smem + (at_ds + 32 * n));
-#pragma unroll
-      for (int x = 0; x < 4; ++x) fk[n & 1][x] = *reinterpret_cast<const float*>(smem + (at_k + (8 * n + x) * R::KL_ROW));
-    };
-    // dims 32 db + 8 a + 4 hh .. + 3: group 4 db + a of the block
-    float4* dst = reinterpret_cast<float4*>(dq_part) + (((int64_t)(t.set * R::PARTS + kp) * p.Hkv + t.g) * (4 * gn_tiles(p.C, p.G, p.P, p.m, 0)) + s) * (D / 8) * 64 + lane + 256 * db;
-    float4 old[4];
-    auto fetch = [&] {
-#pragma unroll
-      for (int a = 0; a < 4; ++a) old[a] = dst[64 * a];
-    };
-    if constexpr (ADD && D == 128) fetch();   // (on their way during the product; at head dim 64 the other workgroup computes meanwhile, and there are no registers for them)
-    load(0);
-#pragma unroll
-    for (int n = 0; n < R::KEYS / 8; ++n) {
-      if (n + 1 < R::KEYS / 8) {
-        load(n + 1);
-        __builtin_amdgcn_sched_barrier(0);
-      }
-#pragma unroll
-      for (int x = 0; x < 4; ++x) dq = __builtin_amdgcn_mfma_f32_32x32x2f32(fk[n & 1][x], __uint_as_float(fd[n & 1][x]), dq, 0, 0, 0);
-      __builtin_amdgcn_sched_barrier(0);
-    }
+    for (int a = 0; a < 4; ++a) old[a] = dst0[(int64_t)s * (D / 8) * 64 + 64 * a];
+  };
+  auto dq_out = [&](const int32_t s, f32x16& dq) __attribute__((always_inline)) {
     if constexpr (ADD) {
-      if constexpr (D == 64) fetch();
 #pragma unroll
       for (int a = 0; a < 4; ++a) {
         dq[4 * a] += old[a].x;
@@ -2034,7 +1968,190 @@ __device__ __forceinline__ void units_body(const Params& p, unsigned char* smem,
       }
     }
 #pragma unroll
-    for (int a = 0; a < 4; ++a) dst[64 * a] = make_float4(dq[4 * a], dq[4 * a + 1], dq[4 * a + 2], dq[4 * a + 3]);
+    for (int a = 0; a < 4; ++a) dst0[(int64_t)s * (D / 8) * 64 + 64 * a] = make_float4(dq[4 * a], dq[4 * a + 1], dq[4 * a + 2], dq[4 * a + 3]);
+  };
+  // lane's addresses of dQ's operands: K^T (the last term apart: an offset has 16 bits), dS of an even and an odd group of 16 keys; + 8: the second four keys of a half
+  uint32_t k_at[2], k_last[2], ds_at[2][2], k_rows = R::KL + wave * (32 * X::RB);
+  if constexpr (R::TERMS) {
+    const uint32_t L = lane & 15, gq = lane >> 4, r = 4 * (gq >> 1) + (L >> 2), k0 = r * X::RB + (((2 * (gq & 1) + ((L & 3) >> 1)) ^ X::swz(r)) << 4) + 8 * (L & 1);
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      k_at[h] = R::KL + (k0 ^ (uint32_t)(db << 6) ^ (uint32_t)(32 * h)) + 8 * h * X::RB;
+      k_last[h] = k_at[h] + 2 * R::K_TERM;
+#pragma unroll
+      for (int e = 0; e < 2; ++e) ds_at[e][h] = R::DS + (r + 8 * h) * 64 + (((4 * (gq & 1) + (L & 3)) ^ ((4 * e + (gq >> 1) + 2 * h) & 7)) << 3);
+    }
+  }
+  auto tr_pair = [&](const uint32_t lo, const uint32_t hi) __attribute__((always_inline)) {
+    const u32x2_t a = __builtin_bit_cast(u32x2_t, __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4_t*)lo));
+    const u32x2_t b = __builtin_bit_cast(u32x2_t, __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4_t*)hi));
+    return __builtin_shufflevector(a, b, 0, 1, 2, 3);
+  };
+  auto publish = [&] {
+    stats_out();
+    wait_copies<0>();
+    __syncthreads();
+  };
+  rows_in(t.s0, 0);
+  rows_in(t.s0, 1);
+  stats_in(t.s0);
+  publish();
+  for (int32_t s = t.s0; s < t.s1; ++s) {
+    // one stage: S, dP with P, dV with dS, dK
+    const int32_t base = 32 * s, rel = r_key - base - 4 * hh;
+    const bool mask = base < r_key_max;   // (wave-uniform)
+    f32x16 sv[2], dp[2];
+    GnP<bf16_t, 3> pr, ds;
+    GnStat st_lse, st_delta;
+    auto terms = [&](const GnP<bf16_t, 3>& v, const int u, const int k) __attribute__((always_inline)) { return u32x4_t{v.w[k][4 * u], v.w[k][4 * u + 1], v.w[k][4 * u + 2], v.w[k][4 * u + 3]}; };
+    auto load = [&](const int i, const int k) __attribute__((always_inline)) {
+      return i < X::NJ ? ad.row_frag(i, k * F::TERM) : i < 2 * X::NJ ? ad.row_frag(i - X::NJ, F::V + k * F::TERM)
+           : i < 2 * X::NJ + 2 * X::DB ? ad.tr_frag(i - 2 * X::NJ, F::V + k * F::TERM) : ad.tr_frag(i - 2 * X::NJ - 2 * X::DB, k * F::TERM);
+    };
+    auto use = [&](const int i, const u32x4_t (&f)[3]) __attribute__((always_inline)) {
+      constexpr int NJ = X::NJ, NV = 2 * X::DB;
+      constexpr bool AHEAD = D == 128;   // (at head dim 64 there are no registers for it, and another workgroup on the compute unit)
+      if (AHEAD && i == NJ - 1) st_lse.fetch(st, hh, 0);
+      if (AHEAD && i == 2 * NJ - 1) st_delta.fetch(st + 64, hh, 0);
+      if (i < NJ) {
+        gn_mma_terms(f, kf[i][0], kf[i][1], kf[i][2], sv[1], sv[0]);
+      } else if (i < 2 * NJ) {   // dP, and P
+        const int j = i - NJ;
+        gn_mma_terms(f, vf[j][0], vf[j][1], vf[j][2], dp[1], dp[0]);
+#pragma unroll
+        for (int x = j * (16 / NJ); x < (j + 1) * (16 / NJ); ++x) {
+          const int row = 8 * (x >> 2) + (x & 3);
+          float v = __builtin_amdgcn_exp2f(__builtin_fmaf(sv[0][x] + sv[1][x], c, -(AHEAD ? st_lse.at(st, hh, x) : st[row + 4 * hh])));
+          if (mask && row < rel) v = 0.f;
+          sv[0][x] = v;
+        }
+#pragma unroll
+        for (int x = j * (16 / NJ); x < (j + 1) * (16 / NJ); x += 2) pr.set2(x, sv[0][x], sv[0][x + 1]);
+      } else if (i < 2 * NJ + NV) {   // dV, and dS
+        const int v = i - 2 * NJ, u = v / X::DB;
+        gn_mma_terms(f, terms(pr, u, 0), terms(pr, u, 1), terms(pr, u, 2), dv[v % X::DB], dv[v % X::DB]);
+#pragma unroll
+        for (int x = v * (16 / NV); x < (v + 1) * (16 / NV); ++x) {
+          const int row = 8 * (x >> 2) + (x & 3);
+          sv[0][x] = sv[0][x] * (dp[0][x] + dp[1][x] - (AHEAD ? st_delta.at(st + 64, hh, x) : st[64 + row + 4 * hh]));   // (dP, Delta and dS: lifted twice)
+          if (!R::TERMS) ds_out[row * (R::DS_ROW / 4)] = sv[0][x];
+        }
+#pragma unroll
+        for (int x = v * (16 / NV); x < (v + 1) * (16 / NV); x += 2) ds.set2(x, sv[0][x], sv[0][x + 1]);
+      } else {
+        const int v = i - 2 * NJ - NV, u = v / X::DB;
+        gn_mma_terms(f, terms(ds, u, 0), terms(ds, u, 1), terms(ds, u, 2), dk[v % X::DB], dk[v % X::DB]);
+      }
+    };
+    if constexpr (R::TERMS) {
+      constexpr int NJ = X::NJ, NV = 2 * X::DB;   // (keys past the list: all of their rows are masked)
+      // S: K's rows come from LDS as well, 24 reads of a stage for 96 registers (in registers, a third of them was spilled)
+      gn_zero(sv);
+      u32x4_t fq[2][3], fr[2][3];
+      auto rows = [&](const int j) __attribute__((always_inline)) {
+        const uint32_t at = ad.row[j] + k_rows, last = at + 2 * R::K_TERM;
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+          fq[j & 1][k] = load(j, k);
+          fr[j & 1][k] = *(__attribute__((address_space(3))) const u32x4_t*)(k < 2 ? at + k * R::K_TERM : last);
+        }
+      };
+      rows(0);
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) {
+        if (j + 1 < NJ) {
+          rows(j + 1);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+        if (j == NJ - 1) st_lse.fetch(st, hh, 0);
+        gn_mma_terms(fq[j & 1], fr[j & 1][0], fr[j & 1][1], fr[j & 1][2], sv[1], sv[0]);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      gn_zero(dp);
+      wait_copies<0>();
+      __syncthreads();   // dO of the stage is in LDS
+      gn_terms_pipeline<NJ + NV>([&](const int i, const int k) __attribute__((always_inline)) { return load(NJ + i, k); },
+                                 [&](const int i, const u32x4_t (&f)[3]) __attribute__((always_inline)) { use(NJ + i, f); });
+      __syncthreads();   // nobody reads dO any more, whose place takes dS
+      unsigned char* const out = smem + R::DS + kq * 64;
+#pragma unroll
+      for (int k = 0; k < 3; ++k)
+#pragma unroll
+        for (int a = 0; a < 4; ++a) *reinterpret_cast<uint2*>(out + k * R::DS_TERM + (((2 * a + hh) ^ ((kq >> 2) & 7)) << 3)) = make_uint2(ds.w[k][2 * a], ds.w[k][2 * a + 1]);
+      gn_terms_pipeline<NV>([&](const int i, const int k) __attribute__((always_inline)) { return load(2 * NJ + NV + i, k); },
+                            [&](const int i, const u32x4_t (&f)[3]) __attribute__((always_inline)) { use(2 * NJ + NV + i, f); });
+      __syncthreads();   // dS is in LDS; nobody reads Q any more, whose place takes the next stage's
+      if (s + 1 < t.s1) {
+        rows_in(s + 1, 0);
+        stats_in(s + 1);
+      }
+      if constexpr (ADD) fetch(s);   // (on their way during the product)
+      f32x16 dq[2];
+      gn_zero(dq);
+      u32x4_t fk[2][3], fd[2][3];
+      auto get = [&](const int n) __attribute__((always_inline)) {   // keys 16 n .. + 15
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+          const uint32_t o = 16 * n * X::RB + (k < 2 ? k * R::K_TERM : 0);
+          fk[n & 1][k] = tr_pair((k < 2 ? k_at[0] : k_last[0]) + o, (k < 2 ? k_at[1] : k_last[1]) + o);
+          fd[n & 1][k] = tr_pair(ds_at[n & 1][0] + (k * R::DS_TERM + 1024 * n), ds_at[n & 1][1] + (k * R::DS_TERM + 1024 * n));
+        }
+      };
+      get(0);
+#pragma unroll
+      for (int n = 0; n < GN_ROWS / 16; ++n) {
+        if (n + 1 < GN_ROWS / 16) {
+          get(n + 1);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+        gn_mma_terms(fk[n & 1], fd[n & 1][0], fd[n & 1][1], fd[n & 1][2], dq[1], dq[0]);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      stats_out();
+      wait_copies<0>();
+#pragma unroll
+      for (int x = 0; x < 16; ++x) dq[0][x] += dq[1][x];
+      dq_out(s, dq[0]);
+      __syncthreads();   // Q and the statistics of the next stage are in LDS; nobody reads dS any more, whose place takes its dO
+      if (s + 1 < t.s1) rows_in(s + 1, 1);
+      continue;
+    }
+    if (active) {
+      gn_zero(sv);
+      gn_zero(dp);
+      gn_terms_pipeline<2 * X::NJ + 4 * X::DB>(load, use);
+    }
+    __syncthreads();   // dS is in LDS; nobody reads the stage any more, whose place takes the next
+    if (s + 1 < t.s1) {
+      rows_in(s + 1, 0);
+      rows_in(s + 1, 1);
+      stats_in(s + 1);
+    }
+    f32x16 dq;
+#pragma unroll
+    for (int x = 0; x < 16; ++x) dq[x] = 0.f;
+    // operands of four instructions: dS of keys 8 n + 4 hh .. + 3 of the part (row lq), K of the same keys (dim 32 db + lq)
+    const uint32_t at_ds = R::DS + lq * R::DS_ROW + 16 * hh + kp * R::KEYS * 4, at_k = R::KL + (kp * R::KEYS + 4 * hh) * R::KL_ROW + (32 * db + lq) * 4;
+    u32x4_t fd[2];
+    float fk[2][4];
+    auto get = [&](const int n) __attribute__((always_inline)) {
+      fd[n & 1] = *reinterpret_cast<const u32x4_t*>(smem + (at_ds + 32 * n));
+#pragma unroll
+      for (int x = 0; x < 4; ++x) fk[n & 1][x] = *reinterpret_cast<const float*>(smem + (at_k + (8 * n + x) * R::KL_ROW));
+    };
+    get(0);
+#pragma unroll
+    for (int n = 0; n < R::KEYS / 8; ++n) {
+      if (n + 1 < R::KEYS / 8) {
+        get(n + 1);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+#pragma unroll
+      for (int x = 0; x < 4; ++x) dq = __builtin_amdgcn_mfma_f32_32x32x2f32(fk[n & 1][x], __uint_as_float(fd[n & 1][x]), dq, 0, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    if constexpr (ADD) fetch(s);   // (the other workgroup computes meanwhile, and there are no registers to have them on their way during the product)
+    dq_out(s, dq);
     publish();
   }
   if (active) {

@@ -495,6 +495,50 @@ __global__ __launch_bounds__(SELECT_THREADS) void select_small_kernel(Params p, 
   if (tid == 0) sel_count[g] = k_eff + p.m;
 }
 
+// Steps S1b and S3 in one kernel, from page means, for few rows to pool: a group of D / 4 lanes per page, as page_score_cached_kernel has, whose
+// lanes walk the chains of their own four dims, eight rows in flight, while the means are under way.
+constexpr int POOLED_PAGES = 2;   // pages per group
+template <int D>
+__global__ __launch_bounds__(256) void page_score_pooled_kernel(Params p, const float* __restrict__ A, float r, const float* __restrict__ means, float* __restrict__ scores) {
+  constexpr int VEC = 4, LPR = D / VEC, GROUPS = 256 / LPR;
+  const int g = blockIdx.y, lr = threadIdx.x % LPR, n = p.m * p.G;
+  const int64_t l0 = (int64_t)blockIdx.x * (GROUPS * POOLED_PAGES) + threadIdx.x / LPR;
+  float4 kb[POOLED_PAGES];
+#pragma unroll
+  for (int u = 0; u < POOLED_PAGES; ++u) {
+    const int64_t l = l0 + u * GROUPS;
+    kb[u] = load_floats(means + ((l < p.n_past ? l : 0) * p.Hkv + g) * D + lr * VEC);
+  }
+  const float* at = A + lr * VEC;
+  auto read = [&](const int k0, float4 (&v)[8]) __attribute__((always_inline)) {
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const int k = k0 + u < n ? k0 + u : n - 1, tau = (int)div_g(p, (uint32_t)k), h = g * p.G + (k - tau * p.G);
+      v[u] = load_floats(at + ((int64_t)h * p.m + tau) * D);
+    }
+  };
+  float4 q = make_float4(0.f, 0.f, 0.f, 0.f);
+  for (int k0 = 0; k0 < n; k0 += 8) {
+    float4 v[8];
+    read(k0, v);
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const bool row = k0 + u < n;
+      q.x = row ? __fadd_rn(q.x, v[u].x) : q.x;
+      q.y = row ? __fadd_rn(q.y, v[u].y) : q.y;
+      q.z = row ? __fadd_rn(q.z, v[u].z) : q.z;
+      q.w = row ? __fadd_rn(q.w, v[u].w) : q.w;
+    }
+  }
+  q = make_float4(__fmul_rn(q.x, r), __fmul_rn(q.y, r), __fmul_rn(q.z, r), __fmul_rn(q.w, r));
+#pragma unroll
+  for (int u = 0; u < POOLED_PAGES; ++u) {
+    const int64_t l = l0 + u * GROUPS;
+    const float s = score_tree<D>(q, kb[u]);
+    if (l < p.n_past && lr == 0) scores[(int64_t)g * p.n_past + l] = s;
+  }
+}
+
 static hipError_t launch_topk_select(const Params& p, const float* scores, int32_t top_k, int32_t* sel, int32_t* sel_count,
                                      int per_qp, hipStream_t st) {
   const dim3 grid((unsigned)(per_qp ? p.Hkv * p.m : p.Hkv)), block(SELECT_THREADS);
@@ -528,6 +572,10 @@ static hipError_t launch_topk_select(const Params& p, const float* scores, int32
 // are there in 6 us more, where the kernel that walks a page per group of lanes takes 18 for 512 x 2 pages of 128 tokens (13 of 64; pages
 // of 16 and 32 are short chains there).  From MEANS_TILES tiles on that one has groups enough to be as fast.
 constexpr int64_t MEANS_TILES = 2048;
+// Few rows to pool: pooled by the scoring kernel itself, in every group of lanes anew, which saves a launch.  The selection before and so, us: 7 rows, 4092
+// (head, page) pairs 12.4 and 10.4; 16 rows, 8184 pairs 13.3 and 11.7, 32760 pairs 16.7 and 16.6; 28 rows, 4092 pairs 12.4 and 12.4, 64000 pairs 26.1 and 33.5; 56
+// rows, 4092 pairs 13.0 and 14.2.
+constexpr int64_t POOLED_ROWS = 16, POOLED_TILES = 32768;
 struct ScoreLayout {
   size_t off_qbar, off_scores, off_means, bytes;   // (means at the end: a call works without them)
   bool means, small;   // scores from means; one workgroup per KV head for what follows them
@@ -573,6 +621,13 @@ static hipError_t launch_scoring(const Params& p, int32_t top_k, int32_t* sel, i
     select_small_kernel<D><<<dim3(p.Hkv), dim3(SELECT_THREADS), final_lds_bytes(p, D, SMALL_ROWS * D), st>>>(p, A, r, kbar_cache ? kbar_cache : means, scores, top_k, sel,
                                                                                          sel_count);
     return hipGetLastError();
+  }
+  if (L.means && p.n_past > 0 && (int64_t)p.m * p.G <= POOLED_ROWS && p.n_past * p.Hkv <= POOLED_TILES) {
+    ProfScope prof_("page_score_pooled", st);
+    constexpr int PAGES = POOLED_PAGES * 256 / (D / 4);   // of a workgroup
+    page_score_pooled_kernel<D><<<dim3((unsigned)((p.n_past + PAGES - 1) / PAGES), p.Hkv), dim3(256), 0, st>>>(p, A, r, kbar_cache ? kbar_cache : means, scores);
+    if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
+    return launch_topk_select(p, scores, top_k, sel, sel_count, 0, st);
   }
   {
     static DeviceOnce lds_once;   // (16 dims of 1024 rows and the rows read ahead: 66 KiB)

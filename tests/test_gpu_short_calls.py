@@ -82,6 +82,25 @@ def test_selection_of_a_short_history_with_many_pooled_rows():
     assert np.array_equal(sel.cpu().numpy(), osel)
 
 
+# Up to 16 rows to pool and 32768 (head, page) pairs the scoring kernel pools them itself, eight rows at a time, 16 or 32 pages per workgroup
+@pytest.mark.parametrize("Hq,Hkv,D,m,n_past", [(2, 2, 128, 1, 209), (8, 1, 128, 1, 207), (9, 1, 64, 1, 225), (14, 2, 128, 1, 1023), (28, 4, 64, 2, 223), (8, 1, 64, 2, 32768),
+                                               (16, 2, 128, 2, 208), (17, 1, 128, 1, 208), (3, 1, 64, 6, 193), (4, 1, 64, 1, 32769)])
+def test_selection_pools_few_rows_where_it_scores(Hq, Hkv, D, m, n_past):
+    g = torch.Generator(device="cuda").manual_seed(440 + n_past)
+    P, n = 16, n_past + m
+    kbar = torch.randn((n, Hkv, D), generator=g, device="cuda")
+    q = torch.randn((m * P, Hq, D), generator=g, device="cuda")
+    desc = api.make_desc(q, torch.empty((1, Hkv, P, D), device="cuda").expand(n, Hkv, P, D), n * P, 0.125)
+    desc.pool_page_stride = Hkv * P * D
+    scores = torch.empty((Hkv, n_past), dtype=torch.float32, device="cuda")
+    ran = ("page_score_pooled", "qpool_final") if m * Hq // Hkv <= 16 and n_past * Hkv <= 32768 else ("qpool_final", "page_score_pooled")
+    with pu.kernels_ran(ran[:1], absent=ran[1:]):
+        sel, cnt = api.page_score_topk_cached(desc, q, kbar, 37, scores_out=scores)
+    osel, ocnt, oscores = orc.page_score_topk_cached(orc.Shape(Hq, Hkv, D, P, m * P, n * P, 0.125), q.cpu().numpy(), kbar.cpu().numpy(), 37)
+    assert np.array_equal(scores.cpu().numpy().view(np.uint32), oscores.view(np.uint32))
+    assert np.array_equal(sel.cpu().numpy(), osel) and np.array_equal(cnt.cpu().numpy(), ocnt)
+
+
 # No history: the lists hold the chunk's own pages, whichever kernels would have scored a past.  Pages of 16 and 32 tokens with more
 # than 192 rows to pool, and (128 tokens) query sums too large for the built-in scratch.
 @pytest.mark.parametrize("Hq,Hkv,D,P,m", [(14, 2, 64, 16, 32), (28, 4, 64, 32, 28), (32, 1, 64, 16, 6), (28, 4, 128, 128, 293)])

@@ -635,7 +635,7 @@ template <typename T, int D> __device__ __forceinline__ bool gn_add_rows(float (
   }
   return __all(D == 64 ? acc[0] != acc[0] : acc[0] != acc[0] && acc[D / 64 - 1] != acc[D / 64 - 1]);
 }
-// O of one row (ref: its largest logit, times log2 e; scale: 1 / the sum of its probabilities), or dQ (ref: LSE times log2 e)
+// O of one row (ref: what its exponentials are relative to, times log2 e; scale: 1 / the sum of its probabilities), or dQ (ref: LSE times log2 e)
 template <typename T, int D, bool DQ>
 __device__ __forceinline__ void gn_redo_row(const Params& p, int g, int i, int h, int lp, int lane, float ref, float scale, float delta) {
   const int lid = list_id(p, g, i);
@@ -658,12 +658,13 @@ __device__ __forceinline__ void gn_redo_row(const Params& p, int g, int i, int h
       off = (int64_t)p.page_table[list_at(p, lid, t >> lp)] * p.pool_page_stride + (int64_t)g * p.pool_head_stride + (int64_t)(t & (p.P - 1)) * p.pool_tok_stride;
       w = __builtin_amdgcn_exp2f(__builtin_fmaf(gn_row_dot<T, D>(q, (const T*)p.k_pool + off), c, -ref));
       if (DQ) w *= gn_row_dot<T, D>(d_o, (const T*)p.v_pool + off) - delta;
+      else w *= scale;   // (before the sum: the largest w may be 2^8, times a value near the edge)
     }
     if (gn_add_rows<T, D>(acc, (const T*)(DQ ? p.k_pool : p.v_pool), w, off, V - t0 < 64 ? V - t0 : 64, lane)) break;
   }
   T* dst = (T*)(DQ ? p.d_q : p.o) + roff;
 #pragma unroll
-  for (int k = 0; k < D / 64; ++k) Elem<T>::store(dst + 64 * k + lane, acc[k] * scale);
+  for (int k = 0; k < D / 64; ++k) Elem<T>::store(dst + 64 * k + lane, DQ || V == 0 ? acc[k] * scale : acc[k]);
 }
 // dK (or dV) of token t of owned page e into the pool
 template <typename T, typename TG, int D> __device__ __forceinline__ void gn_redo_key(const Params& p, int g, int32_t e, int32_t t, bool is_dk, int lp, int lane) {
@@ -705,9 +706,23 @@ template <typename T, typename TG, int D> __device__ __forceinline__ void gn_red
 // Where a running maximum starts: finite, also as a logit, because a row that has seen nothing yet forms (-inf - m) c; below
 // every product that a float holds as a logit of this scale.
 __device__ __forceinline__ float gn_lowest(const Params& p) { return -1e38f / fmaxf(1.f, p.sm_scale); }
-// log-sum-exp of a row: m the largest product, l the sum of exponentials relative to it
+// The reference of a row's exponentials after products of at most mx (and m_run before).  It stays where it is until a product lies GN_LAZY binary orders above it: O, which
+// follows every change, is then rescaled once or twice instead of in most tiles (64 instructions in front of each product at head dim 128).  fp32 probabilities of up
+// to 2^8 keep as many bits as those of up to 1; bf16 ones are exact where they are 1, and keep the largest product (fwd_generic_kernel).
+constexpr float GN_LAZY = 8.f;
+__device__ __forceinline__ float gn_reference(float m_run, float mx, float c) {
+  const float m = fmaxf(m_run, half_max(mx));
+  return (m - m_run) * fabsf(c) > GN_LAZY ? m : m_run;
+}
+// log-sum-exp of a row: m the reference, l the sum of exponentials relative to it
 __device__ __forceinline__ float gn_lse(const Params& p, float m, float l) {
-  return __builtin_fmaf(m, p.sm_scale, __builtin_amdgcn_logf(l) * 0.6931471805599453f);
+  // As a sum of m's share, the exponent of l times ln 2 (in two parts, the first of which times an exponent is exact) and the logarithm of l's fraction, rounded
+  // once: the backward's probabilities have the relative error that LSE has as a difference.  Rounded at every step (28 / 4 heads fp32, 20 pages, x 1e-7): LSE 0.47, dK
+  // 7.6, dV 7.7.
+  const float f = __builtin_amdgcn_frexp_mantf(l), e = (float)__builtin_amdgcn_frexp_expf(l);
+  const float a = m * p.sm_scale, b = e * 0.693145751953125f, s = a + b, t = s - a;
+  const float low = ((a - (s - t)) + (b - t)) + __builtin_fmaf(m, p.sm_scale, -a);
+  return s + (low + __builtin_fmaf(e, 1.4286068203e-6f, __builtin_amdgcn_logf(f) * 0.6931471805599453f));
 }
 
 // n_split > 1: O (not normalised) and {running maximum of the products, sum} of every row go to part[split][block] and
@@ -780,7 +795,7 @@ __global__ __launch_bounds__(256 * KH, 2) void fwd_generic_kernel(Params p, int3
       for (int u = k; u < (REFS == 1 ? Y::U : k + 1); ++u)
 #pragma unroll
         for (int x = u == k; x < 16; ++x) mx = fmaxf(mx, s[u][x]);
-      const float m_new = fmaxf(m_run, half_max(mx));
+      const float m_new = X::BF && NT == 1 ? fmaxf(m_run, half_max(mx)) : gn_reference(m_run, mx, c);
       alpha[k] = __builtin_amdgcn_exp2f((m_run - m_new) * c);
       mc[k] = m_new * c;
       m_run = m_new;
@@ -1148,7 +1163,7 @@ __global__ __launch_bounds__(256, 2) void fwd_terms_kernel(Params p, int32_t til
     float mx = s[1][0];
 #pragma unroll
     for (int x = 1; x < 16; ++x) mx = fmaxf(mx, s[1][x]);
-    const float m_new = fmaxf(m_run, half_max(mx)), alpha = __builtin_amdgcn_exp2f((m_run - m_new) * c), mc = m_new * c;
+    const float m_new = gn_reference(m_run, mx, c), alpha = __builtin_amdgcn_exp2f((m_run - m_new) * c), mc = m_new * c;
     m_run = m_new;
     if (__any(alpha != 1.f)) {
 #pragma unroll

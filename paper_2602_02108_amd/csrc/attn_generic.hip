@@ -25,8 +25,8 @@
 // bf16 the exposed vector work and LDS latency of one or two waves per SIMD; short calls the number
 // of workgroups, which is why the streamed side is cut into splits whose partial sums a second
 // kernel combines in a fixed order.  Measured against one wave per query row (per key in dK / dV)
-// with plain fp32 arithmetic: 28 / 4 heads fp32, chunk 512, 16 + 4 pages of 128: 41.5 -> 0.43 ms
-// (59 GFLOP); 8 / 2 heads bf16, chunk 1088, 24 + 17 pages of 64: 18.4 -> 0.15 ms (32 GFLOP).
+// with plain fp32 arithmetic: 28 / 4 heads fp32, chunk 512, 16 + 4 pages of 128: 41.5 -> 0.41 ms
+// (59 GFLOP); 8 / 2 heads bf16, chunk 1088, 24 + 17 pages of 64: 18.4 -> 0.11 ms (32 GFLOP).
 #include "mfma_common.h"
 #include "launch.h"
 #include "partials.h"
@@ -708,7 +708,8 @@ template <typename T, typename TG, int D> __device__ __forceinline__ void gn_red
 __device__ __forceinline__ float gn_lowest(const Params& p) { return -1e38f / fmaxf(1.f, p.sm_scale); }
 // The reference of a row's exponentials after products of at most mx (and m_run before).  It stays where it is until a product lies GN_LAZY binary orders above it: O, which
 // follows every change, is then rescaled once or twice instead of in most tiles (64 instructions in front of each product at head dim 128).  fp32 probabilities of up
-// to 2^8 keep as many bits as those of up to 1; bf16 ones are exact where they are 1, and keep the largest product (fwd_generic_kernel).
+// to 2^8 keep as many bits as those of up to 1; bf16 ones are exact where they are 1, and keep the largest product (fwd_generic_kernel).  fp32,
+// 28 / 4 heads, 20 pages of 128: pass 420.9 -> 414.3 us; 8 / 2 heads bf16, 41 pages of 64: 112.3 -> 111.7.
 constexpr float GN_LAZY = 8.f;
 __device__ __forceinline__ float gn_reference(float m_run, float mx, float c) {
   const float m = fmaxf(m_run, half_max(mx));
@@ -1829,8 +1830,8 @@ template <int D> struct GnU {
   typedef Gn<bf16_t, D> X;
   typedef GnF3<D> F;
   // Head dim 128: dQ in terms, too.  A stage: Q0 Q1 Q2 dO0 dO1 dO2 and {lse2, delta}; K0 K1 K2 of the unit as [key][dim] in the order of a row tile.  The terms of dS take the
-  // place of dO once dV is done, as [key][row] with word w (four rows) of key k at w ^ (k / 4 mod 8): what 64 lanes write or read at once falls on all banks.
-  // Against dQ on the fp32 pipe, 28 / 4 heads, chunk 512, 20 pages of 128, whole pass: 426 -> 421 us (192 matrix cycles in the place of 512, but three barriers more
+  // place of dO once dV is done, as [key][row] with word w (four rows) of key k at w ^ (k / 4 mod 8): 56 of about 15000
+  // cycles of a stage are bank conflicts.  Against dQ on the fp32 pipe, 28 / 4 heads, chunk 512, 20 pages of 128, whole pass: 426 -> 421 us (192 matrix cycles in the place of 512, but three barriers more
   // a stage); dQ against 64 bits 7.9e-7 -> 7.4e-7.
   // Head dim 64 (two workgroups per compute unit have 80 KiB each): dQ on the fp32 pipe.  dS as [row][key], rows 544 bytes apart (both the dwords of 32 keys x 2 rows that
   // a store moves and the 16 bytes x 64 rows of a read fall on all banks); K as [key][dim]

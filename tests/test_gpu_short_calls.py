@@ -1,5 +1,7 @@
 """Short calls: selection of a short history in one workgroup (edges of its range, more pooled rows than one pass
 holds), append for every element type / head dim, and workspaces sized for another length of the history."""
+import math
+
 import numpy as np
 import pytest
 import torch
@@ -245,3 +247,28 @@ def test_lists_may_be_a_view_that_ends_before_its_stride(dtype, D, P):
     ref = pu.oracle_fwd_bwd(w, pu.host_inputs(x), sel.cpu().numpy(), cnt.cpu().numpy())
     for name, got, want in (("O", o, ref["o"]), ("dQ", dq, ref["dq"]), ("dK", x["dk_pool"], ref["dk_pool"]), ("dV", x["dv_pool"], ref["dv_pool"])):
         pu.check(name, pu.f32(got), want, dtype)
+
+
+# Logits that rise by `rise` binary orders per 32 keys: references that stay where they are (up to 2^8 above), move now and then, and move in every tile.  fp32: a logit
+# of L is off by 2^-24 L a few times over, and so is the logarithm of what it weighs; bf16: O is rounded to 8 bits.
+@pytest.mark.parametrize("dtype,D,P,C,n", [("f32", 64, 16, 64, 12), ("f32", 128, 128, 512, 20), ("bf16", 64, 16, 64, 24), ("bf16", 128, 64, 128, 9)])
+@pytest.mark.parametrize("rise", [0.4, 3.0, 9.0])
+def test_forward_of_rising_logits(dtype, D, P, C, n, rise):
+    w = Workload("rising", 28 if C == 512 else 2, 4 if C == 512 else 1, D, P, C, P * n, None, dtype, "f32", 1.0, seed=700 + n)
+    x = make_inputs(w, "cuda")
+    q, kp, vp, table = x["q"], x["k_pool"], x["v_pool"], x["page_table"].long()
+    t = torch.arange(w.N, device="cuda").reshape(n, 1, P, 1)
+    kp[table] = (kp[table].double() * 0.02 + t * (rise * math.log(2) / 32 / D)).to(kp.dtype)
+    q.copy_(1 + 0.05 * q.float())
+    o, lse = api.paged_attn_fwd(api.make_desc(q, kp, w.N, 1.0), q, kp, vp, table.int(), None, None)
+    K, V = (p[table].double().transpose(0, 1).reshape(w.Hkv, w.N, D).repeat_interleave(w.G, 0) for p in (kp, vp))
+    s = torch.matmul(q.double().transpose(0, 1), K.transpose(1, 2).contiguous())
+    s = s.masked_fill(torch.arange(w.N, device="cuda") > torch.arange(w.N - C, w.N, device="cuda")[:, None], -math.inf)
+    want, top = torch.matmul(torch.softmax(s, 2), V).transpose(0, 1), s[s > -math.inf].abs().max().item()
+    line = 4 * 2.0**-24 * max(top, 4.0) if dtype == "f32" else 2.0**-8
+    assert ((o.double() - want).norm() / want.norm()).item() < line
+    assert (lse.double() - torch.logsumexp(s, 2)).abs().max().item() < 4 * 2.0**-24 * max(top, 8.0)
+    if dtype == "f32":   # the same average of values whose unnormalised sum is out of range
+        vp.fill_(2.5e38)
+        o, _ = api.paged_attn_fwd(api.make_desc(q, kp, w.N, 1.0), q, kp, vp, table.int(), None, None)
+        assert (o.double() / 2.5e38 - 1).abs().max().item() < 4 * 2.0**-24 * max(top, 4.0) + w.N * 2.0**-24

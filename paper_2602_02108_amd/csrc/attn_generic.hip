@@ -1817,7 +1817,7 @@ __global__ __launch_bounds__(256, (D == 128 || sizeof(T) == 4 ? 1 : 2)) void dkv
 }
 
 // The whole backward of fp32 tensors: five products per pair instead of the seven of two kernels, as products of three bf16 terms (at head dim
-// 64 all but dQ's).  A unit is 128 list tokens, 32 per wave: their K and V stay in registers (as terms), the rows of the head stream through
+// 64 all but dQ's).  A unit is 128 list tokens, 32 per wave: their K and V stay in registers as terms (K at head dim 128 in LDS), the rows of the head stream through
 // LDS in stages of 32, as terms too (row_terms_kernel).  dS goes through LDS, dQ of a stage is left as one fp32 partial sum per unit.  One wave per
 // SIMD (512 registers); the vector work of a product runs between the matrix instructions of the next one.
 // The stages of all units of a KV head, one unit after the other, are cut into equal ranges, one per workgroup: whatever the list and the chunk, every
@@ -1831,7 +1831,7 @@ template <int D> struct GnU {
   typedef GnF3<D> F;
   // Head dim 128: dQ in terms, too.  A stage: Q0 Q1 Q2 dO0 dO1 dO2 and {lse2, delta}; K0 K1 K2 of the unit as [key][dim] in the order of a row tile.  The terms of dS take the
   // place of dO once dV is done, as [key][row] with word w (four rows) of key k at w ^ (k / 4 mod 8): 56 of about 15000
-  // cycles of a stage are bank conflicts.  Against dQ on the fp32 pipe, 28 / 4 heads, chunk 512, 20 pages of 128, whole pass: 426 -> 421 us (192 matrix cycles in the place of 512, but three barriers more
+  // cycles of a stage are bank conflicts.  Against dQ on the fp32 pipe, 28 / 4 heads, chunk 512, 20 pages of 128, whole pass: 426 -> 421 us (192 matrix cycles in the place of 512, but two barriers more
   // a stage); dQ against 64 bits 7.9e-7 -> 7.4e-7.
   // Head dim 64 (two workgroups per compute unit have 80 KiB each): dQ on the fp32 pipe.  dS as [row][key], rows 544 bytes apart (both the dwords of 32 keys x 2 rows that
   // a store moves and the 16 bytes x 64 rows of a read fall on all banks); K as [key][dim]

@@ -2431,10 +2431,7 @@ static GnPair gn_pair(const Params& p, bool bf, int32_t max_len) {
   GnPair best = {{0, 1}, {0, 1}, 1e30f};
   const int32_t per = gn_slots(p, bf) / p.Hkv;   // workgroups of a KV head
   const int32_t wq = gn_tiles(p.C, p.G, p.P, p.m, p.qp), wk = gn_key_units(p, max_len);
-  // bf16 pages of 128: up to half of the workgroups' number.  Beyond that it would be faster, too (28 / 4 heads, 512 rows, 10 pages 60 us against 70; 4 / 4, 1024 rows, 30
-  // pages 56 against 67), but its dS is formed from P before P is rounded, that of the kernels for many rows and keys after: calls of this size agree to 2e-3 with
-  // the same lists given per query page, which have those kernels only.
-  if (p.qp || wk < 1 || (bf && gn_one_term(p) ? 2 : 1) * (wq + wk) > per) return best;
+  if (p.qp || wk < 1 || wq + wk > per) return best;
   const float tile = gn_tile_us(p, bf);
   const int32_t whole = gn_key_share(p, bf, max_len, wk).most;
   for (int32_t e = 1, most = 0; e <= 16 && e <= whole; ++e) {   // more parts per unit, until the rows have too few workgroups
@@ -2465,8 +2462,28 @@ static float gn_two_us(const Params& p, bool bf, int32_t max_len) {
   const GnShare k = gn_key_share(p, bf, max_len, gn_head_slots(p, bf));
   return (rows + (float)(((int64_t)k.n * p.Hkv + slots - 1) / slots) * gn_key_us(p, bf, k.most)) * (bf && p.D == 64 ? 1.2f : 1.f) + 16.f;
 }
+// bf16 pages of 128: the one launch forms dS from P before P is rounded, the kernels for many rows and keys after: dK against 64 bits 1.66e-3 and 2.35e-3.  Up to half of the workgroups' number
+// the faster of the two; beyond that the calls that one launch serves with as many splits of every unit as of any other, and of every row tile (estimated as such), and no others: calls of that
+// size agree to 2e-3 with the same lists given per query page, which have the other kernels only.  (It would be faster there, too: 28 / 4 heads, 512 rows, 10 pages 60 us against 70; 4 / 4, 1024
+// rows, 30 pages 56 against 67.)  two: the others' estimate.
+static bool gn_pair_even(const Params& p, int32_t max_len, float two) {
+  const int32_t wq = gn_tiles(p.C, p.G, p.P, p.m, 0) * p.Hkv, wk = gn_key_units(p, max_len) * p.Hkv;
+  if (2 * wq > 256 || 2 * wk > 256) return false;
+  const float nt = (max_len - 0.5f * p.m) * p.P / 64.f, stages = (float)p.C * p.G / 64.f;
+  for (int32_t nk = 1; nk <= 16 && (nk == 1 || nk <= stages) && wk * nk + wq <= 256; ++nk) {
+    int32_t ns = (256 - wk * nk) / wq;
+    ns = ns > 32 ? 32 : ns > nt ? (nt < 1.f ? 1 : (int32_t)nt) : ns;
+    const float tq = (nt / ns > 1.f ? nt / ns : 1.f) * 1.2f + 6.f, tk = (stages / nk > 1.f ? stages / nk : 1.f) * 2.6f + 8.f;
+    if ((tq > tk ? tq : tk) + (wk * nk * 2.f + wq * ns) * p.D * 2.56e-4f < two) return true;
+  }
+  return false;
+}
 static bool gn_takes_pair(const Params& p, bool bf, int32_t max_len, const GnPair& pair) {
-  return pair.us < 1e29f && pair.us < gn_two_us(p, bf, max_len);
+  if (pair.us > 1e29f) return false;
+  const float two = gn_two_us(p, bf, max_len);
+  if (!bf || !gn_one_term(p)) return pair.us < two;
+  const bool half = 2 * (gn_tiles(p.C, p.G, p.P, p.m, 0) + gn_key_units(p, max_len)) <= gn_slots(p, bf) / p.Hkv;
+  return (half && pair.us < two) || gn_pair_even(p, max_len, two - 7.f);   // (7 us of the estimate are what the launches after those of its constants took)
 }
 
 // The backward by units (bwd_units_kernel): units per launch, ranges per KV head -- as many workgroups as run at once --, and the estimate of its time in

@@ -88,7 +88,7 @@ template <int N> __device__ __forceinline__ void gn_zero(f32x16 (&v)[N]) {
 // it, 2^-27 rms -- and these 192 cycles where v_mfma_f32_32x32x2 takes 512.
 // Values below 2^-109 keep fewer bits: the smallest bf16 is 2^-133.  V, dO and dS, on which the results depend linearly, are therefore lifted by 2^16 first (GN_LIFT;
 // what overflows -- products of dO and V of 2^96 -- is not finite and formed anew from fp32 products): they keep their bits down to the smallest normal fp32 value.  Not lifted are Q and K,
-// whose products are the argument of an exponential, and P, whose largest value in a row is not small: a product is off by 2^-134 times the other value.
+// whose products are the argument of an exponential (dQ of small keys: GnU), and P, whose largest value in a row is not small: a product is off by 2^-134 times the other value.
 // S is formed this way on every route.  What the backward makes of S and LSE then has the errors that the forward's S has, whichever
 // kernels the two passes take; those of different products do not cancel in dQ.  Against 64 bits, 2 / 1 heads of 128, logits of 3 times
 // the spread, chunk 1024, 40 pages: dQ both passes with fp32 products 1.95e-6, one of them in terms 4.5e-6 (forward) and 4.1e-6 (backward), S in
@@ -1837,8 +1837,12 @@ template <int D> struct GnU {
   // a store moves and the 16 bytes x 64 rows of a read fall on all banks); K as [key][dim]
   static constexpr bool TERMS = D == 128;
   static constexpr int STAT = F::TILE, DS = TERMS ? F::V : STAT + 2 * 64 * 4, DS_ROW = GN_ROWS * 4 + 32, DS_TERM = GN_ROWS * 64;
-  static constexpr int KL = TERMS ? STAT + 2 * 64 * 4 : DS + 32 * DS_ROW, KL_ROW = D * 4 + 16, K_TERM = GN_ROWS * X::RB, LDS = KL + (TERMS ? 3 * K_TERM : GN_ROWS * KL_ROW);
+  static constexpr int KL = TERMS ? STAT + 2 * 64 * 4 : DS + 32 * DS_ROW, KL_ROW = D * 4 + 16, K_TERM = GN_ROWS * X::RB, OFF = KL + 3 * K_TERM, LDS = TERMS ? OFF + GN_ROWS * 8 : KL + GN_ROWS * KL_ROW;
   static_assert(!TERMS || 3 * DS_TERM <= F::V, "dS in the place of dO");
+  // A value of K below 2^-110 (and not 0) is not the sum of three terms.  dQ is linear in K: units that hold such a value form it on the fp32 pipe from K in the pool (OFF: where its rows lie there), dS
+  // being the sum of its terms.  4 us a stage more; with such a value in every unit the pass above takes 403 us instead of 272.  (Lifted as V is, K would take S along, whose products may be as
+  // large as a float holds.)
+  static constexpr uint32_t TINY = 17u << 24;   // bits of 2^-110, without the sign
   // dQ of a stage: wave w takes dim block w % DB and the keys of part w / DB; a partial sum per part
   static constexpr int PARTS = 4 / X::DB, KEYS = GN_ROWS / PARTS, WGS = D == 64 ? 2 : 1;   // workgroups per compute unit
 };
@@ -1911,10 +1915,16 @@ __device__ __forceinline__ void units_body(const Params& p, unsigned char* smem,
       raw[0][j][e] = reinterpret_cast<const u32x4_t*>((const float*)p.k_pool + koff + 16 * j + 8 * hh)[e];
       raw[1][j][e] = reinterpret_cast<const u32x4_t*>((const float*)p.v_pool + koff + 16 * j + 8 * hh)[e];
     }
+  uint32_t least = ~0u;   // |K| of this lane, in bits, but for zeros
 #pragma unroll
   for (int j = 0; j < X::NJ; ++j) {
     gn_load_terms<false>(raw[0][j][0], raw[0][j][1], kf[j]);
     if constexpr (R::TERMS) {
+#pragma unroll
+      for (int x = 0; x < 8; ++x) {
+        const uint32_t v = 2 * raw[0][j][x >> 2][x & 3] - 1;
+        least = v < least ? v : least;
+      }
 #pragma unroll
       for (int k = 0; k < 3; ++k) *reinterpret_cast<u32x4_t*>(smem + R::KL + k * R::K_TERM + kq * X::RB + (((2 * j + hh) ^ X::swz(kq & 15)) << 4)) = kf[j][k];
     } else {
@@ -1965,6 +1975,10 @@ __device__ __forceinline__ void units_body(const Params& p, unsigned char* smem,
       st[64 + tid] = st_d;
     }
   };
+  if constexpr (R::TERMS) {
+    if (hh == 0) reinterpret_cast<int64_t*>(smem + R::OFF)[kq] = koff;
+    st[96 + wave] = __any(least < R::TINY - 1) ? 1.f : 0.f;
+  }
   // dQ of a stage: dim block db, the keys of part kp; dims 32 db + 8 a + 4 hh .. + 3 are group 4 db + a of the block
   const int db = wave % X::DB, kp = wave / X::DB;
   float4* const dst0 = reinterpret_cast<float4*>(dq_part) + (((int64_t)(t.set * R::PARTS + kp) * p.Hkv + t.g) * (4 * gn_tiles(p.C, p.G, p.P, p.m, 0))) * (D / 8) * 64 + lane + 256 * db;
@@ -2012,6 +2026,8 @@ __device__ __forceinline__ void units_body(const Params& p, unsigned char* smem,
   rows_in(t.s0, 1);
   stats_in(t.s0);
   publish();
+  bool tiny = false;
+  if constexpr (R::TERMS) tiny = __builtin_amdgcn_readfirstlane(__any(st[96 + (lane & 3)] != 0.f));
   for (int32_t s = t.s0; s < t.s1; ++s) {
     // one stage: S, dP with P, dV with dS, dK
     const int32_t base = 32 * s, rel = r_key - base - 4 * hh;
@@ -2113,15 +2129,34 @@ __device__ __forceinline__ void units_body(const Params& p, unsigned char* smem,
           fd[n & 1][k] = tr_pair(ds_at[n & 1][0] + (k * R::DS_TERM + 1024 * n), ds_at[n & 1][1] + (k * R::DS_TERM + 1024 * n));
         }
       };
-      get(0);
+      if (tiny) {   // (operands of an instruction: K of key n + 4 hh + x, dim 32 db + lq; dS of the key, row lq)
+        const float* const k_dim = (const float*)p.k_pool + 32 * db + lq;
+#pragma unroll 1
+        for (int n = 0; n < GN_ROWS; n += 16) {
+          float k_val[8], d_val[8];
 #pragma unroll
-      for (int n = 0; n < GN_ROWS / 16; ++n) {
-        if (n + 1 < GN_ROWS / 16) {
-          get(n + 1);
+          for (int x = 0; x < 8; ++x) {
+            const int key = n + 8 * (x >> 2) + 4 * hh + (x & 3);
+            k_val[x] = k_dim[reinterpret_cast<const int64_t*>(smem + R::OFF)[key]];
+            const unsigned char* d = smem + R::DS + key * 64 + (((lq >> 2) ^ ((key >> 2) & 7)) << 3) + 2 * (lq & 3);
+            d_val[x] = 0.f;
+#pragma unroll
+            for (int k = 2; k >= 0; --k) d_val[x] += bf16_to_f32(*reinterpret_cast<const bf16_t*>(d + k * R::DS_TERM));
+          }
+#pragma unroll
+          for (int x = 0; x < 8; ++x) dq[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(k_val[x], d_val[x], dq[0], 0, 0, 0);
+        }
+      } else {
+        get(0);
+#pragma unroll
+        for (int n = 0; n < GN_ROWS / 16; ++n) {
+          if (n + 1 < GN_ROWS / 16) {
+            get(n + 1);
+            __builtin_amdgcn_sched_barrier(0);
+          }
+          gn_mma_terms(fk[n & 1], fd[n & 1][0], fd[n & 1][1], fd[n & 1][2], dq[1], dq[0]);
           __builtin_amdgcn_sched_barrier(0);
         }
-        gn_mma_terms(fk[n & 1], fd[n & 1][0], fd[n & 1][1], fd[n & 1][2], dq[1], dq[0]);
-        __builtin_amdgcn_sched_barrier(0);
       }
       stats_out();
       wait_copies<0>();

@@ -159,6 +159,26 @@ def test_tensors_of_any_size_keep_their_bits(w, v_exp, do_exp, fwd, bwd):
         assert all(errs[n] <= (2e-5 if v_exp == 105 else LIMITS[fwd][n]) for n in NAMES), errs
 
 
+# dQ is linear in K as well: small keys, keys whose upper dims are small (dQ of each half by itself), and keys of the usual size among which every 128 have one small value.
+@pytest.mark.parametrize("fwd,bwd", [("asked", "asked"), ("none", "least")])
+@pytest.mark.parametrize("k_exp,do_exp,what", [(-108, 0, "all"), (-117, 30, "all"), (-125, 40, "all"), (-117, 30, "half"), (-125, 30, "few")])
+@pytest.mark.parametrize("w", [SHAPES[0].with_(C=384, N=128 * 24), SHAPES[1].with_(N=32 * 130)], ids=lambda w: w.name)
+def test_small_keys_keep_their_bits(w, k_exp, do_exp, what, fwd, bwd):
+    x = make_inputs(w, "cuda")
+    x["d_o"].mul_(2. ** do_exp)
+    half = w.D // 2 if what == "half" else w.D
+    if what == "few":
+        x["k_pool"][:, :, 3, 5] *= 2. ** k_exp
+    else:
+        x["k_pool"][..., w.D - half:] *= 2. ** k_exp
+    got, want = run(w, x, fwd, bwd), exact(w, x)
+    errs = {n: rel(a, b) for n, a, b in zip(NAMES, got, want)}
+    for n, d in (("dq lower", slice(0, half)), ("dq upper", slice(w.D - half, w.D))):
+        errs[n] = rel(got[2][..., d], want[2][..., d])
+    print(w.name, k_exp, what, fwd, bwd, {n: f"{e:.2e}" for n, e in errs.items()}, flush=True)
+    assert all(e <= LIMITS[fwd][n[:2] if n[0] == "d" else n] for n, e in errs.items()), errs
+
+
 # Lists that the passes walk in several launches: the backward because of the room that its workspace leaves for the partial sums of dQ (`units` units of 128
 # keys of all heads a launch), the forward where the terms of the listed keys pass 512 MiB.  A last launch that is not full, units of the chunk's own pages
 # in it, values that are not finite in a key of an early launch that all rows see, and in one of a later launch that few see.

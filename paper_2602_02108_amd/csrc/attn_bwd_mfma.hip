@@ -297,13 +297,13 @@ size_t bwd_mfma_min_bytes(const Params& p, int32_t max_list_len) {
 size_t bwd_mfma_workspace_bytes(const Params& p, int32_t max_list_len) {
   const size_t rows = rows_take_generic(p, max_list_len, true) ? dq_generic_part_bytes(p, true, max_list_len) : 0, stats = stats_bytes(p);
   const size_t two = (rows > stats ? rows : stats) + bias_bytes(p) + dkv_partial_bytes(p, max_list_len, dkv_splits(p, max_list_len, true));
-  const size_t pair = bwd_takes_pair(p, true, max_list_len) ? bwd_pair_bytes(p, true, max_list_len) : 0;
+  const size_t pair = bwd_pair_bytes(p, true, max_list_len);
   return pair > two ? pair : two;
 }
 
 hipError_t launch_bwd_mfma(const Params& p, int32_t max_list_len, void* ws, size_t ws_bytes, hipStream_t st) {
   const bool overlap = dq_overlaps_o(p, true);
-  if (!overlap && bwd_takes_pair(p, true, max_list_len)) {
+  if (!overlap) {
     bool done = false;
     if (hipError_t e = launch_bwd_pair_bf16_128(p, max_list_len, ws, ws_bytes, st, &done); done || e != hipSuccess) return e;
   }

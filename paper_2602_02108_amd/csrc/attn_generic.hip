@@ -1259,6 +1259,12 @@ struct GnKeySteps {
     return s < all ? s : all - 1;
   }
   __host__ __device__ __forceinline__ int32_t operator()(int32_t u) const { return all - from(u); }
+  int32_t over(int32_t v, int32_t units) const {   // units with more than v steps (v >= 0): those up to the last key page that stage all - v comes after
+    if (v == 0) return units;
+    if (v >= all) return 0;
+    const int64_t j = ((int64_t)(all - v) * rows - 1) / PG, n = ((past + j) >> (7 - lp)) + 1;
+    return (int32_t)(n < units ? n : units);
+  }
 };
 struct GnRowSteps {
   int32_t G, rows, past, P, kt, lp;
@@ -1270,6 +1276,12 @@ struct GnRowSteps {
     const int64_t seen = ((int64_t)(past + (i >> lp)) << lp) + (i & (P - 1)) + 1;
     const int32_t n = (int32_t)((seen + kt - 1) / kt);
     return n > 1 ? n : 1;
+  }
+  int32_t over(int32_t v, int32_t tiles) const {   // row tiles with more than v steps: those whose last row lies r rows or more into the chunk
+    const int64_t r = ((int64_t)v * kt - (int64_t)past * P) * G;
+    if (v == 0 || r <= 0) return tiles;
+    const int64_t n = tiles - 1 - (r >> 7);   // (of all but the last, whose last row is rows - 1)
+    return (int32_t)((n > 0 ? n : 0) + (rows - 1 >= r));
   }
 };
 template <typename N> __host__ __device__ __forceinline__ int32_t gn_parts(const N& steps, const GnShare& w, int32_t u) { return (steps(u) + w.most - 1) / w.most; }
@@ -2423,22 +2435,27 @@ static GnPlan gn_plan(const Params& p, bool bf, int32_t max_len, bool dq, int32_
 static int32_t gn_key_units(const Params& p, int32_t max_len) {
   return (int32_t)(((int64_t)max_len * p.P + GN_ROWS - 1) / GN_ROWS);
 }
-// The parts of `units` row tiles or units of a KV head if none has more than `most` steps, and the least `most` with which they are `slots` workgroups or fewer (or the units
-// are more).  Steps fall or rise by the same amount from unit to unit past the first or last `even` ones, all alike: their sum is estimated, then counted.
-template <typename N> static int32_t gn_count(const N& steps, int32_t units, int32_t from, int32_t to, int32_t most) {   // (units outside from .. to - 1 are like the first)
-  int32_t n = (units - (to - from)) * ((steps(0) + most - 1) / most);
-  for (int32_t u = from; u < to; ++u) n += (steps(u) + most - 1) / most;
+// The parts of `units` row tiles or units of a KV head if none has more than `most` steps: those with more than none, `most`, 2 `most` .. steps.
+template <typename N> static int32_t gn_count(const N& steps, int32_t units, int32_t most) {
+  const int32_t first = steps(0), last = steps(units - 1), least = first < last ? first : last, greatest = first < last ? last : first;   // (from unit to unit they only fall, or only rise)
+  int32_t n = 0;
+  for (int32_t v = 0; v < greatest; v += most) n += v < least ? units : steps.over(v, units);
   return n;
 }
-template <typename N> static GnShare gn_share(const N& steps, int32_t units, int32_t from, int32_t to, int32_t slots) {
-  int32_t lo = 1, hi = steps(0) > steps(units - 1) ? steps(0) : steps(units - 1);   // (with hi every unit is one part)
-  if ((hi + 15) / 16 > lo) lo = (hi + 15) / 16;   // (at most 16 parts)
+// The least `most` with which they are `slots` workgroups or fewer, at most 16 of a unit (one each where the units are more).
+template <typename N> static GnShare gn_share(const N& steps, int32_t units, int32_t slots) {
+  const int32_t first = steps(0), last = steps(units - 1), least = first < last ? first : last, greatest = first < last ? last : first;
+  if (slots < units) return {units, greatest};
+  const int32_t each = slots / units, floor16 = (greatest + 15) / 16;
+  int32_t lo = (int32_t)(((int64_t)units * least + slots - 1) / slots), hi = (greatest + each - 1) / each;   // (hi: no unit has more parts than its share of the slots)
+  lo = lo < floor16 ? floor16 : lo;
+  hi = hi < lo ? lo : hi;
   while (lo < hi) {
     const int32_t mid = (lo + hi) / 2;
-    if (gn_count(steps, units, from, to, mid) <= slots) hi = mid;
+    if (gn_count(steps, units, mid) <= slots) hi = mid;
     else lo = mid + 1;
   }
-  return {gn_count(steps, units, from, to, lo), lo};
+  return {gn_count(steps, units, lo), lo};
 }
 // workgroups of the dK / dV and one-launch kernels that run at once
 static int32_t gn_slots(const Params& p, bool bf) { return bf && p.D == 64 ? 512 : 256; }   // (two workgroups per compute unit)
@@ -2448,14 +2465,14 @@ static bool gn_one_term(const Params& p) { return p.D == HD && p.P == TP; }   //
 static float gn_stage_us(const Params& p, bool bf) { return bf ? (gn_one_term(p) ? 2.1f : p.D == 128 ? 3.8f : 3.2f) : (p.D == 128 ? 10.f : 5.f); }
 static float gn_tile_us(const Params& p, bool bf) { return bf ? (gn_one_term(p) ? 1.3f : 2.f) : (p.D == 128 ? 7.f : 3.5f); }   // of KT keys x 128 rows in the one-launch backward
 static GnShare gn_key_share(const Params& p, bool bf, int32_t max_len, int32_t slots, int32_t most = 0) {   // most: the steps of a part, if given
-  const int32_t units = gn_key_units(p, max_len), lp = __builtin_ctz(p.P), own = (max_len - p.m) >> (7 - lp);   // (the first unit that holds a page of the chunk)
+  const int32_t units = gn_key_units(p, max_len);
   if (p.qp || units < 1) return {0, 1};
-  const GnKeySteps steps(p, lp, max_len, bf ? 64 : 32);
-  return most ? GnShare{gn_count(steps, units, own, units, most), most} : gn_share(steps, units, own, units, slots);
+  const GnKeySteps steps(p, __builtin_ctz(p.P), max_len, bf ? 64 : 32);
+  return most ? GnShare{gn_count(steps, units, most), most} : gn_share(steps, units, slots);
 }
 static GnShare gn_row_share(const Params& p, bool bf, int32_t max_len, int32_t slots) {
   const int32_t tiles = gn_tiles(p.C, p.G, p.P, p.m, 0);
-  return gn_share(GnRowSteps(p, __builtin_ctz(p.P), max_len, bf ? 64 : 32), tiles, 0, tiles, slots);
+  return gn_share(GnRowSteps(p, __builtin_ctz(p.P), max_len, bf ? 64 : 32), tiles, slots);
 }
 static float gn_key_us(const Params& p, bool bf, int32_t most) { return most * gn_stage_us(p, bf) + (bf ? 12.f : 8.f); }
 
@@ -2513,12 +2530,17 @@ static bool gn_pair_even(const Params& p, int32_t max_len, float two) {
   }
   return false;
 }
-static bool gn_takes_pair(const Params& p, bool bf, int32_t max_len, const GnPair& pair) {
-  if (pair.us > 1e29f) return false;
+// What a backward takes unless it goes by units: the one launch, if `one`.  A call is planned once (0.2 to 2 us; 100 to 180 where the parts of every row tile were counted).
+struct GnBackward { GnPair pair; bool one; float us; };
+static GnBackward gn_backward(const Params& p, bool bf, int32_t max_len) {
+  const GnPair pair = gn_pair(p, bf, max_len);
   const float two = gn_two_us(p, bf, max_len);
-  if (!bf || !gn_one_term(p)) return pair.us < two;
-  const bool half = 2 * (gn_tiles(p.C, p.G, p.P, p.m, 0) + gn_key_units(p, max_len)) <= gn_slots(p, bf) / p.Hkv;
-  return (half && pair.us < two) || gn_pair_even(p, max_len, two - 7.f);   // (7 us of the estimate are what the launches after those of its constants took)
+  bool one = pair.us < two;
+  if (bf && gn_one_term(p) && pair.us < 1e29f) {
+    const bool half = 2 * (gn_tiles(p.C, p.G, p.P, p.m, 0) + gn_key_units(p, max_len)) <= gn_slots(p, bf) / p.Hkv;
+    one = (half && one) || gn_pair_even(p, max_len, two - 7.f);   // (7 us of the estimate are what the launches after those of its constants took)
+  }
+  return {pair, one, one ? pair.us : two};
 }
 
 // The backward by units (bwd_units_kernel): units per launch, ranges per KV head -- as many workgroups as run at once --, and the estimate of its time in
@@ -2575,7 +2597,11 @@ static GnUnits gn_units(const Params& p, int32_t max_len, size_t room) {   // ro
   }
   return best;
 }
-static bool gn_takes_units(const Params& p, bool bf, int32_t max_len, const GnUnits& u);
+
+// Against the one-launch backward, or dQ and dK / dV one after the other (us: their estimate).  On the 35 shapes above what is chosen is the better one, or within 3 %: calls of 50 us
+// and less are up to 30 % faster without, from 60 us on this is 1.2 to 2.3 times as fast: 28 / 4 heads, chunk 512, 16 + 4 pages of 128: 576 -> 284 us, 300 pages
+// 7.7 -> 4.2 ms; 14 / 2 heads of 64 dims, chunk 1664, 14 + 13 pages of 128: 598 -> 323.
+static bool gn_takes_units(const GnUnits& u, float us) { return u.us < 1e29f && u.us < us; }
 
 static size_t gn_row_blocks(const Params& p) { return (size_t)gn_tiles(p.C, p.G, p.P, p.m, p.qp) * p.Hkv * 4; }
 // splits that fit `bytes` of partial results of `per` bytes each (at least 1: no partial results)
@@ -2626,7 +2652,7 @@ static GnF3Plan gn_f3_plan(const Params& p, bool bf, int32_t max_len, size_t roo
 static bool gn_takes_f3(const Params& p, bool bf, int32_t max_len, const GnF3Plan& f) {
   if (f.us > 1e29f) return false;
   const float other = gn_plan(p, bf, max_len, false).us;
-  return f.us < other || (f.us < 1.22f * other && gn_takes_units(p, bf, max_len, gn_units(p, max_len, SIZE_MAX)));
+  return f.us < other || (f.us < 1.22f * other && gn_takes_units(gn_units(p, max_len, SIZE_MAX), gn_backward(p, bf, max_len).us));
 }
 size_t fwd_generic_workspace_bytes(const Params& p, bool bf, int32_t max_len) {
   const int32_t s = gn_plan(p, bf, max_len, false).n;
@@ -2645,26 +2671,20 @@ static size_t gn_pair_bytes(const Params& p, int32_t max_len, const GnPair& t) {
   const bool whole = t.rows.n <= gn_tiles(p.C, p.G, p.P, p.m, 0);
   return gn_key_part_bytes(p, gn_key_units(p, max_len), t.kv) + (whole ? 0 : (size_t)p.Hkv * t.rows.n * GN_ROWS * p.D * 4);
 }
-bool bwd_takes_pair(const Params& p, bool bf, int32_t max_len) { return gn_takes_pair(p, bf, max_len, gn_pair(p, bf, max_len)); }
-size_t bwd_pair_bytes(const Params& p, bool bf, int32_t max_len) { return gn_pair_bytes(p, max_len, gn_pair(p, bf, max_len)); }
+size_t bwd_pair_bytes(const Params& p, bool bf, int32_t max_len) {
+  const GnBackward b = gn_backward(p, bf, max_len);
+  return b.one ? gn_pair_bytes(p, max_len, b.pair) : 0;
+}
 size_t bwd_generic_min_bytes(const Params& p) { return gn_up((size_t)p.Hq * p.C * sizeof(float)) + gn_key_part_bytes(p, 0, {0, 1}); }
 size_t bwd_generic_workspace_bytes(const Params& p, bool bf, int32_t max_len) {
-  const size_t delta = gn_up((size_t)p.Hq * p.C * sizeof(float)), pair = bwd_takes_pair(p, bf, max_len) ? bwd_pair_bytes(p, bf, max_len) : 0;
+  const GnBackward b = gn_backward(p, bf, max_len);
+  const size_t delta = gn_up((size_t)p.Hq * p.C * sizeof(float)), pair = b.one ? gn_pair_bytes(p, max_len, b.pair) : 0;
   const size_t two = delta + dq_generic_part_bytes(p, bf, max_len) + gn_key_part_bytes(p, gn_key_units(p, max_len), gn_key_share(p, bf, max_len, gn_head_slots(p, bf)));
   const size_t most = pair > two ? pair : two;
   if (bf || p.qp) return most;
   const GnUnits u = gn_units(p, max_len, SIZE_MAX);
-  const size_t units = gn_takes_units(p, bf, max_len, u) ? gn_units_bytes(p, gn_units_fit(p, max_len)) : 0;   // (not less for a longer list, whose launches may take fewer)
+  const size_t units = gn_takes_units(u, b.us) ? gn_units_bytes(p, gn_units_fit(p, max_len)) : 0;   // (not less for a longer list, whose launches may take fewer)
   return units > most ? units : most;
-}
-
-// Against the one-launch backward, or dQ and dK / dV one after the other.  On the 35 shapes above what is chosen is the better one, or within 3 %: calls of 50 us
-// and less are up to 30 % faster without, from 60 us on this is 1.2 to 2.3 times as fast: 28 / 4 heads, chunk 512, 16 + 4 pages of 128: 576 -> 284 us, 300 pages
-// 7.7 -> 4.2 ms; 14 / 2 heads of 64 dims, chunk 1664, 14 + 13 pages of 128: 598 -> 323.
-static bool gn_takes_units(const Params& p, bool bf, int32_t max_len, const GnUnits& u) {
-  if (u.us > 1e29f) return false;
-  const GnPair pair = gn_pair(p, bf, max_len);
-  return u.us < (gn_takes_pair(p, bf, max_len, pair) ? pair.us : gn_two_us(p, bf, max_len));
 }
 
 // terms of a probability (GnP) where a shape has no kernels of its own
@@ -2788,10 +2808,10 @@ hipError_t launch_bwd_finish(const Params& p, bool bf, int32_t dq_split, const f
 
 // The one-launch backward, if the shape takes it and the workspace has room (else *done stays false)
 template <typename T, typename TG, int D, int NT = GN_TERMS<T>>
-static hipError_t bwd_pair(Params p, int32_t max_len, void* ws, size_t ws_bytes, const char* name, hipStream_t st, bool* done) {
-  if (dq_overlaps_o(p, Gn<T, D>::BF)) return hipSuccess;   // (the keys' workgroups would read rows of O that the others have overwritten)
-  const GnPair t = gn_pair(p, Gn<T, D>::BF, max_len);
-  if (!gn_takes_pair(p, Gn<T, D>::BF, max_len, t) || gn_pair_bytes(p, max_len, t) > ws_bytes) return hipSuccess;
+static hipError_t bwd_pair(Params p, const GnBackward& b, int32_t max_len, void* ws, size_t ws_bytes, const char* name, hipStream_t st, bool* done) {
+  const GnPair& t = b.pair;
+  // (dQ over O: the keys' workgroups would read rows of O that the others have overwritten)
+  if (!b.one || dq_overlaps_o(p, Gn<T, D>::BF) || gn_pair_bytes(p, max_len, t) > ws_bytes) return hipSuccess;
   *done = true;
   ProfScope prof_(name, st);
   constexpr int LDS = GnKey<T, D>::LDS > GnRow<T, D, 1>::LDS ? GnKey<T, D>::LDS : GnRow<T, D, 1>::LDS;
@@ -2804,15 +2824,16 @@ static hipError_t bwd_pair(Params p, int32_t max_len, void* ws, size_t ws_bytes,
   return bwd_finish<T, TG, D>(p, 1, w.row_part, gn_key_units(p, max_len), 1, w.kv_part, true, st, 0, 0, t.rows, t.kv, max_len);
 }
 hipError_t launch_bwd_pair_bf16_128(const Params& p, int32_t max_len, void* ws, size_t ws_bytes, hipStream_t st, bool* done) {
-  return p.grad_is_bf16 ? bwd_pair<bf16_t, bf16_t, 128, 1>(p, max_len, ws, ws_bytes, "bwd_pair", st, done)
-                        : bwd_pair<bf16_t, float, 128, 1>(p, max_len, ws, ws_bytes, "bwd_pair", st, done);
+  const GnBackward b = gn_backward(p, true, max_len);
+  return p.grad_is_bf16 ? bwd_pair<bf16_t, bf16_t, 128, 1>(p, b, max_len, ws, ws_bytes, "bwd_pair", st, done)
+                        : bwd_pair<bf16_t, float, 128, 1>(p, b, max_len, ws, ws_bytes, "bwd_pair", st, done);
 }
 
 template <typename TG, int D>
-static hipError_t bwd_units(Params p, int32_t max_len, void* ws, size_t ws_bytes, const char* name, hipStream_t st, bool* done) {
+static hipError_t bwd_units(Params p, const GnBackward& b, int32_t max_len, void* ws, size_t ws_bytes, const char* name, hipStream_t st, bool* done) {
   if (p.qp) return hipSuccess;
   const GnUnits t = gn_units(p, max_len, ws_bytes);
-  if (!gn_takes_units(p, false, max_len, t)) return hipSuccess;
+  if (!gn_takes_units(t, b.us)) return hipSuccess;
   *done = true;
   ProfScope prof_(name, st);
   static DeviceOnce once, once_add;
@@ -2846,9 +2867,10 @@ template <typename T, typename TG, int D>
 static hipError_t bwd_generic(Params p, int32_t max_len, void* ws, size_t ws_bytes, hipStream_t st) {
   const char* name = "attn_bwd_generic";
   bool done = false;
+  const GnBackward b = gn_backward(p, Gn<T, D>::BF, max_len);
   if constexpr (sizeof(T) == 4)
-    if (hipError_t e = bwd_units<TG, D>(p, max_len, ws, ws_bytes, name, st, &done); done || e != hipSuccess) return e;
-  if (hipError_t e = bwd_pair<T, TG, D>(p, max_len, ws, ws_bytes, name, st, &done); done || e != hipSuccess) return e;
+    if (hipError_t e = bwd_units<TG, D>(p, b, max_len, ws, ws_bytes, name, st, &done); done || e != hipSuccess) return e;
+  if (hipError_t e = bwd_pair<T, TG, D>(p, b, max_len, ws, ws_bytes, name, st, &done); done || e != hipSuccess) return e;
   ProfScope prof_(name, st);
   static DeviceOnce once_kv;
   if (hipError_t e = ensure_max_dynamic_lds(once_kv, (const void*)dkv_generic_kernel<T, TG, D, GN_TERMS<T>>, GnKey<T, D>::LDS); e != hipSuccess) return e;

@@ -319,3 +319,18 @@ def test_fp32_workspaces_grow_with_the_history_up_to_a_bound(heads, D, P, C):
         assert f >= 0.9 * most_f, (n, f, most_f)   # (fewer partial sums of O where a longer list needs fewer splits)
         assert f <= (513 << 20) + 32 * (rows + C * hq * 8) and b <= (820 << 20) + 3 * rows + 16384, (n, f, b)
         most_f, most_b = max(f, most_f), b
+
+
+def test_a_backward_is_planned_quickly():
+    """The plan of a backward looks at its row tiles in runs, not one by one: before each launch (and each size asked for) it is to cost
+    less than the launch does.  Sizes with the most row tiles per KV head that one launch takes: 100 us and more if each is counted."""
+    import time
+    for heads, D, P, C, N in [((28, 1), 64, 32, 1504, 1504 + 640), ((28, 1), 64, 64, 1088, 1088 + 2048), ((64, 1), 64, 64, 512, 512), ((14, 2), 64, 64, 1088, 1088 + 8192)]:
+        d = _good_desc(n_q_heads=heads[0], n_kv_heads=heads[1], head_dim=D, page_size=P, chunk_len=C, ctx_len=N, pool_page_stride=heads[1] * P * D, pool_head_stride=P * D,
+                       pool_tok_stride=D, q_tok_stride=heads[0] * D, q_head_stride=D, num_phys_pages=N // P)
+        times = []
+        for _ in range(200):
+            t = time.perf_counter()
+            assert api.workspace_bytes(d, -1, api.OP_ATTN_BWD) > 0
+            times.append(time.perf_counter() - t)
+        assert sorted(times)[100] < 30e-6, (heads, D, C, sorted(times)[100])

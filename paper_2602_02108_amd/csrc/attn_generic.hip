@@ -1284,33 +1284,52 @@ struct GnRowSteps {
     return (int32_t)((n > 0 ? n : 0) + (rows - 1 >= r));
   }
 };
-template <typename N> __host__ __device__ __forceinline__ int32_t gn_parts(const N& steps, const GnShare& w, int32_t u) { return (steps(u) + w.most - 1) / w.most; }
-// what workgroup b of KV head g does of `units` row tiles or units
-template <typename N> __device__ __forceinline__ GnPart gn_part(int32_t units, const GnShare& w, int32_t b, int g, int32_t Hkv, const N& steps) {
-  const int lane = threadIdx.x & 63;
-  int32_t u = 0, before = 0;
-  for (int32_t u0 = 0; u0 < units; u0 += 64) {
-    int32_t upto = u0 + lane < units ? gn_parts(steps, w, u0 + lane) : 0;
+template <typename N> __device__ __forceinline__ int32_t gn_parts(const N& steps, const GnShare& w, int32_t u) { return (int32_t)((uint32_t)(steps(u) + w.most - 1) / (uint32_t)w.most); }
+// Sums over the lanes before this one, and over all, of numbers up to 31 (a unit has at most 16 parts): five ballots.
+__device__ __forceinline__ int32_t gn_sum_before(int32_t v, int32_t& all) {
+  int32_t before = 0;
+  all = 0;
 #pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-      const int32_t v = __shfl_up(upto, o, 64);
-      if (lane >= o) upto += v;
-    }
-    const int past = __builtin_popcountll(__ballot(before + upto <= b));   // (of the 64; the last of all are never past)
-    u = u0 + past;
-    if (past > 0) before += __builtin_amdgcn_readlane(upto, past - 1);
-    if (past < 64) break;
+  for (int k = 0; k < 5; ++k) {
+    const uint64_t bits = __ballot((v >> k) & 1);
+    before += (int32_t)__builtin_amdgcn_mbcnt_hi((uint32_t)(bits >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)bits, 0)) << k;
+    all += __builtin_popcountll(bits) << k;
   }
-  const int32_t e = __builtin_amdgcn_readfirstlane(gn_parts(steps, w, u)), n = __builtin_amdgcn_readfirstlane(steps(u)), x = b - before;
-  return {u, (int32_t)((int64_t)n * x / e), (int32_t)((int64_t)n * (x + 1) / e), e == 1 ? -1 : b * Hkv + g, x == 0, x + 1 == e};
+  return before;
+}
+// What workgroup b of KV head g does of `units` row tiles or units.  (Where each is one part -- all long lists -- nothing is looked for.  With a scan by shuffles and divisions of 64 bits, in front of the
+// first load of every workgroup, one-launch backwards of 20 to 50 us took 0.5 us longer, and their finish kernels as much.)
+template <typename N> __device__ __forceinline__ GnPart gn_part(int32_t units, const GnShare& w, int32_t b, int g, int32_t Hkv, const N& steps) {
+  if (w.n == units) return {b, 0, steps(b), -1, true, true};
+  const int lane = threadIdx.x & 63;
+  int32_t u = 0, before = 0, n = 0, e = 1, x = 0;
+  for (int32_t u0 = 0; u0 < units; u0 += 64) {
+    const bool there = u0 + lane < units;
+    const int32_t mine = there ? gn_parts(steps, w, u0 + lane) : 0;
+    int32_t all;
+    const int32_t first = before + gn_sum_before(mine, all);
+    const uint64_t here = __ballot(first <= b && b < first + mine);
+    if (here) {
+      const int l = __builtin_ctzll(here);
+      u = u0 + l;
+      n = __builtin_amdgcn_readfirstlane(steps(u));
+      e = __builtin_amdgcn_readlane(mine, l);
+      x = b - __builtin_amdgcn_readlane(first, l);
+      break;
+    }
+    before += all;
+  }
+  return {u, (int32_t)((uint32_t)(n * x) / (uint32_t)e), (int32_t)((uint32_t)(n * (x + 1)) / (uint32_t)e), e == 1 ? -1 : b * Hkv + g, x == 0, x + 1 == e};
 }
 // {the first part of u, parts}
 template <typename N> __device__ __forceinline__ int2 gn_parts_of(const GnShare& w, int32_t u, const N& steps) {
-  int32_t before = 0;
-  for (int32_t v = threadIdx.x & 63; v < u; v += 64) before += gn_parts(steps, w, v);
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) before += __shfl_xor(before, o, 64);
-  return make_int2(__builtin_amdgcn_readfirstlane(before), __builtin_amdgcn_readfirstlane(gn_parts(steps, w, u)));
+  const int lane = threadIdx.x & 63;
+  int32_t before = 0, all;
+  for (int32_t u0 = 0; u0 < u; u0 += 64) {
+    gn_sum_before(u0 + lane < u ? gn_parts(steps, w, u0 + lane) : 0, all);
+    before += all;
+  }
+  return make_int2(before, __builtin_amdgcn_readfirstlane(gn_parts(steps, w, u)));
 }
 
 // ---- dQ -----------------------------------------------------------------------------------------

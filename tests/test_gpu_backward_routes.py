@@ -1,4 +1,4 @@
-"""Which kernels a backward takes, and what that does to its results: the one launch of bf16 pages of 128."""
+"""Which kernels a backward takes and how its work is shared out: the one launch of bf16 pages of 128, lists shorter than the plan assumes, workspaces with little room."""
 import pytest
 import torch
 
@@ -31,3 +31,31 @@ def test_one_launch_of_pages_of_128_keeps_dk(heads, m, n_past):
     errs = [rel(a, b) for a, b in zip(got, want)]
     print(heads, m, n_past, [f"{e:.2e}" for e in errs], flush=True)
     assert errs[0] < 5e-3 and errs[1] < 2e-3 and errs[2] < 5e-3
+
+
+# One list per KV head, shorter than its row and not equally long: the work is shared out for the longest one, so that parts of units and of row tiles lie past the end of a list (the first
+# head's is the chunk's own pages and one more).  With the room that is asked for (one launch), a third of it (dQ and dK / dV one after the other, with fewer parts) and the least (none).
+LISTS = [(14, 2, 128, 128, 256, 40, (3, 23), "bf16"), (8, 2, 128, 64, 192, 60, (4, 37), "bf16"), (6, 2, 64, 16, 112, 200, (8, 131), "bf16"), (12, 3, 64, 128, 128, 24, (2, 24, 9), "bf16"),
+         (4, 2, 64, 64, 192, 50, (4, 33), "f32"), (4, 1, 128, 16, 48, 150, (20,), "f32"), (6, 2, 128, 128, 128, 30, (2, 17), "f32")]
+
+
+# (Pages with kernels of their own need room for their slices: what is asked for.)
+@pytest.mark.parametrize("room,Hq,Hkv,D,P,C,stride,counts,dtype", [(room, *case) for case in LISTS for room in (("asked",) if case[:1] == (14,) else ("asked", "third", "least"))])
+def test_lists_shorter_than_their_rows(room, Hq, Hkv, D, P, C, stride, counts, dtype):
+    w = Workload("short", Hq, Hkv, D, P, C, (stride + 12) * P, None, dtype, "f32", D ** -0.5, extra_phys=2, seed=620 + stride)
+    x = make_inputs(w, "cuda")
+    g = torch.Generator().manual_seed(w.seed)
+    sel = torch.zeros((Hkv, stride), dtype=torch.int32)
+    for h, n in enumerate(counts):
+        past = torch.randperm(w.n_past, generator=g)[:n - w.m].sort().values
+        sel[h, :n] = torch.cat([past, torch.arange(w.n_past, w.n)]).int()
+    cnt = torch.tensor(counts, dtype=torch.int32)
+    desc = api.make_desc(x["q"], x["k_pool"], w.N, w.sm_scale)
+    args = (desc, x["q"], x["k_pool"], x["v_pool"], x["page_table"])
+    o, lse = api.paged_attn_fwd(*args, sel.cuda(), cnt.cuda())
+    asked, least = api.workspace_bytes(desc, stride - w.m, api.OP_ATTN_BWD), (Hq * C * 4 + 255) // 256 * 256
+    ws = torch.empty({"asked": asked, "third": least + (asked - least) // 3 // 256 * 256, "least": least}[room], dtype=torch.uint8, device="cuda")
+    dq = api.paged_attn_bwd(*args, o, lse, x["d_o"], x["dk_pool"], x["dv_pool"], sel.cuda(), cnt.cuda(), workspace=ws)
+    ref = pu.oracle_fwd_bwd(w, pu.host_inputs(x), sel.numpy(), cnt.numpy())
+    for name, got, want in (("O", o, ref["o"]), ("dQ", dq, ref["dq"]), ("dK", x["dk_pool"], ref["dk_pool"]), ("dV", x["dv_pool"], ref["dv_pool"])):
+        pu.check(name, pu.f32(got), want, dtype)

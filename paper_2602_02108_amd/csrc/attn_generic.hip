@@ -1285,7 +1285,7 @@ struct GnRowSteps {
   }
 };
 template <typename N> __device__ __forceinline__ int32_t gn_parts(const N& steps, const GnShare& w, int32_t u) { return (int32_t)((uint32_t)(steps(u) + w.most - 1) / (uint32_t)w.most); }
-// Sums over the lanes before this one, and over all, of numbers up to 31 (a unit has at most 16 parts): five ballots.
+// Sums over the lanes before this one, and over all, of numbers up to 31 (a unit has at most 16 parts, a row tile 31): five ballots.
 __device__ __forceinline__ int32_t gn_sum_before(int32_t v, int32_t& all) {
   int32_t before = 0;
   all = 0;
@@ -2461,13 +2461,13 @@ template <typename N> static int32_t gn_count(const N& steps, int32_t units, int
   for (int32_t v = 0; v < greatest; v += most) n += v < least ? units : steps.over(v, units);
   return n;
 }
-// The least `most` with which they are `slots` workgroups or fewer, at most 16 of a unit (one each where the units are more).
-template <typename N> static GnShare gn_share(const N& steps, int32_t units, int32_t slots) {
+// The least `most` with which they are `slots` workgroups or fewer, at most `parts` of a unit (one each where the units are more).
+template <typename N> static GnShare gn_share(const N& steps, int32_t units, int32_t slots, int32_t parts) {
   const int32_t first = steps(0), last = steps(units - 1), least = first < last ? first : last, greatest = first < last ? last : first;
   if (slots < units) return {units, greatest};
-  const int32_t each = slots / units, floor16 = (greatest + 15) / 16;
+  const int32_t each = slots / units, floor = (greatest + parts - 1) / parts;
   int32_t lo = (int32_t)(((int64_t)units * least + slots - 1) / slots), hi = (greatest + each - 1) / each;   // (hi: no unit has more parts than its share of the slots)
-  lo = lo < floor16 ? floor16 : lo;
+  lo = lo < floor ? floor : lo;
   hi = hi < lo ? lo : hi;
   while (lo < hi) {
     const int32_t mid = (lo + hi) / 2;
@@ -2487,34 +2487,64 @@ static GnShare gn_key_share(const Params& p, bool bf, int32_t max_len, int32_t s
   const int32_t units = gn_key_units(p, max_len);
   if (p.qp || units < 1) return {0, 1};
   const GnKeySteps steps(p, __builtin_ctz(p.P), max_len, bf ? 64 : 32);
-  return most ? GnShare{gn_count(steps, units, most), most} : gn_share(steps, units, slots);
+  return most ? GnShare{gn_count(steps, units, most), most} : gn_share(steps, units, slots, 16);
 }
-static GnShare gn_row_share(const Params& p, bool bf, int32_t max_len, int32_t slots) {
+constexpr int32_t GN_ROW_PARTS = 31;   // (what gn_sum_before holds)
+static GnShare gn_row_share(const Params& p, bool bf, int32_t max_len, int32_t slots, int32_t parts) {
   const int32_t tiles = gn_tiles(p.C, p.G, p.P, p.m, 0);
-  return gn_share(GnRowSteps(p, __builtin_ctz(p.P), max_len, bf ? 64 : 32), tiles, slots);
+  return gn_share(GnRowSteps(p, __builtin_ctz(p.P), max_len, bf ? 64 : 32), tiles, slots, parts);
 }
 static float gn_key_us(const Params& p, bool bf, int32_t most) { return most * gn_stage_us(p, bf) + (bf ? 12.f : 8.f); }
 
 // A backward in one launch (bwd_pair_kernel): the workgroups that run at once (256, or 512 at head dim 64 with bf16: two per
-// compute unit) are shared out so that keys and rows take the same time.  us: huge where there is no such launch.
+// compute unit) are shared out so that keys and rows take the same time.  us: the estimate that gn_backward goes by; huge where there is no such launch.
+// How the work is cut: the longest part of the keys takes keys + stage a step, that of the rows rows + tile a step, the finish kernel `launch`, a value of the partial sums `part` (written and read).
+// Fitted to 2 to 16 parts a unit, and as few steps a part of the rows as there is room for and more, of 830 calls.  What is chosen is 0.3 (fp32) to 2 % slower than the best on average.  By the constants of
+// `us`, with 16 parts of a row tile at most, bf16 calls of 15 to 130 us were 4.6 to 7 % slower, at most 36: 6 / 2 heads, 128 rows, 31 pages 33.3 us instead of 28.2, 8 / 8, 256 rows, 3 pages
+// 24.9 instead of 20.8.
 struct GnPair { GnShare kv, rows; float us; };
+struct GnPartUs { float keys, stage, rows, tile, launch, part; };
+static GnPartUs gn_part_us(const Params& p, bool bf) {
+  if (!bf) return p.D == 128 ? GnPartUs{9.8f, 7.8f, 10.1f, 5.3f, 7.2f, 1.24e-4f} : GnPartUs{7.3f, 4.34f, 7.9f, 2.87f, 3.3f, 2.29e-4f};
+  if (gn_one_term(p)) return {10.f, 2.23f, 9.8f, 1.19f, 1.5f, 1.66e-4f};
+  return p.D == 128 ? GnPartUs{11.4f, 3.35f, 9.5f, 1.85f, 0.f, 1.73e-4f} : GnPartUs{5.5f, 2.41f, 3.7f, 1.74f, 2.5f, 2.82e-4f};
+}
 static GnPair gn_pair(const Params& p, bool bf, int32_t max_len) {
   GnPair best = {{0, 1}, {0, 1}, 1e30f};
   const int32_t per = gn_slots(p, bf) / p.Hkv;   // workgroups of a KV head
   const int32_t wq = gn_tiles(p.C, p.G, p.P, p.m, p.qp), wk = gn_key_units(p, max_len);
   if (p.qp || wk < 1 || wq + wk > per) return best;
   const float tile = gn_tile_us(p, bf);
-  const int32_t whole = gn_key_share(p, bf, max_len, wk).most;
+  const GnPartUs t = gn_part_us(p, bf);
+  const GnRowSteps row_steps(p, __builtin_ctz(p.P), max_len, bf ? 64 : 32);
+  const int32_t whole = gn_key_share(p, bf, max_len, wk).most, whole_row = row_steps(wq - 1);
+  float least = 1e30f;
+  bool estimate = true;
   for (int32_t e = 1, most = 0; e <= 16 && e <= whole; ++e) {   // more parts per unit, until the rows have too few workgroups
     if ((whole + e - 1) / e == most) continue;
     most = (whole + e - 1) / e;
-    GnShare k = gn_key_share(p, bf, max_len, 0, most);
-    const GnShare q = k.n > per - wq ? GnShare{0, 1} : gn_row_share(p, bf, max_len, per - k.n);
-    if (q.n == 0) break;
-    const float tk = gn_key_us(p, bf, most), tq = q.most * tile + (bf ? 10.f : 6.f);
-    const float us = (tq > tk ? tq : tk) + p.Hkv * ((k.n > wk ? 2.f * k.n : 0.f) + (q.n > wq ? q.n : 0.f)) * p.D * 2.56e-4f;
-    if (us < best.us) best = {k, q, us};
-    if (tq > tk) break;
+    const GnShare k = gn_key_share(p, bf, max_len, 0, most);
+    if (k.n > per - wq) break;
+    const float k_parts = k.n > wk ? 2.f * k.n : 0.f;
+    if (estimate) {   // (until the rows take longer)
+      const GnShare q = gn_row_share(p, bf, max_len, per - k.n, 16);
+      const float tk = gn_key_us(p, bf, most), tq = q.most * tile + (bf ? 10.f : 6.f), us = (tq > tk ? tq : tk) + p.Hkv * (k_parts + (q.n > wq ? q.n : 0.f)) * p.D * 2.56e-4f;
+      if (us < best.us) best.us = us;
+      estimate = tq <= tk;
+    }
+    // the rows: as many parts as there is room for, or as few as take no longer than the keys, or around that
+    const GnShare q0 = gn_row_share(p, bf, max_len, per - k.n, GN_ROW_PARTS);
+    const float tk = t.keys + most * t.stage;
+    const int32_t even = (int32_t)((tk - t.rows) / t.tile);
+    for (int32_t x = 0; x < 5; ++x) {
+      const int32_t steps = x == 0 ? q0.most : x == 4 ? whole_row : even + x - 1;
+      if (x && (steps <= q0.most || steps > whole_row)) continue;
+      const GnShare q = x ? GnShare{gn_count(row_steps, wq, steps), steps} : q0;
+      const float tq = t.rows + q.most * t.tile, parts = p.Hkv * (k_parts + (q.n > wq ? q.n : 0.f));
+      const float cost = (tq > tk ? tq : tk) + (parts > 0.f ? t.launch : 0.f) + parts * p.D * t.part;
+      if (cost < least) least = cost, best.kv = k, best.rows = q;
+    }
+    if (!estimate && t.rows + q0.most * t.tile > tk) break;
   }
   return best;
 }

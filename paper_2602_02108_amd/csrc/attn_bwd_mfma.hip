@@ -297,7 +297,7 @@ size_t bwd_mfma_min_bytes(const Params& p, int32_t max_list_len) {
 size_t bwd_mfma_workspace_bytes(const Params& p, int32_t max_list_len) {
   const size_t rows = rows_take_generic(p, max_list_len, true) ? dq_generic_part_bytes(p, true, max_list_len) : 0, stats = stats_bytes(p);
   const size_t two = (rows > stats ? rows : stats) + bias_bytes(p) + dkv_partial_bytes(p, max_list_len, dkv_splits(p, max_list_len, true));
-  const size_t pair = bwd_pair_bytes(p, true, max_list_len);
+  const size_t pair = bwd_pair_room(p, true, max_list_len);
   return pair > two ? pair : two;
 }
 

@@ -2712,27 +2712,43 @@ size_t fwd_generic_workspace_bytes(const Params& p, bool bf, int32_t max_len) {
 }
 size_t dq_generic_part_bytes(const Params& p, bool bf, int32_t max_len) { return gn_row_part_bytes(p, gn_plan(p, bf, max_len, true).n); }
 // partial sums of the shares of keys, and of rows
+static size_t gn_key_slot_bytes(const Params& p) { return (size_t)2 * part_key_blocks(p) * 32 * p.D * 4; }
 static size_t gn_key_part_bytes(const Params& p, int32_t units, const GnShare& w) {   // (0: no more parts than units)
   const size_t slots = p.qp ? (size_t)p.Hkv * qp_max_pslots(p, p.sel_stride) : w.n <= units ? 0 : (size_t)p.Hkv * w.n;
-  return gn_up(slots * 2 * part_key_blocks(p) * 32 * p.D * 4);
+  return gn_up(slots * gn_key_slot_bytes(p));
+}
+// the parts of dK / dV in a kernel of their own that `room` has space for
+static GnShare gn_key_share_in(const Params& p, bool bf, int32_t max_len, size_t room) {
+  const size_t fit = room / (gn_key_slot_bytes(p) * p.Hkv);
+  const int32_t slots = gn_head_slots(p, bf);
+  return gn_key_share(p, bf, max_len, fit < (size_t)slots ? (int32_t)fit : slots);
 }
 static size_t gn_pair_bytes(const Params& p, int32_t max_len, const GnPair& t) {
   const bool whole = t.rows.n <= gn_tiles(p.C, p.G, p.P, p.m, 0);
   return gn_key_part_bytes(p, gn_key_units(p, max_len), t.kv) + (whole ? 0 : (size_t)p.Hkv * t.rows.n * GN_ROWS * p.D * 4);
 }
-size_t bwd_pair_bytes(const Params& p, bool bf, int32_t max_len) {
-  const GnBackward b = gn_backward(p, bf, max_len);
-  return b.one ? gn_pair_bytes(p, max_len, b.pair) : 0;
+// What those partial sums take at most for any list of max_len entries or fewer, which may have more parts than the longest: the workspace of a history that grows is asked for once (28 / 4 heads of 64 dims,
+// chunk 512, 64 + 16 pages of 32 in that of 284 + 16 pages, 14.7 MB without this: 158 us instead of 71; 6 / 2 heads of 128, chunk 128, 2K tokens in that of 8K 53 instead of 27).
+static size_t gn_key_room(const Params& p, bool bf, int32_t max_len) {
+  const int64_t units = gn_key_units(p, max_len), slots = gn_head_slots(p, bf);
+  if (p.qp || gn_key_units(p, p.m) >= slots) return gn_key_part_bytes(p, 0, {0, 1});
+  return gn_up((size_t)p.Hkv * (size_t)(16 * units < slots ? 16 * units : slots) * gn_key_slot_bytes(p));
 }
+static size_t gn_pair_room(const Params& p, bool bf, int32_t max_len) {
+  const int64_t per = gn_slots(p, bf) / p.Hkv, wq = gn_tiles(p.C, p.G, p.P, p.m, 0), units = gn_key_units(p, max_len);
+  if (p.qp || wq + gn_key_units(p, p.m) > per) return 0;
+  const int64_t kv = 16 * units < per - wq ? 16 * units : per - wq, rows = GN_ROW_PARTS * wq < per - kv ? GN_ROW_PARTS * wq : per - kv;
+  return gn_up((size_t)p.Hkv * kv * gn_key_slot_bytes(p)) + (size_t)p.Hkv * rows * GN_ROWS * p.D * 4;
+}
+size_t bwd_pair_room(const Params& p, bool bf, int32_t max_len) { return gn_pair_room(p, bf, max_len); }
 size_t bwd_generic_min_bytes(const Params& p) { return gn_up((size_t)p.Hq * p.C * sizeof(float)) + gn_key_part_bytes(p, 0, {0, 1}); }
 size_t bwd_generic_workspace_bytes(const Params& p, bool bf, int32_t max_len) {
-  const GnBackward b = gn_backward(p, bf, max_len);
-  const size_t delta = gn_up((size_t)p.Hq * p.C * sizeof(float)), pair = b.one ? gn_pair_bytes(p, max_len, b.pair) : 0;
-  const size_t two = delta + dq_generic_part_bytes(p, bf, max_len) + gn_key_part_bytes(p, gn_key_units(p, max_len), gn_key_share(p, bf, max_len, gn_head_slots(p, bf)));
+  const size_t delta = gn_up((size_t)p.Hq * p.C * sizeof(float)), pair = gn_pair_room(p, bf, max_len);
+  const size_t two = delta + dq_generic_part_bytes(p, bf, max_len) + gn_key_room(p, bf, max_len);
   const size_t most = pair > two ? pair : two;
   if (bf || p.qp) return most;
   const GnUnits u = gn_units(p, max_len, SIZE_MAX);
-  const size_t units = gn_takes_units(u, b.us) ? gn_units_bytes(p, gn_units_fit(p, max_len)) : 0;   // (not less for a longer list, whose launches may take fewer)
+  const size_t units = gn_takes_units(u, gn_backward(p, bf, max_len).us) ? gn_units_bytes(p, gn_units_fit(p, max_len)) : 0;   // (not less for a longer list, whose launches may take fewer)
   return units > most ? units : most;
 }
 
@@ -2923,14 +2939,13 @@ static hipError_t bwd_generic(Params p, int32_t max_len, void* ws, size_t ws_byt
   ProfScope prof_(name, st);
   static DeviceOnce once_kv;
   if (hipError_t e = ensure_max_dynamic_lds(once_kv, (const void*)dkv_generic_kernel<T, TG, D, GN_TERMS<T>>, GnKey<T, D>::LDS); e != hipSuccess) return e;
-  // [Delta][dK / dV slices][dQ partials]; a workspace without room for the slices of this call takes fewer
+  // [Delta][dK / dV parts][dQ partials]; with less room than the parts of this call need there are as many as fit
   unsigned char* at = (unsigned char*)ws;
   p.delta = (float*)at;
   at += gn_up((size_t)p.Hq * p.C * sizeof(float));
   size_t left = ws_bytes - gn_up((size_t)p.Hq * p.C * sizeof(float));
-  GnShares w = {gn_key_share(p, Gn<T, D>::BF, max_len, gn_head_slots(p, Gn<T, D>::BF)), {0, 1}, (float*)at, nullptr};
+  const GnShares w = {gn_key_share_in(p, Gn<T, D>::BF, max_len, left), {0, 1}, (float*)at, nullptr};
   const int32_t all = gn_key_units(p, max_len);
-  if (gn_key_part_bytes(p, all, w.kv) > left) w.kv = {all, INT32_MAX / 2};   // (a workgroup per unit)
   float* dq_part = (float*)(at + gn_key_part_bytes(p, all, w.kv));
   left -= gn_key_part_bytes(p, all, w.kv);
   const int32_t units = p.qp ? p.max_units : gn_key_units(p, max_len);

@@ -45,8 +45,8 @@ hipError_t launch_bwd_generic(const Params& p, bool is_bf16, int32_t max_len, vo
 // the same forward and dQ kernels for shapes with kernels of their own but too few rows to fill the chip with them
 bool rows_take_generic(const Params& p, int32_t max_len, bool dq);
 hipError_t launch_fwd_generic_bf16_128(const Params& p, int32_t max_len, void* ws, size_t ws_bytes, hipStream_t st);
-// dQ and dK / dV of a short call in one launch (*done: whether it was taken; 0 bytes if the shape does not take it)
-size_t bwd_pair_bytes(const Params& p, bool is_bf16, int32_t max_len);
+// dQ and dK / dV of a short call in one launch (*done: whether it was taken), and what it takes at most for lists of this length or less
+size_t bwd_pair_room(const Params& p, bool is_bf16, int32_t max_len);
 hipError_t launch_bwd_pair_bf16_128(const Params& p, int32_t max_len, void* ws, size_t ws_bytes, hipStream_t st, bool* done);
 size_t dq_generic_part_bytes(const Params& p, bool is_bf16, int32_t max_len);
 // (part_bytes: what the caller has for partial sums; fewer splits if it is less than dq_generic_part_bytes)

@@ -334,3 +334,18 @@ def test_a_backward_is_planned_quickly():
             assert api.workspace_bytes(d, -1, api.OP_ATTN_BWD) > 0
             times.append(time.perf_counter() - t)
         assert sorted(times)[100] < 30e-6, (heads, D, C, sorted(times)[100])
+
+
+# bf16 likewise: what is asked for a longer history has room for every division of a shorter one (one launch, or dQ and dK / dV one after the other); what may be less are splits of dQ by themselves.
+@pytest.mark.parametrize("heads,D,P,C", [((28, 4), 64, 32, 512), ((8, 2), 128, 64, 1088), ((6, 2), 128, 16, 128), ((8, 8), 64, 64, 128), ((28, 1), 64, 128, 1024)])
+def test_bf16_workspaces_do_not_fall_with_the_history(heads, D, P, C):
+    hq, hkv = heads
+    m, most = C // P, 0
+    for n in sorted({m + i for i in range(0, 300, 7)} | {m + int(300 * 1.25 ** i) for i in range(20)}):
+        if n > 65535:
+            break
+        d = api.AttnDesc(hq, hkv, D, P, C, api.BF16, api.F32, D ** -0.5, n * P, hkv * P * D, P * D, D, hq * D, D, n)
+        b = api.workspace_bytes(d, -1, api.OP_ATTN_BWD)
+        assert b >= 0.9 * most, (n, b, most)
+        assert b <= (34 << 20) + 32 * C * hq * D * 4 + C * hq * 4, (n, b)
+        most = max(most, b)

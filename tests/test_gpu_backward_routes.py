@@ -59,3 +59,22 @@ def test_lists_shorter_than_their_rows(room, Hq, Hkv, D, P, C, stride, counts, d
     ref = pu.oracle_fwd_bwd(w, pu.host_inputs(x), sel.numpy(), cnt.numpy())
     for name, got, want in (("O", o, ref["o"]), ("dQ", dq, ref["dq"]), ("dK", x["dk_pool"], ref["dk_pool"]), ("dV", x["dv_pool"], ref["dv_pool"])):
         pu.check(name, pu.f32(got), want, dtype)
+
+
+# A workspace asked for once, for the longest history: shorter ones are cut as they are in one of their own, so the results are the same bits.
+@pytest.mark.parametrize("Hq,Hkv,D,P,C,tokens,longest,dtype", [(28, 4, 64, 32, 512, 2048, 9088, "bf16"), (8, 2, 128, 64, 1088, 1472, 18112, "bf16"), (6, 2, 128, 16, 128, 2048, 8192, "bf16"),
+                                                                (28, 4, 64, 32, 512, 128, 9088, "bf16"), (8, 8, 64, 32, 128, 1024, 2048, "f32"), (28, 4, 128, 16, 16, 640, 38400, "bf16")])
+def test_a_workspace_of_the_longest_history_has_room_for_the_parts_of_shorter_ones(Hq, Hkv, D, P, C, tokens, longest, dtype):
+    w = Workload("room", Hq, Hkv, D, P, C, tokens + C, None, dtype, "f32", D ** -0.5, seed=640)
+    x = make_inputs(w, "cuda")
+    desc, last = (api.make_desc(x["q"], x["k_pool"], w.N, w.sm_scale) for _ in range(2))
+    last.ctx_len, last.num_phys_pages = longest + C, (longest + C) // P
+    args = (desc, x["q"], x["k_pool"], x["v_pool"], x["page_table"])
+    o, lse = api.paged_attn_fwd(*args)
+    out = []
+    for d in (desc, last):
+        x["dk_pool"].zero_()
+        x["dv_pool"].zero_()
+        ws = torch.empty(api.workspace_bytes(d, -1, api.OP_ATTN_BWD), dtype=torch.uint8, device="cuda")
+        out.append([t.clone() for t in (api.paged_attn_bwd(*args, o, lse, x["d_o"], x["dk_pool"], x["dv_pool"], workspace=ws), x["dk_pool"], x["dv_pool"])])
+    assert all(torch.equal(a, b) for a, b in zip(*out))

@@ -2073,18 +2073,17 @@ __device__ __forceinline__ void units_body(const Params& p, unsigned char* smem,
     };
     auto use = [&](const int i, const u32x4_t (&f)[3]) __attribute__((always_inline)) {
       constexpr int NJ = X::NJ, NV = 2 * X::DB;
-      constexpr bool AHEAD = D == 128;   // (at head dim 64 there are no registers for it, and another workgroup on the compute unit)
-      if (AHEAD && i == NJ - 1) st_lse.fetch(st, hh, 0);
-      if (AHEAD && i == 2 * NJ - 1) st_delta.fetch(st + 64, hh, 0);
-      if (i < NJ) {
-        gn_mma_terms(f, kf[i][0], kf[i][1], kf[i][2], sv[1], sv[0]);
+      // (statistics ahead of their use at head dim 128 only: at 64 there are no registers for it, and another workgroup on the compute unit)
+      if (R::TERMS && i == 2 * NJ - 1) st_delta.fetch(st + 64, hh, 0);
+      if (i < NJ) {   // (S at head dim 64: at 128 it is formed below)
+        if constexpr (!R::TERMS) gn_mma_terms(f, kf[i][0], kf[i][1], kf[i][2], sv[1], sv[0]);
       } else if (i < 2 * NJ) {   // dP, and P
         const int j = i - NJ;
         gn_mma_terms(f, vf[j][0], vf[j][1], vf[j][2], dp[1], dp[0]);
 #pragma unroll
         for (int x = j * (16 / NJ); x < (j + 1) * (16 / NJ); ++x) {
           const int row = 8 * (x >> 2) + (x & 3);
-          float v = __builtin_amdgcn_exp2f(__builtin_fmaf(sv[0][x] + sv[1][x], c, -(AHEAD ? st_lse.at(st, hh, x) : st[row + 4 * hh])));
+          float v = __builtin_amdgcn_exp2f(__builtin_fmaf(sv[0][x] + sv[1][x], c, -(R::TERMS ? st_lse.at(st, hh, x) : st[row + 4 * hh])));
           if (mask && row < rel) v = 0.f;
           sv[0][x] = v;
         }
@@ -2096,7 +2095,7 @@ __device__ __forceinline__ void units_body(const Params& p, unsigned char* smem,
 #pragma unroll
         for (int x = v * (16 / NV); x < (v + 1) * (16 / NV); ++x) {
           const int row = 8 * (x >> 2) + (x & 3);
-          sv[0][x] = sv[0][x] * (dp[0][x] + dp[1][x] - (AHEAD ? st_delta.at(st + 64, hh, x) : st[64 + row + 4 * hh]));   // (dP, Delta and dS: lifted twice)
+          sv[0][x] = sv[0][x] * (dp[0][x] + dp[1][x] - (R::TERMS ? st_delta.at(st + 64, hh, x) : st[64 + row + 4 * hh]));   // (dP, Delta and dS: lifted twice)
           if (!R::TERMS) ds_out[row * (R::DS_ROW / 4)] = sv[0][x];
         }
 #pragma unroll

@@ -2497,16 +2497,18 @@ static float gn_key_us(const Params& p, bool bf, int32_t most) { return most * g
 
 // A backward in one launch (bwd_pair_kernel): the workgroups that run at once (256, or 512 at head dim 64 with bf16: two per
 // compute unit) are shared out so that keys and rows take the same time.  us: the estimate that gn_backward goes by; huge where there is no such launch.
-// How the work is cut: the longest part of the keys takes keys + stage a step, that of the rows rows + tile a step, the finish kernel `launch`, a value of the partial sums `part` (written and read).
-// Fitted to 2 to 16 parts a unit, and as few steps a part of the rows as there is room for and more, of 830 calls.  What is chosen is 0.3 (fp32) to 2 % slower than the best on average.  By the constants of
-// `us`, with 16 parts of a row tile at most, bf16 calls of 15 to 130 us were 4.6 to 7 % slower, at most 36: 6 / 2 heads, 128 rows, 31 pages 33.3 us instead of 28.2, 8 / 8, 256 rows, 3 pages
-// 24.9 instead of 20.8.
+// How the work is cut: the longest part of the keys takes keys + stage a step, that of the rows rows + tile a step, these `crowd` longer a step where there are two workgroups on every compute unit; the
+// finish kernel takes `launch`, `each` for every part of the unit or row tile that has most, and `part` a value of the partial sums (written and read).  Fitted to 2 to 16 parts a unit, and to as few steps a
+// part of the rows as there is room for and more, of 1155 bf16 calls of 15 to 250 us (fp32 100).  The best division by these is taken where it is 10 % better than that by the constants of `us` (16
+// parts of a row tile at most) and takes less than 60 us: bf16 calls of that length are 2.5 % faster on average, up to 32, and 1 % of them more than 3 % slower, at most 9.  Nearer than that the two are not
+// told apart (taken from 7 % on, 3 % faster and 2.5 % of them slower), and longer calls are decided by how two workgroups share a compute unit (28 / 4 heads of 64, 640 rows, 46 pages of 128: 205 -> 226 us).
+// 6 / 2 heads, 128 rows, 31 pages 33.3 -> 28.2 us, 8 / 8, 256 rows, 3 pages 24.9 -> 21.
 struct GnPair { GnShare kv, rows; float us; };
-struct GnPartUs { float keys, stage, rows, tile, launch, part; };
+struct GnPartUs { float keys, stage, rows, tile, launch, each, part, crowd; };
 static GnPartUs gn_part_us(const Params& p, bool bf) {
-  if (!bf) return p.D == 128 ? GnPartUs{9.8f, 7.8f, 10.1f, 5.3f, 7.2f, 1.24e-4f} : GnPartUs{7.3f, 4.34f, 7.9f, 2.87f, 3.3f, 2.29e-4f};
-  if (gn_one_term(p)) return {10.f, 2.23f, 9.8f, 1.19f, 1.5f, 1.66e-4f};
-  return p.D == 128 ? GnPartUs{11.4f, 3.35f, 9.5f, 1.85f, 0.f, 1.73e-4f} : GnPartUs{5.5f, 2.41f, 3.7f, 1.74f, 2.5f, 2.82e-4f};
+  if (!bf) return p.D == 128 ? GnPartUs{9.8f, 7.8f, 10.1f, 5.3f, 7.2f, 0.f, 1.24e-4f, 0.f} : GnPartUs{7.3f, 4.34f, 7.9f, 2.87f, 3.3f, 0.f, 2.29e-4f, 0.f};
+  if (gn_one_term(p)) return {8.9f, 2.2f, 8.35f, 1.07f, 0.6f, 0.285f, 1.4e-4f, 0.f};
+  return p.D == 128 ? GnPartUs{12.3f, 2.8f, 10.1f, 1.63f, 0.9f, 0.31f, 1.94e-4f, 0.f} : GnPartUs{6.2f, 2.1f, 3.8f, 1.76f, 2.4f, 0.3f, 2.1e-4f, 0.126f};
 }
 static GnPair gn_pair(const Params& p, bool bf, int32_t max_len) {
   GnPair best = {{0, 1}, {0, 1}, 1e30f};
@@ -2517,6 +2519,12 @@ static GnPair gn_pair(const Params& p, bool bf, int32_t max_len) {
   const GnPartUs t = gn_part_us(p, bf);
   const GnRowSteps row_steps(p, __builtin_ctz(p.P), max_len, bf ? 64 : 32);
   const int32_t whole = gn_key_share(p, bf, max_len, wk).most, whole_row = row_steps(wq - 1);
+  auto cost = [&](const GnShare& k, const GnShare& q) {
+    const float kn = k.n > wk ? k.n : 0, qn = q.n > wq ? q.n : 0, over = p.Hkv * (k.n + q.n) / 256.f - 1.f, slow = over > 0.f ? 1.f + t.crowd * over : 1.f;
+    const float tk = t.keys + k.most * t.stage * slow, tq = t.rows + q.most * t.tile * slow, nk = kn / wk, nq = qn / wq;
+    return (tk > tq ? tk : tq) + (kn + qn > 0.f ? t.launch : 0.f) + t.each * (nk > nq ? nk : nq) + p.Hkv * (2.f * kn + qn) * p.D * t.part;
+  };
+  GnShare k_est = {0, 1}, q_est = {0, 1};   // the division of `us`
   float least = 1e30f;
   bool estimate = true;
   for (int32_t e = 1, most = 0; e <= 16 && e <= whole; ++e) {   // more parts per unit, until the rows have too few workgroups
@@ -2524,27 +2532,26 @@ static GnPair gn_pair(const Params& p, bool bf, int32_t max_len) {
     most = (whole + e - 1) / e;
     const GnShare k = gn_key_share(p, bf, max_len, 0, most);
     if (k.n > per - wq) break;
-    const float k_parts = k.n > wk ? 2.f * k.n : 0.f;
+    const GnShare q0 = gn_row_share(p, bf, max_len, per - k.n, GN_ROW_PARTS);
     if (estimate) {   // (until the rows take longer)
-      const GnShare q = gn_row_share(p, bf, max_len, per - k.n, 16);
-      const float tk = gn_key_us(p, bf, most), tq = q.most * tile + (bf ? 10.f : 6.f), us = (tq > tk ? tq : tk) + p.Hkv * (k_parts + (q.n > wq ? q.n : 0.f)) * p.D * 2.56e-4f;
-      if (us < best.us) best.us = us;
+      const GnShare q = q0.most >= (whole_row + 15) / 16 ? q0 : gn_row_share(p, bf, max_len, per - k.n, 16);
+      const float tk = gn_key_us(p, bf, most), tq = q.most * tile + (bf ? 10.f : 6.f), us = (tq > tk ? tq : tk) + p.Hkv * ((k.n > wk ? 2.f * k.n : 0.f) + (q.n > wq ? q.n : 0.f)) * p.D * 2.56e-4f;
+      if (us < best.us) best.us = us, k_est = k, q_est = q;
       estimate = tq <= tk;
     }
     // the rows: as many parts as there is room for, or as few as take no longer than the keys, or around that
-    const GnShare q0 = gn_row_share(p, bf, max_len, per - k.n, GN_ROW_PARTS);
     const float tk = t.keys + most * t.stage;
     const int32_t even = (int32_t)((tk - t.rows) / t.tile);
     for (int32_t x = 0; x < 5; ++x) {
       const int32_t steps = x == 0 ? q0.most : x == 4 ? whole_row : even + x - 1;
-      if (x && (steps <= q0.most || steps > whole_row)) continue;
+      if (x && (steps <= q0.most || steps > whole_row || tk >= least)) continue;
       const GnShare q = x ? GnShare{gn_count(row_steps, wq, steps), steps} : q0;
-      const float tq = t.rows + q.most * t.tile, parts = p.Hkv * (k_parts + (q.n > wq ? q.n : 0.f));
-      const float cost = (tq > tk ? tq : tk) + (parts > 0.f ? t.launch : 0.f) + parts * p.D * t.part;
-      if (cost < least) least = cost, best.kv = k, best.rows = q;
+      const float us = cost(k, q);
+      if (us < least) least = us, best.kv = k, best.rows = q;
     }
     if (!estimate && t.rows + q0.most * t.tile > tk) break;
   }
+  if (k_est.n > 0 && (least > 60.f || least > 0.9f * cost(k_est, q_est))) best.kv = k_est, best.rows = q_est;
   return best;
 }
 // dQ and dK / dV one after the other, each with the chip to itself
@@ -2578,7 +2585,7 @@ static bool gn_pair_even(const Params& p, int32_t max_len, float two) {
   }
   return false;
 }
-// What a backward takes unless it goes by units: the one launch, if `one`.  A call is planned once (0.2 to 2 us; 100 to 180 where the parts of every row tile were counted).
+// What a backward takes unless it goes by units: the one launch, if `one`.  A call is planned once (0.3 to 3 us, 12 at most; 100 to 180 where the parts of every row tile were counted).
 struct GnBackward { GnPair pair; bool one; float us; };
 static GnBackward gn_backward(const Params& p, bool bf, int32_t max_len) {
   const GnPair pair = gn_pair(p, bf, max_len);

@@ -78,3 +78,14 @@ def test_a_workspace_of_the_longest_history_has_room_for_the_parts_of_shorter_on
         ws = torch.empty(api.workspace_bytes(d, -1, api.OP_ATTN_BWD), dtype=torch.uint8, device="cuda")
         out.append([t.clone() for t in (api.paged_attn_bwd(*args, o, lse, x["d_o"], x["dk_pool"], x["dv_pool"], workspace=ws), x["dk_pool"], x["dv_pool"])])
     assert all(torch.equal(a, b) for a, b in zip(*out))
+
+
+# Row tiles in more than 16 parts, up to the 31 that the lookup holds: few rows against a long list, one row tile and two.  fp32 sums of up to 12K keys: 2e-6; bf16: one rounding of dQ to 8 bits (dS and P keep theirs).
+@pytest.mark.parametrize("heads,D,P,m,n_past,dtype", [((1, 1), 64, 16, 1, 61, "f32"), ((1, 1), 64, 16, 1, 181, "f32"), ((4, 4), 128, 128, 1, 12, "f32"), ((1, 1), 64, 32, 1, 370, "bf16"),
+                                                       ((1, 1), 64, 32, 5, 361, "bf16")])
+def test_row_tiles_in_many_parts(heads, D, P, m, n_past, dtype):
+    w = Workload("rows", *heads, D, P, m * P, (m + n_past) * P, None, dtype, "f32", D ** -0.5, seed=650 + n_past)
+    got, want = backward(w, make_inputs(w, "cuda"), ("attn_bwd_generic",), ("bwd_units",))
+    errs = [rel(a, b) for a, b in zip(got, want)]
+    print(heads, D, P, m, n_past, [f"{e:.2e}" for e in errs], flush=True)
+    assert errs[0] < (2e-6 if dtype == "f32" else 2.5e-3) and max(errs[1:]) < (2e-6 if dtype == "f32" else 1e-3)
